@@ -78,24 +78,34 @@ struct DeviceSide {
     StoreView store{};
     void *d_root_items = nullptr; uint32_t n_root = 0;
     uint32_t *d_import_root = nullptr;               // [MAX_BATCH]
-    uint32_t *h_row_out = nullptr;                   // pinned, [N_SLOTS][MAX_BATCH]: the state each row of a call ends up in
-    uint32_t *d_row_out = nullptr;                   // the same in device memory: the mask kernel writes here, the call's last block copies it out
+    volatile uint64_t *h_store_status = nullptr;     // pinned, [N_SLOTS][STORE_STATUS_WORDS]: see STORE_ST_DONE
+    unsigned long long *d_tickets = nullptr;
+    StoreConst *d_konst = nullptr;
     uint32_t store_epoch = 1;                        // bumped whenever the store is cleared
     uint32_t store_states = 0, store_items = 0;      // as of the last call that reported back
     bool store_dirty = true;                         // the store must be cleared before its next use
-    // What sizes a call's grid: the tokens a row's token-mask cache rows leave to the parser.  The host keeps the token-order
-    // rows and counts the union for every set of cache rows it meets, once (a few microseconds; the sets repeat all the time).
+    // What sizes a call's grid: the tokens a state's token-mask cache rows leave to the parser.  The host keeps the token-order
+    // rows and counts the union for every set of cache rows it meets, once (the sets repeat all the time).
     std::vector<uint32_t> h_valid_tok, h_cd_tok;     // [Q + N][W]
     std::unordered_map<uint64_t, uint32_t> undecided_of;   // signature of the list of cache rows -> undecided tokens
     uint32_t store_backoff = 0, store_backoff_next = 8;   // after a call the store had no room for: calls that take the per-block automaton instead
-    struct CallRecord {                              // what to note in the states once the call in this slot has reported
+    // A call through the persistent automaton until zf_mask_wait has seen its status: the groups whose state the kernel reports,
+    // and their rows.  (Groups the host knows the state of need no note.)
+    struct CallRecord {
         bool active = false;
-        uint32_t epoch = 0;
-        std::vector<std::shared_ptr<StateLink>> st; std::vector<uint32_t> gen; std::vector<uint64_t> upto;
-        std::vector<uint64_t> hop;                   // per row: the (state, token) pair the kernel walks, to be noted with the state it reports; 0 = none
-        std::vector<uint32_t> host;                  // per row: the state's name in the host automaton, to be noted with the name the kernel reports; 0 = none
-        uint32_t host_epoch = 0;                     // ... and the epoch of the host automaton that name belongs to
+        uint32_t seq = 0, epoch = 0;
+        struct Group { uint32_t group, host_id, first, n; uint64_t hop; };   // host_id: the state's name in the host automaton (0 = none); hop: the (state, token) pair the kernel walks (0 = none)
+        struct Row { std::shared_ptr<StateLink> st; uint32_t gen; uint64_t upto; };
+        std::vector<Group> groups;
+        std::vector<Row> rows;
+        uint32_t host_epoch = 0;                     // epoch of the host automaton the names belong to
+        int64_t undecided = 0;                       // for the report
     } rec[N_SLOTS];
+    // State cache (Section 5.2) on this path: the pool's slot of a state by its name in the host automaton.  A name says all there
+    // is to say about a set, so nothing is packed or compared.
+    std::vector<uint32_t> slot_of_host;              // slot + 1; 0 = none
+    std::vector<uint32_t> host_of_slot, slot_stamp;
+    uint32_t pool_victim = 0, pool_epoch = 0, pool_call = 0;
     // The device's name of a state of the host automaton, as the mask kernel has reported it for a row that stood there.  The two
     // automata hold the same sets under different names; once a state's device name is known, a row that arrives in it is sent
     // with that name and no bytes to walk, whatever token took it there.  Valid while neither automaton has been emptied.
@@ -141,6 +151,7 @@ struct DeviceSide {
 namespace {
 
 const int MAX_BATCH = 4096;   // rows per zf_compute_mask call
+const size_t STORE_STATUS_WORDS = STORE_ST_ROW + MAX_BATCH;
 const uint32_t STORE_ROOT_ID = 1;
 
 int fail(int code, const std::string &m) { set_error(m); return code; }
@@ -181,8 +192,9 @@ void free_device(DeviceSide *d) {
     if (d->store.ctl) (void)hipFree(d->store.ctl);
     if (d->d_root_items) (void)hipFree(d->d_root_items);
     if (d->d_import_root) (void)hipFree(d->d_import_root);
-    if (d->h_row_out) (void)hipHostFree(d->h_row_out);
-    if (d->d_row_out) (void)hipFree(d->d_row_out);
+    if (d->h_store_status) (void)hipHostFree((void *)d->h_store_status);
+    if (d->d_tickets) (void)hipFree(d->d_tickets);
+    if (d->d_konst) (void)hipFree(d->d_konst);
     for (auto &ev : d->ev) if (ev) (void)hipEventDestroy(ev);
     delete d;
 }
@@ -242,16 +254,15 @@ int setup_device(zf_engine *e) {
         // The mask kernel over the persistent automaton works in token order: every token's string as byte classes, and the
         // rows of the token-mask cache with one bit per token (bit v = the rank-ordered row's bit for token v's string).
         const size_t V = (size_t)e->V, W = (size_t)e->W, n_rows = tr.Wr > 0 ? tr.ci_valid.size() / (size_t)tr.Wr : 0;
-        std::vector<Str16> tok16(std::max<size_t>(V, 1), Str16{{0, 0, 0, 0}});
-        std::vector<uint8_t> tok_len(std::max<size_t>(V, 1), 0);
+        std::vector<Str16> tok16(std::max<size_t>(V, 1), Str16{{TOK_END, 0, 0, 0}});
         for (size_t v = 0; v < V; v++) {
             const uint32_t r = tr.rank_of[v];
             if (r == 0xFFFFFFFFu) continue;
-            const uint32_t n = tr.str_off[r + 1] - tr.str_off[r];
+            const uint32_t n = tr.str_off[r + 1] - tr.str_off[r], at_hand = std::min(n, TOK_AT_HAND);
             uint8_t first[16] = {0};
-            for (uint32_t k = 0; k < std::min<uint32_t>(16, n); k++) first[k] = t.cls[tr.str_bytes[tr.str_off[r] + k]];
+            for (uint32_t k = 0; k < at_hand; k++) first[k] = t.cls[tr.str_bytes[tr.str_off[r] + k]];
+            first[at_hand] = (uint8_t)(n > TOK_AT_HAND ? TOK_MORE : TOK_END);
             memcpy(&tok16[v], first, 16);
-            tok_len[v] = n <= 16 ? (uint8_t)n : (uint8_t)TOK_LEN_LONG;
         }
         std::vector<uint32_t> &valid_tok = d->h_valid_tok, &cd_tok = d->h_cd_tok;
         valid_tok.assign(std::max<size_t>(n_rows * W, 1), 0); cd_tok.assign(std::max<size_t>(n_rows * W, 1), 0);
@@ -275,7 +286,7 @@ int setup_device(zf_engine *e) {
             for (size_t k = 0; k < n_thr; k++) pool.emplace_back(rows_job, n_rows * k / n_thr, n_rows * (k + 1) / n_thr);
             for (auto &th : pool) th.join();
         }
-        UP(tok16, tok16, nullptr); UP(tok_len, tok_len, nullptr); UP(ci_valid_tok, valid_tok, nullptr); UP(ci_cd_tok, cd_tok, nullptr);
+        UP(tok16, tok16, nullptr); UP(ci_valid_tok, valid_tok, nullptr); UP(ci_cd_tok, cd_tok, nullptr);
     }
     T.Q = t.Q;
 #undef UP
@@ -313,9 +324,15 @@ int setup_device(zf_engine *e) {
         HIP_TRY(hipMalloc((void **)&G.intern, ((size_t)G.intern_mask + 1) * 8));
         HIP_TRY(hipMalloc((void **)&G.ctl, 64));
         HIP_TRY(hipMalloc((void **)&d->d_import_root, (size_t)MAX_BATCH * 4));
-        HIP_TRY(hipHostMalloc((void **)&d->h_row_out, (size_t)DeviceSide::N_SLOTS * MAX_BATCH * 4, hipHostMallocDefault));
-        HIP_TRY(hipMalloc((void **)&d->d_row_out, (size_t)DeviceSide::N_SLOTS * MAX_BATCH * 4));
-        HIP_TRY(hipMemset(d->d_row_out, 0, (size_t)DeviceSide::N_SLOTS * MAX_BATCH * 4));
+        HIP_TRY(hipHostMalloc((void **)&d->h_store_status, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8, hipHostMallocDefault));
+        memset((void *)d->h_store_status, 0, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8);
+        HIP_TRY(hipMalloc((void **)&d->d_tickets, STORE_TICKETS * 8));
+        HIP_TRY(hipMemset(d->d_tickets, 0, STORE_TICKETS * 8));
+        {
+            const StoreConst k{d->tab, G};
+            HIP_TRY(hipMalloc((void **)&d->d_konst, sizeof k));
+            HIP_TRY(hipMemcpy(d->d_konst, &k, sizeof k, hipMemcpyHostToDevice));
+        }
         Chart c0;                                        // the empty prefix's set, completed items dropped, as device item words
         chart_init(t, c0);
         std::vector<uint32_t> root;
@@ -532,7 +549,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         build_trie(v, e->opt.chunk_strings, e->tab.cls, e->trie);
         build_token_mask_cache(e->tab, e->trie);
     } catch (const std::bad_alloc &) { delete e; return fail(ZF_ERR_OOM, "out of memory"); }
-    e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0;
+    e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
     if (e->opt.walk_mode == 2 && e->opt.pruning != 0) {
         e->host_aut = new (std::nothrow) HostAutomaton(e->tab);
         if (!e->host_aut) { delete e; return fail(ZF_ERR_OOM, "out of memory"); }
@@ -993,7 +1010,8 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     if ((int)packed.size() < batch) packed.resize(batch);
     for (int b = 0; b < batch; b++) pack_chart(e->tab, chart_of(states[b]), packed[b]);
     // ---- state cache: rows whose chart has been seen before only need their finished mask copied ----
-    const bool sc = !noalloc && !d->cache.empty() && (size_t)batch * 2 <= d->cache.size();
+    // (an engine with a persistent automaton keeps its finished rows by its names: a call that comes here instead serves none)
+    const bool sc_asked = !noalloc && !d->cache.empty() && (size_t)batch * 2 <= d->cache.size(), sc = sc_asked && !e->store_on;
     static thread_local std::vector<uint32_t> row_slot, miss_rows;
     row_slot.assign(batch, 0);
     miss_rows.clear();
@@ -1007,7 +1025,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         return cx.set_off[cx.n_sets()] - cx.set_off[cx.n_sets() - 1] > cy.set_off[cy.n_sets()] - cy.set_off[cy.n_sets() - 1];
     });
     const int nb = (int)miss_rows.size();                // rows that go through the kernels
-    d->report.cache_hits = n_hits; d->report.cache_misses = sc ? nb : 0;
+    d->report.cache_hits = n_hits; d->report.cache_misses = sc_asked ? nb : 0;
     // ---- upload: [RowChart x nb][set offsets][items][cache rows of the token-mask cache][dst slot x nb][row slot x batch] ----
     size_t n_off = 0, n_items = 0, n_ent = 0, max_off = 0, max_items = 0, max_ent = 0;
     const bool use_cache = !e->opt.disable_token_mask_cache;
@@ -1237,10 +1255,22 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     return zf_mask_wait(e, hip_stream);
 }
 
-// The same call through the persistent automaton (walk_mode 2): the upload names, per row, the state the row was last known
-// to be in and the byte classes fed since; the mask kernel walks them, checks the vocabulary from the state it arrives at and
-// reports that state back (pinned memory), which zf_mask_wait notes in the zf_state.  Rows the store does not know -- after it
-// was cleared, or too far behind -- bring their packed chart along and are made states of by the import kernel first.
+static void forget_cached_masks(DeviceSide *d) {
+    d->cache_index.clear();
+    for (auto &ce : d->cache) ce.used = false;
+    d->slot_of_host.clear();
+    std::fill(d->host_of_slot.begin(), d->host_of_slot.end(), 0u);
+}
+
+// ---- the same call through the persistent automaton (walk_mode 2) ----
+// Rows that stand in the same state -- the host automaton's name says so -- have the same mask: they form a group, which the
+// kernel works out once and stores to all of them (the rows of a batch are queries under one grammar, most of them inside a
+// string, a number or an identifier: 256 rows of a JSON schema stand in about 20 states).  What a group sends is the name of
+// the state on the device and nothing else when the device has reported it before; else the state its rows were last known
+// to be in and the byte classes fed since, which the kernel walks, reporting the state it arrives at (pinned memory), which
+// zf_mask_wait notes in the rows' zf_states.  States the store does not know -- after it was cleared, or too far behind --
+// bring a packed chart along and are made states of by the import kernel first.
+
 // The state's name in the host automaton, when it has a current one there (the caller holds the host automaton's lock) ...
 static bool host_name_valid(const zf_engine *e, const zf_state *st) {
     return e->host_aut && st->host_id != HostAutomaton::ROOT && st->host_id_epoch == e->host_epoch && st->host_id < HostAutomaton::SINK && st->host_id != 0;
@@ -1249,12 +1279,131 @@ static bool host_name_valid(const zf_engine *e, const zf_state *st) {
 static uint32_t device_name_of(const zf_engine *e, const zf_state *st) {
     return host_name_valid(e, st) ? e->dev->name_find(st->host_id, e->host_epoch, e->dev->store_epoch) : 0u;
 }
+static bool device_knows(const DeviceSide *d, const zf_state *st) { return st->dev_id == STORE_ROOT_ID || (st->dev_id != 0 && st->dev_epoch == d->store_epoch); }
+// The row stands in device state `dev`, everything fed so far included.
+static void note_device_state(const DeviceSide *d, zf_state *st, uint32_t dev) {
+    st->dev_id = dev; st->dev_epoch = d->store_epoch;
+    st->pending.clear(); st->pending_base = st->fed_total; st->pending_token = -1;
+}
+
+// Tokens that a list of token-mask cache rows leaves to the parser.
+static int64_t count_undecided(DeviceSide *d, const uint32_t *ent, uint32_t n) {
+    uint64_t sig = 0xCBF29CE484222325ull ^ n;
+    for (uint32_t k = 0; k < n; k++) sig = (sig ^ ent[k]) * 0x100000001B3ull;
+    auto it = d->undecided_of.find(sig);
+    if (it == d->undecided_of.end()) {
+        const size_t Wt = (size_t)d->tab.W;
+        uint32_t cnt = 0;
+        for (size_t w = 0; w < Wt; w++) {
+            uint32_t v = 0, cd = 0;
+            for (uint32_t k = 0; k < n; k++) { v |= d->h_valid_tok[ent[k] * Wt + w]; cd |= d->h_cd_tok[ent[k] * Wt + w]; }
+            cnt += (uint32_t)__builtin_popcount(cd & ~v);
+        }
+        if (d->undecided_of.size() > 65536) d->undecided_of.clear();
+        it = d->undecided_of.emplace(sig, cnt).first;
+    }
+    return it->second;
+}
+
+namespace {
+struct RowGroup {
+    zf_state *lead;                // the row whose knowledge the group sends
+    uint32_t at;                   // name in the host automaton (0: none, the row is a group of its own)
+    uint32_t dev;                  // name on the device (0: the kernel walks the lead's pending bytes, or imports its chart)
+    int32_t last, n;               // rows: the last one (a chain through next_row), how many
+    const Item *items; uint32_t n_items;
+    const uint32_t *ents; uint32_t n_ent;
+    double undecided;
+    uint32_t slot;                 // row of the state cache's pool
+    uint8_t pooled, keep, known;
+    int32_t seg_w, parts;          // launch shape
+};
+struct StoreCall {                 // one call's working memory, kept per thread
+    std::vector<RowGroup> g;
+    std::vector<int32_t> next_row; // chain of the rows of a group
+    std::vector<uint32_t> table;   // open addressing: host name -> group + 1
+    std::vector<uint32_t> ents_at; // entries of groups outside the host automaton
+    std::vector<uint32_t> spare_ents;
+    std::vector<zf_state *> unknown;
+    std::vector<uint32_t> imports; // groups that bring their charts along
+    std::vector<std::vector<uint32_t>> packed;
+    StoreInline in;
+};
+}  // namespace
+
+// Launch shape: mask words a wavefront takes per pass and blocks, per group; returns the blocks of the grid.  A wavefront takes a
+// group's mask words in segments and the undecided tokens among them 64 at a time; groups differ by orders of magnitude in how
+// many tokens their token-mask cache rows leave undecided, which was counted once per list of cache rows.  The grid is never
+// larger than what the chip holds at once: a block that had to wait for a place would start from nothing (LDS cache, the
+// group's state) when the others are nearly done, which costs more than a few more passes of the wavefronts that are there.
+static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget, double apply_us_per_word) {
+    const int n = (int)g.size();
+    static thread_local std::vector<double> inv_cost;
+    static thread_local std::vector<int> segs, passes;
+    inv_cost.resize(n); segs.resize(n); passes.resize(n);
+    double lo = 1e30;
+    for (int r = 0; r < n; r++) {
+        // words per segment: as many as are expected to hold 48 undecided tokens, at most 64 (a batch is 64: the
+        // tokens are spread unevenly, and a second, nearly empty batch costs as much as a full one)
+        const double und = g[r].undecided;
+        const int sw = g[r].pooled ? 16 : (int)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 48.0 * std::max(1, V) / (32.0 * std::max(und, 1.0))));
+        segs[r] = std::max(1, (W + sw - 1) / sw);
+        g[r].seg_w = sw;
+        // what a pass costs a wavefront (microseconds, measured): an empty segment 2.8, a segment with a batch 3.7, each further
+        // batch 3; storing and masking a member's share of it on top
+        const double per_seg = und / segs[r];
+        const double walk = g[r].pooled ? 1.5 : (per_seg < 1.0 ? 2.8 + 0.9 * per_seg : 3.7 + 3.0 * std::max(0.0, per_seg / 64.0 - 0.75));
+        const double cost = walk + g[r].n * (0.03 + apply_us_per_word * sw);
+        inv_cost[r] = 1.0 / cost;
+        lo = std::min(lo, cost);
+    }
+    // Every wavefront of a group takes the same number of passes (a group is as slow as its slowest wavefront).  The
+    // smallest time T is looked for in which every group, taking as many passes as fit into T, leaves the grid within
+    // what the chip holds; groups are then given passes back while blocks are left.
+    auto blocks_for = [&](int r, int n_pass) { return std::max(1, (segs[r] + n_pass * STORE_WAVES - 1) / (n_pass * STORE_WAVES)); };
+    auto need = [&](double T) {
+        int tot = 0;
+        for (int r = 0; r < n; r++) tot += blocks_for(r, std::max(1, (int)(T * inv_cost[r])));
+        return tot;
+    };
+    double hi = lo;
+    if (need(hi) > budget) {
+        while (need(hi) > budget && hi < 1e9) { lo = hi; hi *= 2; }
+        for (int it = 0; it < 6; it++) { const double mid = 0.5 * (lo + hi); if (need(mid) <= budget) hi = mid; else lo = mid; }   // to 2 %: the blocks left over go back to the groups below
+    }
+    int all = 0;
+    for (int r = 0; r < n; r++) { passes[r] = std::max(1, (int)(hi * inv_cost[r])); g[r].parts = blocks_for(r, passes[r]); all += g[r].parts; }
+    for (int r = 0; r < n && all < budget; r++) {
+        if (passes[r] <= 1) continue;
+        const int p = blocks_for(r, passes[r] - 1);
+        if (p - g[r].parts <= budget - all) { all += p - g[r].parts; g[r].parts = p; passes[r]--; }
+    }
+    // Blocks are dealt to the eight XCDs in turn, and every XCD has an L2 of its own.  When groups start at multiples of eight,
+    // the blocks that take the same stretch of the vocabulary for different groups run on the same XCD and find each other's
+    // strings and cache rows in its L2.  So groups of eight blocks or more are rounded UP to a multiple of eight while blocks are
+    // left over (never down: fewer blocks would mean more passes); a block beyond the group's segments leaves at once.
+    for (int r = 0; r < n; r++) {
+        const int up = (8 - (g[r].parts & 7)) & 7;
+        if (g[r].parts >= 8 && up && all + up <= budget) { g[r].parts += up; all += up; }
+    }
+    for (int r = 0; r < n; r++) {
+        // A wavefront that has several segments to take takes them as fewer, wider ones (up to 64 words): the strings of a
+        // segment's first batch are waited for, those of its further batches travel while the batch before is checked.
+        if (passes[r] > 1 && g[r].seg_w < STORE_SEG_WORDS_MAX) {
+            const int words_per_wave = (W + g[r].parts * STORE_WAVES - 1) / (g[r].parts * STORE_WAVES);
+            const int n_pass = (words_per_wave + STORE_SEG_WORDS_MAX - 1) / STORE_SEG_WORDS_MAX;
+            g[r].seg_w = std::max(g[r].seg_w, std::min<int>(STORE_SEG_WORDS_MAX, (words_per_wave + n_pass - 1) / n_pass));
+        }
+    }
+    return all;
+}
 
 static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, uint32_t slot) {
     DeviceSide *d = e->dev;
+    HostAutomaton &A = *e->host_aut;
     hipStream_t stream = (hipStream_t)hip_stream;
-    std::unique_lock<std::mutex> host_lk;                 // the rows' current sets are read from the host automaton (a row it does not know is brought in)
-    if (e->host_aut) host_lk = std::unique_lock<std::mutex>(e->host_mu);
+    static thread_local StoreCall c;
+    std::unique_lock<std::mutex> host_lk(e->host_mu);     // the rows' states are read from the host automaton (a row it does not know is brought in)
     // ---- clear the store when it is new, half full, or has refused a request; only with no call in flight ----
     if (d->pending == 0 && (d->store_dirty || d->store_states > d->store.cap_states / 2 || d->store_items > d->store.cap_items / 2)) {
         HIP_TRY(launch_store_clear(d->store, (uint32_t)std::max(e->tab.n_cls, 1), d->d_root_items, d->n_root, stream));
@@ -1262,62 +1411,140 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         d->store_states = 2; d->store_items = d->n_root;
         d->store_dirty = false;
     }
-    // ---- state cache (keyed by the packed chart, as on the other paths) ----
+    if (d->hop_epoch != d->store_epoch) { if (d->hop_used) std::fill(d->hop_key.begin(), d->hop_key.end(), 0); d->hop_used = 0; d->hop_epoch = d->store_epoch; }
+    // ---- group the rows by the state they stand in ----
+    c.g.clear(); c.spare_ents.clear(); c.imports.clear(); c.unknown.clear();
+    for (int32_t b = 0; b < batch; b++) {                 // rows the host automaton has to take in from their charts (all of them after it was emptied)
+        zf_state *st = states[b];
+        if (st->host_id != HostAutomaton::ROOT && st->host_id_epoch != e->host_epoch && !st->lag.empty()) c.unknown.push_back(st);
+    }
+    if (!c.unknown.empty()) catch_up_batch(c.unknown.data(), (int32_t)c.unknown.size());
+    c.next_row.resize(batch);
+    uint32_t places = 64;
+    while (places < 2u * (uint32_t)batch) places <<= 1;
+    c.table.assign(places, 0);
+    for (int32_t b = 0; b < batch; b++) {
+        zf_state *st = states[b];
+        const uint32_t at = host_place(st);
+        c.next_row[b] = -1;
+        uint32_t k = 0;
+        if (at) {
+            k = (at * 0x9E3779B1u >> 7) & (places - 1);
+            while (c.table[k] && c.g[c.table[k] - 1].at != at) k = (k + 1) & (places - 1);
+        }
+        if (at && c.table[k]) {                           // one more row of a group: whose knowledge is the better one to send?
+            RowGroup &g = c.g[c.table[k] - 1];
+            c.next_row[b] = g.last; g.last = b; g.n++;
+            if (!g.dev) {
+                const bool known = device_knows(d, st);
+                if ((known && !g.known) || (known && st->pending.size() < g.lead->pending.size())) { g.lead = st; g.known = known; }
+            }
+            continue;
+        }
+        RowGroup g{};
+        g.lead = st; g.at = at; g.last = b; g.n = 1;
+        g.dev = at == HostAutomaton::ROOT ? STORE_ROOT_ID : device_name_of(e, st);
+        g.known = device_knows(d, st);
+        c.g.push_back(g);
+        if (at) c.table[k] = (uint32_t)c.g.size();
+    }
+    const int ng = (int)c.g.size();
+    // ---- state cache (Section 5.2): groups whose finished mask is in the pool, and slots for the others ----
     const bool sc = !d->cache.empty() && (size_t)batch * 2 <= d->cache.size();
-    static thread_local std::vector<std::vector<uint32_t>> packed;
-    static thread_local std::vector<uint32_t> row_slot, miss_rows, import_rows;
-    if ((int)packed.size() < batch) packed.resize(batch);
-    row_slot.assign(batch, 0);
-    miss_rows.clear();
-    int n_hits = 0;
+    int n_miss = 0, n_hits = 0;
     if (sc) {
-        catch_up_batch(states, batch);                    // the state cache's key is the packed chart
-        for (int b = 0; b < batch; b++) pack_chart(e->tab, chart_of(states[b]), packed[b]);
-        n_hits = state_cache_lookup(d, packed, batch, row_slot, miss_rows);
-    } else {
-        for (int b = 0; b < batch; b++) miss_rows.push_back((uint32_t)b);
-        // rows the store does not know come in through their charts (all of them after the store was cleared)
-        static thread_local std::vector<zf_state *> unknown;
-        unknown.clear();
-        for (int b = 0; b < batch; b++) {
-            zf_state *st = states[b];
-            if (st->dev_id == STORE_ROOT_ID || (st->dev_id != 0 && st->dev_epoch == d->store_epoch) || st->lag.empty()) continue;
-            if (device_name_of(e, st)) continue;          // the device knows the state under the name the host automaton has for it: no chart needed
-            unknown.push_back(st);
+        if (d->pool_epoch != e->host_epoch) { forget_cached_masks(d); d->pool_epoch = e->host_epoch; }
+        const uint32_t slots = (uint32_t)d->cache.size(), call = ++d->pool_call;
+        d->host_of_slot.resize(slots, 0); d->slot_stamp.resize(slots, 0);
+        for (RowGroup &g : c.g) {
+            if (!g.at || g.at == HostAutomaton::SINK) { n_miss++; n_hits += g.n - 1; continue; }
+            if (g.at >= d->slot_of_host.size()) d->slot_of_host.resize(std::max<size_t>(g.at + 1, d->slot_of_host.size() * 2), 0);
+            const uint32_t have = d->slot_of_host[g.at];
+            if (have) { g.pooled = 1; g.slot = have - 1; d->slot_stamp[g.slot] = call; n_hits += g.n; }
         }
-        if (!unknown.empty()) catch_up_batch(unknown.data(), (int32_t)unknown.size());
+        for (RowGroup &g : c.g) {                         // a slot for each of the others: round-robin victim, never one of this call's
+            if (g.pooled || !g.at || g.at == HostAutomaton::SINK) continue;
+            while (d->slot_stamp[d->pool_victim] == call) d->pool_victim = (d->pool_victim + 1) % slots;
+            g.slot = d->pool_victim; g.keep = 1;
+            d->pool_victim = (d->pool_victim + 1) % slots;
+            if (d->host_of_slot[g.slot]) d->slot_of_host[d->host_of_slot[g.slot]] = 0;
+            d->host_of_slot[g.slot] = g.at; d->slot_of_host[g.at] = g.slot + 1; d->slot_stamp[g.slot] = call;
+            n_miss++; n_hits += g.n - 1;
+        }
     }
-    const int nb = (int)miss_rows.size();
-    d->report.cache_hits = n_hits; d->report.cache_misses = sc ? nb : 0;
-    // ---- what each launched row sends ----
-    import_rows.clear();
-    static thread_local std::vector<uint32_t> row_named;  // per launched row: the device's name of the state it stands in, when the host automaton's name for it has one (0: not known)
-    row_named.assign(miss_rows.size(), 0);
+    d->report.cache_hits = n_hits; d->report.cache_misses = n_miss;
+    // ---- what each group sends ----
+    DeviceSide::CallRecord &rec = d->rec[slot];
+    rec.epoch = d->store_epoch; rec.host_epoch = e->host_epoch;
+    rec.groups.clear(); rec.rows.clear(); rec.undecided = 0;
     const bool use_cache = !e->opt.disable_token_mask_cache;
-    size_t n_pend = 0, n_ent = 0, n_off = 0, n_items = 0, widest = 0, biggest_set = 0;
-    for (int r = 0; r < nb; r++) {
-        zf_state *st = states[miss_rows[r]];
-        const CurrentSet cs = current_set(st);
-        const size_t last = cs.n;
-        widest = std::max(widest, last);
-        biggest_set = std::max<size_t>(biggest_set, cs.biggest);
-        if (use_cache) n_ent += last;
-        row_named[r] = device_name_of(e, st);
-        const bool known = st->dev_id == STORE_ROOT_ID || (st->dev_id != 0 && st->dev_epoch == d->store_epoch);
-        if (row_named[r]) {}                               // sent with its name on the device: no bytes, no chart
-        else if (known) n_pend += st->pending.size();
-        else {
-            const Chart &c = chart_of(st);
-            import_rows.push_back((uint32_t)r);
-            if (!sc) pack_chart(e->tab, c, packed[miss_rows[r]]);
-            n_off += c.set_off.size(); n_items += c.items.size();
+    size_t widest = 0, biggest_set = 0, n_spill_ent = 0, n_spill_pend = 0, n_off = 0, n_items = 0;
+    bool spill = false;
+    uint32_t n_cache_rows = 0;
+    c.unknown.clear();
+    for (RowGroup &g : c.g)
+        if (!g.pooled && !g.dev && !g.known && !g.lead->lag.empty()) c.unknown.push_back(g.lead);
+    if (!c.unknown.empty()) catch_up_batch(c.unknown.data(), (int32_t)c.unknown.size());
+    for (int r = 0; r < ng; r++) {
+        RowGroup &g = c.g[r];
+        if (g.pooled) continue;
+        const CurrentSet cs = current_set(g.lead);
+        g.items = cs.items; g.n_items = cs.n;
+        widest = std::max<size_t>(widest, cs.n); biggest_set = std::max<size_t>(biggest_set, cs.biggest);
+        g.undecided = e->V;
+        if (use_cache) {
+            if (g.at && g.at != HostAutomaton::SINK) {    // worked out once per state
+                HostAutomaton::State &hs = A.st(g.at);
+                if (hs.undecided < 0) {
+                    hs.ents.resize(cs.n);
+                    hs.ents.resize(current_set_entries(e->tab, cs.items, cs.n, hs.ents.data()));
+                    hs.undecided = hs.ents.size() <= 64 ? count_undecided(d, hs.ents.data(), (uint32_t)hs.ents.size()) : e->V;
+                }
+                g.ents = hs.ents.data(); g.n_ent = (uint32_t)hs.ents.size(); g.undecided = (double)hs.undecided;
+            } else g.undecided = cs.n ? e->V : 0;         // gathered below, when the vector they go to no longer moves
         }
     }
-    const int n_imp = (int)import_rows.size();
+    if (use_cache)
+        for (RowGroup &g : c.g) {
+            if (g.pooled || g.ents || !g.n_items) continue;
+            const size_t at = c.spare_ents.size();
+            c.spare_ents.resize(at + g.n_items);
+            g.n_ent = current_set_entries(e->tab, g.items, g.n_items, c.spare_ents.data() + at);
+            c.spare_ents.resize(at + g.n_ent);
+        }
+    {
+        const uint32_t *at = c.spare_ents.data();
+        for (RowGroup &g : c.g) if (!g.pooled && use_cache && !g.ents) { g.ents = at; at += g.n_ent; }
+    }
+    c.packed.resize(std::max<size_t>(c.packed.size(), ng));
+    for (int r = 0; r < ng; r++) {
+        RowGroup &g = c.g[r];
+        if (g.pooled) continue;
+        n_cache_rows += g.n_ent;
+        rec.undecided += (int64_t)g.undecided;
+        bool fits = g.n_ent <= (uint32_t)STORE_GROUP_ENT;
+        for (uint32_t k = 0; fits && k < g.n_ent; k++) fits = g.ents[k] < 65536u;
+        if (!g.dev) {
+            if (g.known) { fits &= g.lead->pending.size() <= (size_t)STORE_GROUP_PEND; n_spill_pend += g.lead->pending.size(); }
+            else {
+                const Chart &ch = chart_of(g.lead);
+                c.imports.push_back((uint32_t)r);
+                pack_chart(e->tab, ch, c.packed[r]);
+                n_off += ch.set_off.size(); n_items += ch.items.size();
+            }
+        }
+        n_spill_ent += g.n_ent;
+        spill |= !fits;
+    }
+    const int n_imp = (int)c.imports.size();
+    const bool big = ng > STORE_INLINE_GROUPS;            // records and members travel in device memory instead of the argument block
     auto align16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
-    const size_t off_srow = 0, off_ent = align16(sizeof(StoreRow) * nb), off_pend = align16(off_ent + 4 * n_ent);
-    const size_t off_dst = align16(off_pend + n_pend), off_rowslot = align16(off_dst + 4 * (size_t)nb);
-    const size_t off_rows = align16(off_rowslot + 4 * (size_t)batch), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
+    // staging: [group records][blocks][members] (uploaded when big), then what the kernels read in place
+    const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
+    const size_t off_block = align16(big ? sizeof(StoreGroup) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
+    const size_t up_bytes = align16(off_mem + 2 * (size_t)batch);
+    const size_t off_spill = up_bytes, off_ent = align16(off_spill + (spill ? sizeof(StoreRow) * ng : 0)), off_pend = align16(off_ent + (spill ? 4 * n_spill_ent : 0));
+    const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
     const size_t off_items = align16(off_so + 4 * n_off), off_imp = align16(off_items + sizeof(Item) * n_items);
     const size_t total = off_imp + 4 * (size_t)n_imp + 16;
     if (total > d->stage_cap[slot]) {
@@ -1327,262 +1554,152 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         HIP_TRY(hipHostMalloc(&d->h_stage[slot], cap, hipHostMallocDefault));
         d->stage_cap[slot] = cap;
     }
-    if (sc && total > d->chart_cap) {
+    if (big && up_bytes > d->chart_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
         if (d->d_chart) (void)hipFree(d->d_chart);
         d->d_chart = nullptr; d->chart_cap = 0;
-        const size_t cap = total * 2 + 4096;
+        const size_t cap = up_bytes * 2 + 4096;
         HIP_TRY(hipMalloc(&d->d_chart, cap));
         d->chart_cap = cap;
     }
-    DeviceSide::CallRecord &rec = d->rec[slot];
-    rec.active = true; rec.epoch = d->store_epoch;
-    rec.st.assign(nb, std::shared_ptr<StateLink>()); rec.gen.assign(nb, 0); rec.upto.assign(nb, 0); rec.hop.assign(nb, 0);
-    rec.host.assign(nb, 0); rec.host_epoch = e->host_epoch;
-    if (d->hop_epoch != d->store_epoch) { if (d->hop_used) std::fill(d->hop_key.begin(), d->hop_key.end(), 0); d->hop_used = 0; d->hop_epoch = d->store_epoch; }
-    uint32_t n_cache_rows = 0;
-    static thread_local std::vector<uint32_t> row_n_ent, row_ent_at, row_n_items;
-    row_n_ent.assign(nb, 0); row_ent_at.assign(nb, 0); row_n_items.assign(nb, 0);
-    static thread_local StoreMiniRows mini;               // short records: they travel in the kernel's argument block
-    const bool use_mini = nb <= STORE_MINI_ROWS;
+    // ---- launch shape ----
+    StoreArgs a{};
+    int scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
+    while (scratch > 32 && store_lds_bytes(d->tab, d->mode, scratch) > (uint32_t)STORE_LDS_MAX) scratch -= 32;
+    const uint32_t lds = store_lds_bytes(d->tab, d->mode, scratch);
+    if (lds > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
+    double apply_us_per_word = 0;
+    if (g_apply.out) {
+        const size_t esz = g_apply.dtype == 0 ? 4 : 2;
+        const bool whole = (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
+        // One kernel for both as long as the logits are few enough that masking them hides behind the walk of the vocabulary;
+        // beyond, a launch of its own masks them at the memory's rate with the work spread evenly over the chip.
+        if (whole && 2ull * (uint64_t)batch * (uint64_t)e->V * esz <= STORE_FUSE_BYTES) {
+            a.logits = g_apply.logits; a.out = g_apply.out; a.stride = g_apply.stride; a.dtype = (uint8_t)(g_apply.dtype + 1);
+            g_apply.fused = true;
+            apply_us_per_word = 0.25 * 32 * (double)esz * 2 / 1024;
+        }
+    }
+    const int budget = std::max(ng, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
+    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, apply_us_per_word);
+    // ---- the records ----
     {
         uint8_t *h = (uint8_t *)d->h_stage[slot];
-        StoreRow *srow = (StoreRow *)(h + off_srow);
+        StoreGroup *gr = big ? (StoreGroup *)h : c.in.g;
+        uint32_t *blk = (uint32_t *)(h + off_block);
+        uint16_t *mem = big || batch > STORE_INLINE_ROWS ? (uint16_t *)(h + off_mem) : c.in.member;
+        StoreRow *srow = (StoreRow *)(h + off_spill);
         uint32_t *ents = (uint32_t *)(h + off_ent);
         uint8_t *pend = h + off_pend;
-        uint32_t *dst = (uint32_t *)(h + off_dst);
         RowChart *rows = (RowChart *)(h + off_rows);
         uint32_t *so = (uint32_t *)(h + off_so);
         uint32_t *dev_items = (uint32_t *)(h + off_items);
         uint32_t *imp = (uint32_t *)(h + off_imp);
-        memcpy(h + off_rowslot, row_slot.data(), 4 * (size_t)batch);
-        uint32_t en_at = 0, pe_at = 0, so_at = 0, it_at = 0, k_imp = 0;
-        for (int r = 0; r < nb; r++) {
-            zf_state *st = states[miss_rows[r]];
-            const CurrentSet cs = current_set(st);
-            StoreRow sr{};
-            sr.ent_off = en_at;
-            if (use_cache) {
-                sr.n_ent = current_set_entries(e->tab, cs.items, cs.n, ents + en_at); sr.flags |= STORE_ROW_CACHE;
-                if (sr.n_ent <= (uint32_t)STORE_ROW_ENT) memcpy(sr.ent, ents + en_at, 4 * sr.n_ent);
-            }
-            row_n_ent[r] = sr.n_ent; row_ent_at[r] = en_at; row_n_items[r] = cs.n;
-            en_at += sr.n_ent;
-            n_cache_rows += sr.n_ent;
-            // the state's name in the host automaton, when it has one there: the key to its name on the device
-            const uint32_t named = row_named[r];
-            if (!named && host_name_valid(e, st)) rec.host[r] = st->host_id;
-            const bool known = named != 0 || st->dev_id == STORE_ROOT_ID || (st->dev_id != 0 && st->dev_epoch == d->store_epoch);
-            if (named) {                                   // the device knows this very state: nothing to walk, nothing to bring in
-                sr.start = named; sr.n_pending = 0; sr.pend_off = pe_at;
-            } else if (known) {
-                sr.start = st->dev_id; sr.n_pending = (uint32_t)st->pending.size(); sr.pend_off = pe_at;
-                if (sr.n_pending && st->pending_token >= 0 && st->dev_id != 0xFFFFFFFDu) {
+        uint32_t mem_at = 0, en_at = 0, pe_at = 0, so_at = 0, it_at = 0, k_imp = 0, blk_at = 0;
+        for (int r = 0; r < ng; r++) {
+            RowGroup &g = c.g[r];
+            zf_state *st = g.lead;
+            uint32_t flags = use_cache ? STORE_ROW_CACHE : 0u, start, n_pending = 0;
+            const uint8_t *pending = nullptr;
+            uint64_t hop = 0;
+            if (g.pooled) { flags = STORE_ROW_POOLED; start = g.slot; }
+            else if (g.dev) start = g.dev;
+            else if (g.known) {
+                start = st->dev_id; n_pending = (uint32_t)st->pending.size(); pending = st->pending.data();
+                if (n_pending && st->pending_token >= 0 && st->dev_id != HostAutomaton::SINK) {
                     const uint64_t key = (uint64_t)st->dev_id << 32 | ((uint32_t)st->pending_token + 1u);
                     const uint32_t to = d->hop_find(key);
-                    if (to) { sr.start = to; sr.n_pending = 0; }           // somebody has walked this token from this state before
-                    else rec.hop[r] = key;
+                    if (to) { start = to; n_pending = 0; }            // somebody has walked this token from this state before
+                    else hop = key;
                 }
-                if (sr.n_pending) memcpy(pend + pe_at, st->pending.data(), sr.n_pending);
-                if (sr.n_pending <= (uint32_t)STORE_ROW_PEND) memcpy(sr.pend, st->pending.data(), sr.n_pending);
-                pe_at += sr.n_pending;
             } else {
-                const Chart &c = chart_of(st);
-                const std::vector<uint32_t> &k = packed[miss_rows[r]];
-                sr.flags |= STORE_ROW_IMPORTED;
-                rows[k_imp] = RowChart{c.n_sets(), so_at, it_at, 0, 0, (uint32_t)c.items.size(), {0, 0}};
-                memcpy(so + so_at, k.data() + 1, 4 * c.set_off.size());
-                memcpy(dev_items + 2 * (size_t)it_at, k.data() + 1 + c.set_off.size(), 8 * c.items.size());
-                so_at += (uint32_t)c.set_off.size(); it_at += (uint32_t)c.items.size();
+                const Chart &ch = chart_of(st);
+                const std::vector<uint32_t> &k = c.packed[r];
+                flags |= STORE_ROW_IMPORTED; start = 0;
+                rows[k_imp] = RowChart{ch.n_sets(), so_at, it_at, 0, 0, (uint32_t)ch.items.size(), {0, 0}};
+                memcpy(so + so_at, k.data() + 1, 4 * ch.set_off.size());
+                memcpy(dev_items + 2 * (size_t)it_at, k.data() + 1 + ch.set_off.size(), 8 * ch.items.size());
+                so_at += (uint32_t)ch.set_off.size(); it_at += (uint32_t)ch.items.size();
                 imp[k_imp++] = (uint32_t)r;
-                st->pending.clear(); st->pending_base = st->fed_total;     // the chart holds everything fed so far
             }
-            srow[r] = sr;
-            d->h_row_out[(size_t)slot * MAX_BATCH + r] = 0;        // "not reported": the kernel writes the state the row arrives at
-            if (use_mini) {
-                StoreRowMini &m = mini.r[r];
-                bool fits = sr.n_pending <= (uint32_t)STORE_MINI_PEND && sr.n_ent <= (uint32_t)STORE_MINI_ENT;
-                for (uint32_t k = 0; fits && k < sr.n_ent; k++) fits = sr.ent[k] < 65536u;
-                m.start = sr.start;
-                if (fits) {
-                    m.meta = sr.n_pending | sr.n_ent << 8 | sr.flags << 16;
-                    memcpy(m.pend, sr.pend, STORE_MINI_PEND);
-                    for (uint32_t k = 0; k < (uint32_t)STORE_MINI_ENT; k++) m.ent[k] = k < sr.n_ent ? (uint16_t)sr.ent[k] : (uint16_t)0;
-                } else m.meta = (sr.flags | STORE_ROW_SPILL) << 16;
-                m.spare = 0;
+            if (g.keep) flags |= STORE_ROW_KEEP;
+            if (!g.pooled && !g.dev) {                    // the kernel says where these rows stand: noted by zf_mask_wait
+                flags |= STORE_ROW_REPORT;
+                rec.groups.push_back({(uint32_t)r, g.at < HostAutomaton::SINK ? g.at : 0u, (uint32_t)rec.rows.size(), (uint32_t)g.n, hop});
             }
-            dst[r] = sc ? row_slot[miss_rows[r]] : miss_rows[r];
-            rec.st[r] = st->link; rec.gen[r] = st->generation; rec.upto[r] = st->fed_total;
+            const uint32_t first_mem = mem_at;
+            for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
+                mem[mem_at++] = (uint16_t)b;
+                if (g.dev) note_device_state(d, states[b], g.dev);
+                else if (!g.pooled) {
+                    rec.rows.push_back({states[b]->link, states[b]->generation, states[b]->fed_total});
+                    if (!g.known) { states[b]->pending.clear(); states[b]->pending_base = states[b]->fed_total; states[b]->pending_token = -1; }   // the chart holds everything fed so far
+                }
+            }
+            StoreGroup &m = gr[r];
+            m.start = start; m.slot = (uint16_t)g.slot; m.member_at = (uint16_t)first_mem; m.n_members = (uint16_t)g.n;
+            bool fits = n_pending <= (uint32_t)STORE_GROUP_PEND && g.n_ent <= (uint32_t)STORE_GROUP_ENT;
+            for (uint32_t k = 0; fits && k < g.n_ent; k++) fits = g.ents[k] < 65536u;
+            if (fits) {
+                m.meta = n_pending | g.n_ent << 8;
+                if (n_pending) memcpy(m.pend, pending, n_pending);
+                for (uint32_t k = 0; k < g.n_ent; k++) m.ent[k] = (uint16_t)g.ents[k];
+            } else {
+                m.meta = 0; flags |= STORE_ROW_SPILL;
+                StoreRow &sr = srow[r];
+                sr.start = start; sr.n_pending = n_pending; sr.pend_off = pe_at; sr.n_ent = g.n_ent; sr.ent_off = en_at; sr.flags = flags;
+                if (g.n_ent <= (uint32_t)STORE_ROW_ENT) memcpy(sr.ent, g.ents, 4 * (size_t)g.n_ent);
+                else { memcpy(ents + en_at, g.ents, 4 * (size_t)g.n_ent); en_at += g.n_ent; }
+                if (n_pending <= (uint32_t)STORE_ROW_PEND) memcpy(sr.pend, pending, n_pending);
+                else { memcpy(pend + pe_at, pending, n_pending); pe_at += n_pending; }
+            }
+            m.meta |= flags << 16 | (uint32_t)(g.seg_w - 1) << 24;
+            if (big) for (int p = 0; p < g.parts; p++) { blk[2 * blk_at] = (uint32_t)r; blk[2 * blk_at + 1] = (uint32_t)p | (uint32_t)g.parts << 16; blk_at++; }
+            else { c.in.first_block[r] = (uint16_t)blk_at; blk_at += (uint32_t)g.parts; }
         }
+        if (!big) for (int r = ng; r < STORE_INLINE_GROUPS + 8; r++) c.in.first_block[r] = r == ng ? (uint16_t)blk_at : (uint16_t)0xFFFF;   // the kernel compares against all of them
     }
-    MaskArgs a{};
-    a.tab = d->tab;
-    a.store = d->store;
-    const bool direct = !sc;                              // the kernels read the pinned slot in place
-    uint8_t *base = direct ? (uint8_t *)d->h_stage[slot] : (uint8_t *)d->d_chart;
-    a.store_rows = (const StoreRow *)(base + off_srow);
-    a.entries = (const uint32_t *)(base + off_ent);
-    a.store_pending = base + off_pend;
-    a.store_import_root = d->d_import_root;
-    a.store_row_out = d->h_row_out + (size_t)slot * MAX_BATCH;
-    a.store_row_dev = d->d_row_out + (size_t)slot * MAX_BATCH;
-    a.rows = (const RowChart *)(base + off_rows);
-    a.set_off = (const uint32_t *)(base + off_so);
-    a.items = (const Item *)(base + off_items);
-    a.rank_mask = nullptr;                                // this kernel writes token-order rows itself: no rank-ordered bitmap, no closing kernel
-    a.out_mask = sc ? d->d_pool : d_mask;
-    a.dst_row = direct ? nullptr : (const uint32_t *)(base + off_dst);
-    a.row_slot = (const uint32_t *)(base + off_rowslot);
-    a.user_mask = d_mask;
-    a.user_batch = batch;
-    a.handoff_in_permute = 0;
-    a.handoff_in_store = sc ? 0 : 1;                      // with the state cache on, the gather is the call's last kernel
-    a.store_mini = use_mini ? 1 : 0;
-    if (g_apply.out && direct && nb == batch) {            // every row runs through the kernel, row r of the call is row r of the tensors
-        const size_t esz = g_apply.dtype == 0 ? 4 : 2;
-        const bool pieces = (uintptr_t)g_apply.logits % 16 == 0 && (uintptr_t)g_apply.out % 16 == 0 && (g_apply.stride * (int64_t)esz) % 16 == 0 &&
-                            (size_t)e->V % (16 / esz) == 0;
-        if (pieces) {
-            a.apply_logits = g_apply.logits; a.apply_out = g_apply.out; a.apply_stride = g_apply.stride; a.apply_dtype = g_apply.dtype;
-            g_apply.fused = true;
-        }
-    }
-    a.counters = d->d_counters + COUNTER_SET_WORDS * d->call_parity;
-    a.counters_next = d->d_counters + COUNTER_SET_WORDS * (d->call_parity ^ 1u);
-    d->call_parity ^= 1u;
-    a.host_status = d->h_status + 8 * slot;
+    const DeviceTables &T = d->tab;
+    uint8_t *stage = (uint8_t *)d->h_stage[slot];
+    a.valid = T.ci_valid_tok; a.cd = T.ci_cd_tok; a.tok16 = T.tok16; a.trans = d->store.trans;
+    a.out_mask = d_mask; a.pool = d->d_pool; a.konst = d->d_konst;
+    a.spilled = (const StoreRow *)(stage + off_spill); a.entries = (const uint32_t *)(stage + off_ent); a.pending = stage + off_pend;
+    a.import_root = d->d_import_root;
+    if (big) {
+        a.groups = (const StoreGroup *)d->d_chart;
+        a.block_of = (const uint32_t *)((const uint8_t *)d->d_chart + off_block);
+        a.members = (const uint16_t *)((const uint8_t *)d->d_chart + off_mem);
+    } else if (batch > STORE_INLINE_ROWS) a.members = (const uint16_t *)(stage + off_mem);
+    a.tickets = d->d_tickets;
+    a.status = (unsigned long long *)d->h_store_status + slot * STORE_STATUS_WORDS;
     if (++d->call_seq == 0) d->call_seq = 1;
-    a.seq = d->call_seq;
-    a.fb_waves = FB_WAVES; a.fb_stride = FB_ITEMS_PER_WAVE;   // the closing kernel's fallback pass has nothing to do on this path
-    a.batch = nb;
-    a.mode = d->mode;
-    a.aut_wide = biggest_set > (size_t)AUT_NARROW_SET_MAX ? 1 : 0;   // a hint: which variant of the byte step to try first on larger sets
-    {   // LDS of a block: the staged tables, the cache of table entries, and per wavefront the set under construction
-        int scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
-        while (scratch > 32 && store_lds_bytes(d->tab, d->mode, scratch) > (uint32_t)STORE_LDS_MAX) scratch -= 32;
-        if (store_lds_bytes(d->tab, d->mode, scratch) > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
-        a.aut_scratch = scratch;
-        // Blocks per row.  A wavefront takes the row's mask words in segments (16 words = 512 tokens, fewer for rows most of
-        // whose tokens are undecided, so that a segment holds about one batch) and the undecided tokens among them 64 at a
-        // time; rows differ by orders of magnitude in how many tokens their token-mask cache rows leave undecided, which
-        // set-up counted per cache row.  The grid is never larger than what the chip holds at once: a block that had to wait
-        // for a place would start from nothing (LDS cache, the row's state) when the others are nearly done, which costs more
-        // than a few more passes of the wavefronts that are there.
-        const int budget = std::max(nb, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
-        if (!use_mini) {
-            const int n_seg = (d->tab.W + STORE_SEG_WORDS - 1) / STORE_SEG_WORDS;
-            a.store_uniform_parts = std::max(1, std::min(std::max(1, (n_seg + STORE_WAVES - 1) / STORE_WAVES), budget / nb));
-        } else {
-            double cost[STORE_MINI_ROWS], inv_cost[STORE_MINI_ROWS];
-            int segs[STORE_MINI_ROWS], parts[STORE_MINI_ROWS], seg_w[STORE_MINI_ROWS];
-            for (int r = 0; r < nb; r++) {
-                double und = d->tab.V;
-                if (use_cache && row_n_items[r] <= 64) {
-                    const uint32_t n = row_n_ent[r];              // the row's cache-row numbers, as gathered for its record
-                    const uint32_t *ent = (const uint32_t *)((uint8_t *)d->h_stage[slot] + off_ent) + row_ent_at[r];
-                    uint64_t sig = 0xCBF29CE484222325ull ^ n;
-                    for (uint32_t k = 0; k < n; k++) sig = (sig ^ ent[k]) * 0x100000001B3ull;
-                    auto it = d->undecided_of.find(sig);
-                    if (it == d->undecided_of.end()) {
-                        const size_t Wt = (size_t)d->tab.W;
-                        uint32_t cnt = 0;
-                        for (size_t w = 0; w < Wt; w++) {
-                            uint32_t v = 0, cd = 0;
-                            for (uint32_t k = 0; k < n; k++) { v |= d->h_valid_tok[ent[k] * Wt + w]; cd |= d->h_cd_tok[ent[k] * Wt + w]; }
-                            cnt += (uint32_t)__builtin_popcount(cd & ~v);
-                        }
-                        if (d->undecided_of.size() > 65536) d->undecided_of.clear();
-                        it = d->undecided_of.emplace(sig, cnt).first;
-                    }
-                    und = it->second;
-                }
-                // words per segment: as many as are expected to hold 48 undecided tokens, at most 64 (a batch is 64: the
-                // tokens are spread unevenly, and a second, nearly empty batch costs as much as a full one)
-                const uint32_t seg_words = (uint32_t)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 48.0 * std::max(1, d->tab.V) / (32.0 * std::max(und, 1.0))));
-                segs[r] = (d->tab.W + (int)seg_words - 1) / (int)seg_words;
-                seg_w[r] = (int)seg_words;
-                // what a pass costs a wavefront (microseconds, measured): an empty segment 2.8, a segment with a batch 3.7, each further batch 3
-                const double per_seg = und / segs[r];
-                cost[r] = per_seg < 1.0 ? 2.8 + 0.9 * per_seg : 3.7 + 3.0 * std::max(0.0, per_seg / 64.0 - 0.75);
-                inv_cost[r] = 1.0 / cost[r];
-            }
-            // Every wavefront of a row takes the same number of passes (a row is as slow as its slowest wavefront).  The
-            // smallest time T is looked for in which every row, taking as many passes as fit into T, leaves the grid within
-            // what the chip holds; rows are then given passes back while blocks are left.
-            int passes[STORE_MINI_ROWS];
-            auto blocks_for = [&](int r, int n_pass) { return std::max(1, (segs[r] + n_pass * STORE_WAVES - 1) / (n_pass * STORE_WAVES)); };
-            auto need = [&](double T) {
-                int tot = 0;
-                for (int r = 0; r < nb; r++) tot += blocks_for(r, std::max(1, (int)(T * inv_cost[r])));
-                return tot;
-            };
-            double lo = cost[0];
-            for (int r = 1; r < nb; r++) lo = std::min(lo, cost[r]);
-            double hi = lo;
-            if (need(hi) > budget) {
-                while (need(hi) > budget && hi < 1e9) { lo = hi; hi *= 2; }
-                for (int it = 0; it < 6; it++) { const double mid = 0.5 * (lo + hi); if (need(mid) <= budget) hi = mid; else lo = mid; }   // to 2 %: the blocks left over go back to the rows below
-            }
-            int all = 0;
-            for (int r = 0; r < nb; r++) { passes[r] = std::max(1, (int)(hi * inv_cost[r])); parts[r] = blocks_for(r, passes[r]); all += parts[r]; }
-            for (int r = 0; r < nb && all < budget; r++) {
-                if (passes[r] <= 1) continue;
-                const int p = blocks_for(r, passes[r] - 1);
-                if (p - parts[r] <= budget - all) { all += p - parts[r]; parts[r] = p; passes[r]--; }
-            }
-            // Blocks are dealt to the eight XCDs in turn, and every XCD has an L2 of its own.  When rows start at multiples of eight,
-            // the blocks that take the same stretch of the vocabulary for different rows run on the same XCD and find each other's
-            // strings and cache rows in its L2.  So rows of eight blocks or more are rounded UP to a multiple of eight while blocks are
-            // left over (never down: fewer blocks would mean more passes); a block beyond the row's segments leaves at once.
-            for (int r = 0; r < nb; r++) {
-                const int up = (8 - (parts[r] & 7)) & 7;
-                if (parts[r] >= 8 && up && all + up <= budget) { parts[r] += up; all += up; }
-            }
-#ifndef ZF_MERGE_SEGMENTS
-#define ZF_MERGE_SEGMENTS 1
-#endif
-            for (int r = 0; r < nb; r++) {
-                // A wavefront that has several segments to take takes them as fewer, wider ones (up to 64 words): the strings of a
-                // segment's first batch are waited for, those of its further batches travel while the batch before is checked.
-                if (ZF_MERGE_SEGMENTS && passes[r] > 1 && seg_w[r] < STORE_SEG_WORDS_MAX) {
-                    const int words_per_wave = (d->tab.W + parts[r] * STORE_WAVES - 1) / (parts[r] * STORE_WAVES);
-                    const int n_pass = (words_per_wave + STORE_SEG_WORDS_MAX - 1) / STORE_SEG_WORDS_MAX;
-                    seg_w[r] = std::max(seg_w[r], std::min<int>(STORE_SEG_WORDS_MAX, (words_per_wave + n_pass - 1) / n_pass));
-                }
-                mini.r[r].meta |= (uint32_t)(seg_w[r] - 1) << 24;
-            }
-            uint32_t at = 0;
-            for (int r = 0; r < nb; r++) { a.store_first_block[r] = (uint16_t)at; at += (uint32_t)parts[r]; }
-            for (int r = nb; r < STORE_MINI_ROWS + 8; r++) a.store_first_block[r] = r == nb ? (uint16_t)at : (uint16_t)0xFFFF;   // the kernel compares against all of them
-            a.store_uniform_parts = 0;
-        }
-    }
+    a.seq = rec.seq = d->call_seq;
+    a.V = (uint32_t)e->V; a.W = (uint32_t)T.W; a.ncls = (uint32_t)T.n_cls; a.cap_states = d->store.cap_states; a.tab_mode = (uint32_t)d->mode;
+    a.scratch = scratch;
+    a.wide = biggest_set > (size_t)AUT_NARROW_SET_MAX ? 1 : 0;   // a hint: which variant of the byte step to try first on larger sets
+    a.complete = wait ? 1 : 0;
+    a.report_size = n_imp ? 1 : 0;
     const bool prof = d->profiling;
-    d->report.chart_bytes = (int64_t)total;
+    d->report.chart_bytes = (int64_t)(total + (big ? 0 : sizeof(StoreGroup) * ng));
     d->report.cache_rows = (int32_t)n_cache_rows;
     d->report.main_ms = d->report.fallback_ms = d->report.permute_ms = 0.f;
     d->report.overflow_chunks = d->report.walk_chunks = d->report.parser_steps = 0;
-    if (!direct) HIP_TRY(launch_upload(d->h_stage[slot], d->d_chart, total, stream));
-    if (n_imp) HIP_TRY(launch_store_import(a, (const uint32_t *)(base + off_imp), (uint32_t)n_imp, stream));
-    const bool run_kernels = nb > 0;
+    if (big) HIP_TRY(launch_upload(stage, d->d_chart, up_bytes, stream));
+    if (n_imp) HIP_TRY(launch_store_import(d->store, (const RowChart *)(stage + off_rows), (const uint32_t *)(stage + off_so), (const Item *)(stage + off_items),
+                                           (const uint32_t *)(stage + off_imp), (uint32_t)n_imp, d->d_import_root, stream));
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
-    d->closing_kernel = sc;
-    if (run_kernels) HIP_TRY(launch_mask_store(a, mini, stream));
-    if (prof) HIP_TRY(hipEventRecord(d->ev[1], stream));
-    if (sc) HIP_TRY(launch_gather(a, stream));
-    if (prof) HIP_TRY(hipEventRecord(d->ev[3], stream));
-    HIP_TRY(hipEventRecord(d->stage_done[slot], stream));
+    d->closing_kernel = false;
+    HIP_TRY(launch_mask_store(a, c.in, lds, stream));
+    if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
+    // No event marks the staging slot free: at most N_SLOTS calls are in flight between two zf_mask_wait calls, so the call that
+    // used this slot before has been waited for.
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;
-    if (!wait) return ZF_OK;
-    HIP_TRY(hipStreamSynchronize(stream));
-    return zf_mask_wait(e, hip_stream);
-}
-
-static void forget_cached_masks(DeviceSide *d) {
-    d->cache_index.clear();
-    for (auto &ce : d->cache) ce.used = false;
+    rec.active = true;
+    host_lk.unlock();
+    // the waiting call returns with the mask complete: the kernel wrote it through to memory before it drew its tickets
+    return wait ? zf_mask_wait(e, hip_stream) : ZF_OK;
 }
 
 // A call that fails part-way may have registered cache slots whose masks were never written.
@@ -1630,7 +1747,7 @@ static void explore_from_the_empty_prefix(zf_engine *e) {
     const size_t budget_states = (size_t)e->opt.precompute_states;
     hipError_t he = hipSetDevice(e->opt.device);
     uint32_t *d_tmp = nullptr;
-    constexpr int ROWS = STORE_MINI_ROWS;
+    constexpr int ROWS = 64;
     if (he != hipSuccess || hipMalloc((void **)&d_tmp, (size_t)ROWS * (size_t)std::max(e->W, 1) * 4) != hipSuccess) { (void)hipGetLastError(); return; }
     std::vector<uint8_t> rep(std::max(e->tab.n_cls, 0), 0);   // one byte of every class
     std::vector<char> have(rep.size(), 0);
@@ -1709,55 +1826,76 @@ int zf_mask_wait(zf_engine *e, void *hip_stream) {
     DeviceSide *d = e->dev;
     HIP_TRY(hipSetDevice(d->device));
     volatile uint32_t *st = d->h_status;
-    if (d->pending) {
-        // The newest call's last kernel writes the call's number into pinned memory after its counters: poll that word
-        // instead of synchronising the stream (which also waits for whatever the caller queued behind the mask kernels,
-        // apply_mask for one, and wakes up microseconds later).  Calls of one engine run in stream order, so the older
-        // calls in flight have finished too.  Bounded: after two seconds the stream is synchronised, which also
-        // surfaces a device error.
-        volatile uint32_t *flag = st + 8 * d->last_slot + 4;
+    // Poll a word that a call's last kernel writes into pinned memory instead of synchronising the stream (which also waits for
+    // whatever the caller queued behind the mask kernels, apply_mask for one, and wakes up microseconds later).  Bounded: after
+    // two seconds the stream is synchronised, which also surfaces a device error.
+    auto await = [&](auto arrived) -> int {
         const auto t0 = std::chrono::steady_clock::now();
-        for (uint32_t spins = 0; *flag != d->last_seq; spins++) {
+        for (uint32_t spins = 0; !arrived(); spins++) {
             __builtin_ia32_pause();
             if ((spins & 0xFFFu) == 0xFFFu && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) {
                 HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));
-                if (*flag != d->last_seq) return fail(ZF_ERR_DEVICE, "the mask kernels did not report back");
+                if (!arrived()) return fail(ZF_ERR_DEVICE, "the mask kernels did not report back");
                 break;
             }
         }
         std::atomic_thread_fence(std::memory_order_acquire);
-        if (d->profiling) HIP_TRY(hipEventSynchronize(d->ev[3]));
-    } else {
-        HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));   // nothing of this engine in flight: plain stream synchronisation
-    }
+        return ZF_OK;
+    };
     uint32_t unresolved = 0;
-    if (e->store_on) {
-        // note where every row of the finished calls stands in the persistent automaton, oldest call first
+    if (d->pending) {
+        int rc = ZF_OK;
+        // calls of one engine run in stream order: once the newest has reported, the older ones in flight have finished too
+        if (!d->rec[d->last_slot].active) {
+            volatile uint32_t *flag = st + 8 * d->last_slot + 4;
+            rc = await([&]() { return *flag == d->last_seq; });
+        }
+        // the calls through the persistent automaton, oldest first: their status, and where their rows stand
         for (int i = 0; i < DeviceSide::N_SLOTS; i++) {
             const uint32_t k = (d->next_slot + i) % DeviceSide::N_SLOTS;
             DeviceSide::CallRecord &rec = d->rec[k];
             if (!rec.active) continue;
             rec.active = false;
-            struct Release { DeviceSide::CallRecord &r; ~Release() { r.st.clear(); } } release{rec};
-            const bool good = st[8 * k + 2] == 0 && rec.epoch == d->store_epoch;
-            const uint32_t *out = d->h_row_out + (size_t)k * MAX_BATCH;
-            for (size_t r = 0; r < rec.st.size() && good; r++) {
-                zf_state *s = rec.st[r] ? rec.st[r]->s : nullptr;
-                if (out[r] == 0 || (out[r] >= d->store.cap_states && out[r] != 0xFFFFFFFDu)) continue;
-                if (rec.hop[r]) d->hop_note(rec.hop[r], out[r]);          // a fact about the automaton, whatever has become of the row
-                if (r < rec.host.size() && rec.host[r] && out[r] != 0xFFFFFFFDu) d->name_note(rec.host[r], rec.host_epoch, rec.epoch, out[r]);   // and so is this
-                if (!s || s->generation != rec.gen[r]) continue;
-                if (rec.upto[r] < s->pending_base) continue;              // a later call's result is already in
-                const size_t drop = std::min<size_t>((size_t)(rec.upto[r] - s->pending_base), s->pending.size());
-                s->pending_token = -1;
-                s->pending.erase(s->pending.begin(), s->pending.begin() + drop);
-                s->pending_base = rec.upto[r];
-                s->dev_id = out[r]; s->dev_epoch = rec.epoch;
+            struct Release { DeviceSide::CallRecord &r; ~Release() { r.rows.clear(); r.groups.clear(); } } release{rec};
+            if (rc != ZF_OK) continue;
+            const volatile uint64_t *out = d->h_store_status + k * STORE_STATUS_WORDS;
+            auto got = [&](size_t w) { return (uint32_t)(out[w] >> 32) == rec.seq; };
+            if ((rc = await([&]() { return got(STORE_ST_DONE); })) != ZF_OK) continue;
+            const uint32_t done = (uint32_t)out[STORE_ST_DONE], failed = done & 0xFFFFFFu;
+            unresolved += failed;
+            d->report.walk_chunks = rec.undecided;
+            d->report.parser_steps = 0;
+            if (failed) d->store_dirty = true;            // a walk failed: start over
+            if (done & STORE_ST_MORE) {                   // every word says by itself whether it is in
+                if ((rc = await([&]() { return got(STORE_ST_STEPS) && got(STORE_ST_STATES) && got(STORE_ST_ITEMS) && got(STORE_ST_REFUSED); })) != ZF_OK) continue;
+                d->report.parser_steps = (int32_t)(uint32_t)out[STORE_ST_STEPS];
+                d->store_states = (uint32_t)out[STORE_ST_STATES]; d->store_items = (uint32_t)out[STORE_ST_ITEMS];
+                if ((uint32_t)out[STORE_ST_REFUSED]) d->store_dirty = true;   // the store refused a request: start over
             }
-            if (st[8 * k + 5]) { d->store_states = st[8 * k + 5]; d->store_items = st[8 * k + 6]; }
-            if (st[8 * k + 7] || st[8 * k + 2]) d->store_dirty = true;    // the store refused a request, or a walk failed: start over
-            st[8 * k + 5] = st[8 * k + 6] = st[8 * k + 7] = 0;
+            if (failed || rec.epoch != d->store_epoch) continue;
+            for (const DeviceSide::CallRecord::Group &g : rec.groups) {
+                if ((rc = await([&]() { return got(STORE_ST_ROW + g.group); })) != ZF_OK) break;
+                const uint32_t at = (uint32_t)out[STORE_ST_ROW + g.group];
+                if (at == 0 || (at >= d->store.cap_states && at != HostAutomaton::SINK)) continue;
+                if (g.hop) d->hop_note(g.hop, at);                                // a fact about the automaton, whatever has become of the rows
+                if (g.host_id && at != HostAutomaton::SINK) d->name_note(g.host_id, rec.host_epoch, rec.epoch, at);   // and so is this
+                for (uint32_t r = g.first; r < g.first + g.n; r++) {
+                    const DeviceSide::CallRecord::Row &row = rec.rows[r];
+                    zf_state *s = row.st ? row.st->s : nullptr;
+                    if (!s || s->generation != row.gen) continue;
+                    if (row.upto < s->pending_base) continue;                     // a later call's result is already in
+                    const size_t drop = std::min<size_t>((size_t)(row.upto - s->pending_base), s->pending.size());
+                    s->pending_token = -1;
+                    s->pending.erase(s->pending.begin(), s->pending.begin() + drop);
+                    s->pending_base = row.upto;
+                    s->dev_id = at; s->dev_epoch = rec.epoch;
+                }
+            }
         }
+        if (rc != ZF_OK) { d->pending = 0; return rc; }
+        if (d->profiling) HIP_TRY(hipEventSynchronize(d->ev[3]));
+    } else {
+        HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));   // nothing of this engine in flight: plain stream synchronisation
     }
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) {
         unresolved += st[8 * k + 2];

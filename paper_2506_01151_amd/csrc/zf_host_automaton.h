@@ -28,6 +28,8 @@ struct HostAutomaton {
         std::vector<uint32_t> trans;      // [n_cls] next state, NONE, DEAD or SINK
         std::vector<uint8_t> acc;         // [n_cls] the prefix is a sentence after that byte
         uint32_t widest = 0;              // items of the largest set among the state and the sets it refers to
+        std::vector<uint32_t> ents;       // what the mask calls work out about the state once: the rows of the token-mask cache its items select ...
+        int64_t undecided = -1;           // ... and how many tokens these leave to the parser (-1: not yet)
     };
     std::vector<std::unique_ptr<State[]>> blocks;   // room for MAX_BLOCKS pointers from the start: the array never moves
     uint32_t n_states = 0;                // ids 0 .. n_states - 1 are taken (0 is not used)

@@ -41,28 +41,28 @@ static const size_t NOALLOC_STAGE_BYTES = 256u << 10;  // pinned staging room pe
 #ifndef ZF_STORE_WAVES
 #define ZF_STORE_WAVES 4
 #endif
-#ifndef ZF_STORE_SUB_WORDS
-#define ZF_STORE_SUB_WORDS 64
-#endif
 #ifndef ZF_STORE_LC_BITS
 #define ZF_STORE_LC_BITS 10
 #endif
 static const int STORE_WAVES = ZF_STORE_WAVES;  // wavefronts per block of the mask kernel over the persistent automaton
 static const int STORE_BLOCK = STORE_WAVES * 64;
-static const int STORE_SUB_WORDS = ZF_STORE_SUB_WORDS;   // words of the rank-ordered bitmap a block merges and checks per pass (at most 128: one wavefront lists the word pairs)
 static const int STORE_LDS_MAX = 159 * 1024;   // dynamic LDS a block of that kernel may ask for (the hand-over of the call's status has a static word of its own)
-static const int STORE_SEG_WORDS = 16;         // mask words (of 32 tokens) a wavefront merges and checks per pass in calls of more than STORE_MINI_ROWS rows ...
-static const int STORE_SEG_WORDS_MAX = 64;     // ... smaller calls choose 1 to 64 per row, so that a pass holds about one batch of undecided tokens
+static const int STORE_SEG_WORDS_MAX = 64;     // mask words (of 32 tokens) a wavefront merges and checks per pass: 1 to 64, chosen per group so that a pass holds about one batch of undecided tokens
 static const int STORE_WARM_ROWS = 32;         // rows of the transition table (states one byte from a row's current state) a block reads ahead into its LDS cache
 static const int STORE_LC_BITS = ZF_STORE_LC_BITS;       // log2 of the entries of a block's LDS cache of table entries (8 bytes each)
 #ifndef ZF_STORE_BLOCKS_PER_CU
 #define ZF_STORE_BLOCKS_PER_CU 3
 #endif
 static const int STORE_BLOCKS_PER_CU = ZF_STORE_BLOCKS_PER_CU;   // blocks per compute unit the grid is made of at most (fewer when a compute unit holds fewer at once)
-static const int STORE_PENDING_LDS = 256;       // pending bytes of a row a block keeps in LDS (more are read from the upload)
+static const uint64_t STORE_FUSE_BYTES = 16u << 20;   // logits read and written by zf_compute_mask_apply_async up to which the mask kernel masks them itself
 static const int STORE_PENDING_MAX = 4096;      // beyond this many bytes since its state was last known a row comes in through its chart again
-static const uint32_t STORE_ROW_CACHE = 1u;     // StoreRow::flags: the token-mask cache rows of the row are listed
-static const uint32_t STORE_ROW_IMPORTED = 2u;  // the row's start state is the one the import kernel made from its chart
+// Flags of a group of rows (StoreGroup::meta, StoreRow::flags):
+static const uint32_t STORE_ROW_CACHE = 1u;     // the token-mask cache rows of the group's current set are listed
+static const uint32_t STORE_ROW_IMPORTED = 2u;  // the group's start state is the one the import kernel made from its chart
+static const uint32_t STORE_ROW_SPILL = 4u;     // the record does not fit the short form: it is in StoreArgs::spilled
+static const uint32_t STORE_ROW_POOLED = 8u;    // the mask is a finished row of the state cache's pool (row number: start): copied, nothing to check
+static const uint32_t STORE_ROW_KEEP = 16u;     // the finished mask goes to the state cache's pool as well (row number: slot)
+static const uint32_t STORE_ROW_REPORT = 32u;   // the host does not know the state the group stands in: the kernel reports it
 struct StoreView {
     uint2 *hdr;                 // [cap_states] (first item in the arena, item count); count 0xFFFFFFFF = not published
     uint2 *arena;               // [cap_items] (item word, name of the set the item's rule started in)
@@ -71,55 +71,88 @@ struct StoreView {
     uint32_t *ctl;              // [0] states handed out (the next name), [1] items handed out, [2] requests the store had no room for
     uint32_t cap_states, cap_items, intern_mask;
 };
-static const int STORE_ROW_ENT = 10, STORE_ROW_ENT_AT = 6;      // token-mask-cache rows a record holds inline, and the word they start at
-static const int STORE_ROW_PEND = 64, STORE_ROW_PEND_AT = 16;   // pending bytes a record holds inline, and the word they start at
-struct StoreRow {               // one row of a call: 128 bytes, read by a wavefront with one load (lane k = word k)
-    uint32_t start;             // [0] the state the row was last known to be in
-    uint32_t n_pending;         // [1] bytes (as byte classes) fed to the row since then: inline when they fit ...
+static const int STORE_ROW_ENT = 10, STORE_ROW_ENT_AT = 6;      // token-mask-cache rows a full record holds inline, and the word they start at
+static const int STORE_ROW_PEND = 64, STORE_ROW_PEND_AT = 16;   // pending bytes a full record holds inline, and the word they start at
+struct StoreRow {               // full record of a group of rows: 128 bytes, read by a wavefront with one load (lane k = word k)
+    uint32_t start;             // [0] the state the group was last known to be in
+    uint32_t n_pending;         // [1] bytes (as byte classes) fed to its rows since then: inline when they fit ...
     uint32_t pend_off;          // [2] ... else at this offset of the call's pending bytes
-    uint32_t n_ent, ent_off;    // [3] [4] token-mask-cache rows of the row's current set: inline when they fit, else in MaskArgs::entries
+    uint32_t n_ent, ent_off;    // [3] [4] token-mask-cache rows of the current set: inline when they fit, else in StoreArgs::entries
     uint32_t flags;             // [5]
     uint32_t ent[STORE_ROW_ENT];
     uint8_t pend[STORE_ROW_PEND];
 };
-static_assert(sizeof(StoreRow) == 128, "a wavefront reads a row's record as 32 words");
-// The same record in 48 bytes, for calls of up to STORE_MINI_ROWS rows: it travels in the kernel's argument block, which the
-// wavefronts read without a trip to the host's memory.  A row whose record does not fit (more pending bytes, more or larger
-// cache row numbers) says so in its flags and is read from store_rows.
-static const int STORE_MINI_ROWS = 64, STORE_MINI_PEND = 16, STORE_MINI_ENT = 10;
-static const uint32_t STORE_ROW_SPILL = 4u;     // flags of a short record: the row's full record is in MaskArgs::store_rows
-struct StoreRowMini {
-    uint32_t start;                               // as StoreRow::start
-    uint32_t meta;                                // n_pending | n_ent << 8 | flags << 16 | (mask words per pass - 1) << 24
-    uint8_t pend[STORE_MINI_PEND];
-    uint16_t ent[STORE_MINI_ENT];
-    uint32_t spare;
+static_assert(sizeof(StoreRow) == 128, "a wavefront reads a full record as 32 words");
+// One group of rows of a call: the rows that stand in the same state of the automaton, whose mask is worked out once.  The
+// records of up to STORE_INLINE_GROUPS groups travel in the kernel's argument block, which the wavefronts read without a trip to
+// the host's memory; larger calls upload them.  A record that does not fit (more pending bytes, more or larger cache row
+// numbers) says so in its flags and is read from StoreArgs::spilled.
+static const int STORE_INLINE_GROUPS = 64, STORE_INLINE_ROWS = 256, STORE_GROUP_PEND = 16, STORE_GROUP_ENT = 9;
+struct StoreGroup {
+    uint32_t start;                               // [0] as StoreRow::start
+    uint32_t meta;                                // [1] n_pending | n_ent << 8 | flags << 16 | (mask words per pass - 1) << 24
+    uint8_t pend[STORE_GROUP_PEND];               // [2 .. 5]
+    uint16_t ent[STORE_GROUP_ENT];                // [6 .. 10 low half]
+    uint16_t slot;                                // [10 high half] row of the state cache's pool (STORE_ROW_KEEP)
+    uint16_t member_at, n_members;                // [11] the group's rows: members[member_at ..]
 };
-static_assert(sizeof(StoreRowMini) == 48, "short row records are twelve words");
-struct StoreMiniRows { StoreRowMini r[STORE_MINI_ROWS]; };
+static_assert(sizeof(StoreGroup) == 48, "group records are twelve words");
+struct StoreInline {
+    uint16_t first_block[STORE_INLINE_GROUPS + 8];   // first block of each group, ascending; 0xFFFF beyond the call's groups
+    uint16_t member[STORE_INLINE_ROWS];
+    StoreGroup g[STORE_INLINE_GROUPS];
+};
+// What only a wavefront that computes a transition reads: in device memory, once per engine.
+struct StoreConst {
+    DeviceTables tab;
+    StoreView view;
+};
+struct StoreArgs {
+    const uint32_t *valid, *cd;        // DeviceTables::ci_valid_tok, ci_cd_tok
+    const Str16 *tok16;
+    const uint8_t *tok_len;
+    uint32_t *trans;                   // StoreView::trans
+    uint32_t *out_mask;                // the caller's [batch][W] tensor
+    uint32_t *pool;                    // the state cache's rows, [entries][W]
+    const void *logits;                // zf_compute_mask_apply_async: the logits to be masked by the same kernel (APPLY builds)
+    void *out;
+    int64_t stride;                    // elements between their rows
+    const StoreConst *konst;
+    const StoreRow *spilled;           // pinned: full records, by group
+    const uint32_t *entries;           // pinned: cache row numbers that do not fit a full record
+    const uint8_t *pending;            // pinned: pending bytes that do not fit a full record
+    const uint32_t *import_root;       // [group] device memory: written by the import kernel
+    const StoreGroup *groups;          // null: in the argument block; else device memory, with ...
+    const uint32_t *block_of;          // ... group | part << 16 of every block
+    const uint16_t *members;           // row numbers of the groups, one group after the other; null: in the argument block
+    unsigned long long *tickets;       // device memory, STORE_TICKETS words, zero between calls (see hand_over_store)
+    unsigned long long *status;        // pinned host memory: (seq << 32 | value) words, see StoreStatus
+    uint32_t seq;                      // the call's number (never 0)
+    uint32_t V, W, ncls, cap_states, tab_mode;
+    int32_t scratch;                   // items of one set under construction (per wavefront)
+    uint8_t wide;                      // the rows' sets hold many items: the wide byte step first on larger sets
+    uint8_t complete;                  // the host takes the status word for the mask's completion: the mask goes out write-through, ahead of the status
+    uint8_t report_size;               // report the store's size whether or not a transition was computed
+    uint8_t dtype;                     // of the logits: 0 = none, 1 = fp32, 2 = bf16
+    uint32_t n_blocks;
+};
+static_assert(sizeof(StoreArgs) + sizeof(StoreInline) <= 4096, "the kernel's argument block");
+// Words of a call's status in pinned host memory.  Every word carries the call's number in its upper half, so the host knows of
+// each word by itself whether it has arrived: no order between them is needed (a release would write the L2 back first).
+enum : uint32_t { STORE_ST_DONE = 0,       // low half: walks that failed (24 bits) | STORE_ST_MORE; written last, by the block that finishes last
+                  STORE_ST_STEPS = 1,      // Earley byte steps   (this word and the next three only with STORE_ST_MORE)
+                  STORE_ST_STATES = 2, STORE_ST_ITEMS = 3, STORE_ST_REFUSED = 4,
+                  STORE_ST_ROW = 8 };      // + group: the state the group arrived in (groups with STORE_ROW_REPORT)
+static const uint32_t STORE_ST_MORE = 0x80000000u;
+static const int STORE_TICKET_GROUPS = 64, STORE_TICKETS = STORE_TICKET_GROUPS + 1;
 
 // A set of per-call counters: words 0-7 as listed at MaskArgs::counters, then the tickets the blocks of a call's last kernel
 // draw when they are done (one word per group of blocks, so that thousands of blocks do not queue up at one address, and a
 // top word the last block of each group draws from).
-// A ticket word is 64 bits: tickets drawn in the low half, and in the high half a partial sum of counter [1] (undecided tokens)
-// that the mask kernel over the persistent automaton adds with the same operation, once per block.  (Thousands of additions to
-// one word, or to one cache line, queue up at the memory channel that holds it and hold up every other request to that channel:
-// 30 us per launch when every wavefront added its count to counters[1].)  The block that hands the status over adds them up.
 static const int COUNTER_SET_WORDS = 160, TICKET_GROUPS = 64, TICKET_AT = 16, TICKET_TOP = 144;
 
 struct MaskArgs {
     DeviceTables tab;
-    StoreView store;
-    const StoreRow *store_rows;        // [batch]
-    const uint8_t *store_pending;
-    uint32_t *store_import_root;       // [batch] device memory: written by the import kernel
-    uint32_t *store_row_out;           // [batch] pinned host memory: the state every row is in after this call's walk ...
-    uint32_t *store_row_dev;           // [batch] ... which the mask kernel notes here (device memory); the block that hands the call's status over copies it out
-    // The grid of the store kernel is one-dimensional.  In calls of up to STORE_MINI_ROWS rows the host gives rows whose
-    // token-mask cache leaves more tokens undecided more blocks: row r has blocks store_first_block[r] .. store_first_block[r + 1]
-    // (ascending; 0xFFFF beyond the call's rows) and store_uniform_parts is 0; larger calls give every row store_uniform_parts blocks.
-    alignas(16) uint16_t store_first_block[STORE_MINI_ROWS + 8];
-    int32_t store_uniform_parts;
     const RowChart *rows;      // [batch]
     const uint32_t *set_off;   // shared CSR offsets of all rows' sets
     const Item *items;         // shared item array of all rows
@@ -132,15 +165,6 @@ struct MaskArgs {
     uint32_t *user_mask;       // the caller's [user_batch][W] tensor (target of the gather)
     int32_t user_batch;
     int32_t handoff_in_permute; // 1: permute is the call's last kernel (state cache off), else the gather is
-    int32_t handoff_in_store;  // 1: the mask kernel over the persistent automaton is the call's last kernel (it writes the caller's rows itself)
-    // zf_compute_mask_apply_async on that path: a wavefront masks the logits of the tokens whose mask words it has just written
-    // (no second kernel); null = the mask only.  Row r of the call is row r of the tensors; 16-byte pieces (V, the row stride
-    // and the pointers are multiples of a piece: the host checks).
-    const void *apply_logits;
-    void *apply_out;
-    int64_t apply_stride;      // elements between rows
-    int32_t apply_dtype;       // 0 = fp32, 1 = bf16
-    int32_t store_mini;        // 1: the rows' records are in the kernel's StoreMiniRows argument
     uint32_t *counters;        // [0] chunks passed to the fallback, [1] length of the work queue, [2] chunks nobody could resolve,
                                // [3] Earley byte steps, [4] fallback wavefronts that have finished, [16..144] tickets of the call's last kernel;
                                // COUNTER_SET_WORDS words per set
@@ -183,9 +207,11 @@ hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s);
 hipError_t prepare_store_kernels();
 uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch);
-hipError_t launch_mask_store(const MaskArgs &a, const StoreMiniRows &mini, hipStream_t s);
+hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s);
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s);
-hipError_t launch_store_import(const MaskArgs &a, const uint32_t *import_rows, uint32_t n_import, hipStream_t s);
+// n charts (packed as for the other mask kernels) become states; import_root[group[k]] = the state of chart k's current set (AT_FAIL: no room)
+hipError_t launch_store_import(const StoreView &G, const RowChart *charts, const uint32_t *set_off, const Item *items, const uint32_t *group,
+                               uint32_t n, uint32_t *import_root, hipStream_t s);
 hipError_t launch_finish(const MaskArgs &a, int cus, hipStream_t s);   // fallback pass (when anything was listed) + permutation into token order
 hipError_t launch_gather(const MaskArgs &a, hipStream_t s);
 // Per-device address of the static device array behind the entry point that may not allocate.

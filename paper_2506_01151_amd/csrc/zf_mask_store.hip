@@ -186,10 +186,41 @@ __device__ __forceinline__ uint32_t store_transition(const TV &T, const StoreVie
     return id;                                               // the table has twice as many slots as states: not reached
 }
 
-// Look the transition (s, cl) up for the whole wavefront (uniform arguments), computing it if nobody has.
-__device__ __forceinline__ uint32_t store_lookup_uniform(const TV &T, const StoreView &G, const Scratch &sc, const Staging &stg, uint32_t *errors,
-                                                         uint32_t *steps, uint32_t s, uint32_t cl, uint32_t lane) {
-    uint32_t *entry = G.trans + (size_t)s * T.ncls + cl;
+// The same as a function of its own, called by the rare wavefront that needs a transition nobody has computed yet.  In line (it
+// has two callers) the byte step made 45 of the kernel's 52 KB of code and its registers were allocated around it: the walk
+// spilled scalar registers and its code lay in pieces between pieces of this.  What it reads beyond its arguments is in device memory.
+// Everything is uniform: the arguments travel in vector registers and are taken back into scalar ones first.
+typedef __attribute__((address_space(3))) uint8_t LdsBytes;
+static const uint32_t SCRATCH_WIDE = 1u << 16;           // with the scratch's capacity (at most LANE_CAP_MAX) below and the wavefront's number above it
+static const uint32_t TABLES_AT = LC_ENTRIES * 8 + 32 + STORE_WAVES * 64 * 4;   // LDS: cache of table entries, staging flag, verdict words; then the staged tables, class representatives, scratch
+template <int MODE>
+__device__ __attribute__((noinline)) uint32_t store_transition_call(const StoreConst *konst_v, LdsBytes *lds_v, uint32_t how_v, uint32_t *errors, uint32_t s_v, uint32_t cl_v) {
+    const uint64_t kp = (uint64_t)(uintptr_t)konst_v;
+    const uint64_t ku = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)kp) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(kp >> 32)) << 32;
+    const StoreConst *konst = reinterpret_cast<const StoreConst *>((uintptr_t)ku);
+    uint8_t *smem = (uint8_t *)(LdsBytes *)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)lds_v);
+    const uint32_t how = (uint32_t)__builtin_amdgcn_readfirstlane((int)how_v);
+    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_v), cl = (uint32_t)__builtin_amdgcn_readfirstlane((int)cl_v);
+    const uint32_t lane = threadIdx.x & 63u;
+    const DeviceTables &D = konst->tab;
+    const StoreView &G = konst->view;
+    uint8_t *const tables_at = smem + TABLES_AT;
+    TV T;
+    uint32_t off = table_view<MODE>(D, tables_at, T);
+    const uint32_t n16 = off / 16;
+    uint8_t *l_rep = tables_at + off; off += 256;
+    const Staging stg{reinterpret_cast<uint32_t *>(smem + LC_ENTRIES * 8), tables_at, D.table_blob, n16, l_rep, D.cls_rep, (uint32_t)D.n_cls, (how & SCRATCH_WIDE) != 0};
+    Scratch sc;
+    sc.cap = how & 0xFFFFu;
+    sc.w = reinterpret_cast<uint32_t *>(tables_at + off) + (size_t)(how >> 24) * (2 * sc.cap + aut_hash_places(sc.cap));
+    sc.o = sc.w + sc.cap;
+    sc.h = sc.o + sc.cap;
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)store_transition(T, G, sc, stg, errors, s, cl, lane));
+}
+
+// Look a transition up for the whole wavefront (uniform arguments), computing it if nobody has.
+template <class Compute>
+__device__ __forceinline__ uint32_t store_lookup_uniform(uint32_t *entry, uint32_t lane, Compute compute) {
     // the read through the caches answers at once when the entry is final; else the claim itself (a compare-and-swap,
     // which returns what device memory holds) is the fresh read
     uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
@@ -197,8 +228,7 @@ __device__ __forceinline__ uint32_t store_lookup_uniform(const TV &T, const Stor
     if (lane == 0) t = atomicCAS(entry, (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
     t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
     if (t == AT_NONE) {
-        const uint32_t r = store_transition(T, G, sc, stg, errors, s, cl, lane);
-        ++*steps;
+        const uint32_t r = compute();
         if (lane == 0) g_store_release(entry, r);            // everything the transition wrote, then the entry
         return r;
     }
@@ -209,188 +239,222 @@ __device__ __forceinline__ uint32_t store_lookup_uniform(const TV &T, const Stor
     return t_final(t) ? t : (uint32_t)AT_FAIL;
 }
 
-// Grid (blocks of all rows), blocks of STORE_WAVES wavefronts.  The kernel works in TOKEN order and writes the caller's mask
-// rows itself: nothing has to be permuted afterwards.  The wavefronts of a block work on their own; what they share is
-// the block's LDS cache of table entries and (once somebody needs them) the staged grammar tables.  A wavefront
-//  (a) takes its row's record -- start state, pending bytes, token-mask-cache row numbers -- from the kernel's argument
-//      block (calls of up to STORE_MINI_ROWS rows), else from the call's upload with one 128-byte load;
-//  (b) requests the token-mask cache words (Section 4.3) of its segment of STORE_SEG_WORDS mask words, and while they are
-//      on their way walks the row's pending bytes (the tokens fed since the row's state was last known) from that state to
-//      the row's current state, then warms the LDS cache with the current state's table row;
+// The status of a call goes to the host from the block that finishes last: every block draws a ticket, which carries the block's
+// failed walks and byte steps along (bits 0-15 blocks, 16-39 failures, 40-63 steps), so that the one that draws the last ticket
+// has the sums in hand and nothing is left to be read.  A few blocks draw from one word; more blocks draw from one word per
+// sixteen of them first (additions to one word queue up at the memory channel that holds it, about 15 ns each).  The words are
+// put back to zero by whoever draws the last ticket of each: the next kernel of the engine finds them so.
+//   The words of the status go out as system-scope stores that each carry the call's number, so there is no order to keep
+// between them and no release, which would write back an L2 full of masks and logits first (the closing sequence of two
+// tickets, counters read back and a release took 3 us of a 12 us kernel at one row).
+__device__ __forceinline__ void hand_over_store(const StoreArgs &a, const uint32_t *blk) {
+    const uint32_t n_blocks = gridDim.x, lin = blockIdx.x;
+    const uint32_t n_groups = n_blocks <= 48u ? 1u : (n_blocks / 16u < (uint32_t)STORE_TICKET_GROUPS ? n_blocks / 16u : (uint32_t)STORE_TICKET_GROUPS);
+    const uint32_t g = lin % n_groups, size = n_blocks / n_groups + (g < n_blocks % n_groups ? 1u : 0u);
+    const unsigned long long err = lds_load(&blk[0]), stp = lds_load(&blk[1]);
+    unsigned long long mine = 1ull | (err < 4095ull ? err : 4095ull) << 16 | (stp < 4095ull ? stp : 4095ull) << 40;
+    unsigned long long sum = atomicAdd(&a.tickets[g], mine) + mine;
+    if ((sum & 0xFFFFull) != size) return;
+    __hip_atomic_store(&a.tickets[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n_groups > 1u) {
+        mine = (sum & ~0xFFFFull) | 1ull;
+        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS], mine) + mine;
+        if ((sum & 0xFFFFull) != n_groups) return;
+        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    auto tell = [&](uint32_t k, uint32_t value) {
+        __hip_atomic_store(&a.status[k], ((unsigned long long)a.seq << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    const uint32_t steps = (uint32_t)(sum >> 40);
+    uint32_t more = 0;
+    if (steps || a.report_size) {                            // the store has grown: how far
+        const uint32_t *ctl = a.konst->view.ctl;
+        const uint32_t c0 = g_load(&ctl[0]), c1 = g_load(&ctl[1]), c2 = g_load(&ctl[2]);
+        tell(STORE_ST_STEPS, steps);
+        tell(STORE_ST_STATES, c0);
+        tell(STORE_ST_ITEMS, c1);
+        tell(STORE_ST_REFUSED, c2);
+        more = STORE_ST_MORE;
+    }
+    tell(STORE_ST_DONE, ((uint32_t)(sum >> 16) & 0xFFFFFFu) | more);
+}
+
+// A piece of 16 bytes of a row of logits, wherever the row begins (rows of a vocabulary that is no multiple of a piece lie at
+// any multiple of an element; the memory system takes such accesses as they are).
+template <int APPLY> struct Piece { typedef u32x4 __attribute__((aligned(4))) type; };
+template <> struct Piece<2> { typedef u32x4 __attribute__((aligned(2))) type; };
+
+// Grid: the blocks of all groups, blocks of STORE_WAVES wavefronts.  A group = the rows of the call that stand in the same state:
+// they have the same mask, which is worked out once and stored to every one of them.  The kernel works in TOKEN order and writes
+// the caller's mask rows itself: nothing has to be permuted afterwards.  The wavefronts of a block work on their own; what they
+// share is the block's LDS cache of table entries and (once somebody needs them) the staged grammar tables.  A wavefront
+//  (a) takes its group's record -- start state, pending bytes, token-mask-cache row numbers, member rows -- from the kernel's
+//      argument block;
+//  (b) requests the token-mask cache words (Section 4.3) of its segment of mask words, and while they are on their way walks the
+//      group's pending bytes (the tokens fed since its state was last known) from that state to the current one, then warms the
+//      LDS cache with the current state's table row;
 //  (c) takes the undecided tokens of the segment, 64 at a time, one lane per token, through the transition table: first the
 //      LDS cache, then device memory, and an Earley byte step for what nobody has computed yet;
-//  (d) stores the segment's words of the row's mask (the next segment's cache words are requested before (c)).
+//  (d) stores the segment's words to the mask rows of the group's members and, in the APPLY builds (1 = fp32, 2 = bf16), masks the
+//      segment of their logits (Section 3.3).
+// A group served by the state cache (STORE_ROW_POOLED) takes the words from the pool in (b) and skips (c).
 // No block-wide barrier between the first one and the hand-over of the call's status at the end.
-template <int MODE>
-__global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, StoreMiniRows mini) {
+template <int MODE, int APPLY>
+__global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_kernel(StoreArgs a, StoreInline in) {
     extern __shared__ __align__(16) uint8_t smem[];
-    __shared__ uint32_t block_undecided;                     // tokens the block's wavefronts walked through the table (for the report)
-    const DeviceTables &D = a.tab;
-    const StoreView &G = a.store;
+    __shared__ uint32_t blk[2];                              // the block's failed walks and Earley byte steps
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const uint32_t W = (uint32_t)D.W, ncls = (uint32_t)D.n_cls;
-    if (tid == 0) block_undecided = 0;
-    // LDS: the cache of table entries and the staging flag come first, at offsets that do not depend on the kernel's arguments:
-    // they are cleared while the arguments are still on their way
+    // LDS: the cache of table entries, the staging flag and the verdict words come first, at offsets that do not depend on the
+    // kernel's arguments: they are cleared while the arguments are still on their way
     unsigned long long *lc = reinterpret_cast<unsigned long long *>(smem);
     uint32_t *ctl = reinterpret_cast<uint32_t *>(smem + LC_ENTRIES * 8);   // [4] state of the staged tables
-    uint8_t *const tables_at = smem + LC_ENTRIES * 8 + 32;
+    uint32_t *vbuf = reinterpret_cast<uint32_t *>(smem + LC_ENTRIES * 8 + 32) + wave * 64;   // per wavefront: verdicts of the pass's words
     for (uint32_t k = tid; k < LC_ENTRIES; k += STORE_BLOCK) lc[k] = LC_EMPTY;
+    if (tid < 2) blk[tid] = 0;
     if (tid == 0) ctl[4] = 0;
     __syncthreads();
-    // Grid (blocks of the row that has most, rows): the row's record -- with the number of blocks the row really has -- is
-    // the first thing read, from the kernel's argument block when the call has few enough rows (one read; a block beyond its
-    // row's count leaves at once).
-    const uint32_t use_mini = (uint32_t)a.store_mini, uniform_parts = (uint32_t)a.store_uniform_parts;
-    // Which row the block belongs to is known only once the rows' first blocks have been read, and the row's record only
-    // after that: so lane l asks for the first block AND the twelve words of the record of row l, all at once, and the
-    // wavefront picks its row's out of the lanes (one trip to the argument block instead of two, one after the other).
-    static_assert(STORE_MINI_ROWS == 64 && sizeof(StoreRowMini) == 48, "one short record per lane");
-    uint32_t rw[12];
-    {
-        const uint32_t *mp = reinterpret_cast<const uint32_t *>(&mini);
+    const uint32_t W = a.W, ncls = a.ncls;
+    // The record of the block's group.  Which group that is is known only once the groups' first blocks have been read, and the
+    // record only after that: so lane l asks for the first block AND the twelve words of the record of group l, all at once,
+    // and the wavefront picks its group's out of the lanes (one trip to the argument block instead of two, one after the
+    // other).  Calls of more groups say which group a block belongs to in device memory.
+    static_assert(STORE_INLINE_GROUPS == 64 && sizeof(StoreGroup) == 48, "one short record per lane");
+    uint32_t rec = 0, group, part, parts;                    // rec: lane k holds word k of the record
+    if (!a.groups) {
+        const uint4 *gp = reinterpret_cast<const uint4 *>(&in.g[lane]);
+        const uint4 r0 = gp[0], r1 = gp[1], r2 = gp[2];
+        const uint32_t fbv = in.first_block[lane], fbv2 = in.first_block[lane + 1u];
+        group = (uint32_t)__popcll(__ballot(blockIdx.x >= fbv)) - 1u;    // groups that start at or before this block (0xFFFF beyond the call's groups)
+        const uint32_t rw[12] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, r2.x, r2.y, r2.z, r2.w};
 #pragma unroll
-        for (int k = 0; k < 12; k++) rw[k] = mp[lane * 12u + (uint32_t)k];
+        for (int k = 0; k < 12; k++) asm("v_writelane_b32 %0, %1, %2" : "+v"(rec) : "s"(__builtin_amdgcn_readlane((int)rw[k], (int)group)), "n"(k));
+        const uint32_t fb0 = (uint32_t)__builtin_amdgcn_readlane((int)fbv, (int)group), fb1 = (uint32_t)__builtin_amdgcn_readlane((int)fbv2, (int)group);
+        part = blockIdx.x - fb0;
+        parts = fb1 - fb0;
+    } else {
+        const uint32_t b0 = a.block_of[2u * blockIdx.x], b1 = a.block_of[2u * blockIdx.x + 1u];
+        group = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+        parts = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 >> 16));
+        part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 & 0xFFFFu));
+        if (lane < 12u) rec = reinterpret_cast<const uint32_t *>(a.groups + group)[lane];
     }
-    const uint32_t fbv = a.store_first_block[lane], fbv2 = a.store_first_block[lane + 1u];
-    const uint32_t n_before = (uint32_t)__popcll(__ballot(blockIdx.x >= fbv));   // rows that start at or before this block (0xFFFF beyond the call's rows)
-    const uint32_t row = uniform_parts ? blockIdx.x / (uniform_parts ? uniform_parts : 1u) : n_before - 1u;
-    const uint32_t frow = row < (uint32_t)STORE_MINI_ROWS ? row : 0u;
-    StoreRowMini m;
-    {
-        uint32_t *mw = reinterpret_cast<uint32_t *>(&m);
-#pragma unroll
-        for (int k = 0; k < 12; k++) mw[k] = (uint32_t)__builtin_amdgcn_readlane((int)rw[k], (int)frow);
-    }
-    const uint32_t fb0 = (uint32_t)__builtin_amdgcn_readlane((int)fbv, (int)frow), fb1 = (uint32_t)__builtin_amdgcn_readlane((int)fbv2, (int)frow);
-    const uint32_t part = uniform_parts ? blockIdx.x - row * uniform_parts : blockIdx.x - fb0;
-    const uint32_t parts = uniform_parts ? uniform_parts : fb1 - fb0;
-    // mask words a wavefront takes per pass: the host picks fewer for rows most of whose tokens are undecided, so that a pass
-    // holds about one batch of 64 tokens and the row can be dealt to more wavefronts
-    const uint32_t sw = use_mini ? ((m.meta >> 24) & 63u) + 1u : (uint32_t)STORE_SEG_WORDS;
+    auto word = [&](uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)rec, (int)k); };
+    const uint32_t meta = word(1), flags = (meta >> 16) & 0xFFu, sw = (meta >> 24) + 1u;   // sw: mask words a wavefront takes per pass
+    const uint32_t keep_slot = word(10) >> 16, member_at = word(11) & 0xFFFFu, n_members = word(11) >> 16;
     // lanes per copy of the segment: the wavefront holds the segment's words 64 / slots times over, and each copy ORs its
-    // share of the row's cache rows (16 words: four copies; up to 64 words -- rows few of whose tokens are undecided: one)
+    // share of the group's cache rows (16 words: four copies; up to 64 words -- groups few of whose tokens are undecided: one)
     const uint32_t slots_log2 = sw <= 16u ? 4u : (sw <= 32u ? 5u : 6u), slots = 1u << slots_log2, n_grp = 64u >> slots_log2;
     const uint32_t n_seg = (W + sw - 1) / sw;
-    const uint32_t unit = part * STORE_WAVES + wave, n_units = parts * STORE_WAVES;   // a unit = one wavefront of one of the row's blocks
-    uint32_t steps = 0;
-    if (part < parts && (part * STORE_WAVES < n_seg || part == 0)) {   // uniform over the block (the row's first block reports the row's state even when there is no mask word)
-    // the row's record in the layout of StoreRow: lane k holds word k
-    uint32_t rec = 0;
-    const bool spilled = !use_mini || ((m.meta >> 16) & STORE_ROW_SPILL) != 0;
-    {
-        const uint32_t *mw = reinterpret_cast<const uint32_t *>(&m);
-        rec = lane == 0u ? m.start : rec;
-        rec = lane == 1u ? (m.meta & 0xFFu) : rec;
-        rec = lane == 3u ? ((m.meta >> 8) & 0xFFu) : rec;
-        rec = lane == 5u ? (m.meta >> 16) : rec;
-#pragma unroll
-        for (int k = 0; k < STORE_MINI_ENT; k++) rec = lane == (uint32_t)(STORE_ROW_ENT_AT + k) ? ((mw[6 + k / 2] >> (16 * (k & 1))) & 0xFFFFu) : rec;
-#pragma unroll
-        for (int k = 0; k < STORE_MINI_PEND / 4; k++) rec = lane == (uint32_t)(STORE_ROW_PEND_AT + k) ? mw[2 + k] : rec;
+    const uint32_t unit = part * STORE_WAVES + wave, n_units = parts * STORE_WAVES;   // a unit = one wavefront of one of the group's blocks
+    const bool pooled = (flags & STORE_ROW_POOLED) != 0;
+    if (unit < n_seg || unit == 0) {                         // the group's first wavefront reports its state even when there is no mask word
+    uint32_t start = word(0), n_pending = meta & 0xFFu, n_ent = (meta >> 8) & 0xFFu, pend_off = 0, ent_off = 0;
+    const bool spilled = (flags & STORE_ROW_SPILL) != 0;
+    if (spilled) {                                           // the full record in its place
+        rec = lane < sizeof(StoreRow) / 4 ? reinterpret_cast<const uint32_t *>(a.spilled + group)[lane] : 0u;
+        n_pending = word(1); pend_off = word(2); n_ent = word(3); ent_off = word(4);
     }
-    if (spilled) rec = lane < sizeof(StoreRow) / 4 ? reinterpret_cast<const uint32_t *>(a.store_rows + row)[lane] : 0u;
-    TV T;
-    uint32_t off = table_view<MODE>(D, tables_at, T);
-    const uint32_t n16 = off / 16;
-    uint8_t *l_rep = tables_at + off; off += 256;
-    uint32_t *vbuf = reinterpret_cast<uint32_t *>(tables_at + off) + wave * 64; off += STORE_WAVES * 64 * 4;   // per wavefront: verdicts of the pass's words
-    const Staging stg{ctl, tables_at, D.table_blob, n16, l_rep, D.cls_rep, ncls, a.aut_wide != 0};
-    Scratch sc;
-    sc.cap = (uint32_t)a.aut_scratch;
-    sc.w = reinterpret_cast<uint32_t *>(tables_at + off) + (size_t)wave * (2 * sc.cap + aut_hash_places(sc.cap));
-    sc.o = sc.w + sc.cap;
-    sc.h = sc.o + sc.cap;
-    if (unit < n_seg || unit == 0) {
-    auto field = [&](uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)rec, (int)k); };
-    const uint32_t flags = field(5), n_pending = field(1), pend_off = field(2), n_ent = field(3), ent_off = field(4);
-    uint32_t start = field(0);
-    if (flags & STORE_ROW_IMPORTED) start = a.store_import_root[row];
+    if (flags & STORE_ROW_IMPORTED) start = a.import_root[group];
     const bool use_cache = (flags & STORE_ROW_CACHE) != 0;
-    const bool ent_inline = n_ent <= (uint32_t)STORE_ROW_ENT, pend_inline = n_pending <= (uint32_t)(spilled ? STORE_ROW_PEND : STORE_MINI_PEND);
-    // the row number of cache row k0 + (the lane's group): the groups' numbers are read out of the record one by one (lane
-    // reads with a uniform index: no trip through LDS, which a shuffle would be) and each lane keeps its group's
-    auto entry = [&](uint32_t k0, uint32_t k) -> uint32_t {
-        uint32_t inl = 0;
-        for (uint32_t j = 0; j < n_grp; j++) {
-            const uint32_t kj = k0 + j < (uint32_t)STORE_ROW_ENT ? k0 + j : 0u;
-            const uint32_t ej = (uint32_t)__builtin_amdgcn_readlane((int)rec, (int)(STORE_ROW_ENT_AT + kj));
-            inl = (lane >> slots_log2) == j ? ej : inl;
-        }
-        return ent_inline ? inl : a.entries[ent_off + k];
+    const bool ent_inline = n_ent <= (uint32_t)(spilled ? STORE_ROW_ENT : STORE_GROUP_ENT);
+    auto entry = [&](uint32_t k) -> uint32_t {               // number of the group's cache row k, uniform (only of an inline list)
+        return spilled ? word(STORE_ROW_ENT_AT + k) : (word(6u + (k >> 1)) >> ((k & 1u) * 16u)) & 0xFFFFu;
     };
     auto pending = [&](uint32_t k) -> uint32_t {
-        return pend_inline ? (field(STORE_ROW_PEND_AT + (k >> 2)) >> ((k & 3u) * 8u)) & 0xFFu : (uint32_t)a.store_pending[pend_off + k];
+        if (spilled && n_pending > (uint32_t)STORE_ROW_PEND) return (uint32_t)a.pending[pend_off + k];
+        return (word((spilled ? (uint32_t)STORE_ROW_PEND_AT : 2u) + (k >> 2)) >> ((k & 3u) * 8u)) & 0xFFu;
     };
-    uint32_t root = AT_FAIL, undecided = 0;
-    uint32_t *errors = &a.counters[2];
-    uint32_t *out_row = a.out_mask + (size_t)(a.dst_row ? a.dst_row[row] : row) * W;
+    uint32_t root = AT_FAIL, steps = 0;
+    uint32_t *errors = &blk[0];
     const uint32_t slot16 = lane & (slots - 1u), grp = lane >> slots_log2;    // lane = (word of the segment, which copy)
-    // the token-mask cache words of segment g: every quarter of the wavefront ORs a quarter of the row's cache rows
-    auto request = [&](uint32_t g, uint32_t &v, uint32_t &c) {
-        const uint32_t w = slot16 < sw ? g * sw + slot16 : 0xFFFFFFFFu;
-        v = 0; c = use_cache ? 0u : 0xFFFFFFFFu;
-        if (use_cache && g < n_seg)
-            for (uint32_t k0 = 0; k0 < n_ent; k0 += n_grp) { // uniform trip count: the row numbers come by shuffle
-                const uint32_t k = k0 + grp;
-                const uint32_t er = entry(k0, k < n_ent ? k : 0u);
-                if (k < n_ent && w < W) { const size_t r = (size_t)er * W + w; v |= D.ci_valid_tok[r]; c |= D.ci_cd_tok[r]; }
+    // The token-mask cache words of segment g: every copy ORs its share of the group's cache rows.  The first three rounds stay
+    // as they were loaded until they are needed (an OR here would wait for them here), which covers three to twelve cache rows.
+    constexpr int RAW = 3;
+    struct Words { uint32_t v[RAW], c[RAW], v_more, c_more; };
+    auto request = [&](uint32_t g) __attribute__((always_inline)) -> Words {
+        Words x;
+        const uint32_t w = slot16 < sw && g < n_seg ? g * sw + slot16 : 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < RAW; j++) { x.v[j] = 0; x.c[j] = 0; }
+        x.v_more = 0; x.c_more = use_cache || pooled ? 0u : 0xFFFFFFFFu;
+        if (pooled) { if (w < W) x.v[0] = a.pool[(size_t)start * W + w]; return x; }
+        if (!use_cache || g >= n_seg) return x;
+        // the number of cache row k0 + (the lane's copy): the copies' numbers are read out of the record one by one (lane reads
+        // with a uniform index: no trip through LDS, which a shuffle would be) and each lane keeps its copy's
+        auto one = [&](uint32_t k0, uint32_t &v, uint32_t &c) __attribute__((always_inline)) {
+            uint32_t er = 0;
+            if (ent_inline) for (uint32_t j = 0; j < n_grp; j++) { const uint32_t ej = entry(k0 + j < n_ent ? k0 + j : 0u); er = grp == j ? ej : er; }
+            const uint32_t k = k0 + grp;
+            if (k < n_ent && w < W) {
+                if (!ent_inline) er = a.entries[ent_off + k];
+                const size_t r = (size_t)er * W + w;
+                v = a.valid[r]; c = a.cd[r];
             }
+        };
+#pragma unroll
+        for (int j = 0; j < RAW; j++) if ((uint32_t)j * n_grp < n_ent) one((uint32_t)j * n_grp, x.v[j], x.c[j]);
+        for (uint32_t k0 = (uint32_t)RAW * n_grp; k0 < n_ent; k0 += n_grp) { uint32_t v = 0, c = 0; one(k0, v, c); x.v_more |= v; x.c_more |= c; }
+        return x;
     };
     // the first look-up of the pending walk is requested ahead of the cache words: loads come back in the order they were issued
     uint32_t hop0 = AT_NONE;
-    const bool start_ok = start != 0 && start < G.cap_states;
-    if (n_pending && start_ok && pending(0) < ncls) hop0 = __hip_atomic_load(&G.trans[start * ncls + pending(0)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    uint32_t v = 0, c = 0;
-    request(unit, v, c);
-    // The logits of a segment (when the call masks them too): 16-byte pieces, the first two of every lane requested one pass
-    // ahead (those of the first segment here), so that they wait in registers when the segment's verdicts are in.
-    const uint32_t tp = a.apply_dtype ? 8u : 4u, esz = a.apply_dtype ? 2u : 4u;   // tokens per 16-byte piece, bytes per logit
-    auto logits_of = [&](uint32_t g, uint32_t &pieces, size_t &at) {
-        const uint32_t tok0 = g * sw * 32u;
-        const uint32_t n_tok = a.apply_out && g < n_seg && tok0 < (uint32_t)D.V ? (sw * 32u < (uint32_t)D.V - tok0 ? sw * 32u : (uint32_t)D.V - tok0) : 0u;
-        pieces = n_tok / tp;
-        at = ((size_t)row * (size_t)a.apply_stride + tok0) * esz;
+    const bool start_ok = start != 0 && start < a.cap_states;
+    if (n_pending && start_ok && pending(0) < ncls) hop0 = __hip_atomic_load(&a.trans[start * ncls + pending(0)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    Words wd = request(unit);
+    // the group's rows: lane l holds the l-th of the 64 in hand (a larger group goes through them 64 at a time)
+    auto members_from = [&](uint32_t m0) __attribute__((always_inline)) -> uint32_t {
+        const uint32_t k = member_at + m0 + lane;
+        return m0 + lane < n_members ? (a.members ? a.members[k] : in.member[k]) : 0u;
     };
-    auto logits_ahead = [&](uint32_t g, u32x4 (&pre)[2]) {
-        uint32_t pieces;
-        size_t at;
-        logits_of(g, pieces, at);
-        const u32x4 *src = reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.apply_logits) + at);
+    uint32_t members = members_from(0);
+    // Logits (APPLY builds): 16-byte pieces, the first two of every lane of the first member requested one pass ahead (those of
+    // the first segment here), so that they wait in registers when the segment's verdicts are in.
+    typedef typename Piece<APPLY>::type piece_t;
+    constexpr uint32_t tp = APPLY == 2 ? 8u : 4u, esz = APPLY == 2 ? 2u : 4u;   // tokens per 16-byte piece, bytes per logit
+    auto tokens_of = [&](uint32_t g) -> uint32_t {
+        const uint32_t tok0 = g * sw * 32u;
+        return g < n_seg && tok0 < a.V ? (sw * 32u < a.V - tok0 ? sw * 32u : a.V - tok0) : 0u;
+    };
+    auto logits_at = [&](uint32_t row, uint32_t g) -> size_t { return ((size_t)row * (size_t)a.stride + g * sw * 32u) * esz; };
+    auto logits_ahead = [&](uint32_t row, uint32_t g, u32x4 (&pre)[2]) __attribute__((always_inline)) {
+        const uint32_t pieces = tokens_of(g) / tp;
+        const piece_t *src = reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + logits_at(row, g));
 #pragma unroll
         for (int u = 0; u < 2; u++) { pre[u] = u32x4{0, 0, 0, 0}; if ((uint32_t)u * 64u + lane < pieces) pre[u] = __builtin_nontemporal_load(src + (uint32_t)u * 64u + lane); }
     };
     u32x4 l_pre[2];
-    logits_ahead(unit, l_pre);
-    auto find_root = [&]() {
-        // ---- the row's current state: walk the bytes fed since `start` was its state (the loads above are in flight) ----
+    if (APPLY) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members), unit, l_pre);
+    auto transition = [&](uint32_t s, uint32_t cl) __attribute__((always_inline)) -> uint32_t {
+        steps++;
+        return store_transition_call<MODE>(a.konst, (LdsBytes *)smem, (uint32_t)a.scratch | (a.wide ? SCRATCH_WIDE : 0u) | wave << 24, errors, s, cl);
+    };
+    auto find_root = [&]() __attribute__((always_inline)) {
+        // ---- the group's current state: walk the bytes fed since `start` was its state (the loads above are in flight) ----
         uint32_t s = start;
-        bool bad = s == 0 || (s >= G.cap_states && s != AT_SINK);
+        bool bad = s == 0 || (s >= a.cap_states && s != AT_SINK);
         for (uint32_t k = 0; k < n_pending && !bad; k++) {
             const uint32_t cl = pending(k);
             if (s == AT_SINK || cl >= ncls) { bad = true; break; }
             uint32_t t = k == 0 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)hop0) : (uint32_t)AT_NONE;
-            if (!t_final(t)) t = store_lookup_uniform(T, G, sc, stg, errors, &steps, s, cl, lane);
+            if (!t_final(t)) t = store_lookup_uniform(a.trans + (size_t)s * ncls + cl, lane, [&]() { return transition(s, cl); });
             if (t == AT_DEAD || t == AT_FAIL) { bad = true; break; }   // the host accepted these bytes: a dead end here is an error
             s = t;
         }
         if (bad) { s = AT_FAIL; if (lane == 0 && unit == 0) atomicAdd(errors, 1u); }
-        // The host reads this word once it has seen the call's status.  It is written through to device memory here (no fence:
-        // a release would write the whole L2 back, and every wavefront of the chip would wait behind that), long before this
-        // block draws its ticket; the block that hands the status over reads it back and passes it on.
-        if (unit == 0 && lane == 0) __hip_atomic_store(&a.store_row_dev[row], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (unit == 0 && lane == 0 && (flags & STORE_ROW_REPORT))
+            __hip_atomic_store(&a.status[STORE_ST_ROW + group], ((unsigned long long)a.seq << 32) | s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         root = s;
         if (root < AT_FAIL) {
             // Warm the block's cache with the current state's row of the table, and with the rows of the states one byte
             // away (every wavefront of the block takes its share of them): a row is read by neighbouring lanes, once per
             // block.  Left to the walk below, thousands of wavefronts would ask for the same few lines at the same
             // moment, lane by lane, and queue up at the one memory channel that holds them (8 us and more).
-            auto warm_row = [&](uint32_t st) {
+            auto warm_row = [&](uint32_t st) __attribute__((always_inline)) {
                 for (uint32_t c0 = 0; c0 < ncls; c0 += 64) {
                     const uint32_t cl = c0 + lane;
                     uint32_t t = AT_NONE;
                     const uint32_t key = st * ncls + cl;
-                    if (cl < ncls) t = __hip_atomic_load(&G.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    if (cl < ncls) t = __hip_atomic_load(&a.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                     if (cl < ncls && t_final(t) && t != AT_FAIL)
                         __hip_atomic_store(&lc[(key * 0x9E3779B1u) >> (32 - LC_BITS)], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     // the states this row leads to, each once: the wavefront's share of them is warmed in turn
@@ -415,7 +479,7 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
 #pragma unroll
                         for (int k = 0; k < SHARE; k++) {
                             t2[k] = AT_NONE;
-                            if ((uint32_t)k < n_mine && lane < ncls) t2[k] = __hip_atomic_load(&G.trans[mine[k] * ncls + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            if ((uint32_t)k < n_mine && lane < ncls) t2[k] = __hip_atomic_load(&a.trans[mine[k] * ncls + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                         }
 #pragma unroll
                         for (int k = 0; k < SHARE; k++) {
@@ -430,9 +494,9 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
         }
     };
     // One token of a batch: where its verdict goes, and its string (requested here, used a batch later).
-    struct Tok { uint32_t slot, bit, len, token; Str16 c16; bool live; };
+    struct Tok { uint32_t slot, bit, token; Str16 c16; bool live; };
     uint32_t incl = 0, want = 0;                             // of the segment in hand: running bit counts of its words, undecided bits
-    auto fetch = [&](uint32_t g, uint32_t b0, uint32_t total) -> Tok {
+    auto fetch = [&](uint32_t g, uint32_t b0, uint32_t total) __attribute__((always_inline)) -> Tok {
         Tok k;
         const uint32_t i = b0 + lane;
         k.live = i < total;
@@ -448,35 +512,34 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
             if (n >= low) { n -= low; k.bit += (uint32_t)sh; }
         }
         k.token = (g * sw + k.slot) * 32u + k.bit;
-        k.len = 0;
-        k.c16 = Str16{{0, 0, 0, 0}};
-        if (k.live) { k.len = D.tok_len[k.token]; k.c16 = D.tok16[k.token]; }   // requested here, looked at a batch later: nothing below waits for them
+        k.c16 = Str16{{TOK_END, 0, 0, 0}};
+        if (k.live) k.c16 = a.tok16[k.token];                // requested here, looked at a batch later: nothing below waits for it
         return k;
     };
-    bool root_ok = false;
-    // the first pass runs even for a wavefront without a segment (the row's first wavefront reports the row's state)
+    bool root_ok = pooled;
+    // the first pass runs even for a wavefront without a segment (the group's first wavefront reports its state)
     for (uint32_t g = unit, first = 1; first || g < n_seg; g += n_units, first = 0) {
         const uint32_t w = slot16 < sw && g < n_seg ? g * sw + slot16 : 0xFFFFFFFFu;
-        uint32_t vn = 0, cn = 0;
-        request(g + n_units, vn, cn);                        // the next segment's words travel while this one's tokens are checked
+        uint32_t v = wd.v[0] | wd.v_more, c = wd.c[0] | wd.c_more;
+#pragma unroll
+        for (int j = 1; j < RAW; j++) { v |= wd.v[j]; c |= wd.c[j]; }
+        wd = request(g + n_units);                           // the next segment's words travel while this one's tokens are checked
         u32x4 l_nxt[2];
-        logits_ahead(g + n_units, l_nxt);                    // and so do its logits
-        uint32_t pieces;
-        size_t l_at;
-        logits_of(g, pieces, l_at);
-        const u32x4 *l_src = reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(a.apply_logits) + l_at);
-        if (slots_log2 <= 4u) { v |= __shfl_xor(v, 16); c |= __shfl_xor(c, 16); }
-        if (slots_log2 <= 5u) { v |= __shfl_xor(v, 32); c |= __shfl_xor(c, 32); }
+        if (APPLY) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members), g + n_units, l_nxt);   // and so do its first logits
+        if (!pooled) {
+            if (slots_log2 <= 4u) { v |= __shfl_xor(v, 16); c |= __shfl_xor(c, 16); }
+            if (slots_log2 <= 5u) { v |= __shfl_xor(v, 32); c |= __shfl_xor(c, 32); }
+        }
         want = c & ~v;
         {
             const uint32_t t0 = w * 32u;
-            if (w >= W || t0 >= (uint32_t)D.V) want = 0;
-            else if ((uint32_t)D.V - t0 < 32u) want &= (1u << ((uint32_t)D.V - t0)) - 1u;
+            if (w >= W || t0 >= a.V) want = 0;
+            else if (a.V - t0 < 32u) want &= (1u << (a.V - t0)) - 1u;
         }
         // ---- one lane per undecided token through the table.  The undecided tokens of the segment's words are numbered
         // through (prefix sum of the words' bit counts) and taken 64 at a time, so that a batch is full whatever the
         // pattern of the bits; verdicts go back to their words through LDS.  The strings of a batch are requested one
-        // batch ahead; those of the first batch travel while the row's current state is worked out ----
+        // batch ahead; those of the first batch travel while the group's current state is worked out ----
         incl = (uint32_t)__popc(want);                       // every copy holds the same words
         // running sums over each copy's lanes by data-parallel-primitive moves (a row of 16 lanes shifts by 1, 2, 4, 8 with
         // zeros coming in; then the last lane of a row is broadcast into the next row, of the lower half into the upper half):
@@ -488,24 +551,14 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
         if (slots_log2 >= 5u) incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
         if (slots_log2 >= 6u) incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
         uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)(slots - 1u));
-        Tok nxt = fetch(g, 0, total);
-        if (first) { find_root(); root_ok = root < AT_FAIL; }   // AT_SINK: nothing can follow; AT_FAIL: the call fails
+        Tok nxt;
+        if (total) nxt = fetch(g, 0, total);
+        if (first && !pooled) { find_root(); root_ok = root < AT_FAIL; }   // AT_SINK: nothing can follow; AT_FAIL: the call fails
         if (!root_ok) { total = 0; v = 0; }                  // no token can follow a finished sentence
-        undecided += total;
         if (lane < slots) lds_store(&vbuf[lane], 0u);
         for (uint32_t b0 = 0; b0 < total; b0 += 64) {
             const Tok cur = nxt;
             if (b0 + 64 < total) nxt = fetch(g, b0 + 64, total);
-            const uint32_t slot = cur.slot, bit = cur.bit;
-            uint32_t soff = 0, len = cur.len;
-            const Str16 c16 = cur.c16;
-            const bool long_one = cur.live & (len == (uint32_t)TOK_LEN_LONG);   // longer than the 16 classes at hand: the rest is with the string's rank
-            if (__ballot(long_one)) {
-                if (long_one) {
-                    const uint32_t rank = D.rank_of[cur.token];
-                    soff = D.str_off[rank]; len = D.str_off[rank + 1] - soff;
-                }
-            }
             // Where a lane stands with its string, in ONE register: the loop below carries no per-lane truth value from one
             // round to the next.  (Carried truth values live in scalar register pairs, and every one of them costs three
             // scalar instructions per round to merge; the four vector units of a compute unit share one scalar unit, which
@@ -513,7 +566,7 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
             enum : uint32_t { PH_GO = 0,      // takes a step in the next round
                               PH_NONE = 1,    // waits: nobody has computed the entry it needs
                               PH_BUSY = 2,    // waits: somebody is computing it
-                              PH_FAR = 3,     // beyond the 16 bytes at hand: the next byte has to be fetched
+                              PH_FAR = 3,     // at the end of the bytes at hand: the next fifteen have to be fetched
                               PH_OK = 4,      // done: the whole string went through (codes from here on: done)
                               PH_DEAD = 5,    // done: the string cannot follow
                               PH_FAIL = 6 };  // done: no room, or a wait that did not end
@@ -521,15 +574,10 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
             // dead, nothing can follow (the one string that ends right here is picked out below), being computed, no room
             constexpr uint32_t PH_OF_SPECIAL = (PH_NONE << 0) | (PH_DEAD << 4) | (PH_DEAD << 8) | (PH_BUSY << 12) | (PH_FAIL << 16);
             static_assert(AT_NONE == ~0u && AT_DEAD == ~1u && AT_SINK == ~2u && AT_BUSY == ~3u && AT_FAIL == ~4u, "the nibbles above");
-            uint32_t ph = cur.live && len > 0 ? (uint32_t)PH_GO : (uint32_t)PH_DEAD;
-            uint32_t s = root, pos = 0, spins = 0, rounds = 0;
-            uint32_t c_far = 0;                              // class of the byte at `pos` of a string beyond the 16 at hand (fetched while the lane is PH_FAR)
-            const uint32_t w0 = c16.w[0], w1 = c16.w[1], w2 = c16.w[2], w3 = c16.w[3];
-            auto class_at = [&](uint32_t at) -> uint32_t {  // byte `at` of the sixteen at hand: the half that holds it, then one byte permute
-                const bool upper = (at & 8u) != 0;
-                const uint32_t c_near = __builtin_amdgcn_perm(upper ? w3 : w1, upper ? w2 : w0, (at & 7u) | 0x0C0C0C00u);
-                return at >= 16u ? c_far : c_near;
-            };
+            uint32_t w0 = cur.c16.w[0], w1 = cur.c16.w[1], w2 = cur.c16.w[2], w3 = cur.c16.w[3];
+            uint32_t cl = w0 & 0xFFu;                        // the class the lane's next step takes
+            uint32_t ph = cur.live && cl != TOK_END ? (uint32_t)PH_GO : (uint32_t)PH_DEAD;   // an empty token is never allowed
+            uint32_t s = root, pos = 0, spins = 0, rounds = 0, passed = 0;   // passed: classes of the string before the ones at hand
             for (;;) {
                 // Every lane follows its own string as far as the table goes: all lanes that can move take a step together,
                 // written without branches on per-lane conditions (selects; an entry that is not in the block's LDS cache
@@ -540,8 +588,7 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
                 for (;;) {
                     const bool go = ph == PH_GO;
                     if (!__builtin_amdgcn_ballot_w64(go)) break;
-                    const uint32_t c_new = class_at(pos);
-                    const uint32_t key = __umul24(s, ncls) + c_new;          // a state has at most 18 bits, a class 8
+                    const uint32_t key = __umul24(s, ncls) + cl;             // a state has at most 18 bits, a class 8
                     const uint32_t lslot = go ? (key * 0x9E3779B1u) >> (32 - LC_BITS) : 0u;
                     const unsigned long long e = __hip_atomic_load(&lc[lslot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     const bool hit = (uint32_t)(e >> 32) == key;
@@ -551,33 +598,41 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
                         if (miss) {
                             // through the caches first; an entry seen unfinished is asked of device memory only on the
                             // way back from the claim below, which is itself a fresh read of the entry it claims
-                            t_new = __hip_atomic_load(&G.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                            if (!t_final(t_new) && rounds) t_new = g_load(&G.trans[key]);
+                            t_new = __hip_atomic_load(&a.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            if (!t_final(t_new) && rounds) t_new = g_load(&a.trans[key]);
                             if (t_final(t_new) && t_new != AT_FAIL) __hip_atomic_store(&lc[lslot], ((unsigned long long)key << 32) | t_new, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         }
                     }
+                    const uint32_t pos1 = pos + 1u;          // at most 15: the sixteenth byte at hand is a mark, never a class
+                    const bool upper = (pos1 & 8u) != 0;
+                    const uint32_t c1 = __builtin_amdgcn_perm(upper ? w3 : w1, upper ? w2 : w0, (pos1 & 7u) | 0x0C0C0C00u);   // the class behind it, or a mark
                     const bool state = t_new < AT_FAIL;      // a state: the lane moves on
-                    const uint32_t pos1 = pos + 1u;
-                    const bool ends = pos1 == len;
+                    const bool ends = c1 == TOK_END;
                     uint32_t nx = __builtin_amdgcn_ubfe(PH_OF_SPECIAL, (~t_new) << 2, 4u);
-                    nx = state ? (pos1 >= 16u ? (uint32_t)PH_FAR : (uint32_t)PH_GO) : nx;
+                    nx = state ? (c1 == TOK_MORE ? (uint32_t)PH_FAR : (uint32_t)PH_GO) : nx;
                     nx = ((state | (t_new == AT_SINK)) & ends) ? (uint32_t)PH_OK : nx;   // (& and | on purpose: && and || would ask for a branch apiece)
                     const bool adv = go & state;
                     s = adv ? t_new : s;
                     pos = adv ? pos1 : pos;
+                    cl = adv ? c1 : cl;
                     ph = go ? nx : ph;
                 }
                 if (!__builtin_amdgcn_ballot_w64(ph < PH_OK)) break;
-                {
-                    const bool fetch_far = ph == PH_FAR;
-                    if (__builtin_amdgcn_ballot_w64(fetch_far)) {   // strings beyond 16 bytes: the next byte's class, then round again
-                        if (fetch_far) {
-                            c_far = D.str_cls[soff + pos];
-                            asm volatile("" : "+v"(c_far));  // waited for here, not at the top of the loop above
-                            ph = PH_GO;
-                        }
-                        continue;
+                if (__builtin_amdgcn_ballot_w64(ph == PH_FAR)) {   // strings beyond the bytes at hand: the next fifteen classes, then round again
+                    if (ph == PH_FAR) {
+                        const DeviceTables &D = a.konst->tab;
+                        const uint32_t rank = D.rank_of[cur.token], at = D.str_off[rank], len = D.str_off[rank + 1] - at;
+                        passed += TOK_AT_HAND;
+                        const uint32_t left = len - passed, n = left < TOK_AT_HAND ? left : TOK_AT_HAND;   // left >= 1: the mark says that the string goes on
+                        uint32_t nw[4] = {0, 0, 0, 0};
+                        for (uint32_t k = 0; k < n; k++) { const uint32_t b = (uint32_t)D.str_cls[at + passed + k] << ((k & 3u) * 8u); nw[0] |= k < 4u ? b : 0u; nw[1] |= (k >> 2) == 1u ? b : 0u; nw[2] |= (k >> 2) == 2u ? b : 0u; nw[3] |= (k >> 2) == 3u ? b : 0u; }
+                        const uint32_t mark = (left > TOK_AT_HAND ? TOK_MORE : TOK_END) << ((n & 3u) * 8u);
+                        w0 = nw[0] | (n < 4u ? mark : 0u); w1 = nw[1] | ((n >> 2) == 1u ? mark : 0u); w2 = nw[2] | ((n >> 2) == 2u ? mark : 0u); w3 = nw[3] | ((n >> 2) == 3u ? mark : 0u);
+                        asm volatile("" : "+v"(w0), "+v"(w1), "+v"(w2), "+v"(w3));   // waited for here, not at the top of the loop above
+                        cl = w0 & 0xFFu; pos = 0;
+                        ph = PH_GO;
                     }
+                    continue;
                 }
                 rounds++;
                 // one of the waiting lanes' transitions is claimed and computed here; the other lanes look again afterwards
@@ -585,14 +640,13 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
                 bool progress = false;
                 if (missing) {
                     const int l = __ffsll((long long)missing) - 1;
-                    const uint32_t rs = (uint32_t)__builtin_amdgcn_readlane((int)s, l), rc = (uint32_t)__builtin_amdgcn_readlane((int)class_at(pos), l);
+                    const uint32_t rs = (uint32_t)__builtin_amdgcn_readlane((int)s, l), rc = (uint32_t)__builtin_amdgcn_readlane((int)cl, l);
                     uint32_t old = 0;
-                    if (lane == 0) old = atomicCAS(&G.trans[rs * ncls + rc], (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
+                    if (lane == 0) old = atomicCAS(&a.trans[rs * ncls + rc], (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
                     old = (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
                     if (old == AT_NONE) {
-                        const uint32_t r = store_transition(T, G, sc, stg, errors, rs, rc, lane);
-                        steps++;
-                        if (lane == 0) g_store_release(&G.trans[rs * ncls + rc], r);   // everything the transition wrote, then the entry
+                        const uint32_t r = transition(rs, rc);
+                        if (lane == 0) g_store_release(&a.trans[rs * ncls + rc], r);   // everything the transition wrote, then the entry
                         progress = true;
                     } else progress = old != AT_BUSY;        // somebody else has it, or has finished it meanwhile
                 }
@@ -607,55 +661,79 @@ __global__ __launch_bounds__(STORE_BLOCK) void mask_store_kernel(MaskArgs a, Sto
                 // every round -- for the strings, words and logits requested ahead as well.
                 __builtin_amdgcn_s_waitcnt(0x0F70);
             }
-            if (ph == PH_OK) atomicOr(&vbuf[slot], 1u << bit);
+            if (ph == PH_OK) atomicOr(&vbuf[cur.slot], 1u << cur.bit);
             const unsigned long long fm = __builtin_amdgcn_ballot_w64(ph == PH_FAIL);    // no room in the scratch or the store, or a wait that did not end
             if (lane == 0 && fm) atomicAdd(errors, (uint32_t)__popcll(fm));
         }
         if (total) v |= lds_load(&vbuf[slot16]);             // LDS serves one wavefront's accesses in issue order
-        if (lane < slots && w < W) out_row[w] = v;
-        if (a.apply_out && g < n_seg) {
-            // Logit masking (Section 3.3) of the segment's tokens, right here: 16-byte pieces, consecutive lanes on consecutive
-            // pieces, the mask word from the lane that holds it.  Allowed logits are copied bit for bit, the others become -inf.
-            uint8_t *dst = reinterpret_cast<uint8_t *>(a.apply_out) + l_at;
-            auto mask_piece = [&](uint32_t p, u32x4 x) {     // all lanes call it together: the shuffle is for all of them
-                const uint32_t t_in = p * tp;
-                const uint32_t mb = (uint32_t)__shfl((int)v, (int)((t_in >> 5) & 63u)) >> (t_in & 31u);
-                if (p < pieces) {
-                    if (a.apply_dtype) {
+        // ---- the segment's words go to every member's mask row (and to the state cache) ----
+        for (uint32_t m0 = 0; m0 < n_members; m0 += 64) {
+            if (n_members > 64u) members = members_from(m0);
+            const uint32_t n = n_members - m0 < 64u ? n_members - m0 : 64u;
+            for (uint32_t k = 0; k < n; k++) {
+                uint32_t *dst = a.out_mask + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)members, (int)k) * W + w;
+                if (lane < slots && w < W) {
+                    if (a.complete) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    else *dst = v;
+                }
+            }
+            if (APPLY) {
+                // Logit masking (Section 3.3) of the segment's tokens, right here: 16-byte pieces, consecutive lanes on consecutive
+                // pieces, the mask word from the lane that holds it.  Allowed logits are copied bit for bit, the others become -inf.
+                const uint32_t n_tok = tokens_of(g), pieces = n_tok / tp, tail = n_tok % tp;
+                auto masked = [&](u32x4 x, uint32_t mb) -> u32x4 {
+                    if (APPLY == 2) {
 #pragma unroll
-                        for (int k = 0; k < 4; k++) {
-                            uint32_t e = x[k];
-                            if (!((mb >> (2 * k)) & 1u)) e = (e & 0xFFFF0000u) | 0xFF80u;
-                            if (!((mb >> (2 * k + 1)) & 1u)) e = (e & 0x0000FFFFu) | 0xFF800000u;
-                            x[k] = e;
+                        for (int j = 0; j < 4; j++) {
+                            uint32_t e = x[j];
+                            if (!((mb >> (2 * j)) & 1u)) e = (e & 0xFFFF0000u) | 0xFF80u;
+                            if (!((mb >> (2 * j + 1)) & 1u)) e = (e & 0x0000FFFFu) | 0xFF800000u;
+                            x[j] = e;
                         }
                     } else {
 #pragma unroll
-                        for (int k = 0; k < 4; k++) if (!((mb >> k) & 1u)) x[k] = 0xFF800000u;
+                        for (int j = 0; j < 4; j++) if (!((mb >> j) & 1u)) x[j] = 0xFF800000u;
                     }
-                    __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(dst) + p);
+                    return x;
+                };
+                auto bits_at = [&](uint32_t t) -> uint32_t { return (uint32_t)__shfl((int)v, (int)((t >> 5) & 63u)) >> (t & 31u); };   // all lanes call it together
+                for (uint32_t k = 0; k < n; k++) {
+                    const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)members, (int)k);
+                    const size_t at = logits_at(row, g);
+                    const piece_t *src = reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + at);
+                    piece_t *dst = reinterpret_cast<piece_t *>(reinterpret_cast<uint8_t *>(a.out) + at);
+                    auto put = [&](uint32_t p, u32x4 x) { const uint32_t mb = bits_at(p * tp); if (p < pieces) __builtin_nontemporal_store(masked(x, mb), dst + p); };
+                    u32x4 cur[2] = {l_pre[0], l_pre[1]};
+                    if (k + 1 < n) logits_ahead((uint32_t)__builtin_amdgcn_readlane((int)members, (int)((k + 1) & 63u)), g, l_pre);   // the next member's first pieces
+                    else if (m0 + 64 < n_members) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members_from(m0 + 64)), g, l_pre);
+                    put(lane, cur[0]);
+                    if (pieces > 64u) put(64u + lane, cur[1]);
+                    for (uint32_t p0 = 128; p0 < pieces; p0 += 256) {   // what was not requested ahead: four pieces per lane in flight
+                        u32x4 x[4];
+#pragma unroll
+                        for (int u = 0; u < 4; u++) { const uint32_t p = p0 + (uint32_t)u * 64u + lane; x[u] = u32x4{0, 0, 0, 0}; if (p < pieces) x[u] = __builtin_nontemporal_load(src + p); }
+#pragma unroll
+                        for (int u = 0; u < 4; u++) if (p0 + (uint32_t)u * 64u < pieces) put(p0 + (uint32_t)u * 64u + lane, x[u]);
+                    }
+                    if (tail) {                              // the last tokens of a vocabulary that is no multiple of a piece
+                        const uint32_t t = pieces * tp + lane, keep = bits_at(t) & 1u;
+                        if (lane < tail) {
+                            if (APPLY == 2) reinterpret_cast<uint16_t *>(dst)[t] = keep ? reinterpret_cast<const uint16_t *>(src)[t] : (uint16_t)0xFF80u;
+                            else reinterpret_cast<uint32_t *>(dst)[t] = keep ? reinterpret_cast<const uint32_t *>(src)[t] : 0xFF800000u;
+                        }
+                    }
                 }
-            };
-            mask_piece(lane, l_pre[0]);
-            if (pieces > 64u) mask_piece(64u + lane, l_pre[1]);
-            for (uint32_t p0 = 128; p0 < pieces; p0 += 256) {   // what was not requested ahead: four pieces per lane in flight
-                u32x4 x[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) { const uint32_t p = p0 + (uint32_t)u * 64u + lane; x[u] = u32x4{0, 0, 0, 0}; if (p < pieces) x[u] = __builtin_nontemporal_load(l_src + p); }
-#pragma unroll
-                for (int u = 0; u < 4; u++) if (p0 + (uint32_t)u * 64u < pieces) mask_piece(p0 + (uint32_t)u * 64u + lane, x[u]);
             }
         }
-        v = vn; c = cn;
-        l_pre[0] = l_nxt[0]; l_pre[1] = l_nxt[1];
+        if ((flags & STORE_ROW_KEEP) && lane < slots && w < W) a.pool[(size_t)keep_slot * W + w] = v;
+        if (APPLY) { l_pre[0] = l_nxt[0]; l_pre[1] = l_nxt[1]; }
+        if (n_members > 64u) members = members_from(0);
     }
-    if (lane == 0 && steps) atomicAdd(&a.counters[3], steps);
-    if (lane == 0 && undecided) atomicAdd(&block_undecided, undecided);   // LDS: the block's sum travels with its ticket
+    if (lane == 0 && steps) atomicAdd(&blk[1], steps);
+    if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
     }
-    }
-    // the call's status goes to the host from the block that finishes last (a failed look-up counts up to the end)
     __syncthreads();
-    hand_over(a, blockIdx.x, gridDim.x, true, block_undecided, !a.handoff_in_store);
+    if (tid == 0) hand_over_store(a, blk);
 }
 
 // Clear the store: every transition unknown, every header unpublished, the hash table empty; then the
@@ -672,66 +750,69 @@ __global__ __launch_bounds__(256) void store_clear_kernel(StoreView G, uint32_t 
 // Bring rows whose state the store does not know (after the store was cleared, or after more bytes than
 // a call carries) in from their host charts: every set of the packed chart becomes a state of its own,
 // origins renamed from set indices to the new names.  One block per such row.
-__global__ __launch_bounds__(256) void store_import_kernel(MaskArgs a, const uint32_t *import_rows, uint32_t n_import) {
-    const StoreView &G = a.store;
+__global__ __launch_bounds__(256) void store_import_kernel(StoreView G, const RowChart *charts, const uint32_t *set_off, const Item *items, const uint32_t *group, uint32_t *import_root) {
     __shared__ uint32_t base[2];
-    const uint32_t r = import_rows[blockIdx.x];
-    const RowChart rc = a.rows[blockIdx.x];
+    const uint32_t g = group[blockIdx.x];
+    const RowChart rc = charts[blockIdx.x];
     if (threadIdx.x == 0) { base[0] = atomicAdd(&G.ctl[0], rc.n_sets); base[1] = atomicAdd(&G.ctl[1], rc.n_items); }
     __syncthreads();
     const uint32_t id0 = base[0], at0 = base[1];
     if (id0 > G.cap_states - rc.n_sets || id0 + rc.n_sets > G.cap_states || at0 > G.cap_items - rc.n_items || rc.n_items > G.cap_items) {
-        if (threadIdx.x == 0) { atomicAdd(&G.ctl[2], 1u); atomicAdd(&a.counters[2], 1u); a.store_import_root[r] = AT_FAIL; }
+        if (threadIdx.x == 0) { atomicAdd(&G.ctl[2], 1u); import_root[g] = AT_FAIL; }   // the mask kernel, which starts from there, fails the call
         return;
     }
-    const uint32_t *so = a.set_off + rc.set_base;
-    const uint2 *it = reinterpret_cast<const uint2 *>(a.items) + rc.item_base;
+    const uint32_t *so = set_off + rc.set_base;
+    const uint2 *it = reinterpret_cast<const uint2 *>(items) + rc.item_base;
     for (uint32_t k = threadIdx.x; k < rc.n_items; k += 256) { const uint2 x = it[k]; G.arena[at0 + k] = make_uint2(x.x, id0 + x.y); }
     for (uint32_t k = threadIdx.x; k < rc.n_sets; k += 256) G.hdr[id0 + k] = make_uint2(at0 + so[k], so[k + 1] - so[k]);
-    if (threadIdx.x == 0) a.store_import_root[r] = id0 + rc.n_sets - 1;
-    (void)n_import;
+    if (threadIdx.x == 0) import_root[g] = id0 + rc.n_sets - 1;
 }
 
 }  // namespace
 
+// the build of the kernel for a table mode and a kind of logits
+typedef void (*StoreKernel)(StoreArgs, StoreInline);
+static StoreKernel store_kernel(int mode, int apply) {
+    static const StoreKernel k[3][3] = {{mask_store_kernel<0, 0>, mask_store_kernel<0, 1>, mask_store_kernel<0, 2>},
+                                        {mask_store_kernel<1, 0>, mask_store_kernel<1, 1>, mask_store_kernel<1, 2>},
+                                        {mask_store_kernel<2, 0>, mask_store_kernel<2, 1>, mask_store_kernel<2, 2>}};
+    return k[mode < 0 ? 0 : (mode > 2 ? 2 : mode)][apply];
+}
+
 hipError_t prepare_store_kernels() {
-    const int max_lds = STORE_LDS_MAX;
-    hipError_t e;
-#define SET_ATTR(k) if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds)) != hipSuccess) return e
-    SET_ATTR(mask_store_kernel<0>); SET_ATTR(mask_store_kernel<1>); SET_ATTR(mask_store_kernel<2>);
-#undef SET_ATTR
+    for (int m = 0; m < 3; m++)
+        for (int p = 0; p < 3; p++) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(store_kernel(m, p)), hipFuncAttributeMaxDynamicSharedMemorySize, STORE_LDS_MAX);
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
 }
 
 uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch) {
-    return table_bytes(t, mode) + 256 + LC_ENTRIES * 8 + 32 + STORE_WAVES * 64 * 4 +
+    return TABLES_AT + table_bytes(t, mode) + 256 +
            STORE_WAVES * ((uint32_t)scratch * 8 + aut_hash_places((uint32_t)scratch) * 4);
 }
 
-// Blocks of the kernel one compute unit holds at once (registers and the LDS the call asks for decide); asked of the runtime once
-// per LDS size.
+// Blocks of the kernel one compute unit holds at once (registers and the LDS the call asks for decide; the builds differ little:
+// the one with the most registers is asked about); asked of the runtime once per LDS size.
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch) {
     static thread_local uint32_t known_lds[3] = {0, 0, 0};
     static thread_local int known[3] = {0, 0, 0};
     const uint32_t lds = store_lds_bytes(t, mode, scratch);
     const int m = mode < 0 ? 0 : (mode > 2 ? 2 : mode);
     if (known[m] && known_lds[m] == lds) return known[m];
-    int n = 0;
-    hipError_t e;
-    if (m == 0) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, mask_store_kernel<0>, STORE_BLOCK, lds);
-    else if (m == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, mask_store_kernel<1>, STORE_BLOCK, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, mask_store_kernel<2>, STORE_BLOCK, lds);
-    if (e != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
-    known[m] = n; known_lds[m] = lds;
-    return n;
+    int least = 1 << 30;
+    for (int p = 0; p < 3; p++) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(store_kernel(m, p)), STORE_BLOCK, lds) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+        least = n < least ? n : least;
+    }
+    known[m] = least; known_lds[m] = lds;
+    return least;
 }
 
-hipError_t launch_mask_store(const MaskArgs &a, const StoreMiniRows &mini, hipStream_t s) {
-    const uint32_t lds = store_lds_bytes(a.tab, a.mode, a.aut_scratch);
-    dim3 grid(a.store_uniform_parts ? (uint32_t)a.store_uniform_parts * (uint32_t)a.batch : (uint32_t)a.store_first_block[a.batch]);
-    if (a.mode == 0) hipLaunchKernelGGL(mask_store_kernel<0>, grid, dim3(STORE_BLOCK), lds, s, a, mini);
-    else if (a.mode == 1) hipLaunchKernelGGL(mask_store_kernel<1>, grid, dim3(STORE_BLOCK), lds, s, a, mini);
-    else hipLaunchKernelGGL(mask_store_kernel<2>, grid, dim3(STORE_BLOCK), lds, s, a, mini);
+hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s) {
+    hipLaunchKernelGGL(store_kernel((int)a.tab_mode, a.dtype), dim3(a.n_blocks), dim3(STORE_BLOCK), lds_bytes, s, a, in);
     return hipGetLastError();
 }
 
@@ -740,9 +821,10 @@ hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *roo
     return hipGetLastError();
 }
 
-hipError_t launch_store_import(const MaskArgs &a, const uint32_t *import_rows, uint32_t n_import, hipStream_t s) {
-    if (n_import == 0) return hipSuccess;
-    hipLaunchKernelGGL(store_import_kernel, dim3(n_import), dim3(256), 0, s, a, import_rows, n_import);
+hipError_t launch_store_import(const StoreView &G, const RowChart *charts, const uint32_t *set_off, const Item *items, const uint32_t *group,
+                               uint32_t n, uint32_t *import_root, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(store_import_kernel, dim3(n), dim3(256), 0, s, G, charts, set_off, items, group, import_root);
     return hipGetLastError();
 }
 
