@@ -88,10 +88,9 @@ typedef struct {
                               byte once a transition is known; results are those of the plain advance) -- with or without a device. */
     int32_t precompute_states; /* walk_mode 2: how much of the persistent automaton is built before the first decode step.  When the
                               engine is compiled, and again whenever zf_engine_clear_state_cache empties it, the automaton is
-                              explored breadth first from the state of the empty prefix, one byte of every byte class at a time,
-                              and the mask at every state found is computed once (a mask call computes every transition its
-                              walk of the vocabulary meets), until no new state turns up, this many states have been visited,
-                              a second has passed, or the store is a quarter full.  A grammar without recursion has a finite automaton and gets
+                              explored breadth first from the state of the empty prefix, one byte of every byte class at a time
+                              (on the host; the device's is filled with the result), until no new state turns up, this many
+                              states have been found, a second has passed, or a quarter of the store is taken.  A grammar without recursion has a finite automaton and gets
                               it whole, the way engines for regular constraints build theirs at compile time (a decode loop then
                               computes no transition at all); of a recursive grammar the states nearest the start are built.  Masks are the same with or without.
                               0 = default (65536 states), -1 = off */
@@ -220,7 +219,7 @@ int zf_last_mask_report(const zf_engine *e, zf_mask_report *out);
 /* Forget every cached mask row and empty the persistent automata on the device and on the host: everything is
  * parsed again the next time it is needed (benchmarks call it to start cold).  Results do not change.  With
  * zf_options.precompute_states on, and no asynchronous mask call in flight, the automata are then explored from the
- * empty prefix again as when the engine was compiled (mask calls on the null stream, which this call waits for):
+ * empty prefix again as when the engine was compiled (the device's is filled on the null stream, which this call waits for):
  * the engine is back to what it knew after zf_compile, not to nothing. */
 int zf_engine_clear_state_cache(zf_engine *e);
 /* on != 0: zf_compute_mask brackets each of its kernels with HIP events (a few microseconds

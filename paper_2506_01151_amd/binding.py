@@ -261,8 +261,8 @@ class Engine:
                          len(csr["term_kind"]), csr["term_kind"].ctypes.data, csr["term_off"].ctypes.data,
                          csr["term_data"].ctypes.data)
         off = np.zeros(len(vocab_tokens) + 1, dtype=np.int64)
-        np.cumsum([len(t) for t in vocab_tokens], out=off[1:])
-        data = np.frombuffer(b"".join(vocab_tokens) or b"\0", dtype=np.uint8).copy()
+        np.cumsum(np.fromiter(map(len, vocab_tokens), dtype=np.int64, count=len(vocab_tokens)), out=off[1:])
+        data = np.frombuffer(b"".join(vocab_tokens) or b"\0", dtype=np.uint8)   # read during the call only
         vd = VocabDesc(len(vocab_tokens), off.ctypes.data, data.ctypes.data)
         opt = Options(int(bool(pruning)), lane_item_cap, device, chunk_strings, fallback_item_cap, state_cache_entries, int(not token_mask_cache), walk_mode, precompute_states)
         h = c_vp()

@@ -10,9 +10,9 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
-#include <unordered_set>
 #include "zf_internal.h"
 #include "zf_host_automaton.h"
 #include "zf_launch.h"
@@ -48,7 +48,11 @@ const Chart &chart_of(const zf_state *s) {
 struct DeviceSide {
     int device = 0;
     DeviceTables tab{};
-    std::vector<void *> owned;           // table allocations
+    // What an engine keeps in device memory for its whole life is carved out of a few large allocations: a schema that a request
+    // brings along is compiled and thrown away again, and hipFree costs about 0.1 ms apiece.
+    static const size_t SLAB_BYTES = (size_t)16 << 20;
+    std::vector<void *> slabs;
+    uint8_t *slab_next = nullptr; size_t slab_left = 0;
     // per-call buffers, grown on demand
     void *d_chart = nullptr; size_t chart_cap = 0;
     static const int N_SLOTS = 4;                    // calls that may be in flight before zf_mask_wait
@@ -157,15 +161,32 @@ const uint32_t STORE_ROOT_ID = 1;
 int fail(int code, const std::string &m) { set_error(m); return code; }
 #define HIP_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return fail(ZF_ERR_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); } while (0)
 
+// Device memory that lives as long as the engine.
+template <class Tv>
+int engine_alloc(DeviceSide *d, size_t bytes, Tv **out) {
+    bytes = (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
+    if (bytes > d->slab_left) {
+        uint8_t *p = nullptr;
+        const bool own = bytes >= DeviceSide::SLAB_BYTES;   // an allocation of its own: the slab in use stays in use
+        HIP_TRY(hipMalloc((void **)&p, own ? bytes : DeviceSide::SLAB_BYTES));
+        d->slabs.push_back(p);
+        if (own) { *out = (Tv *)p; return ZF_OK; }
+        d->slab_next = p; d->slab_left = DeviceSide::SLAB_BYTES;
+    }
+    *out = (Tv *)d->slab_next;
+    d->slab_next += bytes; d->slab_left -= bytes;
+    return ZF_OK;
+}
+
 template <class Tv>
 int upload(DeviceSide *d, const std::vector<Tv> &v, const Tv **out, uint32_t *bytes_out = nullptr) {
     // padded to a multiple of 16 bytes (zero filled) so that blocks can stage it with 16-byte copies
-    void *p = nullptr;
-    size_t bytes = (std::max<size_t>(v.size() * sizeof(Tv), 16) + 15) & ~(size_t)15;
-    HIP_TRY(hipMalloc(&p, bytes));
-    d->owned.push_back(p);
-    HIP_TRY(hipMemset(p, 0, bytes));
-    if (!v.empty()) HIP_TRY(hipMemcpy(p, v.data(), v.size() * sizeof(Tv), hipMemcpyHostToDevice));
+    uint8_t *p = nullptr;
+    const size_t have = v.size() * sizeof(Tv), bytes = (std::max<size_t>(have, 16) + 15) & ~(size_t)15;
+    const int rc = engine_alloc(d, bytes, &p);
+    if (rc != ZF_OK) return rc;
+    if (have < bytes) HIP_TRY(hipMemset(p + have, 0, bytes - have));
+    if (have) HIP_TRY(hipMemcpy(p, v.data(), have, hipMemcpyHostToDevice));
     *out = (const Tv *)p;
     if (bytes_out) *bytes_out = (uint32_t)bytes;
     return ZF_OK;
@@ -174,29 +195,32 @@ int upload(DeviceSide *d, const std::vector<Tv> &v, const Tv **out, uint32_t *by
 void free_device(DeviceSide *d) {
     if (!d) return;
     (void)hipSetDevice(d->device);
-    for (void *p : d->owned) (void)hipFree(p);
+    for (void *p : d->slabs) (void)hipFree(p);
     if (d->d_chart) (void)hipFree(d->d_chart);
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) { if (d->h_stage[k]) (void)hipHostFree(d->h_stage[k]); if (d->stage_done[k]) (void)hipEventDestroy(d->stage_done[k]); }
     if (d->h_status) (void)hipHostFree(d->h_status);
-    if (d->d_pool) (void)hipFree(d->d_pool);
     if (d->d_rank_mask) (void)hipFree(d->d_rank_mask);
     if (d->d_overflow) (void)hipFree(d->d_overflow);
     if (d->d_work) (void)hipFree(d->d_work);
-    if (d->d_counters) (void)hipFree(d->d_counters);
     if (d->d_fb_items) (void)hipFree(d->d_fb_items);
     if (d->d_fb_ss) (void)hipFree(d->d_fb_ss);
-    if (d->store.hdr) (void)hipFree(d->store.hdr);
-    if (d->store.arena) (void)hipFree(d->store.arena);
-    if (d->store.trans) (void)hipFree(d->store.trans);
-    if (d->store.intern) (void)hipFree(d->store.intern);
-    if (d->store.ctl) (void)hipFree(d->store.ctl);
-    if (d->d_root_items) (void)hipFree(d->d_root_items);
-    if (d->d_import_root) (void)hipFree(d->d_import_root);
     if (d->h_store_status) (void)hipHostFree((void *)d->h_store_status);
-    if (d->d_tickets) (void)hipFree(d->d_tickets);
-    if (d->d_konst) (void)hipFree(d->d_konst);
     for (auto &ev : d->ev) if (ev) (void)hipEventDestroy(ev);
     delete d;
+}
+
+const uint32_t STORE_CAP_ITEMS = 1u << 22;
+uint32_t store_cap_states(int n_cls) {
+    uint32_t cap = 1u << 18;
+    while (cap > 4096 && (size_t)cap * (size_t)std::max(n_cls, 1) * 4 > ((size_t)128 << 20)) cap >>= 1;
+    return cap;
+}
+
+// The arenas of the fallback pass (256 MB).
+int alloc_fallback(DeviceSide *d) {
+    if (!d->d_fb_items) HIP_TRY(hipMalloc((void **)&d->d_fb_items, (size_t)FB_ITEMS_PER_WAVE * FB_WAVES * sizeof(uint2)));
+    if (!d->d_fb_ss) HIP_TRY(hipMalloc((void **)&d->d_fb_ss, (size_t)(FB_DEPTH_MAX + 2) * FB_WAVES * sizeof(uint32_t)));
+    return ZF_OK;
 }
 
 int setup_device(zf_engine *e) {
@@ -266,26 +290,24 @@ int setup_device(zf_engine *e) {
         }
         std::vector<uint32_t> &valid_tok = d->h_valid_tok, &cd_tok = d->h_cd_tok;
         valid_tok.assign(std::max<size_t>(n_rows * W, 1), 0); cd_tok.assign(std::max<size_t>(n_rows * W, 1), 0);
-        auto rows_job = [&](size_t r0, size_t r1) {
-            for (size_t r = r0; r < r1; r++) {
-                const uint32_t *sv = &tr.ci_valid[r * tr.Wr], *sc = &tr.ci_cd[r * tr.Wr];
-                uint32_t *dv = &valid_tok[r * W], *dc = &cd_tok[r * W];
-                for (size_t v = 0; v < V; v++) {
-                    const uint32_t k = tr.rank_of[v];
-                    if (k == 0xFFFFFFFFu) continue;
-                    const uint32_t bv = (sv[k >> 5] >> (k & 31)) & 1u, bc = (sc[k >> 5] >> (k & 31)) & 1u;
-                    dv[v >> 5] |= bv << (v & 31);
-                    dc[v >> 5] |= bc << (v & 31);
-                }
+        // A row's set bits are taken one by one and written at the tokens that carry the string (most rows -- the states of literal
+        // terminals -- hold a handful).  Tokens by string: those of string r are tok_by[tok_at[r] ..].
+        std::vector<uint32_t> tok_at((size_t)tr.n_strings + 2, 0), tok_by(V);
+        for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_at[tr.rank_of[v] + 2]++;
+        for (size_t r = 2; r < tok_at.size(); r++) tok_at[r] += tok_at[r - 1];
+        for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_by[tok_at[tr.rank_of[v] + 1]++] = (uint32_t)v;
+        parallel_for(n_rows, n_rows * V >= (size_t)1 << 20 ? 8 : 1, [&](size_t r) {
+            for (int kind = 0; kind < 2; kind++) {
+                const uint32_t *src = (kind ? tr.ci_cd.data() : tr.ci_valid.data()) + r * tr.Wr;
+                uint32_t *dst = (kind ? cd_tok.data() : valid_tok.data()) + r * W;
+                for (size_t w = 0; w < (size_t)tr.Wr; w++)
+                    for (uint32_t bits = src[w]; bits; bits &= bits - 1) {
+                        const size_t k = w * 32 + (size_t)__builtin_ctz(bits);
+                        if (k >= (size_t)tr.n_strings) break;     // bits of the last chunk beyond the strings
+                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) dst[tok_by[j] >> 5] |= 1u << (tok_by[j] & 31);
+                    }
             }
-        };
-        const size_t n_thr = std::min<size_t>(std::max<size_t>(1, std::min<unsigned>(8, std::thread::hardware_concurrency())), std::max<size_t>(n_rows, 1));
-        if (n_thr <= 1 || n_rows * V < (size_t)1 << 22) rows_job(0, n_rows);
-        else {
-            std::vector<std::thread> pool;
-            for (size_t k = 0; k < n_thr; k++) pool.emplace_back(rows_job, n_rows * k / n_thr, n_rows * (k + 1) / n_thr);
-            for (auto &th : pool) th.join();
-        }
+        });
         UP(tok16, tok16, nullptr); UP(ci_valid_tok, valid_tok, nullptr); UP(ci_cd_tok, cd_tok, nullptr);
     }
     T.Q = t.Q;
@@ -298,11 +320,11 @@ int setup_device(zf_engine *e) {
     HIP_TRY(hipDeviceGetAttribute(&d->cus, hipDeviceAttributeMultiprocessorCount, d->device));
     if (e->opt.state_cache_entries > 0 && e->W > 0) {
         d->cache.resize(e->opt.state_cache_entries);
-        HIP_TRY(hipMalloc((void **)&d->d_pool, (size_t)e->opt.state_cache_entries * e->W * 4));
+        if ((rc = engine_alloc(d, (size_t)e->opt.state_cache_entries * e->W * 4, &d->d_pool)) != ZF_OK) return rc;
     }
     if (walk_lds_bytes(T, d->mode, e->opt.lane_item_cap) > 160u * 1024u)
         return fail(ZF_ERR_INVALID_ARG, "lane_item_cap and the grammar tables do not fit the 160 KB of LDS");
-    HIP_TRY(hipMalloc((void **)&d->d_counters, 2 * COUNTER_SET_WORDS * 4));     // two sets of counters (see MaskArgs::counters)
+    if ((rc = engine_alloc(d, 2 * COUNTER_SET_WORDS * 4, &d->d_counters)) != ZF_OK) return rc;     // two sets of counters (see MaskArgs::counters)
     HIP_TRY(hipMemset(d->d_counters, 0, 2 * COUNTER_SET_WORDS * 4));
     HIP_TRY(hipHostMalloc((void **)&d->h_status, 32 * DeviceSide::N_SLOTS, hipHostMallocDefault));
     memset(d->h_status, 0, 32 * DeviceSide::N_SLOTS);
@@ -315,22 +337,21 @@ int setup_device(zf_engine *e) {
         // Room of the persistent automaton: states x byte classes transition words (at most 128 MB), 4 M items, a hash table of
         // twice as many slots as states.  The host clears the store when it is half full (see enqueue_mask_impl).
         StoreView &G = d->store;
-        uint32_t cap = 1u << 18;
-        while (cap > 4096 && (size_t)cap * (size_t)std::max(t.n_cls, 1) * 4 > ((size_t)128 << 20)) cap >>= 1;
-        G.cap_states = cap; G.cap_items = 1u << 22; G.intern_mask = 2 * cap - 1;
-        HIP_TRY(hipMalloc((void **)&G.hdr, (size_t)G.cap_states * sizeof(uint2)));
-        HIP_TRY(hipMalloc((void **)&G.arena, (size_t)G.cap_items * sizeof(uint2)));
-        HIP_TRY(hipMalloc((void **)&G.trans, (size_t)G.cap_states * std::max(t.n_cls, 1) * 4));
-        HIP_TRY(hipMalloc((void **)&G.intern, ((size_t)G.intern_mask + 1) * 8));
-        HIP_TRY(hipMalloc((void **)&G.ctl, 64));
-        HIP_TRY(hipMalloc((void **)&d->d_import_root, (size_t)MAX_BATCH * 4));
+        const uint32_t cap = store_cap_states(t.n_cls);
+        G.cap_states = cap; G.cap_items = STORE_CAP_ITEMS; G.intern_mask = 2 * cap - 1;
+        if ((rc = engine_alloc(d, (size_t)G.cap_states * sizeof(uint2), &G.hdr)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, (size_t)G.cap_items * sizeof(uint2), &G.arena)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, (size_t)G.cap_states * std::max(t.n_cls, 1) * 4, &G.trans)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, ((size_t)G.intern_mask + 1) * 8, &G.intern)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, 64, &G.ctl)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, (size_t)MAX_BATCH * 4, &d->d_import_root)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
         HIP_TRY(hipHostMalloc((void **)&d->h_store_status, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8, hipHostMallocDefault));
         memset((void *)d->h_store_status, 0, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8);
-        HIP_TRY(hipMalloc((void **)&d->d_tickets, STORE_TICKETS * 8));
         HIP_TRY(hipMemset(d->d_tickets, 0, STORE_TICKETS * 8));
         {
             const StoreConst k{d->tab, G};
-            HIP_TRY(hipMalloc((void **)&d->d_konst, sizeof k));
+            if ((rc = engine_alloc(d, sizeof k, &d->d_konst)) != ZF_OK) return rc;
             HIP_TRY(hipMemcpy(d->d_konst, &k, sizeof k, hipMemcpyHostToDevice));
         }
         Chart c0;                                        // the empty prefix's set, completed items dropped, as device item words
@@ -343,15 +364,14 @@ int setup_device(zf_engine *e) {
             root.push_back(0);
         }
         d->n_root = (uint32_t)root.size() / 2;
-        HIP_TRY(hipMalloc(&d->d_root_items, std::max<size_t>(root.size() * 4, 16)));
+        if ((rc = engine_alloc(d, root.size() * 4, (uint32_t **)&d->d_root_items)) != ZF_OK) return rc;
         if (!root.empty()) HIP_TRY(hipMemcpy(d->d_root_items, root.data(), root.size() * 4, hipMemcpyHostToDevice));
         d->store_dirty = true;
     }
     HIP_TRY(scratch_init(d->device));                    // once per device, with that device current
     d->scratch = (uint8_t *)scratch_ptr(d->device);
     if (!d->scratch) return fail(ZF_ERR_DEVICE, "the device address of the static scratch array is unknown");
-    HIP_TRY(hipMalloc((void **)&d->d_fb_items, (size_t)FB_ITEMS_PER_WAVE * FB_WAVES * sizeof(uint2)));
-    HIP_TRY(hipMalloc((void **)&d->d_fb_ss, (size_t)(FB_DEPTH_MAX + 2) * FB_WAVES * sizeof(uint32_t)));
+    if (!e->store_on) return alloc_fallback(d);          // an engine with a persistent automaton may never need it: on first use
     return ZF_OK;
 }
 
@@ -406,7 +426,7 @@ CurrentSet current_set(zf_state *s) {
         }
         const HostAutomaton &A = *e->host_aut;
         const HostAutomaton::State &hs = A.st(at);
-        return CurrentSet{hs.items.data(), (uint32_t)hs.items.size(), hs.widest};
+        return CurrentSet{hs.items, hs.n_items, hs.widest};
     }
     const Chart &c = s->chart;
     uint32_t biggest = 0;
@@ -421,7 +441,7 @@ int feed_token_bytes(zf_state *s, const uint8_t *bytes, int64_t n) {
     const bool pruning = s->eng->opt.pruning != 0;
     if (s->eng->host_aut) {
         // Through the host automaton: a look-up per byte once the transition is known (Sections 4.4, 5.2: nothing is parsed
-        // twice), an Earley byte step the first time -- run on a private copy of the sets it reads, without the lock, so
+        // twice), an Earley byte step the first time -- run without the lock (the sets it reads do not change), so
         // that the rows of a batch can be fed by several threads.  All or nothing, as below.
         zf_engine *e = s->eng;
         HostAutomaton &A = *e->host_aut;
@@ -451,11 +471,10 @@ int feed_token_bytes(zf_state *s, const uint8_t *bytes, int64_t n) {
                     static thread_local HostAutomaton::Work w;
                     e->host_walkers++;
                     lk.unlock();
-                    A.lay_out(at, w);
-                    const StepResult r = earley_step(t, w.c, bytes[i], false, nullptr);
+                    A.look_ahead(at, cl, w);
                     lk.lock();
                     e->host_walkers--;
-                    if (A.st(at).trans[cl] == HostAutomaton::NONE) A.record(at, cl, r, w);   // else somebody else has made it meanwhile
+                    if (A.st(at).trans[cl] == HostAutomaton::NONE) A.record(at, cl, w);   // else somebody else has made it meanwhile
                 }
                 accepted = A.st(at).acc[cl] != 0;
                 at = A.st(at).trans[cl];
@@ -520,7 +539,9 @@ const char *zf_strerror(int code) {
 }
 const char *zf_last_error(void) { return g_err.c_str(); }
 
-static void explore_from_the_empty_prefix(zf_engine *e);
+static bool wants_exploration(const zf_engine *e);
+static void explore_host(zf_engine *e, size_t cap_states, size_t cap_items);
+static void store_adopt(zf_engine *e);
 
 int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_options *opt, zf_engine **out) {
     if (!g || !v || !out || v->V < 0 || (v->V && !v->off)) return fail(ZF_ERR_INVALID_ARG, "null argument");
@@ -541,24 +562,29 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
     if (e->opt.chunk_strings != 8 && e->opt.chunk_strings != 16 && e->opt.chunk_strings != 32) e->opt.chunk_strings = 8;
     if (e->opt.precompute_states == 0) e->opt.precompute_states = 65536;
     if (e->opt.precompute_states < 0) e->opt.precompute_states = 0;
+    std::thread explorer;                                 // the exploration needs the grammar tables only: it runs beside everything else
+    struct Join { std::thread &t; ~Join() { if (t.joinable()) t.join(); } } join{explorer};
+    auto give_up = [&](int rc) { if (explorer.joinable()) explorer.join(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
     try {
         if (!build_tables(g, e->tab)) { delete e; return ZF_ERR_GRAMMAR; }
         e->V = v->V; e->W = (v->V + 31) / 32;
+        e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
+        if (e->opt.walk_mode == 2 && e->opt.pruning != 0) e->host_aut = new HostAutomaton(e->tab);
+        if (wants_exploration(e))
+            explorer = std::thread([e]() {
+                try { explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
+            });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
         build_trie(v, e->opt.chunk_strings, e->tab.cls, e->trie);
         build_token_mask_cache(e->tab, e->trie);
-    } catch (const std::bad_alloc &) { delete e; return fail(ZF_ERR_OOM, "out of memory"); }
-    e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
-    if (e->opt.walk_mode == 2 && e->opt.pruning != 0) {
-        e->host_aut = new (std::nothrow) HostAutomaton(e->tab);
-        if (!e->host_aut) { delete e; return fail(ZF_ERR_OOM, "out of memory"); }
-    }
+    } catch (const std::bad_alloc &) { return give_up(fail(ZF_ERR_OOM, "out of memory")); }
+    catch (const std::system_error &) { return give_up(fail(ZF_ERR_OOM, "no thread to be had")); }
     if (e->opt.device >= 0) {
-        int rc = setup_device(e);
-        if (rc != ZF_OK) { free_device(e->dev); delete e->host_aut; delete e; return rc; }
+        const int rc = setup_device(e);
+        if (rc != ZF_OK) return give_up(rc);
     }
-    explore_from_the_empty_prefix(e);
+    if (explorer.joinable()) { explorer.join(); store_adopt(e); }
     *out = e;
     return ZF_OK;
 }
@@ -735,7 +761,7 @@ int64_t advance_cost(zf_state *const *states, const int32_t *ids, int32_t n) {
             const uint8_t first = e->voc_bytes[(size_t)e->voc_off[ids[b]]];
             const bool has_bytes = e->voc_off[ids[b] + 1] > e->voc_off[ids[b]];
             if (placed && has_bytes && A.st(s->host_id).trans[e->tab.cls[first]] != HostAutomaton::NONE) continue;
-            const int64_t last = placed ? (int64_t)A.st(s->host_id).items.size() : 64, all = placed ? 8 * (int64_t)A.st(s->host_id).widest : 4096;
+            const int64_t last = placed ? (int64_t)A.st(s->host_id).n_items : 64, all = placed ? 8 * (int64_t)A.st(s->host_id).widest : 4096;
             cost += (e->voc_off[ids[b] + 1] - e->voc_off[ids[b]]) * (last + last * last / 16 + all);
             continue;
         }
@@ -1120,6 +1146,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         HIP_TRY(hipMalloc((void **)&d->d_work, need_ovf * sizeof(uint4) + 16));
         d->rank_cap = need_rank; d->overflow_cap = need_ovf;
     }
+    if (!noalloc) { const int rc = alloc_fallback(d); if (rc != ZF_OK) return rc; }
     MaskArgs a{};
     a.tab = d->tab;
     // Where the kernels read the packed charts: with the mask automaton and the state cache off, straight from the pinned
@@ -1728,77 +1755,76 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states, int32_t batch, uint32
     return enqueue_mask(e, states, batch, d_mask, hip_stream, true);
 }
 
-// What the persistent automaton holds when a decode loop starts (zf_options.precompute_states).  The automaton is explored
-// breadth first from the state of the empty prefix, one byte class at a time (every DFA treats the bytes of a class alike, so one
-// byte per class stands for all), on the host and, by computing the mask at every state found, on the device: a mask call
-// computes every transition its walk of the vocabulary needs, so the device learns the states a token's length ahead of the
-// exploration.  The exploration ends when no new state turns up -- a grammar without recursion has a finite automaton, which is
-// then built whole, as engines for regular constraints build theirs when they compile -- or at the budget of states or of
-// time, or when the store is a quarter full.  It uses the library's own calls and nothing else (states, advance by bytes, compute_mask): what it leaves behind is
-// what a decode loop that happened to visit these prefixes would have left.  Failures are not errors: the engine then starts
-// with whatever was learnt, or with nothing, as it did before there was an exploration.
-static void explore_from_the_empty_prefix(zf_engine *e) {
-    if (!e || !e->store_on || !e->dev || !e->host_aut || e->opt.precompute_states <= 0) return;
-    DeviceSide *d = e->dev;
-    if (d->pending != 0) return;                          // calls in flight: the store is cleared lazily, and starts empty
+// What the persistent automaton holds when a decode loop starts (zf_options.precompute_states).  The host's automaton is explored
+// breadth first from the state of the empty prefix, one byte class at a time (every DFA treats the bytes of a class alike), and
+// the device's is filled with it: the same states under the same names, and every transition the host knows.  The exploration
+// ends when no new state turns up -- a grammar without recursion has a finite automaton, which is then built whole, as engines
+// for regular constraints build theirs when they compile -- or at the budget of states or of time, or when it would fill a
+// quarter of the store (the store starts over when it is half full, and what a decode loop adds needs room).
+//   Built by the library's own calls before -- a zf_state cloned and advanced per state and class, a mask call per 64 states
+// and 64 transitions -- the 20,962 states of a JSON schema took 417 ms: 55 clones and steps per state where four classes are
+// live (State::trans: a class on which no item leaves anything is known to be dead), chart copies, an ordered map of item lists.
+static bool wants_exploration(const zf_engine *e) { return e->store_on && e->host_aut && e->opt.precompute_states > 0; }
+
+// The host's part: touches nothing but the host automaton (the caller holds its lock, or is the only one who knows the engine).
+static void explore_host(zf_engine *e, size_t cap_states, size_t cap_items) {
+    HostAutomaton &A = *e->host_aut;
     const auto t0 = std::chrono::steady_clock::now();
-    auto spent = [&]() { return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count(); };
     const double budget_s = 1.0;
-    const size_t budget_states = (size_t)e->opt.precompute_states;
-    hipError_t he = hipSetDevice(e->opt.device);
-    uint32_t *d_tmp = nullptr;
-    constexpr int ROWS = 64;
-    if (he != hipSuccess || hipMalloc((void **)&d_tmp, (size_t)ROWS * (size_t)std::max(e->W, 1) * 4) != hipSuccess) { (void)hipGetLastError(); return; }
-    std::vector<uint8_t> rep(std::max(e->tab.n_cls, 0), 0);   // one byte of every class
-    std::vector<char> have(rep.size(), 0);
-    for (int b = 0; b < 256; b++) { const int c = e->tab.cls[b]; if (c >= 0 && c < (int)rep.size() && !have[c]) { have[c] = 1; rep[c] = (uint8_t)b; } }
-    // Breadth first, 64 states at a time: the masks at the states in hand (the device meets them and everything a token's length
-    // ahead; the host then knows their names on the device), then the states one byte further, which inherit their parent's
-    // name and one pending byte.
-    std::vector<zf_state *> queue, edges;
-    size_t head = 0;
-    std::unordered_set<uint32_t> seen;
-    zf_state *root = nullptr;
-    bool ok = zf_state_new(e, &root) == ZF_OK;
-    if (ok) { queue.push_back(root); seen.insert(HostAutomaton::ROOT); }
-    const uint32_t epoch = e->host_epoch;
-    while (ok && head < queue.size() && spent() < budget_s) {
-        const size_t n = std::min<size_t>(ROWS, queue.size() - head);
-        ok = enqueue_mask(e, queue.data() + head, (int32_t)n, d_tmp, nullptr, true) == ZF_OK;
-        for (size_t k = head; ok && k < head + n; k++) {
-            for (size_t c = 0; c < rep.size() && seen.size() < budget_states; c++) {
-                if (!have[c]) continue;
-                zf_state *child = nullptr;
-                if (zf_state_clone(queue[k], &child) != ZF_OK) { ok = false; break; }
-                const bool alive = zf_advance_bytes(child, &rep[c], 1) == ZF_OK && e->host_epoch == epoch &&
-                                   child->host_id != HostAutomaton::SINK && child->host_id != HostAutomaton::DEAD;
-                if (alive && seen.insert(child->host_id).second) queue.push_back(child);
-                else if (alive) edges.push_back(child);   // a way into a state met before: the device has to have walked it too
-                else zf_state_destroy(child);
-            }
-            zf_state_destroy(queue[k]);
-            queue[k] = nullptr;
+    const size_t most_states = std::min((size_t)e->opt.precompute_states, cap_states / 4), most_items = cap_items / 4;
+    HostAutomaton::Work w;
+    for (uint32_t s = HostAutomaton::ROOT; s < A.n_states; s++) {
+        if ((s & 63u) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() >= budget_s) return;
+        for (int c = 0; c < e->tab.n_cls; c++) {
+            if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
+            if (A.n_states > most_states || (size_t)A.n_items >= most_items) return;
+            A.compute(s, c, w);
         }
-        head += n;
-        // the transitions that led to states met before: a row that takes one has the device walk it (its mask is made of look-ups,
-        // or is the first visit of a state whose turn in the queue comes later)
-        while (ok && edges.size() >= (size_t)ROWS) {
-            ok = enqueue_mask(e, edges.data() + edges.size() - ROWS, ROWS, d_tmp, nullptr, true) == ZF_OK;
-            for (int k = 0; k < ROWS; k++) { zf_state_destroy(edges.back()); edges.pop_back(); }
+    }
+}
+
+// The device's part: the store is cleared and takes over what the host automaton holds, names and all.  A failure is no error:
+// the store then starts empty, as it does without an exploration.
+static void store_adopt(zf_engine *e) {
+    DeviceSide *d = e->dev;
+    const HostAutomaton &A = *e->host_aut;
+    const Tables &t = e->tab;
+    const StoreView &G = d->store;
+    const size_t n = A.n_states, ncls = (size_t)std::max(t.n_cls, 1);
+    static_assert(HostAutomaton::ROOT == 1 && HostAutomaton::NONE == ~0u && HostAutomaton::DEAD == ~1u && HostAutomaton::SINK == ~2u, "the device's table uses the same words");
+    if (n < 2 || n > G.cap_states / 2 || (size_t)A.n_items + d->n_root > G.cap_items / 2) return;
+    std::vector<uint2> hdr(n), items;
+    items.reserve((size_t)A.n_items + d->n_root);
+    hdr[0] = make_uint2(0, 0xFFFFFFFFu);                  // no such state: as the clearing kernel leaves it
+    for (uint32_t id = 1; id < n; id++) {
+        const HostAutomaton::State &s = A.st(id);
+        hdr[id] = make_uint2((uint32_t)items.size(), s.n_items);
+        for (uint32_t i = 0; i < s.n_items; i++) {
+            const uint32_t aw = t.advpq[s.items[i].p];
+            items.push_back(make_uint2((aw & IW_TERM) ? ((aw & 0xFFFFu) | ((uint32_t)s.items[i].q << 16)) : aw, s.items[i].o));
         }
-        if (e->host_epoch != epoch) ok = false;           // the host automaton filled up and started over: enough
-        // a quarter of the store is the most the exploration takes: the store starts over when it is half full, and what a
-        // decode loop adds needs room
-        if (d->store_states > d->store.cap_states / 4 || d->store_items > d->store.cap_items / 4) break;
     }
-    if (ok && !edges.empty() && spent() < budget_s) (void)enqueue_mask(e, edges.data(), (int32_t)edges.size(), d_tmp, nullptr, true);
-    for (zf_state *st : edges) zf_state_destroy(st);
-    for (zf_state *st : queue) if (st) zf_state_destroy(st);
-    (void)hipFree(d_tmp);
-    g_err.clear();                                        // a rejected byte is how a dead class shows: not the caller's error
-    if (d->store_backoff) {                               // a state the store had no room for: the engine starts as if nothing had been explored
-        d->store_backoff = 0; d->store_backoff_next = 8; d->store_dirty = true;
-    }
+    auto run = [&]() -> hipError_t {
+        hipError_t rc = hipSetDevice(d->device);
+        if (rc == hipSuccess) rc = launch_store_clear(G, (uint32_t)ncls, d->d_root_items, d->n_root, nullptr);
+        if (rc == hipSuccess) rc = hipMemcpyAsync(G.hdr, hdr.data(), n * sizeof(uint2), hipMemcpyHostToDevice, nullptr);
+        if (rc == hipSuccess) rc = hipMemcpyAsync(G.arena, items.data(), items.size() * sizeof(uint2), hipMemcpyHostToDevice, nullptr);
+        for (size_t b = 0; rc == hipSuccess && b * HostAutomaton::BLOCK < n; b++) {   // the host's rows of the table, block by block
+            const size_t rows = std::min<size_t>(HostAutomaton::BLOCK, n - b * HostAutomaton::BLOCK);
+            rc = hipMemcpyAsync(G.trans + b * HostAutomaton::BLOCK * ncls, A.blocks[b].trans.get(), rows * ncls * 4, hipMemcpyHostToDevice, nullptr);
+        }
+        if (rc == hipSuccess) rc = launch_store_adopt(G, (uint32_t)n, (uint32_t)items.size(), nullptr);
+        if (rc == hipSuccess) rc = hipStreamSynchronize(nullptr);
+        return rc;
+    };
+    d->store_dirty = true;
+    if (run() != hipSuccess) { (void)hipGetLastError(); return; }
+    d->store_dirty = false;
+    d->store_epoch++;
+    d->store_states = (uint32_t)n; d->store_items = (uint32_t)items.size();
+    d->name_host_epoch = e->host_epoch; d->name_store_epoch = d->store_epoch;
+    d->name_of_host.resize(n);
+    for (uint32_t id = 0; id < n; id++) d->name_of_host[id] = id;
 }
 
 int zf_compute_mask_noalloc(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream) {
@@ -1922,8 +1948,11 @@ int zf_engine_clear_state_cache(zf_engine *e) {
         while (e->host_walkers != 0) { lk.unlock(); std::this_thread::yield(); lk.lock(); }   // somebody is at work on a transition (and waits for nobody)
         e->host_aut->clear();
         e->host_epoch++;
+        if (wants_exploration(e) && e->dev && e->dev->pending == 0) {   // back to what the engine knew when it was compiled (with calls in flight the store is cleared later, and starts empty)
+            explore_host(e, e->dev->store.cap_states, e->dev->store.cap_items);
+            store_adopt(e);
+        }
     }
-    explore_from_the_empty_prefix(e);                     // back to what the engine knew when it was compiled
     return ZF_OK;
 }
 

@@ -194,7 +194,8 @@ extern "C" int zf_debug_twin_mask(zf_twin *tw, uint32_t state, uint32_t *mask, i
         if (root >= a.n_states) { set_error("unknown state"); return ZF_ERR_INVALID_ARG; }
         std::vector<uint32_t> valid(tr.Wr, 0), want(tr.Wr, 0);
         if (e->opt.disable_token_mask_cache) want.assign(tr.Wr, 0xFFFFFFFFu);
-        else for (const Item &it : a.st(root).items) {             // the token-mask cache rows of the state's items (Section 4.3)
+        else for (uint32_t i = 0; i < a.st(root).n_items; i++) {   // the token-mask cache rows of the state's items (Section 4.3)
+            const Item it = a.st(root).items[i];
             const uint16_t code = t.sym[it.p];
             size_t row;
             if ((code >> SYM_KIND_SHIFT) == SYM_TERM) row = it.q;

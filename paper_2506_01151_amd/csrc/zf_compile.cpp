@@ -290,25 +290,46 @@ bool build_tables(const zf_grammar_desc *g, Tables &t) {
 void build_trie(const zf_vocab_desc *v, int CHUNK_RANKS, const uint8_t *cls, Trie &t) {
     t.chunk_ranks = CHUNK_RANKS;
     const int V = v->V;
-    std::vector<int> order;
-    for (int i = 0; i < V; i++) if (v->off[i + 1] > v->off[i]) order.push_back(i);
+    // Sorted by their bytes, then by their numbers: dealt to 256 buckets by the first byte, each sorted by the next eight bytes as
+    // one number; only strings that agree in these are compared byte by byte.  The buckets are independent.
     auto tok = [&](int i, const uint8_t *&p, size_t &n) { p = v->bytes + v->off[i]; n = (size_t)(v->off[i + 1] - v->off[i]); };
-    std::sort(order.begin(), order.end(), [&](int a, int b) {
-        const uint8_t *pa, *pb; size_t na, nb;
-        tok(a, pa, na); tok(b, pb, nb);
-        int c = memcmp(pa, pb, std::min(na, nb));
-        if (c) return c < 0;
-        if (na != nb) return na < nb;
-        return a < b;
+    struct Key { uint64_t next; int id; };
+    std::vector<uint32_t> bucket(257, 0);
+    for (int i = 0; i < V; i++) if (v->off[i + 1] > v->off[i]) bucket[v->bytes[v->off[i]] + 1u]++;
+    for (int b = 0; b < 256; b++) bucket[b + 1] += bucket[b];
+    std::vector<Key> order(bucket[256]);
+    {
+        std::vector<uint32_t> at(bucket.begin(), bucket.end() - 1);
+        for (int i = 0; i < V; i++) {
+            const uint8_t *p; size_t n;
+            tok(i, p, n);
+            if (n == 0) continue;
+            uint64_t next = 0;
+            for (size_t k = 1; k <= 8; k++) next = next << 8 | (k < n ? p[k] : 0u);
+            order[at[p[0]]++] = Key{next, i};
+        }
+    }
+    parallel_for(256, order.size() >= 8192 ? 8 : 1, [&](size_t b) {
+        std::sort(order.begin() + bucket[b], order.begin() + bucket[b + 1], [&](const Key &a, const Key &c) {
+            if (a.next != c.next) return a.next < c.next;
+            const uint8_t *pa, *pb; size_t na, nb;
+            tok(a.id, pa, na); tok(c.id, pb, nb);
+            const int r = memcmp(pa, pb, std::min(na, nb));
+            if (r) return r < 0;
+            if (na != nb) return na < nb;
+            return a.id < c.id;
+        });
     });
     t.nodes.clear(); t.parent.clear(); t.rank_of.assign(V, 0xFFFFFFFFu);
     t.str_off.clear(); t.str_bytes.clear();
+    t.nodes.reserve(2 * order.size()); t.parent.reserve(2 * order.size()); t.str_off.reserve(order.size() + 1); t.str_bytes.reserve(4 * order.size());
     // Walk the sorted strings; the stack holds the node indices of the current path.
     std::vector<uint32_t> path;       // path[d-1] = node index at depth d
     std::vector<uint8_t> path_bytes;
     uint32_t rank = 0;
     const uint8_t *prev = nullptr; size_t prev_n = 0;
-    for (int id : order) {
+    for (const Key &key : order) {
+        const int id = key.id;
         const uint8_t *p; size_t n;
         tok(id, p, n);
         if (n > (size_t)MAX_TOKEN_LEN_ON_DEVICE) n = MAX_TOKEN_LEN_ON_DEVICE;   // guarded by zf_compile

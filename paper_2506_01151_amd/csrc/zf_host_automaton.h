@@ -13,7 +13,6 @@
 // lock.  clear() frees the blocks: the owner calls it only while no thread is between lay_out and record.
 #pragma once
 #include <algorithm>
-#include <map>
 #include <memory>
 #include "zf_internal.h"
 
@@ -23,43 +22,73 @@ struct HostAutomaton {
     const Tables &t;
     static constexpr uint32_t ROOT = 1, SINK = 0xFFFFFFFDu, DEAD = 0xFFFFFFFEu, NONE = 0xFFFFFFFFu;
     static constexpr uint32_t BLOCK = 1024, MAX_BLOCKS = 1024;     // at most BLOCK x MAX_BLOCKS states
+    static constexpr uint32_t ITEM_CHUNK = 1u << 15;               // items are kept in chunks of this many (a larger set has a chunk of its own)
     struct State {
-        std::vector<Item> items;          // an item's origin is a state id
-        std::vector<uint32_t> trans;      // [n_cls] next state, NONE, DEAD or SINK
-        std::vector<uint8_t> acc;         // [n_cls] the prefix is a sentence after that byte
+        const Item *items = nullptr;      // an item's origin is a state id
+        uint32_t n_items = 0;
         uint32_t widest = 0;              // items of the largest set among the state and the sets it refers to
+        uint32_t sig = 0;                 // signature of the content
+        uint32_t *trans = nullptr;        // [n_cls] next state, NONE, DEAD or SINK
+        uint8_t *acc = nullptr;           // [n_cls] the prefix is a sentence after that byte
         std::vector<uint32_t> ents;       // what the mask calls work out about the state once: the rows of the token-mask cache its items select ...
         int64_t undecided = -1;           // ... and how many tokens these leave to the parser (-1: not yet)
     };
-    std::vector<std::unique_ptr<State[]>> blocks;   // room for MAX_BLOCKS pointers from the start: the array never moves
+    // States, and their rows of the transition table (one run of memory per block: the device's table is filled from it).
+    struct Block { std::unique_ptr<State[]> states; std::unique_ptr<uint32_t[]> trans; std::unique_ptr<uint8_t[]> acc; };
+    std::vector<Block> blocks;            // room for MAX_BLOCKS from the start: the array never moves
+    std::vector<std::unique_ptr<Item[]>> chunks;
+    uint32_t chunk_used = ITEM_CHUNK;
     uint32_t n_states = 0;                // ids 0 .. n_states - 1 are taken (0 is not used)
-    std::map<std::vector<uint32_t>, uint32_t> interned;
+    std::vector<uint32_t> interned;       // open addressing by State::sig, at most half full; 0 = free
     int64_t n_steps = 0, n_items = 0;
+    struct Classes { uint64_t w[4] = {0, 0, 0, 0}; void add(int c) { w[c >> 6] |= 1ull << (c & 63); } void add(const Classes &o) { for (int k = 0; k < 4; k++) w[k] |= o.w[k]; } bool has(int c) const { return (w[c >> 6] >> (c & 63)) & 1u; } };
+    std::vector<Classes> q_live, nt_live; // [Q] [N] byte classes on which an item in that DFA state, or waiting for that nonterminal, leaves something
 
-    explicit HostAutomaton(const Tables &t_) : t(t_) { blocks.reserve(MAX_BLOCKS); clear(); }
+    explicit HostAutomaton(const Tables &t_) : t(t_) {
+        blocks.reserve(MAX_BLOCKS);
+        q_live.resize(t.Q); nt_live.resize(t.N);
+        for (int q = 0; q < t.Q; q++) for (int c = 0; c < t.n_cls; c++) if (t.delta[(size_t)q * t.n_cls + c] != DFA_DEAD) q_live[q].add(c);
+        for (int y = 0; y < t.N; y++) for (int c = 0; c < t.n_cls; c++) if (t.scan_off[(size_t)y * t.n_cls + c + 1] > t.scan_off[(size_t)y * t.n_cls + c]) nt_live[y].add(c);
+        clear();
+    }
 
-    State &st(uint32_t id) { return blocks[id / BLOCK][id % BLOCK]; }
-    const State &st(uint32_t id) const { return blocks[id / BLOCK][id % BLOCK]; }
+    State &st(uint32_t id) { return blocks[id / BLOCK].states[id % BLOCK]; }
+    const State &st(uint32_t id) const { return blocks[id / BLOCK].states[id % BLOCK]; }
     static constexpr uint32_t IMPORT_SETS_MAX = 1u << 16;          // the largest chart import takes
     bool full() const { return n_states + IMPORT_SETS_MAX + 2 >= BLOCK * MAX_BLOCKS; }   // no room for another import
 
-    uint32_t add(std::vector<Item> &&items, uint32_t widest) {
+    uint32_t add(const Item *items, uint32_t n, uint32_t widest, uint32_t sig) {
         const uint32_t id = n_states;
-        if (id / BLOCK >= blocks.size()) blocks.emplace_back(new State[BLOCK]);
+        if (id / BLOCK >= blocks.size())
+            blocks.push_back(Block{std::unique_ptr<State[]>(new State[BLOCK]), std::unique_ptr<uint32_t[]>(new uint32_t[(size_t)BLOCK * t.n_cls]), std::unique_ptr<uint8_t[]>(new uint8_t[(size_t)BLOCK * t.n_cls])});
+        if (n > ITEM_CHUNK - chunk_used || chunks.empty()) { chunks.emplace_back(new Item[std::max(n, ITEM_CHUNK)]); chunk_used = 0; }
+        Item *to = chunks.back().get() + chunk_used;
+        std::copy(items, items + n, to);
+        chunk_used = n > ITEM_CHUNK - chunk_used ? ITEM_CHUNK : chunk_used + n;
+        Block &b = blocks[id / BLOCK];
         State &s = st(id);
-        s.items = std::move(items);
-        s.trans.assign(t.n_cls, NONE);
-        s.acc.assign(t.n_cls, 0);
-        s.widest = widest;
+        s.items = to; s.n_items = n;
+        s.widest = widest; s.sig = sig;
+        s.trans = b.trans.get() + (size_t)(id % BLOCK) * t.n_cls;
+        s.acc = b.acc.get() + (size_t)(id % BLOCK) * t.n_cls;
+        // a class on which no item leaves anything needs no step to be known as a dead end
+        Classes live;
+        for (uint32_t i = 0; i < n; i++) {
+            const uint16_t code = t.sym[to[i].p];
+            if ((code >> SYM_KIND_SHIFT) == SYM_TERM) live.add(q_live[to[i].q]);
+            else if ((code >> SYM_KIND_SHIFT) == SYM_NT) live.add(nt_live[code & SYM_ID_MASK_NT]);
+        }
+        for (int c = 0; c < t.n_cls; c++) { s.trans[c] = live.has(c) ? NONE : DEAD; s.acc[c] = 0; }
         n_states++;
         return id;
     }
 
     void clear() {
         blocks.clear();
-        interned.clear();
+        chunks.clear(); chunk_used = ITEM_CHUNK;
+        interned.assign(1u << 12, 0);
         n_states = 0; n_items = 0;
-        add({}, 0);                                            // id 0 is not used
+        add(nullptr, 0, 0, 0);                                 // id 0 is not used
         Chart c;
         chart_init(t, c);
         std::vector<Item> root;
@@ -68,80 +97,142 @@ struct HostAutomaton {
             it.o = ROOT;
             root.push_back(it);
         }
-        const uint32_t w = (uint32_t)root.size();
-        add(std::move(root), w);
+        add(root.data(), (uint32_t)root.size(), (uint32_t)root.size(), 0);
     }
 
-    // A transition in three parts, so that callers that share the automaton can run the Earley byte step without
-    // holding the lock: lay_out reads (the sets s refers to, transitively, as a chart whose current set is s),
-    // earley_step works on that private chart, record writes.
-    struct Work { std::vector<uint32_t> ids; Chart c; };
-    void lay_out(uint32_t s, Work &w) const {
-        // marks instead of searches: a chart of an ambiguous grammar runs to tens of thousands of items
-        static thread_local std::vector<uint32_t> mark, place, todo;
-        static thread_local uint32_t now = 0;
-        const uint32_t room = (s / BLOCK + 1) * BLOCK;         // a state refers to older states only
-        if (mark.size() < room) { mark.resize(room, 0); place.resize(room, 0); }
-        if (++now == 0) { std::fill(mark.begin(), mark.end(), 0); now = 1; }
-        std::vector<uint32_t> &ids = w.ids;
-        ids.clear();
-        todo.assign(1, s);
-        mark[s] = now;
-        while (!todo.empty()) {
-            const uint32_t id = todo.back();
-            todo.pop_back();
-            ids.push_back(id);
-            for (const Item &it : st(id).items) if (mark[it.o] != now) { mark[it.o] = now; todo.push_back(it.o); }
+    // A transition in two parts, so that callers that share the automaton can run the Earley byte step (Scan and Complete
+    // with tabulated Predict, as earley_step does over a chart) without holding the lock: look_ahead reads the state and the
+    // sets it refers to, by their names, and leaves the new set in w; record writes it down.
+    struct Work {
+        std::vector<Item> set;
+        bool alive, accepted;
+        std::vector<uint32_t> seen;       // sets of more than a few items find duplicates by hashing: item number + 1, 0 = free
+        static constexpr size_t FEW = 16;
+        static uint32_t hash(const Item &it) { uint32_t h = ((uint32_t)it.p | (uint32_t)it.q << 16) * 0x9E3779B1u ^ it.o * 0x85EBCA77u; h ^= h >> 15; h *= 0x2C1B3C6Du; return h ^ h >> 13; }
+        static bool same(const Item &a, const Item &b) { return a.p == b.p && a.q == b.q && a.o == b.o; }
+        void insert(const Item &it) {     // a set holds each item once (Section 3.2)
+            if (set.size() <= FEW) {
+                for (const Item &x : set) if (same(x, it)) return;
+                set.push_back(it);
+                if (set.size() > FEW) rehash(64);
+                return;
+            }
+            uint32_t k = hash(it) & (uint32_t)(seen.size() - 1);
+            for (; seen[k]; k = (k + 1) & (uint32_t)(seen.size() - 1)) if (same(set[seen[k] - 1], it)) return;
+            set.push_back(it);
+            seen[k] = (uint32_t)set.size();
+            if (2 * set.size() > seen.size()) rehash(2 * seen.size());
         }
-        std::sort(ids.begin(), ids.end());
-        ids.erase(std::lower_bound(ids.begin(), ids.end(), s));
-        ids.push_back(s);                                      // the source set last: it is the chart's current set
-        for (uint32_t k = 0; k < (uint32_t)ids.size(); k++) place[ids[k]] = k;
-        w.c.items.clear();
-        w.c.set_off.assign(1, 0);
-        for (uint32_t id : ids) {
-            for (Item it : st(id).items) { it.o = place[it.o]; w.c.items.push_back(it); }
-            w.c.set_off.push_back((uint32_t)w.c.items.size());
+        void rehash(size_t room) {
+            seen.assign(room, 0);
+            for (size_t i = 0; i < set.size(); i++) {
+                uint32_t k = hash(set[i]) & (uint32_t)(room - 1);
+                while (seen[k]) k = (k + 1) & (uint32_t)(room - 1);
+                seen[k] = (uint32_t)i + 1;
+            }
+        }
+    };
+    // The dot arrives at position p (origin o): a nullable postdot nonterminal is also skipped, the end of the rule is the
+    // canonical "lhs complete since o" item.
+    void advanced(Work &w, uint32_t p, uint32_t o) const {
+        for (;; p++) {
+            const uint16_t code = t.sym[p];
+            const int kind = code >> SYM_KIND_SHIFT;
+            if (kind == SYM_END) { w.insert(Item{t.end_pos[code & SYM_ID_MASK], 0, o}); return; }
+            if (kind == SYM_TERM) { w.insert(Item{(uint16_t)p, t.term_start[code & SYM_ID_MASK], o}); return; }
+            w.insert(Item{(uint16_t)p, 0, o});
+            if (!(code & SYM_NULLABLE_BIT)) return;
         }
     }
-    void record(uint32_t s, int cl, const StepResult &r, const Work &w) {
+    void look_ahead(uint32_t s, int cl, Work &w) const {
+        w.set.clear(); w.accepted = false;
+        const State &src = st(s);
+        for (uint32_t i = 0; i < src.n_items; i++) {           // Scan
+            const Item it = src.items[i];
+            const uint16_t code = t.sym[it.p];
+            if ((code >> SYM_KIND_SHIFT) == SYM_TERM) {
+                const uint16_t q2 = t.delta[(size_t)it.q * t.n_cls + cl];
+                if (q2 == DFA_DEAD) continue;
+                const uint8_t f = t.qflags[q2];
+                if (f & QF_CONT) w.insert(Item{it.p, q2, it.o});
+                if (f & QF_ACCEPT) advanced(w, it.p + 1u, it.o);
+            } else if ((code >> SYM_KIND_SHIFT) == SYM_NT) {
+                const size_t at = (size_t)(code & SYM_ID_MASK_NT) * t.n_cls + cl;
+                for (uint32_t k = t.scan_off[at]; k < t.scan_off[at + 1]; k++) {
+                    const uint16_t p0 = t.scan_list[k] & 0xFFFF, q2 = t.scan_list[k] >> 16;
+                    const uint8_t f = t.qflags[q2];
+                    if (f & QF_CONT) w.insert(Item{p0, q2, s});
+                    if (f & QF_ACCEPT) advanced(w, p0 + 1u, s);
+                }
+            }
+        }
+        for (size_t i = 0; i < w.set.size(); i++) {            // Complete (the set grows on the way)
+            const Item it = w.set[i];
+            const uint16_t code = t.sym[it.p];
+            if ((code >> SYM_KIND_SHIFT) != SYM_END) continue;
+            const int X = code & SYM_ID_MASK;
+            if (X == t.N - 1) { w.accepted = true; continue; }
+            const State &org = st(it.o);
+            for (uint32_t j = 0; j < org.n_items; j++) {
+                const Item y = org.items[j];
+                const uint16_t yc = t.sym[y.p];
+                if ((yc >> SYM_KIND_SHIFT) != SYM_NT) continue;
+                const size_t at = (size_t)(yc & SYM_ID_MASK_NT) * t.N + X;
+                for (uint32_t k = t.comp_off[at]; k < t.comp_off[at + 1]; k++) {
+                    const uint16_t p = t.comp_list[k];
+                    if (p == COMP_ADVANCE_WAITING) advanced(w, y.p + 1u, y.o);
+                    else w.insert(Item{p, (t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM ? t.term_start[t.sym[p] & SYM_ID_MASK] : (uint16_t)0, it.o});
+                }
+            }
+        }
+        w.alive = !w.set.empty();
+        size_t n = 0;                                          // completed items only matter while their own set is worked on (Figure 3, first rule)
+        for (const Item &it : w.set) if ((t.sym[it.p] >> SYM_KIND_SHIFT) != SYM_END) w.set[n++] = it;
+        w.set.resize(n);
+    }
+    void record(uint32_t s, int cl, const Work &w) {
         n_steps++;
-        st(s).acc[cl] = r.accepted;
-        if (!r.alive) { st(s).trans[cl] = DEAD; return; }
-        if (!r.kernel_nonempty) { st(s).trans[cl] = SINK; return; }
-        const uint32_t last = w.c.n_sets() - 1;
-        std::vector<Item> out(w.c.items.begin() + w.c.set_off[last], w.c.items.end());
-        for (Item &it : out) it.o = w.ids[it.o];               // items scanned from predictions started in the source set: index last - 1 = s
-        st(s).trans[cl] = intern(std::move(out));
+        const uint32_t to = !w.alive ? DEAD : w.set.empty() ? SINK : intern(w.set.data(), (uint32_t)w.set.size());
+        st(s).acc[cl] = w.accepted;
+        st(s).trans[cl] = to;
     }
 
     // The state that holds exactly `items` (origins are state ids), made if it is new.
-    uint32_t intern(std::vector<Item> &&items) {
-        std::vector<uint32_t> key;
-        key.reserve(2 * items.size());
-        for (const Item &it : items) { key.push_back((uint32_t)it.p | ((uint32_t)it.q << 16)); key.push_back(it.o); }
-        auto found = interned.find(key);
-        if (found != interned.end()) return found->second;
-        n_items += (int64_t)items.size();
-        uint32_t w = (uint32_t)items.size();
-        for (const Item &it : items) w = std::max(w, st(it.o).widest);
-        const uint32_t id = add(std::move(items), w);
-        interned.emplace(std::move(key), id);
+    uint32_t intern(const Item *items, uint32_t n) {
+        uint32_t h = n;
+        for (uint32_t i = 0; i < n; i++) h = (h ^ Work::hash(items[i])) * 0x01000193u + (h >> 13);
+        uint32_t k = h & (uint32_t)(interned.size() - 1);
+        for (; interned[k]; k = (k + 1) & (uint32_t)(interned.size() - 1)) {
+            const State &x = st(interned[k]);
+            if (x.sig == h && x.n_items == n && std::equal(items, items + n, x.items, Work::same)) return interned[k];
+        }
+        n_items += n;
+        uint32_t w = n;
+        for (uint32_t i = 0; i < n; i++) w = std::max(w, st(items[i].o).widest);
+        const uint32_t id = add(items, n, w, h);
+        interned[k] = id;
+        if (2 * (size_t)n_states > interned.size()) {
+            interned.assign(2 * interned.size(), 0);
+            for (uint32_t id2 = ROOT + 1; id2 < n_states; id2++) {
+                k = st(id2).sig & (uint32_t)(interned.size() - 1);
+                while (interned[k]) k = (k + 1) & (uint32_t)(interned.size() - 1);
+                interned[k] = id2;
+            }
+        }
         return id;
     }
 
-    void compute(uint32_t s, uint8_t byte) {
-        Work w;
-        lay_out(s, w);
-        const StepResult r = earley_step(t, w.c, byte, false, nullptr);
-        record(s, t.cls[byte], r, w);
+    void compute(uint32_t s, int cl, Work &w) {
+        look_ahead(s, cl, w);
+        record(s, cl, w);
     }
 
     // One byte from state s; returns the next state, SINK or DEAD.
     uint32_t step(uint32_t s, uint8_t byte, bool *accepted) {
         if (s == SINK) { if (accepted) *accepted = false; return DEAD; }
         const int cl = t.cls[byte];
-        if (st(s).trans[cl] == NONE) compute(s, byte);
+        static thread_local Work w;
+        if (st(s).trans[cl] == NONE) compute(s, cl, w);
         if (accepted) *accepted = st(s).acc[cl] != 0;
         return st(s).trans[cl];
     }
@@ -156,7 +247,7 @@ struct HostAutomaton {
             std::vector<Item> items(c.items.begin() + c.set_off[k], c.items.begin() + c.set_off[k + 1]);
             if (items.empty()) { name[k] = SINK; continue; }
             for (Item &it : items) it.o = it.o < k ? name[it.o] : ROOT;
-            name[k] = intern(std::move(items));
+            name[k] = intern(items.data(), (uint32_t)items.size());
         }
         return name[c.n_sets() - 1];
     }

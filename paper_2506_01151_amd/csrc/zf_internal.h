@@ -2,8 +2,12 @@
 #pragma once
 #include <cstdint>
 #include <memory>
+#include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 #include "zf_device.h"
 #include "../../include/zapformat.h"
@@ -13,6 +17,18 @@ namespace zf {
 
 struct HostAutomaton;
 void set_error(const std::string &msg);   // thread-local detail string
+
+// f(0) .. f(n - 1) on up to n_threads threads, the caller's among them (each takes the next number).
+template <class F>
+void parallel_for(size_t n, unsigned n_threads, F f) {
+    std::atomic<size_t> next{0};
+    auto work = [&]() { for (size_t k; (k = next.fetch_add(1, std::memory_order_relaxed)) < n;) f(k); };
+    n_threads = (unsigned)std::min<size_t>(std::min(n_threads, std::max(1u, std::thread::hardware_concurrency())), n);
+    std::vector<std::thread> more;
+    struct Join { std::vector<std::thread> &t; ~Join() { for (auto &x : t) x.join(); } } join{more};
+    for (unsigned k = 1; k < n_threads; k++) { try { more.emplace_back(work); } catch (const std::system_error &) { break; } }
+    work();
+}
 
 // ---- byte-level DFA of one terminal ---------------------------------------------------
 struct Dfa {

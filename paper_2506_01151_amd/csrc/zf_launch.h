@@ -209,6 +209,9 @@ uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch);
 hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s);
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s);
+// The store, cleared, whose headers, items and table rows of the states below n_states were copied in from the host: their places in the
+// hash table, and how far the store is filled.
+hipError_t launch_store_adopt(const StoreView &G, uint32_t n_states, uint32_t n_items, hipStream_t s);
 // n charts (packed as for the other mask kernels) become states; import_root[group[k]] = the state of chart k's current set (AT_FAIL: no room)
 hipError_t launch_store_import(const StoreView &G, const RowChart *charts, const uint32_t *set_off, const Item *items, const uint32_t *group,
                                uint32_t n, uint32_t *import_root, hipStream_t s);

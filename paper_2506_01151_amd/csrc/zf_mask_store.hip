@@ -105,7 +105,16 @@ struct StoreSets {             // resolves the name of a set to its items (devic
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Scratch { uint32_t *w, *o, *h; uint32_t cap; };   // one wavefront's set under construction (+ hash table of the wide step)
 
-// true when state `id` holds exactly the `kept` items in the scratch
+// A set's signature does not depend on the order of its items (the host, which fills the store when the engine is compiled, the
+// narrow and the wide byte step each make them in an order of their own): the sum of its items' words, closed with their count.
+__host__ __device__ __forceinline__ uint32_t item_sum(uint32_t w, uint32_t o) {
+    uint32_t x = (w * 0x9E3779B1u) ^ (o * 0x85EBCA77u);
+    x ^= x >> 15; x *= 0x2C1B3C6Du; x ^= x >> 13;
+    return x * 0x297A2D39u;
+}
+__host__ __device__ __forceinline__ uint32_t set_signature(uint32_t sum, uint32_t n) { const uint32_t h = (sum ^ n) * 0x9E3779B1u; return (h ^ h >> 16) | 1u; }   // never 0: 0 marks a free slot of the hash table
+
+// true when state `id` holds exactly the `kept` items in the scratch, in whatever order
 __device__ __forceinline__ bool same_content(const StoreView &G, uint32_t id, const Scratch &sc, uint32_t kept, uint32_t lane) {
     if (id == 0 || id >= G.cap_states) return false;
     const uint2 hj = G.hdr[id];
@@ -116,7 +125,21 @@ __device__ __forceinline__ bool same_content(const StoreView &G, uint32_t id, co
         if (i0 + lane < kept) { const uint2 x = G.arena[hj.x + i0 + lane]; ne = x.x != lds_load(&sc.w[i0 + lane]) || x.y != lds_load(&sc.o[i0 + lane]); }
         diff |= __ballot(ne);
     }
-    return diff == 0;
+    if (diff == 0) return true;
+    // another order, if it is the same set: both hold each item once, so it is when every one of these is among those
+    for (uint32_t i0 = 0; i0 < kept; i0 += 64) {
+        const bool mine = i0 + lane < kept;
+        const uint32_t w = mine ? lds_load(&sc.w[i0 + lane]) : 0u, o = mine ? lds_load(&sc.o[i0 + lane]) : 0u;
+        bool found = !mine;
+        for (uint32_t j0 = 0; j0 < kept && __ballot(!found); j0 += 64) {
+            uint2 x = make_uint2(0, 0);
+            if (j0 + lane < kept) x = G.arena[hj.x + j0 + lane];
+            const uint32_t n = kept - j0 < 64u ? kept - j0 : 64u;
+            for (uint32_t j = 0; j < n; j++) found |= w == (uint32_t)__builtin_amdgcn_readlane((int)x.x, (int)j) && o == (uint32_t)__builtin_amdgcn_readlane((int)x.y, (int)j);
+        }
+        if (__ballot(!found)) return false;
+    }
+    return true;
 }
 
 // The transition of state s on class cl: one Earley byte step, then the state that holds the
@@ -141,16 +164,11 @@ __device__ __forceinline__ uint32_t store_transition(const TV &T, const StoreVie
     if (st != AUT_OK) return AT_FAIL;
     if (nnew == 0) return AT_DEAD;
     if (kept == 0) return AT_SINK;
-    // signature of the content (never 0: 0 marks a free slot of the hash table)
-    uint32_t h = 0x811C9DC5u;
-    for (uint32_t i0 = 0; i0 < kept; i0 += 64) {
-        uint32_t x = 0;
-        if (i0 + lane < kept) { x = (lds_load(&sc.w[i0 + lane]) * 0x9E3779B1u) ^ (lds_load(&sc.o[i0 + lane]) * 0x85EBCA77u); x ^= x >> 15; x *= (2u * (i0 + lane) + 1u) * 0x2C1B3C6Du; }
+    uint32_t sum = 0;
+    for (uint32_t i0 = 0; i0 < kept; i0 += 64) if (i0 + lane < kept) sum += item_sum(lds_load(&sc.w[i0 + lane]), lds_load(&sc.o[i0 + lane]));
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
-        h = (h ^ x) * 0x01000193u;
-    }
-    h = (uint32_t)__builtin_amdgcn_readfirstlane((int)(h ^ kept)) | 1u;
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane((int)set_signature(sum, kept));
     uint32_t slot = (h * 0x9E3779B1u) & G.intern_mask;
     for (uint32_t probes = 0; probes <= G.intern_mask; probes++) {
         const unsigned long long e = __hip_atomic_load(&G.intern[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -747,6 +765,24 @@ __global__ __launch_bounds__(256) void store_clear_kernel(StoreView G, uint32_t 
     if (i == 0) { G.ctl[0] = STORE_ROOT + 1; G.ctl[1] = n_root; G.ctl[2] = 0; G.ctl[3] = 0; }
 }
 
+// The states the host has filled in get their places in the hash table, one lane per state (sets of a few items), and the store
+// its counts.  State 1 is never looked for.
+__global__ __launch_bounds__(256) void store_adopt_kernel(StoreView G, uint32_t n_states, uint32_t n_items) {
+    const uint32_t id = blockIdx.x * 256 + threadIdx.x;
+    if (id == 0) { G.ctl[0] = n_states; G.ctl[1] = n_items; }
+    if (id <= STORE_ROOT || id >= n_states) return;
+    const uint2 hj = G.hdr[id];
+    if (hj.x > n_items || hj.y > n_items - hj.x) return;
+    uint32_t sum = 0;
+    for (uint32_t i = 0; i < hj.y; i++) { const uint2 x = G.arena[hj.x + i]; sum += item_sum(x.x, x.y); }
+    const uint32_t h = set_signature(sum, hj.y);
+    uint32_t slot = (h * 0x9E3779B1u) & G.intern_mask;
+    for (uint32_t probes = 0; probes <= G.intern_mask; probes++) {
+        if (atomicCAS(&G.intern[slot], 0ull, ((unsigned long long)h << 32) | id) == 0ull) return;
+        slot = (slot + 1) & G.intern_mask;
+    }
+}
+
 // Bring rows whose state the store does not know (after the store was cleared, or after more bytes than
 // a call carries) in from their host charts: every set of the packed chart becomes a state of its own,
 // origins renamed from set indices to the new names.  One block per such row.
@@ -818,6 +854,11 @@ hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t
 
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s) {
     hipLaunchKernelGGL(store_clear_kernel, dim3(2048), dim3(256), 0, s, G, ncls, (const uint2 *)root_items, n_root);
+    return hipGetLastError();
+}
+
+hipError_t launch_store_adopt(const StoreView &G, uint32_t n_states, uint32_t n_items, hipStream_t s) {
+    hipLaunchKernelGGL(store_adopt_kernel, dim3((n_states + 255) / 256), dim3(256), 0, s, G, n_states, n_items);
     return hipGetLastError();
 }
 

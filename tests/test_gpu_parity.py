@@ -631,6 +631,17 @@ def test_exploration_at_compile_time_changes_no_mask(torch_cuda, oracle_lib):
     assert steps_taken[0] < steps_taken[-1], steps_taken
 
 
+@pytest.mark.parametrize("pre", [1, 2, 33, 1025, 0], ids=lambda p: f"budget-{p}")
+@pytest.mark.parametrize("cfg_id", [2, 5])
+def test_store_filled_from_the_host_automaton(cfg_id, pre, torch_cuda, oracle_lib):
+    """Where the exploration's budget ends, the device goes on by itself from states the host has filled in: a budget of one state,
+    budgets in the middle of a block of states and just beyond one, and the default; recursive grammars, one of them ambiguous
+    (sets the host and the device make in different orders have one name)."""
+    import paper_2506_01151_amd as zf
+    cfg = configs.CONFIGS[cfg_id]
+    _run_parity(torch_cuda, zf, oracle_lib.Oracle, cfg.grammar(), cfg.vocab(3000), 5, 14, 4711, walk_mode=2, precompute_states=pre)
+
+
 @pytest.mark.parametrize("cap", [None, 72, 200], ids=["default-budget", "budget-72", "budget-200"])
 def test_wide_sets_of_an_ambiguous_grammar(cap, torch_cuda, oracle_lib):
     """Sets far beyond 64 items (the ambiguous expression grammar after sums of 20 to 150 operands: every
