@@ -202,7 +202,9 @@ int zf_compute_mask_apply_async(zf_engine *e, zf_state *const *states /* host ar
 /* zf_compute_mask for callers that cannot allocate device memory: tight serving loops, harnesses
  * that forbid hipMalloc, code that runs while a HIP graph is being captured on another stream.  Same
  * arguments, same result, same waiting behaviour as zf_compute_mask, but the call allocates nothing
- * (no hipMalloc, hipHostMalloc, hipFree): every per-call device buffer (counters, rank-ordered verdict
+ * (no hipMalloc, hipHostMalloc, hipFree).  The persistent automaton (walk_mode 2) has its memory since
+ * zf_compile; on the other paths -- walk_mode 0 or 1, pruning off, an explicit lane_item_cap, a call the
+ * automaton has no room for -- every per-call device buffer (counters, rank-ordered verdict
  * words, fallback list and arenas, the trie walk's queue and chart copy) is a slice of one static
  * device array of 16 MiB that each GPU the library runs on holds until the process ends, and the
  * packed charts must fit the 256 KiB of pinned staging memory every engine owns from zf_compile on.

@@ -1007,7 +1007,8 @@ static int state_cache_lookup(DeviceSide *d, const std::vector<std::vector<uint3
     return n_hits;
 }
 
-static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, uint32_t slot);
+static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, uint32_t slot);
+static const int STORE_NO_ROOM = 1;                       // enqueue_store_impl: the call does not fit the memory at hand (noalloc); nothing was enqueued
 // zf_compute_mask_apply_async: the logits the call's mask is to be applied to.  The mask kernel over the persistent automaton
 // takes them along when it can (fused = true); whoever set the request launches the logit-masking kernel otherwise.
 struct ApplyRequest { const void *logits = nullptr; void *out = nullptr; int64_t stride = 0; int32_t dtype = 0; bool fused = false; };
@@ -1016,8 +1017,10 @@ static thread_local ApplyRequest g_apply;
 // Pack and upload the charts and enqueue the kernels of one compute_mask call: upload, mask kernel,
 // closing kernel (fallback pass for what the mask kernel listed + permutation into token order),
 // gather when the state cache is on.  wait = true: also wait and return the final status.
-// noalloc = true (zf_compute_mask_noalloc): every per-call device buffer is a slice of the device's static scratch array,
-// the state cache is passed by, and a call that does not fit the array or the staging room is refused.
+// noalloc = true (zf_compute_mask_noalloc): the state cache is passed by and nothing is allocated.  The persistent automaton has
+// its memory since zf_compile (a step of 16 rows of a JSON schema takes 29 us through it, 61 through the per-block automaton, to
+// which such calls went before); on the other paths every per-call device buffer is a slice of the device's static scratch array,
+// and a call that does not fit the array or the staging room is refused.
 static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, bool per_block) {
     if (!e || !states || batch <= 0 || batch > MAX_BATCH || !d_mask) return fail(ZF_ERR_INVALID_ARG, "bad argument (batch must be 1..4096)");
     DeviceSide *d = e->dev;
@@ -1029,7 +1032,11 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     if (d->pending) HIP_TRY(hipEventSynchronize(d->stage_done[slot]));   // the slot's previous upload has left the staging buffer (with no call in flight zf_mask_wait has seen to that)
     for (int b = 0; b < batch; b++)
         if (!states[b] || states[b]->eng != e) return fail(ZF_ERR_INVALID_ARG, "state " + std::to_string(b) + " is null or belongs to another engine");
-    if (e->store_on && !noalloc && !per_block) return enqueue_store_impl(e, states, batch, d_mask, hip_stream, wait, slot);
+    // (noalloc with an explicit item budget: the budget is one of the per-block automaton's wavefronts)
+    if (e->store_on && !per_block && !(noalloc && !e->lane_cap_auto)) {
+        const int rc = enqueue_store_impl(e, states, batch, d_mask, hip_stream, wait, noalloc, slot);
+        if (rc != STORE_NO_ROOM) return rc;
+    }
     catch_up_batch(states, batch);                        // these paths send the charts
     // ---- the packed form of every row: [n_sets][set offsets][item word, origin]... (also the cache key) ----
     static thread_local std::vector<std::vector<uint32_t>> packed;
@@ -1425,7 +1432,7 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
     return all;
 }
 
-static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, uint32_t slot) {
+static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, uint32_t slot) {
     DeviceSide *d = e->dev;
     HostAutomaton &A = *e->host_aut;
     hipStream_t stream = (hipStream_t)hip_stream;
@@ -1477,7 +1484,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     }
     const int ng = (int)c.g.size();
     // ---- state cache (Section 5.2): groups whose finished mask is in the pool, and slots for the others ----
-    const bool sc = !d->cache.empty() && (size_t)batch * 2 <= d->cache.size();
+    const bool sc = !noalloc && !d->cache.empty() && (size_t)batch * 2 <= d->cache.size();
     int n_miss = 0, n_hits = 0;
     if (sc) {
         if (d->pool_epoch != e->host_epoch) { forget_cached_masks(d); d->pool_epoch = e->host_epoch; }
@@ -1574,6 +1581,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
     const size_t off_items = align16(off_so + 4 * n_off), off_imp = align16(off_items + sizeof(Item) * n_items);
     const size_t total = off_imp + 4 * (size_t)n_imp + 16;
+    if (noalloc && (total > d->stage_cap[slot] || (big && up_bytes > NOALLOC_SCRATCH_BYTES))) return STORE_NO_ROOM;
     if (total > d->stage_cap[slot]) {
         if (d->h_stage[slot]) (void)hipHostFree(d->h_stage[slot]);
         d->h_stage[slot] = nullptr; d->stage_cap[slot] = 0;
@@ -1581,7 +1589,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         HIP_TRY(hipHostMalloc(&d->h_stage[slot], cap, hipHostMallocDefault));
         d->stage_cap[slot] = cap;
     }
-    if (big && up_bytes > d->chart_cap) {
+    if (big && !noalloc && up_bytes > d->chart_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
         if (d->d_chart) (void)hipFree(d->d_chart);
         d->d_chart = nullptr; d->chart_cap = 0;
@@ -1692,10 +1700,11 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     a.out_mask = d_mask; a.pool = d->d_pool; a.konst = d->d_konst;
     a.spilled = (const StoreRow *)(stage + off_spill); a.entries = (const uint32_t *)(stage + off_ent); a.pending = stage + off_pend;
     a.import_root = d->d_import_root;
+    uint8_t *const uploaded = noalloc ? d->scratch : (uint8_t *)d->d_chart;
     if (big) {
-        a.groups = (const StoreGroup *)d->d_chart;
-        a.block_of = (const uint32_t *)((const uint8_t *)d->d_chart + off_block);
-        a.members = (const uint16_t *)((const uint8_t *)d->d_chart + off_mem);
+        a.groups = (const StoreGroup *)uploaded;
+        a.block_of = (const uint32_t *)(uploaded + off_block);
+        a.members = (const uint16_t *)(uploaded + off_mem);
     } else if (batch > STORE_INLINE_ROWS) a.members = (const uint16_t *)(stage + off_mem);
     a.tickets = d->d_tickets;
     a.status = (unsigned long long *)d->h_store_status + slot * STORE_STATUS_WORDS;
@@ -1711,7 +1720,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     d->report.cache_rows = (int32_t)n_cache_rows;
     d->report.main_ms = d->report.fallback_ms = d->report.permute_ms = 0.f;
     d->report.overflow_chunks = d->report.walk_chunks = d->report.parser_steps = 0;
-    if (big) HIP_TRY(launch_upload(stage, d->d_chart, up_bytes, stream));
+    if (big) HIP_TRY(launch_upload(stage, uploaded, up_bytes, stream));
     if (n_imp) HIP_TRY(launch_store_import(d->store, (const RowChart *)(stage + off_rows), (const uint32_t *)(stage + off_so), (const Item *)(stage + off_items),
                                            (const uint32_t *)(stage + off_imp), (uint32_t)n_imp, d->d_import_root, stream));
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
@@ -1736,7 +1745,7 @@ static int enqueue_mask(zf_engine *e, zf_state *const *states, int32_t batch, ui
     if (d && e->store_on && d->store_backoff) { d->store_backoff--; per_block = true; }
     int rc = enqueue_mask_impl(e, states, batch, d_mask, hip_stream, wait, noalloc, per_block);
     if (rc != ZF_OK && d) forget_cached_masks(d);
-    if (rc == ZF_ERR_OVERFLOW && d && e->store_on && !noalloc && !per_block) {
+    if (rc == ZF_ERR_OVERFLOW && d && e->store_on && !per_block && !(noalloc && !e->lane_cap_auto)) {
         // A set outgrew a wavefront's scratch, or the store filled up within one call.  The waiting call answers through the
         // per-block automaton, whose fallback pass has room in global memory; either way the next calls go that way too,
         // for longer each time it happens, and the store starts over when it is used again.
