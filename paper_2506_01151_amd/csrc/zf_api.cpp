@@ -1370,17 +1370,21 @@ struct StoreCall {                 // one call's working memory, kept per thread
 // many tokens their token-mask cache rows leave undecided, which was counted once per list of cache rows.  The grid is never
 // larger than what the chip holds at once: a block that had to wait for a place would start from nothing (LDS cache, the
 // group's state) when the others are nearly done, which costs more than a few more passes of the wavefronts that are there.
-static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget, double apply_us_per_word) {
+static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget, int logit_bytes) {
     const int n = (int)g.size();
     static thread_local std::vector<double> inv_cost;
     static thread_local std::vector<int> segs, passes;
     inv_cost.resize(n); segs.resize(n); passes.resize(n);
     double lo = 1e30;
+    const double apply_us_per_word = 0.25 * 32 * logit_bytes * 2 / 1024;
     for (int r = 0; r < n; r++) {
         // words per segment: as many as are expected to hold 48 undecided tokens, at most 64 (a batch is 64: the
         // tokens are spread unevenly, and a second, nearly empty batch costs as much as a full one)
         const double und = g[r].undecided;
-        const int sw = g[r].pooled ? 16 : (int)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 48.0 * std::max(1, V) / (32.0 * std::max(und, 1.0))));
+        int sw = g[r].pooled ? 16 : (int)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 48.0 * std::max(1, V) / (32.0 * std::max(und, 1.0))));
+        // where the logits are masked too: no more words than the logits a wavefront requests ahead for all rows of the group
+        // (two pieces of 16 bytes per lane), so that nothing is waited for at the end while there are wavefronts to spare
+        if (logit_bytes) sw = std::min(sw, std::max(1, STORE_AHEAD_BYTES / (32 * logit_bytes * g[r].n)));
         segs[r] = std::max(1, (W + sw - 1) / sw);
         g[r].seg_w = sw;
         // what a pass costs a wavefront (microseconds, measured): an empty segment 2.8, a segment with a batch 3.7, each further
@@ -1603,7 +1607,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     while (scratch > 32 && store_lds_bytes(d->tab, d->mode, scratch) > (uint32_t)STORE_LDS_MAX) scratch -= 32;
     const uint32_t lds = store_lds_bytes(d->tab, d->mode, scratch);
     if (lds > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
-    double apply_us_per_word = 0;
+    int logit_bytes = 0;                                  // of a logit the mask kernel masks itself
     if (g_apply.out) {
         const size_t esz = g_apply.dtype == 0 ? 4 : 2;
         const bool whole = (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
@@ -1612,11 +1616,11 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         if (whole && 2ull * (uint64_t)batch * (uint64_t)e->V * esz <= STORE_FUSE_BYTES) {
             a.logits = g_apply.logits; a.out = g_apply.out; a.stride = g_apply.stride; a.dtype = (uint8_t)(g_apply.dtype + 1);
             g_apply.fused = true;
-            apply_us_per_word = 0.25 * 32 * (double)esz * 2 / 1024;
+            logit_bytes = (int)esz;
         }
     }
     const int budget = std::max(ng, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
-    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, apply_us_per_word);
+    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes);
     // ---- the records ----
     {
         uint8_t *h = (uint8_t *)d->h_stage[slot];

@@ -425,23 +425,39 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
         return m0 + lane < n_members ? (a.members ? a.members[k] : in.member[k]) : 0u;
     };
     uint32_t members = members_from(0);
-    // Logits (APPLY builds): 16-byte pieces, the first two of every lane of the first member requested one pass ahead (those of
-    // the first segment here), so that they wait in registers when the segment's verdicts are in.
+    // Logits (APPLY builds): the segment's 16-byte pieces of all members in hand as ONE run -- the first member's pieces, then the
+    // second's, ... -- so that every lane has one to move whatever the width of the segment, and so that the pieces of
+    // several members travel together (one member after the other, a memory round trip each, cost a group of 16 rows 8 us).  The
+    // first PRE pieces of every lane are requested one pass ahead (those of the first segment here): they wait in registers when
+    // the segment's verdicts are in.
     typedef typename Piece<APPLY>::type piece_t;
     constexpr uint32_t tp = APPLY == 2 ? 8u : 4u, esz = APPLY == 2 ? 2u : 4u;   // tokens per 16-byte piece, bytes per logit
     auto tokens_of = [&](uint32_t g) -> uint32_t {
         const uint32_t tok0 = g * sw * 32u;
         return g < n_seg && tok0 < a.V ? (sw * 32u < a.V - tok0 ? sw * 32u : a.V - tok0) : 0u;
     };
-    auto logits_at = [&](uint32_t row, uint32_t g) -> size_t { return ((size_t)row * (size_t)a.stride + g * sw * 32u) * esz; };
-    auto logits_ahead = [&](uint32_t row, uint32_t g, u32x4 (&pre)[2]) __attribute__((always_inline)) {
-        const uint32_t pieces = tokens_of(g) / tp;
-        const piece_t *src = reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + logits_at(row, g));
-#pragma unroll
-        for (int u = 0; u < 2; u++) { pre[u] = u32x4{0, 0, 0, 0}; if ((uint32_t)u * 64u + lane < pieces) pre[u] = __builtin_nontemporal_load(src + (uint32_t)u * 64u + lane); }
+    // number i of a run of `per` things per member: which member, and which of its things.  i < 2^15 and per <= 512, so the
+    // half added keeps the product at least 1 / 1024 away from the next whole number, far more than single precision loses
+    auto split = [&](uint32_t i, uint32_t per, float inv, uint32_t &k) -> uint32_t { k = (uint32_t)(((float)i + 0.5f) * inv); return i - k * per; };
+    auto byte_of = [&](uint32_t k, uint32_t g, uint32_t t) -> size_t {   // of token t of segment g in the k-th member's row
+        return ((size_t)(uint32_t)__shfl((int)members, (int)(k & 63u)) * (size_t)a.stride + g * sw * 32u + t) * esz;
     };
-    u32x4 l_pre[2];
-    if (APPLY) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members), unit, l_pre);
+    constexpr int PRE = 2;
+    auto logits_ahead = [&](uint32_t g, u32x4 (&pre)[PRE]) __attribute__((always_inline)) {
+        const uint32_t per = tokens_of(g) / tp, total = per * (n_members < 64u ? n_members : 64u);
+        const float inv = __builtin_amdgcn_rcpf((float)(per ? per : 1u));
+#pragma unroll
+        for (int u = 0; u < PRE; u++) {
+            const uint32_t i = (uint32_t)u * 64u + lane;
+            uint32_t k;
+            const uint32_t p = split(i < total ? i : 0u, per, inv, k);
+            const size_t at = byte_of(k, g, p * tp);
+            pre[u] = u32x4{0, 0, 0, 0};
+            if (i < total) pre[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + at));
+        }
+    };
+    u32x4 l_pre[PRE];
+    if (APPLY) logits_ahead(unit, l_pre);
     auto transition = [&](uint32_t s, uint32_t cl) __attribute__((always_inline)) -> uint32_t {
         steps++;
         return store_transition_call<MODE>(a.konst, (LdsBytes *)smem, (uint32_t)a.scratch | (a.wide ? SCRATCH_WIDE : 0u) | wave << 24, errors, s, cl);
@@ -542,8 +558,8 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
 #pragma unroll
         for (int j = 1; j < RAW; j++) { v |= wd.v[j]; c |= wd.c[j]; }
         wd = request(g + n_units);                           // the next segment's words travel while this one's tokens are checked
-        u32x4 l_nxt[2];
-        if (APPLY) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members), g + n_units, l_nxt);   // and so do its first logits
+        u32x4 l_nxt[PRE];
+        if (APPLY) logits_ahead(g + n_units, l_nxt);         // and so do its first logits
         if (!pooled) {
             if (slots_log2 <= 4u) { v |= __shfl_xor(v, 16); c |= __shfl_xor(c, 16); }
             if (slots_log2 <= 5u) { v |= __shfl_xor(v, 32); c |= __shfl_xor(c, 32); }
@@ -715,37 +731,52 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
                     return x;
                 };
                 auto bits_at = [&](uint32_t t) -> uint32_t { return (uint32_t)__shfl((int)v, (int)((t >> 5) & 63u)) >> (t & 31u); };   // all lanes call it together
-                for (uint32_t k = 0; k < n; k++) {
-                    const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)members, (int)k);
-                    const size_t at = logits_at(row, g);
-                    const piece_t *src = reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + at);
-                    piece_t *dst = reinterpret_cast<piece_t *>(reinterpret_cast<uint8_t *>(a.out) + at);
-                    auto put = [&](uint32_t p, u32x4 x) { const uint32_t mb = bits_at(p * tp); if (p < pieces) __builtin_nontemporal_store(masked(x, mb), dst + p); };
-                    u32x4 cur[2] = {l_pre[0], l_pre[1]};
-                    if (k + 1 < n) logits_ahead((uint32_t)__builtin_amdgcn_readlane((int)members, (int)((k + 1) & 63u)), g, l_pre);   // the next member's first pieces
-                    else if (m0 + 64 < n_members) logits_ahead((uint32_t)__builtin_amdgcn_readfirstlane((int)members_from(m0 + 64)), g, l_pre);
-                    put(lane, cur[0]);
-                    if (pieces > 64u) put(64u + lane, cur[1]);
-                    for (uint32_t p0 = 128; p0 < pieces; p0 += 256) {   // what was not requested ahead: four pieces per lane in flight
-                        u32x4 x[4];
+                const uint32_t run = pieces * n;
+                const float inv = __builtin_amdgcn_rcpf((float)(pieces ? pieces : 1u));
+                const uint8_t *src = reinterpret_cast<const uint8_t *>(a.logits);
+                uint8_t *dst = reinterpret_cast<uint8_t *>(a.out);
+                auto where = [&](uint32_t i, uint32_t &p) -> size_t { uint32_t k; p = split(i < run ? i : 0u, pieces, inv, k); return byte_of(k, g, p * tp); };
+                auto put = [&](uint32_t i, u32x4 x) { uint32_t p; const size_t at = where(i, p); const uint32_t mb = bits_at(p * tp); if (i < run) __builtin_nontemporal_store(masked(x, mb), reinterpret_cast<piece_t *>(dst + at)); };
+                uint32_t i0 = 0;
+                if (m0 == 0) {                               // what was requested ahead
 #pragma unroll
-                        for (int u = 0; u < 4; u++) { const uint32_t p = p0 + (uint32_t)u * 64u + lane; x[u] = u32x4{0, 0, 0, 0}; if (p < pieces) x[u] = __builtin_nontemporal_load(src + p); }
+                    for (int u = 0; u < PRE; u++) if ((uint32_t)u * 64u < run) put((uint32_t)u * 64u + lane, l_pre[u]);
+                    i0 = PRE * 64u;
+                }
+                for (; i0 < run; i0 += 256) {                // the others: four pieces per lane in flight
+                    u32x4 x[4];
 #pragma unroll
-                        for (int u = 0; u < 4; u++) if (p0 + (uint32_t)u * 64u < pieces) put(p0 + (uint32_t)u * 64u + lane, x[u]);
+                    for (int u = 0; u < 4; u++) {
+                        const uint32_t i = i0 + (uint32_t)u * 64u + lane;
+                        uint32_t p;
+                        const size_t at = where(i, p);
+                        x[u] = u32x4{0, 0, 0, 0};
+                        if (i < run) x[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(src + at));
                     }
-                    if (tail) {                              // the last tokens of a vocabulary that is no multiple of a piece
-                        const uint32_t t = pieces * tp + lane, keep = bits_at(t) & 1u;
-                        if (lane < tail) {
-                            if (APPLY == 2) reinterpret_cast<uint16_t *>(dst)[t] = keep ? reinterpret_cast<const uint16_t *>(src)[t] : (uint16_t)0xFF80u;
-                            else reinterpret_cast<uint32_t *>(dst)[t] = keep ? reinterpret_cast<const uint32_t *>(src)[t] : 0xFF800000u;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) if (i0 + (uint32_t)u * 64u < run) put(i0 + (uint32_t)u * 64u + lane, x[u]);
+                }
+                if (tail) {                                  // the last tokens of a vocabulary that is no multiple of a piece
+                    const uint32_t tails = tail * n;
+                    const float tinv = __builtin_amdgcn_rcpf((float)tail);
+                    for (uint32_t i = 0; i < tails; i += 64) {
+                        uint32_t k;
+                        const uint32_t t = pieces * tp + split(i + lane < tails ? i + lane : 0u, tail, tinv, k), keep = bits_at(t) & 1u;
+                        const size_t at = byte_of(k, g, t);
+                        if (i + lane < tails) {
+                            if (APPLY == 2) *reinterpret_cast<uint16_t *>(dst + at) = keep ? *reinterpret_cast<const uint16_t *>(src + at) : (uint16_t)0xFF80u;
+                            else *reinterpret_cast<uint32_t *>(dst + at) = keep ? *reinterpret_cast<const uint32_t *>(src + at) : 0xFF800000u;
                         }
                     }
                 }
             }
         }
         if ((flags & STORE_ROW_KEEP) && lane < slots && w < W) a.pool[(size_t)keep_slot * W + w] = v;
-        if (APPLY) { l_pre[0] = l_nxt[0]; l_pre[1] = l_nxt[1]; }
         if (n_members > 64u) members = members_from(0);
+        if (APPLY) {
+#pragma unroll
+            for (int u = 0; u < PRE; u++) l_pre[u] = l_nxt[u];
+        }
     }
     if (lane == 0 && steps) atomicAdd(&blk[1], steps);
     if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
