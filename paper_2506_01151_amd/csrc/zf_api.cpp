@@ -90,7 +90,7 @@ struct DeviceSide {
     bool store_dirty = true;                         // the store must be cleared before its next use
     // What sizes a call's grid: the tokens a state's token-mask cache rows leave to the parser.  The host keeps the token-order
     // rows and counts the union for every set of cache rows it meets, once (the sets repeat all the time).
-    std::vector<uint32_t> h_valid_tok, h_cd_tok;     // [Q + N][W]
+    std::vector<uint2> h_ci_tok;                     // [Q + N][W]
     std::unordered_map<uint64_t, uint32_t> undecided_of;   // signature of the list of cache rows -> undecided tokens
     uint32_t store_backoff = 0, store_backoff_next = 8;   // after a call the store had no room for: calls that take the per-block automaton instead
     // A call through the persistent automaton until zf_mask_wait has seen its status: the groups whose state the kernel reports,
@@ -115,6 +115,7 @@ struct DeviceSide {
     // with that name and no bytes to walk, whatever token took it there.  Valid while neither automaton has been emptied.
     std::vector<uint32_t> name_of_host;
     uint32_t name_host_epoch = 0, name_store_epoch = 0;
+    uint32_t closed_states = 0, closed_epoch = 0;    // in that epoch of the store every transition out of the states below closed_states is in it
     uint32_t name_find(uint32_t host_id, uint32_t host_epoch, uint32_t st_epoch) const {   // 0 = unknown
         return host_epoch == name_host_epoch && st_epoch == name_store_epoch && host_id < name_of_host.size() ? name_of_host[host_id] : 0u;
     }
@@ -288,8 +289,8 @@ int setup_device(zf_engine *e) {
             first[at_hand] = (uint8_t)(n > TOK_AT_HAND ? TOK_MORE : TOK_END);
             memcpy(&tok16[v], first, 16);
         }
-        std::vector<uint32_t> &valid_tok = d->h_valid_tok, &cd_tok = d->h_cd_tok;
-        valid_tok.assign(std::max<size_t>(n_rows * W, 1), 0); cd_tok.assign(std::max<size_t>(n_rows * W, 1), 0);
+        std::vector<uint2> &ci_tok = d->h_ci_tok;
+        ci_tok.assign(std::max<size_t>(n_rows * W, 1), make_uint2(0, 0));
         // A row's set bits are taken one by one and written at the tokens that carry the string (most rows -- the states of literal
         // terminals -- hold a handful).  Tokens by string: those of string r are tok_by[tok_at[r] ..].
         std::vector<uint32_t> tok_at((size_t)tr.n_strings + 2, 0), tok_by(V);
@@ -299,16 +300,16 @@ int setup_device(zf_engine *e) {
         parallel_for(n_rows, n_rows * V >= (size_t)1 << 20 ? 8 : 1, [&](size_t r) {
             for (int kind = 0; kind < 2; kind++) {
                 const uint32_t *src = (kind ? tr.ci_cd.data() : tr.ci_valid.data()) + r * tr.Wr;
-                uint32_t *dst = (kind ? cd_tok.data() : valid_tok.data()) + r * W;
+                uint2 *dst = ci_tok.data() + r * W;
                 for (size_t w = 0; w < (size_t)tr.Wr; w++)
                     for (uint32_t bits = src[w]; bits; bits &= bits - 1) {
                         const size_t k = w * 32 + (size_t)__builtin_ctz(bits);
                         if (k >= (size_t)tr.n_strings) break;     // bits of the last chunk beyond the strings
-                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) dst[tok_by[j] >> 5] |= 1u << (tok_by[j] & 31);
+                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) (kind ? dst[tok_by[j] >> 5].y : dst[tok_by[j] >> 5].x) |= 1u << (tok_by[j] & 31);
                     }
             }
         });
-        UP(tok16, tok16, nullptr); UP(ci_valid_tok, valid_tok, nullptr); UP(ci_cd_tok, cd_tok, nullptr);
+        UP(tok16, tok16, nullptr); UP(ci_tok, ci_tok, nullptr);
     }
     T.Q = t.Q;
 #undef UP
@@ -540,8 +541,8 @@ const char *zf_strerror(int code) {
 const char *zf_last_error(void) { return g_err.c_str(); }
 
 static bool wants_exploration(const zf_engine *e);
-static void explore_host(zf_engine *e, size_t cap_states, size_t cap_items);
-static void store_adopt(zf_engine *e);
+static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items);
+static void store_adopt(zf_engine *e, bool whole);
 
 int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_options *opt, zf_engine **out) {
     if (!g || !v || !out || v->V < 0 || (v->V && !v->off)) return fail(ZF_ERR_INVALID_ARG, "null argument");
@@ -562,6 +563,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
     if (e->opt.chunk_strings != 8 && e->opt.chunk_strings != 16 && e->opt.chunk_strings != 32) e->opt.chunk_strings = 8;
     if (e->opt.precompute_states == 0) e->opt.precompute_states = 65536;
     if (e->opt.precompute_states < 0) e->opt.precompute_states = 0;
+    bool whole = false;                                   // the explorer's answer
     std::thread explorer;                                 // the exploration needs the grammar tables only: it runs beside everything else
     struct Join { std::thread &t; ~Join() { if (t.joinable()) t.join(); } } join{explorer};
     auto give_up = [&](int rc) { if (explorer.joinable()) explorer.join(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
@@ -571,8 +573,8 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
         if (e->opt.walk_mode == 2 && e->opt.pruning != 0) e->host_aut = new HostAutomaton(e->tab);
         if (wants_exploration(e))
-            explorer = std::thread([e]() {
-                try { explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
+            explorer = std::thread([e, &whole]() {
+                try { whole = explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
@@ -584,7 +586,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         const int rc = setup_device(e);
         if (rc != ZF_OK) return give_up(rc);
     }
-    if (explorer.joinable()) { explorer.join(); store_adopt(e); }
+    if (explorer.joinable()) { explorer.join(); store_adopt(e, whole); }
     *out = e;
     return ZF_OK;
 }
@@ -1330,7 +1332,7 @@ static int64_t count_undecided(DeviceSide *d, const uint32_t *ent, uint32_t n) {
         uint32_t cnt = 0;
         for (size_t w = 0; w < Wt; w++) {
             uint32_t v = 0, cd = 0;
-            for (uint32_t k = 0; k < n; k++) { v |= d->h_valid_tok[ent[k] * Wt + w]; cd |= d->h_cd_tok[ent[k] * Wt + w]; }
+            for (uint32_t k = 0; k < n; k++) { v |= d->h_ci_tok[ent[k] * Wt + w].x; cd |= d->h_ci_tok[ent[k] * Wt + w].y; }
             cnt += (uint32_t)__builtin_popcount(cd & ~v);
         }
         if (d->undecided_of.size() > 65536) d->undecided_of.clear();
@@ -1362,6 +1364,7 @@ struct StoreCall {                 // one call's working memory, kept per thread
     std::vector<uint32_t> imports; // groups that bring their charts along
     std::vector<std::vector<uint32_t>> packed;
     StoreInline in;
+    LookInline look;
 };
 }  // namespace
 
@@ -1378,10 +1381,10 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
     double lo = 1e30;
     const double apply_us_per_word = 0.25 * 32 * logit_bytes * 2 / 1024;
     for (int r = 0; r < n; r++) {
-        // words per segment: as many as are expected to hold 48 undecided tokens, at most 64 (a batch is 64: the
+        // words per segment: as many as are expected to hold 40 undecided tokens, at most 64 (a batch is 64: the
         // tokens are spread unevenly, and a second, nearly empty batch costs as much as a full one)
         const double und = g[r].undecided;
-        int sw = g[r].pooled ? 16 : (int)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 48.0 * std::max(1, V) / (32.0 * std::max(und, 1.0))));
+        int sw = g[r].pooled ? 16 : (int)std::max(1.0, std::min<double>(STORE_SEG_WORDS_MAX, 40.0 * std::max(1, V) / (32.0 * std::max(und, 1.0))));
         // where the logits are masked too: no more words than the logits a wavefront requests ahead for all rows of the group
         // (two pieces of 16 bytes per lane), so that nothing is waited for at the end while there are wavefronts to spare
         if (logit_bytes) sw = std::min(sw, std::max(1, STORE_AHEAD_BYTES / (32 * logit_bytes * g[r].n)));
@@ -1481,7 +1484,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         }
         RowGroup g{};
         g.lead = st; g.at = at; g.last = b; g.n = 1;
-        g.dev = at == HostAutomaton::ROOT ? STORE_ROOT_ID : device_name_of(e, st);
+        g.dev = at == HostAutomaton::ROOT ? STORE_ROOT_ID : at == HostAutomaton::SINK ? (uint32_t)HostAutomaton::SINK : device_name_of(e, st);
         g.known = device_knows(d, st);
         c.g.push_back(g);
         if (at) c.table[k] = (uint32_t)c.g.size();
@@ -1575,11 +1578,20 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         spill |= !fits;
     }
     const int n_imp = (int)c.imports.size();
+    // Look-ups only: the device's name of every group's state is known, and so is every transition its vocabulary walk can meet --
+    // the mask there was computed before in this epoch of the store (a call enqueued earlier on the stream is earlier enough), or
+    // the automaton was explored to its end.
+    bool look = !spill && n_imp == 0 && d->tab.W <= 65535;
+    for (int r = 0; r < ng && look; r++) {
+        const RowGroup &g = c.g[r];
+        if (g.pooled || g.dev == HostAutomaton::SINK) continue;
+        look = g.dev && g.at && (A.st(g.at).walked == d->store_epoch || (d->closed_epoch == d->store_epoch && g.at < d->closed_states && g.dev == g.at));
+    }
     const bool big = ng > STORE_INLINE_GROUPS;            // records and members travel in device memory instead of the argument block
     auto align16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
     // staging: [group records][blocks][members] (uploaded when big), then what the kernels read in place
     const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
-    const size_t off_block = align16(big ? sizeof(StoreGroup) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
+    const size_t off_block = align16(big ? (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
     const size_t up_bytes = align16(off_mem + 2 * (size_t)batch);
     const size_t off_spill = up_bytes, off_ent = align16(off_spill + (spill ? sizeof(StoreRow) * ng : 0)), off_pend = align16(off_ent + (spill ? 4 * n_spill_ent : 0));
     const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
@@ -1619,10 +1631,42 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
             logit_bytes = (int)esz;
         }
     }
-    const int budget = std::max(ng, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
+    const int budget = std::max(ng, (look ? look_blocks_per_cu() : std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch))) * std::max(1, d->cus));
     a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes);
     // ---- the records ----
-    {
+    LookArgs k{};
+    if (look) {
+        uint8_t *h = (uint8_t *)d->h_stage[slot];
+        LookGroup *gr = big ? (LookGroup *)h : c.look.g;
+        uint32_t *blk = (uint32_t *)(h + off_block);
+        const bool members_apart = big || batch > STORE_INLINE_ROWS;
+        uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member;
+        uint32_t mem_at = 0, blk_at = 0;
+        for (int r = 0; r < ng; r++) {
+            const RowGroup &g = c.g[r];
+            LookGroup &m = gr[r];
+            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u);
+            m.w[0] = g.pooled ? g.slot : g.dev;
+            m.w[1] = g.n_ent | flags << 8 | (uint32_t)(g.seg_w - 1) << 16;
+            m.w[2] = (blk_at & 0xFFFFu) | (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16;
+            m.w[3] = mem_at | (uint32_t)g.n << 16;
+            m.w[4] = g.slot & 0xFFFFu;
+            for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;
+            for (uint32_t j = 0; j < g.n_ent; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
+            for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
+                mem[mem_at++] = (uint16_t)b;
+                if (g.dev) note_device_state(d, states[b], g.dev);
+            }
+            if (big) for (int p = 0; p < g.parts; p++) { blk[2 * blk_at] = (uint32_t)r; blk[2 * blk_at + 1] = (uint32_t)p | (uint32_t)g.parts << 16; blk_at++; }
+            else blk_at += (uint32_t)g.parts;
+        }
+        const uint8_t *up = noalloc ? d->scratch : (const uint8_t *)d->d_chart;
+        k.trans = d->store.trans; k.cache = d->tab.ci_tok; k.tok16 = d->tab.tok16; k.out_mask = d_mask; k.pool = d->d_pool;
+        k.logits = a.logits; k.out = a.out; k.stride = a.stride; k.konst = d->d_konst;
+        if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); }
+        else if (members_apart) k.members = (const uint16_t *)(h + off_mem);
+        k.V = (uint32_t)e->V; k.W = (uint32_t)d->tab.W; k.ncls = (uint32_t)d->tab.n_cls; k.n_groups = (uint32_t)ng;
+    } else {
         uint8_t *h = (uint8_t *)d->h_stage[slot];
         StoreGroup *gr = big ? (StoreGroup *)h : c.in.g;
         uint32_t *blk = (uint32_t *)(h + off_block);
@@ -1700,7 +1744,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     }
     const DeviceTables &T = d->tab;
     uint8_t *stage = (uint8_t *)d->h_stage[slot];
-    a.valid = T.ci_valid_tok; a.cd = T.ci_cd_tok; a.tok16 = T.tok16; a.trans = d->store.trans;
+    a.cache = T.ci_tok; a.tok16 = T.tok16; a.trans = d->store.trans;
     a.out_mask = d_mask; a.pool = d->d_pool; a.konst = d->d_konst;
     a.spilled = (const StoreRow *)(stage + off_spill); a.entries = (const uint32_t *)(stage + off_ent); a.pending = stage + off_pend;
     a.import_root = d->d_import_root;
@@ -1729,7 +1773,13 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
                                            (const uint32_t *)(stage + off_imp), (uint32_t)n_imp, d->d_import_root, stream));
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
     d->closing_kernel = false;
-    HIP_TRY(launch_mask_store(a, c.in, lds, stream));
+    if (look) {
+        k.tickets = a.tickets; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
+        HIP_TRY(launch_mask_look(k, c.look, a.n_blocks, a.dtype, stream));
+    } else {
+        HIP_TRY(launch_mask_store(a, c.in, lds, stream));
+        for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
+    }
     if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
     // No event marks the staging slot free: at most N_SLOTS calls are in flight between two zf_mask_wait calls, so the call that
     // used this slot before has been waited for.
@@ -1780,25 +1830,27 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states, int32_t batch, uint32
 static bool wants_exploration(const zf_engine *e) { return e->store_on && e->host_aut && e->opt.precompute_states > 0; }
 
 // The host's part: touches nothing but the host automaton (the caller holds its lock, or is the only one who knows the engine).
-static void explore_host(zf_engine *e, size_t cap_states, size_t cap_items) {
+// True when the automaton is finite and whole.
+static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items) {
     HostAutomaton &A = *e->host_aut;
     const auto t0 = std::chrono::steady_clock::now();
     const double budget_s = 1.0;
     const size_t most_states = std::min((size_t)e->opt.precompute_states, cap_states / 4), most_items = cap_items / 4;
     HostAutomaton::Work w;
     for (uint32_t s = HostAutomaton::ROOT; s < A.n_states; s++) {
-        if ((s & 63u) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() >= budget_s) return;
+        if ((s & 63u) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() >= budget_s) return false;
         for (int c = 0; c < e->tab.n_cls; c++) {
             if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
-            if (A.n_states > most_states || (size_t)A.n_items >= most_items) return;
+            if (A.n_states > most_states || (size_t)A.n_items >= most_items) return false;
             A.compute(s, c, w);
         }
     }
+    return true;
 }
 
 // The device's part: the store is cleared and takes over what the host automaton holds, names and all.  A failure is no error:
 // the store then starts empty, as it does without an exploration.
-static void store_adopt(zf_engine *e) {
+static void store_adopt(zf_engine *e, bool whole) {
     DeviceSide *d = e->dev;
     const HostAutomaton &A = *e->host_aut;
     const Tables &t = e->tab;
@@ -1838,6 +1890,7 @@ static void store_adopt(zf_engine *e) {
     d->name_host_epoch = e->host_epoch; d->name_store_epoch = d->store_epoch;
     d->name_of_host.resize(n);
     for (uint32_t id = 0; id < n; id++) d->name_of_host[id] = id;
+    if (whole) { d->closed_states = (uint32_t)n; d->closed_epoch = d->store_epoch; }
 }
 
 int zf_compute_mask_noalloc(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream) {
@@ -1962,8 +2015,8 @@ int zf_engine_clear_state_cache(zf_engine *e) {
         e->host_aut->clear();
         e->host_epoch++;
         if (wants_exploration(e) && e->dev && e->dev->pending == 0) {   // back to what the engine knew when it was compiled (with calls in flight the store is cleared later, and starts empty)
-            explore_host(e, e->dev->store.cap_states, e->dev->store.cap_items);
-            store_adopt(e);
+            const bool whole = explore_host(e, e->dev->store.cap_states, e->dev->store.cap_items);
+            store_adopt(e, whole);
         }
     }
     return ZF_OK;

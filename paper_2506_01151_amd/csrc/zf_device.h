@@ -1,6 +1,7 @@
 // Plain-data layouts shared by the host code and the HIP kernels.
 #pragma once
 #include <stdint.h>
+#include <hip/hip_vector_types.h>
 
 namespace zf {
 
@@ -88,8 +89,7 @@ struct DeviceTables {
     // The same per TOKEN, for the mask kernel over the persistent automaton, which works in token order and writes the
     // caller's mask rows itself (null unless the engine runs that kernel):
     const Str16 *tok16;         // [V] the first fifteen byte classes of token v's string and a mark (the empty token, never allowed: the mark alone)
-    const uint32_t *ci_valid_tok; // [Q + N][W] the rows of ci_valid with bit v = the verdict on token v's string
-    const uint32_t *ci_cd_tok;    // [Q + N][W] likewise for ci_cd
+    const uint2 *ci_tok;        // [Q + N][W] the rows of ci_valid (x) and ci_cd (y) with bit v = the verdict on token v's string
     int32_t Q;
     int32_t N, n_cls, end_base, n_nodes, n_chunks, n_strings, V, W;
     int32_t chunk_ranks;        // strings per chunk: 8, 16 or 32

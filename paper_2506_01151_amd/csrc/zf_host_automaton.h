@@ -32,6 +32,7 @@ struct HostAutomaton {
         uint8_t *acc = nullptr;           // [n_cls] the prefix is a sentence after that byte
         std::vector<uint32_t> ents;       // what the mask calls work out about the state once: the rows of the token-mask cache its items select ...
         int64_t undecided = -1;           // ... and how many tokens these leave to the parser (-1: not yet)
+        uint32_t walked = 0;              // epoch of the device's store in which the mask at this state was computed: its transitions are all there
     };
     // States, and their rows of the transition table (one run of memory per block: the device's table is filled from it).
     struct Block { std::unique_ptr<State[]> states; std::unique_ptr<uint32_t[]> trans; std::unique_ptr<uint8_t[]> acc; };

@@ -109,9 +109,8 @@ struct StoreConst {
     StoreView view;
 };
 struct StoreArgs {
-    const uint32_t *valid, *cd;        // DeviceTables::ci_valid_tok, ci_cd_tok
+    const uint2 *cache;                // DeviceTables::ci_tok
     const Str16 *tok16;
-    const uint8_t *tok_len;
     uint32_t *trans;                   // StoreView::trans
     uint32_t *out_mask;                // the caller's [batch][W] tensor
     uint32_t *pool;                    // the state cache's rows, [entries][W]
@@ -138,6 +137,35 @@ struct StoreArgs {
     uint32_t n_blocks;
 };
 static_assert(sizeof(StoreArgs) + sizeof(StoreInline) <= 4096, "the kernel's argument block");
+// mask_look_kernel (zf_mask_look.hip): calls whose groups all stand in states whose vocabulary has been walked before.
+#ifndef ZF_LOOK_BLOCKS_PER_CU
+#define ZF_LOOK_BLOCKS_PER_CU 3
+#endif
+static const int LOOK_BLOCKS_PER_CU = ZF_LOOK_BLOCKS_PER_CU;
+static const int LOOK_WORDS = 9;
+struct LookGroup {                     // as StoreGroup, without what a known state does not need, in nine words:
+    uint32_t w[LOOK_WORDS];            // [0] state; [1] n_ent | flags << 8 | (mask words per pass - 1) << 16; [2] first block | segments << 16;
+};                                     // [3] first member | members << 16; [4] pool row | cache row 0 << 16; [5 ..] cache rows 1, 2, ... two to a word
+struct LookInline {
+    LookGroup g[STORE_INLINE_GROUPS];
+    uint16_t member[STORE_INLINE_ROWS];
+};
+struct LookArgs {
+    const uint32_t *trans;             // as in StoreArgs:
+    const uint2 *cache;
+    const Str16 *tok16;
+    uint32_t *out_mask, *pool;
+    const void *logits;
+    void *out;
+    int64_t stride;
+    const StoreConst *konst;
+    const LookGroup *groups;
+    const uint32_t *block_of;
+    const uint16_t *members;
+    unsigned long long *tickets, *status;
+    uint32_t seq, V, W, ncls, n_groups, complete;
+};
+static_assert(sizeof(LookArgs) + sizeof(LookInline) <= 4096, "the kernel's argument block");
 // Words of a call's status in pinned host memory.  Every word carries the call's number in its upper half, so the host knows of
 // each word by itself whether it has arrived: no order between them is needed (a release would write the L2 back first).
 enum : uint32_t { STORE_ST_DONE = 0,       // low half: walks that failed (24 bits) | STORE_ST_MORE; written last, by the block that finishes last
@@ -209,6 +237,8 @@ hipError_t prepare_store_kernels();
 uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch);
 hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s);
+int look_blocks_per_cu();
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, int apply, hipStream_t s);
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s);
 // The store, cleared, whose headers, items and table rows of the states below n_states were copied in from the host: their places in the
 // hash table, and how far the store is filled.

@@ -1,0 +1,390 @@
+// Mask kernel for states whose vocabulary has been walked before (walk_mode 2): mask_look_kernel.
+//
+// The persistent automaton (zf_mask_store.hip) keeps every transition it has ever computed, so once the mask at a state has been
+// computed -- or the automaton was explored to its end when the engine was compiled -- every transition that the vocabulary walk
+// from that state can meet is in the table.  Such a state needs look-ups only: no Earley byte step, no grammar tables, no bytes
+// to be fed first.  That is every call of a decode loop but the first visits of a state, and it is what this kernel is made for;
+// mask_store_kernel takes the other calls.
+//
+// What bounds it.  Not bandwidth (a launch moves a few MB) but the length of one wavefront: dependent trips to memory
+// (arguments, cache words and the state's table row, strings, about 1 us each) and the instructions between them, which one
+// wavefront issues at 4 to 5 cycles apiece.  mask_store_kernel, which this one was split from, carries both halves: 139 scalar registers
+// spilled, a stack for the byte step (0.6 us per launch), 2.4 us from the group's record to its last request, 54 instructions
+// per byte of a walk.  Here the record is a third shorter, the cache rows are read by uniform addresses, the table row is on its
+// way before anything else, undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
+// for, and a byte of the walk takes about 20 instructions: a lane that is done leaves the loop.
+#include "zf_kernel_common.h"
+#include "zf_aut_step.h"
+
+namespace zf {
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+static const int LOOK_LC_BITS = 10;                      // the block's LDS cache of table entries: 1,024 of (key, state)
+static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
+static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
+static const int LOOK_RAW = 4;                           // token-mask cache rows whose words stay in registers as they arrive
+static const int LOOK_WARM = 6;                          // table rows one byte ahead that each wavefront of a block reads into the cache
+
+// 1,024 places by the upper bits of a 24-bit product (full rate; a 32-bit one takes four times as long)
+__device__ __forceinline__ uint32_t look_slot(uint32_t key) { return __umul24(key, 0x9E3779u) >> (32 - LOOK_LC_BITS); }
+__device__ __forceinline__ bool look_final(uint32_t t) { return t != AT_NONE && t != AT_BUSY; }
+
+// As hand_over_store: the block that draws the last ticket tells the host; here there is nothing to tell but failed walks.
+__device__ __forceinline__ void hand_over_look(const LookArgs &a, uint32_t failed) {
+    const uint32_t n_blocks = gridDim.x, lin = blockIdx.x;
+    const uint32_t n_groups = n_blocks <= 48u ? 1u : (n_blocks / 16u < (uint32_t)STORE_TICKET_GROUPS ? n_blocks / 16u : (uint32_t)STORE_TICKET_GROUPS);
+    const uint32_t g = lin % n_groups, size = n_blocks / n_groups + (g < n_blocks % n_groups ? 1u : 0u);
+    unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
+    unsigned long long sum = atomicAdd(&a.tickets[g], mine) + mine;
+    if ((sum & 0xFFFFull) != size) return;
+    __hip_atomic_store(&a.tickets[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n_groups > 1u) {
+        mine = (sum & ~0xFFFFull) | 1ull;
+        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS], mine) + mine;
+        if ((sum & 0xFFFFull) != n_groups) return;
+        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __hip_atomic_store(&a.status[STORE_ST_DONE], ((unsigned long long)a.seq << 32) | ((uint32_t)(sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A piece of 16 bytes of a row of logits, wherever the row begins.
+template <int APPLY> struct LookPiece { typedef u32x4 __attribute__((aligned(4))) type; };
+template <> struct LookPiece<2> { typedef u32x4 __attribute__((aligned(2))) type; };
+
+// Grid and groups as in mask_store_kernel: the blocks of all groups one after the other, a group = the rows of the call that
+// stand in the same state, whose mask is worked out once, in token order.  A wavefront takes every n_units-th segment of `sw` mask words.
+// APPLY: 0 = masks only, 1 / 2 = the rows' fp32 / bf16 logits are masked as well (Section 3.3).
+template <int APPLY>
+__global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_kernel(LookArgs a, LookInline in) {
+    __shared__ unsigned long long lc[LOOK_LC];
+    __shared__ uint32_t lists[STORE_WAVES][LOOK_LIST];
+    __shared__ uint32_t vbufs[STORE_WAVES][64];
+    __shared__ uint32_t blk_failed;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    // ---- the record of the block's group: one trip to the argument block (lane l asks for that of group l), or to device memory ----
+    uint32_t r[LOOK_WORDS], part, parts;
+    if (a.groups) {
+        const uint32_t b0 = a.block_of[2u * blockIdx.x], b1 = a.block_of[2u * blockIdx.x + 1u];
+        const uint32_t group = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+        part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 & 0xFFFFu));
+        parts = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 >> 16));
+#pragma unroll
+        for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[k]);
+    } else if (a.n_groups == 1u) {                           // one group: scalar loads, along with the other arguments
+        part = blockIdx.x; parts = gridDim.x;
+#pragma unroll
+        for (int k = 0; k < LOOK_WORDS; k++) r[k] = in.g[0].w[k];
+    } else {
+        uint32_t x[LOOK_WORDS];
+#pragma unroll
+        for (int k = 0; k < LOOK_WORDS; k++) x[k] = lane < a.n_groups ? in.g[lane].w[k] : 0xFFFFFFFFu;
+        const uint32_t first = x[2] & 0xFFFFu;
+        const uint32_t group = (uint32_t)__popcll(__ballot(blockIdx.x >= first)) - 1u;   // groups that start at or before this block
+#pragma unroll
+        for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readlane((int)x[k], (int)group);
+        const uint32_t fb0 = r[2] & 0xFFFFu, fb1 = group + 1u < a.n_groups ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)(group + 1u)) : gridDim.x;
+        part = blockIdx.x - fb0; parts = fb1 - fb0;
+    }
+    for (uint32_t k = tid; k < LOOK_LC; k += STORE_BLOCK) lc[k] = 0xFFFFFFFF00000000ull;
+    if (tid == 0) blk_failed = 0;
+    __syncthreads();
+    const uint32_t start = r[0], n_ent = r[1] & 0xFFu, sw = ((r[1] >> 16) & 0xFFu) + 1u, n_seg = r[2] >> 16, member_at = r[3] & 0xFFFFu, n_members = r[3] >> 16;
+    const bool pooled = (r[1] & ((uint32_t)STORE_ROW_POOLED << 8)) != 0, keep = (r[1] & ((uint32_t)STORE_ROW_KEEP << 8)) != 0, use_cache = (r[1] & ((uint32_t)STORE_ROW_CACHE << 8)) != 0;
+    const uint32_t unit = part * STORE_WAVES + wave, n_units = parts * STORE_WAVES, W = a.W, V = a.V, ncls = a.ncls;
+    if (unit < n_seg) {
+    uint32_t *const list = lists[wave], *const vbuf = vbufs[wave];
+    const bool walks = !pooled && start < AT_FAIL;            // AT_SINK: the sentence is finished, no token can follow
+    // ---- requests, in the order their answers are needed: the state's table row, the segment's cache words, members, logits ----
+    uint32_t t_root = AT_NONE;
+    const uint32_t *const row0 = a.trans + (size_t)start * ncls;
+    if (walks && lane < ncls) t_root = row0[lane];
+    auto ent = [&](int j) -> uint32_t { return (r[4 + ((j + 1) >> 1)] >> (((j + 1) & 1) * 16)) & 0xFFFFu; };
+    auto request = [&](uint32_t g, uint2 (&x)[LOOK_RAW]) __attribute__((always_inline)) {
+        const uint32_t w = g * sw + lane;
+        const bool on = lane < sw && w < W;
+#pragma unroll
+        for (int j = 0; j < LOOK_RAW; j++) x[j] = make_uint2(0, 0);
+        if (pooled) { if (on) x[0].x = a.pool[(size_t)start * W + w]; return; }
+        if (!use_cache) { x[0].y = 0xFFFFFFFFu; return; }
+#pragma unroll
+        for (int j = 0; j < LOOK_RAW; j++) if ((uint32_t)j < n_ent && on) x[j] = a.cache[(size_t)ent(j) * W + w];
+        if (n_ent > (uint32_t)LOOK_RAW) {
+#pragma unroll
+            for (int j = LOOK_RAW; j < STORE_GROUP_ENT; j++) if ((uint32_t)j < n_ent && on) { const uint2 y = a.cache[(size_t)ent(j) * W + w]; x[0].x |= y.x; x[0].y |= y.y; }
+        }
+    };
+    uint2 x[LOOK_RAW];
+    request(unit, x);
+    auto members_from = [&](uint32_t m0) __attribute__((always_inline)) -> uint32_t {   // lane l: the l-th of the 64 rows in hand
+        const uint32_t k = member_at + m0 + lane;
+        return m0 + lane < n_members ? (a.members ? a.members[k] : in.member[k]) : 0u;
+    };
+    uint32_t members = members_from(0);
+    // ---- the block's LDS cache: the state's row, and the rows of the states one byte away, shared out among the wavefronts ----
+    auto into_cache = [&](uint32_t st, uint32_t t) __attribute__((always_inline)) {
+        if (lane < ncls && look_final(t)) { const uint32_t key = st * ncls + lane; __hip_atomic_store(&lc[look_slot(key)], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+    };
+    uint32_t ahead[LOOK_WARM], t_ahead[LOOK_WARM], n_ahead = 0;
+#pragma unroll
+    for (int k = 0; k < LOOK_WARM; k++) { ahead[k] = 0; t_ahead[k] = AT_NONE; }
+    if (walks) {
+        into_cache(start, t_root);
+        unsigned long long todo = __ballot(lane < ncls && t_root < AT_FAIL && t_root != start);
+        uint32_t n = 0;
+        while (todo && n < (uint32_t)(LOOK_WARM * STORE_WAVES)) {
+            const uint32_t nx = (uint32_t)__builtin_amdgcn_readlane((int)t_root, __ffsll((long long)todo) - 1);
+            todo &= ~__ballot(t_root == nx);
+            if ((n & (STORE_WAVES - 1u)) == wave) {
+#pragma unroll
+                for (int k = 0; k < LOOK_WARM; k++) ahead[k] = n_ahead == (uint32_t)k ? nx : ahead[k];
+                n_ahead++;
+            }
+            n++;
+        }
+#pragma unroll
+        for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead && lane < ncls) t_ahead[k] = a.trans[(size_t)ahead[k] * ncls + lane];
+    }
+    // ---- logits: the segment's 16-byte pieces of all members in hand as one run, the first PRE of every lane requested ahead ----
+    typedef typename LookPiece<APPLY>::type piece_t;
+    constexpr uint32_t tp = APPLY == 2 ? 8u : 4u, esz = APPLY == 2 ? 2u : 4u;   // tokens per 16-byte piece, bytes per logit
+    auto tokens_of = [&](uint32_t g) -> uint32_t {
+        const uint32_t tok0 = g * sw * 32u;
+        return g < n_seg && tok0 < V ? (sw * 32u < V - tok0 ? sw * 32u : V - tok0) : 0u;
+    };
+    // number i of a run of `per` things per member: which member, and which of its things.  i < 2^15 and per <= 512, so the
+    // half added keeps the product at least 1 / 1024 away from the next whole number, far more than single precision loses
+    auto split = [&](uint32_t i, uint32_t per, float inv, uint32_t &k) -> uint32_t { k = (uint32_t)(((float)i + 0.5f) * inv); return i - k * per; };
+    auto byte_of = [&](uint32_t k, uint32_t g, uint32_t t) -> size_t {   // of token t of segment g in the k-th member's row
+        return ((size_t)(uint32_t)__shfl((int)members, (int)(k & 63u)) * (size_t)a.stride + g * sw * 32u + t) * esz;
+    };
+    constexpr int PRE = 2;
+    auto logits_ahead = [&](uint32_t g, u32x4 (&pre)[PRE]) __attribute__((always_inline)) {
+        const uint32_t per = tokens_of(g) / tp, total = per * (n_members < 64u ? n_members : 64u);
+        const float inv = __builtin_amdgcn_rcpf((float)(per ? per : 1u));
+#pragma unroll
+        for (int u = 0; u < PRE; u++) {
+            const uint32_t i = (uint32_t)u * 64u + lane;
+            uint32_t k;
+            const uint32_t p = split(i < total ? i : 0u, per, inv, k);
+            const size_t at = byte_of(k, g, p * tp);
+            pre[u] = u32x4{0, 0, 0, 0};
+            if (i < total) pre[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + at));
+        }
+    };
+    u32x4 l_pre[PRE];
+    if (APPLY) logits_ahead(unit, l_pre);
+    uint32_t failed = 0;
+    bool first = true;
+    for (uint32_t g = unit; g < n_seg; g += n_units) {
+        const uint32_t w = lane < sw ? g * sw + lane : 0xFFFFFFFFu;   // the lane's mask word
+        uint32_t v = x[0].x, c = x[0].y;
+#pragma unroll
+        for (int j = 1; j < LOOK_RAW; j++) { v |= x[j].x; c |= x[j].y; }
+        u32x4 l_nxt[PRE];
+        if (g + n_units < n_seg) {                           // the next segment's words and first logits travel while this one's tokens are checked
+            request(g + n_units, x);
+            if (APPLY) logits_ahead(g + n_units, l_nxt);
+        }
+        uint32_t want = c & ~v;
+        {
+            const uint32_t t0 = w * 32u;
+            if (w >= W || t0 >= V || !walks) want = 0;
+            else if (V - t0 < 32u) want &= (1u << (V - t0)) - 1u;
+        }
+        if (!walks && !pooled) v = 0;
+        // ---- the undecided tokens, listed: running sums of the words' bit counts (data-parallel-primitive moves), then every lane
+        // writes the numbers of its word's tokens where they belong ----
+        const uint32_t cnt = (uint32_t)__popc(want);
+        uint32_t incl = cnt;
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x111, 0xF, 0xF, true);    // row_shr:1
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x112, 0xF, 0xF, true);    // row_shr:2
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x114, 0xF, 0xF, true);    // row_shr:4
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x118, 0xF, 0xF, true);    // row_shr:8
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (lane < sw) lds_store(&vbuf[lane], 0u);
+        for (uint32_t base = 0; base < total; base += LOOK_LIST) {
+            {
+                uint32_t at = incl - cnt - base, bits = want;   // (wraps below the window: not listed)
+                while (bits) {
+                    const uint32_t b = (uint32_t)__ffs((int)bits) - 1u;
+                    bits &= bits - 1u;
+                    if (at < LOOK_LIST) lds_store(&list[at], lane * 32u + b);
+                    at++;
+                }
+            }
+            const uint32_t n = total - base < LOOK_LIST ? total - base : LOOK_LIST;
+            struct Tok { uint32_t at; u32x4 s; };
+            auto fetch = [&](uint32_t b0) __attribute__((always_inline)) -> Tok {   // requested here, looked at a batch later
+                Tok k;
+                k.at = lds_load(&list[b0 + lane < n ? b0 + lane : 0u]);
+                k.s = *reinterpret_cast<const u32x4 *>(&a.tok16[g * sw * 32u + k.at]);
+                return k;
+            };
+            Tok nxt = fetch(0);
+            if (first) {                                     // the rows one byte ahead have arrived meanwhile
+#pragma unroll
+                for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead) into_cache(ahead[k], t_ahead[k]);
+                first = false;
+            }
+            for (uint32_t b0 = 0; b0 < n; b0 += 64) {
+                const Tok cur = nxt;
+                if (b0 + 64 < n) nxt = fetch(b0 + 64);
+                // One lane per token: it follows its string through the table for as long as there is a state and a next byte.  The
+                // classes at hand are a shift register; a mark ends them.
+                uint32_t w0 = cur.s[0], w1 = cur.s[1], w2 = cur.s[2], w3 = cur.s[3];
+                uint32_t cl = w0 & 0xFFu, s = start, t = AT_DEAD, passed = 0;
+                bool go = b0 + lane < n && cl != TOK_END;    // an empty token is never allowed
+                uint32_t c1 = 0;                             // the class behind the one a step was taken on, or a mark
+                while (go) {
+                    const uint32_t key = __umul24(s, ncls) + cl;     // a state has at most 18 bits, a class 8
+                    const uint32_t slot = look_slot(key);
+                    const unsigned long long e = __hip_atomic_load(&lc[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    t = (uint32_t)e;
+                    if ((uint32_t)(e >> 32) != key) {
+                        t = __hip_atomic_load(&a.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        __hip_atomic_store(&lc[slot], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    w0 = __builtin_amdgcn_alignbyte(w1, w0, 1); w1 = __builtin_amdgcn_alignbyte(w2, w1, 1); w2 = __builtin_amdgcn_alignbyte(w3, w2, 1); w3 >>= 8;
+                    c1 = w0 & 0xFFu;
+                    go = t < AT_FAIL && c1 < TOK_MORE;
+                    if (go) { s = t; cl = c1; }
+                    else if (t < AT_FAIL && c1 == TOK_MORE) {   // a string beyond the bytes at hand: its next fifteen classes
+                        const DeviceTables &D = a.konst->tab;
+                        const uint32_t rank = D.rank_of[g * sw * 32u + cur.at], from = D.str_off[rank], len = D.str_off[rank + 1] - from;
+                        passed += TOK_AT_HAND;
+                        const uint32_t left = len - passed, m = left < TOK_AT_HAND ? left : TOK_AT_HAND;   // left >= 1: the mark says that the string goes on
+                        uint32_t nw[4] = {0, 0, 0, 0};
+                        for (uint32_t k = 0; k <= m; k++) {
+                            const uint32_t b = (k < m ? (uint32_t)D.str_cls[from + passed + k] : (left > TOK_AT_HAND ? TOK_MORE : TOK_END)) << ((k & 3u) * 8u);
+                            nw[0] |= k < 4u ? b : 0u; nw[1] |= (k >> 2) == 1u ? b : 0u; nw[2] |= (k >> 2) == 2u ? b : 0u; nw[3] |= (k >> 2) == 3u ? b : 0u;
+                        }
+                        w0 = nw[0]; w1 = nw[1]; w2 = nw[2]; w3 = nw[3];
+                        s = t; cl = w0 & 0xFFu; go = true;
+                    }
+                }
+                if (c1 == TOK_END && (t < AT_FAIL || t == AT_SINK)) atomicOr(&vbuf[cur.at >> 5], 1u << (cur.at & 31u));
+                // an entry that is not there, or stands for no room: the host was wrong about the state, the call fails
+                failed += (uint32_t)__popcll(__ballot(t == AT_NONE || t == AT_BUSY || t == AT_FAIL));
+            }
+        }
+        if (total) v |= lane < sw ? lds_load(&vbuf[lane]) : 0u;   // LDS serves one wavefront's accesses in issue order
+        // ---- the segment's words go to every member's mask row (and to the state cache) ----
+        for (uint32_t m0 = 0; m0 < n_members; m0 += 64) {
+            if (n_members > 64u) members = members_from(m0);
+            const uint32_t n = n_members - m0 < 64u ? n_members - m0 : 64u;
+            if (n < 4u || sw > 32u) {
+                for (uint32_t k = 0; k < n; k++) {
+                    uint32_t *dst = a.out_mask + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)members, (int)k) * W + w;
+                    if (w < W) { if (a.complete) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); else *dst = v; }
+                }
+            } else {                                         // several members per store: the lanes hold the segment 2, 4, 8 or 16 times over
+                const uint32_t lg = sw <= 4u ? 2u : sw <= 8u ? 3u : sw <= 16u ? 4u : 5u, word = lane & ((1u << lg) - 1u), w2 = g * sw + word;
+                const uint32_t v2 = (uint32_t)__shfl((int)v, (int)word);
+                for (uint32_t k0 = 0; k0 < n; k0 += 64u >> lg) {
+                    const uint32_t k = k0 + (lane >> lg);
+                    uint32_t *dst = a.out_mask + (size_t)(uint32_t)__shfl((int)members, (int)(k & 63u)) * W + w2;
+                    if (k < n && word < sw && w2 < W) { if (a.complete) __hip_atomic_store(dst, v2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); else *dst = v2; }
+                }
+            }
+            if (APPLY) {
+                // Logit masking (Section 3.3) of the segment's tokens, right here: 16-byte pieces, consecutive lanes on consecutive
+                // pieces, the mask word from the lane that holds it.  Allowed logits are copied bit for bit, the others become -inf.
+                const uint32_t n_tok = tokens_of(g), pieces = n_tok / tp, tail = n_tok % tp;
+                auto masked = [&](u32x4 y, uint32_t mb) -> u32x4 {
+                    if (APPLY == 2) {
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            uint32_t e = y[j];
+                            if (!((mb >> (2 * j)) & 1u)) e = (e & 0xFFFF0000u) | 0xFF80u;
+                            if (!((mb >> (2 * j + 1)) & 1u)) e = (e & 0x0000FFFFu) | 0xFF800000u;
+                            y[j] = e;
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; j++) if (!((mb >> j) & 1u)) y[j] = 0xFF800000u;
+                    }
+                    return y;
+                };
+                auto bits_at = [&](uint32_t tk) -> uint32_t { return (uint32_t)__shfl((int)v, (int)((tk >> 5) & 63u)) >> (tk & 31u); };   // all lanes call it together
+                const uint32_t run = pieces * n;
+                const float inv = __builtin_amdgcn_rcpf((float)(pieces ? pieces : 1u));
+                const uint8_t *src = reinterpret_cast<const uint8_t *>(a.logits);
+                uint8_t *dst = reinterpret_cast<uint8_t *>(a.out);
+                auto where = [&](uint32_t i, uint32_t &p) -> size_t { uint32_t k; p = split(i < run ? i : 0u, pieces, inv, k); return byte_of(k, g, p * tp); };
+                auto put = [&](uint32_t i, u32x4 y) { uint32_t p; const size_t at = where(i, p); const uint32_t mb = bits_at(p * tp); if (i < run) __builtin_nontemporal_store(masked(y, mb), reinterpret_cast<piece_t *>(dst + at)); };
+                uint32_t i0 = 0;
+                if (m0 == 0) {                               // what was requested ahead
+#pragma unroll
+                    for (int u = 0; u < PRE; u++) if ((uint32_t)u * 64u < run) put((uint32_t)u * 64u + lane, l_pre[u]);
+                    i0 = PRE * 64u;
+                }
+                for (; i0 < run; i0 += 256) {                // the others: four pieces per lane in flight
+                    u32x4 y[4];
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        const uint32_t i = i0 + (uint32_t)u * 64u + lane;
+                        uint32_t p;
+                        const size_t at = where(i, p);
+                        y[u] = u32x4{0, 0, 0, 0};
+                        if (i < run) y[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(src + at));
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; u++) if (i0 + (uint32_t)u * 64u < run) put(i0 + (uint32_t)u * 64u + lane, y[u]);
+                }
+                if (tail) {                                  // the last tokens of a vocabulary that is no multiple of a piece
+                    const uint32_t tails = tail * n;
+                    const float tinv = __builtin_amdgcn_rcpf((float)tail);
+                    for (uint32_t i = 0; i < tails; i += 64) {
+                        uint32_t k;
+                        const uint32_t tk = pieces * tp + split(i + lane < tails ? i + lane : 0u, tail, tinv, k), stays = bits_at(tk) & 1u;
+                        const size_t at = byte_of(k, g, tk);
+                        if (i + lane < tails) {
+                            if (APPLY == 2) *reinterpret_cast<uint16_t *>(dst + at) = stays ? *reinterpret_cast<const uint16_t *>(src + at) : (uint16_t)0xFF80u;
+                            else *reinterpret_cast<uint32_t *>(dst + at) = stays ? *reinterpret_cast<const uint32_t *>(src + at) : 0xFF800000u;
+                        }
+                    }
+                }
+            }
+        }
+        if (keep && w < W) a.pool[(size_t)(r[4] & 0xFFFFu) * W + w] = v;
+        if (n_members > 64u) members = members_from(0);
+        if (APPLY) {
+#pragma unroll
+            for (int u = 0; u < PRE; u++) l_pre[u] = l_nxt[u];
+        }
+    }
+    if (lane == 0 && failed) atomicAdd(&blk_failed, failed);
+    if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
+    }
+    __syncthreads();
+    if (tid == 0) hand_over_look(a, lds_load(&blk_failed));
+}
+
+}  // namespace
+
+static void (*look_kernel(int apply))(LookArgs, LookInline) { return apply == 0 ? mask_look_kernel<0> : apply == 1 ? mask_look_kernel<1> : mask_look_kernel<2>; }
+
+// Blocks of the kernel one compute unit holds at once.
+int look_blocks_per_cu() {
+    static const int least = [] {
+        int n_least = LOOK_BLOCKS_PER_CU;
+        for (int p = 0; p < 3; p++) {
+            int n = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(look_kernel(p)), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+            n_least = n < n_least ? n : n_least;
+        }
+        return n_least;
+    }();
+    return least;
+}
+
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, int apply, hipStream_t s) {
+    hipLaunchKernelGGL(look_kernel(apply), dim3(n_blocks), dim3(STORE_BLOCK), 0, s, a, in);
+    return hipGetLastError();
+}
+
+}  // namespace zf

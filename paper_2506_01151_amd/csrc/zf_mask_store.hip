@@ -406,7 +406,8 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
             if (k < n_ent && w < W) {
                 if (!ent_inline) er = a.entries[ent_off + k];
                 const size_t r = (size_t)er * W + w;
-                v = a.valid[r]; c = a.cd[r];
+                const uint2 vc = a.cache[r];
+                v = vc.x; c = vc.y;
             }
         };
 #pragma unroll
