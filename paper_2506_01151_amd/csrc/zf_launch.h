@@ -173,7 +173,9 @@ enum : uint32_t { STORE_ST_DONE = 0,       // low half: walks that failed (24 bi
                   STORE_ST_STATES = 2, STORE_ST_ITEMS = 3, STORE_ST_REFUSED = 4,
                   STORE_ST_ROW = 8 };      // + group: the state the group arrived in (groups with STORE_ROW_REPORT)
 static const uint32_t STORE_ST_MORE = 0x80000000u;
-static const int STORE_TICKET_GROUPS = 64, STORE_TICKETS = STORE_TICKET_GROUPS + 1;
+// A ticket word lies 64 bytes from the next: additions to words of one line queue up behind each other like additions to one word
+// (launches of 768 blocks that do nothing else: 10.2 us to the status word with the words side by side, 8.2 apart, 6.8 without tickets).
+static const int STORE_TICKET_GROUPS = 64, STORE_TICKET_STRIDE = 8, STORE_TICKETS = (STORE_TICKET_GROUPS + 1) * STORE_TICKET_STRIDE;
 
 // A set of per-call counters: words 0-7 as listed at MaskArgs::counters, then the tickets the blocks of a call's last kernel
 // draw when they are done (one word per group of blocks, so that thousands of blocks do not queue up at one address, and a

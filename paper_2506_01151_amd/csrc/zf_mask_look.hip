@@ -36,14 +36,14 @@ __device__ __forceinline__ void hand_over_look(const LookArgs &a, uint32_t faile
     const uint32_t n_groups = n_blocks <= 48u ? 1u : (n_blocks / 16u < (uint32_t)STORE_TICKET_GROUPS ? n_blocks / 16u : (uint32_t)STORE_TICKET_GROUPS);
     const uint32_t g = lin % n_groups, size = n_blocks / n_groups + (g < n_blocks % n_groups ? 1u : 0u);
     unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
-    unsigned long long sum = atomicAdd(&a.tickets[g], mine) + mine;
+    unsigned long long sum = atomicAdd(&a.tickets[g * STORE_TICKET_STRIDE], mine) + mine;
     if ((sum & 0xFFFFull) != size) return;
-    __hip_atomic_store(&a.tickets[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.tickets[g * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n_groups > 1u) {
         mine = (sum & ~0xFFFFull) | 1ull;
-        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS], mine) + mine;
+        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], mine) + mine;
         if ((sum & 0xFFFFull) != n_groups) return;
-        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(&a.status[STORE_ST_DONE], ((unsigned long long)a.seq << 32) | ((uint32_t)(sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }

@@ -271,14 +271,14 @@ __device__ __forceinline__ void hand_over_store(const StoreArgs &a, const uint32
     const uint32_t g = lin % n_groups, size = n_blocks / n_groups + (g < n_blocks % n_groups ? 1u : 0u);
     const unsigned long long err = lds_load(&blk[0]), stp = lds_load(&blk[1]);
     unsigned long long mine = 1ull | (err < 4095ull ? err : 4095ull) << 16 | (stp < 4095ull ? stp : 4095ull) << 40;
-    unsigned long long sum = atomicAdd(&a.tickets[g], mine) + mine;
+    unsigned long long sum = atomicAdd(&a.tickets[g * STORE_TICKET_STRIDE], mine) + mine;
     if ((sum & 0xFFFFull) != size) return;
-    __hip_atomic_store(&a.tickets[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.tickets[g * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n_groups > 1u) {
         mine = (sum & ~0xFFFFull) | 1ull;
-        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS], mine) + mine;
+        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], mine) + mine;
         if ((sum & 0xFFFFull) != n_groups) return;
-        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     auto tell = [&](uint32_t k, uint32_t value) {
         __hip_atomic_store(&a.status[k], ((unsigned long long)a.seq << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
