@@ -2,11 +2,24 @@
 
 Only marshals arguments: every step of the hot path runs inside the library.  The
 library must have been built (paper_2506_01151_amd/build.py); a missing library is
-an error, there is no substitute path.
+an error, there is no substitute path.  The calls of a decode step are marshalled by the
+extension module _native (csrc/zf_py.cpp); the functions here whose names end in _twin are
+what it hands a call to that is not the ordinary case, and their definition.
 """
 import ctypes
 import os
 import numpy as np
+
+try:
+    from . import _native
+except ImportError as _why:                     # not built: load_library says so
+    _not_built = str(_why)
+
+    class _native:
+        EngineBase = StateBase = BatchBase = object
+        compute_mask = compute_mask_noalloc = compute_mask_async = compute_mask_apply_async = mask_wait = apply_mask = None
+else:
+    _not_built = None
 
 ZF_OK, ZF_ERR_INVALID_ARG, ZF_ERR_GRAMMAR, ZF_ERR_REJECTED = 0, -1, -2, -3
 ZF_ERR_RANGE, ZF_ERR_DEVICE, ZF_ERR_OOM, ZF_ERR_OVERFLOW = -4, -5, -6, -7
@@ -69,6 +82,8 @@ def load_library():
         return _lib
     if not os.path.exists(LIB_PATH):
         raise RuntimeError(f"{LIB_PATH} is missing: build it with `python paper_2506_01151_amd/build.py`")
+    if _not_built is not None:
+        raise RuntimeError(f"the extension module _native is missing ({_not_built}): build it with `python paper_2506_01151_amd/build.py`")
     L = ctypes.CDLL(LIB_PATH)
     L.zf_strerror.restype = ctypes.c_char_p
     L.zf_strerror.argtypes = [ctypes.c_int]
@@ -108,7 +123,23 @@ def load_library():
     L.zf_debug_twin_advance.argtypes = [c_vp, ctypes.POINTER(ctypes.c_uint32), c_vp, c_i64, ctypes.POINTER(c_i32)]
     L.zf_debug_twin_mask.argtypes = [c_vp, ctypes.c_uint32, c_vp, c_vp]
     _lib = L
+    _native.bind_library({n: ctypes.cast(getattr(L, n), c_vp).value for n in (
+        "zf_state_reset", "zf_advance", "zf_advance_batch", "zf_compute_mask", "zf_compute_mask_noalloc", "zf_compute_mask_async",
+        "zf_compute_mask_apply_async", "zf_mask_wait", "zf_apply_mask")}, _check, _TWINS)
     return L
+
+
+def _look_at_tensors():
+    """From the first call with a tensor on: _native reads the tensors itself."""
+    global _looks
+    if not _looks:
+        import torch  # noqa: F401  (its libraries have to be there)
+        from . import _native_torch
+        _native.bind_torch(_native_torch.calls)
+        _looks = True
+
+
+_looks = False
 
 
 def _check(rc):
@@ -116,9 +147,9 @@ def _check(rc):
         raise ZfError(rc, _lib.zf_last_error().decode("utf-8", "replace"))
 
 
-class State:
+class State(_native.StateBase):                # advance(token_id), reset(): csrc/zf_py.cpp
     def __init__(self, engine, handle):
-        self.engine, self.h = engine, handle
+        self.engine, self.h = engine, handle.value
 
     def __del__(self):
         if self.h and _lib is not None:
@@ -129,12 +160,6 @@ class State:
         h = c_vp()
         _check(_lib.zf_state_clone(self.h, ctypes.byref(h)))
         return State(self.engine, h)
-
-    def reset(self):
-        _check(_lib.zf_state_reset(self.h))
-
-    def advance(self, token_id: int):
-        _check(_lib.zf_advance(self.h, token_id))
 
     def try_advance(self, token_id: int) -> int:
         return _lib.zf_advance(self.h, token_id)
@@ -221,7 +246,7 @@ class Twin:
         return out, dict(states=int(st[0]), steps=int(st[1]), lookups=int(st[2]), undecided=int(st[3]), items=int(st[4]))
 
 
-class StateBatch:
+class StateBatch(_native.BatchBase):            # advance(token_ids): csrc/zf_py.cpp
     """The rows of one batch with their handle array marshalled once: pass it wherever a list of
     states is accepted; advance() moves every row by one token in a single library call."""
 
@@ -229,6 +254,7 @@ class StateBatch:
         self.states = list(states)
         self.arr = (c_vp * max(1, len(self.states)))(*[s.h for s in self.states])
         self._ids = (c_i32 * max(1, len(self.states)))()
+        self._bind(self.states)
 
     def __len__(self):
         return len(self.states)
@@ -239,17 +265,26 @@ class StateBatch:
     def __iter__(self):
         return iter(self.states)
 
-    def advance(self, token_ids):
-        """token_ids[b] < 0 resets row b."""
-        self._ids[:len(self.states)] = token_ids
-        _check(_lib.zf_advance_batch(self.arr, self._ids, len(self.states), None))
+
+def _state_reset_twin(self):
+    _check(_lib.zf_state_reset(self.h))
+
+
+def _state_advance_twin(self, token_id: int):
+    _check(_lib.zf_advance(self.h, token_id))
+
+
+def _batch_advance_twin(self, token_ids):
+    """token_ids[b] < 0 resets row b."""
+    self._ids[:len(self.states)] = token_ids
+    _check(_lib.zf_advance_batch(self.arr, self._ids, len(self.states), None))
 
 
 def _handles(states):
     return states.arr if isinstance(states, StateBatch) else (c_vp * len(states))(*[s.h for s in states])
 
 
-class Engine:
+class Engine(_native.EngineBase):
     """compile(grammar rules, vocab byte strings)."""
 
     def __init__(self, grammar, vocab_tokens, *, pruning=True, lane_item_cap=0, device=0, chunk_strings=0, fallback_item_cap=0, token_mask_cache=True, state_cache_entries=0, walk_mode=2, precompute_states=0):
@@ -272,9 +307,11 @@ class Engine:
         self.info = EngineInfo()
         _check(_lib.zf_engine_get_info(self.h, ctypes.byref(self.info)))
         self.V, self.W = self.info.V, self.info.W
+        self._bind(self.h.value, self.info.device, self.V, self.W)
 
     def __del__(self):
         if getattr(self, "h", None) and _lib is not None:
+            self._bind(None, -1, 0, 0)
             _lib.zf_engine_destroy(self.h)
             self.h = None
 
@@ -337,36 +374,40 @@ def _current_stream(engine: Engine) -> int:
     return torch.cuda.current_stream(engine.info.device).cuda_stream
 
 
-def compute_mask(engine: Engine, states, mask_tensor):
+def _compute_mask_twin(engine: Engine, states, mask_tensor):
     """mask_tensor: torch int32 tensor [batch, W] on the engine's device (fully overwritten)."""
     import torch
+    _look_at_tensors()
     assert mask_tensor.is_cuda and mask_tensor.is_contiguous() and mask_tensor.dtype == torch.int32
     assert tuple(mask_tensor.shape) == (len(states), engine.W)
     engine.compute_mask(states, mask_tensor.data_ptr(), _current_stream(engine))
     return mask_tensor
 
 
-def compute_mask_noalloc(engine: Engine, states, mask_tensor):
+def _compute_mask_noalloc_twin(engine: Engine, states, mask_tensor):
     """compute_mask through the entry point that allocates no device memory (static scratch array)."""
     import torch
+    _look_at_tensors()
     assert mask_tensor.is_cuda and mask_tensor.is_contiguous() and mask_tensor.dtype == torch.int32
     assert tuple(mask_tensor.shape) == (len(states), engine.W)
     engine.compute_mask_noalloc(states, mask_tensor.data_ptr(), _current_stream(engine))
     return mask_tensor
 
 
-def compute_mask_async(engine: Engine, states, mask_tensor):
+def _compute_mask_async_twin(engine: Engine, states, mask_tensor):
     """Enqueue only; pair with mask_wait(engine) before reading the mask on the host."""
     import torch
+    _look_at_tensors()
     assert mask_tensor.is_cuda and mask_tensor.is_contiguous() and mask_tensor.dtype == torch.int32
     assert tuple(mask_tensor.shape) == (len(states), engine.W)
     engine.compute_mask_async(states, mask_tensor.data_ptr(), _current_stream(engine))
     return mask_tensor
 
 
-def compute_mask_apply_async(engine: Engine, states, mask_tensor, logits, out=None):
+def _compute_mask_apply_async_twin(engine: Engine, states, mask_tensor, logits, out=None):
     """compute_mask and apply_mask of the same rows, enqueued together; pair with mask_wait(engine)."""
     import torch
+    _look_at_tensors()
     assert mask_tensor.is_cuda and mask_tensor.is_contiguous() and mask_tensor.dtype == torch.int32
     assert tuple(mask_tensor.shape) == (len(states), engine.W)
     assert logits.is_cuda and logits.dim() == 2 and logits.stride(1) == 1 and tuple(logits.shape) == (len(states), engine.V)
@@ -378,13 +419,15 @@ def compute_mask_apply_async(engine: Engine, states, mask_tensor, logits, out=No
     return out
 
 
-def mask_wait(engine: Engine):
+def _mask_wait_twin(engine: Engine):
+    _look_at_tensors()
     engine.mask_wait(_current_stream(engine))
 
 
-def apply_mask(engine: Engine, logits, mask_tensor, out=None):
+def _apply_mask_twin(engine: Engine, logits, mask_tensor, out=None):
     """logits: torch fp32 or bf16 tensor [batch, V] (last dim contiguous) on the device."""
     import torch
+    _look_at_tensors()
     assert logits.is_cuda and logits.dim() == 2 and logits.stride(1) == 1 and logits.shape[1] == engine.V
     dtype = {torch.float32: 0, torch.bfloat16: 1}[logits.dtype]
     if out is None:
@@ -393,3 +436,10 @@ def apply_mask(engine: Engine, logits, mask_tensor, out=None):
     engine.apply_mask(logits.data_ptr(), out.data_ptr(), dtype, logits.shape[0], logits.stride(0),
                       mask_tensor.data_ptr(), _current_stream(engine))
     return out
+
+
+compute_mask, compute_mask_noalloc, compute_mask_async = _native.compute_mask, _native.compute_mask_noalloc, _native.compute_mask_async
+compute_mask_apply_async, mask_wait, apply_mask = _native.compute_mask_apply_async, _native.mask_wait, _native.apply_mask
+_TWINS = {"State.advance": _state_advance_twin, "State.reset": _state_reset_twin, "StateBatch.advance": _batch_advance_twin,
+          "compute_mask": _compute_mask_twin, "compute_mask_noalloc": _compute_mask_noalloc_twin, "compute_mask_async": _compute_mask_async_twin,
+          "compute_mask_apply_async": _compute_mask_apply_async_twin, "mask_wait": _mask_wait_twin, "apply_mask": _apply_mask_twin}

@@ -1,7 +1,8 @@
-"""Builds the HIP library in-tree: paper_2506_01151_amd/libzapformat.so (gfx950 only)."""
+"""Builds the HIP library in-tree, paper_2506_01151_amd/libzapformat.so (gfx950 only), and the binding's extension modules beside it."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -22,6 +23,25 @@ def _run(cmd):
     proc = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
     err = "\n".join(l for l in proc.stderr.splitlines() if NOISE not in l)
     return proc.returncode, err
+
+
+def _extension_jobs(force):
+    """The two extension modules of the Python binding (host code): _native, and _native_torch, which is compiled against torch's headers."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    common = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden", "-I" + sysconfig.get_paths()["include"]]
+    torch_flags = ["-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={abi}", "-isystem", "/opt/rocm/include"]
+    for p in include_paths():
+        torch_flags += ["-isystem", p]
+    libs = [f for p in library_paths() if os.path.isdir(p) for f in ["-L" + p]] + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    jobs = []
+    for src, name, flags, link in (("zf_py.cpp", "_native.so", [], []), ("zf_py_torch.cpp", "_native_torch.so", torch_flags, libs)):
+        path, out = os.path.join(CSRC, src), os.path.join(HERE, name)
+        newest = max(os.path.getmtime(p) for p in (path, os.path.join(CSRC, "zf_py.h"), os.path.join(HERE, "..", "include", "zapformat.h")))
+        if force or not os.path.exists(out) or os.path.getmtime(out) < newest:
+            jobs.append(common + flags + [path, "-o", out] + link)
+    return jobs
 
 
 SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
@@ -45,15 +65,16 @@ def build(force: bool = True, extra_flags=(), sanitize: bool = False) -> str:
         src, obj = os.path.join(CSRC, s), os.path.join(OBJ, s + ".o")
         if force or extra_flags or not os.path.exists(obj) or os.path.getmtime(obj) < max(os.path.getmtime(src), newest_dep):
             jobs.append(["hipcc", "-x", "hip", "-c", src, "-o", obj] + FLAGS + list(extra_flags))
-    with ThreadPoolExecutor(max_workers=min(8, max(1, len(jobs)))) as pool:
-        results = list(pool.map(_run, jobs))
+    todo = jobs + _extension_jobs(force)
+    with ThreadPoolExecutor(max_workers=min(8, max(1, len(todo)))) as pool:
+        results = list(pool.map(_run, todo))
     failed = False
     for rc, err in results:
         if err.strip():
             print(err, file=sys.stderr)
         failed |= rc != 0
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compiling failed")
     if jobs or not os.path.exists(LIB):
         link = ["-fsanitize=address", "-fsanitize=undefined", "-shared-libasan"] if sanitize else []
         rc, err = _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + link + [os.path.join(OBJ, s + ".o") for s in SOURCES])
