@@ -893,10 +893,11 @@ def test_apply_mask_bit_exact(dtype, torch_cuda, oracle_lib):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("V,B,shift", [(3, 2, 0), (9, 3, 1), (257, 7, 0), (2033, 65, 1), (40037, 53, 3)])
+@pytest.mark.parametrize("V,B,shift", [(3, 2, 0), (9, 3, 1), (257, 7, 0), (2033, 65, 1), (40037, 53, 3), (40037, 640, 1)])
 def test_apply_mask_rows_at_any_multiple_of_an_element(V, B, shift, dtype, torch_cuda, oracle_lib):
     """Rows packed one behind the other (no row but the first at a multiple of 16 bytes), the tensor itself beginning `shift`
-    elements into an allocation, vocabularies smaller than a piece of 16 bytes and just beyond one."""
+    elements into an allocation, vocabularies smaller than a piece of 16 bytes and just beyond one; the last tensor is of the size from
+    which pieces that nothing is allowed of are not read (most mask words of every other row are empty)."""
     import paper_2506_01151_amd as zf
     from oracle.frontend import apply_mask as oracle_apply
     torch = torch_cuda
@@ -904,6 +905,7 @@ def test_apply_mask_rows_at_any_multiple_of_an_element(V, B, shift, dtype, torch
     eng = zf.Engine(grammars.w1_grammar(), toks, device=0)
     rng = np.random.default_rng(V + B)
     mask = rng.integers(0, 2**32, size=(B, eng.W), dtype=np.uint32)
+    mask[::2] &= np.where(rng.random((len(mask[::2]), eng.W)) < 0.1, 0xFFFFFFFF, 0).astype(np.uint32)
     u, i, f = (np.uint32, torch.int32, torch.float32) if dtype == "f32" else (np.uint16, torch.int16, torch.bfloat16)
     bits = rng.integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
     room = torch.zeros(B * V + shift, dtype=i, device="cuda")
