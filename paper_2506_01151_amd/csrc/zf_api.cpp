@@ -57,7 +57,6 @@ struct DeviceSide {
     void *d_chart = nullptr; size_t chart_cap = 0;
     static const int N_SLOTS = 4;                    // calls that may be in flight before zf_mask_wait
     void *h_stage[N_SLOTS] = {nullptr, nullptr, nullptr, nullptr}; size_t stage_cap[N_SLOTS] = {0, 0, 0, 0};   // pinned
-    hipEvent_t stage_done[N_SLOTS] = {nullptr, nullptr, nullptr, nullptr};   // the slot's upload has been consumed
     uint32_t *h_status = nullptr;                    // pinned, [N_SLOTS][8]: counters [0..3] and the call's number [4], written by each call's last kernel
     uint32_t call_seq = 0, last_seq = 0, last_slot = 0; // number of the newest call in flight and its slot
     uint32_t next_slot = 0, pending = 0;
@@ -198,7 +197,7 @@ void free_device(DeviceSide *d) {
     (void)hipSetDevice(d->device);
     for (void *p : d->slabs) (void)hipFree(p);
     if (d->d_chart) (void)hipFree(d->d_chart);
-    for (int k = 0; k < DeviceSide::N_SLOTS; k++) { if (d->h_stage[k]) (void)hipHostFree(d->h_stage[k]); if (d->stage_done[k]) (void)hipEventDestroy(d->stage_done[k]); }
+    for (int k = 0; k < DeviceSide::N_SLOTS; k++) if (d->h_stage[k]) (void)hipHostFree(d->h_stage[k]);
     if (d->h_status) (void)hipHostFree(d->h_status);
     if (d->d_rank_mask) (void)hipFree(d->d_rank_mask);
     if (d->d_overflow) (void)hipFree(d->d_overflow);
@@ -329,7 +328,6 @@ int setup_device(zf_engine *e) {
     HIP_TRY(hipMemset(d->d_counters, 0, 2 * COUNTER_SET_WORDS * 4));
     HIP_TRY(hipHostMalloc((void **)&d->h_status, 32 * DeviceSide::N_SLOTS, hipHostMallocDefault));
     memset(d->h_status, 0, 32 * DeviceSide::N_SLOTS);
-    for (auto &ev : d->stage_done) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) {     // staging room every engine has from the start (zf_compute_mask_noalloc never grows it)
         HIP_TRY(hipHostMalloc(&d->h_stage[k], NOALLOC_STAGE_BYTES, hipHostMallocDefault));
         d->stage_cap[k] = NOALLOC_STAGE_BYTES;
@@ -1031,7 +1029,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     HIP_TRY(hipSetDevice(d->device));
     if (d->pending >= (uint32_t)DeviceSide::N_SLOTS) return fail(ZF_ERR_INVALID_ARG, "too many asynchronous mask calls in flight: call zf_mask_wait");
     const uint32_t slot = d->next_slot;
-    if (d->pending) HIP_TRY(hipEventSynchronize(d->stage_done[slot]));   // the slot's previous upload has left the staging buffer (with no call in flight zf_mask_wait has seen to that)
+    // (no event marks the slot free: at most N_SLOTS calls are in flight between two zf_mask_wait calls, so the call that used it before has been waited for)
     for (int b = 0; b < batch; b++)
         if (!states[b] || states[b]->eng != e) return fail(ZF_ERR_INVALID_ARG, "state " + std::to_string(b) + " is null or belongs to another engine");
     // (noalloc with an explicit item budget: the budget is one of the per-block automaton's wavefronts)
@@ -1261,9 +1259,12 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         a.aut_states = n_states; a.aut_arena = arena; a.aut_scratch = scratch;
         a.aut_base_sets = base_sets; a.aut_base_items = base_items;
         a.aut_wide = wide ? 1 : 0;
-        // blocks per row: enough to fill the chip about once, at most one block per pass of AUT_SUB_WORDS words
+        // blocks per row: as many as the chip holds at once, at most two per compute unit and one per pass of AUT_SUB_WORDS words.
+        // (Every block works its row's automaton out from the start: a second round of blocks, where the wide byte step's scratch
+        // leaves room for one block per compute unit, took as long as the first.)
         const int n_sub = (d->tab.Wr + AUT_SUB_WORDS - 1) / AUT_SUB_WORDS;
-        a.aut_parts = std::max(1, std::min(n_sub, (2 * std::max(1, d->cus) + std::max(nb, 1) - 1) / std::max(nb, 1)));
+        const int resident = std::min(2, automaton_blocks_per_cu(a)) * std::max(1, d->cus);
+        a.aut_parts = std::max(1, std::min(n_sub, resident == 2 * d->cus ? (resident + std::max(nb, 1) - 1) / std::max(nb, 1) : resident / std::max(nb, 1)));
     }
     const bool prof = d->profiling;
     d->report.chart_bytes = (int64_t)total;
@@ -1282,7 +1283,6 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     if (run_kernels) HIP_TRY(launch_finish(a, d->cus, stream));   // fallback pass (if anything was listed) + permutation; also hands the counters to the host and clears the next call's
     if (sc) HIP_TRY(launch_gather(a, stream));            // every row's finished mask from its pool slot to the caller's tensor
     if (prof) HIP_TRY(hipEventRecord(d->ev[3], stream));
-    HIP_TRY(hipEventRecord(d->stage_done[slot], stream));   // the staging slot is free again once this point of the stream is reached
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;
@@ -1781,8 +1781,6 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
     }
     if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
-    // No event marks the staging slot free: at most N_SLOTS calls are in flight between two zf_mask_wait calls, so the call that
-    // used this slot before has been waited for.
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;

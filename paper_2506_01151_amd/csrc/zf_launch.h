@@ -234,6 +234,7 @@ hipError_t launch_upload(const void *pinned_src, void *dst, size_t bytes, hipStr
 hipError_t launch_cache_merge(const MaskArgs &a, hipStream_t s);
 hipError_t launch_mask_walk(const MaskArgs &a, hipStream_t s);
 uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide);
+int automaton_blocks_per_cu(const MaskArgs &a);   // of the build and the LDS size that a's call launches
 hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s);
 hipError_t prepare_store_kernels();
 uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);

@@ -402,20 +402,27 @@ uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int ar
            aut_round16(((uint32_t)base_sets + 1) * 4) + aut_round16((uint32_t)base_items * 8) + AUT_ENT_LDS * 4 + 256 + 2 * AUT_SUB_WORDS * 4 + AUT_SUB_WORDS / 2 + aut_round16((uint32_t)arena * 8) +
            AUT_WAVES * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
 }
-hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s) {
-    const uint32_t lds = automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_wide != 0);
-    dim3 grid(a.aut_parts, a.batch);
+static void (*automaton_kernel(const MaskArgs &a))(MaskArgs) {
     // two builds of the kernel: without the wide variant of the byte step (its code costs the narrow path ~10 %
     // in registers and instruction fetch) for charts whose sets are all small, and with it
-    if (a.aut_wide) {
-        if (a.mode == 0) hipLaunchKernelGGL((mask_automaton_kernel<0, true>), grid, dim3(AUT_BLOCK), lds, s, a);
-        else if (a.mode == 1) hipLaunchKernelGGL((mask_automaton_kernel<1, true>), grid, dim3(AUT_BLOCK), lds, s, a);
-        else hipLaunchKernelGGL((mask_automaton_kernel<2, true>), grid, dim3(AUT_BLOCK), lds, s, a);
-    } else {
-        if (a.mode == 0) hipLaunchKernelGGL((mask_automaton_kernel<0, false>), grid, dim3(AUT_BLOCK), lds, s, a);
-        else if (a.mode == 1) hipLaunchKernelGGL((mask_automaton_kernel<1, false>), grid, dim3(AUT_BLOCK), lds, s, a);
-        else hipLaunchKernelGGL((mask_automaton_kernel<2, false>), grid, dim3(AUT_BLOCK), lds, s, a);
-    }
+    if (a.aut_wide) return a.mode == 0 ? mask_automaton_kernel<0, true> : a.mode == 1 ? mask_automaton_kernel<1, true> : mask_automaton_kernel<2, true>;
+    return a.mode == 0 ? mask_automaton_kernel<0, false> : a.mode == 1 ? mask_automaton_kernel<1, false> : mask_automaton_kernel<2, false>;
+}
+static uint32_t automaton_lds_of(const MaskArgs &a) {
+    return automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_wide != 0);
+}
+int automaton_blocks_per_cu(const MaskArgs &a) {
+    static thread_local struct { const void *kernel; uint32_t lds; int blocks; } known = {nullptr, 0, 0};   // asked of the runtime once per size
+    const void *k = reinterpret_cast<const void *>(automaton_kernel(a));
+    const uint32_t lds = automaton_lds_of(a);
+    if (known.kernel == k && known.lds == lds) return known.blocks;
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, AUT_BLOCK, lds) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+    known = {k, lds, n};
+    return n;
+}
+hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(automaton_kernel(a), dim3(a.aut_parts, a.batch), dim3(AUT_BLOCK), automaton_lds_of(a), s, a);
     return hipGetLastError();
 }
 }  // namespace zf
