@@ -913,3 +913,50 @@ def test_apply_mask_rows_at_any_multiple_of_an_element(V, B, shift, dtype, torch
     t.view(i).copy_(torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)))
     zf.apply_mask(eng, t, torch.from_numpy(mask.view(np.int32)).cuda())
     assert t.view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, mask).tobytes()
+
+
+LOOKS = [(31, 1, 1, "f32", 0, True), (33, 3, 1, "bf16", 1, True), (2033, 70, 3, "bf16", 3, True), (2048, 130, 130, "f32", 0, True),
+         (6001, 300, 2, "f32", 1, True), (9000, 5, 2, "bf16", 0, False), (9001, 68, 68, "bf16", 7, False)]
+
+
+@pytest.mark.parametrize("V,B,places,dtype,shift,token_cache", LOOKS, ids=[f"{v}x{b}-in-{p}-{d}-at-{s}-{'' if c else 'parser-only'}" for v, b, p, d, s, c in LOOKS])
+def test_states_met_before(V, B, places, dtype, shift, token_cache, torch_cuda, oracle_lib):
+    """The calls at states whose vocabulary has been walked before (mask_look_kernel), mask and masked logits against the oracle: one
+    state with up to 130 rows and more states than travel in the argument block (64), vocabularies below one word and just beyond
+    one, rows of logits at any multiple of an element, tokens of up to 123 bytes (15 are at hand), and every token undecided.  The
+    rows of a second call stand in the states of the first in another order, so that no row finds its own mask in the tensor."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    from tests.helpers import edge_vocab_json
+    torch = torch_cuda
+    toks = edge_vocab_json()[::-1] + configs.CONFIGS[2].vocab(max(V, 31))
+    toks = toks[:V]
+    off, data = wvocab.vocab_csr(toks)
+    g = grammars.json_grammar()
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, token_mask_cache=token_cache, precompute_states=-1)
+    prefixes = [b"[" * (k // 2) + (b'{"a": ' if k & 1 else b"") for k in range(places)]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    rng = np.random.default_rng(V + B)
+    u, i, f = (np.uint32, torch.int32, torch.float32) if dtype == "f32" else (np.uint16, torch.int16, torch.bfloat16)
+    rows = [eng.new_state() for _ in range(B)]
+    for call in range(3):
+        at = (np.arange(B) + 7 * call) % places
+        for s, p in zip(rows, at):
+            s.reset()
+            s.advance_bytes(prefixes[p])
+        bits = rng.integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
+        room = torch.zeros(B * V + shift, dtype=i, device="cuda")
+        t = room[shift:].view(f).view(B, V)
+        t.view(i).copy_(torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)))
+        d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        zf.compute_mask_apply_async(eng, rows, d_mask, t)
+        zf.mask_wait(eng)
+        torch.cuda.synchronize()
+        wanted = np.stack([want[p] for p in at])
+        assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted), call
+        assert t.view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), call
