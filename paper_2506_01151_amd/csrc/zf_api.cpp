@@ -1262,7 +1262,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         // blocks per row: as many as the chip holds at once, at most two per compute unit and one per pass of AUT_SUB_WORDS words.
         // (Every block works its row's automaton out from the start: a second round of blocks, where the wide byte step's scratch
         // leaves room for one block per compute unit, took as long as the first.)
-        const int n_sub = (d->tab.Wr + AUT_SUB_WORDS - 1) / AUT_SUB_WORDS;
+        const int n_sub = (d->tab.Wr + AUT_PART_WORDS - 1) / AUT_PART_WORDS;
         const int resident = std::min(2, automaton_blocks_per_cu(a)) * std::max(1, d->cus);
         a.aut_parts = std::max(1, std::min(n_sub, resident == 2 * d->cus ? (resident + std::max(nb, 1) - 1) / std::max(nb, 1) : resident / std::max(nb, 1)));
     }

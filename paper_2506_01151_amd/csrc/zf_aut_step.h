@@ -28,9 +28,12 @@ enum { AUT_OK = 0, AUT_WIDE = 1, AUT_OVER = 2 };
 static const int AUT_NARROW_TRIES = 96;   // insert attempts after which the narrow variant hands the step to the wide one
 
 // Narrow variant: the set under construction lives in registers (lane j holds new item j), so the
-// duplicate test is one compare + ballot; the source set is read in strips of 64 items.  With ONE_STRIP a
+// duplicate test is one compare whose result is a scalar; the source set is read in strips of 64 items.  The lanes make
+// candidates in parallel, as in the wide variant; entering them goes through the distinct ones in turn.  With ONE_STRIP a
 // source set of more than 64 items is handed to the wide step at once (AUT_WIDE), which saves the strip
 // loop's registers in a kernel that is short of them.
+//   Candidates made one at a time, each with its own trip to LDS for the table entry and thirty instructions to enter it, took
+// 6.8 us for a step that leaves 7 items (mask_automaton_kernel, expression grammar without pruning).
 template <bool WIDE, bool ONE_STRIP = false, class SetsT>
 __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint32_t *sc_w, uint32_t *sc_o, uint32_t sc_cap,
                                                uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out) {
@@ -39,108 +42,104 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
     S.view(cur, src, ns);
     if (ONE_STRIP && ns > 64u) return AUT_WIDE;
     uint32_t nw = 0xFFFFFFFFu, no = 0, nnew = 0, tries = 0;  // no item word is all ones
-    bool saw_end = false, failed = false;                    // failed is sticky: the step runs on and reports at its end
+    bool failed = false;                                     // sticky: the step runs on and reports at its end
     const uint32_t room = sc_cap < 64u ? sc_cap : 64u;
-    auto insert = [&](uint32_t w, uint32_t o) {              // uniform arguments; no branch
-        tries++;
-        const bool fresh = __ballot(nw == w && no == o) == 0;
-        const bool add = fresh && nnew < room;
-        failed |= fresh && !add;
-        const bool mine = add && lane == nnew;
-        nw = mine ? w : nw;
-        no = mine ? o : no;
-        nnew += add ? 1u : 0u;
+    auto equal = [&](uint32_t x, uint32_t s) -> unsigned long long { return __builtin_amdgcn_uicmp(x, s, 32 /* equal */); };   // the lanes on which x is s, as a scalar
+    auto insert = [&](bool has, uint32_t w, uint32_t o) __attribute__((always_inline)) {   // per-lane arguments: every lane with `has` brings a candidate
+        unsigned long long todo = __ballot(has);
+        while (todo) {                                       // once per distinct candidate
+            const int l = __ffsll((long long)todo) - 1;
+            const uint32_t lw = (uint32_t)__builtin_amdgcn_readlane((int)w, l), lo = (uint32_t)__builtin_amdgcn_readlane((int)o, l);
+            todo &= ~(equal(w, lw) & equal(o, lo));
+            tries++;
+            if (equal(nw, lw) & equal(no, lo)) continue;     // in the set already
+            if (nnew < room) {
+                const bool at = lane == nnew;
+                nw = at ? lw : nw; no = at ? lo : no;
+                nnew++;
+            } else failed = true;
+        }
     };
-    auto advance = [&](uint32_t p, uint32_t o) {             // dot arrives at p: skip nullable nonterminals, canonical END item
-        for (;;) {
-            const uint32_t w = T.advpq[p];
-            insert(w, o);
-            if (w & IW_END) { saw_end = true; return; }
-            if ((w & IW_TERM) || !(w & IW_NT_NULLABLE)) return;
+    auto chain = [&](bool on, uint32_t p, uint32_t o) __attribute__((always_inline)) {     // per lane: the dot arrives at p; skip nullable nonterminals, canonical END item
+        while (__ballot(on)) {
+            uint32_t w = 0;
+            if (on) w = T.advpq[p];
+            insert(on, w, o);
+            on = on && !(w & (IW_END | IW_TERM)) && (w & IW_NT_NULLABLE);
             p++;
         }
     };
     for (uint32_t s0 = 0; s0 < ns; s0 += 64) {
         uint32_t sw = IW_END, so = 0;                        // lanes beyond the set hold an inert item
         if (s0 + lane < ns) { const uint2 x = S.item(src, s0 + lane); sw = x.x; so = x.y; }
-        // Scan, terminal items: all DFA steps at once, then the survivors one after the other
-        uint32_t nx = DFA_DEAD, aw = 0;
-        if (sw & IW_TERM) {
-            aw = T.advpq[(sw & IW_POS_MASK) + 1];            // the item behind the terminal, fetched alongside the DFA step
-            nx = dfa_next(T, sw >> 16, byte, cl);
-        }
-        unsigned long long m = __ballot((nx & 0xFFFFu) != DFA_DEAD);
-        while (m) {
-            const int l = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const uint32_t lw = __builtin_amdgcn_readlane(sw, l), lo = __builtin_amdgcn_readlane(so, l), lnx = __builtin_amdgcn_readlane(nx, l);
-            if ((lnx >> 16) & QF_CONT) insert((lw & 0xFFFFu) | (lnx << 16), lo);   // no longest match: keep matching ...
-            if ((lnx >> 16) & QF_ACCEPT) {                                         // ... and also finish here
-                const uint32_t law = __builtin_amdgcn_readlane(aw, l);
-                insert(law, lo);
-                if (law & IW_END) saw_end = true;
-                else if (!(law & IW_TERM) && (law & IW_NT_NULLABLE)) advance((lw & IW_POS_MASK) + 2, lo);
-            }
-        }
-        // Scan, items that wait for a nonterminal Y: the tabulated first steps of every terminal that can begin Y
-        uint32_t sk0 = 0, sk1 = 0;
-        if (!(sw & (IW_TERM | IW_END))) {
+        // Scan, both kinds of item: the DFA step of a terminal; of an item that waits for a nonterminal Y, the tabulated first steps of
+        // every terminal that can begin Y
+        uint32_t nx = DFA_DEAD, sk0 = 0, sk1 = 0;
+        if (sw & IW_TERM) nx = dfa_next(T, sw >> 16, byte, cl);
+        else if (!(sw & IW_END)) {
             const uint32_t Y = (sw >> IW_NT_SHIFT) & IW_NT_MASK;
             sk0 = T.scan_off[Y * T.ncls + cl]; sk1 = T.scan_off[Y * T.ncls + cl + 1];
         }
-        m = __ballot(sk1 > sk0);
-        while (m) {
-            const int l = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const uint32_t k0 = __builtin_amdgcn_readlane(sk0, l), k1 = __builtin_amdgcn_readlane(sk1, l);
-            for (uint32_t e0 = k0; e0 < k1; e0 += 64) {
-                uint2 ef = make_uint2(0, 0);
-                if (e0 + lane < k1) ef = T.scan_list[e0 + lane];
-                const uint32_t n_e = k1 - e0 < 64 ? k1 - e0 : 64;
-                for (uint32_t t = 0; t < n_e; t++) {
-                    const uint32_t ent = __builtin_amdgcn_readlane(ef.x, t), f = __builtin_amdgcn_readlane(ef.y, t);
-                    if (f & QF_CONT) insert(ent, cur);
-                    if (f & QF_ACCEPT) advance((ent & IW_POS_MASK) + 1, cur);
-                }
-            }
+        bool one = (sw & IW_TERM) && (nx & 0xFFFFu) != DFA_DEAD;             // terminal items bring one step ...
+        uint32_t cont = (sw & 0xFFFFu) | (nx << 16), flags = nx >> 16, p = (sw & IW_POS_MASK) + 1, org = so;
+        for (;;) {                                                          // ... the others their list, a step per round
+            const bool listed = !one && sk0 < sk1;
+            if (!__ballot(one || listed)) break;
+            if (listed) { const uint2 ef = T.scan_list[sk0]; sk0++; cont = ef.x; flags = ef.y; p = (ef.x & IW_POS_MASK) + 1; org = cur; }
+            insert((one || listed) && (flags & QF_CONT), cont, org);        // no longest match: keep matching ...
+            chain((one || listed) && (flags & QF_ACCEPT), p, org);          // ... and also finish here
+            one = false;
         }
         if (ONE_STRIP) break;
     }
-    if (saw_end) {
-        // Complete: new items are visited in order; completing may append more
-        unsigned long long visited = 0;
-        for (;;) {
-            const unsigned long long todo = __ballot(lane < nnew && (nw & IW_END)) & ~visited;
-            if (!todo) break;
-            if (WIDE && tries > (uint32_t)AUT_NARROW_TRIES) return AUT_WIDE;   // candidates come one at a time here: an ambiguous grammar makes hundreds, mostly duplicates
-            const int i = __ffsll((long long)todo) - 1;
-            visited |= 1ull << i;
-            const uint32_t w = __builtin_amdgcn_readlane(nw, i);
-            const uint32_t X = (w & IW_POS_MASK) - T.end_base;
-            if (X == T.N - 1) continue;                      // the start rule is complete: the prefix is a sentence
-            const uint32_t o = __builtin_amdgcn_readlane(no, i);
-            uint64_t yp;
-            uint32_t yn;
-            S.view(o, yp, yn);
-            for (uint32_t j0 = 0; j0 < yn; j0 += 64) {
-                uint32_t yw = IW_END, yo = 0;
-                if (j0 + lane < yn) { const uint2 y = S.item(yp, j0 + lane); yw = y.x; yo = y.y; }
-                const bool nt = !(yw & (IW_TERM | IW_END));
-                const uint32_t Y = (yw >> IW_NT_SHIFT) & IW_NT_MASK;
-                uint32_t c0 = 0, c1 = 0, cw0 = 0;
-                if (nt) { c0 = T.comp_off[Y * T.N + X]; c1 = T.comp_off[Y * T.N + X + 1]; }
-                if (c1 > c0) cw0 = T.comp_list[c0];          // every lane fetches the first entry of its own list
-                unsigned long long mm = __ballot(nt && c1 > c0);
-                while (mm) {
-                    const int l = __ffsll((long long)mm) - 1;
-                    mm &= mm - 1;
-                    const uint32_t lc0 = __builtin_amdgcn_readlane(c0, l), lc1 = __builtin_amdgcn_readlane(c1, l);
-                    for (uint32_t e = lc0; e < lc1; e++) {
-                        const uint32_t cw = e == lc0 ? (uint32_t)__builtin_amdgcn_readlane(cw0, l) : T.comp_list[e];
-                        if (cw != 0xFFFFFFFFu) insert(cw, o);
-                        else advance((__builtin_amdgcn_readlane(yw, l) & IW_POS_MASK) + 1, __builtin_amdgcn_readlane(yo, l));   // Y itself is complete: the waiting item moves on
-                    }
+    // Complete, until no new item is complete: the items of all completed items' origin sets -- the ones that may wait for the
+    // completed nonterminal -- are dealt to the lanes, and the entries of the table that they hit are dealt again.
+    unsigned long long visited = 0;
+    for (;;) {
+        const unsigned long long todo = __ballot(lane < nnew && (nw & IW_END)) & ~visited;
+        if (!todo) break;
+        visited |= todo;
+        const uint32_t X = (nw & IW_POS_MASK) - T.end_base;
+        uint64_t yp = 0;
+        uint32_t yn = 0;
+        if (((todo >> lane) & 1ull) && X != T.N - 1) S.view(no, yp, yn);     // the start rule complete: the prefix is a sentence
+        unsigned long long pend = __ballot(yn > 0);
+        uint32_t from = 0;                                   // of the first pending set: items dealt so far
+        while (pend) {
+            if (WIDE && tries > (uint32_t)AUT_NARROW_TRIES) return AUT_WIDE;   // an ambiguous grammar makes hundreds of candidates, mostly duplicates
+            uint32_t base = 0, oX = 0, oo = 0, at = 0, y_lo = 0, y_hi = 0;
+            bool has = false;
+            while (pend && base < 64u) {
+                const int e = __ffsll((long long)pend) - 1;
+                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)yn, e) - from, take = left < 64u - base ? left : 64u - base;
+                const uint32_t eX = (uint32_t)__builtin_amdgcn_readlane((int)X, e), eo = (uint32_t)__builtin_amdgcn_readlane((int)no, e);
+                const uint32_t e_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yp, e), e_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yp >> 32), e);
+                if (lane - base < take) { has = true; at = from + lane - base; oX = eX; oo = eo; y_lo = e_lo; y_hi = e_hi; }
+                base += take;
+                if (take == left) { pend &= pend - 1; from = 0; } else from += take;
+            }
+            uint32_t yw = IW_END, yo = 0, c0 = 0, c1 = 0;
+            if (has) { const uint2 y = S.item((uint64_t)y_hi << 32 | y_lo, at); yw = y.x; yo = y.y; }
+            if (!(yw & (IW_TERM | IW_END))) { const uint32_t k = ((yw >> IW_NT_SHIFT) & IW_NT_MASK) * T.N + oX; c0 = T.comp_off[k]; c1 = T.comp_off[k + 1]; }
+            unsigned long long hits = __ballot(c0 < c1);
+            uint32_t done = 0;                               // of the first hit's list: entries dealt so far
+            while (hits) {
+                uint32_t dealt = 0, entry = 0, o = 0, p = 0, po = 0;
+                bool mine = false;
+                while (hits && dealt < 64u) {
+                    const int l = __ffsll((long long)hits) - 1;
+                    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)c0, l) + done, left = (uint32_t)__builtin_amdgcn_readlane((int)c1, l) - first;
+                    const uint32_t take = left < 64u - dealt ? left : 64u - dealt;
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)oo, l), lw = (uint32_t)__builtin_amdgcn_readlane((int)yw, l), ly = (uint32_t)__builtin_amdgcn_readlane((int)yo, l);
+                    if (lane - dealt < take) { mine = true; entry = first + lane - dealt; o = lo; p = (lw & IW_POS_MASK) + 1; po = ly; }
+                    dealt += take;
+                    if (take == left) { hits &= hits - 1; done = 0; } else done += take;
                 }
+                uint32_t cw = 0;
+                if (mine) cw = T.comp_list[entry];
+                const bool self = mine && cw == 0xFFFFFFFFu; // the waiting nonterminal itself is complete: the waiting item moves on
+                insert(mine && !self, cw, o);
+                chain(self, p, po);
             }
         }
     }

@@ -15,12 +15,16 @@ static const int WALK_DEPTH_MAX = 32;      // trie depth the walk kernel follows
 static const int BASE_SETS_LDS = 31;       // a row's chart is staged into LDS when it has at most this many sets ...
 static const int BASE_ITEMS_LDS = 64;      // ... and items (the mask-automaton kernel takes larger limits from the host when LDS allows)
 static const int AUT_NARROW_SET_MAX = 8;    // charts whose sets are all this small run the kernel build without the wide variant of the byte step
+// A source set of more items than this goes to the wide variant of the byte step at once.  Both leave the same set; 64 rows of the
+// expression grammar without pruning, sets of up to 17 items, 8 steps of a decode loop: 1,215 us with the line at 8, 1,056 at 16 and at 32.
+static const int AUT_STEP_WIDE_FROM = 32;
 static const int AUT_BASE_SETS_MAX = 1023; // the largest limits the host asks for
 static const int AUT_BASE_ITEMS_MAX = 4096;
 static const int TABLE_LDS_BUDGET = 56 * 1024;
 static const int AUT_WAVES = 8;            // wavefronts per block of the mask-automaton kernel
 static const int AUT_BLOCK = AUT_WAVES * 64;
-static const int AUT_SUB_WORDS = 128;      // words of the rank-ordered bitmap (32 strings each) a block merges and checks per pass ...
+static const int AUT_SUB_WORDS = 512;      // words of the rank-ordered bitmap (32 strings each) a block merges and checks per pass, one per thread ...
+static const int AUT_PART_WORDS = 128;     // ... the fewest a block of a row is made for ...
 static const int AUT_GROUP_WORDS = 4;      // ... taken from the row in groups of this many neighbouring words (two batches of 64 ranks), dealt to the blocks round robin
 static const int AUT_ENT_LDS = 64;         // token-mask-cache rows of the row's current set kept in LDS (more are read from global memory)
 static_assert(AUT_NARROW_SET_MAX <= AUT_ENT_LDS, "the kernel build for small sets keeps all cache-row numbers of a row in LDS");

@@ -27,7 +27,8 @@ struct Aut {               // one block's automaton; every pointer leads into LD
     uint32_t *hash;        // [states_cap] signature of the content (filter for the interning compare)
     uint2 *arena;          // [arena_cap] items of all states
     uint32_t *ctl;         // [0] states handed out, [1] arena items handed out, [2] next batch of strings, [3] number of batches,
-                           // [4] help-queue places handed out, [5] help-queue places taken, [6] batches finished
+                           // [4] help-queue places handed out, [5] help-queue places taken, [6] batches finished,
+                           // [7] undecided strings, [8] byte steps of the whole launch
     uint32_t *hq;          // [AUT_HELP_QUEUE] transitions that wait for a free wavefront: HQ_VALID | state << 8 | class
     const uint8_t *rep;    // [ncls] one byte of each class
     uint32_t states_cap, arena_cap, ncls;
@@ -59,7 +60,7 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
     uint64_t src_p;
     uint32_t src_n;
     S.view(cur, src_p, src_n);
-    int st = WIDE && src_n > (uint32_t)AUT_NARROW_SET_MAX ? AUT_WIDE : aut_step_narrow<WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);   // a wide source set rarely leaves a narrow one
+    int st = WIDE && src_n > (uint32_t)AUT_STEP_WIDE_FROM ? AUT_WIDE : aut_step_narrow<WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);   // a wide source set rarely leaves a narrow one
     if (st == AUT_WIDE) st = WIDE ? aut_step_wide(T, S, sc_w, sc_o, sc_h, sc_cap, cur, byte, cl, lane, nnew, kept) : (int)AUT_OVER;
     if (st != AUT_OK) return AT_FAIL;
     if (nnew == 0) return AT_DEAD;
@@ -107,9 +108,11 @@ template <bool WIDE, class BaseT>
 __device__ __forceinline__ void aut_resolve(const TV &T, const BaseT &B, const Aut &A, uint32_t *sc_w, uint32_t *sc_o, uint32_t *sc_h, uint32_t sc_cap,
                                             uint32_t s, uint32_t cl, uint32_t lane) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // the states this step reads were published by other wavefronts
+    __builtin_amdgcn_s_setprio(3);   // everybody waits for this wavefront: it issues ahead of those that poll (8 steps of 64 rows: 1,395 -> 1,305 us)
     const uint32_t r = aut_transition<WIDE>(T, B, A, sc_w, sc_o, sc_h, sc_cap, s, A.rep[cl], cl, lane);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the new state before the transition that leads to it
     if (lane == 0) lds_store(&A.trans[s * A.ncls + cl], r);
+    __builtin_amdgcn_s_setprio(0);
 }
 
 // A wavefront whose strings miss several transitions at once computes one and leaves the others in
@@ -143,6 +146,9 @@ __host__ __device__ inline uint32_t aut_round16(uint32_t x) { return (x + 15u) &
 // swallows whole are valid at once), lists the strings that need the parser, and its wavefronts
 // take the list in batches of 64 strings, one lane per string.  The verdicts of a slice are
 // collected in LDS and stored once: no atomics on global memory and nothing to clear beforehand.
+//   What bounds it: the chain of byte steps that the strings of a block need one after the other (six to twelve, 3 to 10 us each),
+// not bandwidth and not the strings (a wavefront walks for 20 of 110 us).  So a pass takes a word per thread -- with 128 words a block of 64 rows
+// went through its chains in five passes, one behind the other --, and a wavefront that computes a step issues first.
 // MODE: which grammar tables are staged in LDS (0 all, 1 the small ones, 2 none).  WIDE: the build that
 // holds the wide variant of the byte step and its hash table; the build without it is for charts whose
 // sets are all small (the host knows: it packs them), where a set of more than 64 items fails over to the
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     A.trans = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16(A.states_cap * A.ncls * 4);
     A.hdr = reinterpret_cast<uint2 *>(smem + off); off += aut_round16(A.states_cap * 8);
     A.hash = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16(A.states_cap * 4);
-    A.ctl = reinterpret_cast<uint32_t *>(smem + off); off += 32;
+    A.ctl = reinterpret_cast<uint32_t *>(smem + off); off += 48;
     A.hq = reinterpret_cast<uint32_t *>(smem + off); off += AUT_HELP_QUEUE * 4;
     const uint32_t base_sets_cap = (uint32_t)a.aut_base_sets, base_items_cap = (uint32_t)a.aut_base_items;
     uint32_t *l_so = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16((base_sets_cap + 1) * 4);
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     A.rep = l_rep;
     uint32_t *vslice = reinterpret_cast<uint32_t *>(smem + off); off += AUT_SUB_WORDS * 4;
     uint32_t *cslice = reinterpret_cast<uint32_t *>(smem + off); off += AUT_SUB_WORDS * 4;
-    uint8_t *pairs = smem + off; off += AUT_SUB_WORDS / 2;   // slots of the word pairs that hold undecided strings
+    uint8_t *pairs = smem + off; off += AUT_SUB_WORDS / 2;   // numbers of the word pairs that hold undecided strings
     A.arena = reinterpret_cast<uint2 *>(smem + off); off += aut_round16(A.arena_cap * 8);
     uint32_t *sc_w = reinterpret_cast<uint32_t *>(smem + off) + (size_t)wave * (2 * sc_cap + (WIDE ? aut_hash_places(sc_cap) : 0u));   // the hash table belongs to the wide byte step
     uint32_t *sc_o = sc_w + sc_cap, *sc_h = sc_o + sc_cap;
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     for (uint32_t k = tid; k < A.states_cap * A.ncls; k += AUT_BLOCK) A.trans[k] = AT_NONE;
     for (uint32_t k = tid; k < A.states_cap; k += AUT_BLOCK) A.hdr[k] = make_uint2(0, 0xFFFFFFFFu);
     for (uint32_t k = tid; k < (uint32_t)AUT_HELP_QUEUE; k += AUT_BLOCK) A.hq[k] = 0;
-    if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; }
+    if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; A.ctl[7] = 0; A.ctl[8] = 0; }
     const uint32_t *b_ent = (!WIDE || ent_fits) ? l_ent : g_ent;   // without the wide step: sets of at most AUT_NARROW_SET_MAX items, so at most that many cache rows
     const uint32_t *b_so = (!WIDE || base_fits) ? l_so : g_so;   // the build without the wide step is launched only when every chart fits:
     const uint2 *b_it = (!WIDE || base_fits) ? l_it : g_it;      // its chart pointers are LDS addresses at compile time
@@ -241,38 +247,34 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
             return grp < n_groups ? grp * AUT_GROUP_WORDS + t % AUT_GROUP_WORDS : 0xFFFFFF00u;
         };
         if (tid == 0) { A.ctl[2] = 0; A.ctl[3] = 0; A.ctl[6] = 0; }
-        if (tid < AUT_SUB_WORDS) { vslice[tid] = 0; cslice[tid] = rc.n_ent == 0 ? 0xFFFFFFFFu : 0u; }
         __syncthreads();                                     // also: tables, chart and automaton set-up are in place
-        // ---- merge the token-mask cache rows (all threads: word slot tid % SUB, cache rows tid / SUB, + 4, ...) ----
+        // ---- every thread's word: merge the token-mask cache rows, and list the word pairs (64 ranks) that hold undecided strings ----
+        static_assert(AUT_SUB_WORDS == AUT_BLOCK, "a word per thread");
         {
-            const uint32_t t = tid % AUT_SUB_WORDS, w = word_of(t);
-            uint32_t v = 0, c = 0;
-            if (w < Wr)
-                for (uint32_t k = tid / AUT_SUB_WORDS; k < rc.n_ent; k += AUT_BLOCK / AUT_SUB_WORDS) {
+            const uint32_t w = word_of(tid), r0 = w * 32u;
+            uint32_t v = 0, c = rc.n_ent == 0 ? 0xFFFFFFFFu : 0u;
+            if (w < Wr) {
+#pragma unroll 4
+                for (uint32_t k = 0; k < rc.n_ent; k++) {
                     const size_t r = (size_t)b_ent[k] * Wr + w;
                     v |= D.ci_valid[r]; c |= D.ci_cd[r];
                 }
-            if (v) atomicOr(&vslice[t], v);
-            if (c) atomicOr(&cslice[t], c);
-        }
-        __syncthreads();
-        // ---- the undecided strings, and the word pairs (64 ranks) that hold any: one wavefront, one ballot ----
-        if (tid < AUT_SUB_WORDS / 2) {                       // the first wavefront
-            uint32_t want[2];
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const uint32_t w = word_of(2 * tid + h), r0 = w * 32u;
-                want[h] = cslice[2 * tid + h] & ~vslice[2 * tid + h];
-                if (w >= Wr || r0 >= n_strings) want[h] = 0;                 // strings beyond the last one do not exist
-                else if (n_strings - r0 < 32u) want[h] &= (1u << (n_strings - r0)) - 1u;
-                cslice[2 * tid + h] = want[h];
             }
-            const unsigned long long nz = __ballot((want[0] | want[1]) != 0);
-            if (want[0] | want[1]) pairs[__popcll(nz & ((1ull << lane) - 1ull))] = (uint8_t)tid;
-            uint32_t cnt = (uint32_t)(__popc(want[0]) + __popc(want[1]));
+            uint32_t want = c & ~v;
+            if (w >= Wr || r0 >= n_strings) want = 0;        // strings beyond the last one do not exist
+            else if (n_strings - r0 < 32u) want &= (1u << (n_strings - r0)) - 1u;
+            vslice[tid] = v; cslice[tid] = want;
+            const unsigned long long nz = __ballot(want != 0), some = (nz | nz >> 1) & 0x5555555555555555ull;
+            if (some) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&A.ctl[3], (uint32_t)__popcll(some));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                if ((some >> lane) & 1ull) pairs[at + (uint32_t)__popcll(some & ((1ull << lane) - 1ull))] = (uint8_t)(tid >> 1);
+            }
+            uint32_t n_und = (uint32_t)__popc(want);
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d);
-            if (lane == 0) { A.ctl[3] = (uint32_t)__popcll(nz); if (cnt) atomicAdd(&a.counters[1], cnt); }
+            for (int d = 32; d >= 1; d >>= 1) n_und += __shfl_xor(n_und, d);
+            if (lane == 0 && n_und) atomicAdd(&A.ctl[7], n_und);
         }
         const BaseG B{b_so, b_it, rc.n_sets, b_so[rc.n_sets - 1], rc.n_items};
         if (j0 == 0 && wave == AUT_WAVES - 1)                // meanwhile the last wavefront settles the dead transitions of the row's current set
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
                     if (!batch) spins = 0;
                 } else if (!progress && q == AUT_HQ_EMPTY) { // everything this wavefront waits for is being computed by others
                     if (!batch && (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(&A.ctl[6])) >= n_pairs) break;   // all batches finished, nothing queued
-                    __builtin_amdgcn_s_sleep(4);
+                    __builtin_amdgcn_s_sleep(16);
                     if (++spins > (uint32_t)AUT_SPIN_LIMIT) {   // bounded wait: hand the strings to the fallback
                         if (!batch) break;
                         fail = fail || live;
@@ -380,9 +382,14 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
             }
         }
         __syncthreads();
-        if (tid < AUT_SUB_WORDS) { const uint32_t w = word_of(tid); if (w < Wr) a.rank_mask[(size_t)row * Wr + w] = vslice[tid]; }
+        { const uint32_t w = word_of(tid); if (w < Wr) a.rank_mask[(size_t)row * Wr + w] = vslice[tid]; }
     }
-    if (lane == 0 && steps) atomicAdd(&a.counters[3], steps);
+    if (lane == 0 && steps) atomicAdd(&A.ctl[8], steps);
+    __syncthreads();
+    if (tid == 0) {                                          // one addition per block: thousands of them queue up at one address
+        if (A.ctl[7]) atomicAdd(&a.counters[1], A.ctl[7]);
+        if (A.ctl[8]) atomicAdd(&a.counters[3], A.ctl[8]);
+    }
 }
 
 }  // namespace
@@ -398,7 +405,7 @@ hipError_t prepare_automaton_kernels() {
 }
 
 uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide) {
-    return table_bytes(t, mode) + aut_round16((uint32_t)states * (uint32_t)t.n_cls * 4) + aut_round16((uint32_t)states * 8) + aut_round16((uint32_t)states * 4) + 32 + AUT_HELP_QUEUE * 4 +
+    return table_bytes(t, mode) + aut_round16((uint32_t)states * (uint32_t)t.n_cls * 4) + aut_round16((uint32_t)states * 8) + aut_round16((uint32_t)states * 4) + 48 + AUT_HELP_QUEUE * 4 +
            aut_round16(((uint32_t)base_sets + 1) * 4) + aut_round16((uint32_t)base_items * 8) + AUT_ENT_LDS * 4 + 256 + 2 * AUT_SUB_WORDS * 4 + AUT_SUB_WORDS / 2 + aut_round16((uint32_t)arena * 8) +
            AUT_WAVES * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
 }

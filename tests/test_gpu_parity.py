@@ -960,3 +960,30 @@ def test_states_met_before(V, B, places, dtype, shift, token_cache, torch_cuda, 
         wanted = np.stack([want[p] for p in at])
         assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted), call
         assert t.view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), call
+
+
+@pytest.mark.parametrize("V,B", [(16384, 300), (16385, 300), (33001, 300), (4096, 1), (4097, 3)])
+def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
+    """The per-block automaton where a row's share of a block is one word less, and more, than a pass takes (512 words; 300 rows have a block
+    each), and where a row has hardly a block's worth of words: an ambiguous grammar with pruning off, against the oracle."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    cfg = configs.CONFIGS[5]
+    g, toks = cfg.grammar(), cfg.vocab(V)
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, pruning=False, state_cache_entries=-1)
+    prefixes = [b"", b"a+b*c", b"((x", b"7*(a+b)"][:B]
+    want, rows = [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    for b in range(B):
+        rows.append(eng.new_state())
+        rows[-1].advance_bytes(prefixes[b % len(prefixes)])
+    d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, rows, d_mask)
+    got = d_mask.cpu().numpy().view(np.uint32)
+    for b in range(B):
+        assert np.array_equal(got[b], want[b % len(prefixes)]), b
