@@ -14,7 +14,7 @@ static const int WALK_NODES_LDS = 80;      // trie nodes of a chunk the walk ker
 static const int WALK_DEPTH_MAX = 32;      // trie depth the walk kernel follows (deeper paths go to the fallback)
 static const int BASE_SETS_LDS = 31;       // a row's chart is staged into LDS when it has at most this many sets ...
 static const int BASE_ITEMS_LDS = 64;      // ... and items (the mask-automaton kernel takes larger limits from the host when LDS allows)
-static const int AUT_NARROW_SET_MAX = 8;    // charts whose sets are all this small run the kernel build without the wide variant of the byte step
+static const int AUT_NARROW_SET_MAX = 16;   // charts whose sets are all this small run the kernel build without the wide variant of the byte step (chart addresses known to be LDS, no hash table: 64 rows of the expression grammar without pruning, 8 steps: 1,056 us with the line at 8, 988 at 16; a set that outgrows the narrow step there goes to the fallback pass)
 // A source set of more items than this goes to the wide variant of the byte step at once.  Both leave the same set; 64 rows of the
 // expression grammar without pruning, sets of up to 17 items, 8 steps of a decode loop: 1,215 us with the line at 8, 1,056 at 16 and at 32.
 static const int AUT_STEP_WIDE_FROM = 32;
