@@ -329,6 +329,18 @@ __device__ __forceinline__ void aut_mark_dead(const TV &T, uint32_t ncls, const 
         const bool a_nt = T.scan_off[Y * T.ncls + c + 1] > T.scan_off[Y * T.ncls + c];
         return !end && (term ? a_term : a_nt);
     };
+    if (ncls <= 16u && n <= 32u) {                           // few classes: four items or more side by side, a lane for each item and class
+        const uint32_t sh = ncls > 8u ? 4u : ncls > 4u ? 3u : 2u, c = lane & ((1u << sh) - 1u), cc = c < ncls ? c : ncls - 1u;
+        const uint32_t byte = rep[cc];
+        unsigned long long alive = 0;
+        for (uint32_t i0 = 0; i0 < n; i0 += 64u >> sh) {
+            const uint32_t i = i0 + (lane >> sh);
+            alive |= __ballot(survives(i < n ? item(i) : (uint32_t)IW_END, byte, cc));
+        }
+        for (uint32_t k = 32u; k >> sh; k >>= 1) alive |= alive >> k;
+        if (lane < ncls && !((alive >> lane) & 1ull)) dead(lane);
+        return;
+    }
     if (WIDE && n > 16u) {                                   // a wide set: one item per lane, the classes in turn
         for (uint32_t c0 = 0; c0 < ncls; c0 += 64) {
             const uint32_t nc = ncls - c0 < 64u ? ncls - c0 : 64u;
