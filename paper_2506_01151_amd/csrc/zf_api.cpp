@@ -1233,13 +1233,13 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         int scratch = 0, n_states = 0, arena = 0, base_sets = 0, base_items = 0;
         // The build without the wide byte step also takes the chart from LDS only (its pointers are then
         // known to be LDS addresses): it serves calls whose sets are all small and whose charts all fit.
-        bool wide = biggest_set > (size_t)AUT_NARROW_SET_MAX;
+        int step = biggest_set <= (size_t)AUT_NARROW_SET_MAX ? AUT_STEP_NARROW : biggest_set <= (size_t)AUT_LANES_SET_MAX ? AUT_STEP_LANES : AUT_STEP_WIDE;
         const uint32_t lds_max = 160u * 1024u;
         for (;;) {
             scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
             n_states = AUT_STATES_DEFAULT; arena = std::max(1024, 8 * scratch);
             base_sets = BASE_SETS_LDS; base_items = BASE_ITEMS_LDS;
-            auto lds_now = [&]() { return automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, base_sets, base_items, wide); };
+            auto lds_now = [&]() { return automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, base_sets, base_items, step == AUT_STEP_WIDE); };
             while (lds_now() > lds_max && arena > 2 * scratch) arena /= 2;
             while (lds_now() > lds_max && n_states > 8) n_states /= 2;
             while (lds_now() > lds_max && scratch > 32) { scratch /= 2; arena = std::max(arena / 2, 2 * scratch); }
@@ -1249,16 +1249,16 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
                 const int want_sets = (int)std::max<size_t>(BASE_SETS_LDS, (most_sets + 32) / 32 * 32 - 1);
                 const int want_items = (int)std::max<size_t>(BASE_ITEMS_LDS, (most_items + 63) / 64 * 64);
                 if (want_sets <= AUT_BASE_SETS_MAX && want_items <= AUT_BASE_ITEMS_MAX &&
-                    automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, want_sets, want_items, wide) <= lds_max) {
+                    automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, want_sets, want_items, step == AUT_STEP_WIDE) <= lds_max) {
                     base_sets = want_sets; base_items = want_items;
                 }
             }
-            if (wide || (most_sets <= (size_t)base_sets && most_items <= (size_t)base_items)) break;
-            wide = true;                                  // some chart stays in global memory: the other build
+            if (step == AUT_STEP_WIDE || (most_sets <= (size_t)base_sets && most_items <= (size_t)base_items)) break;
+            step = AUT_STEP_WIDE;                         // some chart stays in global memory: the other build
         }
         a.aut_states = n_states; a.aut_arena = arena; a.aut_scratch = scratch;
         a.aut_base_sets = base_sets; a.aut_base_items = base_items;
-        a.aut_wide = wide ? 1 : 0;
+        a.aut_step = step;
         // blocks per row: as many as the chip holds at once, at most two per compute unit and one per pass of AUT_SUB_WORDS words.
         // (Every block works its row's automaton out from the start: a second round of blocks, where the wide byte step's scratch
         // leaves room for one block per compute unit, took as long as the first.)

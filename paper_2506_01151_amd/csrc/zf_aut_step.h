@@ -1,5 +1,5 @@
 // The wavefront-cooperative Earley byte step (Scan + Complete with tabulated Predict, Section 3.2) that the
-// mask automata are built with, in two variants, and the settling of a new state's dead transitions.  The
+// mask automata are built with, in three variants, and the settling of a new state's dead transitions.  The
 // functions are templates over a "sets view" S: S.view(ref, h, n) resolves an origin reference to a handle of
 // the set it names (a 64-bit word: lanes pass it round by shuffle) and its item count, S.item(h, i) reads item
 // i of that set -- so the same step serves an automaton that lives in one block's LDS, one that lives in
@@ -21,19 +21,16 @@ __device__ __forceinline__ uint32_t lds_load(const uint32_t *p) { return __hip_a
 __device__ __forceinline__ void lds_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 
 // One Earley byte step from state s on byte class cl is done by a whole wavefront with uniform
-// control flow (all lanes call these functions with identical arguments).  Both variants leave the
+// control flow (all lanes call these functions with identical arguments).  All variants leave the
 // new set, completed items dropped, in the wavefront's scratch (sc_w, sc_o) and return AUT_OK,
-// AUT_WIDE (narrow variant only: more than 64 new items, or too many candidates) or AUT_OVER (no room).
+// AUT_WIDE (not the wide variant: more than 64 new items, or too many candidates) or AUT_OVER (no room).
 enum { AUT_OK = 0, AUT_WIDE = 1, AUT_OVER = 2 };
 static const int AUT_NARROW_TRIES = 96;   // insert attempts after which the narrow variant hands the step to the wide one
 
 // Narrow variant: the set under construction lives in registers (lane j holds new item j), so the
-// duplicate test is one compare whose result is a scalar; the source set is read in strips of 64 items.  The lanes make
-// candidates in parallel, as in the wide variant; entering them goes through the distinct ones in turn.  With ONE_STRIP a
+// duplicate test is one compare + ballot; the source set is read in strips of 64 items.  With ONE_STRIP a
 // source set of more than 64 items is handed to the wide step at once (AUT_WIDE), which saves the strip
 // loop's registers in a kernel that is short of them.
-//   Candidates made one at a time, each with its own trip to LDS for the table entry and thirty instructions to enter it, took
-// 6.8 us for a step that leaves 7 items (mask_automaton_kernel, expression grammar without pruning).
 template <bool WIDE, bool ONE_STRIP = false, class SetsT>
 __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint32_t *sc_w, uint32_t *sc_o, uint32_t sc_cap,
                                                uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out) {
@@ -41,6 +38,136 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
     uint32_t ns;
     S.view(cur, src, ns);
     if (ONE_STRIP && ns > 64u) return AUT_WIDE;
+    uint32_t nw = 0xFFFFFFFFu, no = 0, nnew = 0, tries = 0;  // no item word is all ones
+    bool saw_end = false, failed = false;                    // failed is sticky: the step runs on and reports at its end
+    const uint32_t room = sc_cap < 64u ? sc_cap : 64u;
+    auto insert = [&](uint32_t w, uint32_t o) {              // uniform arguments; no branch
+        tries++;
+        const bool fresh = __ballot(nw == w && no == o) == 0;
+        const bool add = fresh && nnew < room;
+        failed |= fresh && !add;
+        const bool mine = add && lane == nnew;
+        nw = mine ? w : nw;
+        no = mine ? o : no;
+        nnew += add ? 1u : 0u;
+    };
+    auto advance = [&](uint32_t p, uint32_t o) {             // dot arrives at p: skip nullable nonterminals, canonical END item
+        for (;;) {
+            const uint32_t w = T.advpq[p];
+            insert(w, o);
+            if (w & IW_END) { saw_end = true; return; }
+            if ((w & IW_TERM) || !(w & IW_NT_NULLABLE)) return;
+            p++;
+        }
+    };
+    for (uint32_t s0 = 0; s0 < ns; s0 += 64) {
+        uint32_t sw = IW_END, so = 0;                        // lanes beyond the set hold an inert item
+        if (s0 + lane < ns) { const uint2 x = S.item(src, s0 + lane); sw = x.x; so = x.y; }
+        // Scan, terminal items: all DFA steps at once, then the survivors one after the other
+        uint32_t nx = DFA_DEAD, aw = 0;
+        if (sw & IW_TERM) {
+            aw = T.advpq[(sw & IW_POS_MASK) + 1];            // the item behind the terminal, fetched alongside the DFA step
+            nx = dfa_next(T, sw >> 16, byte, cl);
+        }
+        unsigned long long m = __ballot((nx & 0xFFFFu) != DFA_DEAD);
+        while (m) {
+            const int l = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const uint32_t lw = __builtin_amdgcn_readlane(sw, l), lo = __builtin_amdgcn_readlane(so, l), lnx = __builtin_amdgcn_readlane(nx, l);
+            if ((lnx >> 16) & QF_CONT) insert((lw & 0xFFFFu) | (lnx << 16), lo);   // no longest match: keep matching ...
+            if ((lnx >> 16) & QF_ACCEPT) {                                         // ... and also finish here
+                const uint32_t law = __builtin_amdgcn_readlane(aw, l);
+                insert(law, lo);
+                if (law & IW_END) saw_end = true;
+                else if (!(law & IW_TERM) && (law & IW_NT_NULLABLE)) advance((lw & IW_POS_MASK) + 2, lo);
+            }
+        }
+        // Scan, items that wait for a nonterminal Y: the tabulated first steps of every terminal that can begin Y
+        uint32_t sk0 = 0, sk1 = 0;
+        if (!(sw & (IW_TERM | IW_END))) {
+            const uint32_t Y = (sw >> IW_NT_SHIFT) & IW_NT_MASK;
+            sk0 = T.scan_off[Y * T.ncls + cl]; sk1 = T.scan_off[Y * T.ncls + cl + 1];
+        }
+        m = __ballot(sk1 > sk0);
+        while (m) {
+            const int l = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const uint32_t k0 = __builtin_amdgcn_readlane(sk0, l), k1 = __builtin_amdgcn_readlane(sk1, l);
+            for (uint32_t e0 = k0; e0 < k1; e0 += 64) {
+                uint2 ef = make_uint2(0, 0);
+                if (e0 + lane < k1) ef = T.scan_list[e0 + lane];
+                const uint32_t n_e = k1 - e0 < 64 ? k1 - e0 : 64;
+                for (uint32_t t = 0; t < n_e; t++) {
+                    const uint32_t ent = __builtin_amdgcn_readlane(ef.x, t), f = __builtin_amdgcn_readlane(ef.y, t);
+                    if (f & QF_CONT) insert(ent, cur);
+                    if (f & QF_ACCEPT) advance((ent & IW_POS_MASK) + 1, cur);
+                }
+            }
+        }
+        if (ONE_STRIP) break;
+    }
+    if (saw_end) {
+        // Complete: new items are visited in order; completing may append more
+        unsigned long long visited = 0;
+        for (;;) {
+            const unsigned long long todo = __ballot(lane < nnew && (nw & IW_END)) & ~visited;
+            if (!todo) break;
+            if (WIDE && tries > (uint32_t)AUT_NARROW_TRIES) return AUT_WIDE;   // candidates come one at a time here: an ambiguous grammar makes hundreds, mostly duplicates
+            const int i = __ffsll((long long)todo) - 1;
+            visited |= 1ull << i;
+            const uint32_t w = __builtin_amdgcn_readlane(nw, i);
+            const uint32_t X = (w & IW_POS_MASK) - T.end_base;
+            if (X == T.N - 1) continue;                      // the start rule is complete: the prefix is a sentence
+            const uint32_t o = __builtin_amdgcn_readlane(no, i);
+            uint64_t yp;
+            uint32_t yn;
+            S.view(o, yp, yn);
+            for (uint32_t j0 = 0; j0 < yn; j0 += 64) {
+                uint32_t yw = IW_END, yo = 0;
+                if (j0 + lane < yn) { const uint2 y = S.item(yp, j0 + lane); yw = y.x; yo = y.y; }
+                const bool nt = !(yw & (IW_TERM | IW_END));
+                const uint32_t Y = (yw >> IW_NT_SHIFT) & IW_NT_MASK;
+                uint32_t c0 = 0, c1 = 0, cw0 = 0;
+                if (nt) { c0 = T.comp_off[Y * T.N + X]; c1 = T.comp_off[Y * T.N + X + 1]; }
+                if (c1 > c0) cw0 = T.comp_list[c0];          // every lane fetches the first entry of its own list
+                unsigned long long mm = __ballot(nt && c1 > c0);
+                while (mm) {
+                    const int l = __ffsll((long long)mm) - 1;
+                    mm &= mm - 1;
+                    const uint32_t lc0 = __builtin_amdgcn_readlane(c0, l), lc1 = __builtin_amdgcn_readlane(c1, l);
+                    for (uint32_t e = lc0; e < lc1; e++) {
+                        const uint32_t cw = e == lc0 ? (uint32_t)__builtin_amdgcn_readlane(cw0, l) : T.comp_list[e];
+                        if (cw != 0xFFFFFFFFu) insert(cw, o);
+                        else advance((__builtin_amdgcn_readlane(yw, l) & IW_POS_MASK) + 1, __builtin_amdgcn_readlane(yo, l));   // Y itself is complete: the waiting item moves on
+                    }
+                }
+            }
+        }
+    }
+    if (failed) return nnew >= 64u ? AUT_WIDE : AUT_OVER;
+    // completed items are needed only while their own set is processed: store the others
+    const bool keep = lane < nnew && !(nw & IW_END);
+    const unsigned long long kb = __ballot(keep);
+    if (keep) { const uint32_t at = (uint32_t)__popcll(kb & ((1ull << lane) - 1ull)); sc_w[at] = nw; sc_o[at] = no; }
+    nnew_out = nnew;
+    kept_out = (uint32_t)__popcll(kb);
+    return AUT_OK;
+}
+
+// Variant for sets of a dozen items or two (the charts of an ambiguous grammar): the set under construction lives in registers as in the
+// narrow variant, and the lanes make candidates in parallel as in the wide one -- in Complete the items of the completed items' origin sets
+// are dealt to the lanes, then the entries of the table that they hit.  Only distinct candidates are entered in turn, each through compares
+// whose results are scalars.  No hash table to clear, no set in LDS to probe: sources of 9 to 16 items, 64 rows of the expression grammar
+// without pruning, 8 steps of a decode loop: 1,215 us through the wide variant, 1,056 through this.  For sets of a few items with a candidate or two the
+// dealing costs more than it saves (per-block automaton, 16 rows of a JSON schema: 61 us per step with the narrow variant, 65 with this; trie walk 103
+// and 125).
+static const int AUT_LANES_TRIES = 96;    // distinct candidates per round, summed up, after which this variant hands the step to the wide one (HAND_OVER)
+template <bool HAND_OVER, class SetsT>
+__device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint32_t *sc_w, uint32_t *sc_o, uint32_t sc_cap,
+                                              uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out) {
+    uint64_t src;
+    uint32_t ns;
+    S.view(cur, src, ns);
     uint32_t nw = 0xFFFFFFFFu, no = 0, nnew = 0, tries = 0;  // no item word is all ones
     bool failed = false;                                     // sticky: the step runs on and reports at its end
     const uint32_t room = sc_cap < 64u ? sc_cap : 64u;
@@ -90,7 +217,6 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
             chain((one || listed) && (flags & QF_ACCEPT), p, org);          // ... and also finish here
             one = false;
         }
-        if (ONE_STRIP) break;
     }
     // Complete, until no new item is complete: the items of all completed items' origin sets -- the ones that may wait for the
     // completed nonterminal -- are dealt to the lanes, and the entries of the table that they hit are dealt again.
@@ -106,7 +232,7 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
         unsigned long long pend = __ballot(yn > 0);
         uint32_t from = 0;                                   // of the first pending set: items dealt so far
         while (pend) {
-            if (WIDE && tries > (uint32_t)AUT_NARROW_TRIES) return AUT_WIDE;   // an ambiguous grammar makes hundreds of candidates, mostly duplicates
+            if (HAND_OVER && tries > (uint32_t)AUT_LANES_TRIES) return AUT_WIDE;   // an ambiguous grammar makes hundreds of candidates, mostly duplicates
             uint32_t base = 0, oX = 0, oo = 0, at = 0, y_lo = 0, y_hi = 0;
             bool has = false;
             while (pend && base < 64u) {

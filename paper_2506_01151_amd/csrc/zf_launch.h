@@ -14,10 +14,12 @@ static const int WALK_NODES_LDS = 80;      // trie nodes of a chunk the walk ker
 static const int WALK_DEPTH_MAX = 32;      // trie depth the walk kernel follows (deeper paths go to the fallback)
 static const int BASE_SETS_LDS = 31;       // a row's chart is staged into LDS when it has at most this many sets ...
 static const int BASE_ITEMS_LDS = 64;      // ... and items (the mask-automaton kernel takes larger limits from the host when LDS allows)
-static const int AUT_NARROW_SET_MAX = 16;   // charts whose sets are all this small run the kernel build without the wide variant of the byte step (chart addresses known to be LDS, no hash table: 64 rows of the expression grammar without pruning, 8 steps: 1,056 us with the line at 8, 988 at 16; a set that outgrows the narrow step there goes to the fallback pass)
-// A source set of more items than this goes to the wide variant of the byte step at once.  Both leave the same set; 64 rows of the
-// expression grammar without pruning, sets of up to 17 items, 8 steps of a decode loop: 1,215 us with the line at 8, 1,056 at 16 and at 32.
-static const int AUT_STEP_WIDE_FROM = 32;
+// The builds of mask_automaton_kernel, by the byte step they hold.  Charts whose sets are all of up to AUT_NARROW_SET_MAX items run the narrow one, of up to
+// AUT_LANES_SET_MAX the one for a dozen items (a set that outgrows 64 items there goes to the fallback pass; chart addresses known to be LDS and no hash table:
+// 64 rows of the expression grammar without pruning, 8 steps of a decode loop, 988 us against 1,056 in the build that follows), others the one that
+// holds the wide step as well, to which source sets of more than AUT_STEP_WIDE_FROM items go at once (the line at 16 measured the same).
+static const int AUT_STEP_NARROW = 0, AUT_STEP_LANES = 1, AUT_STEP_WIDE = 2;
+static const int AUT_NARROW_SET_MAX = 8, AUT_LANES_SET_MAX = 16, AUT_STEP_WIDE_FROM = 32;
 static const int AUT_BASE_SETS_MAX = 1023; // the largest limits the host asks for
 static const int AUT_BASE_ITEMS_MAX = 4096;
 static const int TABLE_LDS_BUDGET = 56 * 1024;
@@ -27,7 +29,7 @@ static const int AUT_SUB_WORDS = 512;      // words of the rank-ordered bitmap (
 static const int AUT_PART_WORDS = 128;     // ... the fewest a block of a row is made for ...
 static const int AUT_GROUP_WORDS = 4;      // ... taken from the row in groups of this many neighbouring words (two batches of 64 ranks), dealt to the blocks round robin
 static const int AUT_ENT_LDS = 64;         // token-mask-cache rows of the row's current set kept in LDS (more are read from global memory)
-static_assert(AUT_NARROW_SET_MAX <= AUT_ENT_LDS, "the kernel build for small sets keeps all cache-row numbers of a row in LDS");
+static_assert(AUT_LANES_SET_MAX <= AUT_ENT_LDS, "the kernel builds for small sets keep all cache-row numbers of a row in LDS");
 static const int AUT_TABLE_LOADS = (TABLE_LDS_BUDGET + AUT_BLOCK * 16 - 1) / (AUT_BLOCK * 16);   // 16-byte pieces of the staged tables per thread
 static const int AUT_HELP_QUEUE = 512;     // transitions one block can leave for free wavefronts in the course of a launch
 static const int AUT_STATES_DEFAULT = 64;  // automaton states a block can hold (more when LDS allows and the grammar is small)
@@ -225,7 +227,7 @@ struct MaskArgs {
     int32_t aut_parts;         // blocks per row (grid.x)
     int32_t aut_base_sets;     // a row's chart is staged into LDS when it has at most this many sets ...
     int32_t aut_base_items;    // ... and items (both at least BASE_SETS_LDS / BASE_ITEMS_LDS)
-    int32_t aut_wide;          // 1: some set of some row's chart has more than AUT_NARROW_SET_MAX items (the kernel build with the wide byte step)
+    int32_t aut_step;          // the kernel build (AUT_STEP_*)
 };
 
 int choose_table_mode(const DeviceTables &t);

@@ -51,7 +51,7 @@ struct AutSets {           // resolves origin references
 // The transition of state s on class cl: take the byte step, then find the state that holds the
 // resulting set (sets are interned by content: the same items in the same order are the same
 // state) or make a new one.  Returns a state id or AT_DEAD / AT_SINK / AT_FAIL.
-template <bool WIDE, class BaseT>
+template <int STEP, class BaseT>
 __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, const Aut &A, uint32_t *sc_w, uint32_t *sc_o, uint32_t *sc_h, uint32_t sc_cap,
                                                    uint32_t s, uint32_t byte, uint32_t cl, uint32_t lane) {
     const AutSets<BaseT> S{B, A};
@@ -60,8 +60,10 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
     uint64_t src_p;
     uint32_t src_n;
     S.view(cur, src_p, src_n);
-    int st = WIDE && src_n > (uint32_t)AUT_STEP_WIDE_FROM ? AUT_WIDE : aut_step_narrow<WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);   // a wide source set rarely leaves a narrow one
-    if (st == AUT_WIDE) st = WIDE ? aut_step_wide(T, S, sc_w, sc_o, sc_h, sc_cap, cur, byte, cl, lane, nnew, kept) : (int)AUT_OVER;
+    int st = AUT_WIDE;
+    if (STEP == AUT_STEP_NARROW) st = aut_step_narrow<false>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);
+    else if (STEP == AUT_STEP_LANES || src_n <= (uint32_t)AUT_STEP_WIDE_FROM) st = aut_step_lanes<STEP == AUT_STEP_WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);   // a wide source set rarely leaves a narrow one
+    if (st == AUT_WIDE) st = STEP == AUT_STEP_WIDE ? aut_step_wide(T, S, sc_w, sc_o, sc_h, sc_cap, cur, byte, cl, lane, nnew, kept) : (int)AUT_OVER;
     if (st != AUT_OK) return AT_FAIL;
     if (nnew == 0) return AT_DEAD;
     if (kept == 0) return AT_SINK;
@@ -95,7 +97,7 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
     if (id >= A.states_cap || at + kept > A.arena_cap) return AT_FAIL;
     for (uint32_t i0 = 0; i0 < kept; i0 += 64)
         if (i0 + lane < kept) A.arena[at + i0 + lane] = make_uint2(sc_w[i0 + lane], sc_o[i0 + lane]);
-    aut_mark_dead<WIDE>(T, A.ncls, A.rep, [&](uint32_t i) { return sc_w[i]; }, kept, lane, [&](uint32_t c) { A.trans[id * A.ncls + c] = AT_DEAD; });
+    aut_mark_dead<STEP != AUT_STEP_NARROW>(T, A.ncls, A.rep, [&](uint32_t i) { return sc_w[i]; }, kept, lane, [&](uint32_t c) { A.trans[id * A.ncls + c] = AT_DEAD; });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // items before the hash, the hash before the header that makes the state visible
     if (lane == 0) A.hash[id] = h;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -104,12 +106,12 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
 }
 
 // Compute the transition of state s on class cl (the caller owns it: its entry is AT_BUSY) and publish it.
-template <bool WIDE, class BaseT>
+template <int STEP, class BaseT>
 __device__ __forceinline__ void aut_resolve(const TV &T, const BaseT &B, const Aut &A, uint32_t *sc_w, uint32_t *sc_o, uint32_t *sc_h, uint32_t sc_cap,
                                             uint32_t s, uint32_t cl, uint32_t lane) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // the states this step reads were published by other wavefronts
     __builtin_amdgcn_s_setprio(3);   // everybody waits for this wavefront: it issues ahead of those that poll (8 steps of 64 rows: 1,395 -> 1,305 us)
-    const uint32_t r = aut_transition<WIDE>(T, B, A, sc_w, sc_o, sc_h, sc_cap, s, A.rep[cl], cl, lane);
+    const uint32_t r = aut_transition<STEP>(T, B, A, sc_w, sc_o, sc_h, sc_cap, s, A.rep[cl], cl, lane);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the new state before the transition that leads to it
     if (lane == 0) lds_store(&A.trans[s * A.ncls + cl], r);
     __builtin_amdgcn_s_setprio(0);
@@ -149,11 +151,10 @@ __host__ __device__ inline uint32_t aut_round16(uint32_t x) { return (x + 15u) &
 //   What bounds it: the chain of byte steps that the strings of a block need one after the other (six to twelve, 3 to 10 us each),
 // not bandwidth and not the strings (a wavefront walks for 20 of 110 us).  So a pass takes a word per thread -- with 128 words a block of 64 rows
 // went through its chains in five passes, one behind the other --, and a wavefront that computes a step issues first.
-// MODE: which grammar tables are staged in LDS (0 all, 1 the small ones, 2 none).  WIDE: the build that
-// holds the wide variant of the byte step and its hash table; the build without it is for charts whose
-// sets are all small (the host knows: it packs them), where a set of more than 64 items fails over to the
-// fallback pass.  Keeping the wide variant out of that build keeps the narrow path's registers and code small.
-template <int MODE, bool WIDE>
+// MODE: which grammar tables are staged in LDS (0 all, 1 the small ones, 2 none).  STEP: the byte step that the build holds
+// (AUT_STEP_*; the host knows how wide the charts' sets are: it packs them).  In a build without the wide variant and its hash table a set of
+// more than 64 items fails over to the fallback pass; keeping the wide variant out keeps registers and code small.
+template <int MODE, int STEP>
 __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     const DeviceTables &D = a.tab;
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     uint32_t *cslice = reinterpret_cast<uint32_t *>(smem + off); off += AUT_SUB_WORDS * 4;
     uint8_t *pairs = smem + off; off += AUT_SUB_WORDS / 2;   // numbers of the word pairs that hold undecided strings
     A.arena = reinterpret_cast<uint2 *>(smem + off); off += aut_round16(A.arena_cap * 8);
-    uint32_t *sc_w = reinterpret_cast<uint32_t *>(smem + off) + (size_t)wave * (2 * sc_cap + (WIDE ? aut_hash_places(sc_cap) : 0u));   // the hash table belongs to the wide byte step
+    uint32_t *sc_w = reinterpret_cast<uint32_t *>(smem + off) + (size_t)wave * (2 * sc_cap + (STEP == AUT_STEP_WIDE ? aut_hash_places(sc_cap) : 0u));   // the hash table belongs to the wide byte step
     uint32_t *sc_o = sc_w + sc_cap, *sc_h = sc_o + sc_cap;
     // the row's chart: its LDS copy when it is small, else global memory (generic pointers either way).  When every
     // row has the same room in the upload (strides), the pieces are requested before the row's header is known.
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     const uint32_t *g_ent = a.entries + rc.ent_base;
     const bool base_fits = rc.n_sets <= base_sets_cap && rc.n_items <= base_items_cap;
     const bool ent_fits = rc.n_ent <= AUT_ENT_LDS;
-    if (!WIDE && !(base_fits && ent_fits)) {                               // never launched like this; if it were, the call must fail loudly
+    if (STEP != AUT_STEP_WIDE && !(base_fits && ent_fits)) {                               // never launched like this; if it were, the call must fail loudly
         if (tid == 0) atomicAdd(&a.counters[2], 1u);
         return;
     }
@@ -232,9 +233,9 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     for (uint32_t k = tid; k < A.states_cap; k += AUT_BLOCK) A.hdr[k] = make_uint2(0, 0xFFFFFFFFu);
     for (uint32_t k = tid; k < (uint32_t)AUT_HELP_QUEUE; k += AUT_BLOCK) A.hq[k] = 0;
     if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; A.ctl[7] = 0; A.ctl[8] = 0; }
-    const uint32_t *b_ent = (!WIDE || ent_fits) ? l_ent : g_ent;   // without the wide step: sets of at most AUT_NARROW_SET_MAX items, so at most that many cache rows
-    const uint32_t *b_so = (!WIDE || base_fits) ? l_so : g_so;   // the build without the wide step is launched only when every chart fits:
-    const uint2 *b_it = (!WIDE || base_fits) ? l_it : g_it;      // its chart pointers are LDS addresses at compile time
+    const uint32_t *b_ent = (STEP != AUT_STEP_WIDE || ent_fits) ? l_ent : g_ent;   // without the wide step: sets of at most AUT_LANES_SET_MAX items, so at most that many cache rows
+    const uint32_t *b_so = (STEP != AUT_STEP_WIDE || base_fits) ? l_so : g_so;   // the build without the wide step is launched only when every chart fits:
+    const uint2 *b_it = (STEP != AUT_STEP_WIDE || base_fits) ? l_it : g_it;      // its chart pointers are LDS addresses at compile time
     uint32_t steps = 0;
     const uint32_t cr = (uint32_t)D.chunk_ranks;
     // The words of the row's bitmap are dealt to the blocks in groups of AUT_GROUP_WORDS, round robin:
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
         }
         const BaseG B{b_so, b_it, rc.n_sets, b_so[rc.n_sets - 1], rc.n_items};
         if (j0 == 0 && wave == AUT_WAVES - 1)                // meanwhile the last wavefront settles the dead transitions of the row's current set
-            aut_mark_dead<WIDE>(T, A.ncls, A.rep, [&](uint32_t i) { return B.it[B.last_lo + i].x; }, B.last_hi - B.last_lo, lane, [&](uint32_t c) { A.trans[c] = AT_DEAD; });
+            aut_mark_dead<STEP != AUT_STEP_NARROW>(T, A.ncls, A.rep, [&](uint32_t i) { return B.it[B.last_lo + i].x; }, B.last_hi - B.last_lo, lane, [&](uint32_t c) { A.trans[c] = AT_DEAD; });
         __syncthreads();
         const uint32_t n_pairs = A.ctl[3];
         // ---- one lane per string through the automaton, 64 neighbouring ranks at a time.  A wavefront that finds
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
                     have = q == AUT_HQ_GOT;
                 }
                 if (have) {
-                    aut_resolve<WIDE>(T, B, A, sc_w, sc_o, sc_h, sc_cap, rs, rc, lane);
+                    aut_resolve<STEP>(T, B, A, sc_w, sc_o, sc_h, sc_cap, rs, rc, lane);
                     steps++;
                     if (!batch) spins = 0;
                 } else if (!progress && q == AUT_HQ_EMPTY) { // everything this wavefront waits for is being computed by others
@@ -398,8 +399,9 @@ hipError_t prepare_automaton_kernels() {
     const int max_lds = 160 * 1024;
     hipError_t e;
 #define SET_ATTR(k) if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds)) != hipSuccess) return e
-    SET_ATTR((mask_automaton_kernel<0, false>)); SET_ATTR((mask_automaton_kernel<1, false>)); SET_ATTR((mask_automaton_kernel<2, false>));
-    SET_ATTR((mask_automaton_kernel<0, true>)); SET_ATTR((mask_automaton_kernel<1, true>)); SET_ATTR((mask_automaton_kernel<2, true>));
+#define SET_ATTRS(step) SET_ATTR((mask_automaton_kernel<0, step>)); SET_ATTR((mask_automaton_kernel<1, step>)); SET_ATTR((mask_automaton_kernel<2, step>))
+    SET_ATTRS(AUT_STEP_NARROW); SET_ATTRS(AUT_STEP_LANES); SET_ATTRS(AUT_STEP_WIDE);
+#undef SET_ATTRS
 #undef SET_ATTR
     return hipSuccess;
 }
@@ -410,13 +412,13 @@ uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int ar
            AUT_WAVES * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
 }
 static void (*automaton_kernel(const MaskArgs &a))(MaskArgs) {
-    // two builds of the kernel: without the wide variant of the byte step (its code costs the narrow path ~10 %
-    // in registers and instruction fetch) for charts whose sets are all small, and with it
-    if (a.aut_wide) return a.mode == 0 ? mask_automaton_kernel<0, true> : a.mode == 1 ? mask_automaton_kernel<1, true> : mask_automaton_kernel<2, true>;
-    return a.mode == 0 ? mask_automaton_kernel<0, false> : a.mode == 1 ? mask_automaton_kernel<1, false> : mask_automaton_kernel<2, false>;
+    // builds of the kernel by the byte step they hold: the wide variant's code costs the others ~10 % in registers and instruction fetch
+#define ZF_BUILD(step) (a.mode == 0 ? mask_automaton_kernel<0, step> : a.mode == 1 ? mask_automaton_kernel<1, step> : mask_automaton_kernel<2, step>)
+    return a.aut_step == AUT_STEP_WIDE ? ZF_BUILD(AUT_STEP_WIDE) : a.aut_step == AUT_STEP_LANES ? ZF_BUILD(AUT_STEP_LANES) : ZF_BUILD(AUT_STEP_NARROW);
+#undef ZF_BUILD
 }
 static uint32_t automaton_lds_of(const MaskArgs &a) {
-    return automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_wide != 0);
+    return automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_step == AUT_STEP_WIDE);
 }
 int automaton_blocks_per_cu(const MaskArgs &a) {
     static thread_local struct { const void *kernel; uint32_t lds; int blocks; } known = {nullptr, 0, 0};   // asked of the runtime once per size

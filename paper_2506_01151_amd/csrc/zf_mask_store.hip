@@ -156,9 +156,9 @@ __device__ __forceinline__ uint32_t store_transition(const TV &T, const StoreVie
     uint32_t src_n;
     S.view(s, src_p, src_n);
     const uint32_t byte = rep[cl];
-    // the narrow step takes sets of up to 64 items; where the charts hold wide sets (an ambiguous grammar) a large source set rarely
-    // leaves a narrow one, and the narrow step's Complete would be wasted
-    const bool wide_first = src_n > 64u || (stg.wide_sets && src_n > (uint32_t)AUT_STEP_WIDE_FROM);
+    // the narrow step takes sets of up to 64 items; where the charts hold wide sets (an ambiguous grammar) a source set of more
+    // than a few items rarely leaves a narrow one, and the narrow step's one-candidate-at-a-time Complete would be wasted
+    const bool wide_first = src_n > 64u || (stg.wide_sets && src_n > (uint32_t)AUT_NARROW_SET_MAX);
     int st = wide_first ? (int)AUT_WIDE : aut_step_narrow<true>(T, S, sc.w, sc.o, sc.cap, s, byte, cl, lane, nnew, kept);
     if (st == AUT_WIDE) st = aut_step_wide(T, S, sc.w, sc.o, sc.h, sc.cap, s, byte, cl, lane, nnew, kept);
     if (st != AUT_OK) return AT_FAIL;
