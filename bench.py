@@ -33,7 +33,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # instruction issue peak of the chip: 256 compute units x 4 SIMDs x one wavefront instruction per cycle x 2.4 GHz
 ISSUE_PEAK_GINST = 256 * 4 * 2.4
-KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_store_kernel"}
+KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_look_kernel / mask_store_kernel"}
 
 # HBM traffic of one launch of the default mask kernel on the default workload, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs
 # scaled by a plain copy of known size (profiles/mask_store_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same runs.  The
