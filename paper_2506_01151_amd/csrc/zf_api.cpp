@@ -1620,10 +1620,10 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const uint32_t lds = store_lds_bytes(d->tab, d->mode, scratch);
     if (lds > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
     int logit_bytes = 0;                                  // of a logit the mask kernel masks itself
-    if (g_apply.out) {
+    if (g_apply.out && !look) {
         const size_t esz = g_apply.dtype == 0 ? 4 : 2;
         const bool whole = (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
-        // One kernel for both as long as the logits are few enough that masking them hides behind the walk of the vocabulary;
+        // mask_store_kernel does both as long as the logits are few enough that masking them hides behind the walk of the vocabulary;
         // beyond, a launch of its own masks them at the memory's rate with the work spread evenly over the chip.
         if (whole && 2ull * (uint64_t)batch * (uint64_t)e->V * esz <= STORE_FUSE_BYTES) {
             a.logits = g_apply.logits; a.out = g_apply.out; a.stride = g_apply.stride; a.dtype = (uint8_t)(g_apply.dtype + 1);
@@ -1662,7 +1662,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         }
         const uint8_t *up = noalloc ? d->scratch : (const uint8_t *)d->d_chart;
         k.trans = d->store.trans; k.cache = d->tab.ci_tok; k.tok16 = d->tab.tok16; k.out_mask = d_mask; k.pool = d->d_pool;
-        k.logits = a.logits; k.out = a.out; k.stride = a.stride; k.konst = d->d_konst;
+        k.konst = d->d_konst;
         if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); }
         else if (members_apart) k.members = (const uint16_t *)(h + off_mem);
         k.V = (uint32_t)e->V; k.W = (uint32_t)d->tab.W; k.ncls = (uint32_t)d->tab.n_cls; k.n_groups = (uint32_t)ng;
@@ -1775,7 +1775,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     d->closing_kernel = false;
     if (look) {
         k.tickets = a.tickets; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
-        HIP_TRY(launch_mask_look(k, c.look, a.n_blocks, a.dtype, stream));
+        HIP_TRY(launch_mask_look(k, c.look, a.n_blocks, stream));
     } else {
         HIP_TRY(launch_mask_store(a, c.in, lds, stream));
         for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;

@@ -61,7 +61,7 @@ static const int STORE_LC_BITS = ZF_STORE_LC_BITS;       // log2 of the entries 
 #define ZF_STORE_BLOCKS_PER_CU 3
 #endif
 static const int STORE_BLOCKS_PER_CU = ZF_STORE_BLOCKS_PER_CU;   // blocks per compute unit the grid is made of at most (fewer when a compute unit holds fewer at once)
-static const uint64_t STORE_FUSE_BYTES = 16u << 20;   // logits read and written by zf_compute_mask_apply_async up to which the mask kernel masks them itself
+static const uint64_t STORE_FUSE_BYTES = 16u << 20;   // logits read and written by zf_compute_mask_apply_async up to which mask_store_kernel masks them itself
 static const int STORE_PENDING_MAX = 4096;      // beyond this many bytes since its state was last known a row comes in through its chart again
 // Flags of a group of rows (StoreGroup::meta, StoreRow::flags):
 static const uint32_t STORE_ROW_CACHE = 1u;     // the token-mask cache rows of the group's current set are listed
@@ -161,9 +161,6 @@ struct LookArgs {
     const uint2 *cache;
     const Str16 *tok16;
     uint32_t *out_mask, *pool;
-    const void *logits;
-    void *out;
-    int64_t stride;
     const StoreConst *konst;
     const LookGroup *groups;
     const uint32_t *block_of;
@@ -247,7 +244,7 @@ uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch);
 hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s);
 int look_blocks_per_cu();
-hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, int apply, hipStream_t s);
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, hipStream_t s);
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s);
 // The store, cleared, whose headers, items and table rows of the states below n_states were copied in from the host: their places in the
 // hash table, and how far the store is filled.

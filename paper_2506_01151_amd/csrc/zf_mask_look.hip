@@ -11,7 +11,8 @@
 // wavefront issues at 4 to 5 cycles apiece.  mask_store_kernel, which this one was split from, carries both halves: 139 scalar registers
 // spilled, a stack for the byte step (0.6 us per launch), 2.4 us from the group's record to its last request, 54 instructions
 // per byte of a walk.  Here the record is a third shorter, the cache rows are read by uniform addresses, the table row is on its
-// way before anything else, undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
+// way before anything else, the logits are left to a launch of their own (their requests and stores lengthened every wavefront: 16 x
+// 128,256 bf16 260 us per 16 steps with them in here, 237 without, and 27.4 for 29.6 us per step synchronised), undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
 // for, and a byte of the walk takes about 20 instructions: a lane that is done leaves the loop.
 #include "zf_kernel_common.h"
 #include "zf_aut_step.h"
@@ -48,14 +49,8 @@ __device__ __forceinline__ void hand_over_look(const LookArgs &a, uint32_t faile
     __hip_atomic_store(&a.status[STORE_ST_DONE], ((unsigned long long)a.seq << 32) | ((uint32_t)(sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// A piece of 16 bytes of a row of logits, wherever the row begins.
-template <int APPLY> struct LookPiece { typedef u32x4 __attribute__((aligned(4))) type; };
-template <> struct LookPiece<2> { typedef u32x4 __attribute__((aligned(2))) type; };
-
 // Grid and groups as in mask_store_kernel: the blocks of all groups one after the other, a group = the rows of the call that
 // stand in the same state, whose mask is worked out once, in token order.  A wavefront takes every n_units-th segment of `sw` mask words.
-// APPLY: 0 = masks only, 1 / 2 = the rows' fp32 / bf16 logits are masked as well (Section 3.3).
-template <int APPLY>
 __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_kernel(LookArgs a, LookInline in) {
     __shared__ unsigned long long lc[LOOK_LC];
     __shared__ uint32_t lists[STORE_WAVES][LOOK_LIST];
@@ -96,7 +91,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
     if (unit < n_seg) {
     uint32_t *const list = lists[wave], *const vbuf = vbufs[wave];
     const bool walks = !pooled && start < AT_FAIL;            // AT_SINK: the sentence is finished, no token can follow
-    // ---- requests, in the order their answers are needed: the state's table row, the segment's cache words, members, logits ----
+    // ---- requests, in the order their answers are needed: the state's table row, the segment's cache words, members ----
     uint32_t t_root = AT_NONE;
     const uint32_t *const row0 = a.trans + (size_t)start * ncls;
     if (walks && lane < ncls) t_root = row0[lane];
@@ -146,35 +141,6 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
 #pragma unroll
         for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead && lane < ncls) t_ahead[k] = a.trans[(size_t)ahead[k] * ncls + lane];
     }
-    // ---- logits: the segment's 16-byte pieces of all members in hand as one run, the first PRE of every lane requested ahead ----
-    typedef typename LookPiece<APPLY>::type piece_t;
-    constexpr uint32_t tp = APPLY == 2 ? 8u : 4u, esz = APPLY == 2 ? 2u : 4u;   // tokens per 16-byte piece, bytes per logit
-    auto tokens_of = [&](uint32_t g) -> uint32_t {
-        const uint32_t tok0 = g * sw * 32u;
-        return g < n_seg && tok0 < V ? (sw * 32u < V - tok0 ? sw * 32u : V - tok0) : 0u;
-    };
-    // number i of a run of `per` things per member: which member, and which of its things.  i < 2^15 and per <= 512, so the
-    // half added keeps the product at least 1 / 1024 away from the next whole number, far more than single precision loses
-    auto split = [&](uint32_t i, uint32_t per, float inv, uint32_t &k) -> uint32_t { k = (uint32_t)(((float)i + 0.5f) * inv); return i - k * per; };
-    auto byte_of = [&](uint32_t k, uint32_t g, uint32_t t) -> size_t {   // of token t of segment g in the k-th member's row
-        return ((size_t)(uint32_t)__shfl((int)members, (int)(k & 63u)) * (size_t)a.stride + g * sw * 32u + t) * esz;
-    };
-    constexpr int PRE = 2;
-    auto logits_ahead = [&](uint32_t g, u32x4 (&pre)[PRE]) __attribute__((always_inline)) {
-        const uint32_t per = tokens_of(g) / tp, total = per * (n_members < 64u ? n_members : 64u);
-        const float inv = __builtin_amdgcn_rcpf((float)(per ? per : 1u));
-#pragma unroll
-        for (int u = 0; u < PRE; u++) {
-            const uint32_t i = (uint32_t)u * 64u + lane;
-            uint32_t k;
-            const uint32_t p = split(i < total ? i : 0u, per, inv, k);
-            const size_t at = byte_of(k, g, p * tp);
-            pre[u] = u32x4{0, 0, 0, 0};
-            if (i < total) pre[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(reinterpret_cast<const uint8_t *>(a.logits) + at));
-        }
-    };
-    u32x4 l_pre[PRE];
-    if (APPLY) logits_ahead(unit, l_pre);
     uint32_t failed = 0;
     bool first = true;
     for (uint32_t g = unit; g < n_seg; g += n_units) {
@@ -182,11 +148,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
         uint32_t v = x[0].x, c = x[0].y;
 #pragma unroll
         for (int j = 1; j < LOOK_RAW; j++) { v |= x[j].x; c |= x[j].y; }
-        u32x4 l_nxt[PRE];
-        if (g + n_units < n_seg) {                           // the next segment's words and first logits travel while this one's tokens are checked
-            request(g + n_units, x);
-            if (APPLY) logits_ahead(g + n_units, l_nxt);
-        }
+        if (g + n_units < n_seg) request(g + n_units, x);    // the next segment's words travel while this one's tokens are checked
         uint32_t want = c & ~v;
         {
             const uint32_t t0 = w * 32u;
@@ -290,72 +252,9 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
                     if (k < n && word < sw && w2 < W) { if (a.complete) __hip_atomic_store(dst, v2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); else *dst = v2; }
                 }
             }
-            if (APPLY) {
-                // Logit masking (Section 3.3) of the segment's tokens, right here: 16-byte pieces, consecutive lanes on consecutive
-                // pieces, the mask word from the lane that holds it.  Allowed logits are copied bit for bit, the others become -inf.
-                const uint32_t n_tok = tokens_of(g), pieces = n_tok / tp, tail = n_tok % tp;
-                auto masked = [&](u32x4 y, uint32_t mb) -> u32x4 {
-                    if (APPLY == 2) {
-#pragma unroll
-                        for (int j = 0; j < 4; j++) {
-                            uint32_t e = y[j];
-                            if (!((mb >> (2 * j)) & 1u)) e = (e & 0xFFFF0000u) | 0xFF80u;
-                            if (!((mb >> (2 * j + 1)) & 1u)) e = (e & 0x0000FFFFu) | 0xFF800000u;
-                            y[j] = e;
-                        }
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; j++) if (!((mb >> j) & 1u)) y[j] = 0xFF800000u;
-                    }
-                    return y;
-                };
-                auto bits_at = [&](uint32_t tk) -> uint32_t { return (uint32_t)__shfl((int)v, (int)((tk >> 5) & 63u)) >> (tk & 31u); };   // all lanes call it together
-                const uint32_t run = pieces * n;
-                const float inv = __builtin_amdgcn_rcpf((float)(pieces ? pieces : 1u));
-                const uint8_t *src = reinterpret_cast<const uint8_t *>(a.logits);
-                uint8_t *dst = reinterpret_cast<uint8_t *>(a.out);
-                auto where = [&](uint32_t i, uint32_t &p) -> size_t { uint32_t k; p = split(i < run ? i : 0u, pieces, inv, k); return byte_of(k, g, p * tp); };
-                auto put = [&](uint32_t i, u32x4 y) { uint32_t p; const size_t at = where(i, p); const uint32_t mb = bits_at(p * tp); if (i < run) __builtin_nontemporal_store(masked(y, mb), reinterpret_cast<piece_t *>(dst + at)); };
-                uint32_t i0 = 0;
-                if (m0 == 0) {                               // what was requested ahead
-#pragma unroll
-                    for (int u = 0; u < PRE; u++) if ((uint32_t)u * 64u < run) put((uint32_t)u * 64u + lane, l_pre[u]);
-                    i0 = PRE * 64u;
-                }
-                for (; i0 < run; i0 += 256) {                // the others: four pieces per lane in flight
-                    u32x4 y[4];
-#pragma unroll
-                    for (int u = 0; u < 4; u++) {
-                        const uint32_t i = i0 + (uint32_t)u * 64u + lane;
-                        uint32_t p;
-                        const size_t at = where(i, p);
-                        y[u] = u32x4{0, 0, 0, 0};
-                        if (i < run) y[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(src + at));
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; u++) if (i0 + (uint32_t)u * 64u < run) put(i0 + (uint32_t)u * 64u + lane, y[u]);
-                }
-                if (tail) {                                  // the last tokens of a vocabulary that is no multiple of a piece
-                    const uint32_t tails = tail * n;
-                    const float tinv = __builtin_amdgcn_rcpf((float)tail);
-                    for (uint32_t i = 0; i < tails; i += 64) {
-                        uint32_t k;
-                        const uint32_t tk = pieces * tp + split(i + lane < tails ? i + lane : 0u, tail, tinv, k), stays = bits_at(tk) & 1u;
-                        const size_t at = byte_of(k, g, tk);
-                        if (i + lane < tails) {
-                            if (APPLY == 2) *reinterpret_cast<uint16_t *>(dst + at) = stays ? *reinterpret_cast<const uint16_t *>(src + at) : (uint16_t)0xFF80u;
-                            else *reinterpret_cast<uint32_t *>(dst + at) = stays ? *reinterpret_cast<const uint32_t *>(src + at) : 0xFF800000u;
-                        }
-                    }
-                }
-            }
         }
         if (keep && w < W) a.pool[(size_t)(r[4] & 0xFFFFu) * W + w] = v;
         if (n_members > 64u) members = members_from(0);
-        if (APPLY) {
-#pragma unroll
-            for (int u = 0; u < PRE; u++) l_pre[u] = l_nxt[u];
-        }
     }
     if (lane == 0 && failed) atomicAdd(&blk_failed, failed);
     if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
@@ -366,24 +265,18 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
 
 }  // namespace
 
-static void (*look_kernel(int apply))(LookArgs, LookInline) { return apply == 0 ? mask_look_kernel<0> : apply == 1 ? mask_look_kernel<1> : mask_look_kernel<2>; }
-
 // Blocks of the kernel one compute unit holds at once.
 int look_blocks_per_cu() {
-    static const int least = [] {
-        int n_least = LOOK_BLOCKS_PER_CU;
-        for (int p = 0; p < 3; p++) {
-            int n = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(look_kernel(p)), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
-            n_least = n < n_least ? n : n_least;
-        }
-        return n_least;
+    static const int blocks = [] {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(mask_look_kernel), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+        return n < LOOK_BLOCKS_PER_CU ? n : LOOK_BLOCKS_PER_CU;
     }();
-    return least;
+    return blocks;
 }
 
-hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, int apply, hipStream_t s) {
-    hipLaunchKernelGGL(look_kernel(apply), dim3(n_blocks), dim3(STORE_BLOCK), 0, s, a, in);
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, hipStream_t s) {
+    hipLaunchKernelGGL(mask_look_kernel, dim3(n_blocks), dim3(STORE_BLOCK), 0, s, a, in);
     return hipGetLastError();
 }
 
