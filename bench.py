@@ -197,7 +197,7 @@ class Runner:
             t0 = time.perf_counter()
             self.states.advance(ids)                    # every row by its token (a negative id starts the row over)
             t1 = time.perf_counter()
-            if fused:                                   # compute_mask and apply_mask of the step in one call (one kernel on the default path)
+            if fused:                                   # compute_mask and apply_mask of the step enqueued together by one call
                 eng.compute_mask_apply_async(self.states, p_mask, p_logits[i % len(p_logits)], p_out, dt, row_stride, h_stream)
             else:
                 eng.compute_mask_async(self.states, p_mask, h_stream)
