@@ -6,6 +6,7 @@
 #include <Python.h>
 #include <climits>
 #include <cstring>
+#include <new>
 #include <vector>
 #include "zf_py.h"
 #include "../../include/zapformat.h"
@@ -111,14 +112,17 @@ void batch_dealloc(PyObject *o) {
 PyObject *batch_bind(PyObject *o, PyObject *list) {    // _bind(states): their handles
     BatchBase *b = (BatchBase *)o;
     if (!PyList_Check(list)) { PyErr_SetString(PyExc_TypeError, "a list of states is wanted"); return nullptr; }
-    if (!b->rows) { b->rows = new std::vector<zf_state *>(); b->ids = new std::vector<int32_t>(); }
-    b->rows->clear();
-    for (Py_ssize_t k = 0; k < PyList_GET_SIZE(list); k++) {
-        PyObject *s = PyList_GET_ITEM(list, k);
-        if (!PyObject_TypeCheck(s, StateType)) { PyErr_SetString(PyExc_TypeError, "a list of states is wanted"); return nullptr; }
-        b->rows->push_back(((StateBase *)s)->h);
-    }
-    b->ids->resize(b->rows->size());
+    try {
+        if (!b->rows) b->rows = new std::vector<zf_state *>();
+        if (!b->ids) b->ids = new std::vector<int32_t>();
+        b->rows->clear();
+        for (Py_ssize_t k = 0; k < PyList_GET_SIZE(list); k++) {
+            PyObject *s = PyList_GET_ITEM(list, k);
+            if (!PyObject_TypeCheck(s, StateType)) { PyErr_SetString(PyExc_TypeError, "a list of states is wanted"); return nullptr; }
+            b->rows->push_back(((StateBase *)s)->h);
+        }
+        b->ids->resize(b->rows->size());
+    } catch (const std::bad_alloc &) { return PyErr_NoMemory(); }
     Py_RETURN_NONE;
 }
 PyObject *batch_advance(PyObject *o, PyObject *const *args, Py_ssize_t n, PyObject *kw) {
@@ -192,8 +196,8 @@ PyObject *mask_call(const char *name, MaskCall call, PyObject *const *args, Py_s
     EngineBase *e;
     Rows rows;
     zfpy::TensorInfo m;
-    if (!T || n != 3 || kw || !engine_of(args[0], &e) || !rows.take(args[1]) || !mask_of(args[2], e, rows.n, &m)) return twin(name, args, n, kw);
-    void *s = T->stream(e->device);
+    void *s;
+    if (!T || n != 3 || kw || !engine_of(args[0], &e) || !rows.take(args[1]) || !mask_of(args[2], e, rows.n, &m) || !T->stream(e->device, &s)) return twin(name, args, n, kw);
     const int rc = unlocked([&] { return call(e->h, rows.p, (int32_t)rows.n, (uint32_t *)m.data, s); });
     return itself(args[2], rc);
 }
@@ -205,11 +209,11 @@ PyObject *compute_mask_apply_async(PyObject *, PyObject *const *args, Py_ssize_t
     Rows rows;
     zfpy::TensorInfo m, x, y;
     PyObject *out;
+    void *s;
     if (!T || !only_out(n, kw, args, 5, &out) || !engine_of(args[0], &e) || !rows.take(args[1]) || !mask_of(args[2], e, rows.n, &m) ||
-        !logits_of(args[3], e, &x) || x.size[0] != rows.n || (out && (!T->look(out, &y) || y.device < 0 || !same_shape(x, y))))
+        !logits_of(args[3], e, &x) || x.size[0] != rows.n || (out && (!T->look(out, &y) || y.device < 0 || !same_shape(x, y))) || !T->stream(e->device, &s))
         return twin("compute_mask_apply_async", args, n, kw);
     if (!out) { out = args[3]; y = x; }
-    void *s = T->stream(e->device);
     const int rc = unlocked([&] { return L.compute_mask_apply_async(e->h, rows.p, (int32_t)rows.n, (uint32_t *)m.data, x.data, y.data, x.dtype, x.stride[0], s); });
     return itself(out, rc);
 }
@@ -217,18 +221,18 @@ PyObject *apply_mask(PyObject *, PyObject *const *args, Py_ssize_t n, PyObject *
     EngineBase *e;
     zfpy::TensorInfo m, x, y;
     PyObject *out;
+    void *s;
     if (!T || !only_out(n, kw, args, 4, &out) || !engine_of(args[0], &e) || !logits_of(args[1], e, &x) || x.size[0] <= 0 || x.size[0] > INT32_MAX ||
-        !T->look(args[2], &m) || m.device < 0 || (out && (!T->look(out, &y) || y.device < 0 || !same_shape(x, y))))
+        !T->look(args[2], &m) || m.device < 0 || (out && (!T->look(out, &y) || y.device < 0 || !same_shape(x, y))) || !T->stream(e->device, &s))
         return twin("apply_mask", args, n, kw);
     if (!out) { out = args[1]; y = x; }
-    void *s = T->stream(e->device);
     const int rc = unlocked([&] { return L.apply_mask(e->h, x.data, y.data, x.dtype, (int32_t)x.size[0], x.stride[0], (const uint32_t *)m.data, s); });
     return itself(out, rc);
 }
 PyObject *mask_wait(PyObject *, PyObject *const *args, Py_ssize_t n, PyObject *kw) {
     EngineBase *e;
-    if (!T || n != 1 || kw || !engine_of(args[0], &e)) return twin("mask_wait", args, n, kw);
-    void *s = T->stream(e->device);
+    void *s;
+    if (!T || n != 1 || kw || !engine_of(args[0], &e) || !T->stream(e->device, &s)) return twin("mask_wait", args, n, kw);
     const int rc = unlocked([&] { return L.mask_wait(e->h, s); });
     return done(rc);
 }
@@ -258,7 +262,13 @@ PyObject *bind_torch(PyObject *, PyObject *capsule) {
     Py_RETURN_NONE;
 }
 
-#define FAST(f) (PyCFunction)(void (*)(void))(f), METH_FASTCALL | METH_KEYWORDS
+// Python calls C: no C++ exception goes that way (the vectors of handles and arguments can fail to grow).
+typedef PyObject *(*FastCall)(PyObject *, PyObject *const *, Py_ssize_t, PyObject *);
+template <FastCall F>
+PyObject *guarded(PyObject *self, PyObject *const *args, Py_ssize_t n, PyObject *kw) {
+    try { return F(self, args, n, kw); } catch (const std::bad_alloc &) { return PyErr_NoMemory(); }
+}
+#define FAST(f) (PyCFunction)(void (*)(void))guarded<f>, METH_FASTCALL | METH_KEYWORDS
 PyMethodDef state_methods[] = {
     {"advance", FAST(state_advance), "advance($self, token_id)\n--\n\nFeed a token's bytes (raises ZfError when the grammar rejects them)."},
     {"reset", state_reset, METH_NOARGS, "reset($self)\n--\n\nBack to the empty prefix."}, {nullptr, nullptr, 0, nullptr}};

@@ -12,8 +12,8 @@ struct TensorInfo {
     int32_t contiguous;
 };
 struct TensorCalls {
-    bool (*look)(void *obj, TensorInfo *out);        // false: not a plain torch.Tensor
-    void *(*stream)(int32_t device);                 // torch's current stream there
+    bool (*look)(void *obj, TensorInfo *out) noexcept;      // false: not a plain torch.Tensor, or one that cannot be looked at
+    bool (*stream)(int32_t device, void **out) noexcept;    // torch's current stream there; false: torch has none to give
 };
 static const char *const TENSOR_CALLS_NAME = "paper_2506_01151_amd._native_torch.calls";
 

@@ -987,3 +987,26 @@ def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
     got = d_mask.cpu().numpy().view(np.uint32)
     for b in range(B):
         assert np.array_equal(got[b], want[b % len(prefixes)]), b
+
+
+def test_function_transforms_raise_and_the_process_goes_on(torch_cuda, oracle_lib):
+    """The wrappers of vmap and grad pass for plain GPU tensors and refuse their address: an exception of Python's, and the next plain call is right."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    cfg = configs.CONFIGS[1]
+    g, toks = cfg.grammar(), cfg.vocab()
+    eng = zf.Engine(g, toks, device=0)
+    st = eng.new_state()
+    d_mask = torch.empty((1, eng.W), dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, [st], d_mask)
+    logits = torch.randn((3, 1, eng.V), device="cuda")
+    for f in (lambda: torch.func.vmap(lambda x: zf.apply_mask(eng, x, d_mask))(logits),
+              lambda: torch.func.vmap(lambda x: zf.compute_mask_apply_async(eng, [st], d_mask, x))(logits),
+              lambda: torch.func.grad(lambda x: zf.apply_mask(eng, x, d_mask).sum())(logits[0])):
+        with pytest.raises(Exception):
+            f()
+    off, data = wvocab.vocab_csr(toks)
+    want = oracle_lib.Oracle(g).new_state().mask(off, data)
+    out = zf.apply_mask(eng, logits[0].clone(), zf.compute_mask(eng, [st], d_mask))
+    assert out.cpu().numpy().view(np.uint32).tobytes() == oracle_apply(logits[0].cpu().numpy().view(np.uint32), want[None, :]).tobytes()

@@ -457,3 +457,46 @@ def test_automaton_twin_long_tokens_deep_nesting_many_classes(zf, oracle_lib):
         assert o.feed_bytes(p)
         s.advance_bytes(p)
         assert (s.debug_host_mask_automaton()[0] == o.mask(off2, data2, 4)).all(), p
+
+
+ODD_TENSORS = r'''
+import sys, torch
+import paper_2506_01151_amd as zf
+from workloads import configs
+cfg = configs.CONFIGS[1]
+eng = zf.Engine(cfg.grammar(), cfg.vocab(), device=-1)
+rows = [eng.new_state(), eng.new_state()]
+mask = torch.zeros((2, eng.W), dtype=torch.int32)
+plain = torch.zeros((2, eng.V))
+odd = {"nested": torch.nested.nested_tensor([torch.zeros(eng.V), torch.zeros(eng.V)]), "sparse": plain.to_sparse(), "meta": torch.empty((2, eng.V), device="meta"),
+       "no tensor": 5, "none": None}
+raised = []
+for name, x in odd.items():
+    for call in (lambda: zf.apply_mask(eng, plain, mask), lambda: zf.apply_mask(eng, x, mask), lambda: zf.apply_mask(eng, plain, x), lambda: zf.apply_mask(eng, plain, mask, out=x),
+                 lambda: zf.compute_mask(eng, rows, x), lambda: zf.compute_mask_apply_async(eng, rows, x, x), lambda: zf.compute_mask_apply_async(eng, rows, mask, plain, out=x)):
+        try:
+            call()
+        except Exception:
+            raised.append(name)
+# the wrappers of function transforms pass for plain tensors
+for name, f in (("vmap", lambda call: torch.func.vmap(call)(plain)), ("grad", lambda call: torch.func.grad(lambda y: call(y).sum())(plain[0]))):
+    try:
+        f(lambda x: zf.apply_mask(eng, x, mask))
+    except Exception:
+        raised.append(name)
+try:
+    zf.mask_wait(eng)
+except Exception:
+    raised.append("wait")
+print(len(raised), raised[-3:])
+'''
+
+
+def test_tensors_that_cannot_be_looked_at_raise_and_do_not_abort():
+    """Tensors that torch refuses to give the strides or the address of, and things that are no tensors: an exception of Python's from
+    every call that takes a tensor, as the plain functions raise it, and the process goes on (a process of its own: an abort would end it)."""
+    import subprocess
+    import sys
+    r = subprocess.run([sys.executable, "-c", ODD_TENSORS], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.split("\n")[-2] == "38 ['vmap', 'grad', 'wait']", r.stdout
