@@ -172,7 +172,10 @@ int zf_position_info(const zf_engine *e, int32_t position, int32_t *lhs, int32_t
  * set (Section 4.1: all tokens are checked at every step).  d_mask: device, [batch][W]
  * uint32, fully overwritten, padding bits zero.  The states' charts are snapshotted before
  * the call returns.  The work is enqueued on hip_stream (a hipStream_t, null = default
- * stream); the call waits for its own kernels so that ZF_ERR_OVERFLOW can be reported. */
+ * stream); the call waits for its own work so that ZF_ERR_OVERFLOW can be reported: when it returns, the mask
+ * (and whatever the engine keeps of it) is complete in device memory, to be read from the host or from any
+ * stream, and the next call on the engine may use another stream.  It does not synchronise hip_stream as such:
+ * with walk_mode 2 it polls a word that its kernel writes last, and the stream may be microseconds from idle. */
 int zf_compute_mask(zf_engine *e, zf_state *const *states /* host array */, int32_t batch,
                     uint32_t *d_mask, void *hip_stream);
 /* The same, without waiting: the kernels (the fallback pass is part of the last one) are only enqueued on
@@ -185,7 +188,7 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states /* host array */, int3
  * the block that finishes last; bounded: after two seconds the stream is synchronised instead).  It does NOT
  * wait for work the caller queued behind them (zf_apply_mask, a sampler), and the mask tensor is to be
  * consumed in stream order: queue its readers on hip_stream, or synchronise the stream before reading it
- * from the host or from another stream (zf_compute_mask, the waiting call, does synchronise).  With no call
+ * from the host or from another stream (not so after zf_compute_mask, the waiting call).  With no call
  * in flight zf_mask_wait synchronises hip_stream. */
 int zf_compute_mask_async(zf_engine *e, zf_state *const *states /* host array */, int32_t batch,
                           uint32_t *d_mask, void *hip_stream);

@@ -82,7 +82,8 @@ struct DeviceSide {
     void *d_root_items = nullptr; uint32_t n_root = 0;
     uint32_t *d_import_root = nullptr;               // [MAX_BATCH]
     volatile uint64_t *h_store_status = nullptr;     // pinned, [N_SLOTS][STORE_STATUS_WORDS]: see STORE_ST_DONE
-    unsigned long long *d_tickets = nullptr;
+    unsigned long long *d_tickets = nullptr;         // [2][STORE_TICKETS]
+    uint32_t ticket_set = 0;                         // the one the next kernel draws from
     StoreConst *d_konst = nullptr;
     uint32_t store_epoch = 1;                        // bumped whenever the store is cleared
     uint32_t store_states = 0, store_items = 0;      // as of the last call that reported back
@@ -344,10 +345,10 @@ int setup_device(zf_engine *e) {
         if ((rc = engine_alloc(d, ((size_t)G.intern_mask + 1) * 8, &G.intern)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, 64, &G.ctl)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, (size_t)MAX_BATCH * 4, &d->d_import_root)) != ZF_OK) return rc;
-        if ((rc = engine_alloc(d, STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
+        if ((rc = engine_alloc(d, 2 * STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
         HIP_TRY(hipHostMalloc((void **)&d->h_store_status, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8, hipHostMallocDefault));
         memset((void *)d->h_store_status, 0, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8);
-        HIP_TRY(hipMemset(d->d_tickets, 0, STORE_TICKETS * 8));
+        HIP_TRY(hipMemset(d->d_tickets, 0, 2 * STORE_TICKETS * 8));
         {
             const StoreConst k{d->tab, G};
             if ((rc = engine_alloc(d, sizeof k, &d->d_konst)) != ZF_OK) return rc;
@@ -1754,7 +1755,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         a.block_of = (const uint32_t *)(uploaded + off_block);
         a.members = (const uint16_t *)(uploaded + off_mem);
     } else if (batch > STORE_INLINE_ROWS) a.members = (const uint16_t *)(stage + off_mem);
-    a.tickets = d->d_tickets;
+    a.tickets = d->d_tickets + d->ticket_set * STORE_TICKETS; a.tickets_next = d->d_tickets + (d->ticket_set ^ 1u) * STORE_TICKETS;
     a.status = (unsigned long long *)d->h_store_status + slot * STORE_STATUS_WORDS;
     if (++d->call_seq == 0) d->call_seq = 1;
     a.seq = rec.seq = d->call_seq;
@@ -1774,12 +1775,13 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
     d->closing_kernel = false;
     if (look) {
-        k.tickets = a.tickets; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
+        k.tickets = a.tickets; k.tickets_next = a.tickets_next; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
         HIP_TRY(launch_mask_look(k, c.look, a.n_blocks, stream));
     } else {
         HIP_TRY(launch_mask_store(a, c.in, lds, stream));
         for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
     }
+    d->ticket_set ^= 1u;
     if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;

@@ -20,6 +20,20 @@ struct TV {
     uint32_t N, ncls, end_base;
 };
 
+// A waiting call is over when the host has its status word: the stream is not synchronised, and the next call may come on another
+// one.  What the call leaves in device memory -- mask rows, rows of the state cache, the ticket words -- therefore goes past the
+// XCD's L2 (a plain store could lie there until the kernel's end) and has arrived before the word goes out.
+__device__ __forceinline__ void put_word(uint32_t *dst, uint32_t v, bool complete) {
+    if (complete) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else *dst = v;
+}
+__device__ __forceinline__ void clear_tickets(unsigned long long *t, uint32_t lane) {   // one wavefront: a set of ticket words
+    static_assert(STORE_TICKET_GROUPS == 64, "a word per lane, and the top one");
+    __hip_atomic_store(&t[lane * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(&t[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }   // of this wavefront
+
 __device__ __forceinline__ void copy16(void *dst, const void *src, uint32_t bytes, uint32_t tid, uint32_t nthreads) {
     const uint4 *s = reinterpret_cast<const uint4 *>(src);
     uint4 *d = reinterpret_cast<uint4 *>(dst);

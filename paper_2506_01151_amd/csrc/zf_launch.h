@@ -131,7 +131,8 @@ struct StoreArgs {
     const StoreGroup *groups;          // null: in the argument block; else device memory, with ...
     const uint32_t *block_of;          // ... group | part << 16 of every block
     const uint16_t *members;           // row numbers of the groups, one group after the other; null: in the argument block
-    unsigned long long *tickets;       // device memory, STORE_TICKETS words, zero between calls (see hand_over_store)
+    unsigned long long *tickets;       // device memory, STORE_TICKETS words, zero when the kernel starts (see hand_over_store)
+    unsigned long long *tickets_next;  // the same number of words for the next kernel, which this one clears
     unsigned long long *status;        // pinned host memory: (seq << 32 | value) words, see StoreStatus
     uint32_t seq;                      // the call's number (never 0)
     uint32_t V, W, ncls, cap_states, tab_mode;
@@ -165,7 +166,7 @@ struct LookArgs {
     const LookGroup *groups;
     const uint32_t *block_of;
     const uint16_t *members;
-    unsigned long long *tickets, *status;
+    unsigned long long *tickets, *tickets_next, *status;
     uint32_t seq, V, W, ncls, n_groups, complete;
 };
 static_assert(sizeof(LookArgs) + sizeof(LookInline) <= 4096, "the kernel's argument block");

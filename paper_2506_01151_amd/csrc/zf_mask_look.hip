@@ -39,12 +39,10 @@ __device__ __forceinline__ void hand_over_look(const LookArgs &a, uint32_t faile
     unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
     unsigned long long sum = atomicAdd(&a.tickets[g * STORE_TICKET_STRIDE], mine) + mine;
     if ((sum & 0xFFFFull) != size) return;
-    __hip_atomic_store(&a.tickets[g * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n_groups > 1u) {
         mine = (sum & ~0xFFFFull) | 1ull;
         sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], mine) + mine;
         if ((sum & 0xFFFFull) != n_groups) return;
-        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(&a.status[STORE_ST_DONE], ((unsigned long long)a.seq << 32) | ((uint32_t)(sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -58,6 +56,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
     __shared__ uint32_t blk_failed;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);
     // ---- the record of the block's group: one trip to the argument block (lane l asks for that of group l), or to device memory ----
     uint32_t r[LOOK_WORDS], part, parts;
     if (a.groups) {
@@ -241,7 +240,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
             if (n < 4u || sw > 32u) {
                 for (uint32_t k = 0; k < n; k++) {
                     uint32_t *dst = a.out_mask + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)members, (int)k) * W + w;
-                    if (w < W) { if (a.complete) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); else *dst = v; }
+                    if (w < W) put_word(dst, v, a.complete);
                 }
             } else {                                         // several members per store: the lanes hold the segment 2, 4, 8 or 16 times over
                 const uint32_t lg = sw <= 4u ? 2u : sw <= 8u ? 3u : sw <= 16u ? 4u : 5u, word = lane & ((1u << lg) - 1u), w2 = g * sw + word;
@@ -249,16 +248,16 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
                 for (uint32_t k0 = 0; k0 < n; k0 += 64u >> lg) {
                     const uint32_t k = k0 + (lane >> lg);
                     uint32_t *dst = a.out_mask + (size_t)(uint32_t)__shfl((int)members, (int)(k & 63u)) * W + w2;
-                    if (k < n && word < sw && w2 < W) { if (a.complete) __hip_atomic_store(dst, v2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); else *dst = v2; }
+                    if (k < n && word < sw && w2 < W) put_word(dst, v2, a.complete);
                 }
             }
         }
-        if (keep && w < W) a.pool[(size_t)(r[4] & 0xFFFFu) * W + w] = v;
+        if (keep && w < W) put_word(&a.pool[(size_t)(r[4] & 0xFFFFu) * W + w], v, a.complete);
         if (n_members > 64u) members = members_from(0);
     }
     if (lane == 0 && failed) atomicAdd(&blk_failed, failed);
-    if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
     }
+    if (a.complete) stores_arrived();                        // every word this wavefront wrote has reached memory before the block's ticket is drawn
     __syncthreads();
     if (tid == 0) hand_over_look(a, lds_load(&blk_failed));
 }

@@ -260,8 +260,9 @@ __device__ __forceinline__ uint32_t store_lookup_uniform(uint32_t *entry, uint32
 // The status of a call goes to the host from the block that finishes last: every block draws a ticket, which carries the block's
 // failed walks and byte steps along (bits 0-15 blocks, 16-39 failures, 40-63 steps), so that the one that draws the last ticket
 // has the sums in hand and nothing is left to be read.  A few blocks draw from one word; more blocks draw from one word per
-// sixteen of them first (additions to one word queue up at the memory channel that holds it, about 15 ns each).  The words are
-// put back to zero by whoever draws the last ticket of each: the next kernel of the engine finds them so.
+// sixteen of them first (additions to one word queue up at the memory channel that holds it, about 15 ns each).  There are two
+// sets of words, taken in turns: a kernel's first wavefront clears the other set, which the kernel before has done with and the
+// one behind will draw from, so that nothing of it is outstanding when the status goes out.
 //   The words of the status go out as system-scope stores that each carry the call's number, so there is no order to keep
 // between them and no release, which would write back an L2 full of masks and logits first (the closing sequence of two
 // tickets, counters read back and a release took 3 us of a 12 us kernel at one row).
@@ -273,12 +274,10 @@ __device__ __forceinline__ void hand_over_store(const StoreArgs &a, const uint32
     unsigned long long mine = 1ull | (err < 4095ull ? err : 4095ull) << 16 | (stp < 4095ull ? stp : 4095ull) << 40;
     unsigned long long sum = atomicAdd(&a.tickets[g * STORE_TICKET_STRIDE], mine) + mine;
     if ((sum & 0xFFFFull) != size) return;
-    __hip_atomic_store(&a.tickets[g * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n_groups > 1u) {
         mine = (sum & ~0xFFFFull) | 1ull;
         sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], mine) + mine;
         if ((sum & 0xFFFFull) != n_groups) return;
-        __hip_atomic_store(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     auto tell = [&](uint32_t k, uint32_t value) {
         __hip_atomic_store(&a.status[k], ((unsigned long long)a.seq << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -331,6 +330,7 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
     if (tid < 2) blk[tid] = 0;
     if (tid == 0) ctl[4] = 0;
     __syncthreads();
+    if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);
     const uint32_t W = a.W, ncls = a.ncls;
     // The record of the block's group.  Which group that is is known only once the groups' first blocks have been read, and the
     // record only after that: so lane l asks for the first block AND the twelve words of the record of group l, all at once,
@@ -707,10 +707,7 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
             const uint32_t n = n_members - m0 < 64u ? n_members - m0 : 64u;
             for (uint32_t k = 0; k < n; k++) {
                 uint32_t *dst = a.out_mask + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)members, (int)k) * W + w;
-                if (lane < slots && w < W) {
-                    if (a.complete) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                    else *dst = v;
-                }
+                if (lane < slots && w < W) put_word(dst, v, a.complete);
             }
             if (APPLY) {
                 // Logit masking (Section 3.3) of the segment's tokens, right here: 16-byte pieces, consecutive lanes on consecutive
@@ -772,7 +769,7 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
                 }
             }
         }
-        if ((flags & STORE_ROW_KEEP) && lane < slots && w < W) a.pool[(size_t)keep_slot * W + w] = v;
+        if ((flags & STORE_ROW_KEEP) && lane < slots && w < W) put_word(&a.pool[(size_t)keep_slot * W + w], v, a.complete);
         if (n_members > 64u) members = members_from(0);
         if (APPLY) {
 #pragma unroll
@@ -780,8 +777,8 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
         }
     }
     if (lane == 0 && steps) atomicAdd(&blk[1], steps);
-    if (a.complete) __builtin_amdgcn_s_waitcnt(0x0F70);      // every mask word this wavefront wrote has reached memory before the block's ticket is drawn
     }
+    if (a.complete) stores_arrived();                        // every word this wavefront wrote has reached memory before the block's ticket is drawn
     __syncthreads();
     if (tid == 0) hand_over_store(a, blk);
 }

@@ -1010,3 +1010,42 @@ def test_function_transforms_raise_and_the_process_goes_on(torch_cuda, oracle_li
     want = oracle_lib.Oracle(g).new_state().mask(off, data)
     out = zf.apply_mask(eng, logits[0].clone(), zf.compute_mask(eng, [st], d_mask))
     assert out.cpu().numpy().view(np.uint32).tobytes() == oracle_apply(logits[0].cpu().numpy().view(np.uint32), want[None, :]).tobytes()
+
+
+@pytest.mark.parametrize("noalloc,precompute", [(False, 0), (False, -1), (True, -1)])
+def test_waiting_calls_on_two_streams(noalloc, precompute, torch_cuda, oracle_lib):
+    """Waiting calls that take turns on two streams, nothing synchronised between them: the second call of a step is served the rows that the
+    first has just left in the state cache (or walks the transitions it has just added), and the masks are the oracle's on both."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    cfg = configs.CONFIGS[4]
+    g, toks = cfg.grammar(), cfg.vocab(16384)
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, precompute_states=precompute)
+    call = zf.compute_mask_noalloc if noalloc else zf.compute_mask
+    n, rs = 24, stream(11, f"two-streams{noalloc}{precompute}")
+    first, second = [eng.new_state() for _ in range(n)], [eng.new_state() for _ in range(n)]
+    oracles = [orc.new_state() for _ in range(n)]
+    masks = [torch.full((n, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda") for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    hits = 0
+    for step in range(10):
+        for turn, rows in enumerate((first, second)):
+            with torch.cuda.stream(streams[(step + turn) & 1]):
+                call(eng, rows, masks[turn])
+        hits += eng.mask_report().cache_hits
+        got = [m.cpu().numpy().view(np.uint32) for m in masks]   # on the default stream, which waits for neither of the two
+        for b in range(n):
+            want = oracles[b].mask(off, data, 8)
+            assert np.array_equal(got[0][b], want) and np.array_equal(got[1][b], want), (step, b)
+            bits = np.flatnonzero(np.unpackbits(want.view(np.uint8), bitorder="little"))
+            if len(bits) == 0:
+                first[b].reset(), second[b].reset()
+                oracles[b] = orc.new_state()
+                continue
+            t = int(bits[rs.below(len(bits))])
+            first[b].advance(t), second[b].advance(t)
+            assert oracles[b].feed_bytes(toks[t])
+    assert noalloc or hits >= 9 * n, hits
