@@ -73,6 +73,8 @@ struct DeviceSide {
     uint4 *d_work = nullptr;
     int cus = 256;
     int mode = 2;
+    bool lanes_call[N_SLOTS] = {false, false, false, false};   // the call ran the per-block automaton's AUT_STEP_LANES build
+    bool lanes_outgrown = false;                     // such a call left strings to the fallback pass: AUT_STEP_WIDE from then on
     uint32_t *d_counters = nullptr;
     uint2 *d_fb_items = nullptr;
     uint32_t *d_fb_ss = nullptr;
@@ -1234,7 +1236,11 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         int scratch = 0, n_states = 0, arena = 0, base_sets = 0, base_items = 0;
         // The build without the wide byte step also takes the chart from LDS only (its pointers are then
         // known to be LDS addresses): it serves calls whose sets are all small and whose charts all fit.
-        int step = biggest_set <= (size_t)AUT_NARROW_SET_MAX ? AUT_STEP_NARROW : biggest_set <= (size_t)AUT_LANES_SET_MAX ? AUT_STEP_LANES : AUT_STEP_WIDE;
+        // AUT_STEP_LANES holds sets of 64 items, which a byte or a long token can take a dozen items beyond: the strings behind such a set
+        // then cost the fallback pass more than the build saves (7 %), and the short list of a call that allocates nothing
+        // might not hold them.  So that call never takes the build, and an engine whose strings have outgrown it once takes the wide one.
+        int step = biggest_set <= (size_t)AUT_NARROW_SET_MAX ? AUT_STEP_NARROW
+                 : biggest_set <= (size_t)AUT_LANES_SET_MAX && !noalloc && !d->lanes_outgrown ? AUT_STEP_LANES : AUT_STEP_WIDE;
         const uint32_t lds_max = 160u * 1024u;
         for (;;) {
             scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
@@ -1260,6 +1266,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         a.aut_states = n_states; a.aut_arena = arena; a.aut_scratch = scratch;
         a.aut_base_sets = base_sets; a.aut_base_items = base_items;
         a.aut_step = step;
+        d->lanes_call[slot] = step == AUT_STEP_LANES;
         // blocks per row: as many as the chip holds at once, at most two per compute unit and one per pass of AUT_SUB_WORDS words.
         // (Every block works its row's automaton out from the start: a second round of blocks, where the wide byte step's scratch
         // leaves room for one block per compute unit, took as long as the first.)
@@ -1991,6 +1998,7 @@ int zf_mask_wait(zf_engine *e, void *hip_stream) {
     }
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) {
         unresolved += st[8 * k + 2];
+        if (st[8 * k + 0] && d->lanes_call[k]) d->lanes_outgrown = true;
         if (st[8 * k + 0] || st[8 * k + 1]) { d->report.overflow_chunks = st[8 * k + 0]; d->report.walk_chunks = st[8 * k + 1]; d->report.parser_steps = st[8 * k + 3]; }
         st[8 * k + 0] = st[8 * k + 1] = st[8 * k + 2] = st[8 * k + 3] = 0;
     }

@@ -15,7 +15,7 @@ static const int WALK_DEPTH_MAX = 32;      // trie depth the walk kernel follows
 static const int BASE_SETS_LDS = 31;       // a row's chart is staged into LDS when it has at most this many sets ...
 static const int BASE_ITEMS_LDS = 64;      // ... and items (the mask-automaton kernel takes larger limits from the host when LDS allows)
 // The builds of mask_automaton_kernel, by the byte step they hold.  Charts whose sets are all of up to AUT_NARROW_SET_MAX items run the narrow one, of up to
-// AUT_LANES_SET_MAX the one for a dozen items (a set that outgrows 64 items there goes to the fallback pass; chart addresses known to be LDS and no hash table:
+// AUT_LANES_SET_MAX the one for a dozen items (a set that outgrows 64 items there goes to the fallback pass, and the engine's next calls to the build behind it; chart addresses known to be LDS and no hash table:
 // 64 rows of the expression grammar without pruning, 8 steps of a decode loop, 988 us against 1,056 in the build that follows), others the one that
 // holds the wide step as well, to which source sets of more than AUT_STEP_WIDE_FROM items go at once (the line at 16 measured the same).
 static const int AUT_STEP_NARROW = 0, AUT_STEP_LANES = 1, AUT_STEP_WIDE = 2;

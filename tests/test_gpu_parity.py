@@ -1049,3 +1049,50 @@ def test_waiting_calls_on_two_streams(noalloc, precompute, torch_cuda, oracle_li
             first[b].advance(t), second[b].advance(t)
             assert oracles[b].feed_bytes(toks[t])
     assert noalloc or hits >= 9 * n, hits
+
+
+def test_per_block_automaton_sets_that_outgrow_the_lanes(torch_cuda, oracle_lib):
+    """Charts whose sets hold ten items, and a byte that leaves eighty: more than the build for a dozen items holds.  The call that allocates
+    nothing does not take that build (nothing is left to the fallback pass); another call leaves the strings behind the byte to that pass once, and
+    the engine's next calls take the build that holds the set.  Masks are the oracle's throughout."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    from workloads.grammar import Grammar
+    g = Grammar(name="keywords")
+    g.set_start("S")
+    g.alts("S", *[[f"A{k}", "K", f"A{k}"] for k in range(10)])
+    for k in range(10):
+        g.alts(f"A{k}", [b"a"])
+    words = [b"k%02dx" % k for k in range(80)]
+    g.alts("K", *[[w] for w in words])
+    toks = [bytes([c]) for c in range(128)] + words + [b"k0", b"k1", b"k07xa", b"k79xb", b"ak33xa", b"aa", b"k80x"] + [b"k%dx" % k for k in range(40)]
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    want = []
+    for p in (b"", b"a", b"ak", b"ak4", b"ak42x"):
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data))
+    engines = [zf.Engine(g, toks, device=0, state_cache_entries=-1, walk_mode=0) for _ in range(2)]
+    d_mask = torch.empty((2, engines[0].W), dtype=torch.int32, device="cuda")
+
+    def masks(eng, call, prefixes):
+        rows = []
+        for p in prefixes:
+            rows.append(eng.new_state())
+            rows[-1].advance_bytes(p)
+        d_mask.fill_(0x5A5A5A5A)
+        call(eng, rows, d_mask)
+        return d_mask.cpu().numpy().view(np.uint32), eng.mask_report().overflow_chunks
+
+    start = engines[0].new_state()
+    start.advance_bytes(b"a")
+    assert sum(1 for it in start.chart()[0] if it[0] == 1) == 10     # the current set: more than the narrow build takes, no more than the next one
+    got, left = masks(engines[0], zf.compute_mask_noalloc, (b"", b"a"))
+    assert np.array_equal(got, np.stack(want[:2])) and left == 0
+    for turn in range(3):
+        got, left = masks(engines[1], zf.compute_mask, (b"", b"a"))
+        assert np.array_equal(got, np.stack(want[:2])) and (left > 0) == (turn == 0), (turn, left)
+    for k, p in ((2, b"ak"), (3, b"ak4"), (4, b"ak42x")):
+        got, left = masks(engines[1], zf.compute_mask, (b"a", p))
+        assert np.array_equal(got, np.stack([want[1], want[k]])), p
