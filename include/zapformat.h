@@ -225,7 +225,8 @@ int zf_last_mask_report(const zf_engine *e, zf_mask_report *out);
  * parsed again the next time it is needed (benchmarks call it to start cold).  Results do not change.  With
  * zf_options.precompute_states on, and no asynchronous mask call in flight, the automata are then explored from the
  * empty prefix again as when the engine was compiled (the device's is filled on the null stream, which this call waits for):
- * the engine is back to what it knew after zf_compile, not to nothing. */
+ * the engine is back to what it knew after zf_compile, not to nothing.  States of the engine may be advanced by
+ * other threads meanwhile. */
 int zf_engine_clear_state_cache(zf_engine *e);
 /* on != 0: zf_compute_mask brackets each of its kernels with HIP events (a few microseconds
  * of extra host time per call) and zf_last_mask_report returns their durations. */

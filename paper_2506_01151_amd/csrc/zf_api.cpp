@@ -542,8 +542,8 @@ const char *zf_strerror(int code) {
 const char *zf_last_error(void) { return g_err.c_str(); }
 
 static bool wants_exploration(const zf_engine *e);
-static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items);
-static void store_adopt(zf_engine *e, bool whole);
+static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items, std::unique_lock<std::mutex> *lk);
+static void store_adopt(zf_engine *e, bool whole, std::unique_lock<std::mutex> *lk);
 
 int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_options *opt, zf_engine **out) {
     if (!g || !v || !out || v->V < 0 || (v->V && !v->off)) return fail(ZF_ERR_INVALID_ARG, "null argument");
@@ -575,7 +575,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         if (e->opt.walk_mode == 2 && e->opt.pruning != 0) e->host_aut = new HostAutomaton(e->tab);
         if (wants_exploration(e))
             explorer = std::thread([e, &whole]() {
-                try { whole = explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
+                try { whole = explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS, nullptr); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
@@ -587,7 +587,10 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         const int rc = setup_device(e);
         if (rc != ZF_OK) return give_up(rc);
     }
-    if (explorer.joinable()) { explorer.join(); store_adopt(e, whole); }
+    if (explorer.joinable()) {
+        explorer.join();
+        try { store_adopt(e, whole, nullptr); } catch (const std::bad_alloc &) {}   // the store starts empty, then
+    }
     *out = e;
     return ZF_OK;
 }
@@ -1836,9 +1839,11 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states, int32_t batch, uint32
 // live (State::trans: a class on which no item leaves anything is known to be dead), chart copies, an ordered map of item lists.
 static bool wants_exploration(const zf_engine *e) { return e->store_on && e->host_aut && e->opt.precompute_states > 0; }
 
-// The host's part: touches nothing but the host automaton (the caller holds its lock, or is the only one who knows the engine).
-// True when the automaton is finite and whole.
-static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items) {
+// The host's part: touches nothing but the host automaton.  True when the automaton is finite and whole.
+// lk: the engine's lock, held, when others may be at work with the engine (null: nobody else knows it yet).  It is let go during
+// every Earley byte step, as zf_advance lets it go: rows that are advanced meanwhile wait for one transition to be written
+// down, not for the exploration.  It is held again when this returns, and nothing has been added since the answer was found.
+static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items, std::unique_lock<std::mutex> *lk) {
     HostAutomaton &A = *e->host_aut;
     const auto t0 = std::chrono::steady_clock::now();
     const double budget_s = 1.0;
@@ -1849,15 +1854,25 @@ static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items) {
         for (int c = 0; c < e->tab.n_cls; c++) {
             if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
             if (A.n_states > most_states || (size_t)A.n_items >= most_items) return false;
-            A.compute(s, c, w);
+            if (!lk) { A.compute(s, c, w); continue; }
+            {
+                struct Walker {                           // keeps the automaton from being emptied meanwhile
+                    int &n;
+                    std::unique_lock<std::mutex> &lk;
+                    Walker(int &n_, std::unique_lock<std::mutex> &lk_) : n(n_), lk(lk_) { n++; lk.unlock(); }
+                    ~Walker() { lk.lock(); n--; }
+                } walker(e->host_walkers, *lk);
+                A.look_ahead(s, c, w);
+            }
+            if (A.st(s).trans[c] == HostAutomaton::NONE) A.record(s, c, w);   // else somebody else has made it meanwhile
         }
     }
     return true;
 }
 
 // The device's part: the store is cleared and takes over what the host automaton holds, names and all.  A failure is no error:
-// the store then starts empty, as it does without an exploration.
-static void store_adopt(zf_engine *e, bool whole) {
+// the store then starts empty, as it does without an exploration.  lk as above; it is let go as soon as what goes to the device has been copied.
+static void store_adopt(zf_engine *e, bool whole, std::unique_lock<std::mutex> *lk) {
     DeviceSide *d = e->dev;
     const HostAutomaton &A = *e->host_aut;
     const Tables &t = e->tab;
@@ -1876,14 +1891,25 @@ static void store_adopt(zf_engine *e, bool whole) {
             items.push_back(make_uint2((aw & IW_TERM) ? ((aw & 0xFFFFu) | ((uint32_t)s.items[i].q << 16)) : aw, s.items[i].o));
         }
     }
+    // the host's rows of the table, block by block: where they are, or copies that others' work on the automaton cannot change
+    std::vector<uint32_t> rows_now;
+    std::vector<const uint32_t *> block_rows;
+    if (lk) rows_now.resize(n * ncls);
+    for (size_t b = 0; b * HostAutomaton::BLOCK < n; b++) {
+        const size_t first = b * HostAutomaton::BLOCK, rows = std::min<size_t>(HostAutomaton::BLOCK, n - first);
+        if (lk) memcpy(rows_now.data() + first * ncls, A.blocks[b].trans.get(), rows * ncls * 4);
+        block_rows.push_back(lk ? rows_now.data() + first * ncls : A.blocks[b].trans.get());
+    }
+    const uint32_t host_epoch = e->host_epoch;
+    if (lk) lk->unlock();
     auto run = [&]() -> hipError_t {
         hipError_t rc = hipSetDevice(d->device);
         if (rc == hipSuccess) rc = launch_store_clear(G, (uint32_t)ncls, d->d_root_items, d->n_root, nullptr);
         if (rc == hipSuccess) rc = hipMemcpyAsync(G.hdr, hdr.data(), n * sizeof(uint2), hipMemcpyHostToDevice, nullptr);
         if (rc == hipSuccess) rc = hipMemcpyAsync(G.arena, items.data(), items.size() * sizeof(uint2), hipMemcpyHostToDevice, nullptr);
-        for (size_t b = 0; rc == hipSuccess && b * HostAutomaton::BLOCK < n; b++) {   // the host's rows of the table, block by block
+        for (size_t b = 0; rc == hipSuccess && b < block_rows.size(); b++) {
             const size_t rows = std::min<size_t>(HostAutomaton::BLOCK, n - b * HostAutomaton::BLOCK);
-            rc = hipMemcpyAsync(G.trans + b * HostAutomaton::BLOCK * ncls, A.blocks[b].trans.get(), rows * ncls * 4, hipMemcpyHostToDevice, nullptr);
+            rc = hipMemcpyAsync(G.trans + b * HostAutomaton::BLOCK * ncls, block_rows[b], rows * ncls * 4, hipMemcpyHostToDevice, nullptr);
         }
         if (rc == hipSuccess) rc = launch_store_adopt(G, (uint32_t)n, (uint32_t)items.size(), nullptr);
         if (rc == hipSuccess) rc = hipStreamSynchronize(nullptr);
@@ -1894,7 +1920,7 @@ static void store_adopt(zf_engine *e, bool whole) {
     d->store_dirty = false;
     d->store_epoch++;
     d->store_states = (uint32_t)n; d->store_items = (uint32_t)items.size();
-    d->name_host_epoch = e->host_epoch; d->name_store_epoch = d->store_epoch;
+    d->name_host_epoch = host_epoch; d->name_store_epoch = d->store_epoch;
     d->name_of_host.resize(n);
     for (uint32_t id = 0; id < n; id++) d->name_of_host[id] = id;
     if (whole) { d->closed_states = (uint32_t)n; d->closed_epoch = d->store_epoch; }
@@ -2023,8 +2049,10 @@ int zf_engine_clear_state_cache(zf_engine *e) {
         e->host_aut->clear();
         e->host_epoch++;
         if (wants_exploration(e) && e->dev && e->dev->pending == 0) {   // back to what the engine knew when it was compiled (with calls in flight the store is cleared later, and starts empty)
-            const bool whole = explore_host(e, e->dev->store.cap_states, e->dev->store.cap_items);
-            store_adopt(e, whole);
+            try {
+                const bool whole = explore_host(e, e->dev->store.cap_states, e->dev->store.cap_items, &lk);
+                store_adopt(e, whole, &lk);
+            } catch (const std::bad_alloc &) {}           // the store starts empty, then
         }
     }
     return ZF_OK;

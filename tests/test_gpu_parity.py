@@ -1096,3 +1096,48 @@ def test_per_block_automaton_sets_that_outgrow_the_lanes(torch_cuda, oracle_lib)
     for k, p in ((2, b"ak"), (3, b"ak4"), (4, b"ak42x")):
         got, left = masks(engines[1], zf.compute_mask, (b"a", p))
         assert np.array_equal(got, np.stack([want[1], want[k]])), p
+
+
+def test_advance_goes_on_while_the_automaton_is_explored_again(torch_cuda, oracle_lib):
+    """zf_engine_clear_state_cache explores the automaton again (of this ambiguous grammar for tens of milliseconds); a row that another thread
+    feeds meanwhile waits for a transition now and then, not for the exploration, and its mask is the oracle's afterwards."""
+    import threading
+    import time
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    from workloads.grammar import Grammar
+    g = Grammar(name="ambiguous")
+    g.set_start("S")
+    g.alts("S", ["S", "S"], ["S", "S", "S"], ["S", b"+", "S"], [b"(", "S", b")"], [b"a"], [b"b"])
+    toks = [bytes([c]) for c in range(128)] + [b"ab", b"a+", b"(a", b"aaa", b"b)", b")b"]
+    off, data = wvocab.vocab_csr(toks)
+    so = oracle_lib.Oracle(g).new_state()
+    text = b"(a+b)ab(a" * 3
+    assert so.feed_bytes(text)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)
+    row, took, longest, n, done = eng.new_state(), [], 0.0, 0, threading.Event()
+
+    def clear():
+        t = time.perf_counter()
+        eng.clear_state_cache()
+        took.append(time.perf_counter() - t)
+        done.set()
+
+    thread = threading.Thread(target=clear)
+    thread.start()
+    while not done.is_set():
+        row.reset()
+        for c in text:
+            t = time.perf_counter()
+            row.advance(c)
+            longest = max(longest, time.perf_counter() - t)
+            n += 1
+    thread.join()
+    print(f"cleared in {took[0] * 1e3:.0f} ms, {n} advances meanwhile, the longest {longest * 1e3:.1f} ms")
+    assert longest < 0.5 * took[0], (took[0], longest)
+    row.reset()
+    for c in text:
+        row.advance(c)
+    d_mask = torch.empty((1, eng.W), dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, [row], d_mask)
+    assert np.array_equal(d_mask.cpu().numpy().view(np.uint32)[0], so.mask(off, data))
