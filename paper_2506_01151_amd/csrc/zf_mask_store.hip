@@ -42,12 +42,14 @@ __device__ __forceinline__ bool t_final(uint32_t t) { return t != AT_NONE && t !
 // right or "not there yet": look-ups read through the caches first and ask device memory (an atomic load, or the
 // compare-and-swap that claims the entry) only when the cached answer is not final.
 
-// Hundreds of wavefronts of a row can wait for the same entry: they ask less and less often, so that their polls do not
-// slow the memory channel the owner works through (at most 64 x 64 cycles between two polls: 1.7 us).
+// Hundreds of wavefronts of a group can wait for the same entry: they ask less and less often, so that their polls do not
+// slow the memory channel the owner works through.  A byte step takes 3 to 10 us; the pauses are 24, 64 and 100 times 64 cycles (0.6, 1.7,
+// 2.7 us; at 8, 24 and 64 times, which was enough when rows had blocks of their own and fewer wavefronts waited, calls of
+// 5 to 8 steps took 46.5 instead of 45 us; at 48, 100 and 127 times 44).
 __device__ __forceinline__ void poll_pause(uint32_t spins) {
-    if (spins < 2) __builtin_amdgcn_s_sleep(8);
-    else if (spins < 6) __builtin_amdgcn_s_sleep(24);
-    else __builtin_amdgcn_s_sleep(64);
+    if (spins < 2) __builtin_amdgcn_s_sleep(24);
+    else if (spins < 6) __builtin_amdgcn_s_sleep(64);
+    else __builtin_amdgcn_s_sleep(100);
 }
 
 struct Staging { uint32_t *ctl; uint8_t *smem; const uint8_t *blob; uint32_t n16; uint8_t *rep; const uint8_t *rep_src; uint32_t ncls; bool wide_sets; };   // what ensure_tables needs; wide_sets: the rows' charts hold sets of many items
@@ -104,6 +106,17 @@ struct StoreSets {             // resolves the name of a set to its items (devic
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Scratch { uint32_t *w, *o, *h; uint32_t cap; };   // one wavefront's set under construction (+ hash table of the wide step)
+
+// Lane l: the sum of the lanes up to l (data-parallel-primitive moves, no trip through LDS).
+__device__ __forceinline__ uint32_t wave_sums(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);    // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);    // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);    // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);    // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
 
 // A set's signature does not depend on the order of its items (the host, which fills the store when the engine is compiled, the
 // narrow and the wide byte step each make them in an order of their own): the sum of its items' words, closed with their count.
@@ -166,9 +179,8 @@ __device__ __forceinline__ uint32_t store_transition(const TV &T, const StoreVie
     if (kept == 0) return AT_SINK;
     uint32_t sum = 0;
     for (uint32_t i0 = 0; i0 < kept; i0 += 64) if (i0 + lane < kept) sum += item_sum(lds_load(&sc.w[i0 + lane]), lds_load(&sc.o[i0 + lane]));
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
-    const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane((int)set_signature(sum, kept));
+    sum = wave_sums(sum);
+    const uint32_t h = set_signature((uint32_t)__builtin_amdgcn_readlane((int)sum, 63), kept);
     uint32_t slot = (h * 0x9E3779B1u) & G.intern_mask;
     for (uint32_t probes = 0; probes <= G.intern_mask; probes++) {
         const unsigned long long e = __hip_atomic_load(&G.intern[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -204,24 +216,15 @@ __device__ __forceinline__ uint32_t store_transition(const TV &T, const StoreVie
     return id;                                               // the table has twice as many slots as states: not reached
 }
 
-// The same as a function of its own, called by the rare wavefront that needs a transition nobody has computed yet.  In line (it
-// has two callers) the byte step made 45 of the kernel's 52 KB of code and its registers were allocated around it: the walk
-// spilled scalar registers and its code lay in pieces between pieces of this.  What it reads beyond its arguments is in device memory.
-// Everything is uniform: the arguments travel in vector registers and are taken back into scalar ones first.
-typedef __attribute__((address_space(3))) uint8_t LdsBytes;
+// The same with the LDS laid out: cache of table entries, staging flag, verdict words; then the staged tables, class representatives, scratch.
+// In line, and with D and G loaded once at the kernel's head: as a function of its own that read them at every call a chain of byte
+// steps took 13 % longer (kernel time of 16 rows of a JSON schema from an empty store, calls of 17 to 32 steps: 74.5 us that way, 71 in line with
+// the loads in place, 66 like this; 64 rows of the query language, calls of 33 to 64 steps: 94, 91.5, 82).
 static const uint32_t SCRATCH_WIDE = 1u << 16;           // with the scratch's capacity (at most LANE_CAP_MAX) below and the wavefront's number above it
-static const uint32_t TABLES_AT = LC_ENTRIES * 8 + 32 + STORE_WAVES * 64 * 4;   // LDS: cache of table entries, staging flag, verdict words; then the staged tables, class representatives, scratch
+static const uint32_t TABLES_AT = LC_ENTRIES * 8 + 32 + STORE_WAVES * 64 * 4;
 template <int MODE>
-__device__ __attribute__((noinline)) uint32_t store_transition_call(const StoreConst *konst_v, LdsBytes *lds_v, uint32_t how_v, uint32_t *errors, uint32_t s_v, uint32_t cl_v) {
-    const uint64_t kp = (uint64_t)(uintptr_t)konst_v;
-    const uint64_t ku = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)kp) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(kp >> 32)) << 32;
-    const StoreConst *konst = reinterpret_cast<const StoreConst *>((uintptr_t)ku);
-    uint8_t *smem = (uint8_t *)(LdsBytes *)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)lds_v);
-    const uint32_t how = (uint32_t)__builtin_amdgcn_readfirstlane((int)how_v);
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_v), cl = (uint32_t)__builtin_amdgcn_readfirstlane((int)cl_v);
+__device__ __forceinline__ uint32_t store_transition_at(const DeviceTables &D, const StoreView &G, uint8_t *smem, uint32_t how, uint32_t *errors, uint32_t s, uint32_t cl) {
     const uint32_t lane = threadIdx.x & 63u;
-    const DeviceTables &D = konst->tab;
-    const StoreView &G = konst->view;
     uint8_t *const tables_at = smem + TABLES_AT;
     TV T;
     uint32_t off = table_view<MODE>(D, tables_at, T);
@@ -330,7 +333,6 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
     if (tid < 2) blk[tid] = 0;
     if (tid == 0) ctl[4] = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);
     const uint32_t W = a.W, ncls = a.ncls;
     // The record of the block's group.  Which group that is is known only once the groups' first blocks have been read, and the
     // record only after that: so lane l asks for the first block AND the twelve words of the record of group l, all at once,
@@ -384,6 +386,9 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
     };
     uint32_t root = AT_FAIL, steps = 0;
     uint32_t *errors = &blk[0];
+    const DeviceTables tables = a.konst->tab;                // what a byte step reads of them, on its way while the record is looked at
+    const StoreView store = a.konst->view;
+    if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);   // (a store ahead of the two would make vector loads of their scalar ones)
     const uint32_t slot16 = lane & (slots - 1u), grp = lane >> slots_log2;    // lane = (word of the segment, which copy)
     // The token-mask cache words of segment g: every copy ORs its share of the group's cache rows.  The first three rounds stay
     // as they were loaded until they are needed (an OR here would wait for them here), which covers three to twelve cache rows.
@@ -461,7 +466,7 @@ __global__ __launch_bounds__(STORE_BLOCK, STORE_BLOCKS_PER_CU) void mask_store_k
     if (APPLY) logits_ahead(unit, l_pre);
     auto transition = [&](uint32_t s, uint32_t cl) __attribute__((always_inline)) -> uint32_t {
         steps++;
-        return store_transition_call<MODE>(a.konst, (LdsBytes *)smem, (uint32_t)a.scratch | (a.wide ? SCRATCH_WIDE : 0u) | wave << 24, errors, s, cl);
+        return store_transition_at<MODE>(tables, store, smem, (uint32_t)a.scratch | (a.wide ? SCRATCH_WIDE : 0u) | wave << 24, errors, s, cl);
     };
     auto find_root = [&]() __attribute__((always_inline)) {
         // ---- the group's current state: walk the bytes fed since `start` was its state (the loads above are in flight) ----
