@@ -93,7 +93,8 @@ struct DeviceSide {
     // What sizes a call's grid: the tokens a state's token-mask cache rows leave to the parser.  The host keeps the token-order
     // rows and counts the union for every set of cache rows it meets, once (the sets repeat all the time).
     std::vector<uint2> h_ci_tok;                     // [Q + N][W]
-    std::unordered_map<uint64_t, uint32_t> undecided_of;   // signature of the list of cache rows -> undecided tokens
+    std::vector<uint32_t> ci_undecided;              // [Q + N] what a row leaves undecided by itself
+    std::unordered_map<uint64_t, uint32_t> undecided_of;   // signature of a list of several cache rows -> undecided tokens
     uint32_t store_backoff = 0, store_backoff_next = 8;   // after a call the store had no room for: calls that take the per-block automaton instead
     // A call through the persistent automaton until zf_mask_wait has seen its status: the groups whose state the kernel reports,
     // and their rows.  (Groups the host knows the state of need no note.)
@@ -226,7 +227,27 @@ int alloc_fallback(DeviceSide *d) {
     return ZF_OK;
 }
 
-int setup_device(zf_engine *e) {
+// Tokens that the cache rows `ent` together leave to the parser: the bits of any row's second words that are in no row's first words.
+// A stretch of words at a time, so that every loop is a plain one over neighbours.
+uint32_t undecided_tokens(const std::vector<uint2> &ci_tok, size_t W, const uint32_t *ent, uint32_t n) {
+    static const size_t STRETCH = 512;
+    uint64_t both[STRETCH];
+    uint32_t left[STRETCH], cnt = 0;
+    for (size_t w0 = 0; w0 < W; w0 += STRETCH) {
+        const size_t m = std::min(STRETCH, W - w0);
+        std::fill(both, both + m, 0);
+        for (uint32_t k = 0; k < n; k++) {
+            const uint2 *row = ci_tok.data() + ent[k] * W + w0;
+            for (size_t j = 0; j < m; j++) both[j] |= (uint64_t)row[j].y << 32 | row[j].x;
+        }
+        for (size_t j = 0; j < m; j++) left[j] = (uint32_t)(both[j] >> 32) & ~(uint32_t)both[j];
+        for (size_t j = 0; j < m; j++) cnt += (uint32_t)__builtin_popcount(left[j]);
+    }
+    return cnt;
+}
+
+template <class F>
+int setup_device(zf_engine *e, F rows_made) {            // rows_made: called when the host's copy of the cache rows is there
     DeviceSide *d = new (std::nothrow) DeviceSide();
     if (!d) return fail(ZF_ERR_OOM, "out of memory");
     e->dev = d;
@@ -235,6 +256,7 @@ int setup_device(zf_engine *e) {
     const Tables &t = e->tab;
     const Trie &tr = e->trie;
     DeviceTables &T = d->tab;
+    T.V = e->V; T.W = e->W;                              // (count_lists reads W as soon as rows_made has been called)
     int rc;
     std::vector<uint8_t> cls(t.cls, t.cls + 256);
 #define UP(field, vec, bytes) if ((rc = upload(d, vec, &T.field, bytes)) != ZF_OK) return rc
@@ -299,7 +321,9 @@ int setup_device(zf_engine *e) {
         for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_at[tr.rank_of[v] + 2]++;
         for (size_t r = 2; r < tok_at.size(); r++) tok_at[r] += tok_at[r - 1];
         for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_by[tok_at[tr.rank_of[v] + 1]++] = (uint32_t)v;
+        d->ci_undecided.assign(n_rows, 0);
         parallel_for(n_rows, n_rows * V >= (size_t)1 << 20 ? 8 : 1, [&](size_t r) {
+            uint32_t undecided = 0;
             for (int kind = 0; kind < 2; kind++) {
                 const uint32_t *src = (kind ? tr.ci_cd.data() : tr.ci_valid.data()) + r * tr.Wr;
                 uint2 *dst = ci_tok.data() + r * W;
@@ -307,16 +331,22 @@ int setup_device(zf_engine *e) {
                     for (uint32_t bits = src[w]; bits; bits &= bits - 1) {
                         const size_t k = w * 32 + (size_t)__builtin_ctz(bits);
                         if (k >= (size_t)tr.n_strings) break;     // bits of the last chunk beyond the strings
-                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) (kind ? dst[tok_by[j] >> 5].y : dst[tok_by[j] >> 5].x) |= 1u << (tok_by[j] & 31);
+                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) {
+                            uint2 &word = dst[tok_by[j] >> 5];
+                            const uint32_t bit = 1u << (tok_by[j] & 31);
+                            if (kind) { word.y |= bit; undecided += (word.x & bit) == 0; } else word.x |= bit;
+                        }
                     }
             }
+            d->ci_undecided[r] = undecided;
         });
+        rows_made();
         UP(tok16, tok16, nullptr); UP(ci_tok, ci_tok, nullptr);
     }
     T.Q = t.Q;
 #undef UP
     T.N = t.N; T.n_cls = t.n_cls; T.end_base = t.end_base; T.n_nodes = (int)tr.nodes.size(); T.n_chunks = (int)tr.chunk_begin.size();
-    T.n_strings = tr.n_strings; T.V = e->V; T.W = e->W; T.chunk_ranks = tr.chunk_ranks;
+    T.n_strings = tr.n_strings; T.chunk_ranks = tr.chunk_ranks;
     T.Wr = tr.Wr;
     d->mode = choose_table_mode(T);
     HIP_TRY(prepare_kernels());
@@ -544,6 +574,8 @@ const char *zf_last_error(void) { return g_err.c_str(); }
 static bool wants_exploration(const zf_engine *e);
 static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items, std::unique_lock<std::mutex> *lk);
 static void store_adopt(zf_engine *e, bool whole, std::unique_lock<std::mutex> *lk);
+static std::vector<std::vector<uint32_t>> explored_entries(const zf_engine *e);
+static void count_lists(zf_engine *e, const std::vector<std::vector<uint32_t>> &lists);
 
 int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_options *opt, zf_engine **out) {
     if (!g || !v || !out || v->V < 0 || (v->V && !v->off)) return fail(ZF_ERR_INVALID_ARG, "null argument");
@@ -564,18 +596,34 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
     if (e->opt.chunk_strings != 8 && e->opt.chunk_strings != 16 && e->opt.chunk_strings != 32) e->opt.chunk_strings = 8;
     if (e->opt.precompute_states == 0) e->opt.precompute_states = 65536;
     if (e->opt.precompute_states < 0) e->opt.precompute_states = 0;
-    bool whole = false;                                   // the explorer's answer
-    std::thread explorer;                                 // the exploration needs the grammar tables only: it runs beside everything else
-    struct Join { std::thread &t; ~Join() { if (t.joinable()) t.join(); } } join{explorer};
-    auto give_up = [&](int rc) { if (explorer.joinable()) explorer.join(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
+    // The exploration needs the grammar tables only: it runs beside everything else.  While the tables go to the device, its thread
+    // counts what the explored states' lists of cache rows leave undecided.
+    struct Explorer {
+        std::thread thread;
+        std::mutex mu;
+        std::condition_variable cv;
+        bool whole = false, explored = false, rows_made = false, stop = false;   // whole: explore_host's answer
+        void tell(bool &what) { { std::lock_guard<std::mutex> lk(mu); what = true; } cv.notify_all(); }
+        void await(const bool &what) { std::unique_lock<std::mutex> lk(mu); cv.wait(lk, [&]() { return what || stop; }); }
+        void end() { if (thread.joinable()) { tell(stop); thread.join(); } }
+        ~Explorer() { end(); }
+    } explorer;
+    auto give_up = [&](int rc) { explorer.end(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
     try {
         if (!build_tables(g, e->tab)) { delete e; return ZF_ERR_GRAMMAR; }
         e->V = v->V; e->W = (v->V + 31) / 32;
         e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
         if (e->opt.walk_mode == 2 && e->opt.pruning != 0) e->host_aut = new HostAutomaton(e->tab);
         if (wants_exploration(e))
-            explorer = std::thread([e, &whole]() {
-                try { whole = explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS, nullptr); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
+            explorer.thread = std::thread([e, &explorer]() {
+                try { explorer.whole = explore_host(e, store_cap_states(e->tab.n_cls), STORE_CAP_ITEMS, nullptr); } catch (const std::bad_alloc &) {}   // what was learnt by then stands
+                explorer.tell(explorer.explored);
+                if (e->opt.disable_token_mask_cache) return;
+                try {
+                    const std::vector<std::vector<uint32_t>> lists = explored_entries(e);
+                    explorer.await(explorer.rows_made);
+                    if (explorer.rows_made) count_lists(e, lists);
+                } catch (const std::bad_alloc &) {}       // the mask calls count, then
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
@@ -584,12 +632,13 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
     } catch (const std::bad_alloc &) { return give_up(fail(ZF_ERR_OOM, "out of memory")); }
     catch (const std::system_error &) { return give_up(fail(ZF_ERR_OOM, "no thread to be had")); }
     if (e->opt.device >= 0) {
-        const int rc = setup_device(e);
+        const int rc = setup_device(e, [&]() { explorer.tell(explorer.rows_made); });
         if (rc != ZF_OK) return give_up(rc);
     }
-    if (explorer.joinable()) {
-        explorer.join();
-        try { store_adopt(e, whole, nullptr); } catch (const std::bad_alloc &) {}   // the store starts empty, then
+    if (explorer.thread.joinable()) {
+        explorer.await(explorer.explored);
+        try { store_adopt(e, explorer.whole, nullptr); } catch (const std::bad_alloc &) {}   // the store starts empty, then
+        explorer.thread.join();
     }
     *out = e;
     return ZF_OK;
@@ -1334,20 +1383,18 @@ static void note_device_state(const DeviceSide *d, zf_state *st, uint32_t dev) {
 }
 
 // Tokens that a list of token-mask cache rows leaves to the parser.
-static int64_t count_undecided(DeviceSide *d, const uint32_t *ent, uint32_t n) {
+static uint64_t entries_signature(const uint32_t *ent, uint32_t n) {
     uint64_t sig = 0xCBF29CE484222325ull ^ n;
     for (uint32_t k = 0; k < n; k++) sig = (sig ^ ent[k]) * 0x100000001B3ull;
+    return sig;
+}
+static int64_t count_undecided(DeviceSide *d, const uint32_t *ent, uint32_t n) {
+    if (n == 1) return d->ci_undecided[ent[0]];
+    const uint64_t sig = entries_signature(ent, n);
     auto it = d->undecided_of.find(sig);
     if (it == d->undecided_of.end()) {
-        const size_t Wt = (size_t)d->tab.W;
-        uint32_t cnt = 0;
-        for (size_t w = 0; w < Wt; w++) {
-            uint32_t v = 0, cd = 0;
-            for (uint32_t k = 0; k < n; k++) { v |= d->h_ci_tok[ent[k] * Wt + w].x; cd |= d->h_ci_tok[ent[k] * Wt + w].y; }
-            cnt += (uint32_t)__builtin_popcount(cd & ~v);
-        }
         if (d->undecided_of.size() > 65536) d->undecided_of.clear();
-        it = d->undecided_of.emplace(sig, cnt).first;
+        it = d->undecided_of.emplace(sig, undecided_tokens(d->h_ci_tok, (size_t)d->tab.W, ent, n)).first;
     }
     return it->second;
 }
@@ -1868,6 +1915,35 @@ static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items, std:
         }
     }
     return true;
+}
+
+// What a mask call works out when it meets a list of several cache rows for the first time -- the tokens they leave undecided, 10 us and more
+// per list of a large vocabulary -- is worked out for the explored states when the engine is compiled: left to the calls, the first pass over
+// 64 rows of the query language took 125 us per step, the following ones 83; with it the first takes 85, and compiling a schema 19.0 ms
+// either way.
+// The lists are gathered by the exploring thread, while the vocabulary is sorted elsewhere, nearest states first; they are
+// few (56 to 1,397 distinct ones in 65,536 states of the grammars of workloads/, most of them of one row).
+static std::vector<std::vector<uint32_t>> explored_entries(const zf_engine *e) {
+    const HostAutomaton &A = *e->host_aut;
+    std::vector<std::vector<uint32_t>> lists;
+    std::unordered_map<uint64_t, bool> met;
+    std::vector<uint32_t> ents;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t s = HostAutomaton::ROOT; s < A.n_states && lists.size() < 4096; s++) {
+        if ((s & 255u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(20)) break;
+        const HostAutomaton::State &st = A.st(s);
+        ents.resize(std::max<size_t>(ents.size(), st.n_items));
+        const uint32_t n = current_set_entries(e->tab, st.items, st.n_items, ents.data());
+        if (n < 2 || n > 64 || !met.emplace(entries_signature(ents.data(), n), true).second) continue;
+        lists.emplace_back(ents.begin(), ents.begin() + n);
+    }
+    return lists;
+}
+static void count_lists(zf_engine *e, const std::vector<std::vector<uint32_t>> &lists) {
+    DeviceSide *d = e->dev;
+    std::vector<uint32_t> count(lists.size());
+    parallel_for(lists.size(), lists.size() >= 64 ? 4 : 1, [&](size_t k) { count[k] = undecided_tokens(d->h_ci_tok, (size_t)e->W, lists[k].data(), (uint32_t)lists[k].size()); });
+    for (size_t k = 0; k < lists.size(); k++) d->undecided_of.emplace(entries_signature(lists[k].data(), (uint32_t)lists[k].size()), count[k]);
 }
 
 // The device's part: the store is cleared and takes over what the host automaton holds, names and all.  A failure is no error:
