@@ -302,7 +302,7 @@ int setup_device(zf_engine *e, F rows_made) {            // rows_made: called wh
     if (e->store_on) {
         // The mask kernel over the persistent automaton works in token order: every token's string as byte classes, and the
         // rows of the token-mask cache with one bit per token (bit v = the rank-ordered row's bit for token v's string).
-        const size_t V = (size_t)e->V, W = (size_t)e->W, n_rows = tr.Wr > 0 ? tr.ci_valid.size() / (size_t)tr.Wr : 0;
+        const size_t V = (size_t)e->V, W = (size_t)e->W, n_rows = (size_t)(t.Q + t.N);   // a row each, of a vocabulary without a string too: the kernels read them
         std::vector<Str16> tok16(std::max<size_t>(V, 1), Str16{{TOK_END, 0, 0, 0}});
         for (size_t v = 0; v < V; v++) {
             const uint32_t r = tr.rank_of[v];

@@ -1141,3 +1141,29 @@ def test_advance_goes_on_while_the_automaton_is_explored_again(torch_cuda, oracl
     d_mask = torch.empty((1, eng.W), dtype=torch.int32, device="cuda")
     zf.compute_mask(eng, [row], d_mask)
     assert np.array_equal(d_mask.cpu().numpy().view(np.uint32)[0], so.mask(off, data))
+
+
+@pytest.mark.parametrize("V", [1, 33, 5000])
+def test_vocabulary_of_empty_tokens(V, torch_cuda):
+    """No string at all: every mask word is zero and every logit -inf, through the waiting, the asynchronous and the allocation-free call, on every path."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    for kw in ({}, {"state_cache_entries": -1, "precompute_states": -1}, {"walk_mode": 0}, {"walk_mode": 1}, {"pruning": False}):
+        eng = zf.Engine(grammars.json_grammar(), [b""] * V, device=0, **kw)
+        rows = []
+        for p in (b"", b"[", b'{"k":"', b"[1,", b'[[{"a":[', b"[]"):
+            rows.append(eng.new_state())
+            if p:
+                rows[-1].advance_bytes(p)
+        d_mask = torch.empty((len(rows), eng.W), dtype=torch.int32, device="cuda")
+        logits = torch.ones((len(rows), V), device="cuda")
+        for call in (zf.compute_mask, zf.compute_mask_noalloc, zf.compute_mask_async):
+            d_mask.fill_(0x5A5A5A5A)
+            call(eng, rows, d_mask)
+            zf.mask_wait(eng)
+            torch.cuda.synchronize()
+            assert not d_mask.any(), (kw, call)
+        out = zf.compute_mask_apply_async(eng, rows, d_mask, logits, out=torch.empty_like(logits))
+        zf.mask_wait(eng)
+        torch.cuda.synchronize()
+        assert not d_mask.any() and bool((out == float("-inf")).all()), kw
