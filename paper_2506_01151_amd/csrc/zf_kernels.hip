@@ -44,9 +44,18 @@ template <bool ALIGNED, typename ElemT> struct ApplyPiece { typedef u32x4 type; 
 template <> struct ApplyPiece<false, uint32_t> { typedef u32x4 __attribute__((aligned(4))) type; };
 template <> struct ApplyPiece<false, uint16_t> { typedef u32x4 __attribute__((aligned(2))) type; };
 //   SKIP: a piece none of whose tokens is allowed is not read.  The mask words have to be in hand before the loads then, a trip
-// to L2 that a large tensor hides: 1,024 x 128,256 bf16 took 84.7 us without, 82 with dense masks, 75 with one word in 16
-// allowing anything, 44 with next to nothing allowed; 64 x 152,064 fp32 13.5 without, 14.5 / 11.9 / 8.4 with, and a dense mask is the
-// common one (a string, a number or an identifier goes on), so tensors of less than 100 MB of traffic are read whole.
+// to L2 that a large tensor hides.  Whether it gains is the masks' doing, so it is done where it costs 2 % at most when every piece is
+// wanted (a string, a number or an identifier goes on: a dense mask is the common one).  Launches back to back over rotating rows, in us,
+// masks: half of the tokens at random / rows of share rand ** 3 / one token in a hundred / next to none,
+//                          three pieces, skipping        two, reading all      eight, reading all
+//   1,024 x 128,256 bf16   83.9 / 76.4 / 68.6 / 59.7     86.0 / 85.7 / 85.9    94.7
+//     512 x 128,256 bf16   44.3 / 40.4 / 36.6 / 31.2     44.9 / 45.3 / 45.0    49.3
+//     256 x 128,256 bf16   24.1 / 22.4 / 20.4 / 16.5     24.5 / 24.4 / 24.4    23.9
+//     200 x 128,256 bf16   20.2 / 18.5 / 17.1 / 13.2     20.1 / 19.9 / 19.9    20.9
+//     128 x 128,256 fp32   23.6 / 21.3 / 19.5 / 13.7     24.0 / 24.0 / 24.0    23.3
+// (two pieces, skipping: 85.9 / 79.6 and 24.3 / 22.9 in the first and third line).  Rows at any alignment take two: 1,024 x 40,037 bf16
+// 32.0 / 30.0 / 28.2 / 20.2 skipping, 32.3 / 30.1 / 26.4 / 20.5 with three, 30.9 / 30.5 reading all.  At 64 x 152,064 fp32 skipping cost a
+// dense mask 8 % (14.5 for 13.5), so tensors of less than 100 MB of traffic are read whole.
 template <int EPV /* elements per 16 bytes */, int U, bool ALIGNED, bool SKIP, typename ElemT>
 __global__ __launch_bounds__(256) void apply_mask_vec_kernel(const ElemT *in, ElemT *out, int64_t stride, int V, int W, int batch,
                                                              const uint32_t *__restrict__ mask, ElemT neg_inf) {
@@ -132,7 +141,7 @@ static void launch_apply_vec(const ElemT *in, ElemT *out, int64_t stride, int V,
     auto blocks = [&](int u) { return (uint32_t)std::max<uint64_t>(std::max<uint64_t>((total + 256ull * u - 1) / (256ull * u), (tail + 255) / 256), 1); };
     // measured on [16..1024] x 128,256 bf16 / fp32 and [64] x 152,064 fp32 (kernel-trace durations): the differences are a few per cent
 #define ZF_APPLY(u, skip) hipLaunchKernelGGL((apply_mask_vec_kernel<EPV, u, ALIGNED, skip, ElemT>), dim3(blocks(u)), dim3(256), 0, s, in, out, stride, V, W, batch, mask, ninf)
-    if (total >= 3ull << 20) ZF_APPLY(2, true);
+    if (total >= 3ull << 20) ZF_APPLY((ALIGNED ? 3 : 2), true);      // 100 MB read and written: see SKIP above
     else if (total >= 1ull << 20) ZF_APPLY(8, false);
     else if (total >= 1ull << 18) ZF_APPLY(4, false);
     else ZF_APPLY(1, false);

@@ -1167,3 +1167,29 @@ def test_vocabulary_of_empty_tokens(V, torch_cuda):
         zf.mask_wait(eng)
         torch.cuda.synchronize()
         assert not d_mask.any() and bool((out == float("-inf")).all()), kw
+
+
+@pytest.mark.parametrize("V,B,pad,dtype", [(40000, 640, 0, "bf16"), (40003, 641, 61, "bf16"), (128256, 197, 0, "bf16"), (40000, 321, 64, "f32"), (12582, 1001, 2, "f32")])
+def test_apply_mask_large_tensors_skip_empty_pieces(V, B, pad, dtype, torch_cuda, oracle_lib):
+    """Aligned rows beyond the size from which pieces that nothing is allowed of are not read: whole words and whole rows empty and full, in
+    place and into another tensor, every bit against the definition."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    from oracle.frontend import apply_mask as oracle_apply
+    f, i, u = (torch.float32, torch.int32, np.uint32) if dtype == "f32" else (torch.bfloat16, torch.int16, np.uint16)
+    assert (V // (4 if dtype == "f32" else 8)) * B >= 3 << 20 and (V + pad) * (4 if dtype == "f32" else 2) % 16 == 0
+    eng = zf.Engine(grammars.parens_grammar(), [b"("] * V, device=0)
+    rng = np.random.default_rng(V + B)
+    mask = rng.integers(0, 2**32, size=(B, eng.W), dtype=np.uint32) & rng.integers(0, 2**32, size=(B, eng.W), dtype=np.uint32)
+    mask[rng.random((B, eng.W)) < 0.4] = 0
+    mask[0] = 0
+    mask[-1] = 0xFFFFFFFF
+    mask[B // 2] = 0
+    bits = rng.integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
+    want = oracle_apply(bits, mask)
+    x = torch.zeros((B, V + pad), dtype=f, device="cuda")[:, :V]
+    x.view(i).copy_(torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)))
+    m = torch.from_numpy(mask.view(np.int32)).cuda()
+    out = torch.empty_strided(x.shape, x.stride(), dtype=f, device="cuda")
+    for y in (zf.apply_mask(eng, x, m, out=out), zf.apply_mask(eng, x, m)):
+        assert y.contiguous().view(i).cpu().numpy().view(u).tobytes() == want.tobytes()
