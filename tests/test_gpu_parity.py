@@ -1193,3 +1193,120 @@ def test_apply_mask_large_tensors_skip_empty_pieces(V, B, pad, dtype, torch_cuda
     out = torch.empty_strided(x.shape, x.stride(), dtype=f, device="cuda")
     for y in (zf.apply_mask(eng, x, m, out=out), zf.apply_mask(eng, x, m)):
         assert y.contiguous().view(i).cpu().numpy().view(u).tobytes() == want.tobytes()
+
+
+def _many_states():
+    """A grammar of 2,600 words told apart by their first four bytes, in twenty terminals: as many states of one item each; what may follow is the word's fifth byte."""
+    from workloads.grammar import Grammar, Rx
+    g = Grammar(name="words")
+    g.set_start("S")
+    stems = [b"%04x" % (7 * k) for k in range(2600)]
+    ends = [bytes([ord("g") + k % 20]) for k in range(2600)]
+    words = [s + e + s for s, e in zip(stems, ends)]         # (the stem again: no two words share a state of their terminal's machine)
+    g.alts("S", *[[Rx(b"(" + b"|".join(words[j::20]) + b")")] for j in range(20)])
+    toks = [bytes([c]) for c in range(128)] + [b"g" * 2, b"z", b"h", b""] + [b"%xk" % k for k in range(16)]
+    want = np.zeros((2600, (len(toks) + 31) // 32), dtype=np.uint32)
+    for k, e in enumerate(ends):
+        for t, tok in enumerate(toks):
+            if tok == e:
+                want[k, t >> 5] |= np.uint32(1 << (t & 31))
+    return g, toks, stems, want
+
+
+def test_calls_of_many_groups(torch_cuda, oracle_lib):
+    """Calls of hundreds and thousands of groups, whose records travel in device memory: through the call that allocates nothing (records in the static
+    array) up to the call whose records no longer fit its staging room, which goes to the per-block automaton; and with the state cache on, where some
+    groups' masks are in the pool and others' are not."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks, stems, want = _many_states()
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    for k in (0, 1, 19, 2599):                               # the table above, as the oracle sees it
+        so = orc.new_state()
+        assert so.feed_bytes(stems[k])
+        assert np.array_equal(so.mask(off, data), want[k])
+
+    def rows_of(eng, ks):
+        rows = []
+        for k in ks:
+            rows.append(eng.new_state())
+            rows[-1].advance_bytes(stems[k])
+        return rows
+
+    def check(eng, call, rows, ks, turn):
+        d_mask = torch.full((len(ks), eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        call(eng, rows, d_mask)
+        if call is zf.compute_mask_async:
+            zf.mask_wait(eng)
+        got = d_mask.cpu().numpy().view(np.uint32)
+        assert np.array_equal(got, want[ks]), (len(ks), turn, np.flatnonzero((got != want[ks]).any(axis=1))[:8])
+        return eng.mask_report()
+
+    for precompute in (0, -1):                               # explored to its end: look-ups; not explored: first visits, then look-ups
+        eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, precompute_states=precompute)
+        rows = rows_of(eng, range(2600))
+        for n in (65, 300, 2000, 2600, 300):
+            ks = [(3 * k + n) % 2600 for k in range(n)] if n < 2600 else list(range(2600))
+            for turn in range(2):
+                r = check(eng, zf.compute_mask_noalloc, [rows[k] for k in ks], ks, turn)
+                assert r.chart_bytes <= 256 << 10, (n, turn, r.chart_bytes)   # 2,600 groups' records and blocks take 280 KiB: the packed charts went instead
+                if precompute == 0 or turn == 1:
+                    assert r.parser_steps == 0, (n, turn, r.parser_steps)
+    eng = zf.Engine(g, toks, device=0)                       # the state cache at its default: 2,048 rows
+    rows = rows_of(eng, range(2600))
+    seen = set()
+    for call in (zf.compute_mask, zf.compute_mask_async):
+        for lo, hi in ((0, 100), (50, 250), (0, 300), (299, 301), (200, 1000)):
+            ks = list(range(lo, hi))
+            r = check(eng, call, [rows[k] for k in ks], ks, 0)
+            assert r.cache_hits == len(seen & set(ks)) and r.cache_misses == len(ks) - r.cache_hits, (lo, hi, r.cache_hits)
+            seen |= set(ks)
+
+
+def test_state_cache_when_the_host_automaton_starts_over(torch_cuda, oracle_lib):
+    """The cached masks go by the host automaton's names: when that fills up and starts over -- here a row of another query is fed sixty thousand
+    brackets at a time until it does -- the same names stand for other states, and no row is served an old mask."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g = grammars.json_grammar()
+    toks = [bytes([c]) for c in range(128)] + [b"tr", b"true", b'":', b"[[", b"}]", b"],"]
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, precompute_states=-1)
+    prefixes = [b"[", b'{"k":"', b"[1,", b"tr", b'["\\u00', b"-1.5e", b'{"a"', b"[[[", b'{"a":1', b'[{"b":[']
+    wants = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        wants.append(so.mask(off, data))
+    order = list(range(len(prefixes)))
+    d_mask = torch.empty((len(prefixes), eng.W), dtype=torch.int32, device="cuda")
+
+    def masks(rows, ks):
+        d_mask.fill_(0x5A5A5A5A)
+        zf.compute_mask(eng, rows, d_mask)
+        assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), np.stack([wants[k] for k in ks]))
+        r = eng.mask_report()
+        return r.cache_hits, r.cache_misses
+
+    def rows_at(ks):
+        rows = []
+        for k in ks:
+            rows.append(eng.new_state())
+            rows[-1].advance_bytes(prefixes[k])
+        return rows
+
+    old = rows_at(order)
+    assert masks(old, order) == (0, len(order)) and masks(old, order) == (len(order), 0)
+    fed = 0
+    for k in range(19):                                      # 1,048,576 states are its bound, less the largest chart it takes in
+        row = eng.new_state()
+        row.advance_bytes(b'{"a":' * k + b"[" * 60000)
+        fed += 60000
+        del row
+    assert fed > 1 << 20
+    back = order[::-1]                                       # other states under the first names of the new automaton
+    new = rows_at(back)
+    assert masks(new, back) == (0, len(order)) and masks(new, back) == (len(order), 0)
+    assert sum(masks(old, order)) == len(order)              # (these come back in through their charts, some under names of their own)
