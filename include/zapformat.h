@@ -72,8 +72,9 @@ typedef struct {
     int32_t chunk_strings; /* vocabulary strings walked by one lane: 8, 16 or 32; 0 = default */
     int32_t fallback_item_cap; /* item budget of a fallback wavefront (global memory), 0 = default
                                   (65536); tests set it low to provoke ZF_ERR_OVERFLOW */
-    int32_t state_cache_entries; /* state cache (Section 5.2): finished mask rows kept on the device,
-                                  keyed by the row's pruned chart; 0 = default (2048 rows), -1 = off */
+    int32_t state_cache_entries; /* state cache (Section 5.2): finished mask rows kept on the device, keyed by the state of the
+                                  host automaton that the row stands in (walk_mode 2), by the row's pruned chart
+                                  otherwise; 0 = default (2048 rows), -1 = off */
     int32_t disable_token_mask_cache; /* 1 = every token goes through the parser walk (Section 4.3
                                   optimisation off); masks are identical either way */
     int32_t walk_mode;     /* which mask kernel checks the tokens the token-mask cache leaves undecided (masks are identical):

@@ -1822,7 +1822,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     a.complete = wait ? 1 : 0;
     a.report_size = n_imp ? 1 : 0;
     const bool prof = d->profiling;
-    d->report.chart_bytes = (int64_t)(total + (big ? 0 : sizeof(StoreGroup) * ng));
+    d->report.chart_bytes = (int64_t)(total + (big ? 0 : (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng));
     d->report.cache_rows = (int32_t)n_cache_rows;
     d->report.main_ms = d->report.fallback_ms = d->report.permute_ms = 0.f;
     d->report.overflow_chunks = d->report.walk_chunks = d->report.parser_steps = 0;

@@ -4,10 +4,10 @@
 // Mask path.  The distinct vocabulary strings are numbered in sorted order (their rank); verdicts
 // are first produced in rank order.  The context-independent token-mask cache (Section 4.3) settles
 // most strings from the terminals of the row's current Earley set alone; the strings it leaves
-// undecided need the parser.  Two kernels can do that part (zf_options.walk_mode), both exact:
-// the mask automaton (zf_mask_automaton.hip, default) and the trie walk (zf_mask_walk.hip, which
+// undecided need the parser.  Two kernels do that part this way (zf_options.walk_mode 0 and 1), both exact:
+// the mask automaton (zf_mask_automaton.hip) and the trie walk (zf_mask_walk.hip, which
 // also holds finish_kernel: the exact fallback pass of both, and the permutation of the verdicts
-// into token order).
+// into token order).  With walk_mode 2 mask_store_kernel and mask_look_kernel work in token order from the start.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include "zf_kernel_common.h"

@@ -10,7 +10,7 @@
 // (arguments, cache words and the state's table row, strings, about 1 us each) and the instructions between them, which one
 // wavefront issues at 4 to 5 cycles apiece.  mask_store_kernel, which this one was split from, carries both halves: 200 scalar registers
 // put by in lanes of vector ones for the byte step's sake, 2.4 us from the group's record to its last request, 54 instructions
-// per byte of a walk.  Here the record is a third shorter, the cache rows are read by uniform addresses, the table row is on its
+// per byte of a walk.  Here the record is a quarter shorter, the cache rows are read by uniform addresses, the table row is on its
 // way before anything else, the logits are left to a launch of their own (their requests and stores lengthened every wavefront: 16 x
 // 128,256 bf16 260 us per 16 steps with them in here, 237 without, and 27.4 for 29.6 us per step synchronised), undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
 // for, and a byte of the walk takes about 20 instructions: a lane that is done leaves the loop.
