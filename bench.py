@@ -3,10 +3,10 @@
 
 A "step" is one pass of the whole hot path over one batch: advance every row by its next token
 (host Earley + ZapFormat compaction), compute_mask and apply_mask on that step's logits -- enqueued
-with one call, zf_compute_mask_apply_async: the fed bytes go up in the kernel's argument block, the
-mask kernel over the persistent automaton writes the mask rows in token order and masks the logits
-of the tokens whose mask words it has just written -- and mask_wait (deferred error check).  The
-same steps through the two separate calls (two kernels) are reported beside it (`two_calls`).  The token
+with one call, zf_compute_mask_apply_async: the rows' states go up in the kernel's argument block, the
+mask kernel over the persistent automaton writes the mask rows in token order, a second launch masks the
+logits (a call that meets states for the first time masks up to 16 MB of them in the mask kernel) --
+and mask_wait (deferred error check).  The same steps through the two separate calls are reported beside it (`two_calls`).  The token
 trajectory is fixed beforehand (tests/golden/trajectory_cfgN.txt, sampled by the CPU oracle), so
 nothing is copied back to the host inside the timed region.  Inputs are seeded and synthetic.
 
@@ -35,17 +35,17 @@ HBM_PEAK_GBS = 8000.0
 ISSUE_PEAK_GINST = 256 * 4 * 2.4
 KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_look_kernel / mask_store_kernel"}
 
-# HBM traffic of one launch of the default mask kernel on the default workload, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs
-# scaled by a plain copy of known size (profiles/mask_store_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same runs.  The
-# figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 16006507, "apply_bytes_per_launch": 8501824, "instructions_per_launch": 5960564,
-                    "kernel_sources_sha256": "17eae1b830e6e8492fd31c03d3d05e3300788c4e57feb5a5198f7bed1dc8a4c0"}
+# HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one) and of apply_mask_vec_kernel, from rocprofv3
+# FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
+# pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 5604889, "apply_bytes_per_launch": 8493685, "instructions_per_launch": 3247068,
+                    "kernel_sources_sha256": "c7e3c216ec9e2b35db7009f4fc77cf1040118e1ac427f92246bbf278dac3eb25"}
 
 
 def kernel_sources_digest():
     import hashlib
     h = hashlib.sha256()
-    for name in ("zf_kernels.hip", "zf_mask_store.hip", "zf_aut_step.h", "zf_mask_automaton.hip", "zf_mask_walk.hip", "zf_kernel_common.h", "zf_launch.h", "zf_device.h",
+    for name in ("zf_kernels.hip", "zf_mask_store.hip", "zf_mask_look.hip", "zf_aut_step.h", "zf_mask_automaton.hip", "zf_mask_walk.hip", "zf_kernel_common.h", "zf_launch.h", "zf_device.h",
                  "zf_api.cpp"):                                # the host chooses the launch shape, which decides what the XCDs' L2s share
         with open(os.path.join(ROOT, "paper_2506_01151_amd", "csrc", name), "rb") as f:
             h.update(f.read())
@@ -290,7 +290,8 @@ def main():
                     help="only run apply_mask with an all-ones mask on a [1024, V] tensor three times: a plain copy of known "
                          "size, used to scale rocprofv3's FETCH_SIZE / WRITE_SIZE counters")
     ap.add_argument("--apply-sweep-only", action="store_true", help="only the apply_mask sweeps (for a kernel trace of them)")
-    ap.add_argument("--two-calls", action="store_true", help="with --headline-only: the steps through zf_compute_mask_async + zf_apply_mask (two kernels) instead of the one call")
+    ap.add_argument("--two-calls", action="store_true", help="with --headline-only: the steps through zf_compute_mask_async + zf_apply_mask instead of the one call")
+    ap.add_argument("--no-exploration", action="store_true", help="with --headline-only: an engine compiled with precompute_states = -1 (first visits go through mask_store_kernel)")
     args = ap.parse_args()
     if args.gpus != 1:
         print("this benchmark runs on one GPU only: rows and vocabulary ranges would shard without any exchange, "
@@ -307,7 +308,8 @@ def main():
     B, K, Wm = cfg.batch, args.steps, args.warmup
     toks = cfg.vocab()
     # headline engine: state cache off, so every row of every step goes through the mask kernels
-    eng = zf.Engine(cfg.grammar(), toks, device=0, pruning=bool(args.pruning), state_cache_entries=-1, walk_mode=args.walk_mode)
+    eng = zf.Engine(cfg.grammar(), toks, device=0, pruning=bool(args.pruning), state_cache_entries=-1, walk_mode=args.walk_mode,
+                    precompute_states=-1 if args.headline_only and args.no_exploration else 0)
     V, W = eng.V, eng.W
     traj = load_trajectory(args.config, B, Wm + K)
     traj_src = "oracle-sampled file"
@@ -392,14 +394,14 @@ def main():
     main_ms = statistics.fmean(kern["main"])
     apply_ms = statistics.fmean(two_prof["kern"]["apply"])
     apply_bytes = 2 * B * V * esz + B * W * 4
-    # Algorithmic bytes of one launch of the default kernel (mask + logit masking in one): the token-mask-cache words merged (two
-    # bitsets of W words per selected cache row), the mask words written, 17 bytes per undecided token (its first 16 byte
-    # classes and its length), the logits read and written, and the upload.  The other mask kernels work in string-rank order
-    # (Wr words per row, 24 bytes per undecided string) and leave the logits to apply_mask.
+    # Algorithmic bytes of one launch of the default kernel, once per state that rows of the call stand in: the token-mask-cache words
+    # merged (two bitsets of W words per selected cache row), the mask words written, 16 bytes per undecided token (its first fifteen
+    # byte classes and a mark), and the upload.  The other mask kernels work in string-rank order (Wr words per row,
+    # 24 bytes per undecided string).  All of them leave the logits to apply_mask.
     Wr = (info.n_strings + 31) // 32
     queued, crows = rep["queued"], rep["cache_rows"]
     if args.walk_mode == 2 and args.pruning:
-        mask_bytes = int(crows / K * W * 8 + B * W * 4 + queued / K * 17 + rep["upload_bytes"] / K) + 2 * B * V * esz
+        mask_bytes = int(crows / K * W * 8 + B * W * 4 + queued / K * 16 + rep["upload_bytes"] / K)
     elif args.walk_mode != 1:
         mask_bytes = int(crows / K * Wr * 8 + B * Wr * 4 + queued / K * 24 + rep["upload_bytes"] / K)
     else:
@@ -427,9 +429,9 @@ def main():
         "p99_mask_apply_latency_us": pct(lat, 0.99) * 1e6, "max_mask_apply_latency_us": max(lat) * 1e6,
         "mean_advance_us_per_step": statistics.fmean(adv) * 1e6,
         "pipelined_steps": {"ms_per_step": piped["total"] / K * 1e3, "value": B * V * K / piped["total"],
-                            "note": "the same steps without the stream synchronisation: a step ends when the call's status, which the kernel writes after its "
-                                    "last masked logit, has reached the host (zf_mask_wait); what is left out is the 5 us between that and the "
-                                    "stream's own completion signal, which a decode loop whose sampler runs on the same stream does not wait for"},
+                            "note": "the same steps without the stream synchronisation: a step ends when the mask kernel's status has reached the host "
+                                    "(zf_mask_wait); what is left out is the end of the logits' masking, which runs behind the mask kernel while the next step "
+                                    "is sent, and the stream's own completion signal: a decode loop whose sampler runs on the same stream does not wait for either"},
         "warm_automaton": {"ms_per_step": warm["total"] / K * 1e3, "value": B * V * K / warm["total"], "p50_mask_apply_latency_us": pct(warm["lat"], 0.5) * 1e6,
                            "note": "the same steps once more without clearing the persistent automaton: every transition is a look-up"},
         "kernel_ms": {k: statistics.fmean(v) for k, v in kern.items() if v},
@@ -437,7 +439,7 @@ def main():
         "kernel_ms_max": {k: max(v) for k, v in kern.items() if v},
         "two_calls": {"value": B * V * K / two["total"], "ms_per_step": two["total"] / K * 1e3, "p50_mask_apply_latency_us": pct(two["lat"], 0.5) * 1e6,
                       "kernel_ms": {k: statistics.fmean(v) for k, v in two_prof["kern"].items() if v},
-                      "note": "the same steps through zf_compute_mask_async + zf_apply_mask: the mask kernel, then apply_mask_vec_kernel"},
+                      "note": "the same steps through zf_compute_mask_async + zf_apply_mask: the mask kernel, then apply_mask_vec_kernel (the one call enqueues the same two where every state's vocabulary has been walked before)"},
         "overflow_chunks_per_step": rep["overflow"] / K,
         ("undecided_tokens_per_step" if args.walk_mode == 2 and args.pruning else "undecided_strings_per_step") if args.walk_mode != 1 else "walk_chunks_per_step": queued / K,
         "undecided_per_s": queued / max(sum(kern["main"]) * 1e-3, 1e-12),
@@ -454,10 +456,10 @@ def main():
         "roofline": {"bound": "hbm", "kernel": kname, "achieved": mask_bytes / (main_ms * 1e-3) / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": mask_bytes / (main_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "traffic": MEASURED_TRAFFIC["bytes_per_launch"] if traffic_ok else None, "algorithmic_bytes": mask_bytes,
-                     "note": "one launch = the mask of every row and the masking of its logits; integer work (a table walk per undecided token), "
-                             "bounded by the chain of dependent memory round trips of a wavefront (row record, cache words, strings, table "
-                             "entries, logits: 0.3 to 1.5 us each) and by the Earley steps of launches that meet new states, far below the HBM "
-                             "roof; the event pair also spans the dispatch gap before the kernel"},
+                     "note": "one launch = the mask of every row, worked out once per state that rows stand in; integer work (a table walk per undecided token), "
+                             "bounded by the chain of dependent memory round trips of a wavefront (the group's record, cache words, strings, table "
+                             "entries: about 1 us each), far below the HBM roof; the event pair also spans the dispatch gap before the kernel; "
+                             "the logits' masking is a launch of its own, see roofline_apply_mask"},
         "roofline_issue": {"bound": "alu", "kernel": kname, "unit": "G wavefront instructions/s", "peak": ISSUE_PEAK_GINST, "instructions": insts,
                            "achieved": insts / (main_ms * 1e-3) / 1e9 if insts else None,
                            "frac": insts / (main_ms * 1e-3) / 1e9 / ISSUE_PEAK_GINST if insts else None,
