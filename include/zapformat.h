@@ -186,7 +186,9 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states /* host array */, int3
  * not overlap from several host threads.
  *   zf_mask_wait returns once the status of the calls in flight is final (a block of their last kernel writes
  * it to pinned host memory, which the call polls; when the fallback pass had work, whose waits can fail, it is
- * the block that finishes last; bounded: after two seconds the stream is synchronised instead).  It does NOT
+ * the block that finishes last; bounded: after two seconds the stream is synchronised instead).  A call of look-ups only -- every
+ * transition it can meet is in the persistent automaton for certain -- cannot fail: its status is final when it is enqueued, and
+ * zf_mask_wait does not wait for it (at most 4 such calls are ahead of the host; the next one waits for the oldest).  It does NOT
  * wait for work the caller queued behind them (zf_apply_mask, a sampler), and the mask tensor is to be
  * consumed in stream order: queue its readers on hip_stream, or synchronise the stream before reading it
  * from the host or from another stream (not so after zf_compute_mask, the waiting call).  With no call

@@ -1051,6 +1051,48 @@ def test_waiting_calls_on_two_streams(noalloc, precompute, torch_cuda, oracle_li
     assert noalloc or hits >= 9 * n, hits
 
 
+@pytest.mark.parametrize("B,dtype", [(3, "bf16"), (64, "f32"), (300, "bf16")])
+def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
+    """Calls of look-ups only, one behind the other with nothing synchronised between them: more of them than there are slots, records and row numbers
+    in the slots' own memory (300 rows), a change of streams with calls still at work, the store filled anew behind them, and a waiting call.
+    Every step's mask and masked logits are the oracle's."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    cfg = configs.CONFIGS[3]
+    g, toks, V, steps = cfg.grammar(), cfg.vocab(8192), 8192, 18
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)      # no recursion: the automaton is there whole, every call is of look-ups only
+    run = OracleRun(oracle_lib.Oracle(g), toks, [stream(31, f"let-go[{k}]") for k in range(8)])
+    rows = zf.StateBatch([eng.new_state() for _ in range(B)])
+    u, i, f = (np.uint32, torch.int32, torch.float32) if dtype == "f32" else (np.uint16, torch.int16, torch.bfloat16)
+    rng = np.random.default_rng(B)
+    bits = rng.integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
+    logits = torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)).cuda().view(f)
+    masks = torch.full((steps, B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    outs = torch.zeros((steps, B, V), dtype=f, device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    want = []
+    for step in range(steps):
+        want.append(run.masks())
+        ids = run.step(want[-1])
+        if step in (9, 14):
+            eng.clear_state_cache()
+        with torch.cuda.stream(streams[step // 6 & 1]):
+            if step == 16:
+                zf.compute_mask(eng, rows, masks[step])
+                zf.apply_mask(eng, logits, masks[step], out=outs[step])
+            else:
+                zf.compute_mask_apply_async(eng, rows, masks[step], logits, out=outs[step])
+                zf.mask_wait(eng)
+        rows.advance([ids[b % 8] for b in range(B)])
+    torch.cuda.synchronize()
+    for step in range(steps):
+        wanted = np.stack([want[step][b % 8] for b in range(B)])
+        assert np.array_equal(masks[step].cpu().numpy().view(np.uint32), wanted), step
+        assert outs[step].view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), step
+
+
 def test_per_block_automaton_sets_that_outgrow_the_lanes(torch_cuda, oracle_lib):
     """Charts whose sets hold ten items, and a byte that leaves eighty: more than the build for a dozen items holds.  The call that allocates
     nothing does not take that build (nothing is left to the fallback pass); another call leaves the strings behind the byte to that pass once, and
