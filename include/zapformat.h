@@ -199,9 +199,10 @@ int zf_mask_wait(zf_engine *e, void *hip_stream);
 /* compute_mask followed by apply_mask on the same rows (Sections 4.1 and 3.3: the verdicts of a step are there to mask that
  * step's logits), enqueued together: the result in d_mask and d_out is exactly what zf_compute_mask_async followed by
  * zf_apply_mask(e, d_logits, d_out, dtype, batch, row_stride_elems, d_mask, hip_stream) gives, and zf_mask_wait reports as
- * for that pair.  With the persistent automaton as the mask kernel, a call that meets states for the first time masks up to 16 MB of
- * logit traffic in the same kernel (a wavefront masks the logits of the tokens whose mask words it has just written), provided the
- * pointers are multiples of a logit; in every other case the call enqueues the two kernels one after the other.  d_out may
+ * for that pair.  With the persistent automaton as the mask kernel the same kernel masks the logits, provided the pointers are
+ * multiples of a logit: a call of look-ups only with wavefronts of their own, which read them while others work the masks out; a call that
+ * meets states for the first time up to 16 MB of logit traffic (a wavefront masks the logits of the tokens whose mask words it has just
+ * written).  In every other case the call enqueues the two kernels one after the other.  d_out may
  * equal d_logits; dtype 0 = fp32, 1 = bf16. */
 int zf_compute_mask_apply_async(zf_engine *e, zf_state *const *states /* host array */, int32_t batch, uint32_t *d_mask,
                                 const void *d_logits, void *d_out, int32_t dtype, int64_t row_stride_elems, void *hip_stream);

@@ -86,6 +86,7 @@ struct DeviceSide {
     volatile uint64_t *h_store_status = nullptr;     // pinned, [N_SLOTS][STORE_STATUS_WORDS]: see STORE_ST_DONE
     unsigned long long *d_tickets = nullptr;         // [2][STORE_TICKETS]
     uint32_t ticket_set = 0;                         // the one the next kernel draws from
+    unsigned long long *d_tagged = nullptr; size_t tagged_cap = 0;   // LookArgs::tagged (words)
     StoreConst *d_konst = nullptr;
     uint32_t store_epoch = 1;                        // bumped whenever the store is cleared
     uint32_t store_states = 0, store_items = 0;      // as of the last call that reported back
@@ -108,6 +109,7 @@ struct DeviceSide {
         uint32_t host_epoch = 0;                     // epoch of the host automaton the names belong to
         int64_t undecided = 0;                       // for the report
         bool sure = false;                           // look-ups only, over transitions that have been reported to be there: nothing in the call can fail
+        uint32_t done_groups = 0;                    // words the call reports in (mask_look_kernel); 0: in STORE_ST_DONE
         bool lazy = false;                           // such a call that zf_mask_wait has let go of: its kernels may still be at work with the slot
     } rec[N_SLOTS];
     uint32_t n_lazy = 0;                             // how many slots are
@@ -204,6 +206,7 @@ int upload(DeviceSide *d, const std::vector<Tv> &v, const Tv **out, uint32_t *by
 void free_device(DeviceSide *d) {
     if (!d) return;
     (void)hipSetDevice(d->device);
+    if (d->d_tagged) (void)hipFree(d->d_tagged);
     for (void *p : d->slabs) (void)hipFree(p);
     if (d->d_chart) (void)hipFree(d->d_chart);
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) if (d->h_stage[k]) (void)hipHostFree(d->h_stage[k]);
@@ -576,6 +579,16 @@ static int await_status(Arrived arrived, Sync synchronise) {
     std::atomic_thread_fence(std::memory_order_acquire);
     return ZF_OK;
 }
+// The words in which a call through mask_look_kernel reports.
+static bool look_done(const volatile uint64_t *status, const DeviceSide::CallRecord &rec) {
+    for (uint32_t g = 0; g < rec.done_groups; g++) if ((uint32_t)(status[STORE_ST_ROW + g] >> 32) != rec.seq) return false;
+    return true;
+}
+static uint32_t look_failed(const volatile uint64_t *status, const DeviceSide::CallRecord &rec) {
+    uint32_t n = 0;
+    for (uint32_t g = 0; g < rec.done_groups; g++) n += (uint32_t)status[STORE_ST_ROW + g] & 0xFFFFFFu;
+    return n;
+}
 // A call that zf_mask_wait has let go of ends before its slot is used again, before a call of the engine comes on another stream and
 // before the store is touched by anything but a kernel behind it on its stream.  (After two seconds the device is synchronised: the
 // call's stream may be gone by then.)
@@ -584,11 +597,16 @@ static int settle_call(DeviceSide *d, uint32_t k) {
     if (!rec.lazy) return ZF_OK;
     rec.lazy = false; d->n_lazy--;
     const volatile uint64_t *out = d->h_store_status + k * STORE_STATUS_WORDS;
-    const int rc = await_status([&]() { return (uint32_t)(out[STORE_ST_DONE] >> 32) == rec.seq; }, [] { return hipDeviceSynchronize(); });
+    const int rc = await_status([&]() { return look_done(out, rec); }, [] { return hipDeviceSynchronize(); });
     if (rc != ZF_OK) return rc;
-    const uint32_t failed = (uint32_t)out[STORE_ST_DONE] & 0xFFFFFFu;
+    const uint32_t failed = look_failed(out, rec);
     if (failed) { d->late_failed += failed; d->store_dirty = true; }
     return ZF_OK;
+}
+static hipError_t next_call_number(DeviceSide *d, hipStream_t stream) {
+    if (++d->call_seq != 0) return hipSuccess;
+    d->call_seq = 1;                                      // numbers start over: no mask word lies about with one that comes again
+    return d->d_tagged ? launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(d->tagged_cap * 2), stream) : hipSuccess;
 }
 static int settle_calls(DeviceSide *d) {
     int rc = ZF_OK;
@@ -1284,7 +1302,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     }
     a.work = noalloc ? (uint4 *)(scr + scr_work) : d->d_work;
     a.host_status = d->h_status + 8 * slot;
-    if (++d->call_seq == 0) d->call_seq = 1;
+    HIP_TRY(next_call_number(d, stream));
     a.seq = d->call_seq;
     a.overflow_list = noalloc ? (uint4 *)(scr + scr_ovf) : d->d_overflow;
     a.overflow_cap = (uint32_t)(noalloc ? scr_ovf_cap : d->overflow_cap);
@@ -1697,7 +1715,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     // staging: [group records][blocks][members] (uploaded when big), then what the kernels read in place
     const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
     const size_t off_block = align16(big ? (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
-    const size_t up_bytes = align16(off_mem + 2 * (size_t)batch);
+    const size_t off_gof = align16(off_mem + 2 * (size_t)batch), up_bytes = align16(off_gof + (big && look && g_apply.out ? 2 * (size_t)batch : 0));
     const size_t off_spill = up_bytes, off_ent = align16(off_spill + (spill ? sizeof(StoreRow) * ng : 0)), off_pend = align16(off_ent + (spill ? 4 * n_spill_ent : 0));
     const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
     const size_t off_items = align16(off_so + 4 * n_off), off_imp = align16(off_items + sizeof(Item) * n_items);
@@ -1725,9 +1743,34 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const uint32_t lds = store_lds_bytes(d->tab, d->mode, scratch);
     if (lds > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
     int logit_bytes = 0;                                  // of a logit the mask kernel masks itself
+    LookArgs k{};
+    const size_t esz = g_apply.dtype == 0 ? 4 : 2;
+    const bool whole = g_apply.out && (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
+    // mask_look_kernel masks the logits with wavefronts of their own, whatever their size: they read them while the others work the masks out.  The
+    // logits are dealt out in units of as many KB as make 2,048 wavefronts, 4 at most (units of 2 / 4 / 6 / 8 KB, us per pass: 16 steps of 16 x 128,256
+    // bf16 171 / 176 / 184 / 186, of 64 x 152,064 fp32 - / 361 / 371 / 379, 8 steps of 130 x 40,037 bf16 148 / 144 / 149 / 151; 256 x 128,256 - / 235 / 229 / 239).
+    if (look && whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32)) {
+        const size_t words = (size_t)ng * (size_t)d->tab.W;
+        if (words > d->tagged_cap) {
+            const int rc = settle_calls(d);
+            if (rc != ZF_OK) return rc;
+            HIP_TRY(hipStreamSynchronize(stream));
+            if (d->d_tagged) (void)hipFree(d->d_tagged);
+            d->d_tagged = nullptr; d->tagged_cap = 0;
+            const size_t cap = std::max(words * 2, (size_t)STORE_INLINE_GROUPS * (size_t)d->tab.W);
+            HIP_TRY(hipMalloc((void **)&d->d_tagged, cap * 8));
+            d->tagged_cap = cap;
+            HIP_TRY(launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(cap * 2), stream));
+        }
+        const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
+        const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
+        k.unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048));
+        k.row_units = (row_kb + k.unit_kb - 1) / k.unit_kb;
+        k.units = k.row_units * (uint32_t)batch;
+        k.tagged = d->d_tagged; k.logits = g_apply.logits; k.out = g_apply.out; k.stride = g_apply.stride; k.dtype = (uint32_t)g_apply.dtype + 1;
+        g_apply.fused = true;
+    }
     if (g_apply.out && !look) {
-        const size_t esz = g_apply.dtype == 0 ? 4 : 2;
-        const bool whole = (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
         // mask_store_kernel does both as long as the logits are few enough that masking them hides behind the walk of the vocabulary;
         // beyond, a launch of its own masks them at the memory's rate with the work spread evenly over the chip.
         if (whole && 2ull * (uint64_t)batch * (uint64_t)e->V * esz <= STORE_FUSE_BYTES) {
@@ -1739,13 +1782,12 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const int budget = std::max(ng, (look ? look_blocks_per_cu() : std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch))) * std::max(1, d->cus));
     a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes);
     // ---- the records ----
-    LookArgs k{};
     if (look) {
         uint8_t *h = (uint8_t *)d->h_stage[slot];
         LookGroup *gr = big ? (LookGroup *)h : c.look.g;
         uint32_t *blk = (uint32_t *)(h + off_block);
         const bool members_apart = big || batch > STORE_INLINE_ROWS;
-        uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member;
+        uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member, *gof = (uint16_t *)(h + off_gof);
         uint32_t mem_at = 0, blk_at = 0;
         for (int r = 0; r < ng; r++) {
             const RowGroup &g = c.g[r];
@@ -1759,6 +1801,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
             for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;
             for (uint32_t j = 0; j < g.n_ent; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
             for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
+                if (big && k.units) gof[mem_at] = (uint16_t)r;
                 mem[mem_at++] = (uint16_t)b;
                 if (g.dev) note_device_state(d, states[b], g.dev);
             }
@@ -1768,7 +1811,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         const uint8_t *up = noalloc ? d->scratch : (const uint8_t *)d->d_chart;
         k.trans = d->store.trans; k.cache = d->tab.ci_tok; k.tok16 = d->tab.tok16; k.out_mask = d_mask; k.pool = d->d_pool;
         k.konst = d->d_konst;
-        if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); }
+        if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); k.group_of = (const uint16_t *)(up + off_gof); }
         else if (members_apart) k.members = (const uint16_t *)(h + off_mem);
         k.V = (uint32_t)e->V; k.W = (uint32_t)d->tab.W; k.ncls = (uint32_t)d->tab.n_cls; k.n_groups = (uint32_t)ng;
     } else {
@@ -1861,7 +1904,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     } else if (batch > STORE_INLINE_ROWS) a.members = (const uint16_t *)(stage + off_mem);
     a.tickets = d->d_tickets + d->ticket_set * STORE_TICKETS; a.tickets_next = d->d_tickets + (d->ticket_set ^ 1u) * STORE_TICKETS;
     a.status = (unsigned long long *)d->h_store_status + slot * STORE_STATUS_WORDS;
-    if (++d->call_seq == 0) d->call_seq = 1;
+    HIP_TRY(next_call_number(d, stream));
     a.seq = rec.seq = d->call_seq;
     a.V = (uint32_t)e->V; a.W = (uint32_t)T.W; a.ncls = (uint32_t)T.n_cls; a.cap_states = d->store.cap_states; a.tab_mode = (uint32_t)d->mode;
     a.scratch = scratch;
@@ -1880,8 +1923,12 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     d->closing_kernel = false;
     if (look) {
         k.tickets = a.tickets; k.tickets_next = a.tickets_next; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
-        HIP_TRY(launch_mask_look(k, c.look, a.n_blocks, stream));
+        k.mask_blocks = a.n_blocks;
+        const uint32_t grid = look_grid(k);
+        k.done_groups = rec.done_groups = grid <= 48u ? 1u : std::min(grid / 16u, (uint32_t)STORE_TICKET_GROUPS);
+        HIP_TRY(launch_mask_look(k, c.look, stream));
     } else {
+        rec.done_groups = 0;
         HIP_TRY(launch_mask_store(a, c.in, lds, stream));
         for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
     }
@@ -2105,8 +2152,8 @@ int zf_mask_wait(zf_engine *e, void *hip_stream) {
             }
             const volatile uint64_t *out = d->h_store_status + k * STORE_STATUS_WORDS;
             auto got = [&](size_t w) { return (uint32_t)(out[w] >> 32) == rec.seq; };
-            if ((rc = await([&]() { return got(STORE_ST_DONE); })) != ZF_OK) continue;
-            const uint32_t done = (uint32_t)out[STORE_ST_DONE], failed = done & 0xFFFFFFu;
+            if ((rc = await([&]() { return rec.done_groups ? look_done(out, rec) : got(STORE_ST_DONE); })) != ZF_OK) continue;
+            const uint32_t done = rec.done_groups ? look_failed(out, rec) : (uint32_t)out[STORE_ST_DONE], failed = done & 0xFFFFFFu;
             unresolved += failed;
             d->report.walk_chunks = rec.undecided;
             d->report.parser_steps = 0;

@@ -150,6 +150,7 @@ static_assert(sizeof(StoreArgs) + sizeof(StoreInline) <= 4096, "the kernel's arg
 #endif
 static const int LOOK_BLOCKS_PER_CU = ZF_LOOK_BLOCKS_PER_CU;
 static const int LOOK_WORDS = 9;
+static const int LOOK_UNIT_KB = 4;      // logits that a wavefront of mask_look_kernel holds while the mask is worked out, at most: a register quadruple per lane and KB
 struct LookGroup {                     // as StoreGroup, without what a known state does not need, in nine words:
     uint32_t w[LOOK_WORDS];            // [0] state; [1] n_ent | flags << 8 | (mask words per pass - 1) << 16; [2] first block | segments << 16;
 };                                     // [3] first member | members << 16; [4] pool row | cache row 0 << 16; [5 ..] cache rows 1, 2, ... two to a word
@@ -168,14 +169,23 @@ struct LookArgs {
     const uint16_t *members;
     unsigned long long *tickets, *tickets_next, *status;
     uint32_t seq, V, W, ncls, n_groups, complete;
+    uint32_t mask_blocks;              // blocks that work the masks out; behind them, where the logits are masked along:
+    uint32_t units, row_units, unit_kb, dtype;   // units of logits, one per wavefront, of unit_kb KB each; of a row; 1 = fp32, 2 = bf16
+    unsigned long long *tagged;        // [groups][W] mask words on their way to those wavefronts: call's number << 32 | word
+    const void *logits;
+    void *out;
+    int64_t stride;                    // elements between rows of logits
+    uint32_t done_groups;              // groups of blocks that report to the host, each in a status word of its own (STORE_ST_ROW + group)
+    const uint16_t *group_of;          // of the k-th entry of `members`, where the records are in device memory
 };
 static_assert(sizeof(LookArgs) + sizeof(LookInline) <= 4096, "the kernel's argument block");
+inline uint32_t look_grid(const LookArgs &a) { return a.mask_blocks + (a.units + STORE_WAVES - 1) / STORE_WAVES; }
 // Words of a call's status in pinned host memory.  Every word carries the call's number in its upper half, so the host knows of
 // each word by itself whether it has arrived: no order between them is needed (a release would write the L2 back first).
 enum : uint32_t { STORE_ST_DONE = 0,       // low half: walks that failed (24 bits) | STORE_ST_MORE; written last, by the block that finishes last
                   STORE_ST_STEPS = 1,      // Earley byte steps   (this word and the next three only with STORE_ST_MORE)
                   STORE_ST_STATES = 2, STORE_ST_ITEMS = 3, STORE_ST_REFUSED = 4,
-                  STORE_ST_ROW = 8 };      // + group: the state the group arrived in (groups with STORE_ROW_REPORT)
+                  STORE_ST_ROW = 8 };      // + group: the state the group arrived in (groups with STORE_ROW_REPORT); mask_look_kernel: + group of blocks: its failed walks, when it is done
 static const uint32_t STORE_ST_MORE = 0x80000000u;
 // A ticket word lies 64 bytes from the next: additions to words of one line queue up behind each other like additions to one word
 // (launches of 768 blocks that do nothing else: 10.2 us to the status word with the words side by side, 8.2 apart, 6.8 without tickets).
@@ -245,7 +255,7 @@ uint32_t store_lds_bytes(const DeviceTables &t, int mode, int scratch);
 int store_blocks_per_cu(const DeviceTables &t, int mode, int scratch);
 hipError_t launch_mask_store(const StoreArgs &a, const StoreInline &in, uint32_t lds_bytes, hipStream_t s);
 int look_blocks_per_cu();
-hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, hipStream_t s);
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, hipStream_t s);
 hipError_t launch_store_clear(const StoreView &G, uint32_t ncls, const void *root_items, uint32_t n_root, hipStream_t s);
 // The store, cleared, whose headers, items and table rows of the states below n_states were copied in from the host: their places in the
 // hash table, and how far the store is filled.

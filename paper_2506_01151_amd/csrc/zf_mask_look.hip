@@ -11,9 +11,17 @@
 // wavefront issues at 4 to 5 cycles apiece.  mask_store_kernel, which this one was split from, carries both halves: 200 scalar registers
 // put by in lanes of vector ones for the byte step's sake, 2.4 us from the group's record to its last request, 54 instructions
 // per byte of a walk.  Here the record is a quarter shorter, the cache rows are read by uniform addresses, the table row is on its
-// way before anything else, the logits are left to a launch of their own (their requests and stores lengthened every wavefront: 16 x
-// 128,256 bf16 260 us per 16 steps with them in here, 237 without, and 27.4 for 29.6 us per step synchronised), undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
+// way before anything else, undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
 // for, and a byte of the walk takes about 20 instructions: a lane that is done leaves the loop.
+//
+// The logits (zf_compute_mask_apply_async).  Memory has little to do while the masks are worked out, and a launch of its own behind this one
+// pays for the gap (1.2 us), its ramp and the whole of the reading.  Masked by the wavefront that has worked their mask out they lengthen
+// the chain (16 x 128,256 bf16 260 us per 16 steps, 237 in a launch of their own).  So wavefronts of their own take them along: blocks behind those
+// of the mask in the grid, which request their logits at once, wait for the mask words, and store.  Against two launches, us per pass: 32 steps of one row x
+// 32,000 fp32 324 -> 252, 16 of 16 x 128,256 bf16 196 -> 170, 16 of 64 x 128,256 bf16 288 -> 228, 16 of 64 x 152,064 fp32 422 -> 364,
+// 8 of 130 x 40,037 bf16 173 -> 143, 8 of 256 x 128,256 bf16 262 -> 233, 4 of 1,024 x 128,256 495 -> 379.
+//   Words travel as (call's number << 32 | word), one 8-byte store past the L2s each: whoever reads the number has the word, nothing is ordered
+// and nothing is counted.  No wavefront of the mask waits for one with logits, and blocks start in the order of the grid, so the wait ends; it is bounded all the same.
 #include "zf_kernel_common.h"
 #include "zf_aut_step.h"
 
@@ -25,31 +33,113 @@ static const int LOOK_LC_BITS = 10;                      // the block's LDS cach
 static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
 static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
 static const int LOOK_RAW = 4;                           // token-mask cache rows whose words stay in registers as they arrive
+static const unsigned long long LOOK_WAIT_TICKS = 200000000ull;   // 2 s of the 100 MHz clock: how long a wavefront with logits waits for mask words
 static const int LOOK_WARM = 6;                          // table rows one byte ahead that each wavefront of a block reads into the cache
 
 // 1,024 places by the upper bits of a 24-bit product (full rate; a 32-bit one takes four times as long)
 __device__ __forceinline__ uint32_t look_slot(uint32_t key) { return __umul24(key, 0x9E3779u) >> (32 - LOOK_LC_BITS); }
 __device__ __forceinline__ bool look_final(uint32_t t) { return t != AT_NONE && t != AT_BUSY; }
 
-// As hand_over_store: the block that draws the last ticket tells the host; here there is nothing to tell but failed walks.
-__device__ __forceinline__ void hand_over_look(const LookArgs &a, uint32_t failed) {
-    const uint32_t n_blocks = gridDim.x, lin = blockIdx.x;
-    const uint32_t n_groups = n_blocks <= 48u ? 1u : (n_blocks / 16u < (uint32_t)STORE_TICKET_GROUPS ? n_blocks / 16u : (uint32_t)STORE_TICKET_GROUPS);
-    const uint32_t g = lin % n_groups, size = n_blocks / n_groups + (g < n_blocks % n_groups ? 1u : 0u);
-    unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
-    unsigned long long sum = atomicAdd(&a.tickets[g * STORE_TICKET_STRIDE], mine) + mine;
-    if ((sum & 0xFFFFull) != size) return;
-    if (n_groups > 1u) {
-        mine = (sum & ~0xFFFFull) | 1ull;
-        sum = atomicAdd(&a.tickets[STORE_TICKET_GROUPS * STORE_TICKET_STRIDE], mine) + mine;
-        if ((sum & 0xFFFFull) != n_groups) return;
+// As hand_over_store, in one level: the block that draws the last ticket of its group of blocks tells the host, which looks at a word per
+// group; there is nothing to tell but failed walks.  In two parts: what a block has left to do between the draw and its answer, the trip to
+// memory hides.
+struct LookTicket { unsigned long long sum; uint32_t group, size; };
+__device__ __forceinline__ LookTicket draw_ticket(const LookArgs &a, uint32_t failed) {
+    LookTicket t;
+    t.group = blockIdx.x % a.done_groups;
+    t.size = gridDim.x / a.done_groups + (t.group < gridDim.x % a.done_groups ? 1u : 0u);
+    const unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
+    t.sum = atomicAdd(&a.tickets[t.group * STORE_TICKET_STRIDE], mine) + mine;
+    return t;
+}
+__device__ __forceinline__ void tell_host(const LookArgs &a, const LookTicket &t) {
+    if ((t.sum & 0xFFFFull) != t.size) return;
+    __hip_atomic_store(&a.status[STORE_ST_ROW + t.group], ((unsigned long long)a.seq << 32) | ((uint32_t)(t.sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A wavefront with logits: `unit_kb` KB of one row's.  It requests them, waits until the row's mask words for them are there, and stores them masked.
+// Where the words are there at once -- a block that started late, most blocks of a large tensor -- pieces of which nothing is allowed are not read.
+template <int DT> struct LookLogit { typedef uint32_t elem; static const int PER_PIECE = 4; static const uint32_t NEG_INF = 0xFF800000u; typedef u32x4 __attribute__((aligned(4))) piece; };
+template <> struct LookLogit<2> { typedef uint16_t elem; static const int PER_PIECE = 8; static const uint32_t NEG_INF = 0xFF80u; typedef u32x4 __attribute__((aligned(2))) piece; };
+// words_read(failed) is called when the mask words are in hand, before anything is stored.
+template <int DT, class WordsRead>
+__device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline &in, uint32_t unit, uint32_t lane, WordsRead words_read) {
+    typedef LookLogit<DT> L;
+    typedef typename L::elem elem;
+    typedef typename L::piece piece_t;
+    constexpr uint32_t EPV = L::PER_PIECE, KB_WORDS = 64 * EPV / 32, WORDS = (LOOK_UNIT_KB * KB_WORDS + 63) / 64;   // mask words of a KB; of a unit, per lane
+    const uint32_t m = unit / a.row_units, part = unit - m * a.row_units, nu = a.unit_kb, W = a.W;
+    uint32_t group = 0;
+    if (a.groups) group = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a.group_of[m]);
+    else if (a.n_groups > 1u) group = (uint32_t)__popcll(__ballot(lane < a.n_groups && (in.g[lane < a.n_groups ? lane : 0u].w[3] & 0xFFFFu) <= m)) - 1u;
+    const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a.members ? a.members[m] : in.member[m]));
+    const unsigned long long *const words = a.tagged + (size_t)group * W;
+    const uint32_t w0 = part * nu * KB_WORDS;
+    unsigned long long t[WORDS];
+    bool here = true;
+#pragma unroll
+    for (uint32_t k = 0; k < WORDS; k++) {
+        const uint32_t j = k * 64u + lane;
+        t[k] = (unsigned long long)a.seq << 32;
+        if (j < nu * KB_WORDS && w0 + j < W) t[k] = __hip_atomic_load(&words[w0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        here &= (uint32_t)(t[k] >> 32) == a.seq;
     }
-    __hip_atomic_store(&a.status[STORE_ST_DONE], ((unsigned long long)a.seq << 32) | ((uint32_t)(sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const bool ready = __all(here);
+    auto bits = [&](uint32_t u) __attribute__((always_inline)) -> uint32_t {   // of the lane's piece of KB u
+        const uint32_t w = (uint32_t)__shfl((int)(uint32_t)t[u * KB_WORDS / 64u], (int)((u * KB_WORDS) % 64u + lane / (32u / EPV)));
+        return (w >> ((lane % (32u / EPV)) * EPV)) & ((1u << EPV) - 1u);
+    };
+    const uint32_t n_vec = a.V / EPV, p0 = part * nu * 64u + lane, tail = a.V - n_vec * EPV;
+    const elem *const src = (const elem *)a.logits + (size_t)row * a.stride;
+    elem *const dst = (elem *)a.out + (size_t)row * a.stride;
+    u32x4 x[LOOK_UNIT_KB];
+#pragma unroll
+    for (uint32_t u = 0; u < (uint32_t)LOOK_UNIT_KB; u++) {
+        x[u] = u32x4{0, 0, 0, 0};
+        if (u >= nu) continue;
+        const bool wanted = !ready || bits(u);               // (all lanes: a lane's word may be with one beyond the row's end)
+        if (wanted && p0 + u * 64u < n_vec) x[u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(src) + p0 + u * 64u);
+    }
+    const bool has_tail = tail && part + 1u == a.row_units && lane < tail;   // V is not a multiple of the piece: the row's last elements, one per lane
+    elem last = 0;
+    if (has_tail) last = src[n_vec * EPV + lane];
+    if (!ready) {
+        const unsigned long long t0 = wall_clock64();
+        for (;;) {
+            __builtin_amdgcn_s_sleep(8);
+            here = true;
+#pragma unroll
+            for (uint32_t k = 0; k < WORDS; k++) {
+                if ((uint32_t)(t[k] >> 32) != a.seq) t[k] = __hip_atomic_load(&words[w0 + k * 64u + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                here &= (uint32_t)(t[k] >> 32) == a.seq;
+            }
+            if (__all(here)) break;
+            if (wall_clock64() - t0 > LOOK_WAIT_TICKS) { words_read(1u); return; }   // never, unless the mask's blocks are not running: the call fails
+        }
+    }
+    words_read(0u);
+#pragma unroll
+    for (uint32_t u = 0; u < (uint32_t)LOOK_UNIT_KB; u++) {
+        if (u >= nu) continue;
+        const uint32_t b = bits(u);
+        elem *e = reinterpret_cast<elem *>(&x[u]);
+#pragma unroll
+        for (uint32_t k = 0; k < EPV; k++) if (!((b >> k) & 1u)) e[k] = (elem)L::NEG_INF;
+        if (p0 + u * 64u < n_vec) __builtin_nontemporal_store(x[u], reinterpret_cast<piece_t *>(dst) + p0 + u * 64u);
+    }
+    if (tail && part + 1u == a.row_units) {
+        const uint32_t v = n_vec * EPV + lane, j = v / 32u - w0;   // the words of the row's end are its unit's
+        uint32_t w = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < WORDS; k++) { const uint32_t y = (uint32_t)__shfl((int)(uint32_t)t[k], (int)(j & 63u)); w = j / 64u == k ? y : w; }
+        if (has_tail) dst[v] = (w >> (v & 31u)) & 1u ? last : (elem)L::NEG_INF;
+    }
 }
 
 // Grid and groups as in mask_store_kernel: the blocks of all groups one after the other, a group = the rows of the call that
 // stand in the same state, whose mask is worked out once, in token order.  A wavefront takes every n_units-th segment of `sw` mask words.
-__global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_kernel(LookArgs a, LookInline in) {
+template <int DT>   // of the logits masked along: 0 = none, 1 = fp32, 2 = bf16
+__global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLOCKS_PER_CU) void mask_look_kernel(LookArgs a, LookInline in) {
     __shared__ unsigned long long lc[LOOK_LC];
     __shared__ uint32_t lists[STORE_WAVES][LOOK_LIST];
     __shared__ uint32_t vbufs[STORE_WAVES][64];
@@ -58,16 +148,33 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);
     // ---- the record of the block's group: one trip to the argument block (lane l asks for that of group l), or to device memory ----
-    uint32_t r[LOOK_WORDS], part, parts;
+    uint32_t r[LOOK_WORDS], part, parts, group = 0;
+    if (DT && blockIdx.x >= a.mask_blocks) {
+        if (tid == 0) blk_failed = 0;                        // wavefronts that have their words, and those that gave up << 16
+        __syncthreads();
+        const uint32_t unit = (blockIdx.x - a.mask_blocks) * STORE_WAVES + wave;
+        LookTicket t{};
+        bool drew = false;
+        // nothing that belongs to the engine is read behind this: the ticket's trip to memory goes along with the stores
+        auto words_read = [&](uint32_t f) __attribute__((always_inline)) {
+            const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lane == 0 ? atomicAdd(&blk_failed, 1u + (f << 16)) : 0u));
+            drew = (before & 0xFFFFu) == STORE_WAVES - 1u;
+            if (drew && lane == 0) t = draw_ticket(a, (before >> 16) + f);
+        };
+        if (unit < a.units) mask_logits<DT>(a, in, unit, lane, words_read);
+        else words_read(0u);
+        if (drew && lane == 0) tell_host(a, t);
+        return;
+    }
     if (a.groups) {
         const uint32_t b0 = a.block_of[2u * blockIdx.x], b1 = a.block_of[2u * blockIdx.x + 1u];
-        const uint32_t group = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+        group = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
         part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 & 0xFFFFu));
         parts = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 >> 16));
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[k]);
     } else if (a.n_groups == 1u) {                           // one group: scalar loads, along with the other arguments
-        part = blockIdx.x; parts = gridDim.x;
+        part = blockIdx.x; parts = a.mask_blocks;
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = in.g[0].w[k];
     } else {
@@ -75,10 +182,10 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) x[k] = lane < a.n_groups ? in.g[lane].w[k] : 0xFFFFFFFFu;
         const uint32_t first = x[2] & 0xFFFFu;
-        const uint32_t group = (uint32_t)__popcll(__ballot(blockIdx.x >= first)) - 1u;   // groups that start at or before this block
+        group = (uint32_t)__popcll(__ballot(blockIdx.x >= first)) - 1u;   // groups that start at or before this block
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readlane((int)x[k], (int)group);
-        const uint32_t fb0 = r[2] & 0xFFFFu, fb1 = group + 1u < a.n_groups ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)(group + 1u)) : gridDim.x;
+        const uint32_t fb0 = r[2] & 0xFFFFu, fb1 = group + 1u < a.n_groups ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)(group + 1u)) : a.mask_blocks;
         part = blockIdx.x - fb0; parts = fb1 - fb0;
     }
     for (uint32_t k = tid; k < LOOK_LC; k += STORE_BLOCK) lc[k] = 0xFFFFFFFF00000000ull;
@@ -125,20 +232,22 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
     for (int k = 0; k < LOOK_WARM; k++) { ahead[k] = 0; t_ahead[k] = AT_NONE; }
     if (walks) {
         into_cache(start, t_root);
-        unsigned long long todo = __ballot(lane < ncls && t_root < AT_FAIL && t_root != start);
-        uint32_t n = 0;
-        while (todo && n < (uint32_t)(LOOK_WARM * STORE_WAVES)) {
-            const uint32_t nx = (uint32_t)__builtin_amdgcn_readlane((int)t_root, __ffsll((long long)todo) - 1);
-            todo &= ~__ballot(t_root == nx);
-            if ((n & (STORE_WAVES - 1u)) == wave) {
+        // a lane per state one byte away: of lanes with the same state one is left (by whose number stays in a common place; different states may
+        // share a place, one of them is not read ahead then), the wavefront takes every STORE_WAVES-th of them
+        const bool live = lane < ncls && t_root < AT_FAIL && t_root != start;
+        uint32_t *const place = &list[t_root % LOOK_LIST];
+        if (live) lds_store(place, lane);
+        const bool mine = live && lds_load(place) == lane;
+        const unsigned long long owners = __ballot(mine);
+        const uint32_t rank = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(owners >> 32), (uint32_t)__builtin_amdgcn_mbcnt_lo((uint32_t)owners, 0)), n = (uint32_t)__popcll(owners);
+        if (mine) lds_store(&list[rank], t_root);
+        n_ahead = n > wave ? (n - wave + STORE_WAVES - 1u) / STORE_WAVES : 0u;
+        const uint32_t at_rank = lds_load(&list[lane]);
 #pragma unroll
-                for (int k = 0; k < LOOK_WARM; k++) ahead[k] = n_ahead == (uint32_t)k ? nx : ahead[k];
-                n_ahead++;
-            }
-            n++;
+        for (int k = 0; k < LOOK_WARM; k++) {
+            ahead[k] = (uint32_t)__builtin_amdgcn_readlane((int)at_rank, k * STORE_WAVES + (int)wave);
+            if ((uint32_t)k < n_ahead && lane < ncls) t_ahead[k] = a.trans[(size_t)ahead[k] * ncls + lane];
         }
-#pragma unroll
-        for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead && lane < ncls) t_ahead[k] = a.trans[(size_t)ahead[k] * ncls + lane];
     }
     uint32_t failed = 0;
     bool first = true;
@@ -233,6 +342,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
             }
         }
         if (total) v |= lane < sw ? lds_load(&vbuf[lane]) : 0u;   // LDS serves one wavefront's accesses in issue order
+        if (DT && w < W) __hip_atomic_store(&a.tagged[(size_t)group * W + w], (unsigned long long)a.seq << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // ---- the segment's words go to every member's mask row (and to the state cache) ----
         for (uint32_t m0 = 0; m0 < n_members; m0 += 64) {
             if (n_members > 64u) members = members_from(m0);
@@ -259,7 +369,7 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
     }
     if (a.complete) stores_arrived();                        // every word this wavefront wrote has reached memory before the block's ticket is drawn
     __syncthreads();
-    if (tid == 0) hand_over_look(a, lds_load(&blk_failed));
+    if (tid == 0) tell_host(a, draw_ticket(a, lds_load(&blk_failed)));
 }
 
 }  // namespace
@@ -268,14 +378,17 @@ __global__ __launch_bounds__(STORE_BLOCK, LOOK_BLOCKS_PER_CU) void mask_look_ker
 int look_blocks_per_cu() {
     static const int blocks = [] {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(mask_look_kernel), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(mask_look_kernel<0>), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
         return n < LOOK_BLOCKS_PER_CU ? n : LOOK_BLOCKS_PER_CU;
     }();
     return blocks;
 }
 
-hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, uint32_t n_blocks, hipStream_t s) {
-    hipLaunchKernelGGL(mask_look_kernel, dim3(n_blocks), dim3(STORE_BLOCK), 0, s, a, in);
+hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, hipStream_t s) {
+    const dim3 grid(look_grid(a)), block(STORE_BLOCK);
+    if (!a.units) hipLaunchKernelGGL(mask_look_kernel<0>, grid, block, 0, s, a, in);
+    else if (a.dtype == 1) hipLaunchKernelGGL(mask_look_kernel<1>, grid, block, 0, s, a, in);
+    else hipLaunchKernelGGL(mask_look_kernel<2>, grid, block, 0, s, a, in);
     return hipGetLastError();
 }
 

@@ -1051,6 +1051,52 @@ def test_waiting_calls_on_two_streams(noalloc, precompute, torch_cuda, oracle_li
     assert noalloc or hits >= 9 * n, hits
 
 
+@pytest.mark.parametrize("V,B,dtype,shift", [(5, 2, "f32", 0), (7, 1, "bf16", 1), (512, 3, "bf16", 0), (513, 70, "bf16", 0), (1023, 3, "f32", 3), (2047, 2, "bf16", 1), (2049, 66, "f32", 0),
+                                             (8193, 5, "bf16", 5), (40037, 600, "bf16", 1), (33001, 300, "f32", 0)])
+def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracle_lib):
+    """The wavefronts of mask_look_kernel that mask logits: rows that end within a piece, within a KB and within a unit of four, rows at any multiple of
+    an element, fewer tokens than a piece, groups in the argument block and beyond it, and tensors larger than what the chip holds at once (wavefronts that
+    find their words there and leave out what nothing is allowed of).  Out of place; masks and logits are the oracle's."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    toks = (configs.CONFIGS[2].vocab(max(V, 2048))[::-1])[:V]
+    off, data = wvocab.vocab_csr(toks)
+    g = grammars.json_grammar()
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)
+    prefixes = [b"", b"[", b'{"a', b"[1", b'["x', b"[[0.5e", b'{"k":', b"tru"] + [b"[" * k for k in range(2, 80 if B in (66, 70) else 2)]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    rng = np.random.default_rng(V + B)
+    u, i, f = (np.uint32, torch.int32, torch.float32) if dtype == "f32" else (np.uint16, torch.int16, torch.bfloat16)
+    states = [eng.new_state() for _ in range(B)]
+    rows = zf.StateBatch(states)
+    wide = torch.zeros(B * (V + 3) + shift, dtype=i, device="cuda")
+    d_mask, out = torch.empty((B, eng.W), dtype=torch.int32, device="cuda"), torch.empty(B * (V + 3) + shift, dtype=i, device="cuda")
+    t, o = (x[shift:].view(B, V + 3)[:, :V] for x in (wide, out))
+    for call in range(3):                          # the first call meets the states, the others look them up
+        at = (np.arange(B) * 3 + 5 * call) % len(prefixes)
+        for s, p in zip(states, at):
+            s.reset()
+            s.advance_bytes(prefixes[p])
+        bits = rng.integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
+        t.copy_(torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)))
+        out.fill_(0x1234)
+        zf.compute_mask_apply_async(eng, rows, d_mask, t.view(f), out=o.view(f))
+        zf.mask_wait(eng)
+        torch.cuda.synchronize()
+        wanted = np.stack([want[p] for p in at])
+        assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted), call
+        assert np.ascontiguousarray(o.cpu().numpy()).view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), call
+        rest = out.cpu()
+        rest[shift:].view(B, V + 3)[:, :V] = 0x1234
+        assert bool((rest == 0x1234).all()), call   # nothing beyond the rows' ends
+
+
 @pytest.mark.parametrize("B,dtype", [(3, "bf16"), (64, "f32"), (300, "bf16")])
 def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
     """Calls of look-ups only, one behind the other with nothing synchronised between them: more of them than there are slots, records and row numbers
