@@ -32,13 +32,26 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 static const int LOOK_LC_BITS = 10;                      // the block's LDS cache of table entries: 1,024 of (key, state)
 static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
 static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
-static const int LOOK_RAW = 4;                           // token-mask cache rows whose words stay in registers as they arrive
+static const int LOOK_RAW = 2;                           // token-mask cache rows that are asked for whether or not there are so many
 static const unsigned long long LOOK_WAIT_TICKS = 200000000ull;   // 2 s of the 100 MHz clock: how long a wavefront with logits waits for mask words
+static_assert(LOOK_LIST >= 64u * STORE_WAVES, "the states one byte away are listed there, read by lane x wavefronts");
 static const int LOOK_WARM = 6;                          // table rows one byte ahead that each wavefront of a block reads into the cache
 
-// 1,024 places by the upper bits of a 24-bit product (full rate; a 32-bit one takes four times as long)
-__device__ __forceinline__ uint32_t look_slot(uint32_t key) { return __umul24(key, 0x9E3779u) >> (32 - LOOK_LC_BITS); }
-__device__ __forceinline__ bool look_final(uint32_t t) { return t != AT_NONE && t != AT_BUSY; }
+// The compiler takes whatever does not change from one segment to the next out of the loop over them: 150 scalar instructions and 30 spills, half a
+// microsecond in front of every wavefront's first segment, most of it for segments that follow (few wavefronts have more than one).  A value that went through here stays where it is used.
+__device__ __forceinline__ uint32_t stay(uint32_t x) { asm volatile("" : "+s"(x)); return x; }
+
+// A row of the table lies in neighbouring places: the states that a walk meets have neighbouring numbers (they were explored breadth first, or met
+// one after the other), so their rows seldom share a place.  With places by a hash of the key two or three of a walk's four to nine rounds
+// asked memory for entries that another lane had just put out (16 x 128,256 bf16 157 -> 151 us per 16 steps, 130 x 40,037 136 -> 129; 2,048 places: 153 and 127, and
+// 4,096 leave room for three blocks).
+__device__ __forceinline__ uint32_t look_slot(uint32_t key) { return key & (LOOK_LC - 1u); }
+// The k-th row number, from device memory or from the argument block.  (Of two generic pointers the compiler makes one flat load, which waits for
+// LDS as well as for memory: the one into device memory says so.)
+__device__ __forceinline__ uint32_t member_row(const LookArgs &a, const LookInline &in, uint32_t k) {
+    if (a.members) return ((const __attribute__((address_space(1))) uint16_t *)a.members)[k];
+    return in.member[k];
+}
 
 // As hand_over_store, in one level: the block that draws the last ticket of its group of blocks tells the host, which looks at a word per
 // group; there is nothing to tell but failed walks.  In two parts: what a block has left to do between the draw and its answer, the trip to
@@ -72,7 +85,7 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
     uint32_t group = 0;
     if (a.groups) group = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a.group_of[m]);
     else if (a.n_groups > 1u) group = (uint32_t)__popcll(__ballot(lane < a.n_groups && (in.g[lane < a.n_groups ? lane : 0u].w[3] & 0xFFFFu) <= m)) - 1u;
-    const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a.members ? a.members[m] : in.member[m]));
+    const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)member_row(a, in, m));
     const unsigned long long *const words = a.tagged + (size_t)group * W;
     const uint32_t w0 = part * nu * KB_WORDS;
     unsigned long long t[WORDS];
@@ -178,17 +191,19 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = in.g[0].w[k];
     } else {
+        const uint32_t at = lane < a.n_groups ? lane : a.n_groups - 1u;
         uint32_t x[LOOK_WORDS];
 #pragma unroll
-        for (int k = 0; k < LOOK_WORDS; k++) x[k] = lane < a.n_groups ? in.g[lane].w[k] : 0xFFFFFFFFu;
+        for (int k = 0; k < LOOK_WORDS; k++) x[k] = in.g[at].w[k];
         const uint32_t first = x[2] & 0xFFFFu;
-        group = (uint32_t)__popcll(__ballot(blockIdx.x >= first)) - 1u;   // groups that start at or before this block
+        group = (uint32_t)__popcll(__ballot(lane < a.n_groups && blockIdx.x >= first)) - 1u;   // groups that start at or before this block
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readlane((int)x[k], (int)group);
         const uint32_t fb0 = r[2] & 0xFFFFu, fb1 = group + 1u < a.n_groups ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)(group + 1u)) : a.mask_blocks;
         part = blockIdx.x - fb0; parts = fb1 - fb0;
     }
-    for (uint32_t k = tid; k < LOOK_LC; k += STORE_BLOCK) lc[k] = 0xFFFFFFFF00000000ull;
+#pragma unroll
+    for (uint32_t k = 0; k < LOOK_LC / STORE_BLOCK; k++) lc[k * STORE_BLOCK + tid] = 0xFFFFFFFF00000000ull;
     if (tid == 0) blk_failed = 0;
     __syncthreads();
     const uint32_t start = r[0], n_ent = r[1] & 0xFFu, sw = ((r[1] >> 16) & 0xFFu) + 1u, n_seg = r[2] >> 16, member_at = r[3] & 0xFFFFu, n_members = r[3] >> 16;
@@ -197,44 +212,52 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
     if (unit < n_seg) {
     uint32_t *const list = lists[wave], *const vbuf = vbufs[wave];
     const bool walks = !pooled && start < AT_FAIL;            // AT_SINK: the sentence is finished, no token can follow
-    // ---- requests, in the order their answers are needed: the state's table row, the segment's cache words, members ----
-    uint32_t t_root = AT_NONE;
-    const uint32_t *const row0 = a.trans + (size_t)start * ncls;
-    if (walks && lane < ncls) t_root = row0[lane];
-    auto ent = [&](int j) -> uint32_t { return (r[4 + ((j + 1) >> 1)] >> (((j + 1) & 1) * 16)) & 0xFFFFu; };
-    auto request = [&](uint32_t g, uint2 (&x)[LOOK_RAW]) __attribute__((always_inline)) {
-        const uint32_t w = g * sw + lane;
-        const bool on = lane < sw && w < W;
+    // ---- requests: the segment's cache words, the state's table row, members.  No lane is left out and nothing is asked for under a condition that
+    // differs (lanes and rows too many ask again for what a neighbour asks for): the compiler then knows how many loads are on their way behind
+    // each, and waits for the one it needs; where it does not know, it waits for all of them ----
+    struct Words { uint2 x[LOOK_RAW], y[STORE_GROUP_ENT - LOOK_RAW]; };
+    auto request = [&](uint32_t g, Words &q) __attribute__((always_inline)) {
+        const uint32_t w = g * sw + lane < W ? g * sw + lane : W - 1u;
+        const uint32_t rows[5] = {stay(r[4]), stay(r[5]), stay(r[6]), stay(r[7]), stay(r[8])};
+        auto ent = [&](int j) -> uint32_t { return (rows[(j + 1) >> 1] >> (((j + 1) & 1) * 16)) & 0xFFFFu; };
+        if (pooled) {
+            q.x[0] = make_uint2(a.pool[(size_t)start * W + w], 0);
 #pragma unroll
-        for (int j = 0; j < LOOK_RAW; j++) x[j] = make_uint2(0, 0);
-        if (pooled) { if (on) x[0].x = a.pool[(size_t)start * W + w]; return; }
-        if (!use_cache) { x[0].y = 0xFFFFFFFFu; return; }
-#pragma unroll
-        for (int j = 0; j < LOOK_RAW; j++) if ((uint32_t)j < n_ent && on) x[j] = a.cache[(size_t)ent(j) * W + w];
+            for (int j = 1; j < LOOK_RAW; j++) q.x[j] = make_uint2(0, 0);
+            return;
+        }
         if (n_ent > (uint32_t)LOOK_RAW) {
 #pragma unroll
-            for (int j = LOOK_RAW; j < STORE_GROUP_ENT; j++) if ((uint32_t)j < n_ent && on) { const uint2 y = a.cache[(size_t)ent(j) * W + w]; x[0].x |= y.x; x[0].y |= y.y; }
+            for (int j = LOOK_RAW; j < STORE_GROUP_ENT; j++) q.y[j - LOOK_RAW] = a.cache[(size_t)((uint32_t)j < n_ent ? ent(j) : ent(0)) * W + w];
         }
+#pragma unroll
+        for (int j = 0; j < LOOK_RAW; j++) q.x[j] = a.cache[(size_t)((uint32_t)j < n_ent ? ent(j) : ent(0)) * W + w];   // (without a row: row 0, not looked at)
     };
-    uint2 x[LOOK_RAW];
+    Words x;
+#pragma unroll
+    for (int j = 0; j < STORE_GROUP_ENT - LOOK_RAW; j++) x.y[j] = make_uint2(0, 0);
     request(unit, x);
+    const uint32_t known = walks ? start : 0u, column = lane < ncls ? lane : 0u;
+    // (the table takes 128 MB at most: an offset of 32 bits)
+    auto table = [&](uint32_t st) __attribute__((always_inline)) -> uint32_t { return *(const uint32_t *)((const uint8_t *)a.trans + (size_t)((st * ncls + column) * 4u)); };
+    uint32_t t_root = table(known);
     auto members_from = [&](uint32_t m0) __attribute__((always_inline)) -> uint32_t {   // lane l: the l-th of the 64 rows in hand
         const uint32_t k = member_at + m0 + lane;
-        return m0 + lane < n_members ? (a.members ? a.members[k] : in.member[k]) : 0u;
+        return m0 + lane < n_members ? member_row(a, in, k) : 0u;
     };
-    uint32_t members = members_from(0);
+    const uint32_t member_k = member_at + (lane < n_members ? lane : 0u);
+    uint32_t members = member_row(a, in, member_k);
+    if (!walks || lane >= ncls) t_root = AT_NONE;
     // ---- the block's LDS cache: the state's row, and the rows of the states one byte away, shared out among the wavefronts ----
     auto into_cache = [&](uint32_t st, uint32_t t) __attribute__((always_inline)) {
-        if (lane < ncls && look_final(t)) { const uint32_t key = st * ncls + lane; __hip_atomic_store(&lc[look_slot(key)], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+        if (lane < ncls) { const uint32_t key = st * ncls + lane; __hip_atomic_store(&lc[look_slot(key)], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
     };
     uint32_t ahead[LOOK_WARM], t_ahead[LOOK_WARM], n_ahead = 0;
-#pragma unroll
-    for (int k = 0; k < LOOK_WARM; k++) { ahead[k] = 0; t_ahead[k] = AT_NONE; }
-    if (walks) {
-        into_cache(start, t_root);
+    into_cache(start, t_root);
+    {
         // a lane per state one byte away: of lanes with the same state one is left (by whose number stays in a common place; different states may
         // share a place, one of them is not read ahead then), the wavefront takes every STORE_WAVES-th of them
-        const bool live = lane < ncls && t_root < AT_FAIL && t_root != start;
+        const bool live = t_root < AT_FAIL && t_root != start;
         uint32_t *const place = &list[t_root % LOOK_LIST];
         if (live) lds_store(place, lane);
         const bool mine = live && lds_load(place) == lane;
@@ -242,20 +265,24 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
         const uint32_t rank = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(owners >> 32), (uint32_t)__builtin_amdgcn_mbcnt_lo((uint32_t)owners, 0)), n = (uint32_t)__popcll(owners);
         if (mine) lds_store(&list[rank], t_root);
         n_ahead = n > wave ? (n - wave + STORE_WAVES - 1u) / STORE_WAVES : 0u;
-        const uint32_t at_rank = lds_load(&list[lane]);
+        const uint32_t at_rank = lds_load(&list[lane * STORE_WAVES + wave]);   // lane k: the wavefront's k-th
 #pragma unroll
         for (int k = 0; k < LOOK_WARM; k++) {
-            ahead[k] = (uint32_t)__builtin_amdgcn_readlane((int)at_rank, k * STORE_WAVES + (int)wave);
-            if ((uint32_t)k < n_ahead && lane < ncls) t_ahead[k] = a.trans[(size_t)ahead[k] * ncls + lane];
+            const uint32_t nx = (uint32_t)__builtin_amdgcn_readlane((int)at_rank, k);
+            ahead[k] = (uint32_t)k < n_ahead ? nx : known;
+            t_ahead[k] = table(ahead[k]);
         }
     }
     uint32_t failed = 0;
     bool first = true;
     for (uint32_t g = unit; g < n_seg; g += n_units) {
         const uint32_t w = lane < sw ? g * sw + lane : 0xFFFFFFFFu;   // the lane's mask word
-        uint32_t v = x[0].x, c = x[0].y;
+        uint32_t v = 0, c = 0;
 #pragma unroll
-        for (int j = 1; j < LOOK_RAW; j++) { v |= x[j].x; c |= x[j].y; }
+        for (int j = 0; j < LOOK_RAW; j++) { v |= x.x[j].x; c |= x.x[j].y; }
+#pragma unroll
+        for (int j = 0; j < STORE_GROUP_ENT - LOOK_RAW; j++) { v |= x.y[j].x; c |= x.y[j].y; }
+        if (!n_ent) { v = pooled ? v : 0u; c = pooled || use_cache ? 0u : 0xFFFFFFFFu; }
         if (g + n_units < n_seg) request(g + n_units, x);    // the next segment's words travel while this one's tokens are checked
         uint32_t want = c & ~v;
         {
@@ -297,12 +324,12 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
             Tok nxt = fetch(0);
             if (first) {                                     // the rows one byte ahead have arrived meanwhile
 #pragma unroll
-                for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead) into_cache(ahead[k], t_ahead[k]);
+                for (int k = 0; k < LOOK_WARM; k++) if ((uint32_t)k < n_ahead) into_cache(stay(ahead[k]), t_ahead[k]);
                 first = false;
             }
             for (uint32_t b0 = 0; b0 < n; b0 += 64) {
                 const Tok cur = nxt;
-                if (b0 + 64 < n) nxt = fetch(b0 + 64);
+                nxt = fetch(b0 + 64);                        // (behind the last batch: the list's first token again)
                 // One lane per token: it follows its string through the table for as long as there is a state and a next byte.  The
                 // classes at hand are a shift register; a mark ends them.
                 uint32_t w0 = cur.s[0], w1 = cur.s[1], w2 = cur.s[2], w3 = cur.s[3];
@@ -353,7 +380,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
                     if (w < W) put_word(dst, v, a.complete);
                 }
             } else {                                         // several members per store: the lanes hold the segment 2, 4, 8 or 16 times over
-                const uint32_t lg = sw <= 4u ? 2u : sw <= 8u ? 3u : sw <= 16u ? 4u : 5u, word = lane & ((1u << lg) - 1u), w2 = g * sw + word;
+                const uint32_t s = stay(sw), lg = s <= 4u ? 2u : s <= 8u ? 3u : s <= 16u ? 4u : 5u, word = lane & ((1u << lg) - 1u), w2 = g * sw + word;
                 const uint32_t v2 = (uint32_t)__shfl((int)v, (int)word);
                 for (uint32_t k0 = 0; k0 < n; k0 += 64u >> lg) {
                     const uint32_t k = k0 + (lane >> lg);
