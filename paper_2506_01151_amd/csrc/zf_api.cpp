@@ -1350,7 +1350,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
             most_items = std::max<size_t>(most_items, c.set_off[c.n_sets()]);
             for (uint32_t k = 0; k < c.n_sets(); k++) biggest_set = std::max<size_t>(biggest_set, c.set_off[k + 1] - c.set_off[k]);
         }
-        int scratch = 0, n_states = 0, arena = 0, base_sets = 0, base_items = 0;
+        int scratch = 0, n_states = 0, arena = 0, base_sets = 0, base_items = 0, waves = nb <= d->cus ? AUT_WAVES : AUT_WAVES_MANY_ROWS;
         // The build without the wide byte step also takes the chart from LDS only (its pointers are then
         // known to be LDS addresses): it serves calls whose sets are all small and whose charts all fit.
         // AUT_STEP_LANES holds sets of 64 items, which a byte or a long token can take a dozen items beyond: the strings behind such a set
@@ -1363,7 +1363,8 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
             scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
             n_states = AUT_STATES_DEFAULT; arena = std::max(1024, 8 * scratch);
             base_sets = BASE_SETS_LDS; base_items = BASE_ITEMS_LDS;
-            auto lds_now = [&]() { return automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, base_sets, base_items, step == AUT_STEP_WIDE); };
+            auto lds_now = [&]() { return automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, base_sets, base_items, step == AUT_STEP_WIDE, waves); };
+            if (lds_now() > lds_max) waves = AUT_WAVES_MANY_ROWS;
             while (lds_now() > lds_max && arena > 2 * scratch) arena /= 2;
             while (lds_now() > lds_max && n_states > 8) n_states /= 2;
             while (lds_now() > lds_max && scratch > 32) { scratch /= 2; arena = std::max(arena / 2, 2 * scratch); }
@@ -1373,22 +1374,24 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
                 const int want_sets = (int)std::max<size_t>(BASE_SETS_LDS, (most_sets + 32) / 32 * 32 - 1);
                 const int want_items = (int)std::max<size_t>(BASE_ITEMS_LDS, (most_items + 63) / 64 * 64);
                 if (want_sets <= AUT_BASE_SETS_MAX && want_items <= AUT_BASE_ITEMS_MAX &&
-                    automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, want_sets, want_items, step == AUT_STEP_WIDE) <= lds_max) {
+                    automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, want_sets, want_items, step == AUT_STEP_WIDE, waves) <= lds_max) {
                     base_sets = want_sets; base_items = want_items;
                 }
             }
-            if (step == AUT_STEP_WIDE || (most_sets <= (size_t)base_sets && most_items <= (size_t)base_items)) break;
+            const bool chart_fits = most_sets <= (size_t)base_sets && most_items <= (size_t)base_items;
+            if (!chart_fits && waves == AUT_WAVES) { waves = AUT_WAVES_MANY_ROWS; continue; }   // smaller blocks leave more of it
+            if (step == AUT_STEP_WIDE || chart_fits) break;
             step = AUT_STEP_WIDE;                         // some chart stays in global memory: the other build
         }
         a.aut_states = n_states; a.aut_arena = arena; a.aut_scratch = scratch;
         a.aut_base_sets = base_sets; a.aut_base_items = base_items;
-        a.aut_step = step;
+        a.aut_step = step; a.aut_waves = waves;
         d->lanes_call[slot] = step == AUT_STEP_LANES;
-        // blocks per row: as many as the chip holds at once, at most two per compute unit and one per pass of AUT_SUB_WORDS words.
+        // blocks per row: as many as the chip holds at once -- of 16 wavefronts one per compute unit, of 8 at most two --, at most one per AUT_PART_WORDS words.
         // (Every block works its row's automaton out from the start: a second round of blocks, where the wide byte step's scratch
         // leaves room for one block per compute unit, took as long as the first.)
-        const int n_sub = (d->tab.Wr + AUT_PART_WORDS - 1) / AUT_PART_WORDS;
-        const int resident = std::min(2, automaton_blocks_per_cu(a)) * std::max(1, d->cus);
+        const int n_sub = (d->tab.Wr + AUT_PART_WORDS - 1) / AUT_PART_WORDS, most = waves == AUT_WAVES ? 1 : 2;
+        const int resident = std::min(most, automaton_blocks_per_cu(a)) * std::max(1, d->cus);
         a.aut_parts = std::max(1, std::min(n_sub, resident == 2 * d->cus ? (resident + std::max(nb, 1) - 1) / std::max(nb, 1) : resident / std::max(nb, 1)));
     }
     const bool prof = d->profiling;

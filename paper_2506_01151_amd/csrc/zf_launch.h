@@ -23,14 +23,17 @@ static const int AUT_NARROW_SET_MAX = 8, AUT_LANES_SET_MAX = 16, AUT_STEP_WIDE_F
 static const int AUT_BASE_SETS_MAX = 1023; // the largest limits the host asks for
 static const int AUT_BASE_ITEMS_MAX = 4096;
 static const int TABLE_LDS_BUDGET = 56 * 1024;
-static const int AUT_WAVES = 8;            // wavefronts per block of the mask-automaton kernel
-static const int AUT_BLOCK = AUT_WAVES * 64;
-static const int AUT_SUB_WORDS = 512;      // words of the rank-ordered bitmap (32 strings each) a block merges and checks per pass, one per thread ...
+// Wavefronts per block of the mask-automaton kernel.  The wavefronts of a block share the automaton they build, so a row of few large blocks works its
+// steps out fewer times; but a compute unit holds one block of 16 (two of 8, three where registers allow).  So: 16 while every row can have such a
+// block at once, 8 for larger batches, and where sets are so wide that 16 would not have their scratch (grammar of expressions without pruning,
+// 8 steps, us, blocks of 8 / of 16: 64 rows x 152,064 893 / 801, 100 rows x 20,001 813 / 724, 200 rows 1,472 / 1,197, 512 rows 2,514 / 2,751; JSON 16 rows x 32,000 1,353 / 1,134).
+static const int AUT_WAVES_MANY_ROWS = 8, AUT_WAVES = 16;
+// A block takes a pass of its row's words with one word of the rank-ordered bitmap (32 strings) per thread; ...
 static const int AUT_PART_WORDS = 128;     // ... the fewest a block of a row is made for ...
 static const int AUT_GROUP_WORDS = 4;      // ... taken from the row in groups of this many neighbouring words (two batches of 64 ranks), dealt to the blocks round robin
 static const int AUT_ENT_LDS = 64;         // token-mask-cache rows of the row's current set kept in LDS (more are read from global memory)
 static_assert(AUT_LANES_SET_MAX <= AUT_ENT_LDS, "the kernel builds for small sets keep all cache-row numbers of a row in LDS");
-static const int AUT_TABLE_LOADS = (TABLE_LDS_BUDGET + AUT_BLOCK * 16 - 1) / (AUT_BLOCK * 16);   // 16-byte pieces of the staged tables per thread
+static const int AUT_TABLE_LOADS = (TABLE_LDS_BUDGET + AUT_WAVES_MANY_ROWS * 1024 - 1) / (AUT_WAVES_MANY_ROWS * 1024);   // 16-byte pieces of the staged tables per thread
 static const int AUT_HELP_QUEUE = 512;     // transitions one block can leave for free wavefronts in the course of a launch
 static const int AUT_STATES_DEFAULT = 64;  // automaton states a block can hold (more when LDS allows and the grammar is small)
 static const int AUT_SPIN_LIMIT = 1 << 16; // polls of a transition another wavefront is computing before giving the strings to the fallback
@@ -235,7 +238,8 @@ struct MaskArgs {
     int32_t aut_parts;         // blocks per row (grid.x)
     int32_t aut_base_sets;     // a row's chart is staged into LDS when it has at most this many sets ...
     int32_t aut_base_items;    // ... and items (both at least BASE_SETS_LDS / BASE_ITEMS_LDS)
-    int32_t aut_step;          // the kernel build (AUT_STEP_*)
+    int32_t aut_step;          // the kernel build (AUT_STEP_*) ...
+    int32_t aut_waves;         // ... and the wavefronts of its blocks
 };
 
 int choose_table_mode(const DeviceTables &t);
@@ -247,7 +251,7 @@ hipError_t prepare_automaton_kernels();
 hipError_t launch_upload(const void *pinned_src, void *dst, size_t bytes, hipStream_t s);   // bytes rounded up to 16: both buffers must hold that much
 hipError_t launch_cache_merge(const MaskArgs &a, hipStream_t s);
 hipError_t launch_mask_walk(const MaskArgs &a, hipStream_t s);
-uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide);
+uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide, int waves);
 int automaton_blocks_per_cu(const MaskArgs &a);   // of the build and the LDS size that a's call launches
 hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s);
 hipError_t prepare_store_kernels();

@@ -143,19 +143,22 @@ __device__ __forceinline__ int aut_help_take(const Aut &A, uint32_t lane, uint32
 
 __host__ __device__ inline uint32_t aut_round16(uint32_t x) { return (x + 15u) & ~15u; }
 
-// Grid (parts, rows).  A block takes slices of AUT_SUB_WORDS words of its row's rank-ordered bitmap in
+// Grid (parts, rows).  A block takes slices of as many words as it has threads of its row's rank-ordered bitmap in
 // turn: it merges the token-mask cache rows of the row's current set (Section 4.3: strings a terminal
 // swallows whole are valid at once), lists the strings that need the parser, and its wavefronts
 // take the list in batches of 64 strings, one lane per string.  The verdicts of a slice are
 // collected in LDS and stored once: no atomics on global memory and nothing to clear beforehand.
 //   What bounds it: the chain of byte steps that the strings of a block need one after the other (six to twelve, 3 to 10 us each),
-// not bandwidth and not the strings (a wavefront walks for 20 of 110 us).  So a pass takes a word per thread -- with 128 words a block of 64 rows
-// went through its chains in five passes, one behind the other --, and a wavefront that computes a step issues first.
+// not bandwidth and not the strings.  So a pass takes a word per thread -- with 128 words a block of 64 rows
+// went through its chains in five passes, one behind the other --, a wavefront that computes a step issues first, and a row has few
+// large blocks rather than many small ones (AUT_WAVES): 64 rows x 152,064 of the expression grammar, launches of 74 to 110 us with eight blocks of 8
+// wavefronts per row, 56 to 91 with four of 16.
 // MODE: which grammar tables are staged in LDS (0 all, 1 the small ones, 2 none).  STEP: the byte step that the build holds
 // (AUT_STEP_*; the host knows how wide the charts' sets are: it packs them).  In a build without the wide variant and its hash table a set of
 // more than 64 items fails over to the fallback pass; keeping the wide variant out keeps registers and code small.
-template <int MODE, int STEP>
-__global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
+template <int MODE, int STEP, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) {
+    constexpr uint32_t BLOCK = WAVES * 64, SUB_WORDS = BLOCK;   // words a pass takes: one per thread
     extern __shared__ __align__(16) uint8_t smem[];
     const DeviceTables &D = a.tab;
     const uint32_t tid = threadIdx.x, row = blockIdx.y, wave = tid >> 6, lane = tid & 63;
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     static_assert(AUT_TABLE_LOADS <= 7, "the staging below holds at most seven 16-byte pieces per thread");
     const uint4 *blob = reinterpret_cast<const uint4 *>(D.table_blob);
     uint4 tb0 = make_uint4(0, 0, 0, 0), tb1 = tb0, tb2 = tb0, tb3 = tb0, tb4 = tb0, tb5 = tb0, tb6 = tb0;   // named registers: an indexed array ends up in scratch memory
-#define ZF_STAGE_LOAD(u) if (tid + (u) * AUT_BLOCK < n16) tb##u = blob[tid + (u) * AUT_BLOCK];
+#define ZF_STAGE_LOAD(u) if (tid + (u) * BLOCK < n16) tb##u = blob[tid + (u) * BLOCK];
     ZF_STAGE_LOAD(0) ZF_STAGE_LOAD(1) ZF_STAGE_LOAD(2) ZF_STAGE_LOAD(3) ZF_STAGE_LOAD(4) ZF_STAGE_LOAD(5) ZF_STAGE_LOAD(6)
 #undef ZF_STAGE_LOAD
     Aut A;
@@ -186,9 +189,9 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     uint32_t *l_ent = reinterpret_cast<uint32_t *>(smem + off); off += AUT_ENT_LDS * 4;
     uint8_t *l_rep = smem + off; off += 256;
     A.rep = l_rep;
-    uint32_t *vslice = reinterpret_cast<uint32_t *>(smem + off); off += AUT_SUB_WORDS * 4;
-    uint32_t *cslice = reinterpret_cast<uint32_t *>(smem + off); off += AUT_SUB_WORDS * 4;
-    uint8_t *pairs = smem + off; off += AUT_SUB_WORDS / 2;   // numbers of the word pairs that hold undecided strings
+    uint32_t *vslice = reinterpret_cast<uint32_t *>(smem + off); off += SUB_WORDS * 4;
+    uint32_t *cslice = reinterpret_cast<uint32_t *>(smem + off); off += SUB_WORDS * 4;
+    uint16_t *pairs = reinterpret_cast<uint16_t *>(smem + off); off += SUB_WORDS;   // numbers of the word pairs that hold undecided strings
     A.arena = reinterpret_cast<uint2 *>(smem + off); off += aut_round16(A.arena_cap * 8);
     uint32_t *sc_w = reinterpret_cast<uint32_t *>(smem + off) + (size_t)wave * (2 * sc_cap + (STEP == AUT_STEP_WIDE ? aut_hash_places(sc_cap) : 0u));   // the hash table belongs to the wide byte step
     uint32_t *sc_o = sc_w + sc_cap, *sc_h = sc_o + sc_cap;
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
         if (ent_fits && tid < rc.n_ent) ent_v = g_ent[tid];
     }
     const uint8_t rep_v = tid < A.ncls ? D.cls_rep[tid] : (uint8_t)0;
-#define ZF_STAGE_STORE(u) if (tid + (u) * AUT_BLOCK < n16) reinterpret_cast<uint4 *>(smem)[tid + (u) * AUT_BLOCK] = tb##u;
+#define ZF_STAGE_STORE(u) if (tid + (u) * BLOCK < n16) reinterpret_cast<uint4 *>(smem)[tid + (u) * BLOCK] = tb##u;
     ZF_STAGE_STORE(0) ZF_STAGE_STORE(1) ZF_STAGE_STORE(2) ZF_STAGE_STORE(3) ZF_STAGE_STORE(4) ZF_STAGE_STORE(5) ZF_STAGE_STORE(6)
 #undef ZF_STAGE_STORE
     if (base_fits && tid <= rc.n_sets) l_so[tid] = so_v;
@@ -226,12 +229,12 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     if (ent_fits && tid < rc.n_ent) l_ent[tid] = ent_v;
     if (tid < 256) l_rep[tid] = rep_v;
     if (base_fits) {                                         // a long chart: what the first load per thread did not cover
-        for (uint32_t k = tid + AUT_BLOCK; k <= rc.n_sets; k += AUT_BLOCK) l_so[k] = g_so[k];
-        for (uint32_t k = tid + AUT_BLOCK; k < rc.n_items; k += AUT_BLOCK) l_it[k] = g_it[k];
+        for (uint32_t k = tid + BLOCK; k <= rc.n_sets; k += BLOCK) l_so[k] = g_so[k];
+        for (uint32_t k = tid + BLOCK; k < rc.n_items; k += BLOCK) l_it[k] = g_it[k];
     }
-    for (uint32_t k = tid; k < A.states_cap * A.ncls; k += AUT_BLOCK) A.trans[k] = AT_NONE;
-    for (uint32_t k = tid; k < A.states_cap; k += AUT_BLOCK) A.hdr[k] = make_uint2(0, 0xFFFFFFFFu);
-    for (uint32_t k = tid; k < (uint32_t)AUT_HELP_QUEUE; k += AUT_BLOCK) A.hq[k] = 0;
+    for (uint32_t k = tid; k < A.states_cap * A.ncls; k += BLOCK) A.trans[k] = AT_NONE;
+    for (uint32_t k = tid; k < A.states_cap; k += BLOCK) A.hdr[k] = make_uint2(0, 0xFFFFFFFFu);
+    for (uint32_t k = tid; k < (uint32_t)AUT_HELP_QUEUE; k += BLOCK) A.hq[k] = 0;
     if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; A.ctl[7] = 0; A.ctl[8] = 0; }
     const uint32_t *b_ent = (STEP != AUT_STEP_WIDE || ent_fits) ? l_ent : g_ent;   // without the wide step: sets of at most AUT_LANES_SET_MAX items, so at most that many cache rows
     const uint32_t *b_so = (STEP != AUT_STEP_WIDE || base_fits) ? l_so : g_so;   // the build without the wide step is launched only when every chart fits:
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
     // The words of the row's bitmap are dealt to the blocks in groups of AUT_GROUP_WORDS, round robin:
     // undecided strings come in runs of thousands of neighbouring ranks (everything that begins
     // with a quote, say), and every block should get its share of each run.
-    const uint32_t n_groups = (Wr + AUT_GROUP_WORDS - 1) / AUT_GROUP_WORDS, groups_per_pass = AUT_SUB_WORDS / AUT_GROUP_WORDS;
+    const uint32_t n_groups = (Wr + AUT_GROUP_WORDS - 1) / AUT_GROUP_WORDS, groups_per_pass = SUB_WORDS / AUT_GROUP_WORDS;
     for (uint32_t j0 = 0; blockIdx.x + j0 * gridDim.x < n_groups; j0 += groups_per_pass) {
         auto word_of = [&](uint32_t t) -> uint32_t {         // the bitmap word slot t of this pass stands for, or Wr and more if none
             const uint32_t grp = blockIdx.x + (j0 + t / AUT_GROUP_WORDS) * gridDim.x;
@@ -250,7 +253,6 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
         if (tid == 0) { A.ctl[2] = 0; A.ctl[3] = 0; A.ctl[6] = 0; }
         __syncthreads();                                     // also: tables, chart and automaton set-up are in place
         // ---- every thread's word: merge the token-mask cache rows, and list the word pairs (64 ranks) that hold undecided strings ----
-        static_assert(AUT_SUB_WORDS == AUT_BLOCK, "a word per thread");
         {
             const uint32_t w = word_of(tid), r0 = w * 32u;
             uint32_t v = 0, c = rc.n_ent == 0 ? 0xFFFFFFFFu : 0u;
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
                 uint32_t at = 0;
                 if (lane == 0) at = atomicAdd(&A.ctl[3], (uint32_t)__popcll(some));
                 at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                if ((some >> lane) & 1ull) pairs[at + (uint32_t)__popcll(some & ((1ull << lane) - 1ull))] = (uint8_t)(tid >> 1);
+                if ((some >> lane) & 1ull) pairs[at + (uint32_t)__popcll(some & ((1ull << lane) - 1ull))] = (uint16_t)(tid >> 1);
             }
             uint32_t n_und = (uint32_t)__popc(want);
 #pragma unroll
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
             if (lane == 0 && n_und) atomicAdd(&A.ctl[7], n_und);
         }
         const BaseG B{b_so, b_it, rc.n_sets, b_so[rc.n_sets - 1], rc.n_items};
-        if (j0 == 0 && wave == AUT_WAVES - 1)                // meanwhile the last wavefront settles the dead transitions of the row's current set
+        if (j0 == 0 && wave == WAVES - 1)                // meanwhile the last wavefront settles the dead transitions of the row's current set
             aut_mark_dead<STEP != AUT_STEP_NARROW>(T, A.ncls, A.rep, [&](uint32_t i) { return B.it[B.last_lo + i].x; }, B.last_hi - B.last_lo, lane, [&](uint32_t c) { A.trans[c] = AT_DEAD; });
         __syncthreads();
         const uint32_t n_pairs = A.ctl[3];
@@ -303,18 +305,26 @@ __global__ __launch_bounds__(AUT_BLOCK) void mask_automaton_kernel(MaskArgs a) {
                 bool have = false, progress = false;         // a transition to compute here; something this wavefront waits for has moved
                 uint32_t rs = 0, rc = 0;
                 if (batch) {
-                    while (live) {                           // every lane follows its own string as far as the table goes
-                        if (pos < 16u) {
-                            const uint32_t q = pos >> 2;
-                            const uint32_t word = q == 0 ? c16.w[0] : (q == 1 ? c16.w[1] : (q == 2 ? c16.w[2] : c16.w[3]));
-                            c = (word >> ((pos & 3u) * 8u)) & 0xFFu;
-                        } else c = D.str_cls[soff + pos];
-                        t = lds_load(&A.trans[s * A.ncls + c]);
-                        if (t < AT_FAIL) { s = t; pos++; if (pos == len) { ok = true; live = false; } }
-                        else if (t == AT_DEAD) live = false;
-                        else if (t == AT_SINK) { ok = pos + 1 == len; live = false; }
-                        else if (t == AT_FAIL) { fail = true; live = false; }
-                        else break;                          // not there yet
+                    // Every lane follows its own string as far as the table goes; the classes at hand are a shift register.
+                    while (live) {
+                        c = c16.w[0] & 0xFFu;
+                        t = lds_load(&A.trans[__umul24(s, A.ncls) + c]);
+                        if (t == AT_NONE || t == AT_BUSY) break;             // not there yet
+                        const bool on = t < AT_FAIL;
+                        s = on ? t : s;
+                        pos++;
+                        ok = pos == len && (on || t == AT_SINK);
+                        fail = t == AT_FAIL;
+                        live = on && pos < len;
+                        c16.w[0] = __builtin_amdgcn_alignbyte(c16.w[1], c16.w[0], 1); c16.w[1] = __builtin_amdgcn_alignbyte(c16.w[2], c16.w[1], 1);
+                        c16.w[2] = __builtin_amdgcn_alignbyte(c16.w[3], c16.w[2], 1); c16.w[3] >>= 8;
+                        if (live && (pos & 15u) == 0) {      // a string beyond the classes at hand: its next sixteen
+#pragma unroll
+                            for (uint32_t k = 0; k < 16u; k++) {
+                                const uint32_t b = pos + k < len ? (uint32_t)D.str_cls[soff + pos + k] : 0u;
+                                c16.w[k >> 2] = (k & 3u) ? c16.w[k >> 2] | b << (8u * (k & 3u)) : b;
+                            }
+                        }
                     }
                     if (!__ballot(live)) break;
                     // Every waiting lane tries to claim the transition it misses, all at once (among lanes that miss
@@ -399,26 +409,30 @@ hipError_t prepare_automaton_kernels() {
     const int max_lds = 160 * 1024;
     hipError_t e;
 #define SET_ATTR(k) if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds)) != hipSuccess) return e
-#define SET_ATTRS(step) SET_ATTR((mask_automaton_kernel<0, step>)); SET_ATTR((mask_automaton_kernel<1, step>)); SET_ATTR((mask_automaton_kernel<2, step>))
-    SET_ATTRS(AUT_STEP_NARROW); SET_ATTRS(AUT_STEP_LANES); SET_ATTRS(AUT_STEP_WIDE);
+#define SET_ATTRS(step, waves) SET_ATTR((mask_automaton_kernel<0, step, waves>)); SET_ATTR((mask_automaton_kernel<1, step, waves>)); SET_ATTR((mask_automaton_kernel<2, step, waves>))
+    SET_ATTRS(AUT_STEP_NARROW, AUT_WAVES); SET_ATTRS(AUT_STEP_LANES, AUT_WAVES); SET_ATTRS(AUT_STEP_WIDE, AUT_WAVES);
+    SET_ATTRS(AUT_STEP_NARROW, AUT_WAVES_MANY_ROWS); SET_ATTRS(AUT_STEP_LANES, AUT_WAVES_MANY_ROWS); SET_ATTRS(AUT_STEP_WIDE, AUT_WAVES_MANY_ROWS);
 #undef SET_ATTRS
 #undef SET_ATTR
     return hipSuccess;
 }
 
-uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide) {
+uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide, int waves) {
+    const uint32_t sub_words = (uint32_t)waves * 64u;
     return table_bytes(t, mode) + aut_round16((uint32_t)states * (uint32_t)t.n_cls * 4) + aut_round16((uint32_t)states * 8) + aut_round16((uint32_t)states * 4) + 48 + AUT_HELP_QUEUE * 4 +
-           aut_round16(((uint32_t)base_sets + 1) * 4) + aut_round16((uint32_t)base_items * 8) + AUT_ENT_LDS * 4 + 256 + 2 * AUT_SUB_WORDS * 4 + AUT_SUB_WORDS / 2 + aut_round16((uint32_t)arena * 8) +
-           AUT_WAVES * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
+           aut_round16(((uint32_t)base_sets + 1) * 4) + aut_round16((uint32_t)base_items * 8) + AUT_ENT_LDS * 4 + 256 + 2 * sub_words * 4 + sub_words + aut_round16((uint32_t)arena * 8) +
+           (uint32_t)waves * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
 }
 static void (*automaton_kernel(const MaskArgs &a))(MaskArgs) {
     // builds of the kernel by the byte step they hold: the wide variant's code costs the others ~10 % in registers and instruction fetch
-#define ZF_BUILD(step) (a.mode == 0 ? mask_automaton_kernel<0, step> : a.mode == 1 ? mask_automaton_kernel<1, step> : mask_automaton_kernel<2, step>)
+#define ZF_BUILD_(step, waves) (a.mode == 0 ? mask_automaton_kernel<0, step, waves> : a.mode == 1 ? mask_automaton_kernel<1, step, waves> : mask_automaton_kernel<2, step, waves>)
+#define ZF_BUILD(step) (a.aut_waves == AUT_WAVES ? ZF_BUILD_(step, AUT_WAVES) : ZF_BUILD_(step, AUT_WAVES_MANY_ROWS))
     return a.aut_step == AUT_STEP_WIDE ? ZF_BUILD(AUT_STEP_WIDE) : a.aut_step == AUT_STEP_LANES ? ZF_BUILD(AUT_STEP_LANES) : ZF_BUILD(AUT_STEP_NARROW);
+#undef ZF_BUILD_
 #undef ZF_BUILD
 }
 static uint32_t automaton_lds_of(const MaskArgs &a) {
-    return automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_step == AUT_STEP_WIDE);
+    return automaton_lds_bytes(a.tab, a.mode, a.aut_states, a.aut_arena, a.aut_scratch, a.aut_base_sets, a.aut_base_items, a.aut_step == AUT_STEP_WIDE, a.aut_waves);
 }
 int automaton_blocks_per_cu(const MaskArgs &a) {
     static thread_local struct { const void *kernel; uint32_t lds; int blocks; } known = {nullptr, 0, 0};   // asked of the runtime once per size
@@ -426,12 +440,12 @@ int automaton_blocks_per_cu(const MaskArgs &a) {
     const uint32_t lds = automaton_lds_of(a);
     if (known.kernel == k && known.lds == lds) return known.blocks;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, AUT_BLOCK, lds) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, a.aut_waves * 64, lds) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
     known = {k, lds, n};
     return n;
 }
 hipError_t launch_mask_automaton(const MaskArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(automaton_kernel(a), dim3(a.aut_parts, a.batch), dim3(AUT_BLOCK), automaton_lds_of(a), s, a);
+    hipLaunchKernelGGL(automaton_kernel(a), dim3(a.aut_parts, a.batch), dim3(a.aut_waves * 64), automaton_lds_of(a), s, a);
     return hipGetLastError();
 }
 }  // namespace zf

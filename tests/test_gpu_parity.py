@@ -989,6 +989,13 @@ def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
         assert np.array_equal(got[b], want[b % len(prefixes)]), b
 
 
+@pytest.mark.parametrize("V,B", [(33001, 200), (70001, 200), (33001, 256), (33001, 257), (2048, 2)])
+def test_per_block_automaton_blocks_of_sixteen(V, B, torch_cuda, oracle_lib):
+    """The same around the passes of a block of 16 wavefronts (1,024 words), with one block per row and with several, and at the batch from which on
+    blocks are of 8 (256 compute units)."""
+    test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib)
+
+
 def test_function_transforms_raise_and_the_process_goes_on(torch_cuda, oracle_lib):
     """The wrappers of vmap and grad pass for plain GPU tensors and refuse their address: an exception of Python's, and the next plain call is right."""
     import paper_2506_01151_amd as zf
