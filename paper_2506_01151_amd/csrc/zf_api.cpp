@@ -95,6 +95,7 @@ struct DeviceSide {
     // rows and counts the union for every set of cache rows it meets, once (the sets repeat all the time).
     std::vector<uint2> h_ci_tok;                     // [Q + N][W]
     std::vector<uint32_t> ci_undecided;              // [Q + N] what a row leaves undecided by itself
+    VocabRows voc{};                                 // the DFAs as the kernels that make cache rows read them, and where the token-order rows go
     std::unordered_map<uint64_t, uint32_t> undecided_of;   // signature of a list of several cache rows -> undecided tokens
     uint32_t store_backoff = 0, store_backoff_next = 8;   // after a call the store had no room for: calls that take the per-block automaton instead
     // A call through the persistent automaton until zf_mask_wait has seen its status: the groups whose state the kernel reports,
@@ -254,20 +255,19 @@ uint32_t undecided_tokens(const std::vector<uint2> &ci_tok, size_t W, const uint
     return cnt;
 }
 
-template <class F>
-int setup_device(zf_engine *e, F rows_made) {            // rows_made: called when the host's copy of the cache rows is there
+// The device's part of an engine, in two: what needs the grammar's tables and the vocabulary as it came -- the cache rows in token order are
+// on their way when this returns --, and, when the vocabulary has been sorted (setup_device), the rest.
+int begin_device(zf_engine *e) {
     DeviceSide *d = new (std::nothrow) DeviceSide();
     if (!d) return fail(ZF_ERR_OOM, "out of memory");
     e->dev = d;
     d->device = e->opt.device;
     HIP_TRY(hipSetDevice(d->device));
     const Tables &t = e->tab;
-    const Trie &tr = e->trie;
     DeviceTables &T = d->tab;
-    T.V = e->V; T.W = e->W;                              // (count_lists reads W as soon as rows_made has been called)
+    T.V = e->V; T.W = e->W;
     int rc;
     std::vector<uint8_t> cls(t.cls, t.cls + 256);
-#define UP(field, vec, bytes) if ((rc = upload(d, vec, &T.field, bytes)) != ZF_OK) return rc
     {   // the grammar tables in one allocation, in the order the kernels lay them out in LDS, each padded
         // to 16 bytes: a block stages whatever prefix fits with one flat copy
         std::vector<uint8_t> blob;
@@ -291,65 +291,70 @@ int setup_device(zf_engine *e, F rows_made) {            // rows_made: called wh
         T.scan_off = (const uint32_t *)(dev + at[3]); T.comp_off = (const uint32_t *)(dev + at[4]); T.delta = (const uint32_t *)(dev + at[5]);
         T.scan_list = (const uint32_t *)(dev + at[6]); T.comp_list = (const uint32_t *)(dev + at[7]);
     }
-    UP(nodes, tr.nodes, nullptr); UP(parent, tr.parent, nullptr); UP(chunk_begin, tr.chunk_begin, nullptr); UP(chunk_end, tr.chunk_end, nullptr);
-    UP(chunk_anc, tr.chunk_anc, nullptr); UP(rank_of, tr.rank_of, nullptr);
-    UP(ci_valid, tr.ci_valid, nullptr); UP(ci_cd, tr.ci_cd, nullptr);
-    {   // the strings as class strings for the mask-automaton kernel
-        std::vector<uint8_t> str_cls(tr.str_bytes.size()), rep(std::max(t.n_cls, 1), 0);
-        for (size_t k = 0; k < tr.str_bytes.size(); k++) str_cls[k] = t.cls[tr.str_bytes[k]];
-        for (int b = 255; b >= 0; b--) rep[t.cls[b]] = (uint8_t)b;
-        std::vector<Str16> str16((size_t)std::max(tr.n_strings, 1), Str16{{0, 0, 0, 0}});
-        for (int r = 0; r < tr.n_strings; r++) {
-            uint8_t first[16] = {0};
-            const uint32_t n = std::min<uint32_t>(16, tr.str_off[r + 1] - tr.str_off[r]);
-            memcpy(first, str_cls.data() + tr.str_off[r], n);
-            memcpy(&str16[r], first, 16);
+    {   // the DFAs as the kernels that make cache rows read them
+        VocabRows &r = d->voc;
+        std::vector<uint32_t> first_off(1, 0), first_state;
+        for (int Y = 0; Y < t.N; Y++) {
+            for (uint16_t term : t.first_terms[Y]) first_state.push_back(t.term_start[term]);
+            first_off.push_back((uint32_t)first_state.size());
         }
-        UP(str_off, tr.str_off, nullptr); UP(str_cls, str_cls, nullptr); UP(str16, str16, nullptr); UP(cls_rep, rep, nullptr);
+        if ((rc = upload(d, t.delta, &r.delta)) != ZF_OK || (rc = upload(d, t.qflags, &r.qflags)) != ZF_OK || (rc = upload(d, first_off, &r.first_off)) != ZF_OK ||
+            (rc = upload(d, first_state, &r.first_state)) != ZF_OK) return rc;
+        r.cls = T.cls; r.Q = (uint32_t)t.Q; r.N = (uint32_t)t.N; r.n_cls = (uint32_t)t.n_cls;
     }
     if (e->store_on) {
-        // The mask kernel over the persistent automaton works in token order: every token's string as byte classes, and the
-        // rows of the token-mask cache with one bit per token (bit v = the rank-ordered row's bit for token v's string).
+        // The mask kernels over the persistent automaton work in token order: every token's string as byte classes, and the
+        // rows of the token-mask cache with one bit per token.
         const size_t V = (size_t)e->V, W = (size_t)e->W, n_rows = (size_t)(t.Q + t.N);   // a row each, of a vocabulary without a string too: the kernels read them
-        std::vector<Str16> tok16(std::max<size_t>(V, 1), Str16{{TOK_END, 0, 0, 0}});
-        for (size_t v = 0; v < V; v++) {
-            const uint32_t r = tr.rank_of[v];
-            if (r == 0xFFFFFFFFu) continue;
-            const uint32_t n = tr.str_off[r + 1] - tr.str_off[r], at_hand = std::min(n, TOK_AT_HAND);
-            uint8_t first[16] = {0};
-            for (uint32_t k = 0; k < at_hand; k++) first[k] = t.cls[tr.str_bytes[tr.str_off[r] + k]];
-            first[at_hand] = (uint8_t)(n > TOK_AT_HAND ? TOK_MORE : TOK_END);
-            memcpy(&tok16[v], first, 16);
-        }
-        std::vector<uint2> &ci_tok = d->h_ci_tok;
-        ci_tok.assign(std::max<size_t>(n_rows * W, 1), make_uint2(0, 0));
-        // A row's set bits are taken one by one and written at the tokens that carry the string (most rows -- the states of literal
-        // terminals -- hold a handful).  Tokens by string: those of string r are tok_by[tok_at[r] ..].
-        std::vector<uint32_t> tok_at((size_t)tr.n_strings + 2, 0), tok_by(V);
-        for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_at[tr.rank_of[v] + 2]++;
-        for (size_t r = 2; r < tok_at.size(); r++) tok_at[r] += tok_at[r - 1];
-        for (size_t v = 0; v < V; v++) if (tr.rank_of[v] != 0xFFFFFFFFu) tok_by[tok_at[tr.rank_of[v] + 1]++] = (uint32_t)v;
-        d->ci_undecided.assign(n_rows, 0);
-        parallel_for(n_rows, n_rows * V >= (size_t)1 << 20 ? 8 : 1, [&](size_t r) {
-            uint32_t undecided = 0;
-            for (int kind = 0; kind < 2; kind++) {
-                const uint32_t *src = (kind ? tr.ci_cd.data() : tr.ci_valid.data()) + r * tr.Wr;
-                uint2 *dst = ci_tok.data() + r * W;
-                for (size_t w = 0; w < (size_t)tr.Wr; w++)
-                    for (uint32_t bits = src[w]; bits; bits &= bits - 1) {
-                        const size_t k = w * 32 + (size_t)__builtin_ctz(bits);
-                        if (k >= (size_t)tr.n_strings) break;     // bits of the last chunk beyond the strings
-                        for (uint32_t j = tok_at[k]; j < tok_at[k + 1]; j++) {
-                            uint2 &word = dst[tok_by[j] >> 5];
-                            const uint32_t bit = 1u << (tok_by[j] & 31);
-                            if (kind) { word.y |= bit; undecided += (word.x & bit) == 0; } else word.x |= bit;
-                        }
-                    }
-            }
-            d->ci_undecided[r] = undecided;
-        });
-        rows_made();
-        UP(tok16, tok16, nullptr); UP(ci_tok, ci_tok, nullptr);
+        const int64_t *off = nullptr;
+        VocabRows &r = d->voc;
+        Str16 *tok16 = nullptr;
+        if ((rc = upload(d, e->voc_off, &off)) != ZF_OK || (rc = upload(d, e->voc_bytes, &r.bytes)) != ZF_OK || (rc = engine_alloc(d, V * sizeof(Str16), &tok16)) != ZF_OK ||
+            (rc = engine_alloc(d, n_rows * W * sizeof(uint2), &r.both)) != ZF_OK || (rc = engine_alloc(d, n_rows * 4, &r.counts)) != ZF_OK) return rc;
+        r.n = (uint32_t)V; r.words = (uint32_t)W;
+        HIP_TRY(hipMemsetAsync(r.counts, 0, n_rows * 4, nullptr));
+        HIP_TRY(launch_vocab_tokens(off, r.bytes, r.cls, r.n, tok16, nullptr));
+        HIP_TRY(launch_vocab_rows(r, off, nullptr));
+        T.tok16 = tok16; T.ci_tok = r.both;
+    }
+    return ZF_OK;
+}
+
+// The host's copy of the rows in token order, and their counts, when the kernels have made them.
+int fetch_rows(zf_engine *e) {
+    DeviceSide *d = e->dev;
+    const size_t n_rows = (size_t)(e->tab.Q + e->tab.N), W = (size_t)e->W;
+    HIP_TRY(hipSetDevice(d->device));
+    d->ci_undecided.assign(std::max<size_t>(n_rows, 1), 0);
+    d->h_ci_tok.resize(std::max<size_t>(n_rows * W, 1));
+    if (n_rows) HIP_TRY(hipMemcpy(d->ci_undecided.data(), d->voc.counts, n_rows * 4, hipMemcpyDeviceToHost));
+    if (n_rows * W) HIP_TRY(hipMemcpy(d->h_ci_tok.data(), d->voc.both, n_rows * W * sizeof(uint2), hipMemcpyDeviceToHost));
+    return ZF_OK;
+}
+
+int setup_device(zf_engine *e) {
+    DeviceSide *d = e->dev;
+    const Tables &t = e->tab;
+    const Trie &tr = e->trie;
+    DeviceTables &T = d->tab;
+    int rc;
+#define UP(field, vec, bytes) if ((rc = upload(d, vec, &T.field, bytes)) != ZF_OK) return rc
+    UP(nodes, tr.nodes, nullptr); UP(parent, tr.parent, nullptr); UP(chunk_begin, tr.chunk_begin, nullptr); UP(chunk_end, tr.chunk_end, nullptr);
+    UP(chunk_anc, tr.chunk_anc, nullptr); UP(rank_of, tr.rank_of, nullptr);
+    {   // in rank order, for the per-block automaton and the trie walk: the distinct strings as class strings, and the cache rows
+        std::vector<uint8_t> rep(std::max(t.n_cls, 1), 0);
+        for (int b = 255; b >= 0; b--) rep[t.cls[b]] = (uint8_t)b;
+        UP(str_off, tr.str_off, nullptr); UP(cls_rep, rep, nullptr);
+        const size_t n = (size_t)tr.n_strings, words = (size_t)(t.Q + t.N) * (size_t)tr.Wr;
+        VocabRows r = d->voc;
+        uint8_t *str_cls = nullptr;
+        Str16 *str16 = nullptr;
+        if ((rc = upload(d, tr.str_bytes, &r.bytes)) != ZF_OK || (rc = engine_alloc(d, tr.str_bytes.size(), &str_cls)) != ZF_OK || (rc = engine_alloc(d, n * sizeof(Str16), &str16)) != ZF_OK ||
+            (rc = engine_alloc(d, words * 4, &r.valid)) != ZF_OK || (rc = engine_alloc(d, words * 4, &r.undecided)) != ZF_OK) return rc;
+        r.both = nullptr; r.counts = nullptr; r.n = (uint32_t)n; r.words = (uint32_t)tr.Wr;
+        HIP_TRY(launch_vocab_strings(T.str_off, r.bytes, r.cls, r.n, str_cls, str16, nullptr));
+        HIP_TRY(launch_vocab_rows(r, T.str_off, nullptr));
+        T.str_cls = str_cls; T.str16 = str16; T.ci_valid = r.valid; T.ci_cd = r.undecided;
     }
     T.Q = t.Q;
 #undef UP
@@ -668,7 +673,14 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         void end() { if (thread.joinable()) { tell(stop); thread.join(); } }
         ~Explorer() { end(); }
     } explorer;
-    auto give_up = [&](int rc) { explorer.end(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
+    struct Fetcher {                                      // brings the rows in token order back while the vocabulary is being sorted
+        std::thread thread;
+        int rc = ZF_OK;
+        std::string error;
+        void end() { if (thread.joinable()) thread.join(); }
+        ~Fetcher() { end(); }
+    } fetcher;
+    auto give_up = [&](int rc) { explorer.end(); fetcher.end(); free_device(e->dev); delete e->host_aut; delete e; return rc; };
     try {
         if (!build_tables(g, e->tab)) { delete e; return ZF_ERR_GRAMMAR; }
         e->V = v->V; e->W = (v->V + 31) / 32;
@@ -687,12 +699,24 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
+        if (e->opt.device >= 0) {
+            const int rc = begin_device(e);
+            if (rc != ZF_OK) return give_up(rc);
+        }
+        if (e->store_on)
+            fetcher.thread = std::thread([e, &explorer, &fetcher]() {
+                try { fetcher.rc = fetch_rows(e); } catch (const std::bad_alloc &) { fetcher.rc = fail(ZF_ERR_OOM, "out of memory"); }
+                if (fetcher.rc == ZF_OK) explorer.tell(explorer.rows_made);
+                else fetcher.error = zf_last_error();
+            });
         build_trie(v, e->opt.chunk_strings, e->tab.cls, e->trie);
-        build_token_mask_cache(e->tab, e->trie);
+        if (e->opt.device < 0) build_token_mask_cache(e->tab, e->trie);
     } catch (const std::bad_alloc &) { return give_up(fail(ZF_ERR_OOM, "out of memory")); }
     catch (const std::system_error &) { return give_up(fail(ZF_ERR_OOM, "no thread to be had")); }
     if (e->opt.device >= 0) {
-        const int rc = setup_device(e, [&]() { explorer.tell(explorer.rows_made); });
+        int rc = setup_device(e);
+        fetcher.end();
+        if (rc == ZF_OK && fetcher.rc != ZF_OK) rc = fail(fetcher.rc, fetcher.error);
         if (rc != ZF_OK) return give_up(rc);
     }
     if (explorer.thread.joinable()) {
@@ -1010,6 +1034,7 @@ int zf_debug_host_mask(zf_engine *e, const zf_state *s, uint32_t *mask) { return
 int zf_debug_host_mask_cached(zf_engine *e, const zf_state *s, uint32_t *mask, int64_t *stats) {
     if (!e || !s || !mask || s->eng != e) return fail(ZF_ERR_INVALID_ARG, "bad argument");
     const Tables &t = e->tab;
+    host_token_mask_cache(t, e->trie);
     const Trie &tr = e->trie;
     Chart c = chart_of(s);
     const uint32_t m0 = c.n_sets();

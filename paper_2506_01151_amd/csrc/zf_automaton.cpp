@@ -109,6 +109,7 @@ using namespace zf;
 extern "C" int zf_debug_host_mask_automaton(zf_engine *e, const zf_state *s, uint32_t *mask, int64_t *stats) {
     if (!e || !s || !mask || s->eng != e) { set_error("bad argument"); return ZF_ERR_INVALID_ARG; }
     const Tables &t = e->tab;
+    host_token_mask_cache(t, e->trie);
     const Trie &tr = e->trie;
     const Chart &c = chart_of(s);
     const uint32_t m0 = c.n_sets();

@@ -86,12 +86,13 @@ struct Trie {
     int n_strings = 0;
     int chunk_ranks = 32;
     int Wr = 0;                       // words per row of a rank-ordered bitmap
-    std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]
-    std::vector<uint32_t> ci_undecided;      // [Q + N] strings of the row that are in ci_cd but not in ci_valid
+    std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]; empty in an engine with a device until somebody asks (host_token_mask_cache)
 };
 // Context-independent token-mask cache (Section 4.3): per DFA state and per nonterminal, which
 // strings are decided by the terminal alone and which need the parser.
 void build_token_mask_cache(const Tables &t, Trie &tr);
+// An engine with a device works its rows out there: the host diagnostics make the host's when they need them.
+inline void host_token_mask_cache(const Tables &t, Trie &tr) { if (tr.ci_valid.empty()) build_token_mask_cache(t, tr); }
 void build_trie(const zf_vocab_desc *v, int chunk_ranks, const uint8_t *cls, Trie &t);
 
 // ---- chart --------------------------------------------------------------------------------------

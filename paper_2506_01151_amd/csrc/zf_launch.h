@@ -273,6 +273,21 @@ hipError_t launch_gather(const MaskArgs &a, hipStream_t s);
 hipError_t scratch_init(int device);            // resolves it once per device; `device` must be current
 void *scratch_ptr(int device);                  // null before scratch_init(device) has succeeded
 hipError_t launch_clear_words(uint32_t *p, uint32_t n_words, hipStream_t s);   // a fill kernel (no memset node in a captured graph)
+// What zf_compile derives from the vocabulary on the device (zf_vocab.hip): rows of the token-mask cache over n strings, `words` words each, rows of
+// the Q DFA states and then of the N nonterminals; both: (valid, undecided) pairs, or valid and undecided apart; counts: [Q + N] undecided strings per row,
+// added to (null: not counted).  first_off / first_state: per nonterminal, the start states of the terminals that can begin it.
+struct VocabRows {
+    const uint8_t *bytes, *cls, *qflags;
+    const uint16_t *delta;             // [Q][n_cls] next state, DFA_DEAD = none
+    const uint32_t *first_off, *first_state;
+    uint2 *both;
+    uint32_t *valid, *undecided, *counts;
+    uint32_t n, words, Q, N, n_cls;
+};
+hipError_t launch_vocab_rows(const VocabRows &a, const int64_t *off, hipStream_t s);    // tokens: offsets of 64 bits
+hipError_t launch_vocab_rows(const VocabRows &a, const uint32_t *off, hipStream_t s);   // strings in rank order
+hipError_t launch_vocab_tokens(const int64_t *off, const uint8_t *bytes, const uint8_t *cls, uint32_t n, Str16 *out, hipStream_t s);
+hipError_t launch_vocab_strings(const uint32_t *off, const uint8_t *bytes, const uint8_t *cls, uint32_t n, uint8_t *str_cls, Str16 *out, hipStream_t s);
 hipError_t launch_apply_mask(const void *logits, void *out, int dtype, int batch, int64_t row_stride, int V, int W,
                              const uint32_t *mask, hipStream_t s);
 

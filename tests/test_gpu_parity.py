@@ -996,6 +996,29 @@ def test_per_block_automaton_blocks_of_sixteen(V, B, torch_cuda, oracle_lib):
     test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib)
 
 
+@pytest.mark.parametrize("V", [1, 31, 32, 33, 64, 65, 255, 256, 257, 2500])
+@pytest.mark.parametrize("walk_mode", [0, 1, 2])
+def test_token_mask_cache_made_on_the_device(V, walk_mode, torch_cuda, oracle_lib):
+    """The rows of the token-mask cache and the strings' records as the device makes them -- vocabularies around a word, a wavefront and a block, tokens beyond the
+    8, 15 and 16 bytes that are at hand and of the greatest length, empty ones among them -- against the host's walk of the trie with the host's rows."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    toks = [b'"' + b"k" * n for n in (0, 6, 7, 8, 13, 14, 15, 16, 40, 254)] + [b"", b"1" * 255, b'"a":', b"[[", b" ", b"-1.5e3"] + sorted(set(configs.CONFIGS[1].vocab(2048)))
+    toks += [b"%d" % k for k in range(10, 2500)]
+    toks = list(dict.fromkeys(toks))[:V][::-1]
+    eng = zf.Engine(grammars.json_grammar(), toks, device=0, walk_mode=walk_mode, state_cache_entries=-1, precompute_states=-1)
+    d_mask = torch.empty((1, eng.W), dtype=torch.int32, device="cuda")
+    for prefix in (b"", b"[", b'{"x', b"[1", b'{"a": -', b"tr"):
+        st = eng.new_state()
+        st.advance_bytes(prefix)
+        want, stats = st.debug_host_mask_cached()
+        for call in range(2):
+            zf.compute_mask(eng, [st], d_mask)
+            assert np.array_equal(d_mask.cpu().numpy().view(np.uint32)[0], want), (prefix, call)
+            if walk_mode == 2:
+                assert eng.mask_report().walk_chunks == stats["undecided"], (prefix, call)   # no token twice: strings and tokens count the same
+
+
 def test_function_transforms_raise_and_the_process_goes_on(torch_cuda, oracle_lib):
     """The wrappers of vmap and grad pass for plain GPU tensors and refuse their address: an exception of Python's, and the next plain call is right."""
     import paper_2506_01151_amd as zf
