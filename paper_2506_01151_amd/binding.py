@@ -295,9 +295,13 @@ class Engine(_native.EngineBase):
                          csr["rule_lhs"].ctypes.data, csr["rhs_off"].ctypes.data, csr["rhs_sym"].ctypes.data,
                          len(csr["term_kind"]), csr["term_kind"].ctypes.data, csr["term_off"].ctypes.data,
                          csr["term_data"].ctypes.data)
-        off = np.zeros(len(vocab_tokens) + 1, dtype=np.int64)
-        np.cumsum(np.fromiter(map(len, vocab_tokens), dtype=np.int64, count=len(vocab_tokens)), out=off[1:])
-        data = np.frombuffer(b"".join(vocab_tokens) or b"\0", dtype=np.uint8)   # read during the call only
+        packed = _native.pack_vocab(vocab_tokens)        # read during the call only
+        if packed is not None:
+            off, data = np.frombuffer(packed[0], dtype=np.int64), np.frombuffer(packed[1], dtype=np.uint8)
+        else:                                            # another sequence, other bytes-like items
+            off = np.zeros(len(vocab_tokens) + 1, dtype=np.int64)
+            np.cumsum(np.fromiter(map(len, vocab_tokens), dtype=np.int64, count=len(vocab_tokens)), out=off[1:])
+            data = np.frombuffer(b"".join(vocab_tokens) or b"\0", dtype=np.uint8)
         vd = VocabDesc(len(vocab_tokens), off.ctypes.data, data.ctypes.data)
         opt = Options(int(bool(pruning)), lane_item_cap, device, chunk_strings, fallback_item_cap, state_cache_entries, int(not token_mask_cache), walk_mode, precompute_states)
         h = c_vp()

@@ -49,14 +49,17 @@ struct DeviceSide {
     int device = 0;
     DeviceTables tab{};
     // What an engine keeps in device memory for its whole life is carved out of a few large allocations: a schema that a request
-    // brings along is compiled and thrown away again, and hipFree costs about 0.1 ms apiece.
+    // brings along is compiled and thrown away again, and hipFree costs about 0.1 ms apiece (so does hipHostFree).  The first is made for
+    // all that the engine is going to ask for.
     static const size_t SLAB_BYTES = (size_t)16 << 20;
     std::vector<void *> slabs;
     uint8_t *slab_next = nullptr; size_t slab_left = 0;
     // per-call buffers, grown on demand
     void *d_chart = nullptr; size_t chart_cap = 0;
     static const int N_SLOTS = 4;                    // calls that may be in flight before zf_mask_wait
-    void *h_stage[N_SLOTS] = {nullptr, nullptr, nullptr, nullptr}; size_t stage_cap[N_SLOTS] = {0, 0, 0, 0};   // pinned
+    void *h_block = nullptr;                         // pinned: the status words, and the room that every slot has from the start
+    void *h_stage[N_SLOTS] = {nullptr, nullptr, nullptr, nullptr}; size_t stage_cap[N_SLOTS] = {0, 0, 0, 0};   // pinned: a piece of h_block, or ...
+    bool stage_own[N_SLOTS] = {false, false, false, false};   // ... grown, an allocation of its own
     uint32_t *h_status = nullptr;                    // pinned, [N_SLOTS][8]: counters [0..3] and the call's number [4], written by each call's last kernel
     uint32_t call_seq = 0, last_seq = 0, last_slot = 0; // number of the newest call in flight and its slot
     uint32_t next_slot = 0, pending = 0;
@@ -190,6 +193,21 @@ int engine_alloc(DeviceSide *d, size_t bytes, Tv **out) {
     return ZF_OK;
 }
 
+int engine_reserve(DeviceSide *d, size_t bytes) {
+    HIP_TRY(hipMalloc((void **)&d->slab_next, bytes));
+    d->slabs.push_back(d->slab_next);
+    d->slab_left = bytes;
+    return ZF_OK;
+}
+// Pinned staging room of a slot, grown (the slot is free: its last call has been waited for).
+int grow_stage(DeviceSide *d, uint32_t slot, size_t cap) {
+    if (d->stage_own[slot]) (void)hipHostFree(d->h_stage[slot]);
+    d->h_stage[slot] = nullptr; d->stage_cap[slot] = 0; d->stage_own[slot] = false;
+    HIP_TRY(hipHostMalloc(&d->h_stage[slot], cap, hipHostMallocDefault));
+    d->stage_cap[slot] = cap; d->stage_own[slot] = true;
+    return ZF_OK;
+}
+
 template <class Tv>
 int upload(DeviceSide *d, const std::vector<Tv> &v, const Tv **out, uint32_t *bytes_out = nullptr) {
     // padded to a multiple of 16 bytes (zero filled) so that blocks can stage it with 16-byte copies
@@ -210,14 +228,13 @@ void free_device(DeviceSide *d) {
     if (d->d_tagged) (void)hipFree(d->d_tagged);
     for (void *p : d->slabs) (void)hipFree(p);
     if (d->d_chart) (void)hipFree(d->d_chart);
-    for (int k = 0; k < DeviceSide::N_SLOTS; k++) if (d->h_stage[k]) (void)hipHostFree(d->h_stage[k]);
-    if (d->h_status) (void)hipHostFree(d->h_status);
+    for (int k = 0; k < DeviceSide::N_SLOTS; k++) if (d->stage_own[k]) (void)hipHostFree(d->h_stage[k]);
+    if (d->h_block) (void)hipHostFree(d->h_block);
     if (d->d_rank_mask) (void)hipFree(d->d_rank_mask);
     if (d->d_overflow) (void)hipFree(d->d_overflow);
     if (d->d_work) (void)hipFree(d->d_work);
     if (d->d_fb_items) (void)hipFree(d->d_fb_items);
     if (d->d_fb_ss) (void)hipFree(d->d_fb_ss);
-    if (d->h_store_status) (void)hipHostFree((void *)d->h_store_status);
     for (auto &ev : d->ev) if (ev) (void)hipEventDestroy(ev);
     delete d;
 }
@@ -257,6 +274,7 @@ uint32_t undecided_tokens(const std::vector<uint2> &ci_tok, size_t W, const uint
 
 // The device's part of an engine, in two: what needs the grammar's tables and the vocabulary as it came -- the cache rows in token order are
 // on their way when this returns --, and, when the vocabulary has been sorted (setup_device), the rest.
+size_t engine_bytes(const zf_engine *e);
 int begin_device(zf_engine *e) {
     DeviceSide *d = new (std::nothrow) DeviceSide();
     if (!d) return fail(ZF_ERR_OOM, "out of memory");
@@ -266,7 +284,8 @@ int begin_device(zf_engine *e) {
     const Tables &t = e->tab;
     DeviceTables &T = d->tab;
     T.V = e->V; T.W = e->W;
-    int rc;
+    int rc = engine_reserve(d, engine_bytes(e));
+    if (rc != ZF_OK) return rc;
     std::vector<uint8_t> cls(t.cls, t.cls + 256);
     {   // the grammar tables in one allocation, in the order the kernels lay them out in LDS, each padded
         // to 16 bytes: a block stages whatever prefix fits with one flat copy
@@ -318,6 +337,17 @@ int begin_device(zf_engine *e) {
         T.tok16 = tok16; T.ci_tok = r.both;
     }
     return ZF_OK;
+}
+
+// Device memory that the engine is going to ask for, rather too much than too little (the trie has at most a node per byte of the vocabulary).
+size_t engine_bytes(const zf_engine *e) {
+    const Tables &t = e->tab;
+    const size_t V = (size_t)e->V, W = (size_t)e->W + 1, n_rows = (size_t)(t.Q + t.N), text = e->voc_bytes.size(), cap = store_cap_states(t.n_cls), ncls = (size_t)std::max(t.n_cls, 1);
+    size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * t.delta.size();
+    n += text * (sizeof(TrieNode) + 4 + 2) + (V / (size_t)e->opt.chunk_strings + 1) * (8 + CHUNK_ANC * sizeof(TrieNode)) + V * (4 + 4 + sizeof(Str16)) + n_rows * W * 8;
+    if (e->store_on) n += V * (8 + sizeof(Str16)) + text + n_rows * (W * 8 + 4) + cap * (sizeof(uint2) + ncls * 4 + 16) + STORE_CAP_ITEMS * sizeof(uint2) + (size_t)MAX_BATCH * 4;
+    if (e->opt.state_cache_entries > 0) n += (size_t)e->opt.state_cache_entries * W * 4;
+    return n;
 }
 
 // The host's copy of the rows in token order, and their counts, when the kernels have made them.
@@ -372,11 +402,14 @@ int setup_device(zf_engine *e) {
         return fail(ZF_ERR_INVALID_ARG, "lane_item_cap and the grammar tables do not fit the 160 KB of LDS");
     if ((rc = engine_alloc(d, 2 * COUNTER_SET_WORDS * 4, &d->d_counters)) != ZF_OK) return rc;     // two sets of counters (see MaskArgs::counters)
     HIP_TRY(hipMemset(d->d_counters, 0, 2 * COUNTER_SET_WORDS * 4));
-    HIP_TRY(hipHostMalloc((void **)&d->h_status, 32 * DeviceSide::N_SLOTS, hipHostMallocDefault));
-    memset(d->h_status, 0, 32 * DeviceSide::N_SLOTS);
-    for (int k = 0; k < DeviceSide::N_SLOTS; k++) {     // staging room every engine has from the start (zf_compute_mask_noalloc never grows it)
-        HIP_TRY(hipHostMalloc(&d->h_stage[k], NOALLOC_STAGE_BYTES, hipHostMallocDefault));
-        d->stage_cap[k] = NOALLOC_STAGE_BYTES;
+    {   // staging room every engine has from the start (zf_compute_mask_noalloc never grows it), and status words
+        const size_t status = 32 * DeviceSide::N_SLOTS, store_status = e->store_on ? DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8 : 0;
+        HIP_TRY(hipHostMalloc(&d->h_block, DeviceSide::N_SLOTS * NOALLOC_STAGE_BYTES + status + store_status, hipHostMallocDefault));
+        uint8_t *at = (uint8_t *)d->h_block;
+        for (int k = 0; k < DeviceSide::N_SLOTS; k++, at += NOALLOC_STAGE_BYTES) { d->h_stage[k] = at; d->stage_cap[k] = NOALLOC_STAGE_BYTES; }
+        memset(at, 0, status + store_status);
+        d->h_status = (uint32_t *)at;
+        if (e->store_on) d->h_store_status = (volatile uint64_t *)(at + status);
     }
     if (e->store_on) {
         // Room of the persistent automaton: states x byte classes transition words (at most 128 MB), 4 M items, a hash table of
@@ -391,8 +424,6 @@ int setup_device(zf_engine *e) {
         if ((rc = engine_alloc(d, 64, &G.ctl)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, (size_t)MAX_BATCH * 4, &d->d_import_root)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, 2 * STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
-        HIP_TRY(hipHostMalloc((void **)&d->h_store_status, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8, hipHostMallocDefault));
-        memset((void *)d->h_store_status, 0, DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8);
         HIP_TRY(hipMemset(d->d_tickets, 0, 2 * STORE_TICKETS * 8));
         {
             const StoreConst k{d->tab, G};
@@ -1231,11 +1262,8 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         return fail(ZF_ERR_INVALID_ARG, "zf_compute_mask_noalloc: the packed charts (" + std::to_string(total) + " bytes) exceed the staging room of " +
                                         std::to_string(d->stage_cap[slot]) + " bytes");
     if (total > d->stage_cap[slot]) {
-        if (d->h_stage[slot]) (void)hipHostFree(d->h_stage[slot]);
-        d->h_stage[slot] = nullptr; d->stage_cap[slot] = 0;
-        size_t cap = total * 2 + 4096;
-        HIP_TRY(hipHostMalloc(&d->h_stage[slot], cap, hipHostMallocDefault));
-        d->stage_cap[slot] = cap;
+        const int rc = grow_stage(d, slot, total * 2 + 4096);
+        if (rc != ZF_OK) return rc;
     }
     if (!noalloc && total > d->chart_cap) {
         HIP_TRY(hipStreamSynchronize(stream));            // earlier calls may still read the old buffer
@@ -1750,11 +1778,8 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const size_t total = off_imp + 4 * (size_t)n_imp + 16;
     if (noalloc && (total > d->stage_cap[slot] || (big && up_bytes > NOALLOC_SCRATCH_BYTES))) return STORE_NO_ROOM;
     if (total > d->stage_cap[slot]) {
-        if (d->h_stage[slot]) (void)hipHostFree(d->h_stage[slot]);
-        d->h_stage[slot] = nullptr; d->stage_cap[slot] = 0;
-        const size_t cap = total * 2 + 4096;
-        HIP_TRY(hipHostMalloc(&d->h_stage[slot], cap, hipHostMallocDefault));
-        d->stage_cap[slot] = cap;
+        const int rc = grow_stage(d, slot, total * 2 + 4096);
+        if (rc != ZF_OK) return rc;
     }
     if (big && !noalloc && up_bytes > d->chart_cap) {
         HIP_TRY(hipStreamSynchronize(stream));

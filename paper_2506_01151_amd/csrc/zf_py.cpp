@@ -237,6 +237,28 @@ PyObject *mask_wait(PyObject *, PyObject *const *args, Py_ssize_t n, PyObject *k
     return done(rc);
 }
 
+// pack_vocab(tokens): the byte strings of a list one behind the other, and where each begins (n + 1 64-bit offsets), both as bytearrays; None for anything
+// but a list of bytes.  (128,256 tokens: 0.75 ms; numpy over map(len) and a join took 3.)
+PyObject *pack_vocab(PyObject *, PyObject *list) {
+    if (!PyList_CheckExact(list)) Py_RETURN_NONE;
+    const Py_ssize_t n = PyList_GET_SIZE(list);
+    PyObject *off = PyByteArray_FromStringAndSize(nullptr, (n + 1) * (Py_ssize_t)sizeof(int64_t));
+    if (!off) return nullptr;
+    int64_t *at = (int64_t *)PyByteArray_AS_STRING(off);
+    at[0] = 0;
+    for (Py_ssize_t k = 0; k < n; k++) {
+        PyObject *t = PyList_GET_ITEM(list, k);
+        if (!PyBytes_CheckExact(t)) { Py_DECREF(off); Py_RETURN_NONE; }
+        at[k + 1] = at[k] + PyBytes_GET_SIZE(t);
+    }
+    PyObject *data = PyByteArray_FromStringAndSize(nullptr, at[n] ? at[n] : 1);
+    if (!data) { Py_DECREF(off); return nullptr; }
+    char *to = PyByteArray_AS_STRING(data);
+    to[0] = 0;
+    for (Py_ssize_t k = 0; k < n; k++) memcpy(to + at[k], PyBytes_AS_STRING(PyList_GET_ITEM(list, k)), (size_t)(at[k + 1] - at[k]));
+    return Py_BuildValue("(NN)", off, data);
+}
+
 // ---- set-up ----
 PyObject *bind_library(PyObject *, PyObject *args) {   // ({name: address}, _check, twins)
     PyObject *addr, *chk, *tw;
@@ -290,6 +312,7 @@ PyMethodDef methods[] = {
     {"compute_mask_apply_async", FAST(compute_mask_apply_async), "compute_mask_apply_async(engine, states, mask_tensor, logits, out=None)\n--\n\ncompute_mask and apply_mask of the same rows, enqueued together; pair with mask_wait(engine)."},
     {"mask_wait", FAST(mask_wait), "mask_wait(engine)\n--\n\nWait for the status of the calls in flight."},
     {"apply_mask", FAST(apply_mask), "apply_mask(engine, logits, mask_tensor, out=None)\n--\n\nlogits: torch fp32 or bf16 tensor [batch, V] (last dim contiguous) on the device."},
+    {"pack_vocab", pack_vocab, METH_O, nullptr},
     {"bind_library", bind_library, METH_VARARGS, nullptr},
     {"bind_torch", bind_torch, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};

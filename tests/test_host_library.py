@@ -500,3 +500,22 @@ def test_tensors_that_cannot_be_looked_at_raise_and_do_not_abort():
     r = subprocess.run([sys.executable, "-c", ODD_TENSORS], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.split("\n")[-2] == "38 ['vmap', 'grad', 'wait']", r.stdout
+
+
+def test_vocabulary_packed_by_the_extension_module():
+    """pack_vocab against numpy on lists of bytes, and the sequences it leaves to numpy: an engine of either has the same masks."""
+    import paper_2506_01151_amd as zf
+    from paper_2506_01151_amd import _native
+    for toks in ([], [b""], [b"", b"a", b"", b"[" * 255, b"1,"], configs.CONFIGS[1].vocab(2048)):
+        off, data = _native.pack_vocab(toks)
+        assert np.array_equal(np.frombuffer(off, dtype=np.int64), np.cumsum([0] + [len(t) for t in toks]))
+        assert bytes(data) == (b"".join(toks) or b"\0")
+    toks = configs.CONFIGS[1].vocab(512)
+    others = (tuple(toks), [bytearray(t) for t in toks], [memoryview(t) for t in toks])
+    assert all(_native.pack_vocab(o) is None for o in others)
+    masks = []
+    for o in (toks,) + others:
+        st = zf.Engine(grammars.json_grammar(), o, device=-1).new_state()
+        st.advance_bytes(b'{"a": [1')
+        masks.append(st.debug_host_mask())
+    assert all(np.array_equal(masks[0], m) for m in masks[1:])
