@@ -62,7 +62,8 @@ __device__ __forceinline__ LookTicket draw_ticket(const LookArgs &a, uint32_t fa
     t.group = blockIdx.x % a.done_groups;
     t.size = gridDim.x / a.done_groups + (t.group < gridDim.x % a.done_groups ? 1u : 0u);
     const unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
-    t.sum = atomicAdd(&a.tickets[t.group * STORE_TICKET_STRIDE], mine) + mine;
+    t.sum = mine;
+    if (t.size > 1u) t.sum += atomicAdd(&a.tickets[t.group * STORE_TICKET_STRIDE], mine);   // a block that is a group by itself has nobody to wait for
     return t;
 }
 __device__ __forceinline__ void tell_host(const LookArgs &a, const LookTicket &t) {
