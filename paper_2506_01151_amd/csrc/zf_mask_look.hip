@@ -12,7 +12,7 @@
 // put by in lanes of vector ones for the byte step's sake, 2.4 us from the group's record to its last request, 54 instructions
 // per byte of a walk.  Here the record is a quarter shorter, the cache rows are read by uniform addresses, the table row is on its
 // way before anything else, undecided tokens are listed by scattering (a few instructions per bit) instead of being searched
-// for, and a byte of the walk takes about 20 instructions: a lane that is done leaves the loop.
+// for, and a byte of the walk takes 22 instructions, the whole wavefront together.
 //
 // The logits (zf_compute_mask_apply_async).  Memory has little to do while the masks are worked out, and a launch of its own behind this one
 // pays for the gap (1.2 us), its ramp and the whole of the reading.  Masked by the wavefront that has worked their mask out they lengthen
@@ -31,6 +31,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 static const int LOOK_LC_BITS = 10;                      // the block's LDS cache of table entries: 1,024 of (key, state)
 static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
+static const uint32_t LOOK_STOP = 256;                   // beyond every class and mark: the walk of a lane has ended
 static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
 static const int LOOK_RAW = 2;                           // token-mask cache rows that are asked for whether or not there are so many
 static const unsigned long long LOOK_WAIT_TICKS = 200000000ull;   // 2 s of the 100 MHz clock: how long a wavefront with logits waits for mask words
@@ -332,25 +333,30 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
                 const Tok cur = nxt;
                 nxt = fetch(b0 + 64);                        // (behind the last batch: the list's first token again)
                 // One lane per token: it follows its string through the table for as long as there is a state and a next byte.  The
-                // classes at hand are a shift register; a mark ends them.
-                uint32_t w0 = cur.s[0], w1 = cur.s[1], w2 = cur.s[2], w3 = cur.s[3];
-                uint32_t cl = w0 & 0xFFu, s = start, t = AT_DEAD, passed = 0;
-                bool go = b0 + lane < n && cl != TOK_END;    // an empty token is never allowed
-                uint32_t c1 = 0;                             // the class behind the one a step was taken on, or a mark
-                while (go) {
-                    const uint32_t key = __umul24(s, ncls) + cl;     // a state has at most 18 bits, a class 8
-                    const uint32_t slot = look_slot(key);
-                    const unsigned long long e = __hip_atomic_load(&lc[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    t = (uint32_t)e;
-                    if ((uint32_t)(e >> 32) != key) {
-                        t = __hip_atomic_load(&a.trans[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                        __hip_atomic_store(&lc[slot], ((unsigned long long)key << 32) | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    w0 = __builtin_amdgcn_alignbyte(w1, w0, 1); w1 = __builtin_amdgcn_alignbyte(w2, w1, 1); w2 = __builtin_amdgcn_alignbyte(w3, w2, 1); w3 >>= 8;
-                    c1 = w0 & 0xFFu;
-                    go = t < AT_FAIL && c1 < TOK_MORE;
-                    if (go) { s = t; cl = c1; }
-                    else if (t < AT_FAIL && c1 == TOK_MORE) {   // a string beyond the bytes at hand: its next fifteen classes
+                // classes at hand are a shift register; a mark ends them.  All lanes take every round; those that are done keep what they
+                // hold: 22 instructions a round, where lanes that leave the loop one by one cost twice as many, in execution masks (16 x 128,256 bf16
+                // 150 -> 143 us per 16 steps, 130 x 40,037 129 -> 122 per 8, one row x 32,000 fp32 212 -> 204 per 32).  Strings that go on are seen to between the rounds.
+                uint32_t w0 = cur.s[0], w1 = cur.s[1], w2 = cur.s[2], w3 = cur.s[3], passed = 0;
+                uint32_t c = b0 + lane < n ? w0 & 0xFFu : TOK_END;         // the next class, or what ended the walk: a mark, or LOOK_STOP + the class or mark behind the last step
+                uint32_t t = c == TOK_END ? AT_DEAD : start;               // the state or the entry that ended the walk; an empty token is never allowed
+                for (;;) {
+                    do {
+                        const bool on = c < TOK_MORE;
+                        const uint32_t key = __umul24(t, ncls) + c;        // a state has at most 18 bits, a class 8
+                        const uint32_t slot = look_slot(key);
+                        const unsigned long long e = __hip_atomic_load(&lc[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        uint32_t to = (uint32_t)e;
+                        if (on & ((uint32_t)(e >> 32) != key)) {
+                            to = __hip_atomic_load((const uint32_t *)((const uint8_t *)a.trans + (size_t)(key * 4u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            __hip_atomic_store(&lc[slot], ((unsigned long long)key << 32) | to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                        w0 = __builtin_amdgcn_alignbyte(w1, w0, 1); w1 = __builtin_amdgcn_alignbyte(w2, w1, 1); w2 = __builtin_amdgcn_alignbyte(w3, w2, 1); w3 >>= 8;
+                        const uint32_t next = (w0 & 0xFFu) | (to < AT_FAIL ? 0u : LOOK_STOP);
+                        t = on ? to : t;
+                        c = on ? next : c;
+                    } while (__ballot(c < TOK_MORE));
+                    if (!__ballot(c == TOK_MORE)) break;
+                    if (c == TOK_MORE) {                     // a string beyond the bytes at hand: its next fifteen classes
                         const DeviceTables &D = a.konst->tab;
                         const uint32_t rank = D.rank_of[g * sw * 32u + cur.at], from = D.str_off[rank], len = D.str_off[rank + 1] - from;
                         passed += TOK_AT_HAND;
@@ -361,10 +367,10 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
                             nw[0] |= k < 4u ? b : 0u; nw[1] |= (k >> 2) == 1u ? b : 0u; nw[2] |= (k >> 2) == 2u ? b : 0u; nw[3] |= (k >> 2) == 3u ? b : 0u;
                         }
                         w0 = nw[0]; w1 = nw[1]; w2 = nw[2]; w3 = nw[3];
-                        s = t; cl = w0 & 0xFFu; go = true;
+                        c = w0 & 0xFFu;
                     }
                 }
-                if (c1 == TOK_END && (t < AT_FAIL || t == AT_SINK)) atomicOr(&vbuf[cur.at >> 5], 1u << (cur.at & 31u));
+                if ((c & 0xFFu) == TOK_END && (t < AT_FAIL || t == AT_SINK)) atomicOr(&vbuf[cur.at >> 5], 1u << (cur.at & 31u));
                 // an entry that is not there, or stands for no room: the host was wrong about the state, the call fails
                 failed += (uint32_t)__popcll(__ballot(t == AT_NONE || t == AT_BUSY || t == AT_FAIL));
             }
