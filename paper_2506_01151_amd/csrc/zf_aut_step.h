@@ -158,7 +158,9 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
 // narrow variant, and the lanes make candidates in parallel as in the wide one -- in Complete the items of the completed items' origin sets
 // are dealt to the lanes, then the entries of the table that they hit.  Only distinct candidates are entered in turn, each through compares
 // whose results are scalars.  No hash table to clear, no set in LDS to probe: sources of 9 to 16 items, 64 rows of the expression grammar
-// without pruning, 8 steps of a decode loop: 1,215 us through the wide variant, 1,056 through this.  For sets of a few items with a candidate or two the
+// without pruning, 8 steps of a decode loop: 1,215 us through the wide variant, 1,056 through this.
+//   What bounds it is the length of the wavefront: a step of 11 new items took 9,900 cycles, 2,700 of them to enter 13 candidates and 2,600 to deal
+// 8 sets and lists; 7,000 with loops that have no branch but their own and hold no more than they must (the same 8 steps 788 -> 721 us).  For sets of a few items with a candidate or two the
 // dealing costs more than it saves (per-block automaton, 16 rows of a JSON schema: 61 us per step with the narrow variant, 65 with this; trie walk 103
 // and 125).
 static const int AUT_LANES_TRIES = 96;    // distinct candidates per round, summed up, after which this variant hands the step to the wide one (HAND_OVER)
@@ -169,107 +171,119 @@ __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint3
     uint32_t ns;
     S.view(cur, src, ns);
     uint32_t nw = 0xFFFFFFFFu, no = 0, nnew = 0, tries = 0;  // no item word is all ones
-    bool failed = false;                                     // sticky: the step runs on and reports at its end
     const uint32_t room = sc_cap < 64u ? sc_cap : 64u;
     auto equal = [&](uint32_t x, uint32_t s) -> unsigned long long { return __builtin_amdgcn_uicmp(x, s, 32 /* equal */); };   // the lanes on which x is s, as a scalar
-    auto insert = [&](bool has, uint32_t w, uint32_t o) __attribute__((always_inline)) {   // per-lane arguments: every lane with `has` brings a candidate
+    // Per-lane arguments: every lane with `has` brings a candidate.  One round per distinct one, without a branch in it (with branches for what is in
+    // the set already, and for no room, a round took 190 cycles).  Items beyond the room are counted, not kept: the step runs on and reports at its end.
+    auto insert = [&](bool has, uint32_t w, uint32_t o) __attribute__((always_inline)) {
         unsigned long long todo = __ballot(has);
-        while (todo) {                                       // once per distinct candidate
+        while (todo) {
             const int l = __ffsll((long long)todo) - 1;
             const uint32_t lw = (uint32_t)__builtin_amdgcn_readlane((int)w, l), lo = (uint32_t)__builtin_amdgcn_readlane((int)o, l);
             todo &= ~(equal(w, lw) & equal(o, lo));
-            tries++;
-            if (equal(nw, lw) & equal(no, lo)) continue;     // in the set already
-            if (nnew < room) {
-                const bool at = lane == nnew;
-                nw = at ? lw : nw; no = at ? lo : no;
-                nnew++;
-            } else failed = true;
+            const bool fresh = (equal(nw, lw) & equal(no, lo)) == 0;
+            const bool at = lane == (fresh ? nnew : 64u);
+            nw = at ? lw : nw; no = at ? lo : no;
+            nnew += fresh ? 1u : 0u;
+            if (HAND_OVER) tries++;
         }
     };
-    auto chain = [&](bool on, uint32_t p, uint32_t o) __attribute__((always_inline)) {     // per lane: the dot arrives at p; skip nullable nonterminals, canonical END item
+    auto nullable = [&](uint32_t w) { return !(w & (IW_END | IW_TERM)) && (w & IW_NT_NULLABLE); };
+    // Per lane: the item with the dot at p is a candidate, and where it waits for a nullable nonterminal so is the one behind (the canonical END item ends the chain).
+    auto chain = [&](bool on, uint32_t w, uint32_t p, uint32_t o) __attribute__((always_inline)) {
         while (__ballot(on)) {
-            uint32_t w = 0;
-            if (on) w = T.advpq[p];
             insert(on, w, o);
-            on = on && !(w & (IW_END | IW_TERM)) && (w & IW_NT_NULLABLE);
+            on = on && nullable(w);
             p++;
+            if (on) w = T.advpq[p];
         }
     };
     for (uint32_t s0 = 0; s0 < ns; s0 += 64) {
         uint32_t sw = IW_END, so = 0;                        // lanes beyond the set hold an inert item
         if (s0 + lane < ns) { const uint2 x = S.item(src, s0 + lane); sw = x.x; so = x.y; }
-        // Scan, both kinds of item: the DFA step of a terminal; of an item that waits for a nonterminal Y, the tabulated first steps of
-        // every terminal that can begin Y
-        uint32_t nx = DFA_DEAD, sk0 = 0, sk1 = 0;
-        if (sw & IW_TERM) nx = dfa_next(T, sw >> 16, byte, cl);
-        else if (!(sw & IW_END)) {
+        // Scan, terminal items: the DFA step, and the item behind the terminal
+        const bool term = (sw & IW_TERM) != 0;
+        uint32_t nx = DFA_DEAD, aw = 0, sk0 = 0, sk1 = 0;
+        if (term) {
+            aw = T.advpq[(sw & IW_POS_MASK) + 1];
+            nx = dfa_next(T, sw >> 16, byte, cl);
+        } else if (!(sw & IW_END)) {
             const uint32_t Y = (sw >> IW_NT_SHIFT) & IW_NT_MASK;
             sk0 = T.scan_off[Y * T.ncls + cl]; sk1 = T.scan_off[Y * T.ncls + cl + 1];
         }
-        bool one = (sw & IW_TERM) && (nx & 0xFFFFu) != DFA_DEAD;             // terminal items bring one step ...
-        uint32_t cont = (sw & 0xFFFFu) | (nx << 16), flags = nx >> 16, p = (sw & IW_POS_MASK) + 1, org = so;
-        for (;;) {                                                          // ... the others their list, a step per round
-            const bool listed = !one && sk0 < sk1;
-            if (!__ballot(one || listed)) break;
-            if (listed) { const uint2 ef = T.scan_list[sk0]; sk0++; cont = ef.x; flags = ef.y; p = (ef.x & IW_POS_MASK) + 1; org = cur; }
-            insert((one || listed) && (flags & QF_CONT), cont, org);        // no longest match: keep matching ...
-            chain((one || listed) && (flags & QF_ACCEPT), p, org);          // ... and also finish here
-            one = false;
+        const bool alive = term && (nx & 0xFFFFu) != DFA_DEAD;
+        insert(alive && ((nx >> 16) & QF_CONT), (sw & 0xFFFFu) | (nx << 16), so);   // no longest match: keep matching ...
+        chain(alive && ((nx >> 16) & QF_ACCEPT), aw, (sw & IW_POS_MASK) + 1, so);   // ... and also finish here
+        // Scan, items that wait for a nonterminal Y: the tabulated first steps of every terminal that can begin Y
+        while (__ballot(sk0 < sk1)) {
+            const bool listed = sk0 < sk1;
+            uint2 ef = make_uint2(0, 0);
+            if (listed) ef = T.scan_list[sk0++];
+            const uint32_t p = (ef.x & IW_POS_MASK) + 1;
+            if (listed) aw = T.advpq[p];
+            insert(listed && (ef.y & QF_CONT), ef.x, cur);
+            chain(listed && (ef.y & QF_ACCEPT), aw, p, cur);
         }
     }
     // Complete, until no new item is complete: the items of all completed items' origin sets -- the ones that may wait for the
     // completed nonterminal -- are dealt to the lanes, and the entries of the table that they hit are dealt again.
     unsigned long long visited = 0;
     for (;;) {
-        const unsigned long long todo = __ballot(lane < nnew && (nw & IW_END)) & ~visited;
+        const uint32_t X = (nw & IW_POS_MASK) - T.end_base;
+        const unsigned long long todo = __ballot(lane < nnew && (nw & IW_END) && X != T.N - 1) & ~visited;   // (the start rule complete: the prefix is a sentence)
         if (!todo) break;
         visited |= todo;
-        const uint32_t X = (nw & IW_POS_MASK) - T.end_base;
         uint64_t yp = 0;
         uint32_t yn = 0;
-        if (((todo >> lane) & 1ull) && X != T.N - 1) S.view(no, yp, yn);     // the start rule complete: the prefix is a sentence
+        if ((todo >> lane) & 1ull) S.view(no, yp, yn);
         unsigned long long pend = __ballot(yn > 0);
         uint32_t from = 0;                                   // of the first pending set: items dealt so far
         while (pend) {
             if (HAND_OVER && tries > (uint32_t)AUT_LANES_TRIES) return AUT_WIDE;   // an ambiguous grammar makes hundreds of candidates, mostly duplicates
-            uint32_t base = 0, oX = 0, oo = 0, at = 0, y_lo = 0, y_hi = 0;
-            bool has = false;
-            while (pend && base < 64u) {
-                const int e = __ffsll((long long)pend) - 1;
-                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)yn, e) - from, take = left < 64u - base ? left : 64u - base;
-                const uint32_t eX = (uint32_t)__builtin_amdgcn_readlane((int)X, e), eo = (uint32_t)__builtin_amdgcn_readlane((int)no, e);
-                const uint32_t e_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yp, e), e_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yp >> 32), e);
-                if (lane - base < take) { has = true; at = from + lane - base; oX = eX; oo = eo; y_lo = e_lo; y_hi = e_hi; }
-                base += take;
-                if (take == left) { pend &= pend - 1; from = 0; } else from += take;
-            }
+            uint32_t base = 0, of = 0, at = 0;               // lanes dealt to so far; whose item this lane has, and which
+            int e;
+            do {                                             // a set takes every lane from `base` on, until the next one does
+                e = __ffsll((long long)pend) - 1;
+                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)yn, e) - from;
+                const bool mine = lane >= base;
+                of = mine ? (uint32_t)e : of; at = mine ? lane - (base - from) : at;
+                base += left; from = 0;
+                pend &= pend - 1;
+            } while (pend && base < 64u);
+            if (base > 64u) { pend |= 1ull << e; from = (uint32_t)__builtin_amdgcn_readlane((int)yn, e) - (base - 64u); }   // the last set goes on in the next round
+            const bool has = lane < base;
+            const uint32_t oX = (uint32_t)__shfl((int)X, (int)of), oo = (uint32_t)__shfl((int)no, (int)of);
+            const uint64_t ys = (uint64_t)(uint32_t)__shfl((int)(uint32_t)(yp >> 32), (int)of) << 32 | (uint32_t)__shfl((int)(uint32_t)yp, (int)of);
             uint32_t yw = IW_END, yo = 0, c0 = 0, c1 = 0;
-            if (has) { const uint2 y = S.item((uint64_t)y_hi << 32 | y_lo, at); yw = y.x; yo = y.y; }
+            if (has) { const uint2 y = S.item(ys, at); yw = y.x; yo = y.y; }
             if (!(yw & (IW_TERM | IW_END))) { const uint32_t k = ((yw >> IW_NT_SHIFT) & IW_NT_MASK) * T.N + oX; c0 = T.comp_off[k]; c1 = T.comp_off[k + 1]; }
             unsigned long long hits = __ballot(c0 < c1);
-            uint32_t done = 0;                               // of the first hit's list: entries dealt so far
             while (hits) {
-                uint32_t dealt = 0, entry = 0, o = 0, p = 0, po = 0;
-                bool mine = false;
-                while (hits && dealt < 64u) {
-                    const int l = __ffsll((long long)hits) - 1;
-                    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)c0, l) + done, left = (uint32_t)__builtin_amdgcn_readlane((int)c1, l) - first;
-                    const uint32_t take = left < 64u - dealt ? left : 64u - dealt;
-                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)oo, l), lw = (uint32_t)__builtin_amdgcn_readlane((int)yw, l), ly = (uint32_t)__builtin_amdgcn_readlane((int)yo, l);
-                    if (lane - dealt < take) { mine = true; entry = first + lane - dealt; o = lo; p = (lw & IW_POS_MASK) + 1; po = ly; }
-                    dealt += take;
-                    if (take == left) { hits &= hits - 1; done = 0; } else done += take;
-                }
-                uint32_t cw = 0;
+                uint32_t dealt = 0, by = 0, entry = 0;
+                int l;
+                do {
+                    l = __ffsll((long long)hits) - 1;
+                    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)c0, l), last = (uint32_t)__builtin_amdgcn_readlane((int)c1, l);
+                    const bool mine = lane >= dealt;
+                    by = mine ? (uint32_t)l : by; entry = mine ? lane - (dealt - first) : entry;
+                    dealt += last - first;
+                    hits &= hits - 1;
+                } while (hits && dealt < 64u);
+                if (dealt > 64u) { hits |= 1ull << l; if (lane == (uint32_t)l) c0 = c1 - (dealt - 64u); }
+                const bool mine = lane < dealt;
+                uint32_t cw = 0, o = (uint32_t)__shfl((int)oo, (int)by), p = ((uint32_t)__shfl((int)yw, (int)by) & IW_POS_MASK) + 1;
+                const uint32_t po = (uint32_t)__shfl((int)yo, (int)by);
                 if (mine) cw = T.comp_list[entry];
                 const bool self = mine && cw == 0xFFFFFFFFu; // the waiting nonterminal itself is complete: the waiting item moves on
-                insert(mine && !self, cw, o);
-                chain(self, p, po);
+                if (self) { cw = T.advpq[p]; o = po; }
+                insert(mine, cw, o);
+                const bool on = self && nullable(cw);
+                if (on) cw = T.advpq[p + 1];
+                chain(on, cw, p + 1, po);
             }
         }
     }
-    if (failed) return nnew >= 64u ? AUT_WIDE : AUT_OVER;
+    if (nnew > room) return room == 64u ? AUT_WIDE : AUT_OVER;
     // completed items are needed only while their own set is processed: store the others
     const bool keep = lane < nnew && !(nw & IW_END);
     const unsigned long long kb = __ballot(keep);

@@ -37,15 +37,26 @@ struct Aut {               // one block's automaton; every pointer leads into LD
 static const uint32_t HQ_VALID = 0x80000000u;
 
 
-template <class BaseT>
-struct AutSets {           // resolves origin references
+template <class BaseT, bool IN_LDS>
+struct AutSets {           // resolves origin references.  IN_LDS: the chart is in LDS as the automaton is, and the loads say so (a generic one waits for memory as well)
     const BaseT &B;
     const Aut &A;
+    typedef const __attribute__((address_space(3))) uint32_t *lds_u32;
+    typedef const __attribute__((address_space(3))) uint2 *lds_u2;
     __device__ __forceinline__ void view(uint32_t ref, uint64_t &h, uint32_t &n) const {   // the handle is the address of the set's first item
-        if (ref & AUT_REF) { const uint2 hd = A.hdr[ref & ~AUT_REF]; h = (uint64_t)(uintptr_t)(A.arena + hd.x); n = hd.y; }
+        const bool st = (ref & AUT_REF) != 0;
+        if (IN_LDS) {                                        // one look-up for both kinds: neither waits for the other's lanes
+            const lds_u32 at = st ? (lds_u32)(A.hdr + (ref & ~AUT_REF)) : (lds_u32)(B.so + ref);
+            const uint32_t lo = at[0], hi = at[1];
+            h = (uint32_t)(uintptr_t)((st ? (lds_u2)A.arena : (lds_u2)B.it) + lo);
+            n = st ? hi : hi - lo;
+        } else if (st) { const uint2 hd = A.hdr[ref & ~AUT_REF]; h = (uint64_t)(uintptr_t)(A.arena + hd.x); n = hd.y; }
         else { const uint32_t lo = B.so[ref]; h = (uint64_t)(uintptr_t)(B.it + lo); n = B.so[ref + 1] - lo; }
     }
-    __device__ __forceinline__ uint2 item(uint64_t h, uint32_t i) const { return reinterpret_cast<const uint2 *>((uintptr_t)h)[i]; }
+    __device__ __forceinline__ uint2 item(uint64_t h, uint32_t i) const {
+        if (IN_LDS) { const lds_u32 x = (lds_u32)(uintptr_t)h + 2 * i; return make_uint2(x[0], x[1]); }
+        return reinterpret_cast<const uint2 *>((uintptr_t)h)[i];
+    }
 };
 
 // The transition of state s on class cl: take the byte step, then find the state that holds the
@@ -54,7 +65,7 @@ struct AutSets {           // resolves origin references
 template <int STEP, class BaseT>
 __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, const Aut &A, uint32_t *sc_w, uint32_t *sc_o, uint32_t *sc_h, uint32_t sc_cap,
                                                    uint32_t s, uint32_t byte, uint32_t cl, uint32_t lane) {
-    const AutSets<BaseT> S{B, A};
+    const AutSets<BaseT, STEP != AUT_STEP_WIDE> S{B, A};
     const uint32_t cur = s == 0 ? B.m - 1 : (AUT_REF | s);   // the source set; also what items predicted in it get as origin
     uint32_t nnew = 0, kept = 0;
     uint64_t src_p;

@@ -1019,6 +1019,34 @@ def test_token_mask_cache_made_on_the_device(V, walk_mode, torch_cuda, oracle_li
                 assert eng.mask_report().walk_chunks == stats["undecided"], (prefix, call)   # no token twice: strings and tokens count the same
 
 
+@pytest.mark.parametrize("pruning", [False, True])
+@pytest.mark.parametrize("most", [2, 4, 5, 6, 7, 8, 12, 20, 40])
+def test_byte_step_of_growing_sums(most, pruning, torch_cuda, oracle_lib):
+    """The per-block automaton's byte steps on sums of up to `most` operators of the ambiguous grammar, every operand another origin: sets from a few items, through the step
+    for a dozen, to the wide one; origin sets and table entries to deal from fewer than the lanes of a wavefront to several times as many."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    cfg = configs.CONFIGS[5]
+    g = cfg.grammar()
+    toks = list(dict.fromkeys(cfg.vocab(700) + [b"+b" * n for n in (1, 2, 5, 9)] + [b"*(" * 4, b")" * 3, b"+(a*b)" * 2, b"a" + b"+a" * 12]))
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, state_cache_entries=-1)
+    so, ss = [], []
+    for k in range(most + 1):
+        a, b = orc.new_state(), eng.new_state()
+        p = b"(" * (k % 3) + b"a" + b"+b" * k + b"+" * (k % 2)
+        assert a.feed_bytes(p)
+        b.advance_bytes(p)
+        so.append(a)
+        ss.append(b)
+    d_mask = torch.full((len(ss), eng.W), -1, dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, ss, d_mask)
+    got = d_mask.cpu().numpy().view(np.uint32)
+    for k, a in enumerate(so):
+        assert (got[k] == a.mask(off, data, 4)).all(), k
+
+
 def test_function_transforms_raise_and_the_process_goes_on(torch_cuda, oracle_lib):
     """The wrappers of vmap and grad pass for plain GPU tensors and refuse their address: an exception of Python's, and the next plain call is right."""
     import paper_2506_01151_amd as zf
