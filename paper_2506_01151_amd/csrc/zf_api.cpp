@@ -1461,6 +1461,13 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     if (run_kernels && d->tab.n_chunks > 0) HIP_TRY(automaton ? launch_mask_automaton(a, stream) : launch_mask_walk(a, stream));
     if (prof) HIP_TRY(hipEventRecord(d->ev[1], stream));
     d->closing_kernel = true;
+    if (g_apply.out && !a.dst_row && run_kernels) {       // the closing kernel of all of the caller's rows, in their order, masks their logits along
+        const size_t esz = g_apply.dtype == 0 ? 4 : 2;
+        if ((uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0) {
+            a.logits = g_apply.logits; a.logits_out = g_apply.out; a.logit_stride = g_apply.stride; a.logit_dtype = g_apply.dtype + 1;
+            g_apply.fused = true;
+        }
+    }
     if (run_kernels) HIP_TRY(launch_finish(a, d->cus, stream));   // fallback pass (if anything was listed) + permutation; also hands the counters to the host and clears the next call's
     if (sc) HIP_TRY(launch_gather(a, stream));            // every row's finished mask from its pool slot to the caller's tensor
     if (prof) HIP_TRY(hipEventRecord(d->ev[3], stream));

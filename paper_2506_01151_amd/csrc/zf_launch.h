@@ -240,6 +240,11 @@ struct MaskArgs {
     int32_t aut_base_items;    // ... and items (both at least BASE_SETS_LDS / BASE_ITEMS_LDS)
     int32_t aut_step;          // the kernel build (AUT_STEP_*) ...
     int32_t aut_waves;         // ... and the wavefronts of its blocks
+    // logits that the closing kernel masks along (zf_compute_mask_apply_async; dst_row is null then)
+    const void *logits;        // [batch] rows, logit_stride elements apart
+    void *logits_out;
+    int64_t logit_stride;
+    int32_t logit_dtype;       // 0: none, 1: fp32, 2: bf16
 };
 
 int choose_table_mode(const DeviceTables &t);

@@ -490,40 +490,68 @@ __device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, ui
 // together with the wavefronts it waits for, whatever the order the blocks were started in, and the
 // fallback wavefronts wait for nothing, so the wait ends.  It is bounded all the same, and running
 // into the bound makes the call fail with ZF_ERR_OVERFLOW.
-//   Permutation: verdicts are produced in trie order, the caller wants bit v at word v >> 5.  One lane
-// per token and PERMUTE_ROWS rows looks the token's rank up once, and a wavefront ballot packs 64
-// verdicts into two words.
-//   Hand-over: see hand_over (zf_kernel_common.h).
-static const int FINISH_BLOCK = 256;
-static const int FINISH_WAVES = FINISH_BLOCK / 64;
+//   Permutation: verdicts are produced in trie order, the caller wants bit v at word v >> 5.  A lane takes four neighbouring tokens of
+// PERMUTE_ROWS rows: four ranks, the four rows' words of each, four bits a row; eight lanes put a mask word together.
+//   Logits (zf_compute_mask_apply_async): the lane that has a token's bits masks its logits along.  They are requested with the ranks, before
+// anything is known of the mask, so that the reading of a pass hides the look-ups of the one before.
+//   Hand-over: see hand_over (zf_kernel_common.h).  With nothing listed the status is final when this kernel starts, and is handed over first.
 static const int PERMUTE_ROWS = 4;
-static const int PERMUTE_AHEAD = 4;                   // rank look-ups a thread has in flight
+static const uint32_t PERMUTE_TOKENS = 4;             // neighbouring tokens of a lane
 static const uint32_t FINISH_SPIN_LIMIT = 1u << 21;   // polls of about 2 us each
+constexpr int finish_block(bool staged) { return staged ? 512 : 256; }
+typedef uint32_t finish_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t finish_u32x2 __attribute__((ext_vector_type(2)));
+// Four logits, at any alignment of an element.
+template <int DT> struct FinishLogit { typedef uint32_t elem; typedef finish_u32x4 __attribute__((aligned(4))) piece; static const uint32_t NEG_INF = 0xFF800000u; };
+template <> struct FinishLogit<2> { typedef uint16_t elem; typedef finish_u32x2 __attribute__((aligned(2))) piece; static const uint32_t NEG_INF = 0xFF80u; };
 
-// STAGED: the block copies its rows of the rank-ordered bitmap into LDS first (PERMUTE_ROWS x Wr words) and serves a
-// long run of tokens from there: 64 lanes that look 64 unrelated ranks up in global memory are 64 cache-line requests
+// STAGED: the block copies its rows of the rank-ordered bitmap into LDS first, the four rows' words of a rank side by side (one 16-byte look-up), and
+// serves a long run of tokens from there: 64 lanes that look 64 unrelated ranks up in global memory are 64 cache-line requests
 // per instruction, which is what bounded the unstaged version (5 us at 16 rows, 16 us at 64).  The unstaged version
 // remains for vocabularies whose rows do not fit LDS and for small batches.
-template <bool STAGED>
-__global__ __launch_bounds__(FINISH_BLOCK) void finish_kernel(MaskArgs a, uint32_t tokens_per_block, uint32_t row_groups) {
-    extern __shared__ __align__(16) uint32_t rows_lds[];
+// DT: 0 no logits, 1 fp32, 2 bf16.
+template <bool STAGED, int DT>
+__global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a, uint32_t tokens_per_block, uint32_t row_groups) {
+    constexpr uint32_t BLOCK = (uint32_t)finish_block(STAGED), WAVES = BLOCK / 64, PASS = BLOCK * PERMUTE_TOKENS;
+    typedef FinishLogit<DT> L;
+    typedef typename L::elem elem;
+    typedef typename L::piece piece_t;
+    extern __shared__ __align__(16) uint4 rows_lds[];     // [Wr + 1]: the words of the group's rows; the last one is zero, for tokens without a rank
     const DeviceTables &D = a.tab;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, Wr = (uint32_t)D.Wr;
-    const uint32_t v_begin = blockIdx.x * tokens_per_block;            // a multiple of 64: a wavefront's ballot is two whole words
-    const uint32_t v_end = v_begin + tokens_per_block < (uint32_t)D.V ? v_begin + tokens_per_block : (uint32_t)D.V;
-    constexpr int AHEAD = STAGED ? PERMUTE_AHEAD : 1;
-    uint32_t r_first[AHEAD];                              // requested alongside the fallback count: they do not depend on it
+    const uint32_t tid = threadIdx.x, lane = tid & 63, Wr = (uint32_t)D.Wr, V = (uint32_t)D.V;
+    const uint32_t v_begin = blockIdx.x * tokens_per_block;            // a multiple of 256: a wavefront's tokens are eight whole words
+    const uint32_t v_end = v_begin + tokens_per_block < V ? v_begin + tokens_per_block : V;
+    struct Ahead { uint32_t r[PERMUTE_TOKENS]; piece_t x[DT ? PERMUTE_ROWS : 1]; };   // what a pass has requested
+    auto request = [&](uint32_t v, uint32_t row0, uint32_t n_rows) __attribute__((always_inline)) -> Ahead {
+        Ahead q;
 #pragma unroll
-    for (int u = 0; u < AHEAD; u++) {
-        const uint32_t v = v_begin + (uint32_t)u * FINISH_BLOCK + tid;
-        r_first[u] = v < v_end ? D.rank_of[v] : 0xFFFFFFFFu;
-    }
-    const uint32_t n_blocks = gridDim.x * gridDim.y;
+        for (uint32_t j = 0; j < PERMUTE_TOKENS; j++) q.r[j] = 0xFFFFFFFFu;
+        if (DT) {
+#pragma unroll
+            for (int k = 0; k < PERMUTE_ROWS; k++) q.x[DT ? k : 0] = piece_t{};
+        }
+        if (v + PERMUTE_TOKENS <= v_end) {
+            const finish_u32x4 r = *reinterpret_cast<const finish_u32x4 __attribute__((aligned(4))) *>(D.rank_of + v);
+#pragma unroll
+            for (uint32_t j = 0; j < PERMUTE_TOKENS; j++) q.r[j] = r[j];
+            if (DT) {
+#pragma unroll
+                for (int k = 0; k < PERMUTE_ROWS; k++)
+                    if ((uint32_t)k < n_rows) q.x[DT ? k : 0] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>((const elem *)a.logits + (size_t)(row0 + k) * (size_t)a.logit_stride + v));
+            }
+        } else {                                          // the last tokens of a vocabulary that is no multiple of four: their logits are read when they are stored
+#pragma unroll
+            for (uint32_t j = 0; j < PERMUTE_TOKENS; j++) if (v + j < v_end) q.r[j] = D.rank_of[v + j];
+        }
+        return q;
+    };
+    auto rows_of = [&](uint32_t rg) -> uint32_t { const uint32_t left = (uint32_t)a.batch - rg * PERMUTE_ROWS; return left < (uint32_t)PERMUTE_ROWS ? left : (uint32_t)PERMUTE_ROWS; };
+    Ahead next = request(v_begin + tid * PERMUTE_TOKENS, blockIdx.y * PERMUTE_ROWS, rows_of(blockIdx.y));   // does not depend on the fallback count
+    const uint32_t n_blocks = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x;
     const uint32_t n_over = a.counters[0];
     if (n_over != 0) {
-        const uint32_t lin = blockIdx.y * gridDim.x + blockIdx.x;
-        const uint32_t fb_waves = n_blocks * FINISH_WAVES < a.fb_waves ? n_blocks * FINISH_WAVES : a.fb_waves;
-        const uint32_t gw = lin * FINISH_WAVES + (tid >> 6);
+        const uint32_t fb_waves = n_blocks * WAVES < a.fb_waves ? n_blocks * WAVES : a.fb_waves;
+        const uint32_t gw = lin * WAVES + (tid >> 6);
         if (gw < fb_waves) {
             fallback_wave(a, gw, fb_waves, n_over, lane);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // its verdict bits and error counts before its count
@@ -538,55 +566,80 @@ __global__ __launch_bounds__(FINISH_BLOCK) void finish_kernel(MaskArgs a, uint32
         }
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
+    } else if (a.handoff_in_permute) hand_over(a, lin, n_blocks, false);
     for (uint32_t rg = blockIdx.y; rg < row_groups; rg += gridDim.y) {
-        const uint32_t row0 = rg * PERMUTE_ROWS;
-        const uint32_t n_rows = (uint32_t)a.batch - row0 < (uint32_t)PERMUTE_ROWS ? (uint32_t)a.batch - row0 : (uint32_t)PERMUTE_ROWS;
-        uint32_t r_ahead[AHEAD];
-#pragma unroll
-        for (int u = 0; u < AHEAD; u++) r_ahead[u] = r_first[u];
+        const uint32_t row0 = rg * PERMUTE_ROWS, n_rows = rows_of(rg);
         const uint32_t *rows = a.rank_mask + (size_t)row0 * Wr;           // the group's rows are neighbours in memory
+        if (rg != blockIdx.y) next = request(v_begin + tid * PERMUTE_TOKENS, row0, n_rows);
         if (STAGED) {
             if (rg != blockIdx.y) __syncthreads();                        // the previous group's readers are done with the LDS copy
-            const uint32_t n_words = n_rows * Wr, n16 = n_words / 4;
-            const uint4 *src = reinterpret_cast<const uint4 *>(rows);     // row0 * Wr * 4 bytes: 16-byte aligned when Wr is a multiple of 4
-            if (((size_t)row0 * Wr) % 4 == 0) {
-                for (uint32_t k = tid; k < n16; k += FINISH_BLOCK) reinterpret_cast<uint4 *>(rows_lds)[k] = src[k];
-                for (uint32_t k = n16 * 4 + tid; k < n_words; k += FINISH_BLOCK) rows_lds[k] = rows[k];
-            } else {
-                for (uint32_t k = tid; k < n_words; k += FINISH_BLOCK) rows_lds[k] = rows[k];
+#pragma unroll 5
+            for (uint32_t k = tid; k <= Wr; k += BLOCK) {
+                uint32_t w[PERMUTE_ROWS];
+#pragma unroll
+                for (int m = 0; m < PERMUTE_ROWS; m++) w[m] = k < Wr && (uint32_t)m < n_rows ? rows[(size_t)m * Wr + k] : 0u;
+                rows_lds[k] = make_uint4(w[0], w[1], w[2], w[3]);
             }
             __syncthreads();
-            rows = rows_lds;
         }
-        for (uint32_t v0 = v_begin; v0 < v_end; v0 += AHEAD * FINISH_BLOCK) {
-            uint32_t r_next[AHEAD];
+        const uint32_t my = (lane & 7u) < n_rows ? lane & 7u : 0u;         // the row whose words this lane stores
+        uint32_t *const dst = a.out_mask + (size_t)(a.dst_row ? a.dst_row[row0 + my] : row0 + my) * D.W;
+        for (uint32_t v0 = v_begin; v0 < v_end; v0 += PASS) {              // uniform over the block
+            const uint32_t v = v0 + tid * PERMUTE_TOKENS;
+            const Ahead q = next;
+            if (v0 + PASS < v_end) next = request(v + PASS, row0, n_rows); // the next pass's ranks and logits are requested before this one's are used
+            uint32_t bits[PERMUTE_ROWS] = {0, 0, 0, 0};
 #pragma unroll
-            for (int u = 0; u < AHEAD; u++) {                              // the next round's ranks are requested before this round's are used
-                const uint32_t v = v0 + (uint32_t)(AHEAD + u) * FINISH_BLOCK + tid;
-                r_next[u] = v < v_end ? D.rank_of[v] : 0xFFFFFFFFu;
+            for (uint32_t j = 0; j < PERMUTE_TOKENS; j++) {
+                const uint32_t r = q.r[j];
+                uint4 w = make_uint4(0, 0, 0, 0);
+                if (STAGED) w = rows_lds[(r >> 5) < Wr ? r >> 5 : Wr];
+                else if (r != 0xFFFFFFFFu) {
+                    w.x = rows[r >> 5];
+                    if (n_rows > 1u) w.y = rows[(size_t)Wr + (r >> 5)];
+                    if (n_rows > 2u) w.z = rows[2 * (size_t)Wr + (r >> 5)];
+                    if (n_rows > 3u) w.w = rows[3 * (size_t)Wr + (r >> 5)];
+                }
+                bits[0] |= ((w.x >> (r & 31u)) & 1u) << j; bits[1] |= ((w.y >> (r & 31u)) & 1u) << j;
+                bits[2] |= ((w.z >> (r & 31u)) & 1u) << j; bits[3] |= ((w.w >> (r & 31u)) & 1u) << j;
             }
+            uint32_t word = 0;
 #pragma unroll
-            for (int u = 0; u < AHEAD; u++) {
-                const uint32_t v = v0 + (uint32_t)u * FINISH_BLOCK + tid, r = r_ahead[u];
-                if (v0 + (uint32_t)u * FINISH_BLOCK >= v_end) break;      // uniform over the block
-                uint32_t word[PERMUTE_ROWS];
-#pragma unroll
-                for (int k = 0; k < PERMUTE_ROWS; k++)                     // all rows' words are requested before the first one is used
-                    word[k] = (r != 0xFFFFFFFFu && (uint32_t)k < n_rows) ? rows[(size_t)k * Wr + (r >> 5)] : 0u;
-                const uint32_t w = v >> 5;
+            for (int k = 0; k < PERMUTE_ROWS; k++) {
+                uint32_t x = bits[k] << (4u * (lane & 7u));
+                x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm 1 0 3 2 */, 0xF, 0xF, true);
+                x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm 2 3 0 1 */, 0xF, 0xF, true);
+                x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141 /* row_half_mirror */, 0xF, 0xF, true);
+                word = (lane & 7u) == (uint32_t)k ? x : word;
+            }
+            if ((lane & 7u) < n_rows && (v & ~31u) < v_end) dst[v >> 5] = word;
+            if (DT) {
 #pragma unroll
                 for (int k = 0; k < PERMUTE_ROWS; k++) {
-                    const unsigned long long b = __ballot((word[k] >> (r & 31)) & 1u);
-                    if ((uint32_t)k < n_rows && (lane & 31) == 0 && v < v_end)   // v is the word's first token; words past the block's run belong to the next block
-                        a.out_mask[(size_t)(a.dst_row ? a.dst_row[row0 + k] : row0 + k) * D.W + w] = (uint32_t)(b >> lane);
+                    if ((uint32_t)k >= n_rows) break;
+                    const size_t at = (size_t)(row0 + k) * (size_t)a.logit_stride + v;
+                    if (v + PERMUTE_TOKENS <= v_end) {
+                        piece_t x = q.x[DT ? k : 0];
+                        if (DT == 1) {
+#pragma unroll
+                            for (int j = 0; j < 4; j++) x[DT == 1 ? j : 0] = (bits[k] >> j) & 1u ? x[DT == 1 ? j : 0] : L::NEG_INF;
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 2; j++) {
+                                const uint32_t lo = (bits[k] >> (2 * j)) & 1u ? x[j] & 0xFFFFu : L::NEG_INF, hi = (bits[k] >> (2 * j + 1)) & 1u ? x[j] >> 16 : L::NEG_INF;
+                                x[j] = lo | hi << 16;
+                            }
+                        }
+                        __builtin_nontemporal_store(x, reinterpret_cast<piece_t *>((elem *)a.logits_out + at));
+                    } else {
+                        for (uint32_t j = 0; j < PERMUTE_TOKENS; j++)
+                            if (v + j < v_end) ((elem *)a.logits_out)[at + j] = (bits[k] >> j) & 1u ? ((const elem *)a.logits)[at + j] : (elem)L::NEG_INF;
+                    }
                 }
             }
-#pragma unroll
-            for (int u = 0; u < AHEAD; u++) r_ahead[u] = r_next[u];
         }
     }
-    if (a.handoff_in_permute) hand_over(a, blockIdx.y * gridDim.x + blockIdx.x, n_blocks, n_over != 0);
+    if (a.handoff_in_permute && n_over != 0) hand_over(a, lin, n_blocks, true);
 }
 
 }  // namespace
@@ -604,7 +657,8 @@ hipError_t prepare_walk_kernels() {
     SET_ATTR(mask_walk_kernel<0>); SET_ATTR(mask_walk_kernel<1>); SET_ATTR(mask_walk_kernel<2>);
 #undef SET_ATTR
     // the closing kernel also has a static word of LDS (hand_over): leave room for it below the 160 KB
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&finish_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024)) != hipSuccess) return e;
+    for (const void *k : {reinterpret_cast<const void *>(&finish_kernel<true, 0>), reinterpret_cast<const void *>(&finish_kernel<true, 1>), reinterpret_cast<const void *>(&finish_kernel<true, 2>)})
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024)) != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -636,43 +690,41 @@ hipError_t launch_mask_walk(const MaskArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 hipError_t launch_finish(const MaskArgs &a, int cus, hipStream_t s) {
-    const uint32_t row_groups = (uint32_t)(a.batch + PERMUTE_ROWS - 1) / PERMUTE_ROWS;
-    const uint32_t lds = (uint32_t)PERMUTE_ROWS * (uint32_t)a.tab.Wr * 4u;
+    const uint32_t row_groups = (uint32_t)(a.batch + PERMUTE_ROWS - 1) / PERMUTE_ROWS, V = (uint32_t)a.tab.V;
+    const uint32_t lds = ((uint32_t)a.tab.Wr + 1u) * 16u;
     const uint32_t n_cu = (uint32_t)(cus > 0 ? cus : 256);
-    // staged: about four blocks per compute unit, each serving a run of tokens (a multiple of 64) from its LDS copy of the rows;
-    // unstaged: one block per 256 tokens, one token per thread.  Staging pays when a block's run is long enough to earn the copy
-    // back: from 1024 tokens on, with four blocks per compute unit (config 3, 16 rows: 5.1 us unstaged, 5.9 us staged with runs
-    // of 512; config 4, 64 rows: 13.4 us unstaged, 9.4 us staged with runs of 2016; one, two, eight blocks per unit: 16.2, 11.4, 12.2 us).
-    uint32_t x_blocks = ((uint32_t)a.tab.V + FINISH_BLOCK - 1) / FINISH_BLOCK;
-    const uint32_t want = (4u * n_cu + row_groups - 1) / row_groups;
-    const bool staged = lds <= 150u * 1024u && (uint32_t)a.tab.V / (want > 0 ? want : 1u) >= 1024u;
+    // staged: two blocks per compute unit, each serving a run of tokens from its LDS copy of the rows; unstaged: a pass (1,024 tokens) per block, or a
+    // wavefront's share of one (256) while that makes no more than two blocks per unit.  Staging pays when a block's run is long enough to earn the copy back.
+    const uint32_t want = (2u * n_cu + row_groups - 1) / row_groups;
+    uint32_t x_blocks = std::min<uint32_t>((V + 255u) / 256u, std::max<uint32_t>((V + 1023u) / 1024u, want));
+    const bool staged = lds <= 150u * 1024u && V / (want > 0 ? want : 1u) >= 2048u;
     if (staged && want < x_blocks) x_blocks = want;
     if (x_blocks < 1) x_blocks = 1;
     // The chip must hold the whole grid at once (blocks may wait for the fallback wavefronts of other blocks): ask the runtime how
     // many blocks a compute unit takes, and let blocks loop over row groups, then over longer token runs, when there are more.
-    static int occ[2] = {0, 0};
-    static uint32_t occ_lds = 0xFFFFFFFFu;
-    if (!occ[staged] || (staged && occ_lds != lds)) {
+    typedef void (*kernel_t)(MaskArgs, uint32_t, uint32_t);
+    static const kernel_t kernels[2][3] = {{finish_kernel<false, 0>, finish_kernel<false, 1>, finish_kernel<false, 2>}, {finish_kernel<true, 0>, finish_kernel<true, 1>, finish_kernel<true, 2>}};
+    const int dt = (int)a.logit_dtype;
+    const kernel_t kernel = kernels[staged][dt];
+    const int block = finish_block(staged);
+    static int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};
+    static uint32_t occ_lds[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+    if (!occ[staged][dt] || (staged && occ_lds[dt] != lds)) {
         int n = 0;
-        const hipError_t e = staged ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, finish_kernel<true>, FINISH_BLOCK, lds)
-                                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, finish_kernel<false>, FINISH_BLOCK, 0);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(kernel), block, staged ? lds : 0);
         if (e != hipSuccess) return e;
-        occ[staged] = n < 1 ? 1 : n;
-        if (staged) occ_lds = lds;
+        occ[staged][dt] = n < 1 ? 1 : n;
+        if (staged) occ_lds[dt] = lds;
     }
-    const uint32_t cap = (uint32_t)occ[staged] * n_cu;
+    const uint32_t cap = (uint32_t)occ[staged][dt] * n_cu;
     uint32_t y_blocks = row_groups;
     if (x_blocks * y_blocks > cap) {
         y_blocks = cap / x_blocks < 1 ? 1 : (cap / x_blocks < row_groups ? cap / x_blocks : row_groups);
         if (x_blocks * y_blocks > cap) x_blocks = cap;           // a single row group per pass and still too many blocks: longer token runs
     }
-    uint32_t tokens_per_block = (((uint32_t)a.tab.V + x_blocks - 1) / x_blocks + (staged ? 63u : (uint32_t)FINISH_BLOCK - 1)) & ~(staged ? 63u : (uint32_t)FINISH_BLOCK - 1);
-    if (tokens_per_block < 64) tokens_per_block = 64;
-    x_blocks = ((uint32_t)a.tab.V + tokens_per_block - 1) / tokens_per_block;
-    if (x_blocks < 1) x_blocks = 1;
-    dim3 grid(x_blocks, y_blocks);
-    if (staged) hipLaunchKernelGGL(finish_kernel<true>, grid, dim3(FINISH_BLOCK), lds, s, a, tokens_per_block, row_groups);
-    else hipLaunchKernelGGL(finish_kernel<false>, grid, dim3(FINISH_BLOCK), 0, s, a, tokens_per_block, row_groups);
+    const uint32_t tokens_per_block = std::max<uint32_t>(256u, ((V + x_blocks - 1) / x_blocks + 255u) & ~255u);
+    x_blocks = std::max<uint32_t>(1u, (V + tokens_per_block - 1) / tokens_per_block);
+    hipLaunchKernelGGL(kernel, dim3(x_blocks, y_blocks), dim3(block), staged ? lds : 0, s, a, tokens_per_block, row_groups);
     return hipGetLastError();
 }
 }  // namespace zf

@@ -1155,6 +1155,53 @@ def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracl
         assert bool((rest == 0x1234).all()), call   # nothing beyond the rows' ends
 
 
+@pytest.mark.parametrize("dtype,shift", [("f32", 0), ("bf16", 1)])
+@pytest.mark.parametrize("walk_mode,V,B", [(0, 1, 1), (0, 3, 2), (1, 31, 3), (0, 33, 4), (0, 255, 5), (1, 257, 6), (0, 1023, 9), (0, 1026, 64), (0, 2053, 130), (1, 8195, 70),
+                                           (0, 8195, 601), (0, 40037, 110)])
+def test_logits_masked_along_by_the_closing_kernel(walk_mode, V, B, dtype, shift, torch_cuda, oracle_lib):
+    """finish_kernel with logits and without: vocabularies that end within a lane's four tokens, a word, a wavefront's 256 and a block's pass, batches that
+    end within a group of four rows, rows at any multiple of an element, the rows in LDS (from 8,195 x 601 on) and groups of rows in turn.
+    Masks and logits are the oracle's, with nothing stored beyond the rows' ends."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    toks = (configs.CONFIGS[2].vocab(max(V, 2048))[::-1])[:V]
+    off, data = wvocab.vocab_csr(toks)
+    g = grammars.json_grammar()
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, walk_mode=walk_mode, state_cache_entries=-1)
+    prefixes = [b"", b"[", b'{"a', b"[1", b'["x', b'{"k":', b"tru"]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    at = np.arange(B) * 3 % len(prefixes)
+    wanted = np.stack([want[p] for p in at])
+    states = [eng.new_state() for _ in range(B)]
+    for s, p in zip(states, at):
+        s.advance_bytes(prefixes[p])
+    rows = zf.StateBatch(states)
+    u, i, f = (np.uint32, torch.int32, torch.float32) if dtype == "f32" else (np.uint16, torch.int16, torch.bfloat16)
+    bits = np.random.default_rng(V + B).integers(0, np.iinfo(u).max, size=(B, V), dtype=u)
+    wide = torch.zeros(B * (V + 3) + shift, dtype=i, device="cuda")
+    guard = torch.full((B + 2, eng.W), 0x1234, dtype=torch.int32, device="cuda")
+    out = torch.full((B * (V + 3) + shift,), 0x1234, dtype=i, device="cuda")
+    t, o = (x[shift:].view(B, V + 3)[:, :V] for x in (wide, out))
+    t.copy_(torch.from_numpy(bits.view(np.int32 if dtype == "f32" else np.int16)))
+    zf.compute_mask_apply_async(eng, rows, guard[1:-1], t.view(f), out=o.view(f))
+    zf.mask_wait(eng)
+    torch.cuda.synchronize()
+    assert np.array_equal(guard[1:-1].cpu().numpy().view(np.uint32), wanted)
+    assert np.ascontiguousarray(o.cpu().numpy()).view(u).tobytes() == oracle_apply(bits, wanted).tobytes()
+    rest = out.cpu()
+    rest[shift:].view(B, V + 3)[:, :V] = 0x1234
+    assert bool((rest == 0x1234).all()) and bool((guard[0] == 0x1234).all()) and bool((guard[-1] == 0x1234).all())
+    guard.fill_(0x77)
+    zf.compute_mask(eng, rows, guard[1:-1])
+    assert np.array_equal(guard[1:-1].cpu().numpy().view(np.uint32), wanted)
+
+
 @pytest.mark.parametrize("B,dtype", [(3, "bf16"), (64, "f32"), (300, "bf16")])
 def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
     """Calls of look-ups only, one behind the other with nothing synchronised between them: more of them than there are slots, records and row numbers
