@@ -551,7 +551,7 @@ __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a
     const uint32_t n_over = a.counters[0];
     if (n_over != 0) {
         const uint32_t fb_waves = n_blocks * WAVES < a.fb_waves ? n_blocks * WAVES : a.fb_waves;
-        const uint32_t gw = lin * WAVES + (tid >> 6);
+        const uint32_t gw = (tid >> 6) * n_blocks + lin;       // one to a block first: they are spread over the chip
         if (gw < fb_waves) {
             fallback_wave(a, gw, fb_waves, n_over, lane);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // its verdict bits and error counts before its count
