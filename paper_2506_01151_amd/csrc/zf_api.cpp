@@ -1414,10 +1414,12 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         const uint32_t lds_max = 160u * 1024u;
         for (;;) {
             scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;
-            n_states = AUT_STATES_DEFAULT; arena = std::max(1024, 8 * scratch);
+            auto room_for = [&](int n) { n_states = n; arena = std::max(AUT_ARENA_PER_STATE * n, 8 * scratch); };
+            room_for(AUT_STATES_DEFAULT);
             base_sets = BASE_SETS_LDS; base_items = BASE_ITEMS_LDS;
             auto lds_now = [&]() { return automaton_lds_bytes(d->tab, d->mode, n_states, arena, scratch, base_sets, base_items, step == AUT_STEP_WIDE, waves); };
             if (lds_now() > lds_max) waves = AUT_WAVES_MANY_ROWS;
+            if (waves == AUT_WAVES_MANY_ROWS && lds_now() > lds_max / 2) room_for(AUT_STATES_TIGHT);
             while (lds_now() > lds_max && arena > 2 * scratch) arena /= 2;
             while (lds_now() > lds_max && n_states > 8) n_states /= 2;
             while (lds_now() > lds_max && scratch > 32) { scratch /= 2; arena = std::max(arena / 2, 2 * scratch); }

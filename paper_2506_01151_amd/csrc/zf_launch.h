@@ -35,7 +35,10 @@ static const int AUT_ENT_LDS = 64;         // token-mask-cache rows of the row's
 static_assert(AUT_LANES_SET_MAX <= AUT_ENT_LDS, "the kernel builds for small sets keep all cache-row numbers of a row in LDS");
 static const int AUT_TABLE_LOADS = (TABLE_LDS_BUDGET + AUT_WAVES_MANY_ROWS * 1024 - 1) / (AUT_WAVES_MANY_ROWS * 1024);   // 16-byte pieces of the staged tables per thread
 static const int AUT_HELP_QUEUE = 512;     // transitions one block can leave for free wavefronts in the course of a launch
-static const int AUT_STATES_DEFAULT = 64;  // automaton states a block can hold (more when LDS allows and the grammar is small)
+// Automaton states a block can hold, and items of theirs per state (tables that leave no room for so many get fewer).  With 64, a vocabulary of a JSON grammar left thousands of
+// strings per row to the fallback pass: 8 steps of 16 rows x 32,000 without pruning 858 us, 522 with 96, 523 with 128; a first step of 256 rows x 40,037 3,300, 1,130 and
+// 370.  Blocks of 8 wavefronts keep 64 where two of them would not fit a compute unit otherwise.
+static const int AUT_STATES_DEFAULT = 128, AUT_STATES_TIGHT = 64, AUT_ARENA_PER_STATE = 16;
 static const int AUT_SPIN_LIMIT = 1 << 16; // polls of a transition another wavefront is computing before giving the strings to the fallback
 static const int FB_DEPTH_MAX = 256;
 static const int FB_WAVES = 512;           // wavefronts of the closing kernel that run the fallback pass (each has its own arena)
