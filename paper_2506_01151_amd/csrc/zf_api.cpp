@@ -1708,7 +1708,8 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     rec.groups.clear(); rec.rows.clear(); rec.undecided = 0;
     const bool use_cache = !e->opt.disable_token_mask_cache;
     size_t widest = 0, biggest_set = 0, n_spill_ent = 0, n_spill_pend = 0, n_off = 0, n_items = 0;
-    bool spill = false;
+    bool spill = false, short_rows = true;                // some record does not fit the short form; every cache row's number does
+    size_t n_more = 0;                                    // cache rows that a look-up's record does not hold
     uint32_t n_cache_rows = 0;
     c.unknown.clear();
     for (RowGroup &g : c.g)
@@ -1751,8 +1752,10 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         if (g.pooled) continue;
         n_cache_rows += g.n_ent;
         rec.undecided += (int64_t)g.undecided;
-        bool fits = g.n_ent <= (uint32_t)STORE_GROUP_ENT;
-        for (uint32_t k = 0; fits && k < g.n_ent; k++) fits = g.ents[k] < 65536u;
+        bool fits = g.n_ent <= (uint32_t)STORE_GROUP_ENT, low = g.n_ent <= LOOK_ENT_MAX;
+        for (uint32_t k = 0; low && k < g.n_ent; k++) low = g.ents[k] < 65536u;
+        if (!fits) n_more += g.n_ent - LOOK_ENT_OF_MORE;
+        fits &= low; short_rows &= low;
         if (!g.dev) {
             if (g.known) { fits &= g.lead->pending.size() <= (size_t)STORE_GROUP_PEND; n_spill_pend += g.lead->pending.size(); }
             else {
@@ -1769,18 +1772,20 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     // Look-ups only: the device's name of every group's state is known, and so is every transition its vocabulary walk can meet --
     // the mask there was computed before in this epoch of the store (a call enqueued earlier on the stream is earlier enough), or
     // the automaton was explored to its end.
-    bool look = !spill && n_imp == 0 && d->tab.W <= 65535;
+    bool look = short_rows && n_imp == 0 && d->tab.W <= 65535 && (size_t)batch + n_more <= 65535;
     for (int r = 0; r < ng && look; r++) {
         const RowGroup &g = c.g[r];
         if (g.pooled || g.dev == HostAutomaton::SINK) continue;
         look = g.dev && g.at && (A.st(g.at).walked == d->store_epoch || (d->closed_epoch == d->store_epoch && g.at < d->closed_states && g.dev == g.at));
     }
+    if (look) spill = false;
+    const size_t n_members = (size_t)batch + (look ? n_more : 0);   // behind the members: the cache rows that the records do not hold
     const bool big = ng > STORE_INLINE_GROUPS;            // records and members travel in device memory instead of the argument block
     auto align16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
     // staging: [group records][blocks][members] (uploaded when big), then what the kernels read in place
     const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
     const size_t off_block = align16(big ? (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
-    const size_t off_gof = align16(off_mem + 2 * (size_t)batch), up_bytes = align16(off_gof + (big && look && g_apply.out ? 2 * (size_t)batch : 0));
+    const size_t off_gof = align16(off_mem + 2 * n_members), up_bytes = align16(off_gof + (big && look && g_apply.out ? 2 * (size_t)batch : 0));
     const size_t off_spill = up_bytes, off_ent = align16(off_spill + (spill ? sizeof(StoreRow) * ng : 0)), off_pend = align16(off_ent + (spill ? 4 * n_spill_ent : 0));
     const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
     const size_t off_items = align16(off_so + 4 * n_off), off_imp = align16(off_items + sizeof(Item) * n_items);
@@ -1848,9 +1853,9 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         uint8_t *h = (uint8_t *)d->h_stage[slot];
         LookGroup *gr = big ? (LookGroup *)h : c.look.g;
         uint32_t *blk = (uint32_t *)(h + off_block);
-        const bool members_apart = big || batch > STORE_INLINE_ROWS;
+        const bool members_apart = big || n_members > (size_t)STORE_INLINE_ROWS;
         uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member, *gof = (uint16_t *)(h + off_gof);
-        uint32_t mem_at = 0, blk_at = 0;
+        uint32_t mem_at = 0, blk_at = 0, more_at = (uint32_t)batch;
         for (int r = 0; r < ng; r++) {
             const RowGroup &g = c.g[r];
             LookGroup &m = gr[r];
@@ -1861,7 +1866,12 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
             m.w[3] = mem_at | (uint32_t)g.n << 16;
             m.w[4] = g.slot & 0xFFFFu;
             for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;
-            for (uint32_t j = 0; j < g.n_ent; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
+            const uint32_t n_here = g.n_ent > (uint32_t)STORE_GROUP_ENT ? LOOK_ENT_OF_MORE : g.n_ent;
+            for (uint32_t j = 0; j < n_here; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
+            if (n_here < g.n_ent) {
+                m.w[4 + ((n_here + 1) >> 1)] |= more_at << (((n_here + 1) & 1u) * 16u);
+                for (uint32_t j = n_here; j < g.n_ent; j++) mem[more_at++] = (uint16_t)g.ents[j];
+            }
             for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
                 if (big && k.units) gof[mem_at] = (uint16_t)r;
                 mem[mem_at++] = (uint16_t)b;

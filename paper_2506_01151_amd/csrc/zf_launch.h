@@ -156,10 +156,12 @@ static_assert(sizeof(StoreArgs) + sizeof(StoreInline) <= 4096, "the kernel's arg
 #endif
 static const int LOOK_BLOCKS_PER_CU = ZF_LOOK_BLOCKS_PER_CU;
 static const int LOOK_WORDS = 9;
+static const uint32_t LOOK_ENT_OF_MORE = 8, LOOK_ENT_MAX = 255;
 static const int LOOK_UNIT_KB = 4;      // logits that a wavefront of mask_look_kernel holds while the mask is worked out, at most: a register quadruple per lane and KB
 struct LookGroup {                     // as StoreGroup, without what a known state does not need, in nine words:
     uint32_t w[LOOK_WORDS];            // [0] state; [1] n_ent | flags << 8 | (mask words per pass - 1) << 16; [2] first block | segments << 16;
-};                                     // [3] first member | members << 16; [4] pool row | cache row 0 << 16; [5 ..] cache rows 1, 2, ... two to a word
+};                                     // [3] first member | members << 16; [4] pool row | cache row 0 << 16; [5 ..] cache rows 1, 2, ... two to a word; of more than STORE_GROUP_ENT the first
+                                       // LOOK_ENT_OF_MORE, then where in the list of members, behind them, the others are
 struct LookInline {
     LookGroup g[STORE_INLINE_GROUPS];
     uint16_t member[STORE_INLINE_ROWS];

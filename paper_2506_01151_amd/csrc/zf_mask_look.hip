@@ -209,6 +209,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
     if (tid == 0) blk_failed = 0;
     __syncthreads();
     const uint32_t start = r[0], n_ent = r[1] & 0xFFu, sw = ((r[1] >> 16) & 0xFFu) + 1u, n_seg = r[2] >> 16, member_at = r[3] & 0xFFFFu, n_members = r[3] >> 16;
+    const uint32_t n_here = n_ent > (uint32_t)STORE_GROUP_ENT ? LOOK_ENT_OF_MORE : n_ent;   // cache rows in the record; the others are listed behind the members
     const bool pooled = (r[1] & ((uint32_t)STORE_ROW_POOLED << 8)) != 0, keep = (r[1] & ((uint32_t)STORE_ROW_KEEP << 8)) != 0, use_cache = (r[1] & ((uint32_t)STORE_ROW_CACHE << 8)) != 0;
     const uint32_t unit = part * STORE_WAVES + wave, n_units = parts * STORE_WAVES, W = a.W, V = a.V, ncls = a.ncls;
     if (unit < n_seg) {
@@ -228,12 +229,12 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
             for (int j = 1; j < LOOK_RAW; j++) q.x[j] = make_uint2(0, 0);
             return;
         }
-        if (n_ent > (uint32_t)LOOK_RAW) {
+        if (n_here > (uint32_t)LOOK_RAW) {
 #pragma unroll
-            for (int j = LOOK_RAW; j < STORE_GROUP_ENT; j++) q.y[j - LOOK_RAW] = a.cache[(size_t)((uint32_t)j < n_ent ? ent(j) : ent(0)) * W + w];
+            for (int j = LOOK_RAW; j < STORE_GROUP_ENT; j++) q.y[j - LOOK_RAW] = a.cache[(size_t)((uint32_t)j < n_here ? ent(j) : ent(0)) * W + w];
         }
 #pragma unroll
-        for (int j = 0; j < LOOK_RAW; j++) q.x[j] = a.cache[(size_t)((uint32_t)j < n_ent ? ent(j) : ent(0)) * W + w];   // (without a row: row 0, not looked at)
+        for (int j = 0; j < LOOK_RAW; j++) q.x[j] = a.cache[(size_t)((uint32_t)j < n_here ? ent(j) : ent(0)) * W + w];   // (without a row: row 0, not looked at)
     };
     Words x;
 #pragma unroll
@@ -284,6 +285,22 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
         for (int j = 0; j < LOOK_RAW; j++) { v |= x.x[j].x; c |= x.x[j].y; }
 #pragma unroll
         for (int j = 0; j < STORE_GROUP_ENT - LOOK_RAW; j++) { v |= x.y[j].x; c |= x.y[j].y; }
+        const uint32_t n_rows = stay(n_ent);
+        if (__builtin_expect(n_rows > (uint32_t)STORE_GROUP_ENT, 0)) {   // a state of many items: the rest of its cache rows, four at a time
+            const uint32_t more_at = stay(r[8]) >> 16, n_more = n_rows - LOOK_ENT_OF_MORE, wc = g * sw + lane < W ? g * sw + lane : W - 1u;
+#pragma unroll 1
+            for (uint32_t k0 = 0; k0 < n_more; k0 += 64) {
+                const uint32_t n = n_more - k0 < 64u ? n_more - k0 : 64u, ent = member_row(a, in, more_at + k0 + (lane < n ? lane : 0u));
+#pragma unroll 1
+                for (uint32_t j = 0; j < n; j += 4) {
+                    uint2 y[4];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; i++) y[i] = a.cache[(size_t)(uint32_t)__builtin_amdgcn_readlane((int)ent, (int)(j + i < n ? j + i : j)) * W + wc];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; i++) { v |= y[i].x; c |= y[i].y; }
+                }
+            }
+        }
         if (!n_ent) { v = pooled ? v : 0u; c = pooled || use_cache ? 0u : 0xFFFFFFFFu; }
         if (g + n_units < n_seg) request(g + n_units, x);    // the next segment's words travel while this one's tokens are checked
         uint32_t want = c & ~v;

@@ -1202,6 +1202,49 @@ def test_logits_masked_along_by_the_closing_kernel(walk_mode, V, B, dtype, shift
     assert np.array_equal(guard[1:-1].cpu().numpy().view(np.uint32), wanted)
 
 
+@pytest.mark.parametrize("B", [1, 5, 252, 300])
+@pytest.mark.parametrize("n", [1, 8, 9, 10, 11, 12, 13, 16, 72, 73, 140, 255, 256])
+def test_look_ups_of_states_with_many_cache_rows(n, B, torch_cuda, oracle_lib):
+    """mask_look_kernel on states whose `n` items each have a token-mask cache row of their own (n terminals have one byte in common): around the nine rows a record
+    holds, around the four that are read and the 64 that are numbered at a time, the most the short form counts and one more (the other kernel's); rows and members in the argument
+    block together and apart.  The second call is the one of look-ups."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    g = grammars.Grammar(name=f"one_byte_in_common_{n}")
+    g.set_start("S")
+    words = [b"a%03d" % k + bytes([97 + k % 26]) * (k % 5) for k in range(n)]
+    for w in words:
+        g.rule("S", [w, "E"])
+    g.rule("E", [b"!"])
+    toks = list(dict.fromkeys([b"a", b"!", b"0", b"00", b"01", b"1", b"12", b"25", b"b!", b"bb", b"a0"] + [w[1:] for w in words] + [w[1:] + b"!" for w in words[::3]] + [b"%03d" % k for k in range(0, 300, 7)] + [b"zz%d" % k for k in range(700)]))
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)
+    prefixes = [b"a", b"a0", b"", b"a"]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 4))
+    at = np.arange(B) % len(prefixes)
+    wanted = np.stack([want[p] for p in at])
+    states = [eng.new_state() for _ in range(B)]
+    for s, p in zip(states, at):
+        s.advance_bytes(prefixes[p])
+    rows = zf.StateBatch(states)
+    bits = np.random.default_rng(n + B).integers(0, 2**32, size=(B, eng.V), dtype=np.uint32)
+    t = torch.from_numpy(bits.view(np.int32)).cuda()
+    d_mask, out = torch.empty((B, eng.W), dtype=torch.int32, device="cuda"), torch.empty_like(t)
+    for call in range(3):
+        d_mask.fill_(-1); out.fill_(7)
+        zf.compute_mask_apply_async(eng, rows, d_mask, t.view(torch.float32), out=out.view(torch.float32))
+        zf.mask_wait(eng)
+        torch.cuda.synchronize()
+        assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted), call
+        assert out.cpu().numpy().view(np.uint32).tobytes() == oracle_apply(bits, wanted).tobytes(), call
+
+
 @pytest.mark.parametrize("B,dtype", [(3, "bf16"), (64, "f32"), (300, "bf16")])
 def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
     """Calls of look-ups only, one behind the other with nothing synchronised between them: more of them than there are slots, records and row numbers
