@@ -35,11 +35,11 @@ HBM_PEAK_GBS = 8000.0
 ISSUE_PEAK_GINST = 256 * 4 * 2.4
 KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_look_kernel / mask_store_kernel"}
 
-# HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one) and of apply_mask_vec_kernel, from rocprofv3
+# HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one; masks and logits) and of apply_mask_vec_kernel, from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 5604881, "apply_bytes_per_launch": 8493669, "instructions_per_launch": 3247078,
-                    "kernel_sources_sha256": "5c7227666c25381082ed945d9d6a929824cc558fd2503fa6d4796afff39de4e6"}
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 15762808, "apply_bytes_per_launch": 8493669, "instructions_per_launch": 3842486,
+                    "kernel_sources_sha256": "2b4649b8888a602943e88471e60165ed8a174d8fc7609d57b7efaa9154ed9cbc"}
 
 
 def kernel_sources_digest():
@@ -206,7 +206,7 @@ class Runner:
                 eng.apply_mask(p_logits[i % len(p_logits)], p_out, dt, self.B, row_stride, p_mask, h_stream)
                 if profile and i >= n_warm:
                     evs[k][1].record()
-            eng.mask_wait(h_stream)                     # returns once the mask kernels are complete; apply_mask may still run
+            eng.mask_wait(h_stream)                     # returns once the call's outcome is known; its kernels may still run
             if sync_steps:                              # until the masked logits are there
                 stream.synchronize()
             t2 = time.perf_counter()
@@ -397,11 +397,11 @@ def main():
     # Algorithmic bytes of one launch of the default kernel, once per state that rows of the call stand in: the token-mask-cache words
     # merged (two bitsets of W words per selected cache row), the mask words written, 16 bytes per undecided token (its first fifteen
     # byte classes and a mark), and the upload.  The other mask kernels work in string-rank order (Wr words per row,
-    # 24 bytes per undecided string).  All of them leave the logits to apply_mask.
+    # 24 bytes per undecided string).  The default kernel masks the logits as well: they are read and written.
     Wr = (info.n_strings + 31) // 32
     queued, crows = rep["queued"], rep["cache_rows"]
     if args.walk_mode == 2 and args.pruning:
-        mask_bytes = int(crows / K * W * 8 + B * W * 4 + queued / K * 16 + rep["upload_bytes"] / K)
+        mask_bytes = int(crows / K * W * 8 + B * W * 4 + queued / K * 16 + rep["upload_bytes"] / K) + 2 * B * V * esz
     elif args.walk_mode != 1:
         mask_bytes = int(crows / K * Wr * 8 + B * Wr * 4 + queued / K * 24 + rep["upload_bytes"] / K)
     else:
@@ -429,9 +429,9 @@ def main():
         "p99_mask_apply_latency_us": pct(lat, 0.99) * 1e6, "max_mask_apply_latency_us": max(lat) * 1e6,
         "mean_advance_us_per_step": statistics.fmean(adv) * 1e6,
         "pipelined_steps": {"ms_per_step": piped["total"] / K * 1e3, "value": B * V * K / piped["total"],
-                            "note": "the same steps without the stream synchronisation: a step ends when the mask kernel's status has reached the host "
-                                    "(zf_mask_wait); what is left out is the end of the logits' masking, which runs behind the mask kernel while the next step "
-                                    "is sent, and the stream's own completion signal: a decode loop whose sampler runs on the same stream does not wait for either"},
+                            "note": "the same steps without the stream synchronisation: a step ends when zf_mask_wait has returned, which is when the call's outcome is known -- "
+                                    "for a call of look-ups when it is enqueued; the passes' total ends with the stream synchronised, so every kernel is in it: "
+                                    "a decode loop whose sampler runs on the same stream"},
         "warm_automaton": {"ms_per_step": warm["total"] / K * 1e3, "value": B * V * K / warm["total"], "p50_mask_apply_latency_us": pct(warm["lat"], 0.5) * 1e6,
                            "note": "the same steps once more without clearing the persistent automaton: every transition is a look-up"},
         "kernel_ms": {k: statistics.fmean(v) for k, v in kern.items() if v},
@@ -439,7 +439,7 @@ def main():
         "kernel_ms_max": {k: max(v) for k, v in kern.items() if v},
         "two_calls": {"value": B * V * K / two["total"], "ms_per_step": two["total"] / K * 1e3, "p50_mask_apply_latency_us": pct(two["lat"], 0.5) * 1e6,
                       "kernel_ms": {k: statistics.fmean(v) for k, v in two_prof["kern"].items() if v},
-                      "note": "the same steps through zf_compute_mask_async + zf_apply_mask: the mask kernel, then apply_mask_vec_kernel (the one call enqueues the same two where every state's vocabulary has been walked before)"},
+                      "note": "the same steps through zf_compute_mask_async + zf_apply_mask: the mask kernel, then apply_mask_vec_kernel (the one call masks the logits in the kernel that works the masks out)"},
         "overflow_chunks_per_step": rep["overflow"] / K,
         ("undecided_tokens_per_step" if args.walk_mode == 2 and args.pruning else "undecided_strings_per_step") if args.walk_mode != 1 else "walk_chunks_per_step": queued / K,
         "undecided_per_s": queued / max(sum(kern["main"]) * 1e-3, 1e-12),
@@ -456,10 +456,10 @@ def main():
         "roofline": {"bound": "hbm", "kernel": kname, "achieved": mask_bytes / (main_ms * 1e-3) / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": mask_bytes / (main_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "traffic": MEASURED_TRAFFIC["bytes_per_launch"] if traffic_ok else None, "algorithmic_bytes": mask_bytes,
-                     "note": "one launch = the mask of every row, worked out once per state that rows stand in; integer work (a table walk per undecided token), "
+                     "note": "one launch = the mask of every row, worked out once per state that rows stand in, and the rows' logits masked by wavefronts of their own; integer work (a table walk per undecided token), "
                              "bounded by the chain of dependent memory round trips of a wavefront (the group's record, cache words, strings, table "
                              "entries: about 1 us each), far below the HBM roof; the event pair also spans the dispatch gap before the kernel; "
-                             "the logits' masking is a launch of its own, see roofline_apply_mask"},
+                             "roofline_apply_mask is the logits' masking as a call of its own"},
         "roofline_issue": {"bound": "alu", "kernel": kname, "unit": "G wavefront instructions/s", "peak": ISSUE_PEAK_GINST, "instructions": insts,
                            "achieved": insts / (main_ms * 1e-3) / 1e9 if insts else None,
                            "frac": insts / (main_ms * 1e-3) / 1e9 / ISSUE_PEAK_GINST if insts else None,

@@ -2193,7 +2193,7 @@ int zf_compute_mask_apply_async(zf_engine *e, zf_state *const *states, int32_t b
     const bool fused = g_apply.fused;
     g_apply = ApplyRequest{};
     if (rc != ZF_OK || fused) return rc;
-    return zf_apply_mask(e, d_logits, d_out, dtype, batch, row_stride, d_mask, hip_stream);   // the other mask kernels, the state cache, odd shapes: two launches
+    return zf_apply_mask(e, d_logits, d_out, dtype, batch, row_stride, d_mask, hip_stream);   // the trie walk, the state cache, first visits over many logits, odd addresses: two launches
 }
 
 int zf_mask_wait(zf_engine *e, void *hip_stream) {

@@ -483,7 +483,7 @@ __device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, ui
 // string-rank order into token order, in one launch.  As a kernel of its own the fallback pass costs
 // 4.5 us per call even when its list is empty (a launch and two dependent loads), and with the mask
 // automata almost every call leaves it empty.
-//   When the list is not empty, the wavefronts of the blocks with the lowest linear index walk the
+//   When the list is not empty, wavefronts of all blocks, one to a block first, walk the
 // listed chunks first and count themselves off; every block then waits for that count before it
 // reads the verdicts.  The host sizes the grid so that the chip holds all of its blocks at once
 // (blocks loop over row groups when a batch has more of them): every block that waits is resident
@@ -493,7 +493,8 @@ __device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, ui
 //   Permutation: verdicts are produced in trie order, the caller wants bit v at word v >> 5.  A lane takes four neighbouring tokens of
 // PERMUTE_ROWS rows: four ranks, the four rows' words of each, four bits a row; eight lanes put a mask word together.
 //   Logits (zf_compute_mask_apply_async): the lane that has a token's bits masks its logits along.  They are requested with the ranks, before
-// anything is known of the mask, so that the reading of a pass hides the look-ups of the one before.
+// anything is known of the mask, so that the reading of a pass hides the look-ups of the one before: 64 rows x 152,064 fp32 19.4 us, where the permutation (a token per lane
+// and four look-ups, a store for every 64 tokens and row) took 10.8 and the launch behind it 13.5; 8 steps of the expression grammar without pruning 644 -> 606 us.
 //   Hand-over: see hand_over (zf_kernel_common.h).  With nothing listed the status is final when this kernel starts, and is handed over first.
 static const int PERMUTE_ROWS = 4;
 static const uint32_t PERMUTE_TOKENS = 4;             // neighbouring tokens of a lane
