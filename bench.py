@@ -39,7 +39,7 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
 MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 15762808, "apply_bytes_per_launch": 8493669, "instructions_per_launch": 3842486,
-                    "kernel_sources_sha256": "2b4649b8888a602943e88471e60165ed8a174d8fc7609d57b7efaa9154ed9cbc"}
+                    "kernel_sources_sha256": "2842787a680504c1aa965e769abf3db15c1a6e572490b1c2f83caf09d4813d15"}
 
 
 def kernel_sources_digest():

@@ -708,8 +708,8 @@ hipError_t launch_finish(const MaskArgs &a, int cus, hipStream_t s) {
     const int dt = (int)a.logit_dtype;
     const kernel_t kernel = kernels[staged][dt];
     const int block = finish_block(staged);
-    static int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};
-    static uint32_t occ_lds[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+    static thread_local int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};   // per thread: a pair of numbers that belong together
+    static thread_local uint32_t occ_lds[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
     if (!occ[staged][dt] || (staged && occ_lds[dt] != lds)) {
         int n = 0;
         const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(kernel), block, staged ? lds : 0);
