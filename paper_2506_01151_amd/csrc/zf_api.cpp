@@ -755,6 +755,12 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         try { store_adopt(e, explorer.whole, nullptr); } catch (const std::bad_alloc &) {}   // the store starts empty, then
         explorer.thread.join();
     }
+    // The kernels that make the strings and the cache rows are on the null stream, for which the caller's need not wait: what they write is there when
+    // this returns.  (An engine without a persistent automaton has nothing behind them that waits; behind store_adopt the stream is idle.)
+    if (e->dev) {
+        const hipError_t rc = hipStreamSynchronize(nullptr);
+        if (rc != hipSuccess) return give_up(fail(ZF_ERR_DEVICE, std::string("the tables' kernels: ") + hipGetErrorString(rc)));
+    }
     *out = e;
     return ZF_OK;
 }

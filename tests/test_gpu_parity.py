@@ -996,6 +996,33 @@ def test_per_block_automaton_blocks_of_sixteen(V, B, torch_cuda, oracle_lib):
     test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib)
 
 
+@pytest.mark.parametrize("walk_mode,pruning", [(0, True), (1, True), (2, False), (2, True)])
+def test_first_call_on_a_stream_of_its_own(walk_mode, pruning, torch_cuda, oracle_lib):
+    """The first mask call of an engine, right behind zf_compile and on a stream that does not wait for the null stream: strings and cache rows, which
+    kernels on the null stream make, are there when zf_compile returns.  The masks are the oracle's."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks = configs.CONFIGS[3].grammar(), configs.CONFIGS[3].vocab()
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    prefixes = [b"", b'{"']
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    side = torch.cuda.Stream()
+    d_mask = torch.full((len(prefixes), (len(toks) + 31) // 32), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, walk_mode=walk_mode, pruning=pruning, precompute_states=-1)
+    rows = [eng.new_state() for _ in prefixes]
+    for s, p in zip(rows, prefixes):
+        s.advance_bytes(p)
+    with torch.cuda.stream(side):
+        zf.compute_mask(eng, rows, d_mask)
+    assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), np.stack(want))
+
+
 @pytest.mark.parametrize("V", [1, 31, 32, 33, 64, 65, 255, 256, 257, 2500])
 @pytest.mark.parametrize("walk_mode", [0, 1, 2])
 def test_token_mask_cache_made_on_the_device(V, walk_mode, torch_cuda, oracle_lib):
