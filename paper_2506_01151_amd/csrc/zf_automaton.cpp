@@ -185,6 +185,7 @@ extern "C" int zf_debug_twin_mask(zf_twin *tw, uint32_t state, uint32_t *mask, i
     if (!tw || !mask) { set_error("bad argument"); return ZF_ERR_INVALID_ARG; }
     zf_engine *e = tw->eng;
     const Tables &t = e->tab;
+    host_token_mask_cache(t, e->trie);
     const Trie &tr = e->trie;
     HostAutomaton &a = tw->a;
     const uint32_t root = state == 0 ? HostAutomaton::ROOT : state;

@@ -996,6 +996,29 @@ def test_per_block_automaton_blocks_of_sixteen(V, B, torch_cuda, oracle_lib):
     test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib)
 
 
+def test_host_diagnostics_of_an_engine_with_a_device(torch_cuda, oracle_lib):
+    """The host's diagnostics read token-mask cache rows that an engine with a device does not hold on the host until somebody asks: each of them,
+    the first to ask of an engine of its own."""
+    import paper_2506_01151_amd as zf
+    cfg = configs.CONFIGS[1]
+    g, toks = cfg.grammar(), cfg.vocab()
+    off, data = wvocab.vocab_csr(toks)
+    so = oracle_lib.Oracle(g).new_state()
+    assert so.feed_bytes(b'{"a": [1')
+    want = so.mask(off, data)
+
+    def twin(s):
+        t = zf.binding.Twin(s.engine)
+        rc, at, _ = t.advance(0, b'{"a": [1')
+        assert rc == 0
+        return t.mask(at)[0]
+
+    for ask in (twin, lambda s: s.debug_host_mask_cached()[0], lambda s: s.debug_host_mask_automaton()[0]):
+        s = zf.Engine(g, toks, device=0).new_state()
+        s.advance_bytes(b'{"a": [1')
+        assert np.array_equal(ask(s), want)
+
+
 @pytest.mark.parametrize("walk_mode,pruning", [(0, True), (1, True), (2, False), (2, True)])
 def test_first_call_on_a_stream_of_its_own(walk_mode, pruning, torch_cuda, oracle_lib):
     """The first mask call of an engine, right behind zf_compile and on a stream that does not wait for the null stream: strings and cache rows, which
