@@ -91,8 +91,12 @@ struct Trie {
 // Context-independent token-mask cache (Section 4.3): per DFA state and per nonterminal, which
 // strings are decided by the terminal alone and which need the parser.
 void build_token_mask_cache(const Tables &t, Trie &tr);
-// An engine with a device works its rows out there: the host diagnostics make the host's when they need them.
-inline void host_token_mask_cache(const Tables &t, Trie &tr) { if (tr.ci_valid.empty()) build_token_mask_cache(t, tr); }
+// An engine with a device works its rows out there: the host diagnostics make the host's when they need them, one thread at a time.
+inline void host_token_mask_cache(const Tables &t, Trie &tr) {
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lk(mu);
+    if (tr.ci_valid.empty()) build_token_mask_cache(t, tr);
+}
 void build_trie(const zf_vocab_desc *v, int chunk_ranks, const uint8_t *cls, Trie &t);
 
 // ---- chart --------------------------------------------------------------------------------------

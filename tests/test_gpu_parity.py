@@ -1019,6 +1019,33 @@ def test_host_diagnostics_of_an_engine_with_a_device(torch_cuda, oracle_lib):
         assert np.array_equal(ask(s), want)
 
 
+def test_host_diagnostics_asked_by_several_threads(torch_cuda, oracle_lib):
+    """Eight threads ask an engine with a device for a host mask at once, the first anybody asks of it: one makes the rows, all have the oracle's mask."""
+    import threading
+    import paper_2506_01151_amd as zf
+    cfg = configs.CONFIGS[2]
+    g, toks = cfg.grammar(), cfg.vocab()
+    off, data = wvocab.vocab_csr(toks)
+    so = oracle_lib.Oracle(g).new_state()
+    assert so.feed_bytes(b'{"a": [1')
+    want = so.mask(off, data, 8)
+    eng = zf.Engine(g, toks, device=0)
+    rows, got, at_once = [eng.new_state() for _ in range(8)], [None] * 8, threading.Barrier(8)
+    for s in rows:
+        s.advance_bytes(b'{"a": [1')
+
+    def ask(k):
+        at_once.wait()
+        got[k] = (rows[k].debug_host_mask_cached if k % 2 else rows[k].debug_host_mask_automaton)()[0]
+
+    threads = [threading.Thread(target=ask, args=(k,)) for k in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(x is not None and np.array_equal(x, want) for x in got)
+
+
 @pytest.mark.parametrize("walk_mode,pruning", [(0, True), (1, True), (2, False), (2, True)])
 def test_first_call_on_a_stream_of_its_own(walk_mode, pruning, torch_cuda, oracle_lib):
     """The first mask call of an engine, right behind zf_compile and on a stream that does not wait for the null stream: strings and cache rows, which
