@@ -2022,7 +2022,9 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     // then has nothing to wait for, and the host gets the next step ready while this one is at work (a step of one row x 32,000: 13.6 us
     // waited for, 10.1 not; 16 x 128,256 bf16 14.4 and 12.3; 130 x 40,037 bf16 26.1 and 21.6).
     rec.sure = look && !wait && !prof && !d->store_dirty;
-    for (const DeviceSide::CallRecord &other : d->rec) if (other.active && !other.sure) rec.sure &= &other == &rec;
+    uint32_t in_store = 0;                                // calls in flight that went through the store; the others have flags that zf_mask_wait has to await
+    for (const DeviceSide::CallRecord &other : d->rec) if (other.active) { in_store++; if (!other.sure) rec.sure &= &other == &rec; }
+    rec.sure &= in_store == d->pending;
     if (rec.sure) d->lazy_stream = stream;
     host_lk.unlock();
     // the waiting call returns with the mask complete: the kernel wrote it through to memory before it drew its tickets

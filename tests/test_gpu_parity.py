@@ -1364,6 +1364,52 @@ def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
         assert outs[step].view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), step
 
 
+def test_look_ups_behind_a_per_block_call_in_flight(torch_cuda, oracle_lib):
+    """A call of look-ups right behind one through the per-block automaton, both in flight: mask_wait has the status of the first as well (the report
+    counts what its item budget of two left to the fallback pass), and calls that use its slot again find it free.  Masks are the oracle's."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks, B = configs.CONFIGS[3].grammar(), configs.CONFIGS[3].vocab(8192), 64
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, lane_item_cap=2)
+    prefixes = [b"", b"{", b'{"']
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    want = np.stack([want[b % 3] for b in range(B)])
+    rows = [eng.new_state() for _ in range(B)]
+    for b, s in enumerate(rows):
+        s.advance_bytes(prefixes[b % 3])
+    masks = torch.full((15, B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+
+    def check(k):
+        assert np.array_equal(masks[k].cpu().numpy().view(np.uint32), want), k
+
+    zf.compute_mask_async(eng, rows, masks[0])
+    eng.clear_state_cache()                        # with a call in flight: the store starts empty, and sets outgrow the budget
+    zf.mask_wait(eng)
+    zf.compute_mask(eng, rows, masks[1])           # does not fit the store: the next eight calls take the per-block automaton
+    check(0), check(1)
+    eng.clear_state_cache()                        # the automaton whole again
+    for k in range(7):
+        zf.compute_mask_async(eng, rows, masks[2 + k])
+        zf.mask_wait(eng)
+        assert eng.mask_report().overflow_chunks > 0, k
+    zf.compute_mask_async(eng, rows, masks[9])     # the eighth
+    zf.compute_mask_async(eng, rows, masks[10])    # look-ups
+    zf.mask_wait(eng)
+    assert eng.mask_report().overflow_chunks > 0   # of the eighth: its status was there
+    for k in range(11, 15):
+        zf.compute_mask_async(eng, rows, masks[k])
+        zf.mask_wait(eng)
+        assert eng.mask_report().overflow_chunks == 0, k
+    for k in range(2, 15):
+        check(k)
+
+
 def test_per_block_automaton_sets_that_outgrow_the_lanes(torch_cuda, oracle_lib):
     """Charts whose sets hold ten items, and a byte that leaves eighty: more than the build for a dozen items holds.  The call that allocates
     nothing does not take that build (nothing is left to the fallback pass); another call leaves the strings behind the byte to that pass once, and
