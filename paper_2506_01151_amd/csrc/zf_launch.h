@@ -203,6 +203,8 @@ static const int STORE_TICKET_GROUPS = 64, STORE_TICKET_STRIDE = 8, STORE_TICKET
 // draw when they are done (one word per group of blocks, so that thousands of blocks do not queue up at one address, and a
 // top word the last block of each group draws from).
 static const int COUNTER_SET_WORDS = 160, TICKET_GROUPS = 64, TICKET_AT = 16, TICKET_TOP = 144;
+static const int FB_WALKED = 96, FB_CLAIMED = 112;   // words of it, a line each: shares of the fallback pass that have been walked; a bit per share that somebody walks
+static_assert(FB_WAVES <= 32 * 16 && FB_CLAIMED + 16 <= TICKET_TOP, "a line of bits");
 
 struct MaskArgs {
     DeviceTables tab;
@@ -219,7 +221,7 @@ struct MaskArgs {
     int32_t user_batch;
     int32_t handoff_in_permute; // 1: permute is the call's last kernel (state cache off), else the gather is
     uint32_t *counters;        // [0] chunks passed to the fallback, [1] length of the work queue, [2] chunks nobody could resolve,
-                               // [3] Earley byte steps, [4] fallback wavefronts that have finished, [16..144] tickets of the call's last kernel;
+                               // [3] Earley byte steps, [16..144] tickets and the fallback pass's counts (FB_...) of the call's last kernel;
                                // COUNTER_SET_WORDS words per set
     uint32_t *host_status;     // pinned host memory, 8 words: this call's counters [0..3], written by its last kernel, then [4] = seq
     uint32_t seq;              // the call's number (never 0): the last word the call's last kernel writes, which is what the host waits for

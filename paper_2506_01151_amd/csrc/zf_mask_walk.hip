@@ -450,15 +450,14 @@ __global__ __launch_bounds__(WALK_BLOCK) __attribute__((amdgpu_waves_per_eu(6)))
 }
 
 // Fallback: one wavefront per chunk that outgrew LDS; same walk with the strip-wise step and the
-// item list in a global-memory arena.  Wavefront gw of n_waves takes entries gw, gw + n_waves, ... of the
-// n listed ones.
-__device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, uint32_t n_waves, uint32_t n, uint32_t lane) {
+// item list in a global-memory arena.  Share `share` of n_shares is entries share, share + n_shares, ... of the
+// n listed ones, and an arena.
+__device__ __forceinline__ void fallback_share(const MaskArgs &a, uint32_t share, uint32_t n_shares, uint32_t n, uint32_t lane) {
     const DeviceTables &D = a.tab;
     TV T;
     stage_tables<2>(D, nullptr, T, 0, 1);
-    if (n > a.overflow_cap) { if (gw == 0 && lane == 0) atomicAdd(&a.counters[2], n - a.overflow_cap); n = a.overflow_cap; }
-    GlobalStore st{a.fb_items + (size_t)gw * a.fb_stride, a.fb_set_start + (size_t)gw * (FB_DEPTH_MAX + 2), (uint32_t)a.fb_cap};
-    for (uint32_t e = gw; e < n; e += n_waves) {
+    GlobalStore st{a.fb_items + (size_t)share * a.fb_stride, a.fb_set_start + (size_t)share * (FB_DEPTH_MAX + 2), (uint32_t)a.fb_cap};
+    for (uint32_t e = share; e < n; e += n_shares) {
         const uint4 ent = a.overflow_list[e];
         const BaseG B = global_base(a, ent.x);
         const uint32_t begin = D.chunk_begin[ent.y], end = D.chunk_end[ent.y];
@@ -483,13 +482,11 @@ __device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, ui
 // string-rank order into token order, in one launch.  As a kernel of its own the fallback pass costs
 // 4.5 us per call even when its list is empty (a launch and two dependent loads), and with the mask
 // automata almost every call leaves it empty.
-//   When the list is not empty, wavefronts of all blocks, one to a block first, walk the
-// listed chunks first and count themselves off; every block then waits for that count before it
-// reads the verdicts.  The host sizes the grid so that the chip holds all of its blocks at once
-// (blocks loop over row groups when a batch has more of them): every block that waits is resident
-// together with the wavefronts it waits for, whatever the order the blocks were started in, and the
-// fallback wavefronts wait for nothing, so the wait ends.  It is bounded all the same, and running
-// into the bound makes the call fail with ZF_ERR_OVERFLOW.
+//   When the list is not empty, its chunks are shared out among wavefronts of all blocks, one to a block first, and every
+// block waits until all shares have been walked before it reads the verdicts.  The wait ends whichever blocks of the grid the
+// chip holds (another engine's closing kernel, waiting in its turn, may have the other places): shares are claimed, and who has walked its
+// own claims those that nobody has begun, so once a block waits every share is with a wavefront that runs and waits for
+// nothing.  It is bounded all the same, and running into the bound makes the call fail with ZF_ERR_OVERFLOW.
 //   Permutation: verdicts are produced in trie order, the caller wants bit v at word v >> 5.  A lane takes four neighbouring tokens of
 // PERMUTE_ROWS rows: four ranks, the four rows' words of each, four bits a row; eight lanes put a mask word together.
 //   Logits (zf_compute_mask_apply_async): the lane that has a token's bits masks its logits along.  They are requested with the ranks, before
@@ -498,7 +495,7 @@ __device__ __forceinline__ void fallback_wave(const MaskArgs &a, uint32_t gw, ui
 //   Hand-over: see hand_over (zf_kernel_common.h).  With nothing listed the status is final when this kernel starts, and is handed over first.
 static const int PERMUTE_ROWS = 4;
 static const uint32_t PERMUTE_TOKENS = 4;             // neighbouring tokens of a lane
-static const uint32_t FINISH_SPIN_LIMIT = 1u << 21;   // polls of about 2 us each
+static const uint32_t FINISH_SPIN_LIMIT = 1u << 23;   // polls of about 2 us each (a chunk whose sets hold 600 items is walked for four seconds)
 constexpr int finish_block(bool staged) { return staged ? 512 : 256; }
 typedef uint32_t finish_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t finish_u32x2 __attribute__((ext_vector_type(2)));
@@ -513,7 +510,7 @@ template <> struct FinishLogit<2> { typedef uint16_t elem; typedef finish_u32x2 
 // DT: 0 no logits, 1 fp32, 2 bf16.
 template <bool STAGED, int DT>
 __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a, uint32_t tokens_per_block, uint32_t row_groups) {
-    constexpr uint32_t BLOCK = (uint32_t)finish_block(STAGED), WAVES = BLOCK / 64, PASS = BLOCK * PERMUTE_TOKENS;
+    constexpr uint32_t BLOCK = (uint32_t)finish_block(STAGED), PASS = BLOCK * PERMUTE_TOKENS;
     typedef FinishLogit<DT> L;
     typedef typename L::elem elem;
     typedef typename L::piece piece_t;
@@ -551,16 +548,36 @@ __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a
     const uint32_t n_blocks = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x;
     const uint32_t n_over = a.counters[0];
     if (n_over != 0) {
-        const uint32_t fb_waves = n_blocks * WAVES < a.fb_waves ? n_blocks * WAVES : a.fb_waves;
-        const uint32_t gw = (tid >> 6) * n_blocks + lin;       // one to a block first: they are spread over the chip
-        if (gw < fb_waves) {
-            fallback_wave(a, gw, fb_waves, n_over, lane);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // its verdict bits and error counts before its count
-            if (lane == 0) atomicAdd(&a.counters[4], 1u);
+        const uint32_t n_listed = n_over < a.overflow_cap ? n_over : a.overflow_cap;
+        const uint32_t most = min(n_blocks * (BLOCK / 64u), a.fb_waves), n_shares = min(most, n_listed);
+        uint32_t share = (tid >> 6) * n_blocks + lin;          // one to a block first: they are spread over the chip
+        if (lin == 0 && tid == 0 && n_over > n_listed) { atomicAdd(&a.counters[2], n_over - n_listed); __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
+        if (share < n_shares || tid < 64u) for (;;) {
+            if (share < n_shares) {
+                const uint32_t bit = 1u << (share & 31u);
+                uint32_t claimed = 0;
+                if (lane == 0) claimed = atomicOr(&a.counters[FB_CLAIMED + (share >> 5)], bit);
+                claimed = (uint32_t)__builtin_amdgcn_readfirstlane((int)claimed);
+                if (!(claimed & bit)) {
+                    fallback_share(a, share, n_shares, n_listed, lane);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // its verdict bits and error counts before its count
+                    if (lane == 0) atomicAdd(&a.counters[FB_WALKED], 1u);
+                }
+            }
+            // a share that nobody has claimed: its block has not started
+            uint32_t left = 0;
+            if (lane * 32u < n_shares) {
+                left = ~__hip_atomic_load(&a.counters[FB_CLAIMED + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (n_shares - lane * 32u < 32u) left &= (1u << (n_shares - lane * 32u)) - 1u;
+            }
+            const unsigned long long any = __ballot(left != 0);
+            if (!any) break;
+            const int at = __ffsll((long long)any) - 1;
+            share = (uint32_t)at * 32u + (uint32_t)__ffs((int)__builtin_amdgcn_readlane((int)left, at)) - 1u;
         }
         if (tid == 0) {
             uint32_t spins = 0;
-            while (__hip_atomic_load(&a.counters[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < fb_waves) {
+            while (__hip_atomic_load(&a.counters[FB_WALKED], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_shares) {
                 __builtin_amdgcn_s_sleep(64);
                 if (++spins > FINISH_SPIN_LIMIT) { atomicAdd(&a.counters[2], 1u); __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); break; }
             }
@@ -701,8 +718,8 @@ hipError_t launch_finish(const MaskArgs &a, int cus, hipStream_t s) {
     const bool staged = lds <= 150u * 1024u && V / (want > 0 ? want : 1u) >= 2048u;
     if (staged && want < x_blocks) x_blocks = want;
     if (x_blocks < 1) x_blocks = 1;
-    // The chip must hold the whole grid at once (blocks may wait for the fallback wavefronts of other blocks): ask the runtime how
-    // many blocks a compute unit takes, and let blocks loop over row groups, then over longer token runs, when there are more.
+    // No more blocks than the chip holds at once (with chunks listed, those behind would start only when the others have waited for all of them): ask the
+    // runtime how many blocks a compute unit takes, and let blocks loop over row groups, then over longer token runs, when there are more.
     typedef void (*kernel_t)(MaskArgs, uint32_t, uint32_t);
     static const kernel_t kernels[2][3] = {{finish_kernel<false, 0>, finish_kernel<false, 1>, finish_kernel<false, 2>}, {finish_kernel<true, 0>, finish_kernel<true, 1>, finish_kernel<true, 2>}};
     const int dt = (int)a.logit_dtype;

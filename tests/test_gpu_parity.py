@@ -1410,6 +1410,45 @@ def test_look_ups_behind_a_per_block_call_in_flight(torch_cuda, oracle_lib):
         check(k)
 
 
+@pytest.mark.parametrize("walk_mode,noalloc", [(0, False), (1, False), (0, True)])
+def test_fallback_passes_of_two_engines_at_once(walk_mode, noalloc, torch_cuda, oracle_lib):
+    """Two engines, each on a stream of its own, whose strings all go to the fallback pass: their closing kernels share the chip, and neither waits for
+    blocks of its own that have no place.  (The call that allocates nothing has fewer arenas than blocks; its calls take turns.)  Masks are the oracle's."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks, B = configs.CONFIGS[3].grammar(), configs.CONFIGS[3].vocab(8192), 24 if noalloc else 130
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    prefixes = [b"", b"{", b'{"']
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    want = np.stack([want[b % 3] for b in range(B)])
+    engines = [zf.Engine(g, toks, device=0, state_cache_entries=-1, walk_mode=walk_mode, lane_item_cap=1) for _ in range(2)]
+    rows = [[e.new_state() for _ in range(B)] for e in engines]
+    for batch in rows:
+        for b, s in enumerate(batch):
+            s.advance_bytes(prefixes[b % 3])
+    streams = [torch.cuda.Stream() for _ in engines]
+    masks = torch.full((2, 4, B, engines[0].W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for call in range(4):
+        for k, e in enumerate(engines):
+            with torch.cuda.stream(streams[k]):
+                (zf.compute_mask_noalloc if noalloc else zf.compute_mask_async)(e, rows[k], masks[k, call])
+    for k, e in enumerate(engines):
+        with torch.cuda.stream(streams[k]):
+            zf.mask_wait(e)
+        assert e.mask_report().overflow_chunks > 0
+    torch.cuda.synchronize()
+    got = masks.cpu().numpy().view(np.uint32)
+    for k in range(2):
+        for call in range(4):
+            assert np.array_equal(got[k, call], want), (k, call)
+
+
 def test_per_block_automaton_sets_that_outgrow_the_lanes(torch_cuda, oracle_lib):
     """Charts whose sets hold ten items, and a byte that leaves eighty: more than the build for a dozen items holds.  The call that allocates
     nothing does not take that build (nothing is left to the fallback pass); another call leaves the strings behind the byte to that pass once, and
