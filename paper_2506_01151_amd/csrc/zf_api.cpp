@@ -77,6 +77,11 @@ struct DeviceSide {
     int cus = 256;
     int mode = 2;
     bool lanes_call[N_SLOTS] = {false, false, false, false};   // the call ran the per-block automaton's AUT_STEP_LANES build
+    // The status of a call through the closing kernel is final when that kernel starts, and zf_mask_wait returns with the kernel at work on the engine's
+    // buffers (d_rank_mask, d_chart): a call on another stream goes behind this event.
+    hipEvent_t closing_done = nullptr;
+    hipStream_t closing_stream = nullptr;            // the newest stream that is behind it
+    bool closing_open = false;                       // it stands behind the last call through the closing kernel (which was not a waiting one)
     bool lanes_outgrown = false;                     // such a call left strings to the fallback pass: AUT_STEP_WIDE from then on
     uint32_t *d_counters = nullptr;
     uint2 *d_fb_items = nullptr;
@@ -236,6 +241,7 @@ void free_device(DeviceSide *d) {
     if (d->d_fb_items) (void)hipFree(d->d_fb_items);
     if (d->d_fb_ss) (void)hipFree(d->d_fb_ss);
     for (auto &ev : d->ev) if (ev) (void)hipEventDestroy(ev);
+    if (d->closing_done) (void)hipEventDestroy(d->closing_done);
     delete d;
 }
 
@@ -1212,6 +1218,10 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         const int rc = stream == d->lazy_stream ? settle_call(d, slot) : settle_calls(d);
         if (rc != ZF_OK) return rc;
     }
+    if (d->closing_open && stream != d->closing_stream) {
+        HIP_TRY(hipStreamWaitEvent(stream, d->closing_done, 0));
+        d->closing_stream = stream;                       // which is behind it now
+    }
     for (int b = 0; b < batch; b++)
         if (!states[b] || states[b]->eng != e) return fail(ZF_ERR_INVALID_ARG, "state " + std::to_string(b) + " is null or belongs to another engine");
     // (noalloc with an explicit item budget: the budget is one of the per-block automaton's wavefronts)
@@ -1482,7 +1492,13 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;
-    if (!wait) return ZF_OK;
+    d->closing_open = !wait;
+    if (!wait) {
+        if (!d->closing_done) HIP_TRY(hipEventCreateWithFlags(&d->closing_done, hipEventDisableTiming));
+        HIP_TRY(hipEventRecord(d->closing_done, stream));
+        d->closing_stream = stream;
+        return ZF_OK;
+    }
     HIP_TRY(hipStreamSynchronize(stream));               // the waiting call returns with the mask complete, not only its status known
     return zf_mask_wait(e, hip_stream);
 }

@@ -1364,6 +1364,43 @@ def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
         assert outs[step].view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), step
 
 
+@pytest.mark.parametrize("walk_mode,pruning", [(0, True), (1, True), (2, False)])
+def test_status_ahead_of_the_closing_kernel_and_another_stream(walk_mode, pruning, torch_cuda, oracle_lib):
+    """mask_wait returns when a call's closing kernel has begun; the next call comes on another stream, nothing synchronised between them, and does not
+    write the verdicts that the first kernel still reads.  Rows stand in other states from call to call; masks and masked logits are the oracle's."""
+    import paper_2506_01151_amd as zf
+    from oracle.frontend import apply_mask as oracle_apply
+    torch = torch_cuda
+    g, toks, B, calls = configs.CONFIGS[2].grammar(), configs.CONFIGS[2].vocab(32000), 64, 12
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, walk_mode=walk_mode, pruning=pruning)
+    prefixes = [b"", b'{"a": [1', b'{"', b"[[", b'{"a": tr']
+    per_state, rows = [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        per_state.append(so.mask(off, data, 8))
+        rows.append([eng.new_state() for _ in range(B)])
+        for s in rows[-1]:
+            s.advance_bytes(p)
+    logits = torch.randn(B, len(toks), device="cuda")
+    masks = torch.full((calls, B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    outs = torch.zeros((calls, B, len(toks)), device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for call in range(calls):
+        with torch.cuda.stream(streams[call % 3]):
+            zf.compute_mask_apply_async(eng, [rows[(b + call) % len(rows)][b] for b in range(B)], masks[call], logits, out=outs[call])
+            zf.mask_wait(eng)
+    torch.cuda.synchronize()
+    bits = logits.cpu().numpy().view(np.uint32)
+    for call in range(calls):
+        want = np.stack([per_state[(b + call) % len(rows)] for b in range(B)])
+        assert np.array_equal(masks[call].cpu().numpy().view(np.uint32), want), call
+        assert outs[call].cpu().numpy().view(np.uint32).tobytes() == oracle_apply(bits, want).tobytes(), call
+
+
 def test_look_ups_behind_a_per_block_call_in_flight(torch_cuda, oracle_lib):
     """A call of look-ups right behind one through the per-block automaton, both in flight: mask_wait has the status of the first as well (the report
     counts what its item budget of two left to the fallback pass), and calls that use its slot again find it free.  Masks are the oracle's."""
