@@ -30,6 +30,9 @@ int zf_debug_host_mask_cached(zf_engine *e, const zf_state *s, uint32_t *mask /*
  * mask).  stats[0..4] (host, may be null): automaton states created, Earley byte steps taken,
  * transition look-ups, undecided strings, largest set. */
 int zf_debug_host_mask_automaton(zf_engine *e, const zf_state *s, uint32_t *mask /* host [W] */, int64_t *stats);
+/* Diagnostic: how often a wavefront of zf_compute_mask_apply_async's look-ups that is to mask logits looks for their mask words before it
+ * leaves the logits to whoever is done last (0 or 1: once).  Results do not depend on it. */
+int zf_debug_look_polls(zf_engine *e, uint32_t polls);
 
 /* Host twin of the persistent automaton (the mask kernels' cross-step store, Sections 4.4 / 5.2): every
  * Earley set is named by its content, items carrying the name of the set their rule started in, so the

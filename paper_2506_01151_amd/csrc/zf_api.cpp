@@ -95,6 +95,7 @@ struct DeviceSide {
     unsigned long long *d_tickets = nullptr;         // [2][STORE_TICKETS]
     uint32_t ticket_set = 0;                         // the one the next kernel draws from
     unsigned long long *d_tagged = nullptr; size_t tagged_cap = 0;   // LookArgs::tagged (words)
+    uint32_t look_polls = LOOK_POLLS;
     StoreConst *d_konst = nullptr;
     uint32_t store_epoch = 1;                        // bumped whenever the store is cleared
     uint32_t store_states = 0, store_items = 0;      // as of the last call that reported back
@@ -1074,6 +1075,12 @@ int zf_position_info(const zf_engine *e, int32_t p, int32_t *lhs, int32_t *rule,
 
 int zf_debug_host_mask(zf_engine *e, const zf_state *s, uint32_t *mask) { return zf_debug_host_mask_stats(e, s, mask, nullptr); }
 
+int zf_debug_look_polls(zf_engine *e, uint32_t polls) {
+    if (!e || !e->dev) return fail(ZF_ERR_INVALID_ARG, "bad argument");
+    e->dev->look_polls = polls;
+    return ZF_OK;
+}
+
 int zf_debug_host_mask_cached(zf_engine *e, const zf_state *s, uint32_t *mask, int64_t *stats) {
     if (!e || !s || !mask || s->eng != e) return fail(ZF_ERR_INVALID_ARG, "bad argument");
     const Tables &t = e->tab;
@@ -1839,7 +1846,12 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     // logits are dealt out in units of as many KB as make 2,048 wavefronts, 4 at most (units of 2 / 4 / 6 / 8 KB, us per pass: 16 steps of 16 x 128,256
     // bf16 171 / 176 / 184 / 186, of 64 x 152,064 fp32 - / 361 / 371 / 379, 8 steps of 130 x 40,037 bf16 148 / 144 / 149 / 151; 256 x 128,256 - / 235 / 229 / 239).
     if (look && whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32)) {
-        const size_t words = (size_t)ng * (size_t)d->tab.W;
+        const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
+        const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
+        k.unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048));
+        k.row_units = (row_kb + k.unit_kb - 1) / k.unit_kb;
+        k.units = k.row_units * (uint32_t)batch;
+        const size_t words = (size_t)ng * (size_t)d->tab.W + (k.units + STORE_WAVES - 1) / STORE_WAVES;
         if (words > d->tagged_cap) {
             const int rc = settle_calls(d);
             if (rc != ZF_OK) return rc;
@@ -1851,11 +1863,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
             d->tagged_cap = cap;
             HIP_TRY(launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(cap * 2), stream));
         }
-        const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
-        const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
-        k.unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048));
-        k.row_units = (row_kb + k.unit_kb - 1) / k.unit_kb;
-        k.units = k.row_units * (uint32_t)batch;
+        k.polls = d->look_polls;
         k.tagged = d->d_tagged; k.logits = g_apply.logits; k.out = g_apply.out; k.stride = g_apply.stride; k.dtype = (uint32_t)g_apply.dtype + 1;
         g_apply.fused = true;
     }

@@ -157,6 +157,7 @@ static_assert(sizeof(StoreArgs) + sizeof(StoreInline) <= 4096, "the kernel's arg
 static const int LOOK_BLOCKS_PER_CU = ZF_LOOK_BLOCKS_PER_CU;
 static const int LOOK_WORDS = 9;
 static const uint32_t LOOK_ENT_OF_MORE = 8, LOOK_ENT_MAX = 255;
+static const uint32_t LOOK_POLLS = 1024;   // LookArgs::polls: a millisecond and more, where a wait lasts as long as a block of the mask is at work (6 to 130 us)
 static const int LOOK_UNIT_KB = 4;      // logits that a wavefront of mask_look_kernel holds while the mask is worked out, at most: a register quadruple per lane and KB
 struct LookGroup {                     // as StoreGroup, without what a known state does not need, in nine words:
     uint32_t w[LOOK_WORDS];            // [0] state; [1] n_ent | flags << 8 | (mask words per pass - 1) << 16; [2] first block | segments << 16;
@@ -179,7 +180,8 @@ struct LookArgs {
     uint32_t seq, V, W, ncls, n_groups, complete;
     uint32_t mask_blocks;              // blocks that work the masks out; behind them, where the logits are masked along:
     uint32_t units, row_units, unit_kb, dtype;   // units of logits, one per wavefront, of unit_kb KB each; of a row; 1 = fp32, 2 = bf16
-    unsigned long long *tagged;        // [groups][W] mask words on their way to those wavefronts: call's number << 32 | word
+    uint32_t polls;                    // how often such a wavefront looks for its mask words before it leaves its unit to its group of blocks
+    unsigned long long *tagged;        // [groups][W] mask words on their way to those wavefronts: call's number << 32 | word; behind them a word per block with logits, likewise
     const void *logits;
     void *out;
     int64_t stride;                    // elements between rows of logits

@@ -21,7 +21,12 @@
 // 32,000 fp32 324 -> 252, 16 of 16 x 128,256 bf16 196 -> 170, 16 of 64 x 128,256 bf16 288 -> 228, 16 of 64 x 152,064 fp32 422 -> 364,
 // 8 of 130 x 40,037 bf16 173 -> 143, 8 of 256 x 128,256 bf16 262 -> 233, 4 of 1,024 x 128,256 495 -> 379.
 //   Words travel as (call's number << 32 | word), one 8-byte store past the L2s each: whoever reads the number has the word, nothing is ordered
-// and nothing is counted.  No wavefront of the mask waits for one with logits, and blocks start in the order of the grid, so the wait ends; it is bounded all the same.
+// and nothing is counted.  Blocks start in the order of the grid, so as a rule the mask's are at work while those with logits wait.  But each XCD takes
+// up its share of a grid by itself, and two grids of the kind (two engines') can each fill an XCD with waiting blocks while a block of their mask
+// has no place on it.  So a wavefront with logits looks for its words a limited number of times; then it leaves its unit to its group of blocks
+// (those that report in one status word) and ends, and the block of the group that is done last masks what was left, however long the words take.  That
+// leaves two blocks per XCD and call that wait for as long as it takes, of 160 places, and no block of the mask waits for another: all grids go on.
+// (Calls of up to 64 blocks, eight per XCD, leave nothing to anybody.)
 #include "zf_kernel_common.h"
 #include "zf_aut_step.h"
 
@@ -34,7 +39,7 @@ static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
 static const uint32_t LOOK_STOP = 256;                   // beyond every class and mark: the walk of a lane has ended
 static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
 static const int LOOK_RAW = 2;                           // token-mask cache rows that are asked for whether or not there are so many
-static const unsigned long long LOOK_WAIT_TICKS = 200000000ull;   // 2 s of the 100 MHz clock: how long a wavefront with logits waits for mask words
+static const uint32_t LOOK_POLLS_MAX = 1u << 24;         // how often a wavefront that can leave a unit to nobody looks for mask words before the call fails: tens of seconds
 static_assert(LOOK_LIST >= 64u * STORE_WAVES, "the states one byte away are listed there, read by lane x wavefronts");
 static const int LOOK_WARM = 6;                          // table rows one byte ahead that each wavefront of a block reads into the cache
 
@@ -56,13 +61,14 @@ __device__ __forceinline__ uint32_t member_row(const LookArgs &a, const LookInli
 
 // As hand_over_store, in one level: the block that draws the last ticket of its group of blocks tells the host, which looks at a word per
 // group; there is nothing to tell but failed walks.  In two parts: what a block has left to do between the draw and its answer, the trip to
-// memory hides.
+// memory hides.  A ticket: 1 | failed walks << 16 | has left units to the group << 48.
 struct LookTicket { unsigned long long sum; uint32_t group, size; };
-__device__ __forceinline__ LookTicket draw_ticket(const LookArgs &a, uint32_t failed) {
+__device__ __forceinline__ uint32_t ticket_group_size(const LookArgs &a, uint32_t group) { return gridDim.x / a.done_groups + (group < gridDim.x % a.done_groups ? 1u : 0u); }
+__device__ __forceinline__ LookTicket draw_ticket(const LookArgs &a, uint32_t failed, bool left) {
     LookTicket t;
     t.group = blockIdx.x % a.done_groups;
-    t.size = gridDim.x / a.done_groups + (t.group < gridDim.x % a.done_groups ? 1u : 0u);
-    const unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16;
+    t.size = ticket_group_size(a, t.group);
+    const unsigned long long mine = 1ull | (unsigned long long)(failed < 4095u ? failed : 4095u) << 16 | (unsigned long long)(left ? 1u : 0u) << 48;
     t.sum = mine;
     if (t.size > 1u) t.sum += atomicAdd(&a.tickets[t.group * STORE_TICKET_STRIDE], mine);   // a block that is a group by itself has nobody to wait for
     return t;
@@ -71,14 +77,17 @@ __device__ __forceinline__ void tell_host(const LookArgs &a, const LookTicket &t
     if ((t.sum & 0xFFFFull) != t.size) return;
     __hip_atomic_store(&a.status[STORE_ST_ROW + t.group], ((unsigned long long)a.seq << 32) | ((uint32_t)(t.sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+// Blocks that have left units: behind the mask words, a word for every block with logits, which travels as they do: call's number << 32 | a bit per wavefront.
+__device__ __forceinline__ unsigned long long *left_units(const LookArgs &a) { return a.tagged + (size_t)a.n_groups * a.W; }
 
 // A wavefront with logits: `unit_kb` KB of one row's.  It requests them, waits until the row's mask words for them are there, and stores them masked.
 // Where the words are there at once -- a block that started late, most blocks of a large tensor -- pieces of which nothing is allowed are not read.
 template <int DT> struct LookLogit { typedef uint32_t elem; static const int PER_PIECE = 4; static const uint32_t NEG_INF = 0xFF800000u; typedef u32x4 __attribute__((aligned(4))) piece; };
 template <> struct LookLogit<2> { typedef uint16_t elem; static const int PER_PIECE = 8; static const uint32_t NEG_INF = 0xFF80u; typedef u32x4 __attribute__((aligned(2))) piece; };
-// words_read(failed) is called when the mask words are in hand, before anything is stored.
-template <int DT, class WordsRead>
-__device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline &in, uint32_t unit, uint32_t lane, WordsRead words_read) {
+// words_read(failed, left) is called when the mask words are in hand, before anything is stored, or when they were not there after `polls` looks: with
+// LEAVE the unit is then left to the group, else the call fails.
+template <int DT, bool LEAVE, class WordsRead>
+__device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline &in, uint32_t unit, uint32_t lane, uint32_t polls, WordsRead words_read) {
     typedef LookLogit<DT> L;
     typedef typename L::elem elem;
     typedef typename L::piece piece_t;
@@ -119,7 +128,6 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
     elem last = 0;
     if (has_tail) last = src[n_vec * EPV + lane];
     if (!ready) {
-        const unsigned long long t0 = wall_clock64();
         for (;;) {
             // few wavefronts look again at once, many stay out of the way (16 x 128,256 bf16 145.0 us per 16 steps with 8 here, 142.8 with 1, 146.5 with 16;
             // one row x 32,000 201.6, 198.4, 207.4; 64 x 152,064 fp32 342.7, 343.7 with 3, 341.2 with 16; 256 x 128,256 225.2, 227.5 with 3, 224.1)
@@ -131,10 +139,11 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
                 here &= (uint32_t)(t[k] >> 32) == a.seq;
             }
             if (__all(here)) break;
-            if (wall_clock64() - t0 > LOOK_WAIT_TICKS) { words_read(1u); return; }   // never, unless the mask's blocks are not running: the call fails
+            if (polls <= 1u) { words_read(LEAVE ? 0u : 1u, LEAVE); return; }
+            polls--;
         }
     }
-    words_read(0u);
+    words_read(0u, false);
 #pragma unroll
     for (uint32_t u = 0; u < (uint32_t)LOOK_UNIT_KB; u++) {
         if (u >= nu) continue;
@@ -153,6 +162,28 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
     }
 }
 
+// What blocks of a group have left, by the wavefront that has drawn the group's last ticket: `n` blocks' units.  Returns how many never got their words.
+template <int DT>
+__device__ __forceinline__ uint32_t mask_left_units(const LookArgs &a, const LookInline &in, uint32_t group, uint32_t n, uint32_t lane) {
+    uint32_t failed = 0, polls = LOOK_POLLS_MAX;
+    unsigned long long *const left = left_units(a);
+    const uint32_t blocks = gridDim.x - a.mask_blocks, stride = a.done_groups;
+    uint32_t first = group;                                  // the group's first block with logits ...
+    while (first < a.mask_blocks) first += stride;
+    while (n) {                                              // (a word may be on its way still)
+        for (uint32_t k = first - a.mask_blocks; n && k < blocks; k += stride) {
+            const unsigned long long e = __hip_atomic_load(&left[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32)) != a.seq) continue;
+            if (lane == 0) __hip_atomic_store(&left[k], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            n--;
+            for (uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e); bits; bits &= bits - 1u)
+                mask_logits<DT, false>(a, in, k * STORE_WAVES + (uint32_t)__ffs((int)bits) - 1u, lane, LOOK_POLLS_MAX, [&](uint32_t f, bool) __attribute__((always_inline)) { failed += f; });
+        }
+        if (n && polls-- <= 1u) return failed + n;           // never: the call fails
+    }
+    return failed;
+}
+
 // Grid and groups as in mask_store_kernel: the blocks of all groups one after the other, a group = the rows of the call that
 // stand in the same state, whose mask is worked out once, in token order.  A wavefront takes every n_units-th segment of `sw` mask words.
 template <int DT>   // of the logits masked along: 0 = none, 1 = fp32, 2 = bf16
@@ -166,21 +197,40 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
     if (blockIdx.x == 0 && wave == 0) clear_tickets(a.tickets_next, lane);
     // ---- the record of the block's group: one trip to the argument block (lane l asks for that of group l), or to device memory ----
     uint32_t r[LOOK_WORDS], part, parts, group = 0;
+    // the block's ticket has been drawn, by lane 0 of this wavefront
+    auto drawn = [&](LookTicket t) __attribute__((always_inline)) {
+        if (DT) {
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)((t.sum & 0xFFFFull) == t.size ? (uint32_t)(t.sum >> 48) : 0u));
+            if (__builtin_expect(n, 0)) {                    // (rare: the arguments are read anew, none is kept for it from the kernel's start)
+                const void *at = (const void *)__builtin_amdgcn_kernarg_segment_ptr();
+                asm volatile("" : "+s"(at));
+                static_assert(sizeof(LookArgs) % alignof(LookInline) == 0, "the second argument follows the first");
+                const LookArgs &a2 = *(const LookArgs *)at;
+                const LookInline &in2 = *(const LookInline *)((const uint8_t *)at + sizeof(LookArgs));
+                t.sum += (unsigned long long)mask_left_units<DT>(a2, in2, blockIdx.x % a2.done_groups, n, lane) << 16;
+            }
+        }
+        if (lane == 0) tell_host(a, t);
+    };
     if (DT && blockIdx.x >= a.mask_blocks) {
-        if (tid == 0) blk_failed = 0;                        // wavefronts that have their words, and those that gave up << 16
+        if (tid == 0) blk_failed = 0;                        // wavefronts that have their words or have left their unit; who has, << 8; those that gave up << 16
         __syncthreads();
-        const uint32_t unit = (blockIdx.x - a.mask_blocks) * STORE_WAVES + wave;
+        const uint32_t block = blockIdx.x - a.mask_blocks, unit = block * STORE_WAVES + wave;
         LookTicket t{};
         bool drew = false;
         // nothing that belongs to the engine is read behind this: the ticket's trip to memory goes along with the stores
-        auto words_read = [&](uint32_t f) __attribute__((always_inline)) {
-            const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lane == 0 ? atomicAdd(&blk_failed, 1u + (f << 16)) : 0u));
-            drew = (before & 0xFFFFu) == STORE_WAVES - 1u;
-            if (drew && lane == 0) t = draw_ticket(a, (before >> 16) + f);
+        auto words_read = [&](uint32_t f, bool left) __attribute__((always_inline)) {
+            const uint32_t mine = 1u + (left ? 256u << wave : 0u) + (f << 16);
+            const uint32_t sum = mine + (uint32_t)__builtin_amdgcn_readfirstlane((int)(lane == 0 ? atomicAdd(&blk_failed, mine) : 0u)), who = (sum >> 8) & 255u;
+            drew = (sum & 255u) == STORE_WAVES;
+            if (drew && lane == 0) {
+                if (who) __hip_atomic_store(&left_units(a)[block], (unsigned long long)a.seq << 32 | who, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                t = draw_ticket(a, sum >> 16, who != 0);
+            }
         };
-        if (unit < a.units) mask_logits<DT>(a, in, unit, lane, words_read);
-        else words_read(0u);
-        if (drew && lane == 0) tell_host(a, t);
+        if (unit < a.units) mask_logits<DT, true>(a, in, unit, lane, a.polls, words_read);
+        else words_read(0u, false);
+        if (drew) drawn(t);
         return;
     }
     if (a.groups) {
@@ -422,7 +472,11 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
     }
     if (a.complete) stores_arrived();                        // every word this wavefront wrote has reached memory before the block's ticket is drawn
     __syncthreads();
-    if (tid == 0) tell_host(a, draw_ticket(a, lds_load(&blk_failed)));
+    if (wave == 0) {
+        LookTicket t{};
+        if (lane == 0) t = draw_ticket(a, lds_load(&blk_failed), false);
+        drawn(t);
+    }
 }
 
 }  // namespace

@@ -1188,7 +1188,7 @@ def test_waiting_calls_on_two_streams(noalloc, precompute, torch_cuda, oracle_li
 
 @pytest.mark.parametrize("V,B,dtype,shift", [(5, 2, "f32", 0), (7, 1, "bf16", 1), (512, 3, "bf16", 0), (513, 70, "bf16", 0), (1023, 3, "f32", 3), (2047, 2, "bf16", 1), (2049, 66, "f32", 0),
                                              (8193, 5, "bf16", 5), (40037, 600, "bf16", 1), (33001, 300, "f32", 0)])
-def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracle_lib):
+def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracle_lib, polls=None):
     """The wavefronts of mask_look_kernel that mask logits: rows that end within a piece, within a KB and within a unit of four, rows at any multiple of
     an element, fewer tokens than a piece, groups in the argument block and beyond it, and tensors larger than what the chip holds at once (wavefronts that
     find their words there and leave out what nothing is allowed of).  Out of place; masks and logits are the oracle's."""
@@ -1200,6 +1200,8 @@ def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracl
     g = grammars.json_grammar()
     orc = oracle_lib.Oracle(g)
     eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)
+    if polls is not None:
+        zf.load_library().zf_debug_look_polls(eng.h, polls)
     prefixes = [b"", b"[", b'{"a', b"[1", b'["x', b"[[0.5e", b'{"k":', b"tru"] + [b"[" * k for k in range(2, 80 if B in (66, 70) else 2)]
     want = []
     for p in prefixes:
@@ -1230,6 +1232,57 @@ def test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracl
         rest = out.cpu()
         rest[shift:].view(B, V + 3)[:, :V] = 0x1234
         assert bool((rest == 0x1234).all()), call   # nothing beyond the rows' ends
+
+
+@pytest.mark.parametrize("V,B,dtype,shift", [(5, 2, "f32", 0), (513, 70, "bf16", 0), (2047, 2, "bf16", 1), (2049, 66, "f32", 0), (8193, 5, "bf16", 5), (40037, 600, "bf16", 1), (33001, 300, "f32", 0)])
+def test_logits_left_to_the_block_that_is_last(V, B, dtype, shift, torch_cuda, oracle_lib):
+    """The same with wavefronts that look for their mask words once: those that come before the words leave their logits to the block that is done last
+    with the masks.  From one block of the mask to hundreds, records in the argument block and beyond it."""
+    test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracle_lib, polls=0)
+
+
+@pytest.mark.parametrize("polls", [None, 0, 3])
+def test_look_ups_with_logits_of_two_engines_at_once(polls, torch_cuda, oracle_lib):
+    """Two engines, each on a stream of its own, both with more blocks of logits than the chip holds: whichever blocks have the places, every logit is masked."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    V, B, calls = 64000, 96, 8
+    toks = configs.CONFIGS[2].vocab(V)
+    off, data = wvocab.vocab_csr(toks)
+    g = grammars.json_grammar()
+    orc = oracle_lib.Oracle(g)
+    prefixes = [b"", b"[", b'{"a', b"[1", b'["x', b"[[0.5e", b'{"k":', b"tru"]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    want = np.stack([want[b % 8] for b in range(B)])
+    engines, rows = [zf.Engine(g, toks, device=0, state_cache_entries=-1) for _ in range(2)], []
+    for e in engines:
+        if polls is not None:
+            zf.load_library().zf_debug_look_polls(e.h, polls)
+        batch = [e.new_state() for _ in range(B)]
+        for b, s in enumerate(batch):
+            s.advance_bytes(prefixes[b % 8])
+        rows.append(zf.StateBatch(batch))
+    streams = [torch.cuda.Stream() for _ in engines]
+    logits = torch.randn(B, V, device="cuda")
+    masks = torch.full((2, calls, B, engines[0].W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    outs = torch.zeros((2, calls, B, V), device="cuda")
+    torch.cuda.synchronize()
+    for call in range(calls):                      # the first call meets the states
+        for k, e in enumerate(engines):
+            with torch.cuda.stream(streams[k]):
+                zf.compute_mask_apply_async(e, rows[k], masks[k, call], logits, out=outs[k, call])
+                zf.mask_wait(e)
+    torch.cuda.synchronize()
+    allowed = torch.from_numpy(np.unpackbits(want.view(np.uint8), axis=1, bitorder="little")[:, :V].astype(bool)).cuda()
+    wanted = torch.where(allowed, logits, torch.full_like(logits, float("-inf")))
+    for k in range(2):
+        for call in range(calls):
+            assert np.array_equal(masks[k, call].cpu().numpy().view(np.uint32), want), (k, call)
+            assert torch.equal(outs[k, call], wanted), (k, call)
 
 
 @pytest.mark.parametrize("dtype,shift", [("f32", 0), ("bf16", 1)])
