@@ -187,12 +187,15 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states /* host array */, int3
  *   zf_mask_wait returns once the status of the calls in flight is final (a block of their last kernel writes
  * it to pinned host memory, which the call polls; when the fallback pass had work, whose waits can fail, it is
  * the block that finishes last; bounded: after two seconds the stream is synchronised instead).  A call of look-ups only -- every
- * transition it can meet is in the persistent automaton for certain -- cannot fail: its status is final when it is enqueued, and
- * zf_mask_wait does not wait for it (at most 4 such calls are ahead of the host; the next one waits for the oldest).  It does NOT
+ * transition it can meet is in the persistent automaton for certain -- is not expected to fail, and zf_mask_wait lets go of it: it
+ * returns without waiting for it (at most 4 such calls are ahead of the host; the next one waits for the oldest).  Should one fail all the same, a later
+ * zf_mask_wait or waiting call returns ZF_ERR_OVERFLOW for it, and zf_last_error says so: the mask of the call that was let go of is not valid, that of
+ * the call that reports it is.  zf_mask_wait with no call in flight waits for those that were let go of and
+ * reports for all of them (zf_engine_destroy waits too, and has nobody to tell).  A stream is to be synchronised before it is destroyed.  zf_mask_wait does NOT
  * wait for work the caller queued behind them (zf_apply_mask, a sampler), and the mask tensor is to be
  * consumed in stream order: queue its readers on hip_stream, or synchronise the stream before reading it
  * from the host or from another stream (not so after zf_compute_mask, the waiting call).  With no call
- * in flight zf_mask_wait synchronises hip_stream. */
+ * in flight zf_mask_wait synchronises hip_stream, too. */
 int zf_compute_mask_async(zf_engine *e, zf_state *const *states /* host array */, int32_t batch,
                           uint32_t *d_mask, void *hip_stream);
 int zf_mask_wait(zf_engine *e, void *hip_stream);

@@ -34,6 +34,10 @@ int zf_debug_host_mask_automaton(zf_engine *e, const zf_state *s, uint32_t *mask
  * leaves the logits to whoever is done last (0 or 1: once).  Results do not depend on it. */
 int zf_debug_look_polls(zf_engine *e, uint32_t polls);
 
+/* Diagnostic: the engine's next call of look-ups reports so many failed walks, though none has: its mask is right, and the error it makes
+ * is reported where a failure would be. */
+int zf_debug_fail_look_ups(zf_engine *e, uint32_t walks);
+
 /* Host twin of the persistent automaton (the mask kernels' cross-step store, Sections 4.4 / 5.2): every
  * Earley set is named by its content, items carrying the name of the set their rule started in, so the
  * sets of all rows and steps are the states of one automaton over byte classes.  A twin lives beside an

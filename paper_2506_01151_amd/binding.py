@@ -67,7 +67,7 @@ EXPORTS = ["zf_strerror", "zf_last_error", "zf_compile", "zf_engine_destroy", "z
            "zf_compute_mask", "zf_compute_mask_noalloc", "zf_compute_mask_async", "zf_compute_mask_apply_async", "zf_mask_wait", "zf_last_mask_report", "zf_engine_clear_state_cache", "zf_engine_set_profiling", "zf_apply_mask"]
 # test-only diagnostics (include/zapformat_debug.h)
 DEBUG_EXPORTS = ["zf_debug_host_mask", "zf_debug_host_mask_stats", "zf_debug_host_mask_cached", "zf_debug_host_mask_automaton",
-                 "zf_debug_look_polls", "zf_debug_twin_new", "zf_debug_twin_destroy", "zf_debug_twin_advance", "zf_debug_twin_mask"]
+                 "zf_debug_look_polls", "zf_debug_fail_look_ups", "zf_debug_twin_new", "zf_debug_twin_destroy", "zf_debug_twin_advance", "zf_debug_twin_mask"]
 
 
 class ZfError(RuntimeError):
@@ -118,6 +118,7 @@ def load_library():
     L.zf_debug_host_mask_cached.argtypes = [c_vp, c_vp, c_vp, c_vp]
     L.zf_debug_host_mask_automaton.argtypes = [c_vp, c_vp, c_vp, c_vp]
     L.zf_debug_look_polls.argtypes = [c_vp, ctypes.c_uint32]
+    L.zf_debug_fail_look_ups.argtypes = [c_vp, ctypes.c_uint32]
     L.zf_debug_twin_new.argtypes = [c_vp, ctypes.POINTER(c_vp)]
     L.zf_debug_twin_destroy.argtypes = [c_vp]
     L.zf_debug_twin_destroy.restype = None

@@ -118,13 +118,15 @@ struct DeviceSide {
         std::vector<Row> rows;
         uint32_t host_epoch = 0;                     // epoch of the host automaton the names belong to
         int64_t undecided = 0;                       // for the report
-        bool sure = false;                           // look-ups only, over transitions that have been reported to be there: nothing in the call can fail
+        bool sure = false;                           // look-ups only, over transitions that have been reported to be there: nothing in the call is expected to fail
         uint32_t done_groups = 0;                    // words the call reports in (mask_look_kernel); 0: in STORE_ST_DONE
+        uint32_t debug_failed = 0;                   // added to what the call reports
         bool lazy = false;                           // such a call that zf_mask_wait has let go of: its kernels may still be at work with the slot
     } rec[N_SLOTS];
     uint32_t n_lazy = 0;                             // how many slots are
     hipStream_t lazy_stream = nullptr;               // the stream these calls are on
-    uint32_t late_failed = 0;                        // walks that failed in them all the same: an error of the next zf_mask_wait
+    uint32_t late_failed = 0;                        // walks that failed in them all the same: an error that the next call that waits reports (report_late)
+    uint32_t debug_failed = 0;                       // zf_debug_fail_look_ups
     // State cache (Section 5.2) on this path: the pool's slot of a state by its name in the host automaton.  A name says all there
     // is to say about a set, so nothing is packed or compared.
     std::vector<uint32_t> slot_of_host;              // slot + 1; 0 = none
@@ -628,13 +630,14 @@ static bool look_done(const volatile uint64_t *status, const DeviceSide::CallRec
     return true;
 }
 static uint32_t look_failed(const volatile uint64_t *status, const DeviceSide::CallRecord &rec) {
-    uint32_t n = 0;
+    uint32_t n = rec.debug_failed;
     for (uint32_t g = 0; g < rec.done_groups; g++) n += (uint32_t)status[STORE_ST_ROW + g] & 0xFFFFFFu;
     return n;
 }
 // A call that zf_mask_wait has let go of ends before its slot is used again, before a call of the engine comes on another stream and
 // before the store is touched by anything but a kernel behind it on its stream.  (After two seconds the device is synchronised: the
 // call's stream may be gone by then.)
+static void forget_cached_masks(DeviceSide *d);
 static int settle_call(DeviceSide *d, uint32_t k) {
     DeviceSide::CallRecord &rec = d->rec[k];
     if (!rec.lazy) return ZF_OK;
@@ -643,8 +646,15 @@ static int settle_call(DeviceSide *d, uint32_t k) {
     const int rc = await_status([&]() { return look_done(out, rec); }, [] { return hipDeviceSynchronize(); });
     if (rc != ZF_OK) return rc;
     const uint32_t failed = look_failed(out, rec);
-    if (failed) { d->late_failed += failed; d->store_dirty = true; }
+    if (failed) { d->late_failed += failed; d->store_dirty = true; forget_cached_masks(d); }
     return ZF_OK;
+}
+// The failure of a call that zf_mask_wait has let go of, by a call that waits and has itself ended well.
+static int report_late(DeviceSide *d) {
+    if (!d->late_failed) return ZF_OK;
+    const uint32_t n = d->late_failed;
+    d->late_failed = 0;
+    return fail(ZF_ERR_OVERFLOW, std::to_string(n) + " walks failed in a call of look-ups that zf_mask_wait had let go of: its mask is not valid (the one of the call that reports it is)");
 }
 static hipError_t next_call_number(DeviceSide *d, hipStream_t stream) {
     if (++d->call_seq != 0) return hipSuccess;
@@ -1075,6 +1085,12 @@ int zf_position_info(const zf_engine *e, int32_t p, int32_t *lhs, int32_t *rule,
 
 int zf_debug_host_mask(zf_engine *e, const zf_state *s, uint32_t *mask) { return zf_debug_host_mask_stats(e, s, mask, nullptr); }
 
+int zf_debug_fail_look_ups(zf_engine *e, uint32_t walks) {
+    if (!e || !e->dev) return fail(ZF_ERR_INVALID_ARG, "bad argument");
+    e->dev->debug_failed = walks;
+    return ZF_OK;
+}
+
 int zf_debug_look_polls(zf_engine *e, uint32_t polls) {
     if (!e || !e->dev) return fail(ZF_ERR_INVALID_ARG, "bad argument");
     e->dev->look_polls = polls;
@@ -1199,6 +1215,7 @@ static int state_cache_lookup(DeviceSide *d, const std::vector<std::vector<uint3
 }
 
 static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, uint32_t slot);
+static int wait_for_calls(zf_engine *e, void *hip_stream);
 static const int STORE_NO_ROOM = 1;                       // enqueue_store_impl: the call does not fit the memory at hand (noalloc); nothing was enqueued
 // zf_compute_mask_apply_async: the logits the call's mask is to be applied to.  The mask kernel over the persistent automaton
 // takes them along when it can (fused = true); whoever set the request launches the logit-masking kernel otherwise.
@@ -1507,7 +1524,7 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         return ZF_OK;
     }
     HIP_TRY(hipStreamSynchronize(stream));               // the waiting call returns with the mask complete, not only its status known
-    return zf_mask_wait(e, hip_stream);
+    return wait_for_calls(e, hip_stream);
 }
 
 static void forget_cached_masks(DeviceSide *d) {
@@ -2023,7 +2040,9 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
                                            (const uint32_t *)(stage + off_imp), (uint32_t)n_imp, d->d_import_root, stream));
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
     d->closing_kernel = false;
+    rec.debug_failed = 0;
     if (look) {
+        rec.debug_failed = d->debug_failed; d->debug_failed = 0;
         k.tickets = a.tickets; k.tickets_next = a.tickets_next; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
         k.mask_blocks = a.n_blocks;
         const uint32_t grid = look_grid(k);
@@ -2042,17 +2061,19 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;
     rec.active = true;
-    // Nothing in the call can fail: its states' transitions are in the table for certain, no call in flight is still to say so.  zf_mask_wait
+    // Nothing in the call is expected to fail: its states' transitions are in the table for certain, no call in flight is still to say so.  zf_mask_wait
     // then has nothing to wait for, and the host gets the next step ready while this one is at work (a step of one row x 32,000: 13.6 us
     // waited for, 10.1 not; 16 x 128,256 bf16 14.4 and 12.3; 130 x 40,037 bf16 26.1 and 21.6).
+    // (Not one that leaves rows in the state cache's pool: later calls are served those.)
     rec.sure = look && !wait && !prof && !d->store_dirty;
+    for (const RowGroup &g : c.g) rec.sure &= g.pooled || !g.keep;
     uint32_t in_store = 0;                                // calls in flight that went through the store; the others have flags that zf_mask_wait has to await
     for (const DeviceSide::CallRecord &other : d->rec) if (other.active) { in_store++; if (!other.sure) rec.sure &= &other == &rec; }
     rec.sure &= in_store == d->pending;
     if (rec.sure) d->lazy_stream = stream;
     host_lk.unlock();
     // the waiting call returns with the mask complete: the kernel wrote it through to memory before it drew its tickets
-    return wait ? zf_mask_wait(e, hip_stream) : ZF_OK;
+    return wait ? wait_for_calls(e, hip_stream) : ZF_OK;
 }
 
 // A call that fails part-way may have registered cache slots whose masks were never written.
@@ -2073,6 +2094,10 @@ static int enqueue_mask(zf_engine *e, zf_state *const *states, int32_t batch, ui
             rc = enqueue_mask_impl(e, states, batch, d_mask, hip_stream, wait, noalloc, true);
             if (rc != ZF_OK) forget_cached_masks(d);
         }
+    }
+    if (rc == ZF_OK && wait) {                            // calls that were let go of are behind the stream's newest by now: what they have to report is there
+        rc = settle_calls(d);
+        if (rc == ZF_OK) rc = report_late(d);
     }
     return rc;
 }
@@ -2228,8 +2253,7 @@ int zf_compute_mask_apply_async(zf_engine *e, zf_state *const *states, int32_t b
     return zf_apply_mask(e, d_logits, d_out, dtype, batch, row_stride, d_mask, hip_stream);   // the trie walk, the state cache, first visits over many logits, odd addresses: two launches
 }
 
-int zf_mask_wait(zf_engine *e, void *hip_stream) {
-    if (!e || !e->dev) return fail(ZF_ERR_INVALID_ARG, "bad argument");
+static int wait_for_calls(zf_engine *e, void *hip_stream) {
     DeviceSide *d = e->dev;
     HIP_TRY(hipSetDevice(d->device));
     volatile uint32_t *st = d->h_status;
@@ -2293,10 +2317,10 @@ int zf_mask_wait(zf_engine *e, void *hip_stream) {
         if (rc != ZF_OK) { d->pending = 0; return rc; }
         if (d->profiling) HIP_TRY(hipEventSynchronize(d->ev[3]));
     } else {
-        HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));   // nothing of this engine in flight: plain stream synchronisation
+        HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));   // nothing of this engine in flight: plain stream synchronisation ...
+        const int rc = settle_calls(d);                   // ... but for calls that were let go of
+        if (rc != ZF_OK) return rc;
     }
-    unresolved += d->late_failed;
-    d->late_failed = 0;
     for (int k = 0; k < DeviceSide::N_SLOTS; k++) {
         unresolved += st[8 * k + 2];
         if (st[8 * k + 0] && d->lanes_call[k]) d->lanes_outgrown = true;
@@ -2313,6 +2337,12 @@ int zf_mask_wait(zf_engine *e, void *hip_stream) {
     if (unresolved) forget_cached_masks(d);               // masks written by the failed call must not be served from the cache
     if (unresolved) return fail(ZF_ERR_OVERFLOW, std::to_string(unresolved) + " trie chunks exceeded the fallback arena");
     return ZF_OK;
+}
+
+int zf_mask_wait(zf_engine *e, void *hip_stream) {
+    if (!e || !e->dev) return fail(ZF_ERR_INVALID_ARG, "bad argument");
+    const int rc = wait_for_calls(e, hip_stream);
+    return rc != ZF_OK ? rc : report_late(e->dev);
 }
 
 int zf_engine_clear_state_cache(zf_engine *e) {

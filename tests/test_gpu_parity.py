@@ -1417,6 +1417,67 @@ def test_calls_that_mask_wait_lets_go_of(B, dtype, torch_cuda, oracle_lib):
         assert outs[step].view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), step
 
 
+def test_failures_of_calls_that_mask_wait_has_let_go_of(torch_cuda, oracle_lib):
+    """A call of look-ups that reports failed walks after mask_wait has let go of it: mask_wait with nothing in flight says so, and so does a waiting call,
+    whose own mask is right, and which is not taken for the one that failed (nothing is answered again, the persistent automaton is not put on hold).  A waiting
+    call's own failure is answered again; a call that leaves rows in the state cache is not let go of."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks = configs.CONFIGS[3].grammar(), configs.CONFIGS[3].vocab(8192)
+    off, data = wvocab.vocab_csr(toks)
+    so = oracle_lib.Oracle(g).new_state()
+    assert so.feed_bytes(b'{"')
+    want = so.mask(off, data, 8)
+    lib, logits = zf.load_library(), torch.randn(1, len(toks), device="cuda")
+
+    def engine(**kw):
+        eng = zf.Engine(g, toks, device=0, **kw)         # no recursion: every call is of look-ups only
+        rows = zf.StateBatch([eng.new_state()])
+        rows.states[0].advance_bytes(b'{"')
+        return eng, rows, torch.full((1, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+
+    def good(d_mask):
+        torch.cuda.synchronize()
+        return np.array_equal(d_mask.cpu().numpy().view(np.uint32)[0], want)
+
+    def start(eng, rows, d_mask, apply, failing=3):
+        assert lib.zf_debug_fail_look_ups(eng.h, failing) == 0
+        if apply:
+            zf.compute_mask_apply_async(eng, rows, d_mask, logits)
+        else:
+            zf.compute_mask_async(eng, rows, d_mask)
+
+    for apply in (False, True):
+        eng, rows, d_mask = engine(state_cache_entries=-1)
+        start(eng, rows, d_mask, apply)
+        zf.mask_wait(eng)                                # let go of
+        with pytest.raises(zf.ZfError, match="3 walks failed in a call of look-ups that zf_mask_wait had let go of"):
+            zf.mask_wait(eng)                            # nothing in flight
+        zf.mask_wait(eng)                                # said once
+        zf.compute_mask(eng, rows, d_mask)
+        assert good(d_mask)
+        start(eng, rows, d_mask, apply)
+        zf.mask_wait(eng)
+        other = torch.full_like(d_mask, 0x5A5A5A5A)
+        with pytest.raises(zf.ZfError, match="let go of"):
+            zf.compute_mask(eng, rows, other)
+        assert good(other)
+        eng.set_profiling(True)
+        zf.compute_mask(eng, rows, d_mask)
+        assert eng.mask_report().permute_ms == 0 and good(d_mask)   # no closing kernel: not through the per-block automaton
+        eng.set_profiling(False)
+    zf.compute_mask(eng, rows, d_mask)
+    lib.zf_debug_fail_look_ups(eng.h, 5)
+    d_mask.fill_(-1)
+    eng.set_profiling(True)
+    zf.compute_mask(eng, rows, d_mask)                   # its own failure: answered through the per-block automaton
+    assert good(d_mask) and eng.mask_report().permute_ms > 0
+    eng, rows, d_mask = engine()                         # the state cache on
+    start(eng, rows, d_mask, False)
+    with pytest.raises(zf.ZfError, match="exceeded the fallback arena"):
+        zf.mask_wait(eng)
+
+
 @pytest.mark.parametrize("walk_mode,pruning", [(0, True), (1, True), (2, False)])
 def test_status_ahead_of_the_closing_kernel_and_another_stream(walk_mode, pruning, torch_cuda, oracle_lib):
     """mask_wait returns when a call's closing kernel has begun; the next call comes on another stream, nothing synchronised between them, and does not
