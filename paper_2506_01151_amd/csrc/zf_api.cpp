@@ -661,6 +661,8 @@ static hipError_t next_call_number(DeviceSide *d, hipStream_t stream) {
     d->call_seq = 1;                                      // numbers start over: no mask word lies about with one that comes again
     return d->d_tagged ? launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(d->tagged_cap * 2), stream) : hipSuccess;
 }
+// Whether work on `now` is behind what was enqueued on `then`.  (The handle of a thread's own stream is the same in every thread.)
+static bool same_stream(hipStream_t now, hipStream_t then) { return now == then && now != hipStreamPerThread; }
 static int settle_calls(DeviceSide *d) {
     int rc = ZF_OK;
     for (int k = 0; d->n_lazy && k < DeviceSide::N_SLOTS; k++) { const int r = settle_call(d, (uint32_t)k); if (rc == ZF_OK) rc = r; }
@@ -1239,10 +1241,10 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     const uint32_t slot = d->next_slot;
     // (no event marks the slot free: at most N_SLOTS calls are in flight between two zf_mask_wait calls, so the call that used it before has been waited for, or is now)
     if (d->n_lazy) {
-        const int rc = stream == d->lazy_stream ? settle_call(d, slot) : settle_calls(d);
+        const int rc = same_stream(stream, d->lazy_stream) ? settle_call(d, slot) : settle_calls(d);
         if (rc != ZF_OK) return rc;
     }
-    if (d->closing_open && stream != d->closing_stream) {
+    if (d->closing_open && !same_stream(stream, d->closing_stream)) {
         HIP_TRY(hipStreamWaitEvent(stream, d->closing_done, 0));
         d->closing_stream = stream;                       // which is behind it now
     }

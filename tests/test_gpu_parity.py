@@ -1515,6 +1515,56 @@ def test_status_ahead_of_the_closing_kernel_and_another_stream(walk_mode, prunin
         assert outs[call].cpu().numpy().view(np.uint32).tobytes() == oracle_apply(bits, want).tobytes(), call
 
 
+@pytest.mark.parametrize("walk_mode", [0, 2])
+def test_threads_that_take_turns_on_their_own_streams(walk_mode, torch_cuda, oracle_lib):
+    """Two threads that take turns with an engine, each on its per-thread default stream -- one handle, two streams: a call goes behind the one before it.  More
+    calls than slots, rows in other states each time; masks and masked logits are the oracle's."""
+    import threading
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g, toks, B, calls = configs.CONFIGS[3].grammar(), configs.CONFIGS[3].vocab(8192), 96, 12
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1, walk_mode=walk_mode)
+    prefixes, per_state, rows = [b"", b"{", b'{"'], [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        per_state.append(so.mask(off, data, 8))
+        rows.append([eng.new_state() for _ in range(B)])
+        for s in rows[-1]:
+            s.advance_bytes(p)
+    logits = torch.randn(B, len(toks), device="cuda")
+    masks = torch.full((calls, B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    outs = torch.zeros((calls, B, len(toks)), device="cuda")
+    torch.cuda.synchronize()
+    turn, failed = [threading.Semaphore(1), threading.Semaphore(0)], []
+
+    def work(k):
+        for call in range(k, calls, 2):
+            turn[k].acquire()
+            try:
+                with torch.cuda.stream(torch.cuda.ExternalStream(2)):   # hipStreamPerThread
+                    zf.compute_mask_apply_async(eng, [rows[(b + call) % 3][b] for b in range(B)], masks[call], logits, out=outs[call])
+                    zf.mask_wait(eng)
+            except Exception as e:
+                failed.append(e)
+            turn[1 - k].release()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    torch.cuda.synchronize()
+    for call in range(calls):
+        want = np.stack([per_state[(b + call) % 3] for b in range(B)])
+        allowed = torch.from_numpy(np.unpackbits(want.view(np.uint8), axis=1, bitorder="little")[:, :len(toks)].astype(bool)).cuda()
+        assert np.array_equal(masks[call].cpu().numpy().view(np.uint32), want), call
+        assert torch.equal(outs[call], torch.where(allowed, logits, torch.full_like(logits, float("-inf")))), call
+
+
 def test_look_ups_behind_a_per_block_call_in_flight(torch_cuda, oracle_lib):
     """A call of look-ups right behind one through the per-block automaton, both in flight: mask_wait has the status of the first as well (the report
     counts what its item budget of two left to the fallback pass), and calls that use its slot again find it free.  Masks are the oracle's."""
