@@ -1864,11 +1864,13 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     // mask_look_kernel masks the logits with wavefronts of their own, whatever their size: they read them while the others work the masks out.  The
     // logits are dealt out in units of as many KB as make 2,048 wavefronts, 4 at most (units of 2 / 4 / 6 / 8 KB, us per pass: 16 steps of 16 x 128,256
     // bf16 171 / 176 / 184 / 186, of 64 x 152,064 fp32 - / 361 / 371 / 379, 8 steps of 130 x 40,037 bf16 148 / 144 / 149 / 151; 256 x 128,256 - / 235 / 229 / 239).
-    if (look && whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32)) {
-        const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
-        const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
-        k.unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048));
-        k.row_units = (row_kb + k.unit_kb - 1) / k.unit_kb;
+    const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
+    const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
+    const uint32_t unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048)), row_units = (row_kb + unit_kb - 1) / unit_kb;
+    if (look && whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32) && (uint64_t)row_units * (uint64_t)batch <= LOOK_UNITS_MAX) {
+        static_assert(LOOK_UNITS_MAX / STORE_WAVES + 9 * MAX_BATCH + 4096 <= 16 * 65535, "with the mask's (max_blocks) the blocks of a group fit their count");
+        k.unit_kb = unit_kb;
+        k.row_units = row_units;
         k.units = k.row_units * (uint32_t)batch;
         const size_t words = (size_t)ng * (size_t)d->tab.W + (k.units + STORE_WAVES - 1) / STORE_WAVES;
         if (words > d->tagged_cap) {

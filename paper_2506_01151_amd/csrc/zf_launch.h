@@ -189,6 +189,8 @@ struct LookArgs {
     const uint16_t *group_of;          // of the k-th entry of `members`, where the records are in device memory
 };
 static_assert(sizeof(LookArgs) + sizeof(LookInline) <= 4096, "the kernel's argument block");
+// Units of a call: its blocks report in 16 groups, each counted in 16 bits.
+static const uint32_t LOOK_UNITS_MAX = 4000000;
 inline uint32_t look_grid(const LookArgs &a) { return a.mask_blocks + (a.units + STORE_WAVES - 1) / STORE_WAVES; }
 // Words of a call's status in pinned host memory.  Every word carries the call's number in its upper half, so the host knows of
 // each word by itself whether it has arrived: no order between them is needed (a release would write the L2 back first).

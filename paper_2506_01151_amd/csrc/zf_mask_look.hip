@@ -75,7 +75,8 @@ __device__ __forceinline__ LookTicket draw_ticket(const LookArgs &a, uint32_t fa
 }
 __device__ __forceinline__ void tell_host(const LookArgs &a, const LookTicket &t) {
     if ((t.sum & 0xFFFFull) != t.size) return;
-    __hip_atomic_store(&a.status[STORE_ST_ROW + t.group], ((unsigned long long)a.seq << 32) | ((uint32_t)(t.sum >> 16) & 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const uint32_t failed = (uint32_t)(t.sum >> 16);
+    __hip_atomic_store(&a.status[STORE_ST_ROW + t.group], ((unsigned long long)a.seq << 32) | (failed < 0xFFFFFFu ? failed : 0xFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 // Blocks that have left units: behind the mask words, a word for every block with logits, which travels as they do: call's number << 32 | a bit per wavefront.
 __device__ __forceinline__ unsigned long long *left_units(const LookArgs &a) { return a.tagged + (size_t)a.n_groups * a.W; }

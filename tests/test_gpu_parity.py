@@ -1241,6 +1241,40 @@ def test_logits_left_to_the_block_that_is_last(V, B, dtype, shift, torch_cuda, o
     test_logits_masked_along_with_look_ups(V, B, dtype, shift, torch_cuda, oracle_lib, polls=0)
 
 
+@pytest.mark.parametrize("V", [974848, 1048575])
+def test_logits_masked_along_to_the_largest_grid(V, torch_cuda, oracle_lib):
+    """4,096 rows of fp32 logits, 16 GB in place: about the most blocks that are counted in a group's 16 bits, and more than that (a launch of its own masks them)."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    B = 4096
+    toks = (configs.CONFIGS[2].vocab(4096) + [b"%d" % k for k in range(10**7, 10**7 + V)])[:V]
+    off, data = wvocab.vocab_csr(toks)
+    g = grammars.json_grammar()
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, state_cache_entries=-1)
+    prefixes, want, first = [b"[1", b'{"k":'], [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+        first.append(eng.new_state())
+        first[-1].advance_bytes(p)
+    rows = zf.StateBatch([first[b % 2].clone() for b in range(B)])
+    base = torch.randn(V, device="cuda")
+    logits = base.repeat(B, 1)
+    d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, first, d_mask[:2])                  # the states have been met: what follows is look-ups
+    zf.compute_mask_apply_async(eng, rows, d_mask, logits, out=logits)
+    zf.mask_wait(eng)
+    zf.mask_wait(eng)                                        # nothing in flight: for the calls that were let go of
+    for k in range(2):
+        allowed = torch.from_numpy(np.unpackbits(want[k].view(np.uint8), bitorder="little")[:V].astype(bool)).cuda()
+        wanted, mask = torch.where(allowed, base, torch.full_like(base, float("-inf"))), torch.from_numpy(want[k].view(np.int32)).cuda()
+        for b in range(k, B, 64):
+            assert torch.equal(logits[b:b + 64:2], wanted.expand_as(logits[b:b + 64:2])), b
+            assert torch.equal(d_mask[b:b + 64:2], mask.expand_as(d_mask[b:b + 64:2])), b
+
+
 @pytest.mark.parametrize("polls", [None, 0, 3])
 def test_look_ups_with_logits_of_two_engines_at_once(polls, torch_cuda, oracle_lib):
     """Two engines, each on a stream of its own, both with more blocks of logits than the chip holds: whichever blocks have the places, every logit is masked."""
