@@ -1520,7 +1520,8 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
     d->last_seq = a.seq; d->last_slot = slot;
     d->closing_open = !wait;
     if (!wait) {
-        if (!d->closing_done) HIP_TRY(hipEventCreateWithFlags(&d->closing_done, hipEventDisableTiming));
+        // (without the fences that show memory to the host and other devices: what waits for it only has to come later, on this device)
+        if (!d->closing_done) HIP_TRY(hipEventCreateWithFlags(&d->closing_done, hipEventDisableTiming | hipEventDisableSystemFence));
         HIP_TRY(hipEventRecord(d->closing_done, stream));
         d->closing_stream = stream;
         return ZF_OK;
