@@ -38,8 +38,8 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one; masks and logits) and of apply_mask_vec_kernel, from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 15762808, "apply_bytes_per_launch": 8493669, "instructions_per_launch": 3842486,
-                    "kernel_sources_sha256": "2842787a680504c1aa965e769abf3db15c1a6e572490b1c2f83caf09d4813d15"}
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 15756312, "apply_bytes_per_launch": 8493560, "instructions_per_launch": 3780991,
+                    "kernel_sources_sha256": "d1a96e3116e018bcf818f6154083b0c1b75b4b9494bdde66116f892d74403c0a"}
 
 
 def kernel_sources_digest():

@@ -2051,8 +2051,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         k.tickets = a.tickets; k.tickets_next = a.tickets_next; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
         k.mask_blocks = a.n_blocks;
         const uint32_t grid = look_grid(k);
-        // Up to 64 blocks each have a status word of their own, and nobody draws a ticket (one row x 32,000 223 -> 214 us per 32 steps, x 2,048 of
-        // plain calls 396 -> 387); more share 16 (16 x 128,256, eight waiting calls: 139; with 64 words to look at 143, in two levels 139).
+        // Up to 64 blocks each have a status word of their own, and nobody draws a ticket (one row x 32,000 223 -> 214 us per 32 steps); more share 16 (16 x 128,256, eight waiting calls: 139; with 64 words to look at 143, in two levels 139).
         k.done_groups = rec.done_groups = grid <= (uint32_t)STORE_TICKET_GROUPS ? grid : 16u;
         HIP_TRY(launch_mask_look(k, c.look, stream));
     } else {

@@ -130,8 +130,8 @@ __device__ __forceinline__ BaseG global_base(const MaskArgs &a, uint32_t row) {
 
 // What the last kernel of a call does at the end of every block: one block copies the call's counters to pinned host memory,
 // clears the next call's set, and then writes the word the host polls.  ticketed = false: the counters were final before this
-// kernel started (nothing in it can fail), and the block with the highest index does it at its end: the word then says "the
-// status is known", and readers of the mask are ordered behind the kernel by the stream.  ticketed = true (the closing kernel
+// kernel started (nothing in it can fail), and the block with the highest index does it, first of all: the word then says "the
+// status is known", and readers of the mask are ordered behind the kernel by the stream (what the kernel itself reads of the engine, by an event behind it).  ticketed = true (the closing kernel
 // with a fallback pass to run, whose waits can fail): every block draws a ticket when it is done and the block that draws
 // the last one does it, so that no error is counted after the hand-over.  Tickets are drawn in two levels (group of blocks,
 // then groups); even so they cost the kernel 5 us at 2,004 blocks (a ticket is a round trip to memory), which is why the

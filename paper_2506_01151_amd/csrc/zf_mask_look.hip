@@ -131,7 +131,8 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
     if (!ready) {
         for (;;) {
             // few wavefronts look again at once, many stay out of the way (16 x 128,256 bf16 145.0 us per 16 steps with 8 here, 142.8 with 1, 146.5 with 16;
-            // one row x 32,000 201.6, 198.4, 207.4; 64 x 152,064 fp32 342.7, 343.7 with 3, 341.2 with 16; 256 x 128,256 225.2, 227.5 with 3, 224.1)
+            // one row x 32,000 201.6, 198.4, 207.4; 64 x 152,064 fp32 342.7, 343.7 with 3, 341.2 with 16; 256 x 128,256 225.2, 227.5 with 3, 224.1: differences
+            // of 1 to 4 %, where runs of one side differ by as much at one row and by 0.1 to 1 % at the others; where the line lies between them is not borne out)
             if (a.units <= 2048u) __builtin_amdgcn_s_sleep(1); else __builtin_amdgcn_s_sleep(16);
             here = true;
 #pragma unroll
