@@ -430,7 +430,7 @@ def main():
         "mean_advance_us_per_step": statistics.fmean(adv) * 1e6,
         "pipelined_steps": {"ms_per_step": piped["total"] / K * 1e3, "value": B * V * K / piped["total"],
                             "note": "the same steps without the stream synchronisation: a step ends when zf_mask_wait has returned, which is when the call's outcome is known -- "
-                                    "for a call of look-ups when it is enqueued; the passes' total ends with the stream synchronised, so every kernel is in it: "
+                                    "for a call of look-ups, which is not expected to fail, when it is enqueued; the passes' total ends with the stream synchronised, so every kernel is in it: "
                                     "a decode loop whose sampler runs on the same stream"},
         "warm_automaton": {"ms_per_step": warm["total"] / K * 1e3, "value": B * V * K / warm["total"], "p50_mask_apply_latency_us": pct(warm["lat"], 0.5) * 1e6,
                            "note": "the same steps once more without clearing the persistent automaton: every transition is a look-up"},
