@@ -327,7 +327,7 @@ int begin_device(zf_engine *e) {
             first_off.push_back((uint32_t)first_state.size());
         }
         if ((rc = upload(d, t.delta, &r.delta)) != ZF_OK || (rc = upload(d, t.qflags, &r.qflags)) != ZF_OK || (rc = upload(d, first_off, &r.first_off)) != ZF_OK ||
-            (rc = upload(d, first_state, &r.first_state)) != ZF_OK) return rc;
+            (rc = upload(d, first_state, &r.first_state)) != ZF_OK || (rc = upload(d, e->follow.behind, &r.behind)) != ZF_OK || (rc = upload(d, e->follow.next, &r.follow)) != ZF_OK) return rc;
         r.cls = T.cls; r.Q = (uint32_t)t.Q; r.N = (uint32_t)t.N; r.n_cls = (uint32_t)t.n_cls;
     }
     if (e->store_on) {
@@ -352,7 +352,7 @@ int begin_device(zf_engine *e) {
 size_t engine_bytes(const zf_engine *e) {
     const Tables &t = e->tab;
     const size_t V = (size_t)e->V, W = (size_t)e->W + 1, n_rows = (size_t)(t.Q + t.N), text = e->voc_bytes.size(), cap = store_cap_states(t.n_cls), ncls = (size_t)std::max(t.n_cls, 1);
-    size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * t.delta.size();
+    size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * (t.delta.size() + e->follow.behind.size() + e->follow.next.size());
     n += text * (sizeof(TrieNode) + 4 + 2) + (V / (size_t)e->opt.chunk_strings + 1) * (8 + CHUNK_ANC * sizeof(TrieNode)) + V * (4 + 4 + sizeof(Str16)) + n_rows * W * 8;
     if (e->store_on) n += V * (8 + sizeof(Str16)) + text + n_rows * (W * 8 + 4) + cap * (sizeof(uint2) + ncls * 4 + 16) + STORE_CAP_ITEMS * sizeof(uint2) + (size_t)MAX_BATCH * 4;
     if (e->opt.state_cache_entries > 0) n += (size_t)e->opt.state_cache_entries * W * 4;
@@ -749,6 +749,8 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
+        if (e->lane_cap_auto) build_follow(e->tab, e->follow);
+        else follow_everything(e->tab, e->follow);        // an explicit item budget is there to see sets outgrow it: every string that a terminal leaves open is walked
         if (e->opt.device >= 0) {
             const int rc = begin_device(e);
             if (rc != ZF_OK) return give_up(rc);
@@ -760,7 +762,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
                 else fetcher.error = zf_last_error();
             });
         build_trie(v, e->opt.chunk_strings, e->tab.cls, e->trie);
-        if (e->opt.device < 0) build_token_mask_cache(e->tab, e->trie);
+        if (e->opt.device < 0) build_token_mask_cache(e->tab, e->follow, e->trie);
     } catch (const std::bad_alloc &) { return give_up(fail(ZF_ERR_OOM, "out of memory")); }
     catch (const std::system_error &) { return give_up(fail(ZF_ERR_OOM, "no thread to be had")); }
     if (e->opt.device >= 0) {
@@ -1102,7 +1104,7 @@ int zf_debug_look_polls(zf_engine *e, uint32_t polls) {
 int zf_debug_host_mask_cached(zf_engine *e, const zf_state *s, uint32_t *mask, int64_t *stats) {
     if (!e || !s || !mask || s->eng != e) return fail(ZF_ERR_INVALID_ARG, "bad argument");
     const Tables &t = e->tab;
-    host_token_mask_cache(t, e->trie);
+    host_token_mask_cache(t, e->follow, e->trie);
     const Trie &tr = e->trie;
     Chart c = chart_of(s);
     const uint32_t m0 = c.n_sets();

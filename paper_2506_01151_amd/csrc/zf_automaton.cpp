@@ -109,7 +109,7 @@ using namespace zf;
 extern "C" int zf_debug_host_mask_automaton(zf_engine *e, const zf_state *s, uint32_t *mask, int64_t *stats) {
     if (!e || !s || !mask || s->eng != e) { set_error("bad argument"); return ZF_ERR_INVALID_ARG; }
     const Tables &t = e->tab;
-    host_token_mask_cache(t, e->trie);
+    host_token_mask_cache(t, e->follow, e->trie);
     const Trie &tr = e->trie;
     const Chart &c = chart_of(s);
     const uint32_t m0 = c.n_sets();
@@ -185,7 +185,7 @@ extern "C" int zf_debug_twin_mask(zf_twin *tw, uint32_t state, uint32_t *mask, i
     if (!tw || !mask) { set_error("bad argument"); return ZF_ERR_INVALID_ARG; }
     zf_engine *e = tw->eng;
     const Tables &t = e->tab;
-    host_token_mask_cache(t, e->trie);
+    host_token_mask_cache(t, e->follow, e->trie);
     const Trie &tr = e->trie;
     HostAutomaton &a = tw->a;
     const uint32_t root = state == 0 ? HostAutomaton::ROOT : state;
@@ -196,14 +196,14 @@ extern "C" int zf_debug_twin_mask(zf_twin *tw, uint32_t state, uint32_t *mask, i
         if (root >= a.n_states) { set_error("unknown state"); return ZF_ERR_INVALID_ARG; }
         std::vector<uint32_t> valid(tr.Wr, 0), want(tr.Wr, 0);
         if (e->opt.disable_token_mask_cache) want.assign(tr.Wr, 0xFFFFFFFFu);
-        else for (uint32_t i = 0; i < a.st(root).n_items; i++) {   // the token-mask cache rows of the state's items (Section 4.3)
+        else for (uint32_t i = 0; i < a.st(root).n_items; i++) {   // the token-mask cache rows of the state's items (Section 4.3), without what Follow decides: it is checked here
             const Item it = a.st(root).items[i];
             const uint16_t code = t.sym[it.p];
             size_t row;
             if ((code >> SYM_KIND_SHIFT) == SYM_TERM) row = it.q;
             else if ((code >> SYM_KIND_SHIFT) == SYM_NT) row = (size_t)t.Q + (code & SYM_ID_MASK_NT);
             else continue;
-            for (int w = 0; w < tr.Wr; w++) { valid[w] |= tr.ci_valid[row * tr.Wr + w]; want[w] |= tr.ci_cd[row * tr.Wr + w]; }
+            for (int w = 0; w < tr.Wr; w++) { valid[w] |= tr.ci_valid[row * tr.Wr + w]; want[w] |= tr.ci_ends[row * tr.Wr + w]; }
         }
         for (int w = 0; w < tr.Wr; w++) want[w] &= ~valid[w];
         for (uint32_t r = 0; r < (uint32_t)tr.n_strings; r++) {

@@ -106,7 +106,7 @@ struct HostAutomaton {
     // sets it refers to, by their names, and leaves the new set in w; record writes it down.
     struct Work {
         std::vector<Item> set;
-        bool alive, accepted;
+        bool alive = false, accepted = false;
         std::vector<uint32_t> seen;       // sets of more than a few items find duplicates by hashing: item number + 1, 0 = free
         static constexpr size_t FEW = 16;
         static uint32_t hash(const Item &it) { uint32_t h = ((uint32_t)it.p | (uint32_t)it.q << 16) * 0x9E3779B1u ^ it.o * 0x85EBCA77u; h ^= h >> 15; h *= 0x2C1B3C6Du; return h ^ h >> 13; }
@@ -146,7 +146,11 @@ struct HostAutomaton {
         }
     }
     void look_ahead(uint32_t s, int cl, Work &w) const {
-        w.set.clear(); w.accepted = false;
+        scan(s, cl, s, w);
+        close(w);
+    }
+    void scan(uint32_t s, int cl, uint32_t begun, Work &w) const {   // begun: the set that the rules begun by this byte are said to start in
+        w.set.clear();
         const State &src = st(s);
         for (uint32_t i = 0; i < src.n_items; i++) {           // Scan
             const Item it = src.items[i];
@@ -162,11 +166,14 @@ struct HostAutomaton {
                 for (uint32_t k = t.scan_off[at]; k < t.scan_off[at + 1]; k++) {
                     const uint16_t p0 = t.scan_list[k] & 0xFFFF, q2 = t.scan_list[k] >> 16;
                     const uint8_t f = t.qflags[q2];
-                    if (f & QF_CONT) w.insert(Item{p0, q2, s});
-                    if (f & QF_ACCEPT) advanced(w, p0 + 1u, s);
+                    if (f & QF_CONT) w.insert(Item{p0, q2, begun});
+                    if (f & QF_ACCEPT) advanced(w, p0 + 1u, begun);
                 }
             }
         }
+    }
+    void close(Work &w) const {
+        w.accepted = false;
         for (size_t i = 0; i < w.set.size(); i++) {            // Complete (the set grows on the way)
             const Item it = w.set[i];
             const uint16_t code = t.sym[it.p];
@@ -186,6 +193,9 @@ struct HostAutomaton {
                 }
             }
         }
+        drop_completed(w);
+    }
+    void drop_completed(Work &w) const {
         w.alive = !w.set.empty();
         size_t n = 0;                                          // completed items only matter while their own set is worked on (Figure 3, first rule)
         for (const Item &it : w.set) if ((t.sym[it.p] >> SYM_KIND_SHIFT) != SYM_END) w.set[n++] = it;

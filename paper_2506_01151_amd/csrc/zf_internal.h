@@ -74,6 +74,16 @@ struct Tables {
 };
 bool build_tables(const zf_grammar_desc *g, Tables &t);
 
+// ---- what may follow a terminal ---------------------------------------------------------------
+// A finite automaton over byte classes that takes, behind a terminal, every string that some context takes there, and others.  Its states are
+// sets of Earley items without origins: a completed nonterminal is handed to every position of the grammar that waits for one.
+struct Follow {
+    std::vector<uint16_t> behind;     // [Q] state behind the terminal that the DFA state belongs to (or FOLLOW_ANY, FOLLOW_DEAD)
+    std::vector<uint16_t> next;       // [states][n_cls]
+};
+void build_follow(const Tables &t, Follow &f);
+inline void follow_everything(const Tables &t, Follow &f) { f.behind.assign(t.Q, FOLLOW_ANY); f.next.assign(t.n_cls, FOLLOW_ANY); }
+
 // ---- vocabulary trie ------------------------------------------------------------------------
 struct Trie {
     std::vector<TrieNode> nodes;      // preorder
@@ -87,15 +97,16 @@ struct Trie {
     int chunk_ranks = 32;
     int Wr = 0;                       // words per row of a rank-ordered bitmap
     std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]; empty in an engine with a device until somebody asks (host_token_mask_cache)
+    std::vector<uint32_t> ci_ends;    // ci_cd, and the strings whose rest no context takes: what the terminal by itself leaves open
 };
 // Context-independent token-mask cache (Section 4.3): per DFA state and per nonterminal, which
-// strings are decided by the terminal alone and which need the parser.
-void build_token_mask_cache(const Tables &t, Trie &tr);
+// strings are decided by the terminal alone, or by what may follow it in any context, and which need the parser.
+void build_token_mask_cache(const Tables &t, const Follow &f, Trie &tr);
 // An engine with a device works its rows out there: the host diagnostics make the host's when they need them, one thread at a time.
-inline void host_token_mask_cache(const Tables &t, Trie &tr) {
+inline void host_token_mask_cache(const Tables &t, const Follow &f, Trie &tr) {
     static std::mutex mu;
     std::lock_guard<std::mutex> lk(mu);
-    if (tr.ci_valid.empty()) build_token_mask_cache(t, tr);
+    if (tr.ci_valid.empty()) build_token_mask_cache(t, f, tr);
 }
 void build_trie(const zf_vocab_desc *v, int chunk_ranks, const uint8_t *cls, Trie &t);
 
@@ -119,6 +130,7 @@ void chart_compact(const Tables &t, Chart &c);
 
 struct zf_engine {
     zf::Tables tab;
+    zf::Follow follow;
     zf::Trie trie;
     zf_options opt;
     int32_t V = 0, W = 0;

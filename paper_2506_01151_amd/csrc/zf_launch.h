@@ -296,6 +296,7 @@ struct VocabRows {
     const uint8_t *bytes, *cls, *qflags;
     const uint16_t *delta;             // [Q][n_cls] next state, DFA_DEAD = none
     const uint32_t *first_off, *first_state;
+    const uint16_t *behind, *follow;   // what may follow a terminal (Follow): [Q] state behind it, [states][n_cls] next state
     uint2 *both;
     uint32_t *valid, *undecided, *counts;
     uint32_t n, words, Q, N, n_cls;

@@ -1,6 +1,6 @@
 // What zf_compile derives from the vocabulary's bytes and the terminals' DFAs, worked out on the device: the strings as byte
 // classes, and the token-mask cache (Section 4.3): for every DFA state and every nonterminal, the strings that a terminal
-// entered in that state swallows whole, and those on which it dies after it has passed an accepting state.
+// entered in that state swallows whole, and those on which it dies after it has passed an accepting state and whose rest some context takes.
 //   Every row is independent of every other and every string of every other string, so a lane takes a string and walks it through the DFAs of 32 rows
 // one after the other; most walks end at the first byte.  A schema of 229 rows and a vocabulary of 128,256 tokens are 29 million walks, which the
 // host did down the trie and then turned into token order: 2.2 + 0.9 ms of a compile, and 1.5 + 0.7 for the strings as byte classes;
@@ -32,20 +32,30 @@ __global__ __launch_bounds__(VOCAB_BLOCK) void vocab_rows_kernel(VocabRows a, co
     string_at(off, a.n, i, from, len);
 #pragma unroll
     for (uint32_t k = 0; k < 8u; k++) if (k < len) at_hand[k >> 2] |= (uint32_t)cls[a.bytes[from + k]] << (8u * (k & 3u));
+    auto class_at = [&](uint32_t k) __attribute__((always_inline)) -> uint32_t { return k < 8u ? (at_hand[k >> 2] >> (8u * (k & 3u))) & 0xFFu : (uint32_t)cls[a.bytes[from + k]]; };
     for (uint32_t q = q0; q < q0 + VOCAB_ROWS && q < a.Q; q++) {
         bool valid = false, undecided = false;
         if (a.qflags[q] & QF_CONT) {                         // no item ever waits in a state without outgoing edges
             uint32_t s = q, k = 0;
             bool accepted = false;
             while (k < len) {
-                const uint32_t c = k < 8u ? (at_hand[k >> 2] >> (8u * (k & 3u))) & 0xFFu : (uint32_t)cls[a.bytes[from + k]];
-                s = a.delta[(size_t)s * a.n_cls + c];
+                s = a.delta[(size_t)s * a.n_cls + class_at(k)];
                 if (s == DFA_DEAD) break;
                 accepted |= (a.qflags[s] & QF_ACCEPT) != 0;
                 k++;
             }
             valid = len > 0 && k == len;
-            undecided = k < len && accepted;
+            if (k < len && accepted) {                       // it dies behind an accepting state: where it may end, is there a context that takes the rest?
+                s = q;
+                for (k = 0; !undecided && k + 1u < len; k++) {
+                    s = a.delta[(size_t)s * a.n_cls + class_at(k)];
+                    if (s == DFA_DEAD) break;
+                    if (!(a.qflags[s] & QF_ACCEPT)) continue;
+                    uint32_t f = a.behind[s];
+                    for (uint32_t j = k + 1u; f != FOLLOW_DEAD && j < len; j++) f = a.follow[(size_t)f * a.n_cls + class_at(j)];
+                    undecided = f != FOLLOW_DEAD;
+                }
+            }
         }
         const unsigned long long v = __ballot(valid), u = __ballot(undecided);
         const uint32_t w = i >> 5;

@@ -429,6 +429,29 @@ def test_random_grammars_host_walk_equals_oracle(seed, zf, oracle_lib):
             s.reset() if t < 0 else s.advance(t)
 
 
+@pytest.mark.parametrize("words,length", [(3, 4), (220, 20), (260, 20)])
+def test_what_follows_a_terminal_decides_no_token_that_a_context_takes(words, length, zf, oracle_lib):
+    """The automaton of what may follow a terminal, small, near its budget of 4,096 states and beyond it (where it takes everything): masks with the token-mask
+    cache equal the oracle's, over tokens that hold the end of a word, a separator whose choice depends on the context, and the beginning of the next word."""
+    rng = stream(words, "words")
+    names = [bytes(b"abcdefghij"[rng.next_u64() % 10] for _ in range(length - 3)) + b"%03d" % k for k in range(words)]
+    g = Grammar("words").alts("L", ["W", b",", "L"], [b"(", "M", b")"]).alts("M", ["W", b";", "M"], ["W"], []).alts("W", *[[n] for n in names]).set_start("L")
+    toks = [bytes([b]) for b in b"abcdefghij0123456789,;()"] + list(names[:8]) + [b"", b"((", b"()"]
+    for a, b in ((names[0], names[1]), (names[1], names[2]), (names[2], names[0])):
+        for sep in (b",", b";", b",(", b")", b"),", b";)", b")x"):
+            toks += [a + sep, a[-2:] + sep + b[:2], a[-1:] + sep + b, a[-1:] + sep]
+    orc, eng = oracle_lib.Oracle(g), zf.Engine(g, toks, device=-1)
+    off, data = wvocab.vocab_csr(toks)
+    for prefix in (b"", names[0][:-1], names[0], names[0] + b",", b"(", b"(" + names[1][:-2], b"(" + names[2][:-1], names[1] + b",(" + names[0] + b";" + names[2][:-1]):
+        so, st = orc.new_state(), eng.new_state()
+        assert so.feed_bytes(prefix)
+        st.advance_bytes(prefix)
+        want = so.mask(off, data, 8)
+        got, stats = st.debug_host_mask_cached()
+        assert np.array_equal(got, want), prefix
+        assert np.array_equal(st.debug_host_mask_automaton()[0], want), prefix
+
+
 def test_automaton_twin_long_tokens_deep_nesting_many_classes(zf, oracle_lib):
     """The mask automaton's host twin on the inputs that stress its ends: tokens longer than 16 bytes, nesting
     deeper than any state budget, more than 64 byte classes."""
