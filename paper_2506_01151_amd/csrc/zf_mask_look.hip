@@ -36,7 +36,16 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 static const int LOOK_LC_BITS = 10;                      // the block's LDS cache of table entries: 1,024 of (key, state)
 static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
+// A group's wavefronts store its mask words to every member's row, one member or a few at a time: a batch that stands in one state, 256 rows x 128,256,
+// kept 63 wavefronts at it for 18 us.  With logits, those of groups of more members than these (in the argument block) leave it to the wavefronts that mask the
+// logits, each for its unit: 16 members of bf16 logits (16 steps of 64 x 128,256 of the query language 178.4 -> 178.0 us, 8 of 130 x 40,037 109.1 -> 106.1, 8 of
+// 256 x 128,256 226.2 -> 224.8; 32 members: 180.3, 108.9, 223.7), 128 of fp32, whose units hold half as many words (16 steps of 64 x 152,064 of the expression grammar 312.8 us
+// without, 317.0 from 16 members on, 315.2 from 32).
+template <int DT> constexpr uint32_t look_members_max() { return DT == 2 ? 16u : 128u; }
 static const uint32_t LOOK_STOP = 256;                   // beyond every class and mark: the walk of a lane has ended
+// Where the groups' records are: one in the argument block, up to 64 there, or any number in device memory.  A build each, so that the records are asked
+// for along with the other arguments and not after them.
+enum { LOOK_ONE, LOOK_FEW, LOOK_MANY };
 static const uint32_t LOOK_LIST = 512;                   // undecided tokens a wavefront lists at a time
 static const int LOOK_RAW = 2;                           // token-mask cache rows that are asked for whether or not there are so many
 static const uint32_t LOOK_POLLS_MAX = 1u << 24;         // how often a wavefront that can leave a unit to nobody looks for mask words before the call fails: tens of seconds
@@ -87,16 +96,22 @@ template <int DT> struct LookLogit { typedef uint32_t elem; static const int PER
 template <> struct LookLogit<2> { typedef uint16_t elem; static const int PER_PIECE = 8; static const uint32_t NEG_INF = 0xFF80u; typedef u32x4 __attribute__((aligned(2))) piece; };
 // words_read(failed, left) is called when the mask words are in hand, before anything is stored, or when they were not there after `polls` looks: with
 // LEAVE the unit is then left to the group, else the call fails.
-template <int DT, bool LEAVE, class WordsRead>
+template <int DT, int HOW, bool LEAVE, class WordsRead>
 __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline &in, uint32_t unit, uint32_t lane, uint32_t polls, WordsRead words_read) {
     typedef LookLogit<DT> L;
     typedef typename L::elem elem;
     typedef typename L::piece piece_t;
     constexpr uint32_t EPV = L::PER_PIECE, KB_WORDS = 64 * EPV / 32, WORDS = (LOOK_UNIT_KB * KB_WORDS + 63) / 64;   // mask words of a KB; of a unit, per lane
     const uint32_t m = unit / a.row_units, part = unit - m * a.row_units, nu = a.unit_kb, W = a.W;
-    uint32_t group = 0;
-    if (a.groups) group = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a.group_of[m]);
-    else if (a.n_groups > 1u) group = (uint32_t)__popcll(__ballot(lane < a.n_groups && (in.g[lane < a.n_groups ? lane : 0u].w[3] & 0xFFFFu) <= m)) - 1u;
+    uint32_t group = 0, n_members = 0;
+    if (HOW == LOOK_MANY) group = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a.group_of[m]);
+    if (HOW == LOOK_ONE) n_members = in.g[0].w[3] >> 16;
+    if (HOW == LOOK_FEW) {
+        const uint32_t x = in.g[lane].w[3];
+        group = (uint32_t)__popcll(__ballot(((x & 0xFFFFu) <= m) & (lane < a.n_groups))) - 1u;
+        n_members = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)group) >> 16;
+    }
+    const bool stores_row = n_members > look_members_max<DT>();
     const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)member_row(a, in, m));
     const unsigned long long *const words = a.tagged + (size_t)group * W;
     const uint32_t w0 = part * nu * KB_WORDS;
@@ -146,6 +161,10 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
         }
     }
     words_read(0u, false);
+    if (stores_row) {                                        // the row's mask words as well
+#pragma unroll
+        for (uint32_t k = 0; k < WORDS; k++) if (k * 64u + lane < nu * KB_WORDS && w0 + k * 64u + lane < W) a.out_mask[(size_t)row * W + w0 + k * 64u + lane] = (uint32_t)t[k];
+    }
 #pragma unroll
     for (uint32_t u = 0; u < (uint32_t)LOOK_UNIT_KB; u++) {
         if (u >= nu) continue;
@@ -165,7 +184,7 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
 }
 
 // What blocks of a group have left, by the wavefront that has drawn the group's last ticket: `n` blocks' units.  Returns how many never got their words.
-template <int DT>
+template <int DT, int HOW>
 __device__ __forceinline__ uint32_t mask_left_units(const LookArgs &a, const LookInline &in, uint32_t group, uint32_t n, uint32_t lane) {
     uint32_t failed = 0, polls = LOOK_POLLS_MAX;
     unsigned long long *const left = left_units(a);
@@ -179,7 +198,7 @@ __device__ __forceinline__ uint32_t mask_left_units(const LookArgs &a, const Loo
             if (lane == 0) __hip_atomic_store(&left[k], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             n--;
             for (uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e); bits; bits &= bits - 1u)
-                mask_logits<DT, false>(a, in, k * STORE_WAVES + (uint32_t)__ffs((int)bits) - 1u, lane, LOOK_POLLS_MAX, [&](uint32_t f, bool) __attribute__((always_inline)) { failed += f; });
+                mask_logits<DT, HOW, false>(a, in, k * STORE_WAVES + (uint32_t)__ffs((int)bits) - 1u, lane, LOOK_POLLS_MAX, [&](uint32_t f, bool) __attribute__((always_inline)) { failed += f; });
         }
         if (n && polls-- <= 1u) return failed + n;           // never: the call fails
     }
@@ -188,7 +207,7 @@ __device__ __forceinline__ uint32_t mask_left_units(const LookArgs &a, const Loo
 
 // Grid and groups as in mask_store_kernel: the blocks of all groups one after the other, a group = the rows of the call that
 // stand in the same state, whose mask is worked out once, in token order.  A wavefront takes every n_units-th segment of `sw` mask words.
-template <int DT>   // of the logits masked along: 0 = none, 1 = fp32, 2 = bf16
+template <int DT, int HOW>   // of the logits masked along: 0 = none, 1 = fp32, 2 = bf16
 __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLOCKS_PER_CU) void mask_look_kernel(LookArgs a, LookInline in) {
     __shared__ unsigned long long lc[LOOK_LC];
     __shared__ uint32_t lists[STORE_WAVES][LOOK_LIST];
@@ -209,7 +228,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
                 static_assert(sizeof(LookArgs) % alignof(LookInline) == 0, "the second argument follows the first");
                 const LookArgs &a2 = *(const LookArgs *)at;
                 const LookInline &in2 = *(const LookInline *)((const uint8_t *)at + sizeof(LookArgs));
-                t.sum += (unsigned long long)mask_left_units<DT>(a2, in2, blockIdx.x % a2.done_groups, n, lane) << 16;
+                t.sum += (unsigned long long)mask_left_units<DT, HOW>(a2, in2, blockIdx.x % a2.done_groups, n, lane) << 16;
             }
         }
         if (lane == 0) tell_host(a, t);
@@ -230,29 +249,28 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
                 t = draw_ticket(a, sum >> 16, who != 0);
             }
         };
-        if (unit < a.units) mask_logits<DT, true>(a, in, unit, lane, a.polls, words_read);
+        if (unit < a.units) mask_logits<DT, HOW, true>(a, in, unit, lane, a.polls, words_read);
         else words_read(0u, false);
         if (drew) drawn(t);
         return;
     }
-    if (a.groups) {
+    if (HOW == LOOK_MANY) {
         const uint32_t b0 = a.block_of[2u * blockIdx.x], b1 = a.block_of[2u * blockIdx.x + 1u];
         group = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
         part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 & 0xFFFFu));
         parts = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b1 >> 16));
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[k]);
-    } else if (a.n_groups == 1u) {                           // one group: scalar loads, along with the other arguments
+    } else if (HOW == LOOK_ONE) {                           // one group: scalar loads, along with the other arguments
         part = blockIdx.x; parts = a.mask_blocks;
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = in.g[0].w[k];
     } else {
-        const uint32_t at = lane < a.n_groups ? lane : a.n_groups - 1u;
-        uint32_t x[LOOK_WORDS];
+        uint32_t x[LOOK_WORDS];                              // (the block holds 64 records, of which n_groups mean something: the loads need not wait for that number)
 #pragma unroll
-        for (int k = 0; k < LOOK_WORDS; k++) x[k] = in.g[at].w[k];
+        for (int k = 0; k < LOOK_WORDS; k++) x[k] = in.g[lane].w[k];
         const uint32_t first = x[2] & 0xFFFFu;
-        group = (uint32_t)__popcll(__ballot(lane < a.n_groups && blockIdx.x >= first)) - 1u;   // groups that start at or before this block
+        group = (uint32_t)__popcll(__ballot((blockIdx.x >= first) & (lane < a.n_groups))) - 1u;   // groups that start at or before this block
 #pragma unroll
         for (int k = 0; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readlane((int)x[k], (int)group);
         const uint32_t fb0 = r[2] & 0xFFFFu, fb1 = group + 1u < a.n_groups ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)(group + 1u)) : a.mask_blocks;
@@ -264,6 +282,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
     __syncthreads();
     const uint32_t start = r[0], n_ent = r[1] & 0xFFu, sw = ((r[1] >> 16) & 0xFFu) + 1u, n_seg = r[2] >> 16, member_at = r[3] & 0xFFFFu, n_members = r[3] >> 16;
     const uint32_t n_here = n_ent > (uint32_t)STORE_GROUP_ENT ? LOOK_ENT_OF_MORE : n_ent;   // cache rows in the record; the others are listed behind the members
+    const uint32_t n_store = DT && HOW != LOOK_MANY && n_members > look_members_max<DT>() ? 0u : n_members;   // members whose mask rows the wavefronts without logits store
     const bool pooled = (r[1] & ((uint32_t)STORE_ROW_POOLED << 8)) != 0, keep = (r[1] & ((uint32_t)STORE_ROW_KEEP << 8)) != 0, use_cache = (r[1] & ((uint32_t)STORE_ROW_CACHE << 8)) != 0;
     const uint32_t unit = part * STORE_WAVES + wave, n_units = parts * STORE_WAVES, W = a.W, V = a.V, ncls = a.ncls;
     if (unit < n_seg) {
@@ -449,9 +468,9 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
         if (total) v |= lane < sw ? lds_load(&vbuf[lane]) : 0u;   // LDS serves one wavefront's accesses in issue order
         if (DT && w < W) __hip_atomic_store(&a.tagged[(size_t)group * W + w], (unsigned long long)a.seq << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // ---- the segment's words go to every member's mask row (and to the state cache) ----
-        for (uint32_t m0 = 0; m0 < n_members; m0 += 64) {
-            if (n_members > 64u) members = members_from(m0);
-            const uint32_t n = n_members - m0 < 64u ? n_members - m0 : 64u;
+        for (uint32_t m0 = 0; m0 < n_store; m0 += 64) {
+            if (n_store > 64u) members = members_from(m0);
+            const uint32_t n = n_store - m0 < 64u ? n_store - m0 : 64u;
             if (n < 4u || sw > 32u) {
                 for (uint32_t k = 0; k < n; k++) {
                     uint32_t *dst = a.out_mask + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)members, (int)k) * W + w;
@@ -468,7 +487,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
             }
         }
         if (keep && w < W) put_word(&a.pool[(size_t)(r[4] & 0xFFFFu) * W + w], v, a.complete);
-        if (n_members > 64u) members = members_from(0);
+        if (n_store > 64u) members = members_from(0);
     }
     if (lane == 0 && failed) atomicAdd(&blk_failed, failed);
     }
@@ -487,7 +506,7 @@ __global__ __launch_bounds__(STORE_BLOCK, DT ? LOOK_BLOCKS_PER_CU + 2 : LOOK_BLO
 int look_blocks_per_cu() {
     static const int blocks = [] {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(mask_look_kernel<0>), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(mask_look_kernel<0, LOOK_FEW>), STORE_BLOCK, 0) != hipSuccess || n < 1) { (void)hipGetLastError(); n = 1; }
         return n < LOOK_BLOCKS_PER_CU ? n : LOOK_BLOCKS_PER_CU;
     }();
     return blocks;
@@ -495,9 +514,13 @@ int look_blocks_per_cu() {
 
 hipError_t launch_mask_look(const LookArgs &a, const LookInline &in, hipStream_t s) {
     const dim3 grid(look_grid(a)), block(STORE_BLOCK);
-    if (!a.units) hipLaunchKernelGGL(mask_look_kernel<0>, grid, block, 0, s, a, in);
-    else if (a.dtype == 1) hipLaunchKernelGGL(mask_look_kernel<1>, grid, block, 0, s, a, in);
-    else hipLaunchKernelGGL(mask_look_kernel<2>, grid, block, 0, s, a, in);
+    const int dt = a.units ? (int)a.dtype : 0, how = a.groups ? LOOK_MANY : a.n_groups == 1u ? LOOK_ONE : LOOK_FEW;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a, in); };
+#define LOOK_HOW(DT) (how == LOOK_MANY ? launch(mask_look_kernel<DT, LOOK_MANY>) : how == LOOK_ONE ? launch(mask_look_kernel<DT, LOOK_ONE>) : launch(mask_look_kernel<DT, LOOK_FEW>))
+    if (dt == 0) LOOK_HOW(0);
+    else if (dt == 1) LOOK_HOW(1);
+    else LOOK_HOW(2);
+#undef LOOK_HOW
     return hipGetLastError();
 }
 

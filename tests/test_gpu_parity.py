@@ -962,6 +962,30 @@ def test_states_met_before(V, B, places, dtype, shift, token_cache, torch_cuda, 
         assert t.view(i).cpu().numpy().view(u).tobytes() == oracle_apply(bits, wanted).tobytes(), call
 
 
+@pytest.mark.parametrize("V,B,places,dtype,shift", [(2033, 16, 1, "bf16", 0), (33, 17, 1, "bf16", 1), (6001, 35, 2, "bf16", 3), (2049, 128, 1, "f32", 1), (2047, 129, 1, "f32", 0),
+                                                    (4097, 256, 1, "bf16", 5), (4096, 257, 1, "bf16", 0)])
+def test_rows_of_large_groups(V, B, places, dtype, shift, torch_cuda, oracle_lib):
+    """Groups around the sizes from which on the wavefronts that mask the logits store the mask rows (17 bf16 rows, 129 fp32), with all rows of the argument block and one more."""
+    test_states_met_before(V, B, places, dtype, shift, True, torch_cuda, oracle_lib)
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 64, 65, 257, 1024, 1500])
+def test_rows_of_large_groups_without_logits(n, torch_cuda):
+    """Waiting calls whose rows all stand in one state: the more rows, the fewer words a wavefront takes; every row is the row of a call of its own."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    eng = zf.Engine(grammars.json_grammar(), configs.CONFIGS[2].vocab(6007), device=0, state_cache_entries=-1)
+    st = eng.new_state()
+    st.advance_bytes(b'{"a": [1')
+    want = torch.empty((1, eng.W), dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, [st], want)
+    got = torch.full((n + 1, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        zf.compute_mask(eng, [st] * n, got[:n])
+        assert torch.equal(got[:n], want.expand(n, -1)) and bool((got[n] == 0x5A5A5A5A).all())
+        got[:n].fill_(0x5A5A5A5A)
+
+
 @pytest.mark.parametrize("V,B", [(16384, 300), (16385, 300), (33001, 300), (4096, 1), (4097, 3)])
 def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
     """The per-block automaton where a row's share of a block is one word less, and more, than a pass takes (512 words; 300 rows have a block
