@@ -1453,8 +1453,10 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         // AUT_STEP_LANES holds sets of 64 items, which a byte or a long token can take a dozen items beyond: the strings behind such a set
         // then cost the fallback pass more than the build saves (7 %), and the short list of a call that allocates nothing
         // might not hold them.  So that call never takes the build, and an engine whose strings have outgrown it once takes the wide one.
-        int step = biggest_set <= (size_t)AUT_NARROW_SET_MAX ? AUT_STEP_NARROW
-                 : biggest_set <= (size_t)AUT_LANES_SET_MAX && !noalloc && !d->lanes_outgrown ? AUT_STEP_LANES : AUT_STEP_WIDE;
+        // Where every operand completes all operations before it, the sets of the strings outgrow a narrow step's, however small the charts' are.
+        const bool lanes = !noalloc && !d->lanes_outgrown;
+        int step = biggest_set <= (size_t)AUT_NARROW_SET_MAX ? (e->tab.operators && lanes ? AUT_STEP_LANES : AUT_STEP_NARROW)
+                 : biggest_set <= (size_t)AUT_LANES_SET_MAX && lanes ? AUT_STEP_LANES : AUT_STEP_WIDE;
         const uint32_t lds_max = 160u * 1024u;
         for (;;) {
             scratch = e->lane_cap_auto ? (int)std::min<size_t>(LANE_CAP_MAX, (4 * widest + 128 + 31) / 32 * 32) : e->opt.lane_item_cap;

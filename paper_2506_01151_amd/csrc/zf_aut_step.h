@@ -24,7 +24,7 @@ __device__ __forceinline__ void lds_store(uint32_t *p, uint32_t v) { __hip_atomi
 // control flow (all lanes call these functions with identical arguments).  All variants leave the
 // new set, completed items dropped, in the wavefront's scratch (sc_w, sc_o) and return AUT_OK,
 // AUT_WIDE (not the wide variant: more than 64 new items, or too many candidates) or AUT_OVER (no room).
-enum { AUT_OK = 0, AUT_WIDE = 1, AUT_OVER = 2 };
+enum { AUT_OK = 0, AUT_WIDE = 1, AUT_OVER = 2, AUT_SEEN = 3 };   // AUT_SEEN: see aut_step_lanes
 static const int AUT_NARROW_TRIES = 96;   // insert attempts after which the narrow variant hands the step to the wide one
 
 // Narrow variant: the set under construction lives in registers (lane j holds new item j), so the
@@ -164,9 +164,12 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
 // dealing costs more than it saves (per-block automaton, 16 rows of a JSON schema: 61 us per step with the narrow variant, 65 with this; trie walk 103
 // and 125).
 static const int AUT_LANES_TRIES = 96;    // distinct candidates per round, summed up, after which this variant hands the step to the wide one (HAND_OVER)
-template <bool HAND_OVER, class SetsT>
+// What Complete makes of a set is a function of what Scan has left in it, so a set whose first items are those of a known set's is that set: seen(w, o, n), asked
+// between the two with lane i < n holding item i, says whether they are (AUT_SEEN).  The first items of the new set, `scanned` of them, stand
+// in the scratch behind the kept ones where there is room.
+template <bool HAND_OVER, class SetsT, class Seen>
 __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint32_t *sc_w, uint32_t *sc_o, uint32_t sc_cap,
-                                              uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out) {
+                                              uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out, uint32_t &scanned, Seen seen) {
     uint64_t src;
     uint32_t ns;
     S.view(cur, src, ns);
@@ -225,6 +228,8 @@ __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint3
             chain(listed && (ef.y & QF_ACCEPT), aw, p, cur);
         }
     }
+    scanned = nnew;
+    if (nnew && seen(nw, no, nnew)) return AUT_SEEN;
     // Complete, until no new item is complete: the items of all completed items' origin sets -- the ones that may wait for the
     // completed nonterminal -- are dealt to the lanes, and the entries of the table that they hit are dealt again.
     unsigned long long visited = 0;
@@ -290,6 +295,8 @@ __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint3
     if (keep) { const uint32_t at = (uint32_t)__popcll(kb & ((1ull << lane) - 1ull)); sc_w[at] = nw; sc_o[at] = no; }
     nnew_out = nnew;
     kept_out = (uint32_t)__popcll(kb);
+    if (kept_out + scanned > sc_cap) scanned = 0;
+    if (lane < scanned) { sc_w[kept_out + lane] = nw; sc_o[kept_out + lane] = no; }
     return AUT_OK;
 }
 

@@ -94,6 +94,7 @@ bool build_tables(const zf_grammar_desc *g, Tables &t) {
     }
     rules.push_back(Rule{SP, -1, {nt_new[g->start]}});
     t.n_rules_kept = (int)rules.size() - 1;
+    t.operators = std::any_of(rules.begin(), rules.end(), [](const Rule &r) { return r.rhs.size() > 1 && r.rhs.front() == r.lhs && r.rhs.back() == r.lhs; });
     // ---- nullable ----
     std::vector<uint8_t> nullable(N, 0);
     for (bool ch = true; ch;) {

@@ -71,6 +71,7 @@ struct Tables {
     // for zf_position_info: original rule index / lhs / dot of each position (-1 for added ones)
     std::vector<int32_t> pos_rule, pos_dot, pos_lhs_orig;
     int n_rules_kept = 0;
+    bool operators = false;           // some rule begins and ends with its own nonterminal (E -> E + E): sets grow with every operand
 };
 bool build_tables(const zf_grammar_desc *g, Tables &t);
 

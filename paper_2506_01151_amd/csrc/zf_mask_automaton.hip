@@ -25,6 +25,7 @@ struct Aut {               // one block's automaton; every pointer leads into LD
     uint32_t *trans;       // [states_cap][ncls] next state or AT_*
     uint2 *hdr;            // [states_cap] (first item in arena, item count); count 0xFFFFFFFF = not written yet
     uint32_t *hash;        // [states_cap] signature of the content (filter for the interning compare)
+    uint32_t *scanned;     // [states_cap] items that Scan left in the state's set before Complete: they stand behind its items (0: not known)
     uint2 *arena;          // [arena_cap] items of all states
     uint32_t *ctl;         // [0] states handed out, [1] arena items handed out, [2] next batch of strings, [3] number of batches,
                            // [4] help-queue places handed out, [5] help-queue places taken, [6] batches finished,
@@ -72,9 +73,20 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
     uint32_t src_n;
     S.view(cur, src_p, src_n);
     int st = AUT_WIDE;
+    // A terminal that goes on in place -- a digit behind a digit -- leaves what it left before: the source set's own first items (64 rows of the expression
+    // grammar, 4.2 to 6.1 us such a step, 0.9 so).
+    uint32_t scanned = 0;
+    const uint32_t src_scanned = STEP == AUT_STEP_NARROW ? 0u : lds_load(&A.scanned[s]);
+    auto seen = [&](uint32_t w, uint32_t o, uint32_t n) -> bool {
+        if (n != src_scanned) return false;
+        uint2 x = make_uint2(w, o);
+        if (lane < n) x = S.item(src_p, src_n + lane);
+        return __ballot(x.x != w || x.y != o) == 0;
+    };
     if (STEP == AUT_STEP_NARROW) st = aut_step_narrow<false>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);
-    else if (STEP == AUT_STEP_LANES || src_n <= (uint32_t)AUT_STEP_WIDE_FROM) st = aut_step_lanes<STEP == AUT_STEP_WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept);   // a wide source set rarely leaves a narrow one
+    else if (STEP == AUT_STEP_LANES || src_n <= (uint32_t)AUT_STEP_WIDE_FROM) st = aut_step_lanes<STEP == AUT_STEP_WIDE>(T, S, sc_w, sc_o, sc_cap, cur, byte, cl, lane, nnew, kept, scanned, seen);   // a wide source set rarely leaves a narrow one
     if (st == AUT_WIDE) st = STEP == AUT_STEP_WIDE ? aut_step_wide(T, S, sc_w, sc_o, sc_h, sc_cap, cur, byte, cl, lane, nnew, kept) : (int)AUT_OVER;
+    if (STEP != AUT_STEP_NARROW && st == AUT_SEEN) return s;
     if (st != AUT_OK) return AT_FAIL;
     if (nnew == 0) return AT_DEAD;
     if (kept == 0) return AT_SINK;
@@ -102,15 +114,16 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
         }
     }
     uint32_t id = 0, at = 0;
-    if (lane == 0) { id = atomicAdd(&A.ctl[0], 1u); at = atomicAdd(&A.ctl[1], kept); }
+    if (lds_load(&A.ctl[1]) + kept + scanned > A.arena_cap) scanned = 0;
+    if (lane == 0) { id = atomicAdd(&A.ctl[0], 1u); at = atomicAdd(&A.ctl[1], kept + scanned); }
     id = (uint32_t)__builtin_amdgcn_readfirstlane((int)id);
     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    if (id >= A.states_cap || at + kept > A.arena_cap) return AT_FAIL;
-    for (uint32_t i0 = 0; i0 < kept; i0 += 64)
-        if (i0 + lane < kept) A.arena[at + i0 + lane] = make_uint2(sc_w[i0 + lane], sc_o[i0 + lane]);
+    if (id >= A.states_cap || at + kept + scanned > A.arena_cap) return AT_FAIL;
+    for (uint32_t i0 = 0; i0 < kept + scanned; i0 += 64)
+        if (i0 + lane < kept + scanned) A.arena[at + i0 + lane] = make_uint2(sc_w[i0 + lane], sc_o[i0 + lane]);
     aut_mark_dead<STEP != AUT_STEP_NARROW>(T, A.ncls, A.rep, [&](uint32_t i) { return sc_w[i]; }, kept, lane, [&](uint32_t c) { A.trans[id * A.ncls + c] = AT_DEAD; });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // items before the hash, the hash before the header that makes the state visible
-    if (lane == 0) A.hash[id] = h;
+    if (lane == 0) { A.hash[id] = h; A.scanned[id] = scanned; }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) A.hdr[id] = make_uint2(at, kept);
     return id;
@@ -150,6 +163,18 @@ __device__ __forceinline__ int aut_help_take(const Aut &A, uint32_t lane, uint32
     s = (e & ~HQ_VALID) >> 8;
     cl = e & 0xFFu;
     return AUT_HQ_GOT;
+}
+
+// Leaves the transitions (s, c) of the lanes `who`, which the caller owns, in the queue.
+__device__ __forceinline__ void aut_help_leave(const Aut &A, uint32_t lane, unsigned long long who, uint32_t s, uint32_t c) {
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&A.ctl[4], (uint32_t)__popcll(who));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if ((who >> lane) & 1ull) {
+        const uint32_t k = at + (uint32_t)__popcll(who & ((1ull << lane) - 1ull));
+        if (k < (uint32_t)AUT_HELP_QUEUE) lds_store(&A.hq[k], HQ_VALID | (s << 8) | c);
+        else lds_store(&A.trans[s * A.ncls + c], (uint32_t)AT_NONE);   // no room in the queue: the claim is given back
+    }
 }
 
 __host__ __device__ inline uint32_t aut_round16(uint32_t x) { return (x + 15u) & ~15u; }
@@ -192,6 +217,7 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
     A.trans = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16(A.states_cap * A.ncls * 4);
     A.hdr = reinterpret_cast<uint2 *>(smem + off); off += aut_round16(A.states_cap * 8);
     A.hash = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16(A.states_cap * 4);
+    A.scanned = reinterpret_cast<uint32_t *>(smem + off); off += aut_round16(A.states_cap * 4);
     A.ctl = reinterpret_cast<uint32_t *>(smem + off); off += 48;
     A.hq = reinterpret_cast<uint32_t *>(smem + off); off += AUT_HELP_QUEUE * 4;
     const uint32_t base_sets_cap = (uint32_t)a.aut_base_sets, base_items_cap = (uint32_t)a.aut_base_items;
@@ -246,7 +272,7 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
     for (uint32_t k = tid; k < A.states_cap * A.ncls; k += BLOCK) A.trans[k] = AT_NONE;
     for (uint32_t k = tid; k < A.states_cap; k += BLOCK) A.hdr[k] = make_uint2(0, 0xFFFFFFFFu);
     for (uint32_t k = tid; k < (uint32_t)AUT_HELP_QUEUE; k += BLOCK) A.hq[k] = 0;
-    if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; A.ctl[7] = 0; A.ctl[8] = 0; }
+    if (tid == 0) { A.ctl[0] = 1; A.ctl[1] = 0; A.ctl[4] = 0; A.ctl[5] = 0; A.ctl[7] = 0; A.ctl[8] = 0; A.scanned[0] = 0; }
     const uint32_t *b_ent = (STEP != AUT_STEP_WIDE || ent_fits) ? l_ent : g_ent;   // without the wide step: sets of at most AUT_LANES_SET_MAX items, so at most that many cache rows
     const uint32_t *b_so = (STEP != AUT_STEP_WIDE || base_fits) ? l_so : g_so;   // the build without the wide step is launched only when every chart fits:
     const uint2 *b_it = (STEP != AUT_STEP_WIDE || base_fits) ? l_it : g_it;      // its chart pointers are LDS addresses at compile time
@@ -362,20 +388,22 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
                     uint32_t old = AT_BUSY;                  // lanes that found the transition being computed need not ask again
                     if (live && t == AT_NONE) old = atomicCAS(&A.trans[s * A.ncls + c], (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
                     const unsigned long long won = __ballot(live && old == AT_NONE);
+                    // What the strings that wait here need if the class leaves them in the state that they are in (a terminal that goes on: digits, letters) is left
+                    // in the queue as well, for wavefronts that have nothing to do, while half of the room for states is left (64 rows x 152,064 of the expression grammar, 8 steps,
+                    // 589 -> 579 us; with what the string's own first items say, below, 568).  (The row's current set ahead of the first strings: no gain.)
+                    {
+                        const uint32_t w0 = c16.w[0], c1 = (w0 >> 8) & 0xFFu, c2 = (w0 >> 16) & 0xFFu, c3 = w0 >> 24;
+                        const uint32_t cx = c1 != c ? c1 : c2 != c ? c2 : c3, need = c1 != c ? 2u : c2 != c ? 3u : 4u;
+                        uint32_t got = AT_BUSY;
+                        if (live && hand >= need && cx != c && lds_load(&A.trans[s * A.ncls + cx]) == AT_NONE && lds_load(&A.ctl[0]) < A.states_cap / 2u && lds_load(&A.ctl[1]) < A.arena_cap / 2u && lds_load(&A.ctl[4]) < (uint32_t)AUT_HELP_QUEUE / 2u) got = atomicCAS(&A.trans[s * A.ncls + cx], (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
+                        const unsigned long long who = __ballot(got == AT_NONE);
+                        if (who) aut_help_leave(A, lane, who, s, cx);
+                    }
                     progress = won != 0 || __ballot(live && old != AT_NONE && old != AT_BUSY) != 0;   // claimed, or published meanwhile
                     if (won) {
                         const int first = __ffsll((long long)won) - 1;
                         const unsigned long long rest = won & ~(1ull << first);
-                        if (rest) {
-                            uint32_t at = 0;
-                            if (lane == 0) at = atomicAdd(&A.ctl[4], (uint32_t)__popcll(rest));
-                            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                            if ((rest >> lane) & 1ull) {
-                                const uint32_t k = at + (uint32_t)__popcll(rest & ((1ull << lane) - 1ull));
-                                if (k < (uint32_t)AUT_HELP_QUEUE) lds_store(&A.hq[k], HQ_VALID | (s << 8) | c);
-                                else lds_store(&A.trans[s * A.ncls + c], (uint32_t)AT_NONE);   // no room in the queue: the claim is given back
-                            }
-                        }
+                        if (rest) aut_help_leave(A, lane, rest, s, c);
                         have = true;
                         rs = (uint32_t)__builtin_amdgcn_readlane((int)s, first);
                         rc = (uint32_t)__builtin_amdgcn_readlane((int)c, first);
@@ -448,7 +476,7 @@ hipError_t prepare_automaton_kernels() {
 
 uint32_t automaton_lds_bytes(const DeviceTables &t, int mode, int states, int arena, int scratch, int base_sets, int base_items, bool wide, int waves) {
     const uint32_t sub_words = (uint32_t)waves * 64u;
-    return table_bytes(t, mode) + aut_round16((uint32_t)states * (uint32_t)t.n_cls * 4) + aut_round16((uint32_t)states * 8) + aut_round16((uint32_t)states * 4) + 48 + AUT_HELP_QUEUE * 4 +
+    return table_bytes(t, mode) + aut_round16((uint32_t)states * (uint32_t)t.n_cls * 4) + aut_round16((uint32_t)states * 8) + 2 * aut_round16((uint32_t)states * 4) + 48 + AUT_HELP_QUEUE * 4 +
            aut_round16(((uint32_t)base_sets + 1) * 4) + aut_round16((uint32_t)base_items * 8) + AUT_ENT_LDS * 4 + 256 + 2 * sub_words * 4 + sub_words + aut_round16((uint32_t)arena * 8) +
            (uint32_t)waves * ((uint32_t)scratch * 8 + (wide ? aut_hash_places((uint32_t)scratch) * 4 : 0u));
 }

@@ -1020,6 +1020,37 @@ def test_per_block_automaton_blocks_of_sixteen(V, B, torch_cuda, oracle_lib):
     test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib)
 
 
+@pytest.mark.parametrize("grammar,pruning,B", [("expr", False, 3), ("expr", False, 300), ("expr", True, 3), ("json", False, 3), ("json", True, 300)])
+def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cuda, oracle_lib):
+    """Runs of digits, letters and blanks, what ends them and what follows, from within a run and from its beginning, with charts of small and of large sets: the steps
+    whose set is known from what Scan leaves, and those that are worked out before a string asks for them, against the oracle."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    if grammar == "expr":
+        g, runs, joins, prefixes = configs.CONFIGS[5].grammar(), [b"1", b"12", b"777", b"a", b"ab"], [b"+", b"*", b")+", b"+(", b"*(", b")"], [b"", b"1", b"12", b"a+b*c+1", b"((x", b"1+2*3+4*5+6*7+8"]
+    else:
+        g, runs, joins, prefixes = grammars.json_grammar(), [b"1", b"12", b"7.25", b"  ", b"true"], [b",", b" ,", b"]", b"],", b":", b", "], [b"", b"[1", b"[12, 3", b'{"a": 1', b"[[ ", b'{"k" ']
+    toks = runs + joins + [r + j + s for r in runs for j in joins for s in runs] + [r + j + r + j + r for r in runs for j in joins] + [r * 20 for r in runs] + [b""]
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, state_cache_entries=-1)
+    want, rows = [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p), p
+        want.append(so.mask(off, data, 8))
+    for b in range(B):
+        rows.append(eng.new_state())
+        rows[-1].advance_bytes(prefixes[b % len(prefixes)])
+    d_mask = torch.empty((B, eng.W), dtype=torch.int32, device="cuda")
+    for at in ([0], [1], [2], list(range(3)), list(range(B))) if B <= 6 else (list(range(B)),):
+        d_mask.fill_(0x5A5A5A5A)
+        zf.compute_mask(eng, [rows[b] for b in at], d_mask[:len(at)])
+        got = d_mask.cpu().numpy().view(np.uint32)
+        for k, b in enumerate(at):
+            assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
+
+
 def test_host_diagnostics_of_an_engine_with_a_device(torch_cuda, oracle_lib):
     """The host's diagnostics read token-mask cache rows that an engine with a device does not hold on the host until somebody asks: each of them,
     the first to ask of an engine of its own."""
