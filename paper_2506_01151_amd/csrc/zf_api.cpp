@@ -2138,22 +2138,38 @@ static bool explore_host(zf_engine *e, size_t cap_states, size_t cap_items, std:
     const double budget_s = 1.0;
     const size_t most_states = std::min((size_t)e->opt.precompute_states, cap_states / 4), most_items = cap_items / 4;
     HostAutomaton::Work w;
+    HostAutomaton::Completed known;
+    std::vector<Item> scanned;
     for (uint32_t s = HostAutomaton::ROOT; s < A.n_states; s++) {
         if ((s & 63u) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() >= budget_s) return false;
-        for (int c = 0; c < e->tab.n_cls; c++) {
+        const HostAutomaton::Classes live = A.live_classes(A.st(s).items, A.st(s).n_items);
+        for (int k = 0; k < 4; k++) for (uint64_t left = live.w[k]; left; left &= left - 1) {
+            const int c = 64 * k + __builtin_ctzll(left);
             if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
             if (A.n_states > most_states || (size_t)A.n_items >= most_items) return false;
-            if (!lk) { A.compute(s, c, w); continue; }
-            {
+            const HostAutomaton::Completed::Entry *to = nullptr;
+            uint32_t sig = 0;
+            bool completes = false;
+            auto step = [&]() {
+                A.scan(s, c, s, w);
+                completes = A.completes(w);
+                if (completes && (to = known.find(w.set, sig))) return;
+                if (completes) scanned = w.set;
+                A.close(w);
+            };
+            if (lk) {
                 struct Walker {                           // keeps the automaton from being emptied meanwhile
                     int &n;
                     std::unique_lock<std::mutex> &lk;
                     Walker(int &n_, std::unique_lock<std::mutex> &lk_) : n(n_), lk(lk_) { n++; lk.unlock(); }
                     ~Walker() { lk.lock(); n--; }
                 } walker(e->host_walkers, *lk);
-                A.look_ahead(s, c, w);
-            }
-            if (A.st(s).trans[c] == HostAutomaton::NONE) A.record(s, c, w);   // else somebody else has made it meanwhile
+                step();
+            } else step();
+            if (A.st(s).trans[c] != HostAutomaton::NONE) continue;   // somebody else has made it meanwhile
+            if (to) { A.record(s, c, to->to, to->accepted); continue; }
+            A.record(s, c, w);
+            if (completes) known.add(scanned, sig, A.st(s).trans[c], w.accepted);
         }
     }
     return true;

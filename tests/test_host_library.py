@@ -452,6 +452,27 @@ def test_what_follows_a_terminal_decides_no_token_that_a_context_takes(words, le
         assert np.array_equal(st.debug_host_mask_automaton()[0], want), prefix
 
 
+@pytest.mark.parametrize("size,first", [(1, None), (40, None), (40, b"1"), (8191, None), (8200, None), (9000, b"("), (9000, b"")])
+def test_trie_made_in_pieces(size, first, zf, oracle_lib):
+    """The vocabulary's trie is made a first byte at a time, by one thread or by several (8,192 strings and more): vocabularies of any first byte, of one (all in
+    one piece) and of none, with duplicates, empty tokens and the longest strings; the walk down the trie gives the oracle's masks."""
+    rng = stream(size, "pieces")
+    toks = [b"" if first == b"" else (first or b"") + bytes(b"a1+*()"[rng.next_u64() % 6] for _ in range(rng.next_u64() % 6)) for _ in range(size)]
+    if size > 8 and first != b"":
+        toks[3:8] = [b"1" * 255, b"1" * 254, b"(" * 255, b"1" * 255, bytes([255])]
+    g = grammars.expr_grammar()
+    orc, off, data = oracle_lib.Oracle(g), *wvocab.vocab_csr(toks)
+    for chunk_strings in (8, 32):
+        eng = zf.Engine(g, toks, device=-1, chunk_strings=chunk_strings)
+        for prefix in (b"", b"(1+", b"a"):
+            so, st = orc.new_state(), eng.new_state()
+            assert so.feed_bytes(prefix)
+            st.advance_bytes(prefix)
+            want = so.mask(off, data, 8)
+            assert np.array_equal(st.debug_host_mask(), want)
+            assert np.array_equal(st.debug_host_mask_cached()[0], want)
+
+
 def test_automaton_twin_long_tokens_deep_nesting_many_classes(zf, oracle_lib):
     """The mask automaton's host twin on the inputs that stress its ends: tokens longer than 16 bytes, nesting
     deeper than any state budget, more than 64 byte classes."""
