@@ -327,7 +327,8 @@ int begin_device(zf_engine *e) {
             first_off.push_back((uint32_t)first_state.size());
         }
         if ((rc = upload(d, t.delta, &r.delta)) != ZF_OK || (rc = upload(d, t.qflags, &r.qflags)) != ZF_OK || (rc = upload(d, first_off, &r.first_off)) != ZF_OK ||
-            (rc = upload(d, first_state, &r.first_state)) != ZF_OK || (rc = upload(d, e->follow.behind, &r.behind)) != ZF_OK || (rc = upload(d, e->follow.next, &r.follow)) != ZF_OK) return rc;
+            (rc = upload(d, first_state, &r.first_state)) != ZF_OK || (rc = upload(d, e->follow.behind, &r.behind)) != ZF_OK || (rc = upload(d, e->follow.next, &r.follow)) != ZF_OK ||
+            (rc = upload(d, e->follow.sure_behind, &r.sure_behind)) != ZF_OK || (rc = upload(d, e->follow.sure_next, &r.sure_next)) != ZF_OK) return rc;
         r.cls = T.cls; r.Q = (uint32_t)t.Q; r.N = (uint32_t)t.N; r.n_cls = (uint32_t)t.n_cls;
     }
     if (e->store_on) {
@@ -352,7 +353,7 @@ int begin_device(zf_engine *e) {
 size_t engine_bytes(const zf_engine *e) {
     const Tables &t = e->tab;
     const size_t V = (size_t)e->V, W = (size_t)e->W + 1, n_rows = (size_t)(t.Q + t.N), text = e->voc_bytes.size(), cap = store_cap_states(t.n_cls), ncls = (size_t)std::max(t.n_cls, 1);
-    size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * (t.delta.size() + e->follow.behind.size() + e->follow.next.size());
+    size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * (t.delta.size() + e->follow.behind.size() + e->follow.next.size() + e->follow.sure_behind.size() + e->follow.sure_next.size());
     n += text * (sizeof(TrieNode) + 4 + 2) + (V / (size_t)e->opt.chunk_strings + 1) * (8 + CHUNK_ANC * sizeof(TrieNode)) + V * (4 + 4 + sizeof(Str16)) + n_rows * W * 8;
     if (e->store_on) n += V * (8 + sizeof(Str16)) + text + n_rows * (W * 8 + 4) + cap * (sizeof(uint2) + ncls * 4 + 16) + STORE_CAP_ITEMS * sizeof(uint2) + (size_t)MAX_BATCH * 4;
     if (e->opt.state_cache_entries > 0) n += (size_t)e->opt.state_cache_entries * W * 4;
@@ -749,7 +750,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
-        if (e->lane_cap_auto) build_follow(e->tab, e->follow);
+        if (e->lane_cap_auto) { build_follow(e->tab, e->follow); build_sure(e->tab, e->follow); }
         else follow_everything(e->tab, e->follow);        // an explicit item budget is there to see sets outgrow it: every string that a terminal leaves open is walked
         if (e->opt.device >= 0) {
             const int rc = begin_device(e);

@@ -203,7 +203,7 @@ extern "C" int zf_debug_twin_mask(zf_twin *tw, uint32_t state, uint32_t *mask, i
             if ((code >> SYM_KIND_SHIFT) == SYM_TERM) row = it.q;
             else if ((code >> SYM_KIND_SHIFT) == SYM_NT) row = (size_t)t.Q + (code & SYM_ID_MASK_NT);
             else continue;
-            for (int w = 0; w < tr.Wr; w++) { valid[w] |= tr.ci_valid[row * tr.Wr + w]; want[w] |= tr.ci_ends[row * tr.Wr + w]; }
+            for (int w = 0; w < tr.Wr; w++) { valid[w] |= tr.ci_alone[row * tr.Wr + w]; want[w] |= tr.ci_ends[row * tr.Wr + w]; }
         }
         for (int w = 0; w < tr.Wr; w++) want[w] &= ~valid[w];
         for (uint32_t r = 0; r < (uint32_t)tr.n_strings; r++) {

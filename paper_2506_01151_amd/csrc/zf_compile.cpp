@@ -391,56 +391,102 @@ void build_trie(const zf_vocab_desc *v, int CHUNK_RANKS, const uint8_t *cls, Tri
 
 namespace zf {
 
-// What may follow a terminal, whatever its context: Earley sets whose items all say that their rule started in one set, which waits for everything
-// that the grammar waits for anywhere.  A real set, its origins forgotten, is always contained in the set that the same bytes lead to
-// here (by induction over Scan, Complete and Predict), so a string that dies here dies in every context.  Such sets are few: 39 states for RFC 8259 JSON, 323 for
-// a schema of 210 DFA states, 1,419 for a query language of 2,131, worked out in 0.1 to 1 ms.  Beyond the budget the automaton takes everything.
-void build_follow(const Tables &t, Follow &f) {
-    static const size_t MOST_STATES = 4096, MOST_WORK = (size_t)1 << 22;
-    HostAutomaton A(t);
-    const uint32_t all = A.n_states;
-    std::vector<Item> waiting;
-    std::vector<std::vector<uint16_t>> at(t.T);                // the positions before each terminal
-    for (int p = 0; p < t.P; p++) {
-        const uint16_t code = t.sym[p];
-        if ((code >> SYM_KIND_SHIFT) == SYM_NT) waiting.push_back(Item{(uint16_t)p, 0, all});
-        else if ((code >> SYM_KIND_SHIFT) == SYM_TERM) at[code & SYM_ID_MASK].push_back((uint16_t)p);
-    }
-    A.add(waiting.data(), (uint32_t)waiting.size(), 0, 0);
-    const uint32_t first = A.n_states;
+// Earley sets behind a terminal whose context is not known: a rule that a string begins itself starts in a set that is known, and completing it leads where it
+// leads there; what started before starts in one of a few sets that stand for the unknown ones (`unknown`: begun by an item that waits for nonterminal Y, in the set
+// unknown[Y]; complete: what completing X in such a set leads to).  Sets that are known to a depth of DEEPEST, or beyond EXACT_STATES of them, count as unknown,
+// so that grammars with recursion have finitely many.  What that leaves undecided in the rows of a cache, of 67,435 strings: JSON 24,767, a schema 16,017, the expression grammar 3,817 with what may follow alone and
+// nothing known exactly; with what surely follows 24,106, 15,117 and none; with sets known to a depth of 1 17,208 and 6,287, of 2 16,247 and 5,638, of 3 15,929 and
+// 5,606 (and twice the states).  0.3 to 0.9 ms a grammar, beside the exploration.
+struct BehindTerminal {
+    static constexpr uint8_t DEEPEST = 2;
+    static constexpr uint32_t EXACT_STATES = 256;
+    const Tables &t;
+    HostAutomaton A;
     HostAutomaton::Work w;
-    std::vector<std::vector<Item>> done(t.N);                  // what completing a nonterminal leads to, worked out once
-    auto close = [&]() {
+    std::vector<uint32_t> unknown;
+    uint32_t first = 0;                                        // ids below it are unknown sets
+    std::vector<uint8_t> depth;                                // [id - first]
+    explicit BehindTerminal(const Tables &t_) : t(t_), A(t_), unknown(t_.N, 0) {}
+    uint32_t depth_of(uint32_t id) {                           // how many known sets stand between the set and the unknown ones, itself included
+        for (uint32_t s = first + (uint32_t)depth.size(); s < A.n_states; s++) {   // (a set refers to earlier ones only)
+            uint8_t d = 0;
+            for (uint32_t i = 0; i < A.st(s).n_items; i++) { const uint32_t o = A.st(s).items[i].o; if (o >= first) d = std::max(d, depth[o - first]); }
+            depth.push_back((uint8_t)(d + 1));
+        }
+        return depth[id - first];
+    }
+    template <class Complete> void close(Complete complete) {
         for (size_t i = 0; i < w.set.size(); i++) {
-            const uint16_t code = t.sym[w.set[i].p];
-            if ((code >> SYM_KIND_SHIFT) != SYM_END) continue;
-            std::vector<Item> &to = done[code & SYM_ID_MASK];
-            if (to.empty()) {
-                HostAutomaton::Work x;
-                x.insert(w.set[i]);
-                A.close(x);
-                to = x.set;
-                to.push_back(w.set[i]);                        // (never empty again)
-            }
-            for (const Item &it : to) w.insert(it);
+            const Item it = w.set[i];
+            const uint16_t code = t.sym[it.p];
+            if ((code >> SYM_KIND_SHIFT) != SYM_END || (code & SYM_ID_MASK) == t.N - 1) continue;
+            if (it.o < first) complete(it, (uint32_t)(code & SYM_ID_MASK));
+            else A.completed(w, it, (uint32_t)(code & SYM_ID_MASK));
         }
         A.drop_completed(w);
+    }
+    uint32_t set() { return !w.alive ? HostAutomaton::DEAD : w.set.empty() ? HostAutomaton::SINK : A.intern(w.set.data(), (uint32_t)w.set.size()); }
+    template <class Complete> uint32_t behind(uint16_t p, Complete complete) {   // the terminal at position p
+        w.set.clear();
+        A.advanced(w, p + 1u, unknown[t.lhs_of[p]]);
+        close(complete);
+        return set();
+    }
+    template <class Complete> uint32_t step(uint32_t s, int c, Complete complete) {
+        if (A.st(s).trans[c] == HostAutomaton::NONE) {
+            const bool known = A.n_states < first + EXACT_STATES && depth_of(s) <= DEEPEST;
+            A.scan(s, c, [&](uint32_t Y) { return known ? s : unknown[Y]; }, w);
+            close(complete);
+            A.record(s, c, set(), false);
+        }
+        return A.st(s).trans[c];
+    }
+};
+static std::vector<std::vector<uint16_t>> positions_of_terminals(const Tables &t) {
+    std::vector<std::vector<uint16_t>> at(t.T);
+    for (int p = 0; p < t.P; p++) if ((t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM) at[t.sym[p] & SYM_ID_MASK].push_back((uint16_t)p);
+    return at;
+}
+
+// What may follow a terminal, whatever its context: the unknown set waits for everything that the grammar waits for anywhere.  A real set
+// is always contained in the set that the same bytes lead to here (by induction over Scan, Complete and Predict), so a string that dies here dies in
+// every context.  Beyond the budget the automaton takes everything.
+void build_follow(const Tables &t, Follow &f) {
+    static const size_t MOST_STATES = 4096, MOST_WORK = (size_t)1 << 22;
+    BehindTerminal B(t);
+    HostAutomaton &A = B.A;
+    const uint32_t all = A.n_states;
+    std::vector<Item> waiting;
+    const std::vector<std::vector<uint16_t>> at = positions_of_terminals(t);
+    for (int p = 0; p < t.P; p++) if ((t.sym[p] >> SYM_KIND_SHIFT) == SYM_NT) waiting.push_back(Item{(uint16_t)p, 0, all});
+    A.add(waiting.data(), (uint32_t)waiting.size(), 0, 0);
+    B.unknown.assign(t.N, all);
+    const uint32_t first = B.first = A.n_states;
+    std::vector<std::vector<Item>> done(t.N);                  // what completing a nonterminal leads to, worked out once
+    auto complete = [&](const Item &it, uint32_t X) {
+        std::vector<Item> &to = done[X];
+        if (to.empty()) {
+            HostAutomaton::Work x;
+            x.insert(it);
+            A.close(x);
+            to = x.set;
+            to.push_back(it);                                  // (never empty again)
+        }
+        for (const Item &i : to) B.w.insert(i);
     };
     std::vector<uint32_t> behind(t.T);
     for (int k = 0; k < t.T; k++) {
-        w.set.clear();
-        for (uint16_t p : at[k]) A.advanced(w, p + 1u, all);
-        close();
-        behind[k] = !w.alive ? HostAutomaton::DEAD : w.set.empty() ? HostAutomaton::SINK : A.intern(w.set.data(), (uint32_t)w.set.size());
+        B.w.set.clear();
+        for (uint16_t p : at[k]) A.advanced(B.w, p + 1u, all);
+        B.close(complete);
+        behind[k] = B.set();
     }
     size_t work = 0;
     for (uint32_t s = first; s < A.n_states; s++)
         for (int c = 0; c < t.n_cls; c++) {
             if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
             if (A.n_states > first + MOST_STATES || (work += waiting.size() + 32) > MOST_WORK) continue;
-            A.scan(s, c, all, w);
-            close();
-            A.record(s, c, w);
+            B.step(s, c, complete);
         }
     const uint32_t sink = A.n_states - first + 1;              // a finished sentence: nothing follows
     auto name = [&](uint32_t s) -> uint16_t { return s == HostAutomaton::DEAD ? FOLLOW_DEAD : s == HostAutomaton::SINK ? (uint16_t)sink : s == HostAutomaton::NONE ? FOLLOW_ANY : (uint16_t)(s - first + 1); };
@@ -453,35 +499,105 @@ void build_follow(const Tables &t, Follow &f) {
         for (int c = 0; c < t.n_cls; c++) f.next[(size_t)(s - first + 1) * t.n_cls + c] = name(A.st(s).trans[c]);
 }
 
-// Whether the terminal, entered in DFA state q, may end inside the string with the rest of it behind.
-static bool may_end_inside(const Tables &t, const Follow &f, uint32_t q, const uint8_t *bytes, size_t n) {
+// What every context takes behind a terminal: of an unknown set nothing is supposed but that it waits for one nonterminal Z, a set for each, and completing X
+// there leads to COMP(Z, X) without the item that waits (its continuation is not known).  A rule that started before a string started in a set
+// that waits for something that its left-hand side L begins, Y, and COMP(L, X) is contained in COMP(Y, X).  So every real set contains what stands here (by the same
+// induction), and a string that lives here lives in every context.  A terminal may stand in several positions: a state is the list of the sets behind
+// each, all of which must live.  Beyond the budget nothing is sure.
+void build_sure(const Tables &t, Follow &f) {
+    static const size_t MOST_STATES = 2048, MOST_WORK = (size_t)1 << 20;
+    BehindTerminal B(t);
+    HostAutomaton &A = B.A;
+    for (int p = 0; p < t.P; p++) {
+        const uint16_t code = t.sym[p];
+        if ((code >> SYM_KIND_SHIFT) != SYM_NT || B.unknown[code & SYM_ID_MASK_NT]) continue;
+        const Item it{(uint16_t)p, 0, A.n_states};
+        B.unknown[code & SYM_ID_MASK_NT] = A.add(&it, 1, 0, 0);
+    }
+    B.first = A.n_states;
+    auto complete = [&](const Item &it, uint32_t X) {
+        const size_t at = (size_t)(t.sym[A.st(it.o).items[0].p] & SYM_ID_MASK_NT) * t.N + X;
+        for (uint32_t k = t.comp_off[at]; k < t.comp_off[at + 1]; k++) {
+            const uint16_t p = t.comp_list[k];
+            if (p != COMP_ADVANCE_WAITING) B.w.insert(Item{p, (t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM ? t.term_start[t.sym[p] & SYM_ID_MASK] : (uint16_t)0, it.o});
+        }
+    };
+    size_t work = 0;
+    std::map<std::vector<uint32_t>, uint32_t> names;
+    std::vector<const std::vector<uint32_t> *> states{nullptr};   // 0: SURE_NOT
+    std::vector<uint32_t> key;
+    auto name = [&]() -> uint16_t {
+        std::sort(key.begin(), key.end());
+        key.erase(std::unique(key.begin(), key.end()), key.end());
+        const auto found = names.find(key);
+        if (found != names.end()) return (uint16_t)found->second;
+        if (states.size() > MOST_STATES) return SURE_NOT;
+        const auto at = names.emplace(key, (uint32_t)states.size()).first;
+        states.push_back(&at->first);
+        return (uint16_t)at->second;
+    };
+    const std::vector<std::vector<uint16_t>> at = positions_of_terminals(t);
+    f.sure_behind.assign(t.Q, SURE_NOT);
+    for (int k = 0; k < t.T; k++) {
+        if (at[k].empty()) continue;
+        key.clear();
+        for (uint16_t p : at[k]) { key.push_back(B.behind(p, complete)); work += 32; }
+        const uint16_t behind = name();
+        for (int q = t.term_start[k]; q < (k + 1 < t.T ? (int)t.term_start[k + 1] : t.Q); q++) f.sure_behind[q] = behind;
+    }
+    f.sure_next.assign(t.n_cls, SURE_NOT);
+    for (size_t s = 1; s < states.size(); s++)
+        for (int c = 0; c < t.n_cls; c++) {
+            bool all = work < MOST_WORK;
+            key.clear();
+            for (size_t i = 0; all && i < states[s]->size(); i++) {
+                const uint32_t from = (*states[s])[i];
+                work += from != HostAutomaton::SINK && A.st(from).trans[c] == HostAutomaton::NONE ? 32 : 1;
+                const uint32_t to = from == HostAutomaton::SINK ? HostAutomaton::DEAD : B.step(from, c, complete);
+                all = to != HostAutomaton::DEAD;
+                key.push_back(to);
+            }
+            f.sure_next.push_back(all ? name() : (uint16_t)SURE_NOT);
+        }
+}
+
+// Whether the terminal, entered in DFA state q, ends inside the string with the rest of it behind: in no context, in some perhaps, in every one.
+enum class EndsInside { NO, PERHAPS, SURELY };
+static EndsInside ends_inside(const Tables &t, const Follow &f, uint32_t q, const uint8_t *bytes, size_t n) {
+    EndsInside answer = EndsInside::NO;
     for (size_t k = 0; k + 1 < n; k++) {
         q = t.delta[(size_t)q * t.n_cls + t.cls[bytes[k]]];
-        if (q == DFA_DEAD) return false;
+        if (q == DFA_DEAD) break;
         if (!(t.qflags[q] & QF_ACCEPT)) continue;
-        uint32_t s = f.behind[q];
-        for (size_t j = k + 1; j < n && s != FOLLOW_DEAD; j++) s = f.next[(size_t)s * t.n_cls + t.cls[bytes[j]]];
-        if (s != FOLLOW_DEAD) return true;
+        uint32_t s = f.behind[q], sure = f.sure_behind[q];
+        for (size_t j = k + 1; j < n && s != FOLLOW_DEAD; j++) {
+            s = f.next[(size_t)s * t.n_cls + t.cls[bytes[j]]];
+            sure = f.sure_next[(size_t)sure * t.n_cls + t.cls[bytes[j]]];
+        }
+        if (s == FOLLOW_DEAD) continue;
+        if (sure != SURE_NOT) return EndsInside::SURELY;
+        answer = EndsInside::PERHAPS;
     }
-    return false;
+    return answer;
 }
 
 // For every DFA state q: run the DFA alone from q down the trie.  A string the DFA survives is
 // valid whatever the context (the in-progress terminal item survives or has just completed).  A
 // string on which the DFA dies is hopeless for this item unless the DFA passed an accepting state
-// first -- then the terminal may end there, and unless no context takes the rest, what follows depends on the parser.  Rows of
+// first -- then the terminal may end there: it is valid if every context takes the rest, hopeless if none does, and else depends on the parser.  Rows of
 // nonterminals are the union over the terminals that can begin them.
 void build_token_mask_cache(const Tables &t, const Follow &f, Trie &tr) {
     const int Wr = tr.Wr, rows = t.Q + t.N;
     tr.ci_valid.assign((size_t)rows * Wr, 0);
     tr.ci_cd.assign((size_t)rows * Wr, 0);
     tr.ci_ends.assign((size_t)rows * Wr, 0);
+    tr.ci_alone.assign((size_t)rows * Wr, 0);
     const uint32_t n = (uint32_t)tr.nodes.size();
     std::vector<uint16_t> st(MAX_TOKEN_LEN_ON_DEVICE + 2);
     std::vector<uint8_t> acc(MAX_TOKEN_LEN_ON_DEVICE + 2);
     for (int q = 0; q < t.Q; q++) {
         if (!(t.qflags[q] & QF_CONT)) continue;   // no item ever waits in a state without outgoing edges
-        uint32_t *V = &tr.ci_valid[(size_t)q * Wr], *C = &tr.ci_cd[(size_t)q * Wr], *E = &tr.ci_ends[(size_t)q * Wr];
+        uint32_t *V = &tr.ci_valid[(size_t)q * Wr], *C = &tr.ci_cd[(size_t)q * Wr], *E = &tr.ci_ends[(size_t)q * Wr], *S = &tr.ci_alone[(size_t)q * Wr];
         st[0] = (uint16_t)q; acc[0] = 0;
         for (uint32_t i = 0; i < n;) {
             const TrieNode &nd = tr.nodes[i];
@@ -491,21 +607,23 @@ void build_token_mask_cache(const Tables &t, const Follow &f, Trie &tr) {
                 if (acc[d - 1])
                     for (uint32_t r = nd.rank; r < nd.rank + nd.n_sub; r++) {
                         E[r >> 5] |= 1u << (r & 31);
-                        if (may_end_inside(t, f, (uint32_t)q, &tr.str_bytes[tr.str_off[r]], tr.str_off[r + 1] - tr.str_off[r])) C[r >> 5] |= 1u << (r & 31);
+                        const EndsInside ends = ends_inside(t, f, (uint32_t)q, &tr.str_bytes[tr.str_off[r]], tr.str_off[r + 1] - tr.str_off[r]);
+                        if (ends == EndsInside::PERHAPS) C[r >> 5] |= 1u << (r & 31);
+                        if (ends == EndsInside::SURELY) V[r >> 5] |= 1u << (r & 31);
                     }
                 i = nd.skip;
             } else {
                 st[d] = s2; acc[d] = acc[d - 1] | (t.qflags[s2] & QF_ACCEPT);
-                if (nd.has_string) V[nd.rank >> 5] |= 1u << (nd.rank & 31);
+                if (nd.has_string) { V[nd.rank >> 5] |= 1u << (nd.rank & 31); S[nd.rank >> 5] |= 1u << (nd.rank & 31); }
                 i++;
             }
         }
     }
     for (int Y = 0; Y < t.N; Y++) {
-        uint32_t *V = &tr.ci_valid[(size_t)(t.Q + Y) * Wr], *C = &tr.ci_cd[(size_t)(t.Q + Y) * Wr], *E = &tr.ci_ends[(size_t)(t.Q + Y) * Wr];
+        uint32_t *V = &tr.ci_valid[(size_t)(t.Q + Y) * Wr], *C = &tr.ci_cd[(size_t)(t.Q + Y) * Wr], *E = &tr.ci_ends[(size_t)(t.Q + Y) * Wr], *S = &tr.ci_alone[(size_t)(t.Q + Y) * Wr];
         for (uint16_t term : t.first_terms[Y]) {
             const size_t from = (size_t)t.term_start[term] * Wr;
-            for (int w = 0; w < Wr; w++) { V[w] |= tr.ci_valid[from + w]; C[w] |= tr.ci_cd[from + w]; E[w] |= tr.ci_ends[from + w]; }
+            for (int w = 0; w < Wr; w++) { V[w] |= tr.ci_valid[from + w]; C[w] |= tr.ci_cd[from + w]; E[w] |= tr.ci_ends[from + w]; S[w] |= tr.ci_alone[from + w]; }
         }
     }
 }

@@ -16,6 +16,7 @@ enum : uint16_t {
     SYM_ID_MASK = (1u << 14) - 1,
     DFA_DEAD = 0xFFFF,
     FOLLOW_ANY = 0, FOLLOW_DEAD = 0xFFFF,   // states of Follow: takes every string; takes none
+    SURE_NOT = 0,                           // of its second automaton: some context may not take it
 };
 // Item word used on the device: bits 0-13 dotted position, bit 14 = completed ("lhs complete since
 // origin"), bit 15 = the postdot symbol is a terminal and bits 16-31 hold its DFA state; for an item
@@ -85,8 +86,8 @@ struct DeviceTables {
     const uint8_t *cls_rep;     // [n_cls] one byte of each class (every DFA treats the bytes of a class alike)
     // Context-independent token-mask cache (paper Section 4.3), one bitset row of Wr words per DFA
     // state q (row q) and per nonterminal Y (row Q + Y), in string-rank order:
-    const uint32_t *ci_valid;   // strings a terminal entered in state q swallows whole
-    const uint32_t *ci_cd;      // strings on which that terminal dies after passing an accepting state, the rest of which may follow there in some context
+    const uint32_t *ci_valid;   // strings a terminal entered in state q swallows whole, or dies on after passing an accepting state, the rest of which follows there in every context
+    const uint32_t *ci_cd;      // ... the rest of which may follow there in some context
     // The same per TOKEN, for the mask kernel over the persistent automaton, which works in token order and writes the
     // caller's mask rows itself (null unless the engine runs that kernel):
     const Str16 *tok16;         // [V] the first fifteen byte classes of token v's string and a mark (the empty token, never allowed: the mark alone)

@@ -165,7 +165,9 @@ struct HostAutomaton {
         scan(s, cl, s, w);
         close(w);
     }
-    void scan(uint32_t s, int cl, uint32_t begun, Work &w) const {   // begun: the set that the rules begun by this byte are said to start in
+    void scan(uint32_t s, int cl, uint32_t begun, Work &w) const { scan(s, cl, [&](uint32_t) { return begun; }, w); }
+    template <class Begun>
+    void scan(uint32_t s, int cl, Begun begun_for, Work &w) const {   // begun_for(Y): the set that rules begun by this byte, for an item that waits for Y, are said to start in
         w.set.clear();
         const State &src = st(s);
         for (uint32_t i = 0; i < src.n_items; i++) {           // Scan
@@ -179,6 +181,7 @@ struct HostAutomaton {
                 if (f & QF_ACCEPT) advanced(w, it.p + 1u, it.o);
             } else if ((code >> SYM_KIND_SHIFT) == SYM_NT) {
                 const size_t at = (size_t)(code & SYM_ID_MASK_NT) * t.n_cls + cl;
+                const uint32_t begun = begun_for((uint32_t)(code & SYM_ID_MASK_NT));
                 for (uint32_t k = t.scan_off[at]; k < t.scan_off[at + 1]; k++) {
                     const uint16_t p0 = t.scan_list[k] & 0xFFFF, q2 = t.scan_list[k] >> 16;
                     const uint8_t f = t.qflags[q2];
@@ -196,20 +199,23 @@ struct HostAutomaton {
             if ((code >> SYM_KIND_SHIFT) != SYM_END) continue;
             const int X = code & SYM_ID_MASK;
             if (X == t.N - 1) { w.accepted = true; continue; }
-            const State &org = st(it.o);
-            for (uint32_t j = 0; j < org.n_items; j++) {
-                const Item y = org.items[j];
-                const uint16_t yc = t.sym[y.p];
-                if ((yc >> SYM_KIND_SHIFT) != SYM_NT) continue;
-                const size_t at = (size_t)(yc & SYM_ID_MASK_NT) * t.N + X;
-                for (uint32_t k = t.comp_off[at]; k < t.comp_off[at + 1]; k++) {
-                    const uint16_t p = t.comp_list[k];
-                    if (p == COMP_ADVANCE_WAITING) advanced(w, y.p + 1u, y.o);
-                    else w.insert(Item{p, (t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM ? t.term_start[t.sym[p] & SYM_ID_MASK] : (uint16_t)0, it.o});
-                }
-            }
+            completed(w, it, (uint32_t)X);
         }
         drop_completed(w);
+    }
+    void completed(Work &w, const Item it, uint32_t X) const {   // it: "X is complete"
+        const State &org = st(it.o);
+        for (uint32_t j = 0; j < org.n_items; j++) {
+            const Item y = org.items[j];
+            const uint16_t yc = t.sym[y.p];
+            if ((yc >> SYM_KIND_SHIFT) != SYM_NT) continue;
+            const size_t at = (size_t)(yc & SYM_ID_MASK_NT) * t.N + X;
+            for (uint32_t k = t.comp_off[at]; k < t.comp_off[at + 1]; k++) {
+                const uint16_t p = t.comp_list[k];
+                if (p == COMP_ADVANCE_WAITING) advanced(w, y.p + 1u, y.o);
+                else w.insert(Item{p, (t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM ? t.term_start[t.sym[p] & SYM_ID_MASK] : (uint16_t)0, it.o});
+            }
+        }
     }
     void drop_completed(Work &w) const {
         w.alive = !w.set.empty();

@@ -81,9 +81,15 @@ bool build_tables(const zf_grammar_desc *g, Tables &t);
 struct Follow {
     std::vector<uint16_t> behind;     // [Q] state behind the terminal that the DFA state belongs to (or FOLLOW_ANY, FOLLOW_DEAD)
     std::vector<uint16_t> next;       // [states][n_cls]
+    // And one that takes nothing but strings that every context takes: [Q] state behind the terminal (or SURE_NOT), [states][n_cls]
+    std::vector<uint16_t> sure_behind, sure_next;
 };
 void build_follow(const Tables &t, Follow &f);
-inline void follow_everything(const Tables &t, Follow &f) { f.behind.assign(t.Q, FOLLOW_ANY); f.next.assign(t.n_cls, FOLLOW_ANY); }
+void build_sure(const Tables &t, Follow &f);
+inline void follow_everything(const Tables &t, Follow &f) {
+    f.behind.assign(t.Q, FOLLOW_ANY); f.next.assign(t.n_cls, FOLLOW_ANY);
+    f.sure_behind.assign(t.Q, SURE_NOT); f.sure_next.assign(t.n_cls, SURE_NOT);
+}
 
 // ---- vocabulary trie ------------------------------------------------------------------------
 struct Trie {
@@ -98,7 +104,7 @@ struct Trie {
     int chunk_ranks = 32;
     int Wr = 0;                       // words per row of a rank-ordered bitmap
     std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]; empty in an engine with a device until somebody asks (host_token_mask_cache)
-    std::vector<uint32_t> ci_ends;    // ci_cd, and the strings whose rest no context takes: what the terminal by itself leaves open
+    std::vector<uint32_t> ci_alone, ci_ends;   // what the terminal decides by itself: strings it swallows whole; strings on which it dies behind an accepting state
 };
 // Context-independent token-mask cache (Section 4.3): per DFA state and per nonterminal, which
 // strings are decided by the terminal alone, or by what may follow it in any context, and which need the parser.

@@ -298,6 +298,7 @@ struct VocabRows {
     const uint16_t *delta;             // [Q][n_cls] next state, DFA_DEAD = none
     const uint32_t *first_off, *first_state;
     const uint16_t *behind, *follow;   // what may follow a terminal (Follow): [Q] state behind it, [states][n_cls] next state
+    const uint16_t *sure_behind, *sure_next;   // what every context takes behind it, likewise
     uint2 *both;
     uint32_t *valid, *undecided, *counts;
     uint32_t n, words, Q, N, n_cls;

@@ -452,6 +452,34 @@ def test_what_follows_a_terminal_decides_no_token_that_a_context_takes(words, le
         assert np.array_equal(st.debug_host_mask_automaton()[0], want), prefix
 
 
+def _nested_grammar():
+    """Terminals in several positions (the comma, the word), contexts that tell them apart, a nullable tail, nesting beyond what is known exactly."""
+    return (Grammar("nested").alts("V", [b"[", "L", b"]"], [b"{", "M", b"}"], [Rx(rb"[ab]+")]).alts("L", ["V", b",", "L"], ["V"], [])
+            .alts("M", [Rx(rb"[ab]+"), b":", "V", "T"]).alts("T", [b",", "M"], []).set_start("V"))
+
+
+@pytest.mark.parametrize("gram,alphabet,length", [(g, a, 5 if len(a) <= 3 else 4) for g, a in SMALL] + [(_nested_grammar, b"[]{},:a", 5)], ids=[s[0].__name__ for s in SMALL] + ["nested"])
+def test_what_every_context_takes_behind_a_terminal(gram, alphabet, length, zf, oracle_lib):
+    """Strings that the token-mask cache decides by what no context, and by what every context takes behind a terminal: masks equal the oracle's over every string up
+    to `length`, behind every viable prefix of up to three bytes and some longer ones (the first and the last string that may follow it)."""
+    g = gram()
+    toks = list(_all_strings(alphabet, length)) + [bytes(alphabet[:1]) * 9]
+    orc, eng = oracle_lib.Oracle(g), zf.Engine(g, toks, device=-1)
+    off, data = wvocab.vocab_csr(toks)
+    todo = [b""] + [p for p in _all_strings(alphabet, 3 if len(alphabet) <= 3 else 2)]
+    for prefix in todo:
+        so, st = orc.new_state(), eng.new_state()
+        if prefix:
+            if not so.feed_bytes(prefix):
+                continue
+            st.advance_bytes(prefix)
+        want = so.mask(off, data, 8)
+        assert np.array_equal(st.debug_host_mask_cached()[0], want), prefix
+        ids = np.flatnonzero(np.unpackbits(want.view(np.uint8), bitorder="little"))
+        if len(prefix) <= 1 and len(ids):
+            todo += [prefix + toks[ids[0]], prefix + toks[ids[-1]]]
+
+
 @pytest.mark.parametrize("size,first", [(1, None), (40, None), (40, b"1"), (8191, None), (8200, None), (9000, b"("), (9000, b"")])
 def test_trie_made_in_pieces(size, first, zf, oracle_lib):
     """The vocabulary's trie is made a first byte at a time, by one thread or by several (8,192 strings and more): vocabularies of any first byte, of one (all in
