@@ -490,12 +490,13 @@ __device__ __forceinline__ void fallback_share(const MaskArgs &a, uint32_t share
 //   Permutation: verdicts are produced in trie order, the caller wants bit v at word v >> 5.  A lane takes four neighbouring tokens of
 // PERMUTE_ROWS rows: four ranks, the four rows' words of each, four bits a row; eight lanes put a mask word together.
 //   Logits (zf_compute_mask_apply_async): the lane that has a token's bits masks its logits along.  They are requested with the ranks, before
-// anything is known of the mask, so that the reading of a pass hides the look-ups of the one before: 64 rows x 152,064 fp32 19.4 us, where the permutation (a token per lane
+// anything is known of the mask, so that the reading of a pass hides the look-ups of the one before: 64 rows x 152,064 fp32 17.4 us, where the permutation (a token per lane
 // and four look-ups, a store for every 64 tokens and row) took 10.8 and the launch behind it 13.5; 8 steps of the expression grammar without pruning 644 -> 606 us.
 //   Hand-over: see hand_over (zf_kernel_common.h).  With nothing listed the status is final when this kernel starts, and is handed over first.
 static const int PERMUTE_ROWS = 4;
 static const uint32_t PERMUTE_TOKENS = 4;             // neighbouring tokens of a lane
 static const uint32_t FINISH_SPIN_LIMIT = 1u << 23;   // polls of about 2 us each (a chunk whose sets hold 600 items is walked for four seconds)
+static const uint32_t FINISH_ROW_WORDS = 5;           // words of each row's bitmap that a thread requests at once: 81,920 strings
 constexpr int finish_block(bool staged) { return staged ? 512 : 256; }
 typedef uint32_t finish_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t finish_u32x2 __attribute__((ext_vector_type(2)));
@@ -544,7 +545,19 @@ __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a
         return q;
     };
     auto rows_of = [&](uint32_t rg) -> uint32_t { const uint32_t left = (uint32_t)a.batch - rg * PERMUTE_ROWS; return left < (uint32_t)PERMUTE_ROWS ? left : (uint32_t)PERMUTE_ROWS; };
-    Ahead next = request(v_begin + tid * PERMUTE_TOKENS, blockIdx.y * PERMUTE_ROWS, rows_of(blockIdx.y));   // does not depend on the fallback count
+    // Requested before it is known whether the fallback pass has work, which seldom is: the first group's words of the bitmap (they are asked for again behind
+    // that pass), ahead of the logits, since loads come back in order (64 rows x 152,064 fp32 19.2 -> 17.4 us), then the ranks and logits of the first pass (of two
+    // passes 18.2, of three 18.8: the words wait behind other blocks' logits).
+    constexpr uint32_t ROW_WORDS = STAGED ? FINISH_ROW_WORDS : 1;
+    uint32_t row_words[ROW_WORDS][PERMUTE_ROWS];
+    if (STAGED) {
+        const uint32_t *rows = a.rank_mask + (size_t)blockIdx.y * PERMUTE_ROWS * Wr, n_rows = rows_of(blockIdx.y);
+#pragma unroll
+        for (uint32_t i = 0; i < ROW_WORDS; i++)
+#pragma unroll
+            for (int m = 0; m < PERMUTE_ROWS; m++) { row_words[i][m] = 0; if (tid + i * BLOCK < Wr && (uint32_t)m < n_rows) row_words[i][m] = rows[(size_t)m * Wr + tid + i * BLOCK]; }
+    }
+    Ahead next = request(v_begin + tid * PERMUTE_TOKENS, blockIdx.y * PERMUTE_ROWS, rows_of(blockIdx.y));
     const uint32_t n_blocks = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x;
     const uint32_t n_over = a.counters[0];
     if (n_over != 0) {
@@ -591,8 +604,14 @@ __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a
         if (rg != blockIdx.y) next = request(v_begin + tid * PERMUTE_TOKENS, row0, n_rows);
         if (STAGED) {
             if (rg != blockIdx.y) __syncthreads();                        // the previous group's readers are done with the LDS copy
+            uint32_t from = tid;
+            if (rg == blockIdx.y && n_over == 0) {
+#pragma unroll
+                for (uint32_t i = 0; i < ROW_WORDS; i++) if (tid + i * BLOCK <= Wr) rows_lds[tid + i * BLOCK] = make_uint4(row_words[i][0], row_words[i][1], row_words[i][2], row_words[i][3]);
+                from += ROW_WORDS * BLOCK;
+            }
 #pragma unroll 5
-            for (uint32_t k = tid; k <= Wr; k += BLOCK) {
+            for (uint32_t k = from; k <= Wr; k += BLOCK) {
                 uint32_t w[PERMUTE_ROWS];
 #pragma unroll
                 for (int m = 0; m < PERMUTE_ROWS; m++) w[m] = k < Wr && (uint32_t)m < n_rows ? rows[(size_t)m * Wr + k] : 0u;

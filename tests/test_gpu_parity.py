@@ -1051,6 +1051,95 @@ def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cud
             assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
 
 
+@pytest.mark.parametrize("V,B", [(33001, 200), (70001, 3), (33001, 257), (2048, 2)])
+@pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
+def test_per_block_automaton_without_cache_rows(V, B, pruning, torch_cuda, oracle_lib):
+    """Every string through the per-block automaton (no token-mask cache, so no row of it to ask for early), in one pass of a block and in several."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    cfg = configs.CONFIGS[5]
+    g, toks = cfg.grammar(), cfg.vocab(V)
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, token_mask_cache=False, state_cache_entries=-1)
+    prefixes = [b"", b"a+b*c", b"((x", b"7*(a+b)"][:B]
+    want, rows = [], []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    for b in range(B):
+        rows.append(eng.new_state())
+        rows[-1].advance_bytes(prefixes[b % len(prefixes)])
+    d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    zf.compute_mask(eng, rows, d_mask)
+    got = d_mask.cpu().numpy().view(np.uint32)
+    for b in range(B):
+        assert np.array_equal(got[b], want[b % len(prefixes)]), b
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 16, 63, 64, 65, 130])
+def test_per_block_automaton_of_many_cache_rows(n, torch_cuda, oracle_lib):
+    """Sets that select n rows of the token-mask cache (the words of up to 64 are asked for ahead of the chart, eight at a time), in passes with undecided strings
+    and without: literals with a common beginning, a comma or a semicolon behind them by the context."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g = grammars.Grammar("many").alts("L", ["W", b",", "L"], [b"(", "M", b")"]).alts("M", ["W", b";", "M"], []).alts("W", *[[b"k%03d" % k] for k in range(n)]).set_start("L")
+    toks = [b"", b"k", b"0", b"00", b"01", b"000", b"(", b",", b";"] + [b"%03d%s" % (k, e) for k in range(n + 2) for e in (b"", b",", b";", b",(", b";k", b";)", b",k0")]
+    toks += [b"x%d" % k for k in range(40000)]                # passes of nothing but strings that are decided
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    prefixes = [b"k", b"(k", b"k0", b"(", b"(k000;k"]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p), p
+        want.append(so.mask(off, data, 8))
+    for pruning in (True, False):
+        eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, state_cache_entries=-1)
+        rows = [eng.new_state() for _ in prefixes]
+        for r, p in zip(rows, prefixes):
+            r.advance_bytes(p)
+        for at in ([0], [1], list(range(len(prefixes)))):
+            d_mask = torch.full((len(at), eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+            zf.compute_mask(eng, [rows[b] for b in at], d_mask)
+            got = d_mask.cpu().numpy().view(np.uint32)
+            for k, b in enumerate(at):
+                assert np.array_equal(got[k], want[b]), (prefixes[b], pruning)
+
+
+@pytest.mark.parametrize("n", [81800, 81919, 81920, 81921, 100003])
+def test_closing_kernel_over_many_strings(n, torch_cuda, oracle_lib):
+    """Rows of the rank-ordered bitmap of as many words as a block of the closing kernel requests at once, fewer and more, a last group of two rows: masks are
+    the oracle's, logits masked along with them."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g = configs.CONFIGS[5].grammar()
+    toks = [b"%d" % k for k in range(n - 60)] + [b"%d)+%d" % (k, k) for k in range(20)] + [b"%d+%d" % (k, k) for k in range(20)] + [b"%d)" % k for k in range(20)]
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    eng = zf.Engine(g, toks, device=0, pruning=False, state_cache_entries=-1)
+    prefixes = [b"", b"a+b*c", b"((x", b"7*(a+b)", b"(1"]
+    want = []
+    for p in prefixes:
+        so = orc.new_state()
+        assert so.feed_bytes(p)
+        want.append(so.mask(off, data, 8))
+    at = np.arange(50) % len(prefixes)
+    rows = [eng.new_state() for _ in at]
+    for r, p in zip(rows, at):
+        r.advance_bytes(prefixes[p])
+    logits = torch.randn((len(at), n), device="cuda")
+    d_mask, out = torch.full((len(at), eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda"), torch.zeros_like(logits)
+    zf.compute_mask_apply_async(eng, zf.StateBatch(rows), d_mask, logits, out=out)
+    zf.mask_wait(eng)
+    torch.cuda.synchronize()
+    wanted = np.stack([want[p] for p in at])
+    assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted)
+    allowed = torch.from_numpy(np.unpackbits(wanted.view(np.uint8), axis=1, bitorder="little")[:, :n].astype(bool)).cuda()
+    assert torch.equal(out, torch.where(allowed, logits, torch.full_like(logits, float("-inf"))))
+
+
 def test_host_diagnostics_of_an_engine_with_a_device(torch_cuda, oracle_lib):
     """The host's diagnostics read token-mask cache rows that an engine with a device does not hold on the host until somebody asks: each of them,
     the first to ask of an engine of its own."""
