@@ -97,6 +97,7 @@ struct DeviceSide {
     unsigned long long *d_tagged = nullptr; size_t tagged_cap = 0;   // LookArgs::tagged (words)
     uint32_t look_polls = LOOK_POLLS;
     StoreConst *d_konst = nullptr;
+    const uint32_t *no_trans = nullptr;     // engine without a persistent automaton: the row of the table that mask_look_kernel reads of a state without transitions
     uint32_t store_epoch = 1;                        // bumped whenever the store is cleared
     uint32_t store_states = 0, store_items = 0;      // as of the last call that reported back
     bool store_dirty = true;                         // the store must be cleared before its next use
@@ -331,8 +332,8 @@ int begin_device(zf_engine *e) {
             (rc = upload(d, e->follow.sure_behind, &r.sure_behind)) != ZF_OK || (rc = upload(d, e->follow.sure_next, &r.sure_next)) != ZF_OK) return rc;
         r.cls = T.cls; r.Q = (uint32_t)t.Q; r.N = (uint32_t)t.N; r.n_cls = (uint32_t)t.n_cls;
     }
-    if (e->store_on) {
-        // The mask kernels over the persistent automaton work in token order: every token's string as byte classes, and the
+    if (e->rows_on) {
+        // The mask kernels over the persistent automaton, and mask_look_kernel for calls that leave nothing to any, work in token order: every token's string as byte classes, and the
         // rows of the token-mask cache with one bit per token.
         const size_t V = (size_t)e->V, W = (size_t)e->W, n_rows = (size_t)(t.Q + t.N);   // a row each, of a vocabulary without a string too: the kernels read them
         const int64_t *off = nullptr;
@@ -355,7 +356,8 @@ size_t engine_bytes(const zf_engine *e) {
     const size_t V = (size_t)e->V, W = (size_t)e->W + 1, n_rows = (size_t)(t.Q + t.N), text = e->voc_bytes.size(), cap = store_cap_states(t.n_cls), ncls = (size_t)std::max(t.n_cls, 1);
     size_t n = ((size_t)1 << 20) + 4 * (t.advpq.size() + t.qinfo.size() + t.scan_off.size() + t.comp_off.size() + t.delta_dense.size() + t.dev_scan_list.size() + t.dev_comp_list.size()) + 2 * (t.delta.size() + e->follow.behind.size() + e->follow.next.size() + e->follow.sure_behind.size() + e->follow.sure_next.size());
     n += text * (sizeof(TrieNode) + 4 + 2) + (V / (size_t)e->opt.chunk_strings + 1) * (8 + CHUNK_ANC * sizeof(TrieNode)) + V * (4 + 4 + sizeof(Str16)) + n_rows * W * 8;
-    if (e->store_on) n += V * (8 + sizeof(Str16)) + text + n_rows * (W * 8 + 4) + cap * (sizeof(uint2) + ncls * 4 + 16) + STORE_CAP_ITEMS * sizeof(uint2) + (size_t)MAX_BATCH * 4;
+    if (e->rows_on) n += V * (8 + sizeof(Str16)) + text + n_rows * (W * 8 + 4);
+    if (e->store_on) n += cap * (sizeof(uint2) + ncls * 4 + 16) + STORE_CAP_ITEMS * sizeof(uint2) + (size_t)MAX_BATCH * 4;
     if (e->opt.state_cache_entries > 0) n += (size_t)e->opt.state_cache_entries * W * 4;
     return n;
 }
@@ -366,9 +368,9 @@ int fetch_rows(zf_engine *e) {
     const size_t n_rows = (size_t)(e->tab.Q + e->tab.N), W = (size_t)e->W;
     HIP_TRY(hipSetDevice(d->device));
     d->ci_undecided.assign(std::max<size_t>(n_rows, 1), 0);
-    d->h_ci_tok.resize(std::max<size_t>(n_rows * W, 1));
+    if (e->store_on) d->h_ci_tok.resize(std::max<size_t>(n_rows * W, 1));
     if (n_rows) HIP_TRY(hipMemcpy(d->ci_undecided.data(), d->voc.counts, n_rows * 4, hipMemcpyDeviceToHost));
-    if (n_rows * W) HIP_TRY(hipMemcpy(d->h_ci_tok.data(), d->voc.both, n_rows * W * sizeof(uint2), hipMemcpyDeviceToHost));
+    if (e->store_on && n_rows * W) HIP_TRY(hipMemcpy(d->h_ci_tok.data(), d->voc.both, n_rows * W * sizeof(uint2), hipMemcpyDeviceToHost));
     return ZF_OK;
 }
 
@@ -413,13 +415,18 @@ int setup_device(zf_engine *e) {
     if ((rc = engine_alloc(d, 2 * COUNTER_SET_WORDS * 4, &d->d_counters)) != ZF_OK) return rc;     // two sets of counters (see MaskArgs::counters)
     HIP_TRY(hipMemset(d->d_counters, 0, 2 * COUNTER_SET_WORDS * 4));
     {   // staging room every engine has from the start (zf_compute_mask_noalloc never grows it), and status words
-        const size_t status = 32 * DeviceSide::N_SLOTS, store_status = e->store_on ? DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8 : 0;
+        const size_t status = 32 * DeviceSide::N_SLOTS, store_status = e->rows_on ? DeviceSide::N_SLOTS * STORE_STATUS_WORDS * 8 : 0;
         HIP_TRY(hipHostMalloc(&d->h_block, DeviceSide::N_SLOTS * NOALLOC_STAGE_BYTES + status + store_status, hipHostMallocDefault));
         uint8_t *at = (uint8_t *)d->h_block;
         for (int k = 0; k < DeviceSide::N_SLOTS; k++, at += NOALLOC_STAGE_BYTES) { d->h_stage[k] = at; d->stage_cap[k] = NOALLOC_STAGE_BYTES; }
         memset(at, 0, status + store_status);
         d->h_status = (uint32_t *)at;
-        if (e->store_on) d->h_store_status = (volatile uint64_t *)(at + status);
+        if (e->rows_on) d->h_store_status = (volatile uint64_t *)(at + status);
+    }
+    if (e->rows_on) {
+        if ((rc = engine_alloc(d, 2 * STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
+        HIP_TRY(hipMemset(d->d_tickets, 0, 2 * STORE_TICKETS * 8));
+        if (!e->store_on && (rc = upload(d, std::vector<uint32_t>((size_t)std::max(t.n_cls, 1), HostAutomaton::NONE), &d->no_trans)) != ZF_OK) return rc;
     }
     if (e->store_on) {
         // Room of the persistent automaton: states x byte classes transition words (at most 128 MB), 4 M items, a hash table of
@@ -433,8 +440,6 @@ int setup_device(zf_engine *e) {
         if ((rc = engine_alloc(d, ((size_t)G.intern_mask + 1) * 8, &G.intern)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, 64, &G.ctl)) != ZF_OK) return rc;
         if ((rc = engine_alloc(d, (size_t)MAX_BATCH * 4, &d->d_import_root)) != ZF_OK) return rc;
-        if ((rc = engine_alloc(d, 2 * STORE_TICKETS * 8, &d->d_tickets)) != ZF_OK) return rc;
-        HIP_TRY(hipMemset(d->d_tickets, 0, 2 * STORE_TICKETS * 8));
         {
             const StoreConst k{d->tab, G};
             if ((rc = engine_alloc(d, sizeof k, &d->d_konst)) != ZF_OK) return rc;
@@ -736,6 +741,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
         if (!build_tables(g, e->tab)) { delete e; return ZF_ERR_GRAMMAR; }
         e->V = v->V; e->W = (v->V + 31) / 32;
         e->store_on = e->opt.device >= 0 && e->opt.walk_mode == 2 && e->opt.pruning != 0 && e->tab.n_cls <= (int)TOK_MORE;   // (a byte class for nearly every byte: the per-block automaton's records hold any class)
+        e->rows_on = e->store_on || (e->opt.device >= 0 && e->opt.walk_mode == 2 && !e->opt.disable_token_mask_cache && e->lane_cap_auto && e->tab.n_cls <= (int)TOK_MORE);
         if (e->opt.walk_mode == 2 && e->opt.pruning != 0) e->host_aut = new HostAutomaton(e->tab);
         if (wants_exploration(e))
             explorer.thread = std::thread([e, &explorer]() {
@@ -756,7 +762,7 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
             const int rc = begin_device(e);
             if (rc != ZF_OK) return give_up(rc);
         }
-        if (e->store_on)
+        if (e->rows_on)
             fetcher.thread = std::thread([e, &explorer, &fetcher]() {
                 try { fetcher.rc = fetch_rows(e); } catch (const std::bad_alloc &) { fetcher.rc = fail(ZF_ERR_OOM, "out of memory"); }
                 if (fetcher.rc == ZF_OK) explorer.tell(explorer.rows_made);
@@ -1220,6 +1226,7 @@ static int state_cache_lookup(DeviceSide *d, const std::vector<std::vector<uint3
 }
 
 static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, uint32_t slot);
+static int enqueue_decided(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, hipStream_t stream, bool wait, uint32_t slot);
 static int wait_for_calls(zf_engine *e, void *hip_stream);
 static const int STORE_NO_ROOM = 1;                       // enqueue_store_impl: the call does not fit the memory at hand (noalloc); nothing was enqueued
 // zf_compute_mask_apply_async: the logits the call's mask is to be applied to.  The mask kernel over the persistent automaton
@@ -1259,6 +1266,10 @@ static int enqueue_mask_impl(zf_engine *e, zf_state *const *states, int32_t batc
         if (rc != STORE_NO_ROOM) return rc;
     }
     catch_up_batch(states, batch);                        // these paths send the charts
+    if (e->rows_on && !e->store_on && !noalloc && d->cache.empty()) {
+        const int rc = enqueue_decided(e, states, batch, d_mask, stream, wait, slot);
+        if (rc != STORE_NO_ROOM) return rc;
+    }
     // ---- the packed form of every row: [n_sets][set offsets][item word, origin]... (also the cache key) ----
     static thread_local std::vector<std::vector<uint32_t>> packed;
     if ((int)packed.size() < batch) packed.resize(batch);
@@ -1684,6 +1695,195 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
     return all;
 }
 
+// A call of look-ups only, whose groups are in c.g: its shape, its records and its launch.  n_more: cache rows that the groups' records do not hold.
+static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int32_t batch, uint32_t *d_mask, hipStream_t stream, bool wait, bool noalloc, uint32_t slot,
+                        size_t n_more, uint32_t n_cache_rows, std::unique_lock<std::mutex> &host_lk) {
+    DeviceSide *d = e->dev;
+    DeviceSide::CallRecord &rec = d->rec[slot];
+    const int ng = (int)c.g.size();
+    const bool use_cache = !e->opt.disable_token_mask_cache;
+    const size_t n_members = (size_t)batch + n_more;      // behind the members: the cache rows that the records do not hold
+    const bool big = ng > STORE_INLINE_GROUPS;            // records and members travel in device memory instead of the argument block
+    auto align16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    // staging: [group records][blocks][members][groups of the members] (uploaded when big)
+    const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
+    const size_t off_block = align16(big ? sizeof(LookGroup) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
+    const size_t off_gof = align16(off_mem + 2 * n_members), up_bytes = align16(off_gof + (big && g_apply.out ? 2 * (size_t)batch : 0)), total = up_bytes + 16;
+    if (noalloc && (total > d->stage_cap[slot] || (big && up_bytes > NOALLOC_SCRATCH_BYTES))) return STORE_NO_ROOM;
+    if (total > d->stage_cap[slot]) {
+        const int rc = grow_stage(d, slot, total * 2 + 4096);
+        if (rc != ZF_OK) return rc;
+    }
+    if (big && !noalloc && up_bytes > d->chart_cap) {
+        HIP_TRY(hipStreamSynchronize(stream));
+        if (d->d_chart) (void)hipFree(d->d_chart);
+        d->d_chart = nullptr; d->chart_cap = 0;
+        const size_t cap = up_bytes * 2 + 4096;
+        HIP_TRY(hipMalloc(&d->d_chart, cap));
+        d->chart_cap = cap;
+    }
+    LookArgs k{};
+    const size_t esz = g_apply.dtype == 0 ? 4 : 2;
+    const bool whole = g_apply.out && (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
+    // mask_look_kernel masks the logits with wavefronts of their own, whatever their size: they read them while the others work the masks out.  The
+    // logits are dealt out in units of as many KB as make 2,048 wavefronts, 4 at most (units of 2 / 4 / 6 / 8 KB, us per pass: 16 steps of 16 x 128,256
+    // bf16 171 / 176 / 184 / 186, of 64 x 152,064 fp32 - / 361 / 371 / 379, 8 steps of 130 x 40,037 bf16 148 / 144 / 149 / 151; 256 x 128,256 - / 235 / 229 / 239).
+    const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
+    const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
+    const uint32_t unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048)), row_units = (row_kb + unit_kb - 1) / unit_kb;
+    if (whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32) && (uint64_t)row_units * (uint64_t)batch <= LOOK_UNITS_MAX) {
+        static_assert(LOOK_UNITS_MAX / STORE_WAVES + 9 * MAX_BATCH + 4096 <= 16 * 65535, "with the mask's (max_blocks) the blocks of a group fit their count");
+        k.unit_kb = unit_kb;
+        k.row_units = row_units;
+        k.units = k.row_units * (uint32_t)batch;
+        const size_t words = (size_t)ng * (size_t)d->tab.W + (k.units + STORE_WAVES - 1) / STORE_WAVES;
+        if (words > d->tagged_cap) {
+            const int rc = settle_calls(d);
+            if (rc != ZF_OK) return rc;
+            HIP_TRY(hipStreamSynchronize(stream));
+            if (d->d_tagged) (void)hipFree(d->d_tagged);
+            d->d_tagged = nullptr; d->tagged_cap = 0;
+            const size_t cap = std::max(words * 2, (size_t)STORE_INLINE_GROUPS * (size_t)d->tab.W);
+            HIP_TRY(hipMalloc((void **)&d->d_tagged, cap * 8));
+            d->tagged_cap = cap;
+            HIP_TRY(launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(cap * 2), stream));
+        }
+        k.polls = d->look_polls;
+        k.tagged = d->d_tagged; k.logits = g_apply.logits; k.out = g_apply.out; k.stride = g_apply.stride; k.dtype = (uint32_t)g_apply.dtype + 1;
+        g_apply.fused = true;
+    }
+    const int budget = std::max(ng, look_blocks_per_cu() * std::max(1, d->cus));
+    k.mask_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, 0, k.units != 0);
+    // ---- the records ----
+    {
+        uint8_t *h = (uint8_t *)d->h_stage[slot];
+        LookGroup *gr = big ? (LookGroup *)h : c.look.g;
+        uint32_t *blk = (uint32_t *)(h + off_block);
+        const bool members_apart = big || n_members > (size_t)STORE_INLINE_ROWS;
+        uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member, *gof = (uint16_t *)(h + off_gof);
+        uint32_t mem_at = 0, blk_at = 0, more_at = (uint32_t)batch;
+        for (int r = 0; r < ng; r++) {
+            const RowGroup &g = c.g[r];
+            LookGroup &m = gr[r];
+            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u);
+            m.w[0] = g.pooled ? g.slot : g.dev;
+            m.w[1] = g.n_ent | flags << 8 | (uint32_t)(g.seg_w - 1) << 16;
+            m.w[2] = (blk_at & 0xFFFFu) | (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16;
+            m.w[3] = mem_at | (uint32_t)g.n << 16;
+            m.w[4] = g.slot & 0xFFFFu;
+            for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;
+            const uint32_t n_here = g.n_ent > (uint32_t)STORE_GROUP_ENT ? LOOK_ENT_OF_MORE : g.n_ent;
+            for (uint32_t j = 0; j < n_here; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
+            if (n_here < g.n_ent) {
+                m.w[4 + ((n_here + 1) >> 1)] |= more_at << (((n_here + 1) & 1u) * 16u);
+                for (uint32_t j = n_here; j < g.n_ent; j++) mem[more_at++] = (uint16_t)g.ents[j];
+            }
+            for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
+                if (big && k.units) gof[mem_at] = (uint16_t)r;
+                mem[mem_at++] = (uint16_t)b;
+                if (g.dev) note_device_state(d, states[b], g.dev);
+            }
+            if (big) for (int p = 0; p < g.parts; p++) { blk[2 * blk_at] = (uint32_t)r; blk[2 * blk_at + 1] = (uint32_t)p | (uint32_t)g.parts << 16; blk_at++; }
+            else blk_at += (uint32_t)g.parts;
+        }
+        const uint8_t *up = noalloc ? d->scratch : (const uint8_t *)d->d_chart;
+        k.trans = e->store_on ? d->store.trans : d->no_trans; k.cache = d->tab.ci_tok; k.tok16 = d->tab.tok16; k.out_mask = d_mask; k.pool = d->d_pool;
+        k.konst = d->d_konst;
+        if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); k.group_of = (const uint16_t *)(up + off_gof); }
+        else if (members_apart) k.members = (const uint16_t *)(h + off_mem);
+        k.V = (uint32_t)e->V; k.W = (uint32_t)d->tab.W; k.ncls = (uint32_t)d->tab.n_cls; k.n_groups = (uint32_t)ng;
+    }
+    k.tickets = d->d_tickets + d->ticket_set * STORE_TICKETS; k.tickets_next = d->d_tickets + (d->ticket_set ^ 1u) * STORE_TICKETS;
+    k.status = (unsigned long long *)d->h_store_status + slot * STORE_STATUS_WORDS;
+    HIP_TRY(next_call_number(d, stream));
+    k.seq = rec.seq = d->call_seq;
+    k.complete = wait ? 1 : 0;
+    const bool prof = d->profiling;
+    d->report.chart_bytes = (int64_t)(total + (big ? 0 : sizeof(LookGroup) * ng));
+    d->report.cache_rows = (int32_t)n_cache_rows;
+    d->report.main_ms = d->report.fallback_ms = d->report.permute_ms = 0.f;
+    d->report.overflow_chunks = d->report.walk_chunks = d->report.parser_steps = 0;
+    if (big) HIP_TRY(launch_upload(d->h_stage[slot], noalloc ? d->scratch : (uint8_t *)d->d_chart, up_bytes, stream));
+    if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
+    d->closing_kernel = false;
+    rec.debug_failed = d->debug_failed; d->debug_failed = 0;
+    const uint32_t grid = look_grid(k);
+    // Up to 64 blocks each have a status word of their own, and nobody draws a ticket (one row x 32,000 223 -> 214 us per 32 steps); more share 16 (16 x 128,256, eight waiting calls: 139; with 64 words to look at 143, in two levels 139).
+    k.done_groups = rec.done_groups = grid <= (uint32_t)STORE_TICKET_GROUPS ? grid : 16u;
+    HIP_TRY(launch_mask_look(k, c.look, stream));
+    d->ticket_set ^= 1u;
+    if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
+    d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
+    d->pending++;
+    d->last_seq = k.seq; d->last_slot = slot;
+    rec.active = true;
+    // Nothing in the call is expected to fail: its states' transitions are in the table for certain, no call in flight is still to say so.  zf_mask_wait
+    // then has nothing to wait for, and the host gets the next step ready while this one is at work (a step of one row x 32,000: 13.6 us
+    // waited for, 10.1 not; 16 x 128,256 bf16 14.4 and 12.3; 130 x 40,037 bf16 26.1 and 21.6).
+    // (Not one that leaves rows in the state cache's pool: later calls are served those.)
+    rec.sure = !wait && !prof && !(e->store_on && d->store_dirty);
+    for (const RowGroup &g : c.g) rec.sure &= g.pooled || !g.keep;
+    uint32_t in_store = 0;                                // calls in flight that went through the store; the others have flags that zf_mask_wait has to await
+    for (const DeviceSide::CallRecord &other : d->rec) if (other.active) { in_store++; if (!other.sure) rec.sure &= &other == &rec; }
+    rec.sure &= in_store == d->pending;
+    if (rec.sure) d->lazy_stream = stream;
+    host_lk.unlock();
+    // the waiting call returns with the mask complete: the kernel wrote it through to memory before it drew its tickets
+    return wait ? wait_for_calls(e, (void *)stream) : ZF_OK;
+}
+
+// An engine without a persistent automaton (pruning off): a call all of whose rows select token-mask cache rows that leave no token to the parser is one of look-ups
+// too, without any to make.  Rows with the same list are a group.  STORE_NO_ROOM: some row leaves something, or does not fit a record; nothing was enqueued.
+// (64 rows x 152,064 of the expression grammar, 8 steps: 262 us through the per-block automaton and its closing kernel, 144 so.  Calls with a state cache or
+// without allocations keep to the per-block automaton: it is what knows the one, and fits the static array.)
+static int enqueue_decided(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, hipStream_t stream, bool wait, uint32_t slot) {
+    DeviceSide *d = e->dev;
+    static thread_local StoreCall c;
+    std::unique_lock<std::mutex> host_lk(e->host_mu);
+    c.g.clear(); c.spare_ents.clear(); c.next_row.resize(batch);
+    static thread_local std::unordered_multimap<uint64_t, uint32_t> by_list;
+    static thread_local std::vector<size_t> at_of;        // of each group: where its list begins
+    by_list.clear(); at_of.clear();
+    size_t n_more = 0;
+    uint32_t n_cache_rows = 0;
+    for (int32_t b = 0; b < batch; b++) {
+        const Chart &ch = chart_of(states[b]);
+        const uint32_t lo = ch.set_off[ch.n_sets() - 1], n_items = ch.set_off[ch.n_sets()] - lo;
+        const size_t at = c.spare_ents.size();
+        c.spare_ents.resize(at + n_items);
+        const uint32_t n = current_set_entries(e->tab, ch.items.data() + lo, n_items, c.spare_ents.data() + at);
+        const uint32_t *ents = c.spare_ents.data() + at;
+        if (n > LOOK_ENT_MAX) return STORE_NO_ROOM;
+        for (uint32_t k = 0; k < n; k++) if (ents[k] >= 65536u || d->ci_undecided[ents[k]] != 0) return STORE_NO_ROOM;
+        const uint64_t sig = entries_signature(ents, n);
+        c.next_row[b] = -1;
+        RowGroup *g = nullptr;
+        for (auto range = by_list.equal_range(sig); range.first != range.second && !g; ++range.first) {
+            RowGroup &x = c.g[range.first->second];
+            if (x.n_ent == n && std::equal(ents, ents + n, c.spare_ents.data() + at_of[range.first->second])) g = &x;
+        }
+        if (g) {
+            c.next_row[b] = g->last; g->last = b; g->n++;
+            c.spare_ents.resize(at);
+            continue;
+        }
+        c.spare_ents.resize(at + n);
+        RowGroup x{};
+        x.lead = states[b]; x.last = b; x.n = 1; x.n_ent = n;
+        if (n > (uint32_t)STORE_GROUP_ENT) n_more += n - LOOK_ENT_OF_MORE;
+        n_cache_rows += n;
+        by_list.emplace(sig, (uint32_t)c.g.size());
+        c.g.push_back(x); at_of.push_back(at);
+    }
+    if (d->tab.W > 65535 || (size_t)batch + n_more > 65535) return STORE_NO_ROOM;
+    for (size_t r = 0; r < c.g.size(); r++) c.g[r].ents = c.spare_ents.data() + at_of[r];
+    d->report.cache_hits = 0; d->report.cache_misses = 0;
+    DeviceSide::CallRecord &rec = d->rec[slot];
+    rec.epoch = d->store_epoch; rec.host_epoch = e->host_epoch;
+    rec.groups.clear(); rec.rows.clear(); rec.undecided = 0;
+    return enqueue_look(e, c, states, batch, d_mask, stream, wait, false, slot, n_more, n_cache_rows, host_lk);
+}
+
 static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, void *hip_stream, bool wait, bool noalloc, uint32_t slot) {
     DeviceSide *d = e->dev;
     HostAutomaton &A = *e->host_aut;
@@ -1835,14 +2035,13 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         if (g.pooled || g.dev == HostAutomaton::SINK) continue;
         look = g.dev && g.at && (A.st(g.at).walked == d->store_epoch || (d->closed_epoch == d->store_epoch && g.at < d->closed_states && g.dev == g.at));
     }
-    if (look) spill = false;
-    const size_t n_members = (size_t)batch + (look ? n_more : 0);   // behind the members: the cache rows that the records do not hold
+    if (look) return enqueue_look(e, c, states, batch, d_mask, stream, wait, noalloc, slot, n_more, n_cache_rows, host_lk);
     const bool big = ng > STORE_INLINE_GROUPS;            // records and members travel in device memory instead of the argument block
     auto align16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
     // staging: [group records][blocks][members] (uploaded when big), then what the kernels read in place
     const int max_blocks = std::max(ng, STORE_BLOCKS_PER_CU * std::max(1, d->cus)) + 8 * ng;
-    const size_t off_block = align16(big ? (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
-    const size_t off_gof = align16(off_mem + 2 * n_members), up_bytes = align16(off_gof + (big && look && g_apply.out ? 2 * (size_t)batch : 0));
+    const size_t off_block = align16(big ? sizeof(StoreGroup) * ng : 0), off_mem = align16(off_block + (big ? 8 * (size_t)max_blocks : 0));
+    const size_t up_bytes = align16(off_mem + 2 * (size_t)batch);
     const size_t off_spill = up_bytes, off_ent = align16(off_spill + (spill ? sizeof(StoreRow) * ng : 0)), off_pend = align16(off_ent + (spill ? 4 * n_spill_ent : 0));
     const size_t off_rows = align16(off_pend + (spill ? n_spill_pend : 0)), off_so = align16(off_rows + sizeof(RowChart) * n_imp);
     const size_t off_items = align16(off_so + 4 * n_off), off_imp = align16(off_items + sizeof(Item) * n_items);
@@ -1867,37 +2066,9 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     const uint32_t lds = store_lds_bytes(d->tab, d->mode, scratch);
     if (lds > (uint32_t)STORE_LDS_MAX) return fail(ZF_ERR_INVALID_ARG, "the grammar tables leave no LDS for the mask kernel");
     int logit_bytes = 0;                                  // of a logit the mask kernel masks itself
-    LookArgs k{};
     const size_t esz = g_apply.dtype == 0 ? 4 : 2;
     const bool whole = g_apply.out && (uintptr_t)g_apply.logits % esz == 0 && (uintptr_t)g_apply.out % esz == 0;
-    // mask_look_kernel masks the logits with wavefronts of their own, whatever their size: they read them while the others work the masks out.  The
-    // logits are dealt out in units of as many KB as make 2,048 wavefronts, 4 at most (units of 2 / 4 / 6 / 8 KB, us per pass: 16 steps of 16 x 128,256
-    // bf16 171 / 176 / 184 / 186, of 64 x 152,064 fp32 - / 361 / 371 / 379, 8 steps of 130 x 40,037 bf16 148 / 144 / 149 / 151; 256 x 128,256 - / 235 / 229 / 239).
-    const uint32_t row_kb = (uint32_t)(((uint64_t)e->V * esz + 1023) / 1024);
-    const uint64_t kb = (uint64_t)row_kb * (uint64_t)batch;
-    const uint32_t unit_kb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(LOOK_UNIT_KB, (kb + 2047) / 2048)), row_units = (row_kb + unit_kb - 1) / unit_kb;
-    if (look && whole && e->V > 0 && (uint64_t)batch * (uint64_t)e->V < (1ull << 32) && (uint64_t)row_units * (uint64_t)batch <= LOOK_UNITS_MAX) {
-        static_assert(LOOK_UNITS_MAX / STORE_WAVES + 9 * MAX_BATCH + 4096 <= 16 * 65535, "with the mask's (max_blocks) the blocks of a group fit their count");
-        k.unit_kb = unit_kb;
-        k.row_units = row_units;
-        k.units = k.row_units * (uint32_t)batch;
-        const size_t words = (size_t)ng * (size_t)d->tab.W + (k.units + STORE_WAVES - 1) / STORE_WAVES;
-        if (words > d->tagged_cap) {
-            const int rc = settle_calls(d);
-            if (rc != ZF_OK) return rc;
-            HIP_TRY(hipStreamSynchronize(stream));
-            if (d->d_tagged) (void)hipFree(d->d_tagged);
-            d->d_tagged = nullptr; d->tagged_cap = 0;
-            const size_t cap = std::max(words * 2, (size_t)STORE_INLINE_GROUPS * (size_t)d->tab.W);
-            HIP_TRY(hipMalloc((void **)&d->d_tagged, cap * 8));
-            d->tagged_cap = cap;
-            HIP_TRY(launch_clear_words((uint32_t *)d->d_tagged, (uint32_t)(cap * 2), stream));
-        }
-        k.polls = d->look_polls;
-        k.tagged = d->d_tagged; k.logits = g_apply.logits; k.out = g_apply.out; k.stride = g_apply.stride; k.dtype = (uint32_t)g_apply.dtype + 1;
-        g_apply.fused = true;
-    }
-    if (g_apply.out && !look) {
+    if (g_apply.out) {
         // mask_store_kernel does both as long as the logits are few enough that masking them hides behind the walk of the vocabulary;
         // beyond, a launch of its own masks them at the memory's rate with the work spread evenly over the chip.
         if (whole && 2ull * (uint64_t)batch * (uint64_t)e->V * esz <= STORE_FUSE_BYTES) {
@@ -1906,47 +2077,10 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
             logit_bytes = (int)esz;
         }
     }
-    const int budget = std::max(ng, (look ? look_blocks_per_cu() : std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch))) * std::max(1, d->cus));
-    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes, look && k.units);
+    const int budget = std::max(ng, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
+    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes, false);
     // ---- the records ----
-    if (look) {
-        uint8_t *h = (uint8_t *)d->h_stage[slot];
-        LookGroup *gr = big ? (LookGroup *)h : c.look.g;
-        uint32_t *blk = (uint32_t *)(h + off_block);
-        const bool members_apart = big || n_members > (size_t)STORE_INLINE_ROWS;
-        uint16_t *mem = members_apart ? (uint16_t *)(h + off_mem) : c.look.member, *gof = (uint16_t *)(h + off_gof);
-        uint32_t mem_at = 0, blk_at = 0, more_at = (uint32_t)batch;
-        for (int r = 0; r < ng; r++) {
-            const RowGroup &g = c.g[r];
-            LookGroup &m = gr[r];
-            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u);
-            m.w[0] = g.pooled ? g.slot : g.dev;
-            m.w[1] = g.n_ent | flags << 8 | (uint32_t)(g.seg_w - 1) << 16;
-            m.w[2] = (blk_at & 0xFFFFu) | (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16;
-            m.w[3] = mem_at | (uint32_t)g.n << 16;
-            m.w[4] = g.slot & 0xFFFFu;
-            for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;
-            const uint32_t n_here = g.n_ent > (uint32_t)STORE_GROUP_ENT ? LOOK_ENT_OF_MORE : g.n_ent;
-            for (uint32_t j = 0; j < n_here; j++) m.w[4 + ((j + 1) >> 1)] |= g.ents[j] << (((j + 1) & 1u) * 16u);
-            if (n_here < g.n_ent) {
-                m.w[4 + ((n_here + 1) >> 1)] |= more_at << (((n_here + 1) & 1u) * 16u);
-                for (uint32_t j = n_here; j < g.n_ent; j++) mem[more_at++] = (uint16_t)g.ents[j];
-            }
-            for (int32_t b = g.last; b >= 0; b = c.next_row[b]) {
-                if (big && k.units) gof[mem_at] = (uint16_t)r;
-                mem[mem_at++] = (uint16_t)b;
-                if (g.dev) note_device_state(d, states[b], g.dev);
-            }
-            if (big) for (int p = 0; p < g.parts; p++) { blk[2 * blk_at] = (uint32_t)r; blk[2 * blk_at + 1] = (uint32_t)p | (uint32_t)g.parts << 16; blk_at++; }
-            else blk_at += (uint32_t)g.parts;
-        }
-        const uint8_t *up = noalloc ? d->scratch : (const uint8_t *)d->d_chart;
-        k.trans = d->store.trans; k.cache = d->tab.ci_tok; k.tok16 = d->tab.tok16; k.out_mask = d_mask; k.pool = d->d_pool;
-        k.konst = d->d_konst;
-        if (big) { k.groups = (const LookGroup *)up; k.block_of = (const uint32_t *)(up + off_block); k.members = (const uint16_t *)(up + off_mem); k.group_of = (const uint16_t *)(up + off_gof); }
-        else if (members_apart) k.members = (const uint16_t *)(h + off_mem);
-        k.V = (uint32_t)e->V; k.W = (uint32_t)d->tab.W; k.ncls = (uint32_t)d->tab.n_cls; k.n_groups = (uint32_t)ng;
-    } else {
+    {
         uint8_t *h = (uint8_t *)d->h_stage[slot];
         StoreGroup *gr = big ? (StoreGroup *)h : c.in.g;
         uint32_t *blk = (uint32_t *)(h + off_block);
@@ -2044,7 +2178,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     a.complete = wait ? 1 : 0;
     a.report_size = n_imp ? 1 : 0;
     const bool prof = d->profiling;
-    d->report.chart_bytes = (int64_t)(total + (big ? 0 : (look ? sizeof(LookGroup) : sizeof(StoreGroup)) * ng));
+    d->report.chart_bytes = (int64_t)(total + (big ? 0 : sizeof(StoreGroup) * ng));
     d->report.cache_rows = (int32_t)n_cache_rows;
     d->report.main_ms = d->report.fallback_ms = d->report.permute_ms = 0.f;
     d->report.overflow_chunks = d->report.walk_chunks = d->report.parser_steps = 0;
@@ -2054,35 +2188,16 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
     if (prof) HIP_TRY(hipEventRecord(d->ev[0], stream));
     d->closing_kernel = false;
     rec.debug_failed = 0;
-    if (look) {
-        rec.debug_failed = d->debug_failed; d->debug_failed = 0;
-        k.tickets = a.tickets; k.tickets_next = a.tickets_next; k.status = a.status; k.seq = a.seq; k.complete = a.complete;
-        k.mask_blocks = a.n_blocks;
-        const uint32_t grid = look_grid(k);
-        // Up to 64 blocks each have a status word of their own, and nobody draws a ticket (one row x 32,000 223 -> 214 us per 32 steps); more share 16 (16 x 128,256, eight waiting calls: 139; with 64 words to look at 143, in two levels 139).
-        k.done_groups = rec.done_groups = grid <= (uint32_t)STORE_TICKET_GROUPS ? grid : 16u;
-        HIP_TRY(launch_mask_look(k, c.look, stream));
-    } else {
-        rec.done_groups = 0;
-        HIP_TRY(launch_mask_store(a, c.in, lds, stream));
-        for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
-    }
+    rec.done_groups = 0;
+    HIP_TRY(launch_mask_store(a, c.in, lds, stream));
+    for (const RowGroup &g : c.g) if (!g.pooled && g.at && g.at != HostAutomaton::SINK) A.st(g.at).walked = d->store_epoch;
     d->ticket_set ^= 1u;
     if (prof) { HIP_TRY(hipEventRecord(d->ev[1], stream)); HIP_TRY(hipEventRecord(d->ev[3], stream)); }
     d->next_slot = (slot + 1) % DeviceSide::N_SLOTS;
     d->pending++;
     d->last_seq = a.seq; d->last_slot = slot;
     rec.active = true;
-    // Nothing in the call is expected to fail: its states' transitions are in the table for certain, no call in flight is still to say so.  zf_mask_wait
-    // then has nothing to wait for, and the host gets the next step ready while this one is at work (a step of one row x 32,000: 13.6 us
-    // waited for, 10.1 not; 16 x 128,256 bf16 14.4 and 12.3; 130 x 40,037 bf16 26.1 and 21.6).
-    // (Not one that leaves rows in the state cache's pool: later calls are served those.)
-    rec.sure = look && !wait && !prof && !d->store_dirty;
-    for (const RowGroup &g : c.g) rec.sure &= g.pooled || !g.keep;
-    uint32_t in_store = 0;                                // calls in flight that went through the store; the others have flags that zf_mask_wait has to await
-    for (const DeviceSide::CallRecord &other : d->rec) if (other.active) { in_store++; if (!other.sure) rec.sure &= &other == &rec; }
-    rec.sure &= in_store == d->pending;
-    if (rec.sure) d->lazy_stream = stream;
+    rec.sure = false;
     host_lk.unlock();
     // the waiting call returns with the mask complete: the kernel wrote it through to memory before it drew its tickets
     return wait ? wait_for_calls(e, hip_stream) : ZF_OK;

@@ -146,6 +146,7 @@ struct zf_engine {
     bool start_nullable = false;
     bool lane_cap_auto = true;          // no explicit lane_item_cap: the budget follows the rows' set sizes
     bool store_on = false;              // the mask calls go through the persistent automaton (walk_mode 2, pruning on, a device)
+    bool rows_on = false;               // the rows of the token-mask cache are there in token order (for that, and with pruning off for calls they decide)
     // zf_advance through the persistent automaton on the host (walk_mode 2, pruning on): a token's bytes are walked through
     // the table of known transitions, an Earley byte step runs only for a transition nobody has taken before, and the
     // state's chart is brought up to date only when somebody asks for it.  One automaton per engine.

@@ -1051,7 +1051,7 @@ def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cud
             assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
 
 
-@pytest.mark.parametrize("V,B", [(33001, 200), (70001, 3), (33001, 257), (2048, 2)])
+@pytest.mark.parametrize("V,B", [(16384, 300), (16385, 300), (33001, 200), (70001, 3), (33001, 257), (4097, 3), (2048, 2)])
 @pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
 def test_per_block_automaton_without_cache_rows(V, B, pruning, torch_cuda, oracle_lib):
     """Every string through the per-block automaton (no token-mask cache, so no row of it to ask for early), in one pass of a block and in several."""
@@ -1138,6 +1138,62 @@ def test_closing_kernel_over_many_strings(n, torch_cuda, oracle_lib):
     assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), wanted)
     allowed = torch.from_numpy(np.unpackbits(wanted.view(np.uint8), axis=1, bitorder="little")[:, :n].astype(bool)).cuda()
     assert torch.equal(out, torch.where(allowed, logits, torch.full_like(logits, float("-inf"))))
+
+
+@pytest.mark.parametrize("B,dtype", [(1, "f32"), (5, "bf16"), (70, "f32"), (300, "bf16")])
+def test_calls_that_the_cache_rows_decide(B, dtype, torch_cuda, oracle_lib):
+    """Without pruning: calls whose rows leave nothing to the parser (look-ups without any), of one group, of several and of more than the argument block holds, of more rows
+    than it holds, of sentences that are complete, and calls of rows that leave something (the per-block automaton's) between them, with no wait but
+    zf_mask_wait and on two streams; waiting calls; a state cache (which keeps to the per-block automaton).  Masks and logits are the oracle's."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    g = grammars.Grammar("decided").alts("S", *[[b"k%03d" % k, b"!"] for k in range(90)], [b"(", "L", b")"]).alts("L", ["W", b",", "L"], ["W"], [b"[", "M", b"]"]).alts("M", ["W", b";", "M"], ["W"]).alts("W", [b"xy"], [b"xyz"]).set_start("S")
+    toks = [b"", b"k", b"(", b"xy", b"xyz", b"y,", b"y;", b"y)", b"y,x", b"yz;xy", b"z", b"!", b"9!", b"(xy"] + [b"%02d" % k for k in range(100)] + [b"%03d!" % k for k in range(100)] + [b"n%d" % k for k in range(3000)]
+    off, data = wvocab.vocab_csr(toks)
+    orc = oracle_lib.Oracle(g)
+    decided = [b"k%03d" % k for k in range(90)] + [b"k", b"k0", b"", b"k001!", b"(xy,xyz)"]
+    mixed = [b"(x", b"([x", b"(xy", b"([xyz"]
+    masks = {}
+    for p in decided + mixed:
+        so = orc.new_state()
+        assert not p or so.feed_bytes(p), p
+        masks[p] = so.mask(off, data, 8)
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    V = len(toks)
+
+    def batch(eng, prefixes):
+        rows = [eng.new_state() for _ in prefixes]
+        for r, p in zip(rows, prefixes):
+            if p:
+                r.advance_bytes(p)
+        return zf.StateBatch(rows)
+
+    eng = zf.Engine(g, toks, device=0, pruning=False, state_cache_entries=-1)
+    lists = [[decided[k % len(decided)] for k in range(B)], [decided[-1]] * B, [mixed[k % len(mixed)] for k in range(B)], [(decided + mixed)[(7 * k) % (len(decided) + len(mixed))] for k in range(B)], [b"k"] * B, [decided[(3 * k) % 9] for k in range(B)]]
+    batches = [batch(eng, x) for x in lists]
+    order = [0, 0, 1, 4, 2, 0, 3, 5, 0, 2, 2, 4, 0, 1, 5, 3, 0, 0, 0]
+    logits = torch.randn((len(order), B, V), device="cuda").to(kind)
+    got = torch.full((len(order), B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    out = torch.zeros_like(logits)
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for k, b in enumerate(order):
+        with torch.cuda.stream(streams[1 if k in (8, 9, 10, 15) else 0]):
+            zf.compute_mask_apply_async(eng, batches[b], got[k], logits[k], out=out[k])
+            zf.mask_wait(eng)
+    torch.cuda.synchronize()
+    for k, b in enumerate(order):
+        wanted = np.stack([masks[p] for p in lists[b]])
+        assert np.array_equal(got[k].cpu().numpy().view(np.uint32), wanted), (k, b)
+        allowed = torch.from_numpy(np.unpackbits(wanted.view(np.uint8), axis=1, bitorder="little")[:, :V].astype(bool)).cuda()
+        assert torch.equal(out[k], torch.where(allowed, logits[k], torch.full_like(logits[k], float("-inf")))), (k, b)
+    cached = zf.Engine(g, toks, device=0, pruning=False)
+    for e in (eng, cached):
+        for _ in range(2):
+            for x in lists:
+                one = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+                zf.compute_mask(e, batch(e, x), one)
+                assert np.array_equal(one.cpu().numpy().view(np.uint32), np.stack([masks[p] for p in x]))
 
 
 def test_host_diagnostics_of_an_engine_with_a_device(torch_cuda, oracle_lib):
