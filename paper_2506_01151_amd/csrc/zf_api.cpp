@@ -1765,7 +1765,7 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
         for (int r = 0; r < ng; r++) {
             const RowGroup &g = c.g[r];
             LookGroup &m = gr[r];
-            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u);
+            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u) | (use_cache && g.undecided == 0 && g.n_ent <= (uint32_t)STORE_GROUP_ENT ? STORE_ROW_DECIDED : 0u);
             m.w[0] = g.pooled ? g.slot : g.dev;
             m.w[1] = g.n_ent | flags << 8 | (uint32_t)(g.seg_w - 1) << 16;
             m.w[2] = (blk_at & 0xFFFFu) | (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16;

@@ -76,6 +76,7 @@ static const uint32_t STORE_ROW_IMPORTED = 2u;  // the group's start state is th
 static const uint32_t STORE_ROW_SPILL = 4u;     // the record does not fit the short form: it is in StoreArgs::spilled
 static const uint32_t STORE_ROW_POOLED = 8u;    // the mask is a finished row of the state cache's pool (row number: start): copied, nothing to check
 static const uint32_t STORE_ROW_KEEP = 16u;     // the finished mask goes to the state cache's pool as well (row number: slot)
+static const uint32_t STORE_ROW_DECIDED = 64u;  // mask_look_kernel: the listed cache rows, all in the record, leave no token to the parser
 static const uint32_t STORE_ROW_REPORT = 32u;   // the host does not know the state the group stands in: the kernel reports it
 struct StoreView {
     uint2 *hdr;                 // [cap_states] (first item in the arena, item count); count 0xFFFFFFFF = not published
