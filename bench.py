@@ -38,8 +38,8 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one; masks and logits) and of apply_mask_vec_kernel, from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 15756312, "apply_bytes_per_launch": 8493560, "instructions_per_launch": 3780991,
-                    "kernel_sources_sha256": "d1a96e3116e018bcf818f6154083b0c1b75b4b9494bdde66116f892d74403c0a"}
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 10924223, "apply_bytes_per_launch": 8493573, "instructions_per_launch": 2243667,
+                    "kernel_sources_sha256": "394c11796a200f9380c7deae51794161f68d17b629184877ac37a5a14d6fc25b"}
 
 
 def kernel_sources_digest():
@@ -258,7 +258,7 @@ def side_config(zf, torch, configs, idx, steps, warm, pruning=True, walk_mode=2)
     apply_bytes = 2 * B * V * esz + B * eng.W * 4
     apply_ms = statistics.fmean(p["kern"]["apply"])
     out = {"workload": f"configs[{idx - 1}] {cfg.name}: V={V} batch={B} logits={cfg.dtype} pruning={'on' if pruning else 'off'}",
-           "trajectory": "oracle-sampled file", "steps": steps, "mask_kernel": KERNEL_OF_MODE[walk_mode if pruning else 0],
+           "trajectory": "oracle-sampled file", "steps": steps, "mask_kernel": KERNEL_OF_MODE[walk_mode] if pruning or walk_mode != 2 else "mask_look_kernel / mask_automaton_kernel",
            "value": B * V * steps / r["total"], "ms_per_step": r["total"] / steps * 1e3, "timed_passes_ms_per_step": [x["total"] / steps * 1e3 for x in runs],
            "p50_mask_apply_latency_us": pct(r["lat"], 0.5) * 1e6, "p99_mask_apply_latency_us": pct(r["lat"], 0.99) * 1e6, "max_mask_apply_latency_us": max(r["lat"]) * 1e6,
            "mean_advance_us_per_step": statistics.fmean(r["adv"]) * 1e6,
