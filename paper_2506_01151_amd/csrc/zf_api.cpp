@@ -1604,7 +1604,7 @@ struct RowGroup {
     const uint32_t *ents; uint32_t n_ent;
     double undecided;
     uint32_t slot;                 // row of the state cache's pool
-    uint8_t pooled, keep, known;
+    uint8_t pooled, keep, known, decided, alone;   // decided: its cache rows, all in a record, leave nothing undecided; alone: the wavefronts with logits do all there is to do
     int32_t seg_w, parts;          // launch shape
 };
 struct StoreCall {                 // one call's working memory, kept per thread
@@ -1644,6 +1644,7 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
         // nor more words than its wavefront stores to all its rows in a few stores (256 rows x 128,256 in some 20 states, 8 waiting calls: 241 -> 213 us; 64 rows of
         // the query language, 16 calls: 274 -> 258; with half as many words 216 and 254)
         if (!rows_apart) sw = std::min(sw, std::max(1, STORE_MEMBER_WORDS / g[r].n));
+        else if (g[r].alone) sw = W;                      // (nothing to do: a block that reports)
         segs[r] = std::max(1, (W + sw - 1) / sw);
         g[r].seg_w = sw;
         // what a pass costs a wavefront (microseconds, measured): an empty segment 2.8, a segment with a batch 3.7, each further
@@ -1752,6 +1753,12 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
         k.tagged = d->d_tagged; k.logits = g_apply.logits; k.out = g_apply.out; k.stride = g_apply.stride; k.dtype = (uint32_t)g_apply.dtype + 1;
         g_apply.fused = true;
     }
+    for (RowGroup &g : c.g) {
+        g.decided = use_cache && !g.pooled && g.undecided == 0 && g.n_ent <= (uint32_t)STORE_GROUP_ENT;
+        // Where the wavefronts with logits make a group's mask they may as well store it, and no others work it out: 16 steps of 64 x 128,256 bf16 of the query language 161 -> 150 us
+        // (from four rows a group on 160), 8 of 130 x 40,037 103.1 -> 102.3.  Not with fp32, whose units hold half as many words: 16 of 64 x 152,064 288 -> 294.
+        g.alone = k.units && g.decided && !g.keep && k.dtype == 2;
+    }
     const int budget = std::max(ng, look_blocks_per_cu() * std::max(1, d->cus));
     k.mask_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, 0, k.units != 0);
     // ---- the records ----
@@ -1765,10 +1772,10 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
         for (int r = 0; r < ng; r++) {
             const RowGroup &g = c.g[r];
             LookGroup &m = gr[r];
-            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u) | (use_cache && g.undecided == 0 && g.n_ent <= (uint32_t)STORE_GROUP_ENT ? STORE_ROW_DECIDED : 0u);
+            const uint32_t flags = g.pooled ? STORE_ROW_POOLED : (use_cache ? STORE_ROW_CACHE : 0u) | (g.keep ? STORE_ROW_KEEP : 0u) | (g.decided ? STORE_ROW_DECIDED : 0u);
             m.w[0] = g.pooled ? g.slot : g.dev;
-            m.w[1] = g.n_ent | flags << 8 | (uint32_t)(g.seg_w - 1) << 16;
-            m.w[2] = (blk_at & 0xFFFFu) | (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16;
+            m.w[1] = g.n_ent | flags << 8 | (g.alone ? 0u : (uint32_t)(g.seg_w - 1) << 16);
+            m.w[2] = (blk_at & 0xFFFFu) | (g.alone ? 0u : (uint32_t)((d->tab.W + g.seg_w - 1) / g.seg_w) << 16);
             m.w[3] = mem_at | (uint32_t)g.n << 16;
             m.w[4] = g.slot & 0xFFFFu;
             for (int j = 5; j < LOOK_WORDS; j++) m.w[j] = 0;

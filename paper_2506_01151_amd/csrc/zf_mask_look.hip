@@ -29,7 +29,7 @@
 // (Calls of up to 64 blocks, eight per XCD, leave nothing to anybody.)
 //   Where the cache rows leave no token undecided they are the mask: those wavefronts put it together themselves (STORE_ROW_DECIDED), wait for nobody and read no logit of which nothing
 // comes: 16 steps of 64 x 128,256 bf16 of the query language 175 -> 158 us, 8 of 256 x 128,256 of the schema 222 -> 217, 16 of 16 x 128,256 133 -> 127,
-// 16 of 64 x 152,064 fp32 293 -> 290 (176, 230, 132 and 292 with every logit read).
+// 16 of 64 x 152,064 fp32 293 -> 290 (176, 230, 132 and 292 with every logit read).  Of bf16 logits they store the group's mask rows too, and no others work it out: 161 -> 150 for the first.
 #include "zf_kernel_common.h"
 #include "zf_aut_step.h"
 
@@ -110,7 +110,7 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
     r[3] = 0;
     if (HOW == LOOK_MANY) {
         group = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a.group_of[m]);
-        r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[1]);
+        r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[1]); r[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[2]);
 #pragma unroll
         for (int k = 4; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.groups[group].w[k]);
     } else if (HOW == LOOK_ONE) {
@@ -124,13 +124,14 @@ __device__ __forceinline__ void mask_logits(const LookArgs &a, const LookInline 
 #pragma unroll
         for (int k = 1; k < LOOK_WORDS; k++) r[k] = (uint32_t)__builtin_amdgcn_readlane((int)x[k], (int)group);
     }
-    const bool stores_row = (r[3] >> 16) > look_members_max<DT>();
+    const bool decided = (r[1] & ((uint32_t)STORE_ROW_DECIDED << 8)) != 0;
+    const bool stores_row = (decided && r[2] >> 16 == 0) || (r[3] >> 16) > look_members_max<DT>();   // (a decided group without segments: nobody else does)
     const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)member_row(a, in, m));
     const unsigned long long *const words = a.tagged + (size_t)group * W;
     const uint32_t w0 = part * nu * KB_WORDS;
     unsigned long long t[WORDS];
     bool here = true;
-    if (r[1] & ((uint32_t)STORE_ROW_DECIDED << 8)) {         // the cache rows are the mask: nothing is waited for, and no logit read of which nothing comes
+    if (decided) {                                           // the cache rows are the mask: nothing is waited for, and no logit read of which nothing comes
         const uint32_t n_ent = r[1] & 0xFFu;
 #pragma unroll
         for (uint32_t k = 0; k < WORDS; k++) {
