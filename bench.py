@@ -38,8 +38,8 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one; masks and logits) and of apply_mask_vec_kernel, from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 10924223, "apply_bytes_per_launch": 8493573, "instructions_per_launch": 2243667,
-                    "kernel_sources_sha256": "394c11796a200f9380c7deae51794161f68d17b629184877ac37a5a14d6fc25b"}
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 11494079, "apply_bytes_per_launch": 8493574, "instructions_per_launch": 2187746,
+                    "kernel_sources_sha256": "33cdf595bd5bd79ee84d8bb1edfb1e2d09334f2ad5e0fd0d69a4dc9c70b672e8"}
 
 
 def kernel_sources_digest():
