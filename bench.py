@@ -39,7 +39,7 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
 MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 11494079, "apply_bytes_per_launch": 8493574, "instructions_per_launch": 2187746,
-                    "kernel_sources_sha256": "33cdf595bd5bd79ee84d8bb1edfb1e2d09334f2ad5e0fd0d69a4dc9c70b672e8"}
+                    "kernel_sources_sha256": "032f9f2f7db6126cdbc67034baccbfb9f9c1142801e8a86fda4b5ad1e0f925f5"}
 
 
 def kernel_sources_digest():

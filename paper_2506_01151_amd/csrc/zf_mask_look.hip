@@ -4,7 +4,7 @@
 // computed -- or the automaton was explored to its end when the engine was compiled -- every transition that the vocabulary walk
 // from that state can meet is in the table.  Such a state needs look-ups only: no Earley byte step, no grammar tables, no bytes
 // to be fed first.  That is every call of a decode loop but the first visits of a state, and it is what this kernel is made for;
-// mask_store_kernel takes the other calls.
+// mask_store_kernel takes the other calls.  (Without pruning, calls whose rows the token-mask cache decides: there is no string to walk.)
 //
 // What bounds it.  Not bandwidth (a launch moves a few MB) but the length of one wavefront: dependent trips to memory
 // (arguments, cache words and the state's table row, strings, about 1 us each) and the instructions between them, which one
