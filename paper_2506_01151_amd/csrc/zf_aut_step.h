@@ -166,13 +166,14 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
 static const int AUT_LANES_TRIES = 96;    // distinct candidates per round, summed up, after which this variant hands the step to the wide one (HAND_OVER)
 // What Complete makes of a set is a function of what Scan has left in it, so a set whose first items are those of a known set's is that set: seen(w, o, n), asked
 // between the two with lane i < n holding item i, says whether they are (AUT_SEEN).  The first items of the new set, `scanned` of them, stand
-// in the scratch behind the kept ones where there is room.
+// in the scratch behind the kept ones where there is room; with any other answer than AUT_OK nothing does, and `scanned` is 0.
 template <bool HAND_OVER, class SetsT, class Seen>
 __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint32_t *sc_w, uint32_t *sc_o, uint32_t sc_cap,
                                               uint32_t cur, uint32_t byte, uint32_t cl, uint32_t lane, uint32_t &nnew_out, uint32_t &kept_out, uint32_t &scanned, Seen seen) {
     uint64_t src;
     uint32_t ns;
     S.view(cur, src, ns);
+    scanned = 0;
     uint32_t nw = 0xFFFFFFFFu, no = 0, nnew = 0, tries = 0;  // no item word is all ones
     const uint32_t room = sc_cap < 64u ? sc_cap : 64u;
     auto equal = [&](uint32_t x, uint32_t s) -> unsigned long long { return __builtin_amdgcn_uicmp(x, s, 32 /* equal */); };   // the lanes on which x is s, as a scalar
@@ -228,7 +229,7 @@ __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint3
             chain(listed && (ef.y & QF_ACCEPT), aw, p, cur);
         }
     }
-    scanned = nnew;
+    const uint32_t first_items = nnew;                       // (with items that there was no room for, which a set is not kept with)
     if (nnew && seen(nw, no, nnew)) return AUT_SEEN;
     // Complete, until no new item is complete: the items of all completed items' origin sets -- the ones that may wait for the
     // completed nonterminal -- are dealt to the lanes, and the entries of the table that they hit are dealt again.
@@ -295,7 +296,7 @@ __device__ __forceinline__ int aut_step_lanes(const TV &T, const SetsT &S, uint3
     if (keep) { const uint32_t at = (uint32_t)__popcll(kb & ((1ull << lane) - 1ull)); sc_w[at] = nw; sc_o[at] = no; }
     nnew_out = nnew;
     kept_out = (uint32_t)__popcll(kb);
-    if (kept_out + scanned > sc_cap) scanned = 0;
+    if (kept_out + first_items <= sc_cap) scanned = first_items;
     if (lane < scanned) { sc_w[kept_out + lane] = nw; sc_o[kept_out + lane] = no; }
     return AUT_OK;
 }

@@ -1051,6 +1051,35 @@ def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cud
             assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
 
 
+@pytest.mark.parametrize("depth", [40, 70, 120])
+@pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
+def test_per_block_automaton_steps_that_are_handed_over(depth, pruning, torch_cuda, oracle_lib):
+    """A byte that completes `depth` rules at once and leaves 20 items: more than the step for a dozen items holds or tries (64, 96), so that the wide one takes it over, and
+    what Scan had left is not known of the new set.  Item 20 of the set, before the completed ones are dropped, is a terminal that goes on in place, and the only one that
+    the next byte leaves: with it for what Scan had left, that byte would lead back to the whole set."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    ends = [[b"m", "X", bytes([65 + k])] for k in range(19)]
+    g = (grammars.Grammar("nest").alts("S", [b"q", "L"]).alts("L", [b"k", "L"], [b"k", "P"]).alts("P", *ends, [b"m", "X", grammars.Rx(rb"a*b")], [b"m", "X"])
+         .alts("X", [b"x"]).set_start("S"))
+    toks = [b"x", b"xa", b"xab", b"xaab", b"xb"] + [p + bytes([65 + k]) for k in range(19) for p in (b"x", b"xa", b"xaa", b"xab")] + [b"xaax", b"xx", b"", b"k", b"m"]
+    prefix = b"q" + b"k" * depth + b"m"
+    off, data = wvocab.vocab_csr(toks)
+    so = oracle_lib.Oracle(g).new_state()
+    assert so.feed_bytes(prefix)
+    want = so.mask(off, data, 8)
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, token_mask_cache=False, state_cache_entries=-1)
+    rows = [eng.new_state() for _ in range(3)]
+    for r in rows:
+        r.advance_bytes(prefix)
+    for n in (1, 3):
+        d_mask = torch.full((n, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        zf.compute_mask(eng, rows[:n], d_mask)
+        assert eng.mask_report().parser_steps > 0 and eng.mask_report().overflow_chunks == 0
+        for got in d_mask.cpu().numpy().view(np.uint32):
+            assert np.array_equal(got, want), [t for k, t in enumerate(toks) if (got[k >> 5] ^ want[k >> 5]) >> (k & 31) & 1]
+
+
 @pytest.mark.parametrize("V,B", [(16384, 300), (16385, 300), (33001, 200), (70001, 3), (33001, 257), (4097, 3), (2048, 2)])
 @pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
 def test_per_block_automaton_without_cache_rows(V, B, pruning, torch_cuda, oracle_lib):
