@@ -756,8 +756,9 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
             });
         e->voc_off.assign(v->off, v->off + v->V + 1);
         e->voc_bytes.assign(v->bytes, v->bytes + v->off[v->V]);
-        if (e->lane_cap_auto) { build_follow(e->tab, e->follow); build_sure(e->tab, e->follow); }
-        else follow_everything(e->tab, e->follow);        // an explicit item budget is there to see sets outgrow it: every string that a terminal leaves open is walked
+        // an explicit item budget is there to see sets outgrow it: every string that a terminal leaves open is walked
+        if (!e->lane_cap_auto || e->opt.disable_token_mask_cache) follow_everything(e->tab, e->follow);
+        else if (e->opt.device >= 0) { build_follow(e->tab, e->follow); build_sure(e->tab, e->follow); }
         if (e->opt.device >= 0) {
             const int rc = begin_device(e);
             if (rc != ZF_OK) return give_up(rc);
@@ -769,7 +770,6 @@ int zf_compile(const zf_grammar_desc *g, const zf_vocab_desc *v, const zf_option
                 else fetcher.error = zf_last_error();
             });
         build_trie(v, e->opt.chunk_strings, e->tab.cls, e->trie);
-        if (e->opt.device < 0) build_token_mask_cache(e->tab, e->follow, e->trie);
     } catch (const std::bad_alloc &) { return give_up(fail(ZF_ERR_OOM, "out of memory")); }
     catch (const std::system_error &) { return give_up(fail(ZF_ERR_OOM, "no thread to be had")); }
     if (e->opt.device >= 0) {

@@ -396,17 +396,30 @@ namespace zf {
 // unknown[Y]; complete: what completing X in such a set leads to).  Sets that are known to a depth of DEEPEST, or beyond EXACT_STATES of them, count as unknown,
 // so that grammars with recursion have finitely many.  What that leaves undecided in the rows of a cache, of 67,435 strings: JSON 24,767, a schema 16,017, the expression grammar 3,817 with what may follow alone and
 // nothing known exactly; with what surely follows 24,106, 15,117 and none; with sets known to a depth of 1 17,208 and 6,287, of 2 16,247 and 5,638, of 3 15,929 and
-// 5,606 (and twice the states).  0.3 to 0.9 ms a grammar, beside the exploration.
+// 5,606 (and twice the states).
+//   What all of it may cost is bounded by what it does: every candidate of Scan and Complete, and every item of an origin set that Complete looks at, is paid for
+// before it is looked at (`left`); a step that cannot be paid for is not made, and what is not known then stays open.  A candidate takes 2 to 12 ns.  JSON spends
+// 126,000 on what may follow and 82,000 on what surely does, a schema 582,000 and 90,000, the query language 219,000 and 286,000, the expression grammar 9,000 each;
+// their cache rows are the same from 200,000 on (with 100,000 the query language leaves 92 of 32,000 tokens open in place of 8).  The budget is 0.5 to 3 ms for either, beside an exploration of 8 ms and more.
+// (Bounded by steps, whatever they cost, a value of 500 object types took 1.3 s, a hundred mutually recursive nonterminals 0.15 and four hundred 10.)
 struct BehindTerminal {
     static constexpr uint8_t DEEPEST = 2;
     static constexpr uint32_t EXACT_STATES = 256;
+    static constexpr size_t BUDGET = 1u << 18, STEP = 32;      // STEP: what a step costs besides: its set is looked up, its transitions are laid out
     const Tables &t;
     HostAutomaton A;
     HostAutomaton::Work w;
+    HostAutomaton::Completed done;                             // where Complete led from what Scan has left
+    std::vector<Item> scanned;
     std::vector<uint32_t> unknown;
     uint32_t first = 0;                                        // ids below it are unknown sets
     std::vector<uint8_t> depth;                                // [id - first]
-    explicit BehindTerminal(const Tables &t_) : t(t_), A(t_), unknown(t_.N, 0) {}
+    std::vector<uint32_t> arriving;                            // [position] items that the dot's arrival there makes (HostAutomaton::advanced)
+    size_t left = BUDGET;
+    explicit BehindTerminal(const Tables &t_) : t(t_), A(t_), unknown(t_.N, 0), arriving(t_.P, 1) {
+        for (int p = t.P - 2; p >= 0; p--) if ((t.sym[p] >> SYM_KIND_SHIFT) == SYM_NT && (t.sym[p] & SYM_NULLABLE_BIT)) arriving[p] += arriving[p + 1];
+    }
+    bool spend(size_t n) { if (n > left) { left = 0; return false; } left -= n; return true; }
     uint32_t depth_of(uint32_t id) {                           // how many known sets stand between the set and the unknown ones, itself included
         for (uint32_t s = first + (uint32_t)depth.size(); s < A.n_states; s++) {   // (a set refers to earlier ones only)
             uint8_t d = 0;
@@ -415,29 +428,70 @@ struct BehindTerminal {
         }
         return depth[id - first];
     }
-    template <class Complete> void close(Complete complete) {
+    bool spend_scan(uint32_t s, int c) {
+        const HostAutomaton::State &src = A.st(s);
+        size_t n = STEP;
+        for (uint32_t i = 0; i < src.n_items && n <= left; i++) {
+            const uint16_t p = src.items[i].p, code = t.sym[p];
+            if ((code >> SYM_KIND_SHIFT) == SYM_TERM) n += 1 + arriving[p + 1];
+            else if ((code >> SYM_KIND_SHIFT) == SYM_NT) {
+                const size_t at = (size_t)(code & SYM_ID_MASK_NT) * t.n_cls + c;
+                for (uint32_t k = t.scan_off[at]; k < t.scan_off[at + 1]; k++) n += 1 + arriving[(t.scan_list[k] & 0xFFFF) + 1];
+            }
+        }
+        return spend(n);
+    }
+    bool spend_completed(const Item &it, uint32_t X) {
+        const HostAutomaton::State &org = A.st(it.o);
+        size_t n = org.n_items;
+        for (uint32_t j = 0; j < org.n_items && n <= left; j++) {
+            const uint16_t p = org.items[j].p, code = t.sym[p];
+            if ((code >> SYM_KIND_SHIFT) != SYM_NT) continue;
+            const size_t at = (size_t)(code & SYM_ID_MASK_NT) * t.N + X;
+            n += t.comp_off[at + 1] - t.comp_off[at];
+            if (t.comp_off[at + 1] > t.comp_off[at] && t.comp_list[t.comp_off[at + 1] - 1] == COMP_ADVANCE_WAITING) n += arriving[p + 1];
+        }
+        return spend(n);
+    }
+    // complete(item, X): what it leads to is in the set, or false: nothing is left to spend
+    template <class Complete> bool close(Complete complete) {
         for (size_t i = 0; i < w.set.size(); i++) {
             const Item it = w.set[i];
             const uint16_t code = t.sym[it.p];
             if ((code >> SYM_KIND_SHIFT) != SYM_END || (code & SYM_ID_MASK) == t.N - 1) continue;
-            if (it.o < first) complete(it, (uint32_t)(code & SYM_ID_MASK));
-            else A.completed(w, it, (uint32_t)(code & SYM_ID_MASK));
+            const uint32_t X = code & SYM_ID_MASK;
+            if (it.o < first) { if (!complete(it, X)) return false; continue; }
+            if (!spend_completed(it, X)) return false;
+            A.completed(w, it, X);
         }
         A.drop_completed(w);
+        return true;
     }
     uint32_t set() { return !w.alive ? HostAutomaton::DEAD : w.set.empty() ? HostAutomaton::SINK : A.intern(w.set.data(), (uint32_t)w.set.size()); }
-    template <class Complete> uint32_t behind(uint16_t p, Complete complete) {   // the terminal at position p
+    // Behind the terminal at the positions p, in rules that started in the unknown sets begun_for(p); NONE: nothing is left to spend.
+    template <class Positions, class Begun, class Complete> uint32_t behind(const Positions &p, Begun begun_for, Complete complete) {
+        size_t n = STEP;
+        for (uint16_t x : p) n += arriving[x + 1];
+        if (!spend(n)) return HostAutomaton::NONE;
         w.set.clear();
-        A.advanced(w, p + 1u, unknown[t.lhs_of[p]]);
-        close(complete);
-        return set();
+        for (uint16_t x : p) A.advanced(w, x + 1u, begun_for(x));
+        return close(complete) ? set() : HostAutomaton::NONE;
     }
     template <class Complete> uint32_t step(uint32_t s, int c, Complete complete) {
-        if (A.st(s).trans[c] == HostAutomaton::NONE) {
+        if (A.st(s).trans[c] == HostAutomaton::NONE && spend_scan(s, c)) {
             const bool known = A.n_states < first + EXACT_STATES && depth_of(s) <= DEEPEST;
             A.scan(s, c, [&](uint32_t Y) { return known ? s : unknown[Y]; }, w);
-            close(complete);
-            A.record(s, c, set(), false);
+            uint32_t sig = 0;
+            const bool completes = A.completes(w);
+            const HostAutomaton::Completed::Entry *met = completes ? done.find(w.set, sig) : nullptr;
+            if (met) A.record(s, c, met->to, false);
+            else {
+                if (completes) scanned = w.set;
+                if (close(complete)) {
+                    A.record(s, c, set(), false);
+                    if (completes) done.add(scanned, sig, A.st(s).trans[c], false);
+                }
+            }
         }
         return A.st(s).trans[c];
     }
@@ -450,44 +504,35 @@ static std::vector<std::vector<uint16_t>> positions_of_terminals(const Tables &t
 
 // What may follow a terminal, whatever its context: the unknown set waits for everything that the grammar waits for anywhere.  A real set
 // is always contained in the set that the same bytes lead to here (by induction over Scan, Complete and Predict), so a string that dies here dies in
-// every context.  Beyond the budget the automaton takes everything.
+// every context.  What the budget does not reach takes everything.
 void build_follow(const Tables &t, Follow &f) {
-    static const size_t MOST_STATES = 4096, MOST_WORK = (size_t)1 << 22;
+    static const size_t MOST_STATES = 4096;
     BehindTerminal B(t);
     HostAutomaton &A = B.A;
     const uint32_t all = A.n_states;
     std::vector<Item> waiting;
     const std::vector<std::vector<uint16_t>> at = positions_of_terminals(t);
-    for (int p = 0; p < t.P; p++) if ((t.sym[p] >> SYM_KIND_SHIFT) == SYM_NT) waiting.push_back(Item{(uint16_t)p, 0, all});
+    struct Waits { std::vector<uint16_t> at; size_t arriving = 0; };
+    std::vector<Waits> waits(t.N);                             // the positions that wait for a nonterminal: behind them is all that completing it leads to, since what is predicted waits here as well
+    for (int p = 0; p < t.P; p++) {
+        if ((t.sym[p] >> SYM_KIND_SHIFT) != SYM_NT) continue;
+        waiting.push_back(Item{(uint16_t)p, 0, all});
+        Waits &x = waits[t.sym[p] & SYM_ID_MASK_NT];
+        x.at.push_back((uint16_t)p); x.arriving += B.arriving[p + 1];
+    }
     A.add(waiting.data(), (uint32_t)waiting.size(), 0, 0);
     B.unknown.assign(t.N, all);
     const uint32_t first = B.first = A.n_states;
-    std::vector<std::vector<Item>> done(t.N);                  // what completing a nonterminal leads to, worked out once
     auto complete = [&](const Item &it, uint32_t X) {
-        std::vector<Item> &to = done[X];
-        if (to.empty()) {
-            HostAutomaton::Work x;
-            x.insert(it);
-            A.close(x);
-            to = x.set;
-            to.push_back(it);                                  // (never empty again)
-        }
-        for (const Item &i : to) B.w.insert(i);
+        if (!B.spend(waits[X].arriving)) return false;
+        for (uint16_t p : waits[X].at) A.advanced(B.w, p + 1u, it.o);
+        return true;
     };
     std::vector<uint32_t> behind(t.T);
-    for (int k = 0; k < t.T; k++) {
-        B.w.set.clear();
-        for (uint16_t p : at[k]) A.advanced(B.w, p + 1u, all);
-        B.close(complete);
-        behind[k] = B.set();
-    }
-    size_t work = 0;
-    for (uint32_t s = first; s < A.n_states; s++)
-        for (int c = 0; c < t.n_cls; c++) {
-            if (A.st(s).trans[c] != HostAutomaton::NONE) continue;
-            if (A.n_states > first + MOST_STATES || (work += waiting.size() + 32) > MOST_WORK) continue;
-            B.step(s, c, complete);
-        }
+    for (int k = 0; k < t.T; k++) behind[k] = B.behind(at[k], [&](uint16_t) { return all; }, complete);
+    for (uint32_t s = first; s < A.n_states && B.left; s++)
+        for (int c = 0; c < t.n_cls && B.left; c++)
+            if (A.st(s).trans[c] == HostAutomaton::NONE && A.n_states <= first + MOST_STATES) B.step(s, c, complete);
     const uint32_t sink = A.n_states - first + 1;              // a finished sentence: nothing follows
     auto name = [&](uint32_t s) -> uint16_t { return s == HostAutomaton::DEAD ? FOLLOW_DEAD : s == HostAutomaton::SINK ? (uint16_t)sink : s == HostAutomaton::NONE ? FOLLOW_ANY : (uint16_t)(s - first + 1); };
     f.behind.assign(t.Q, FOLLOW_DEAD);
@@ -503,9 +548,9 @@ void build_follow(const Tables &t, Follow &f) {
 // there leads to COMP(Z, X) without the item that waits (its continuation is not known).  A rule that started before a string started in a set
 // that waits for something that its left-hand side L begins, Y, and COMP(L, X) is contained in COMP(Y, X).  So every real set contains what stands here (by the same
 // induction), and a string that lives here lives in every context.  A terminal may stand in several positions: a state is the list of the sets behind
-// each, all of which must live.  Beyond the budget nothing is sure.
+// each, all of which must live.  Of what the budget does not reach nothing is sure.
 void build_sure(const Tables &t, Follow &f) {
-    static const size_t MOST_STATES = 2048, MOST_WORK = (size_t)1 << 20;
+    static const size_t MOST_STATES = 2048;
     BehindTerminal B(t);
     HostAutomaton &A = B.A;
     for (int p = 0; p < t.P; p++) {
@@ -515,14 +560,15 @@ void build_sure(const Tables &t, Follow &f) {
         B.unknown[code & SYM_ID_MASK_NT] = A.add(&it, 1, 0, 0);
     }
     B.first = A.n_states;
-    auto complete = [&](const Item &it, uint32_t X) {
+    auto complete = [&](const Item &it, uint32_t X) {          // (every nonterminal with rules but the added start symbol is waited for: rules that nothing reaches are gone, and the start symbol's has no terminal)
         const size_t at = (size_t)(t.sym[A.st(it.o).items[0].p] & SYM_ID_MASK_NT) * t.N + X;
+        if (!B.spend(t.comp_off[at + 1] - t.comp_off[at])) return false;
         for (uint32_t k = t.comp_off[at]; k < t.comp_off[at + 1]; k++) {
             const uint16_t p = t.comp_list[k];
             if (p != COMP_ADVANCE_WAITING) B.w.insert(Item{p, (t.sym[p] >> SYM_KIND_SHIFT) == SYM_TERM ? t.term_start[t.sym[p] & SYM_ID_MASK] : (uint16_t)0, it.o});
         }
+        return true;
     };
-    size_t work = 0;
     std::map<std::vector<uint32_t>, uint32_t> names;
     std::vector<const std::vector<uint32_t> *> states{nullptr};   // 0: SURE_NOT
     std::vector<uint32_t> key;
@@ -538,23 +584,28 @@ void build_sure(const Tables &t, Follow &f) {
     };
     const std::vector<std::vector<uint16_t>> at = positions_of_terminals(t);
     f.sure_behind.assign(t.Q, SURE_NOT);
+    std::vector<uint16_t> one(1);
     for (int k = 0; k < t.T; k++) {
-        if (at[k].empty()) continue;
+        bool all = !at[k].empty();
         key.clear();
-        for (uint16_t p : at[k]) { key.push_back(B.behind(p, complete)); work += 32; }
+        for (size_t i = 0; all && i < at[k].size(); i++) {
+            one[0] = at[k][i];
+            key.push_back(B.behind(one, [&](uint16_t p) { return B.unknown[t.lhs_of[p]]; }, complete));
+            all = key.back() != HostAutomaton::NONE;
+        }
+        if (!all) continue;
         const uint16_t behind = name();
         for (int q = t.term_start[k]; q < (k + 1 < t.T ? (int)t.term_start[k + 1] : t.Q); q++) f.sure_behind[q] = behind;
     }
     f.sure_next.assign(t.n_cls, SURE_NOT);
     for (size_t s = 1; s < states.size(); s++)
         for (int c = 0; c < t.n_cls; c++) {
-            bool all = work < MOST_WORK;
+            bool all = true;
             key.clear();
             for (size_t i = 0; all && i < states[s]->size(); i++) {
                 const uint32_t from = (*states[s])[i];
-                work += from != HostAutomaton::SINK && A.st(from).trans[c] == HostAutomaton::NONE ? 32 : 1;
-                const uint32_t to = from == HostAutomaton::SINK ? HostAutomaton::DEAD : B.step(from, c, complete);
-                all = to != HostAutomaton::DEAD;
+                const uint32_t to = from == HostAutomaton::SINK || !B.spend(1) ? HostAutomaton::DEAD : B.step(from, c, complete);
+                all = to != HostAutomaton::DEAD && to != HostAutomaton::NONE;
                 key.push_back(to);
             }
             f.sure_next.push_back(all ? name() : (uint16_t)SURE_NOT);

@@ -103,17 +103,19 @@ struct Trie {
     int n_strings = 0;
     int chunk_ranks = 32;
     int Wr = 0;                       // words per row of a rank-ordered bitmap
-    std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]; empty in an engine with a device until somebody asks (host_token_mask_cache)
+    std::vector<uint32_t> ci_valid, ci_cd;   // [(Q + N) * Wr]; empty until somebody asks (host_token_mask_cache)
     std::vector<uint32_t> ci_alone, ci_ends;   // what the terminal decides by itself: strings it swallows whole; strings on which it dies behind an accepting state
 };
 // Context-independent token-mask cache (Section 4.3): per DFA state and per nonterminal, which
 // strings are decided by the terminal alone, or by what may follow it in any context, and which need the parser.
 void build_token_mask_cache(const Tables &t, const Follow &f, Trie &tr);
-// An engine with a device works its rows out there: the host diagnostics make the host's when they need them, one thread at a time.
-inline void host_token_mask_cache(const Tables &t, const Follow &f, Trie &tr) {
+// An engine with a device works its rows out there, one without has no mask calls: the host diagnostics make the host's when they need them, one thread at a time.
+inline void host_token_mask_cache(const Tables &t, Follow &f, Trie &tr) {
     static std::mutex mu;
     std::lock_guard<std::mutex> lk(mu);
-    if (tr.ci_valid.empty()) build_token_mask_cache(t, f, tr);
+    if (!tr.ci_valid.empty()) return;
+    if (f.behind.empty()) { build_follow(t, f); build_sure(t, f); }
+    build_token_mask_cache(t, f, tr);
 }
 void build_trie(const zf_vocab_desc *v, int chunk_ranks, const uint8_t *cls, Trie &t);
 

@@ -11,7 +11,7 @@ import pytest
 from workloads import grammars, configs, vocab as wvocab
 from workloads.grammar import Grammar, Lit, Rx
 from workloads.rng import SplitMix64, stream
-from tests.helpers import OracleRun, popcount, load_trajectory
+from tests.helpers import OracleRun, popcount, load_trajectory, pick_set_bit
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -450,6 +450,62 @@ def test_what_follows_a_terminal_decides_no_token_that_a_context_takes(words, le
         got, stats = st.debug_host_mask_cached()
         assert np.array_equal(got, want), prefix
         assert np.array_equal(st.debug_host_mask_automaton()[0], want), prefix
+
+
+def _ladder_grammar(n):
+    g = Grammar("ladder").alts("P", ["S", "P"], ["S"]).alts("S", *[[b"kw%d " % k, "E0", b";"] for k in range(3 * n)], [b"{", "P", b"}"])
+    for k in range(n):
+        g.alts("E%d" % k, ["E%d" % k, b"+%d" % k, "E%d" % (k + 1)], ["E%d" % (k + 1)])
+    return g.alts("E%d" % n, [b"(", "E0", b")"], [Rx(rb"[a-z]+")], [Rx(rb"[0-9]+")]).set_start("P")
+
+
+def _objects_grammar(n):
+    g = Grammar("objects")
+    for k in range(n):
+        g.alts("V", ["O%d" % k]).alts("O%d" % k, [b"{t%d:" % k, "V", b",n:", Rx(rb"[0-9]+"), "R%d" % k, b"}"]).alts("R%d" % k, [b",x%d:" % k, "V"], [])
+    return g.alts("V", [Rx(rb"[a-z]+")]).set_start("V")
+
+
+def _mutual_grammar(n):
+    g = Grammar("mutual")
+    for k in range(n):
+        g.alts("N%d" % k, ["N%d" % ((k + 1) % n), b"a%d" % k], ["N%d" % ((k * 7 + 3) % n), b"b", "N%d" % ((k * 5 + 1) % n)], [b"(", "N%d" % ((k + 2) % n), b")"], [b"x%d" % k])
+    return g.set_start("N0")
+
+
+def _nullable_grammar(n):
+    g = Grammar("nullable").alts("S", ["A%d" % k for k in range(n)] + [b";", "S"], [b"."])
+    for k in range(n):
+        g.alts("A%d" % k, [b"[", "S", b"]"] if k % 3 == 0 else [b"w%d" % k, "A%d" % (k * 5 % n)], [])
+    return g.set_start("S")
+
+
+@pytest.mark.parametrize("gram,n,s", [(_ladder_grammar, 2, 1), (_ladder_grammar, 30, 1), (_objects_grammar, 4, 1), (_objects_grammar, 150, 1), (_mutual_grammar, 6, 1), (_mutual_grammar, 400, 2), (_nullable_grammar, 6, 1), (_nullable_grammar, 120, 1)])
+def test_what_follows_a_terminal_is_bounded(gram, n, s, zf, oracle_lib):
+    """Grammars within what working out what follows a terminal may cost, and many times beyond it (what is not worked out then stays open): masks with the token-mask cache
+    are the oracle's, over pairs and pieces of the grammar's words, and take a moment to be ready for (four hundred nonterminals that begin one another took ten
+    seconds when steps were counted whatever they cost)."""
+    import time
+    g = gram(n)
+    lits = [t.data for t in g.terminals if isinstance(t, Lit)]
+    words = lits[:6] + lits[-6:] + [b"z", b"7"]
+    toks = [b"", b"zz7", b"7;"] + words + [a + b for a in words for b in words] + [a[-1:] + b + c[:1] for a in words for b in words for c in words[::3]]
+    off, data = wvocab.vocab_csr(toks)
+    t0 = time.perf_counter()
+    eng = zf.Engine(g, toks, device=-1)
+    eng.new_state().debug_host_mask_cached()
+    assert time.perf_counter() - t0 < 3.0
+    orc, rng = oracle_lib.Oracle(g), stream(n, "bounded")
+    for _ in range(s):
+        so, st = orc.new_state(), eng.new_state()
+        for _ in range(5):
+            want = so.mask(off, data, 8)
+            assert np.array_equal(st.debug_host_mask_cached()[0], want)
+            if not want.any():
+                break
+            t = pick_set_bit(want, rng.below(popcount(want)))
+            assert so.feed_bytes(toks[t])
+            st.advance(t)
 
 
 def _nested_grammar():
