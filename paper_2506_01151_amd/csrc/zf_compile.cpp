@@ -616,12 +616,14 @@ void build_sure(const Tables &t, Follow &f) {
 enum class EndsInside { NO, PERHAPS, SURELY };
 static EndsInside ends_inside(const Tables &t, const Follow &f, uint32_t q, const uint8_t *bytes, size_t n) {
     EndsInside answer = EndsInside::NO;
+    size_t walked = 0;
     for (size_t k = 0; k + 1 < n; k++) {
         q = t.delta[(size_t)q * t.n_cls + t.cls[bytes[k]]];
         if (q == DFA_DEAD) break;
         if (!(t.qflags[q] & QF_ACCEPT)) continue;
         uint32_t s = f.behind[q], sure = f.sure_behind[q];
-        for (size_t j = k + 1; j < n && s != FOLLOW_DEAD; j++) {
+        for (size_t j = k + 1; j < n && s != FOLLOW_DEAD; j++, walked++) {
+            if (walked == FOLLOW_BYTES_MAX) return EndsInside::PERHAPS;
             s = f.next[(size_t)s * t.n_cls + t.cls[bytes[j]]];
             sure = f.sure_next[(size_t)sure * t.n_cls + t.cls[bytes[j]]];
         }

@@ -18,6 +18,9 @@ enum : uint16_t {
     FOLLOW_ANY = 0, FOLLOW_DEAD = 0xFFFF,   // states of Follow: takes every string; takes none
     SURE_NOT = 0,                           // of its second automaton: some context may not take it
 };
+// A terminal may end behind every byte of a string: what follows each end is walked for so many bytes in all, and a string that takes more is left to the
+// parser.  (All ends of a string of 45 bytes.  Without the line, strings of 253 bytes a-a-a- under words that may hold dashes, and dashes between them, took the host 30 us each and row, 2 so.)
+static const uint32_t FOLLOW_BYTES_MAX = 1024;
 // Item word used on the device: bits 0-13 dotted position, bit 14 = completed ("lhs complete since
 // origin"), bit 15 = the postdot symbol is a terminal and bits 16-31 hold its DFA state; for an item
 // that waits for a nonterminal Y: bit 16 = Y is nullable, bits 17-29 = Y.

@@ -48,18 +48,20 @@ __global__ __launch_bounds__(VOCAB_BLOCK) void vocab_rows_kernel(VocabRows a, co
             }
             valid = len > 0 && k == len;
             if (k < len && accepted) {                       // it dies behind an accepting state: where it may end, does every context take the rest, or does any?
+                uint32_t left = FOLLOW_BYTES_MAX;
                 s = q;
-                for (k = 0; !valid && k + 1u < len; k++) {
+                for (k = 0; !valid && left && k + 1u < len; k++) {
                     s = a.delta[(size_t)s * a.n_cls + class_at(k)];
                     if (s == DFA_DEAD) break;
                     if (!(a.qflags[s] & QF_ACCEPT)) continue;
                     uint32_t f = a.behind[s], g = a.sure_behind[s];
-                    for (uint32_t j = k + 1u; f != FOLLOW_DEAD && j < len; j++) {
+                    uint32_t j = k + 1u;
+                    for (; left && f != FOLLOW_DEAD && j < len; j++, left--) {
                         f = a.follow[(size_t)f * a.n_cls + class_at(j)];
                         g = a.sure_next[(size_t)g * a.n_cls + class_at(j)];
                     }
-                    undecided |= f != FOLLOW_DEAD;
-                    valid = f != FOLLOW_DEAD && g != SURE_NOT;
+                    undecided |= f != FOLLOW_DEAD || !left;   // (the bytes that are walked for may end with a walk: the next end is then not known to lead nowhere)
+                    valid = f != FOLLOW_DEAD && j == len && g != SURE_NOT;
                 }
                 undecided = undecided && !valid;
             }

@@ -1051,6 +1051,27 @@ def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cud
             assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
 
 
+@pytest.mark.parametrize("kw", [{}, {"walk_mode": 0}, {"pruning": False}], ids=["store", "per_block", "unpruned"])
+def test_strings_that_a_terminal_may_end_in_everywhere(kw, torch_cuda, oracle_lib):
+    """Cache rows made on the device: what follows every end that a terminal may have in a string is walked up to a number of bytes, with strings shorter and longer than that takes."""
+    import paper_2506_01151_amd as zf
+    from tests.test_host_library import dashes
+    g, toks = dashes(2, [(b"a-" * k)[:2 * k - 1] + t + b"b" for k in (1, 2, 20, 21, 22, 23, 24, 30) for t in (b";", b"-", b")-", b"-;", b"(", b")")])
+    orc, eng = oracle_lib.Oracle(g), zf.Engine(g, toks, device=0, state_cache_entries=-1, **kw)
+    off, data = wvocab.vocab_csr(toks)
+    want, rows = [], []
+    for prefix in (b"", b"a", b"a-", b"a-a", b"(", b"(a", b"a;"):
+        so = orc.new_state()
+        rows.append(eng.new_state())
+        if prefix:
+            assert so.feed_bytes(prefix)
+            rows[-1].advance_bytes(prefix)
+        want.append(so.mask(off, data, 8))
+    d_mask = torch_cuda.full((len(rows), eng.W), 0x5A5A5A5A, dtype=torch_cuda.int32, device="cuda")
+    zf.compute_mask(eng, rows, d_mask)
+    assert np.array_equal(d_mask.cpu().numpy().view(np.uint32), np.stack(want))
+
+
 @pytest.mark.parametrize("depth", [40, 70, 120])
 @pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
 def test_per_block_automaton_steps_that_are_handed_over(depth, pruning, torch_cuda, oracle_lib):

@@ -536,6 +536,35 @@ def test_what_every_context_takes_behind_a_terminal(gram, alphabet, length, zf, 
             todo += [prefix + toks[ids[0]], prefix + toks[ids[-1]]]
 
 
+def dashes(words, tails):
+    """Words that may hold dashes, lists of words with dashes between them and lists without: a word may end at every letter."""
+    g = Grammar("dashes").alts("S", ["W", b";", "S"], [b"(", "T", b")"], ["W"]).alts("T", ["W", b"-", "T"], ["W"])
+    for k in range(words):
+        g.rule("W", [Rx(b"[a-%c]+(-[a-z]+)*" % (101 + k))])
+    return g.set_start("S"), [b"", b"a", b"a-", b"-a"] + tails
+
+
+def test_strings_that_a_terminal_may_end_in_everywhere(zf, oracle_lib):
+    """What follows every end that a terminal may have in a string is walked up to a number of bytes: masks equal the oracle's with strings shorter and longer than that takes,
+    and the cache rows of strings of up to 255 bytes take a moment to make (ten seconds when every end was walked to the string's end)."""
+    import time
+    g, toks = dashes(16, [(b"a-" * 125)[k % 2:] + b"%04d" % k for k in range(4000)])
+    t0 = time.perf_counter()
+    st = zf.Engine(g, toks, device=-1).new_state()
+    st.advance_bytes(b"(a)")                                  # nothing follows: the rows are made and no string is walked
+    assert not st.debug_host_mask_cached()[0].any()
+    assert time.perf_counter() - t0 < 4.0
+    g, toks = dashes(2, [(b"a-" * k)[:2 * k - 1] + t + b"b" for k in (1, 2, 20, 21, 22, 23, 24, 30) for t in (b";", b"-", b")-", b"-;", b"(", b")")])
+    orc, eng = oracle_lib.Oracle(g), zf.Engine(g, toks, device=-1)
+    off, data = wvocab.vocab_csr(toks)
+    for prefix in (b"", b"a", b"a-", b"a-a", b"(", b"(a", b"a;"):
+        so, st = orc.new_state(), eng.new_state()
+        if prefix:
+            assert so.feed_bytes(prefix)
+            st.advance_bytes(prefix)
+        assert np.array_equal(st.debug_host_mask_cached()[0], so.mask(off, data, 8)), prefix
+
+
 @pytest.mark.parametrize("size,first", [(1, None), (40, None), (40, b"1"), (8191, None), (8200, None), (9000, b"("), (9000, b"")])
 def test_trie_made_in_pieces(size, first, zf, oracle_lib):
     """The vocabulary's trie is made a first byte at a time, by one thread or by several (8,192 strings and more): vocabularies of any first byte, of one (all in
