@@ -1626,7 +1626,7 @@ struct StoreCall {                 // one call's working memory, kept per thread
 // many tokens their token-mask cache rows leave undecided, which was counted once per list of cache rows.  The grid is never
 // larger than what the chip holds at once: a block that had to wait for a place would start from nothing (LDS cache, the
 // group's state) when the others are nearly done, which costs more than a few more passes of the wavefronts that are there.
-static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget, int logit_bytes, bool rows_apart) {
+static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget, int logit_bytes, int member_words) {
     const int n = (int)g.size();
     static thread_local std::vector<double> inv_cost;
     static thread_local std::vector<int> segs, passes;
@@ -1643,7 +1643,7 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
         if (logit_bytes) sw = std::min(sw, std::max(1, STORE_AHEAD_BYTES / (32 * logit_bytes * g[r].n)));
         // nor more words than its wavefront stores to all its rows in a few stores (256 rows x 128,256 in some 20 states, 8 waiting calls: 241 -> 213 us; 64 rows of
         // the query language, 16 calls: 274 -> 258; with half as many words 216 and 254)
-        if (!rows_apart) sw = std::min(sw, std::max(1, STORE_MEMBER_WORDS / g[r].n));
+        if (member_words) sw = std::min(sw, std::max(1, member_words / g[r].n));
         else if (g[r].alone) sw = W;                      // (nothing to do: a block that reports)
         segs[r] = std::max(1, (W + sw - 1) / sw);
         g[r].seg_w = sw;
@@ -1760,7 +1760,7 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
         g.alone = k.units && g.decided && !g.keep && k.dtype == 2;
     }
     const int budget = std::max(ng, look_blocks_per_cu() * std::max(1, d->cus));
-    k.mask_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, 0, k.units != 0);
+    k.mask_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, 0, k.units ? 0 : LOOK_MEMBER_WORDS);
     // ---- the records ----
     {
         uint8_t *h = (uint8_t *)d->h_stage[slot];
@@ -2085,7 +2085,7 @@ static int enqueue_store_impl(zf_engine *e, zf_state *const *states, int32_t bat
         }
     }
     const int budget = std::max(ng, std::min(STORE_BLOCKS_PER_CU, store_blocks_per_cu(d->tab, d->mode, scratch)) * std::max(1, d->cus));
-    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes, false);
+    a.n_blocks = (uint32_t)store_launch_shape(c.g, d->tab.W, e->V, budget, logit_bytes, 0);
     // ---- the records ----
     {
         uint8_t *h = (uint8_t *)d->h_stage[slot];

@@ -61,7 +61,7 @@ static const int STORE_BLOCK = STORE_WAVES * 64;
 static const int STORE_LDS_MAX = 159 * 1024;   // dynamic LDS a block of that kernel may ask for (the hand-over of the call's status has a static word of its own)
 static const int STORE_SEG_WORDS_MAX = 64;     // mask words (of 32 tokens) a wavefront merges and checks per pass: 1 to 64, chosen per group so that a pass holds about one batch of undecided tokens
 static const int STORE_AHEAD_BYTES = 2 * 64 * 16;  // of the logits a wavefront requests one pass ahead (two pieces per lane)
-static const int STORE_MEMBER_WORDS = 1024;    // mask words a wavefront stores per pass, all members of the group together, at most
+static const int LOOK_MEMBER_WORDS = 1024;     // mask words a wavefront of mask_look_kernel stores per pass, all members of the group together, at most
 static const int STORE_WARM_ROWS = 32;         // rows of the transition table (states one byte from a row's current state) a block reads ahead into its LDS cache
 static const int STORE_LC_BITS = ZF_STORE_LC_BITS;       // log2 of the entries of a block's LDS cache of table entries (8 bytes each)
 #ifndef ZF_STORE_BLOCKS_PER_CU
