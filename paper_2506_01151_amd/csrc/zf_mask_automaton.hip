@@ -332,6 +332,7 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
         if (lane == 0) A.some[wave] = nz != 0;
         if (tid == 0) { A.ctl[2] = 0; A.ctl[3] = 0; A.ctl[6] = 0; }
         __syncthreads();                                     // also: tables, chart and automaton set-up are in place
+        if (j0 && tid == 0) { A.ctl[4] = 0; A.ctl[5] = 0; }  // the help queue starts over (its places were cleared behind the pass before)
         // a pass without an undecided string is over (64 rows x 152,064 of the expression grammar: with that, and the cache rows asked for early, launches of 13.0 us take 11.2)
         if (__ballot(A.some[lane % WAVES] != 0) == 0) {
             if (w < Wr) a.rank_mask[(size_t)row * Wr + w] = v;
@@ -447,6 +448,8 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
                         rc = (uint32_t)__builtin_amdgcn_readlane((int)c, first);
                     }
                 }
+                // All batches finished: nobody waits for what is left in the queue, which was asked for ahead.
+                if (!batch && (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(&A.ctl[6])) >= n_pairs) break;
                 int q = AUT_HQ_EMPTY;
                 if (!have && !progress) {                    // nothing of its own to compute: lend a hand
                     q = aut_help_take(A, lane, rs, rc);
@@ -457,7 +460,6 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
                     steps++;
                     if (!batch) spins = 0;
                 } else if (!progress && q == AUT_HQ_EMPTY) { // everything this wavefront waits for is being computed by others
-                    if (!batch && (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(&A.ctl[6])) >= n_pairs) break;   // all batches finished, nothing queued
                     __builtin_amdgcn_s_sleep(16);
                     if (++spins > (uint32_t)AUT_SPIN_LIMIT) {   // bounded wait: hand the strings to the fallback
                         if (!batch) break;
@@ -489,6 +491,12 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
         }
         __syncthreads();
         { const uint32_t w = word_of(tid); if (w < Wr) a.rank_mask[(size_t)row * Wr + w] = vslice[tid]; }
+        if (blockIdx.x + (j0 + groups_per_pass) * gridDim.x < n_groups)   // another pass: transitions that were left in the queue are anybody's again
+            for (uint32_t k = tid, taken = A.ctl[5]; k < (uint32_t)AUT_HELP_QUEUE; k += BLOCK) {
+                const uint32_t e = A.hq[k];
+                if ((e & HQ_VALID) && k >= taken) A.trans[((e & ~HQ_VALID) >> 8) * A.ncls + (e & 0xFFu)] = AT_NONE;
+                A.hq[k] = 0;
+            }
     }
     if (lane == 0 && steps) atomicAdd(&A.ctl[8], steps);
     __syncthreads();

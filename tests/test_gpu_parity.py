@@ -1051,6 +1051,29 @@ def test_per_block_automaton_terminals_that_go_on(grammar, pruning, B, torch_cud
             assert np.array_equal(got[k], want[b % len(prefixes)]), (prefixes[b % len(prefixes)], len(at))
 
 
+@pytest.mark.parametrize("words", [2, 1100], ids=["one pass", "passes"])
+def test_per_block_automaton_drops_what_nobody_waits_for(words, torch_cuda, oracle_lib):
+    """Sixty strings wait for the byte that they begin with, behind which none goes on: steps that were asked for ahead meanwhile, one for the second byte of each, are dropped
+    when the strings are decided (with them a block took 61 steps).  In passes, transitions that were dropped are there for the strings of a later one."""
+    import paper_2506_01151_amd as zf
+    torch = torch_cuda
+    seconds = [bytes([c]) for c in range(140, 200)]
+    g = grammars.Grammar("ahead").alts("S", [b"a", b"Z"], *[[c, b"Y"] for c in seconds]).set_start("S")
+    toks = [b"a" + c for c in seconds] + [b""] * 4
+    if words > 2:                                            # strings of other ranks: the last of them go the way of the steps that were dropped
+        toks += [b"a" + bytes([100 + k % 30, 100 + k // 30 % 30, 100 + k // 900]) for k in range(32 * (words - 4))] + [c + e for c in seconds for e in (b"Y", b"Z")]
+    off, data = wvocab.vocab_csr(toks)
+    eng = zf.Engine(g, toks, device=0, walk_mode=0, token_mask_cache=False, state_cache_entries=-1)
+    B = 1 if words == 2 else 300                              # 300 rows: a block each, of 512 words a pass
+    want = oracle_lib.Oracle(g).new_state().mask(off, data, 8)
+    d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    rows = [eng.new_state() for _ in range(B)]
+    for _ in range(3):
+        zf.compute_mask(eng, rows, d_mask)
+        assert (d_mask.cpu().numpy().view(np.uint32) == want).all()
+        assert 1 <= eng.mask_report().parser_steps < (50 if B == 1 else 250 * B)
+
+
 @pytest.mark.parametrize("kw", [{}, {"walk_mode": 0}, {"pruning": False}], ids=["store", "per_block", "unpruned"])
 def test_strings_that_a_terminal_may_end_in_everywhere(kw, torch_cuda, oracle_lib):
     """Cache rows made on the device: what follows every end that a terminal may have in a string is walked up to a number of bytes, with strings shorter and longer than that takes."""
