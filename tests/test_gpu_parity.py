@@ -172,12 +172,13 @@ CFG5_CHECK_STEPS = 12      # steps of the trajectory at which masks are compared
 CFG5_CHECK_ROWS = 6        # ... on this many seeded rows each: the oracle keeps every Earley set, a mask at step 600 costs it about a second
 
 
-@pytest.mark.parametrize("mode", list(MODES))
-@pytest.mark.parametrize("pruning", [True, False], ids=["pruned", "unpruned"])
-def test_config5_full_batch_pruning_on_and_off(pruning, mode, torch_cuda, oracle_lib):
+@pytest.mark.parametrize("pruning,mode,token_cache", [(p, m, c) for c in (True, False) for p in (True, False) for m in MODES],
+                         ids=[f"{p}-{m}{c}" for c in ("", "-parser-only") for p in ("pruned", "unpruned") for m in MODES])
+def test_config5_full_batch_pruning_on_and_off(pruning, mode, token_cache, torch_cuda, oracle_lib):
     """Configuration 5 at its stated batch and vocabulary (64 rows, V = 152,064) along the oracle-sampled trajectory, as far
     as the file goes: one compute_mask call covers all 64 rows (the launch shape the benchmark times); a seeded, reported
-    subsample of (step, row) pairs is compared bit for bit with the oracle, with ZapFormat pruning on and off, every mask kernel (with pruning off the persistent automaton is not used: the per-block automaton runs in its place)."""
+    subsample of (step, row) pairs is compared bit for bit with the oracle, with ZapFormat pruning on and off, every mask kernel (with pruning off the persistent automaton is not used: calls that
+    the token-mask cache decides, as it does every one of this configuration, go through the look-ups' kernel, others through the per-block automaton), with every token left to the parser as well."""
     import paper_2506_01151_amd as zf
     torch = torch_cuda
     cfg = configs.CONFIGS[5]
@@ -188,7 +189,7 @@ def test_config5_full_batch_pruning_on_and_off(pruning, mode, torch_cuda, oracle
     steps = len(traj)
     assert steps >= 256
     g = cfg.grammar()
-    eng = zf.Engine(g, toks, device=0, pruning=pruning, state_cache_entries=-1, walk_mode=MODES[mode])
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, state_cache_entries=-1, walk_mode=MODES[mode], token_mask_cache=token_cache)
     orc = oracle_lib.Oracle(g)
     so = [orc.new_state() for _ in range(rows)]
     ss = zf.StateBatch([eng.new_state() for _ in range(rows)])
@@ -989,15 +990,21 @@ def test_rows_of_large_groups_without_logits(n, torch_cuda):
 @pytest.mark.parametrize("V,B", [(16384, 300), (16385, 300), (33001, 300), (4096, 1), (4097, 3)])
 def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
     """The per-block automaton where a row's share of a block is one word less, and more, than a pass takes (512 words; 300 rows have a block
-    each), and where a row has hardly a block's worth of words: an ambiguous grammar with pruning off, against the oracle."""
+    each), and where a row has hardly a block's worth of words: an ambiguous grammar with pruning off, against the oracle.  Every ninth token ends a group, which
+    only the parser knows of, so that strings of every pass are left to it."""
     import paper_2506_01151_amd as zf
     torch = torch_cuda
     cfg = configs.CONFIGS[5]
     g, toks = cfg.grammar(), cfg.vocab(V)
+    for k in range(0, V, 9):
+        n, word = k // 9, b""
+        for _ in range(4):
+            word, n = word + bytes([97 + n % 26]), n // 26
+        toks[k] = [word, b"%d" % k][k % 2] + [b")", b")+1", b"))"][k % 3]
     off, data = wvocab.vocab_csr(toks)
     orc = oracle_lib.Oracle(g)
-    eng = zf.Engine(g, toks, device=0, pruning=False, state_cache_entries=-1)
-    prefixes = [b"", b"a+b*c", b"((x", b"7*(a+b)"][:B]
+    eng = zf.Engine(g, toks, device=0, pruning=False, walk_mode=0, state_cache_entries=-1)
+    prefixes = [b"(a", b"a+b*c", b"((x", b"7*(a+b)"][:B]
     want, rows = [], []
     for p in prefixes:
         so = orc.new_state()
@@ -1008,6 +1015,8 @@ def test_per_block_automaton_passes(V, B, torch_cuda, oracle_lib):
         rows[-1].advance_bytes(prefixes[b % len(prefixes)])
     d_mask = torch.full((B, eng.W), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
     zf.compute_mask(eng, rows, d_mask)
+    report = eng.mask_report()
+    assert report.walk_chunks > B * V // 30 and report.parser_steps > 0   # strings left to the parser; steps of the per-block automaton
     got = d_mask.cpu().numpy().view(np.uint32)
     for b in range(B):
         assert np.array_equal(got[b], want[b % len(prefixes)]), b
@@ -1369,11 +1378,13 @@ def test_token_mask_cache_made_on_the_device(V, walk_mode, torch_cuda, oracle_li
                 assert eng.mask_report().walk_chunks == stats["undecided"], (prefix, call)   # no token twice: strings and tokens count the same
 
 
+@pytest.mark.parametrize("token_cache", [True, False], ids=["", "parser-only"])
 @pytest.mark.parametrize("pruning", [False, True])
 @pytest.mark.parametrize("most", [2, 4, 5, 6, 7, 8, 12, 20, 40])
-def test_byte_step_of_growing_sums(most, pruning, torch_cuda, oracle_lib):
+def test_byte_step_of_growing_sums(most, pruning, token_cache, torch_cuda, oracle_lib):
     """The per-block automaton's byte steps on sums of up to `most` operators of the ambiguous grammar, every operand another origin: sets from a few items, through the step
-    for a dozen, to the wide one; origin sets and table entries to deal from fewer than the lanes of a wavefront to several times as many."""
+    for a dozen, to the wide one; origin sets and table entries to deal from fewer than the lanes of a wavefront to several times as many.  With the token-mask cache
+    the strings that end a group are left to the parser, without it all."""
     import paper_2506_01151_amd as zf
     torch = torch_cuda
     cfg = configs.CONFIGS[5]
@@ -1381,7 +1392,7 @@ def test_byte_step_of_growing_sums(most, pruning, torch_cuda, oracle_lib):
     toks = list(dict.fromkeys(cfg.vocab(700) + [b"+b" * n for n in (1, 2, 5, 9)] + [b"*(" * 4, b")" * 3, b"+(a*b)" * 2, b"a" + b"+a" * 12]))
     off, data = wvocab.vocab_csr(toks)
     orc = oracle_lib.Oracle(g)
-    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, state_cache_entries=-1)
+    eng = zf.Engine(g, toks, device=0, pruning=pruning, walk_mode=0, token_mask_cache=token_cache, state_cache_entries=-1)
     so, ss = [], []
     for k in range(most + 1):
         a, b = orc.new_state(), eng.new_state()
@@ -1392,6 +1403,7 @@ def test_byte_step_of_growing_sums(most, pruning, torch_cuda, oracle_lib):
         ss.append(b)
     d_mask = torch.full((len(ss), eng.W), -1, dtype=torch.int32, device="cuda")
     zf.compute_mask(eng, ss, d_mask)
+    assert eng.mask_report().parser_steps > 0
     got = d_mask.cpu().numpy().view(np.uint32)
     for k, a in enumerate(so):
         assert (got[k] == a.mask(off, data, 4)).all(), k
