@@ -46,7 +46,8 @@ def kernel_sources_digest():
     import hashlib
     h = hashlib.sha256()
     for name in ("zf_kernels.hip", "zf_mask_store.hip", "zf_mask_look.hip", "zf_aut_step.h", "zf_mask_automaton.hip", "zf_mask_walk.hip", "zf_kernel_common.h", "zf_launch.h", "zf_device.h",
-                 "zf_api.cpp"):                                # the host chooses the launch shape, which decides what the XCDs' L2s share
+                 "zf_api.cpp",                                 # the host chooses the launch shape, which decides what the XCDs' L2s share
+                 "zf_compile.cpp", "zf_vocab.hip", "zf_host_automaton.h"):   # and how many strings the cache rows leave to a launch
         with open(os.path.join(ROOT, "paper_2506_01151_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
