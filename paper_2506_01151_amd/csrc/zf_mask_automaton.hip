@@ -428,9 +428,10 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
                     if (live && t == AT_NONE) old = atomicCAS(&A.trans[s * A.ncls + c], (uint32_t)AT_NONE, (uint32_t)AT_BUSY);
                     const unsigned long long won = __ballot(live && old == AT_NONE);
                     // What the strings that wait here need if the class leaves them in the state that they are in (a terminal that goes on: digits, letters) is left
-                    // in the queue as well, for wavefronts that have nothing to do, while half of the room for states is left (64 rows x 152,064 of the expression grammar, 8 steps,
-                    // 589 -> 579 us; with what the string's own first items say, below, 568).  (The row's current set ahead of the first strings: no gain.)
-                    {
+                    // in the queue as well, for wavefronts that have nothing to do, while half of the room for states is left (64 rows x 152,064 of the expression grammar
+                    // with every string left to the kernel, 87.1 us a step without, 84.2 so).  Not with the narrow step, which takes 2 us: what nobody comes to need holds
+                    // those back that do, and takes the room of others' states (256 rows x 40,037 of JSON without pruning 237 us a step so, 172 without; 16 x 32,000 66.9 and 65.1).
+                    if (STEP != AUT_STEP_NARROW) {
                         const uint32_t w0 = c16.w[0], c1 = (w0 >> 8) & 0xFFu, c2 = (w0 >> 16) & 0xFFu, c3 = w0 >> 24;
                         const uint32_t cx = c1 != c ? c1 : c2 != c ? c2 : c3, need = c1 != c ? 2u : c2 != c ? 3u : 4u;
                         uint32_t got = AT_BUSY;

@@ -1067,7 +1067,7 @@ def test_per_block_automaton_drops_what_nobody_waits_for(words, torch_cuda, orac
     import paper_2506_01151_amd as zf
     torch = torch_cuda
     seconds = [bytes([c]) for c in range(140, 200)]
-    g = grammars.Grammar("ahead").alts("S", [b"a", b"Z"], *[[c, b"Y"] for c in seconds]).set_start("S")
+    g = grammars.Grammar("ahead").alts("S", [b"a", b"Z"], *[[c, b"Y"] for c in seconds], ["S", b"+", "S"]).set_start("S")   # (a grammar of operators: the step for a dozen items)
     toks = [b"a" + c for c in seconds] + [b""] * 4
     if words > 2:                                            # strings of other ranks: the last of them go the way of the steps that were dropped
         toks += [b"a" + bytes([100 + k % 30, 100 + k // 30 % 30, 100 + k // 900]) for k in range(32 * (words - 4))] + [c + e for c in seconds for e in (b"Y", b"Z")]
