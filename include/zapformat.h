@@ -187,7 +187,8 @@ int zf_compute_mask(zf_engine *e, zf_state *const *states /* host array */, int3
  *   zf_mask_wait returns once the status of the calls in flight is final (a block of their last kernel writes
  * it to pinned host memory, which the call polls; when the fallback pass had work, whose waits can fail, it is
  * the block that finishes last; bounded: after two seconds the stream is synchronised instead).  A call of look-ups only -- every
- * transition it can meet is in the persistent automaton for certain -- is not expected to fail, and zf_mask_wait lets go of it: it
+ * transition it can meet is in the persistent automaton for certain, or, with pruning off and no state cache, the token-mask cache decides every
+ * token of every row -- is not expected to fail, and zf_mask_wait lets go of it: it
  * returns without waiting for it (at most 4 such calls are ahead of the host; the next one waits for the oldest).  Should one fail all the same, a later
  * zf_mask_wait or waiting call returns ZF_ERR_OVERFLOW for it, and zf_last_error says so: the mask of the call that was let go of is not valid, that of
  * the call that reports it is.  zf_mask_wait with no call in flight waits for those that were let go of and
@@ -205,8 +206,8 @@ int zf_mask_wait(zf_engine *e, void *hip_stream);
  * for that pair.  With the persistent automaton as the mask kernel the same kernel masks the logits, provided the pointers are
  * multiples of a logit: a call of look-ups only with wavefronts of their own, which read them while others work the masks out; a call that
  * meets states for the first time up to 16 MB of logit traffic (a wavefront masks the logits of the tokens whose mask words it has just
- * written).  In every other case the call enqueues the two kernels one after the other.  d_out may
- * equal d_logits; dtype 0 = fp32, 1 = bf16. */
+ * written).  So does the closing kernel of the per-block automaton, but for a state cache's rows.  In every other case the call
+ * enqueues the two kernels one after the other.  d_out may equal d_logits; dtype 0 = fp32, 1 = bf16. */
 int zf_compute_mask_apply_async(zf_engine *e, zf_state *const *states /* host array */, int32_t batch, uint32_t *d_mask,
                                 const void *d_logits, void *d_out, int32_t dtype, int64_t row_stride_elems, void *hip_stream);
 /* zf_compute_mask for callers that cannot allocate device memory: tight serving loops, harnesses

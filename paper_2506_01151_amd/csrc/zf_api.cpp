@@ -1641,8 +1641,9 @@ static int store_launch_shape(std::vector<RowGroup> &g, int W, int V, int budget
         // where the logits are masked too: no more words than the logits a wavefront requests ahead for all rows of the group
         // (two pieces of 16 bytes per lane), so that nothing is waited for at the end while there are wavefronts to spare
         if (logit_bytes) sw = std::min(sw, std::max(1, STORE_AHEAD_BYTES / (32 * logit_bytes * g[r].n)));
-        // nor more words than its wavefront stores to all its rows in a few stores (256 rows x 128,256 in some 20 states, 8 waiting calls: 241 -> 213 us; 64 rows of
-        // the query language, 16 calls: 274 -> 258; with half as many words 216 and 254)
+        // nor, in a call of look-ups, more words than its wavefront stores to all its rows in a few stores (256 rows x 128,256 in some 20 states, 8 waiting calls: 241 -> 213 us;
+        // 64 rows of the query language, 16 calls: 274 -> 258; with half as many words 216 and 254).  First visits, all of whose rows stand in a state or two, have no
+        // wavefronts to spare for that: 256 x 128,256 of the schema 56.5 us a step, 65 so.
         if (member_words) sw = std::min(sw, std::max(1, member_words / g[r].n));
         else if (g[r].alone) sw = W;                      // (nothing to do: a block that reports)
         segs[r] = std::max(1, (W + sw - 1) / sw);
@@ -1756,7 +1757,8 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
     for (RowGroup &g : c.g) {
         g.decided = use_cache && !g.pooled && g.undecided == 0 && g.n_ent <= (uint32_t)STORE_GROUP_ENT;
         // Where the wavefronts with logits make a group's mask they may as well store it, and no others work it out: 16 steps of 64 x 128,256 bf16 of the query language 161 -> 150 us
-        // (from four rows a group on 160), 8 of 130 x 40,037 103.1 -> 102.3.  Not with fp32, whose units hold half as many words: 16 of 64 x 152,064 288 -> 294.
+        // (from four rows a group on 160), 8 of 130 x 40,037 103.1 -> 102.3.  Not with fp32, whose units hold half as many words: 16 of 64 x 152,064 288 -> 294, a step of 256 x 128,256
+        // of the expression grammar 52.1 -> 53.7, of the query language 43.3 -> 43.0; 16 rows and 1,000 x 32,000 the same either way.
         g.alone = k.units && g.decided && !g.keep && k.dtype == 2;
     }
     const int budget = std::max(ng, look_blocks_per_cu() * std::max(1, d->cus));
@@ -1841,7 +1843,8 @@ static int enqueue_look(zf_engine *e, StoreCall &c, zf_state *const *states, int
 
 // An engine without a persistent automaton (pruning off): a call all of whose rows select token-mask cache rows that leave no token to the parser is one of look-ups
 // too, without any to make.  Rows with the same list are a group.  STORE_NO_ROOM: some row leaves something, or does not fit a record; nothing was enqueued.
-// (64 rows x 152,064 of the expression grammar, 8 steps: 262 us through the per-block automaton and its closing kernel, 144 so.  Calls with a state cache or
+// (64 rows x 152,064 of the expression grammar, 8 steps: 262 us through the per-block automaton and its closing kernel, 144 so.  A call of which the last row alone is
+// undecided is enqueued as fast as without the look: 6.6 us of 16 rows, 17.8 of 256.  Calls with a state cache or
 // without allocations keep to the per-block automaton: it is what knows the one, and fits the static array.)
 static int enqueue_decided(zf_engine *e, zf_state *const *states, int32_t batch, uint32_t *d_mask, hipStream_t stream, bool wait, uint32_t slot) {
     DeviceSide *d = e->dev;

@@ -158,7 +158,8 @@ __device__ __forceinline__ int aut_step_narrow(const TV &T, const SetsT &S, uint
 // narrow variant, and the lanes make candidates in parallel as in the wide one -- in Complete the items of the completed items' origin sets
 // are dealt to the lanes, then the entries of the table that they hit.  Only distinct candidates are entered in turn, each through compares
 // whose results are scalars.  No hash table to clear, no set in LDS to probe: sources of 9 to 16 items, 64 rows of the expression grammar
-// without pruning, 8 steps of a decode loop: 1,215 us through the wide variant, 1,056 through this.
+// without pruning, 8 steps of a decode loop: 1,215 us through the wide variant, 1,056 through this (when token-mask cache rows left a million strings a step to the
+// parser; with the cache off and this step taken for sets of up to 8 items as well, 673 us, with the narrow one for those 692).
 //   What bounds it is the length of the wavefront: a step of 11 new items took 9,900 cycles, 2,700 of them to enter 13 candidates and 2,600 to deal
 // 8 sets and lists; 7,000 with loops that have no branch but their own and hold no more than they must (the same 8 steps 788 -> 721 us).  For sets of a few items with a candidate or two the
 // dealing costs more than it saves (per-block automaton, 16 rows of a JSON schema: 61 us per step with the narrow variant, 65 with this; trie walk 103

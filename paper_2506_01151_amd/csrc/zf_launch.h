@@ -16,7 +16,8 @@ static const int BASE_SETS_LDS = 31;       // a row's chart is staged into LDS w
 static const int BASE_ITEMS_LDS = 64;      // ... and items (the mask-automaton kernel takes larger limits from the host when LDS allows)
 // The builds of mask_automaton_kernel, by the byte step they hold.  Charts whose sets are all of up to AUT_NARROW_SET_MAX items run the narrow one, of up to
 // AUT_LANES_SET_MAX the one for a dozen items (a set that outgrows 64 items there goes to the fallback pass, and the engine's next calls to the build behind it; chart addresses known to be LDS and no hash table:
-// 64 rows of the expression grammar without pruning, 8 steps of a decode loop, 988 us against 1,056 in the build that follows), others the one that
+// 64 rows of the expression grammar without pruning, 8 steps of a decode loop, 988 us against 1,056 in the build that follows, while token-mask cache rows left
+// its strings to this kernel: today they leave none, and with the cache off the same 8 steps take 673), others the one that
 // holds the wide step as well, to which source sets of more than AUT_STEP_WIDE_FROM items go at once (the line at 16 measured the same).
 static const int AUT_STEP_NARROW = 0, AUT_STEP_LANES = 1, AUT_STEP_WIDE = 2;
 static const int AUT_NARROW_SET_MAX = 8, AUT_LANES_SET_MAX = 16, AUT_STEP_WIDE_FROM = 32;

@@ -75,7 +75,7 @@ __device__ __forceinline__ uint32_t aut_transition(const TV &T, const BaseT &B, 
     S.view(cur, src_p, src_n);
     int st = AUT_WIDE;
     // A terminal that goes on in place -- a digit behind a digit -- leaves what it left before: the source set's own first items (64 rows of the expression
-    // grammar, 4.2 to 6.1 us such a step, 0.9 so).
+    // grammar, 4.2 to 6.1 us such a step, 0.9 so; a call of 64 x 152,064 with every string left to the kernel 89.2 -> 84.2).
     uint32_t scanned = 0;
     const uint32_t src_scanned = STEP == AUT_STEP_NARROW ? 0u : lds_load(&A.scanned[s]);
     auto seen = [&](uint32_t w, uint32_t o, uint32_t n) -> bool {
@@ -333,7 +333,8 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
         if (tid == 0) { A.ctl[2] = 0; A.ctl[3] = 0; A.ctl[6] = 0; }
         __syncthreads();                                     // also: tables, chart and automaton set-up are in place
         if (j0 && tid == 0) { A.ctl[4] = 0; A.ctl[5] = 0; }  // the help queue starts over (its places were cleared behind the pass before)
-        // a pass without an undecided string is over (64 rows x 152,064 of the expression grammar: with that, and the cache rows asked for early, launches of 13.0 us take 11.2)
+        // a pass without an undecided string is over (a decode loop through walk_mode 0, us a step: 64 rows x 152,064 of the expression grammar 40.8 -> 39.3, 64 x 128,256 of the query
+        // language 32.9 -> 31.0; with the cache rows asked for behind the chart 40.5 and 31.7)
         if (__ballot(A.some[lane % WAVES] != 0) == 0) {
             if (w < Wr) a.rank_mask[(size_t)row * Wr + w] = v;
             __syncthreads();                                 // before the next pass's words
@@ -383,9 +384,9 @@ __global__ __launch_bounds__(WAVES * 64) void mask_automaton_kernel(MaskArgs a) 
                 uint32_t rs = 0, rc = 0;
                 if (batch) {
                     // Every lane follows its own string as far as the table goes; the classes at hand are a shift register.  The wavefront goes
-                    // together: lanes that have come to their end, or miss a transition, move by nothing (64 rows x 152,064 of the expression grammar without pruning, 8 steps,
-                    // 720 -> 646 us: lanes that leave the loop one by one cost as many instructions again, in execution masks).  (Asking for the strings
-                    // of the batch that follows beforehand means to claim it beforehand: 687 us.)
+                    // together: lanes that have come to their end, or miss a transition, move by nothing (64 rows x 152,064 of the expression grammar without pruning, 8 steps
+                    // with a million undecided strings each, 720 -> 646 us: lanes that leave the loop one by one cost as many instructions again, in execution masks).  (Asking
+                    // for the strings of the batch that follows beforehand means to claim it beforehand: 687 us.)
                     bool go = live;
                     for (;;) {
                         do {

@@ -41,9 +41,10 @@ static const int LOOK_LC_BITS = 10;                      // the block's LDS cach
 static const uint32_t LOOK_LC = 1u << LOOK_LC_BITS;
 // A group's wavefronts store its mask words to every member's row, one member or a few at a time: a batch that stands in one state, 256 rows x 128,256,
 // kept 63 wavefronts at it for 18 us.  With logits, those of groups of more members than these (in the argument block) leave it to the wavefronts that mask the
-// logits, each for its unit: 16 members of bf16 logits (16 steps of 64 x 128,256 of the query language 178.4 -> 178.0 us, 8 of 130 x 40,037 109.1 -> 106.1, 8 of
-// 256 x 128,256 226.2 -> 224.8; 32 members: 180.3, 108.9, 223.7), 128 of fp32, whose units hold half as many words (16 steps of 64 x 152,064 of the expression grammar 312.8 us
-// without, 317.0 from 16 members on, 315.2 from 32).
+// logits, each for its unit.  It takes large groups to tell: of fp32 logits, 1,000 rows x 32,000 in a few states 82 -> 50 us a step (query language), 62 -> 52 (schema), 63 -> 57
+// (expression grammar), 256 rows 26 -> 21.  Units of fp32 hold half as many words as those of bf16, and groups of a few dozen lose by it (16 steps of 64 x 152,064 312.8 us
+// without, 315.2 from 32 members on, 317.0 from 16), hence 128.  Of bf16 logits the line matters little, since groups that the cache rows decide store their own rows
+// (STORE_ROW_DECIDED): before they did, 8 steps of 130 x 40,037 109.1 -> 106.1 us from 16 members on, 108.9 from 32.
 template <int DT> constexpr uint32_t look_members_max() { return DT == 2 ? 16u : 128u; }
 static const uint32_t LOOK_STOP = 256;                   // beyond every class and mark: the walk of a lane has ended
 // Where the groups' records are: one in the argument block, up to 64 there, or any number in device memory.  A build each, so that the records are asked

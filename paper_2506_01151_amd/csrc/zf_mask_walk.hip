@@ -491,7 +491,8 @@ __device__ __forceinline__ void fallback_share(const MaskArgs &a, uint32_t share
 // PERMUTE_ROWS rows: four ranks, the four rows' words of each, four bits a row; eight lanes put a mask word together.
 //   Logits (zf_compute_mask_apply_async): the lane that has a token's bits masks its logits along.  They are requested with the ranks, before
 // anything is known of the mask, so that the reading of a pass hides the look-ups of the one before: 64 rows x 152,064 fp32 17.4 us, where the permutation (a token per lane
-// and four look-ups, a store for every 64 tokens and row) took 10.8 and the launch behind it 13.5; 8 steps of the expression grammar without pruning 644 -> 606 us.
+// and four look-ups, a store for every 64 tokens and row) took 10.8 and the launch behind it 13.5; 8 steps of the expression grammar without pruning, whose strings the
+// per-block automaton then walked, 644 -> 606 us.
 //   Hand-over: see hand_over (zf_kernel_common.h).  With nothing listed the status is final when this kernel starts, and is handed over first.
 static const int PERMUTE_ROWS = 4;
 static const uint32_t PERMUTE_TOKENS = 4;             // neighbouring tokens of a lane
@@ -546,8 +547,8 @@ __global__ __launch_bounds__(finish_block(STAGED)) void finish_kernel(MaskArgs a
     };
     auto rows_of = [&](uint32_t rg) -> uint32_t { const uint32_t left = (uint32_t)a.batch - rg * PERMUTE_ROWS; return left < (uint32_t)PERMUTE_ROWS ? left : (uint32_t)PERMUTE_ROWS; };
     // Requested before it is known whether the fallback pass has work, which seldom is: the first group's words of the bitmap (they are asked for again behind
-    // that pass), ahead of the logits, since loads come back in order (64 rows x 152,064 fp32 19.2 -> 17.4 us), then the ranks and logits of the first pass (of two
-    // passes 18.2, of three 18.8: the words wait behind other blocks' logits).
+    // that pass), ahead of the logits, since loads come back in order (64 rows x 152,064 fp32, the kernel by itself 19.2 -> 17.4 us; a step of a decode loop through walk_mode 0 is 39.3
+    // either way), then the ranks and logits of the first pass (of two passes 18.2, of three 18.8: the words wait behind other blocks' logits).
     constexpr uint32_t ROW_WORDS = STAGED ? FINISH_ROW_WORDS : 1;
     uint32_t row_words[ROW_WORDS][PERMUTE_ROWS];
     if (STAGED) {
