@@ -38,8 +38,8 @@ KERNEL_OF_MODE = {0: "mask_automaton_kernel", 1: "mask_walk_kernel", 2: "mask_lo
 # HBM traffic of one launch of mask_look_kernel (every launch of the default workload is one; masks and logits) and of apply_mask_vec_kernel, from rocprofv3
 # FETCH_SIZE / WRITE_SIZE runs scaled by a plain copy of known size (profiles/mask_look_kernel_cfg3_hbm_traffic.txt), and SQ_INSTS of the same
 # pass.  The figures describe the kernel sources with the digest below; once they change they are reported as null until measured again.
-MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 11494079, "apply_bytes_per_launch": 8493574, "instructions_per_launch": 2187746,
-                    "kernel_sources_sha256": "032f9f2f7db6126cdbc67034baccbfb9f9c1142801e8a86fda4b5ad1e0f925f5"}
+MEASURED_TRAFFIC = {"config": 3, "bytes_per_launch": 11492183, "apply_bytes_per_launch": 8493664, "instructions_per_launch": 2183682,
+                    "kernel_sources_sha256": "61d3ef8574356516efc2403f75cde538786dba1114402c7fcdeb70a3fe5e8ae1"}
 
 
 def kernel_sources_digest():
